@@ -3,146 +3,16 @@
 //
 // All of them stream N and F once.  The streaming kernels view F as 16-byte vectors; they need
 // kept * sizeof(index) to be a multiple of 16 bytes (every vector lies inside one block) and 16-byte
-// aligned pointers.  Everything else takes the slower per-element kernels at the end of this file.
-#include "pbz_device.h"
-#include "pbz_internal.h"
+// aligned pointers.  Everything else goes through LDS (pbz_ops_staged.hip).
+#include "pbz_ops_common.h"
 
 namespace pbz {
+
+using namespace ops;
+
 namespace {
 
-constexpr int kThreads = 256;
 constexpr int kUnroll = 4;
-constexpr int kReduceGroupsOneSegment = 1024;
-
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
-int ilog2_exact(int64_t v) {  // log2(v) when v is a power of two, else -1
-  if (v < 1 || (v & (v - 1))) return -1;
-  int s = 0;
-  while ((int64_t(1) << s) < v) ++s;
-  return s;
-}
-
-int stream_groups(int64_t items, int per_thread) {
-  int64_t g = (items + int64_t(kThreads) * per_thread - 1) / (int64_t(kThreads) * per_thread);
-  if (g < 1) g = 1;
-  if (g > kReduceMaxGroups) g = kReduceMaxGroups;
-  return int(g);
-}
-
-// ---------------------------------------------------------------------------------------------
-// packed integer helpers on one dword
-// ---------------------------------------------------------------------------------------------
-template <int kIType>
-__device__ __forceinline__ uint32_t negate_packed(uint32_t x) {
-  if (kIType == PBZ_I8) {
-    uint32_t y = ~x;
-    return ((y & 0x7f7f7f7fu) + 0x01010101u) ^ (y & 0x80808080u);
-  } else if (kIType == PBZ_I16) {
-    uint32_t y = ~x;
-    return ((y & 0x7fff7fffu) + 0x00010001u) ^ (y & 0x80008000u);
-  } else {
-    return uint32_t(-int32_t(x));
-  }
-}
-
-typedef short short2v __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ short2v as_short2(uint32_t u) {
-  short2v s;
-  s.x = short(u & 0xffffu);
-  s.y = short(u >> 16);
-  return s;
-}
-
-// sum over the elements of one dword of a*b, as a double (exact)
-template <int kIType>
-__device__ __forceinline__ double dot_dword(uint32_t a, uint32_t b) {
-  if (kIType == PBZ_I8) {
-    return double(__builtin_amdgcn_sdot4(int(a), int(b), 0, false));
-  } else if (kIType == PBZ_I16) {
-    return double(__builtin_amdgcn_sdot2(as_short2(a), as_short2(b), 0, false));
-  } else {
-    return double(int32_t(a)) * double(int32_t(b));
-  }
-}
-
-// exact integer dot product of two 16-byte vectors for 8- and 16-bit indices
-template <int kIType>
-__device__ __forceinline__ double dot_vec(const uint4& a, const uint4& b) {
-  if (kIType == PBZ_I8) {
-    int acc = __builtin_amdgcn_sdot4(int(a.x), int(b.x), 0, false);
-    acc = __builtin_amdgcn_sdot4(int(a.y), int(b.y), acc, false);
-    acc = __builtin_amdgcn_sdot4(int(a.z), int(b.z), acc, false);
-    acc = __builtin_amdgcn_sdot4(int(a.w), int(b.w), acc, false);
-    return double(acc);
-  } else if (kIType == PBZ_I16) {
-    // one dword: at most 2 * 32767^2 < 2^31; four of them need 64 bits
-    long long acc = (long long)__builtin_amdgcn_sdot2(as_short2(a.x), as_short2(b.x), 0, false);
-    acc += (long long)__builtin_amdgcn_sdot2(as_short2(a.y), as_short2(b.y), 0, false);
-    acc += (long long)__builtin_amdgcn_sdot2(as_short2(a.z), as_short2(b.z), 0, false);
-    acc += (long long)__builtin_amdgcn_sdot2(as_short2(a.w), as_short2(b.w), 0, false);
-    return double(acc);
-  } else {
-    return dot_dword<PBZ_I32>(a.x, b.x) + dot_dword<PBZ_I32>(a.y, b.y) + dot_dword<PBZ_I32>(a.z, b.z) +
-           dot_dword<PBZ_I32>(a.w, b.w);
-  }
-}
-
-template <int kIType>
-__device__ __forceinline__ int first_element(uint32_t x) {
-  if (kIType == PBZ_I8) return int(int8_t(x & 0xffu));
-  if (kIType == PBZ_I16) return int(int16_t(x & 0xffffu));
-  return int(x);
-}
-
-template <int kIType>
-__device__ __forceinline__ void unpack_dword(uint32_t x, double* out) {  // 4 / 2 / 1 elements
-  if (kIType == PBZ_I8) {
-    out[0] = double(int(int8_t(x & 0xffu)));
-    out[1] = double(int(int8_t((x >> 8) & 0xffu)));
-    out[2] = double(int(int8_t((x >> 16) & 0xffu)));
-    out[3] = double(int(int8_t(x >> 24)));
-  } else if (kIType == PBZ_I16) {
-    out[0] = double(int(int16_t(x & 0xffffu)));
-    out[1] = double(int(int16_t(x >> 16)));
-  } else {
-    out[0] = double(int32_t(x));
-  }
-}
-
-// the low bytes (int8) or halves (int16) of 4 / 2 integers gathered into one dword by byte permutes
-template <int kIType>
-__device__ __forceinline__ uint32_t pack_dword(const int* v) {
-  if (kIType == PBZ_I8) {
-    const uint32_t lo = __builtin_amdgcn_perm(uint32_t(v[1]), uint32_t(v[0]), 0x0c0c0400u);   // v0.b0, v1.b0
-    const uint32_t hi = __builtin_amdgcn_perm(uint32_t(v[3]), uint32_t(v[2]), 0x0c0c0400u);   // v2.b0, v3.b0
-    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-  }
-  if (kIType == PBZ_I16) return __builtin_amdgcn_perm(uint32_t(v[1]), uint32_t(v[0]), 0x05040100u);
-  return uint32_t(v[0]);
-}
-
-// rint(t) as an integer for |t| < 2^31: adding 1.5 * 2^52 rounds t to an integer in the current (nearest-even)
-// mode and leaves that integer, in two's complement, in the low word of the sum
-__device__ __forceinline__ int rint_to_int(double t) {
-  return int(uint32_t(__builtin_bit_cast(uint64_t, t + 6755399441055744.0)));
-}
-
-// F1 N1 + F2 N2 with both products and the sum rounded separately (Algorithm 2 as printed): a fused
-// multiply-add would skip one rounding and break A + (-A) == 0 when N has more than 37 significant bits.
-__device__ __forceinline__ double unfused_sum_of_products(double f1, double n1, double f2, double n2) {
-#pragma clang fp contract(off)
-  const double p1 = f1 * n1;
-  const double p2 = f2 * n2;
-  return p1 + p2;
-}
-
-template <int kIType>
-struct PerDword {
-  static constexpr int value = kIType == PBZ_I8 ? 4 : kIType == PBZ_I16 ? 2 : 1;
-};
-
 // ---------------------------------------------------------------------------------------------
 // Algorithm 1 (and the F part of Algorithm 5): F_out = sign * F_in over 16-byte vectors
 // ---------------------------------------------------------------------------------------------
@@ -162,9 +32,13 @@ __device__ __forceinline__ uint4 apply_sign(uint4 a) {
 // (kThreads vectors apart), then the stores.  The element-wise kernels of this file may be called in place (an
 // output aliasing the operand it replaces), so none of their pointers is declared __restrict__; every lane reads
 // all it needs of an element before it writes that element.
+// The `n_tail` indices after the last whole vector (a block count and a kept count that make no multiple of 16 bytes)
+// are group 0's.
 template <int kIType, int kSign>
-__device__ __forceinline__ void scale_sign_run(const uint4* in, uint4* out, int64_t nvec,
+__device__ __forceinline__ void scale_sign_run(const uint4* in, uint4* out, int64_t nvec, int n_tail,
                                                int64_t group) {
+  if (group == 0 && int(threadIdx.x) < n_tail)
+    store_index(out + nvec, kIType, threadIdx.x, kSign == 0 ? 0 : kSign * load_index(in + nvec, kIType, threadIdx.x));
   const int64_t base = group * (kThreads * kUnroll) + threadIdx.x;
   if (base + (kUnroll - 1) * kThreads < nvec) {
     uint4 a[kUnroll];
@@ -182,19 +56,19 @@ __device__ __forceinline__ void scale_sign_run(const uint4* in, uint4* out, int6
 
 template <int kIType, int kSign>
 __global__ __launch_bounds__(kThreads) void k_scale_sign_vec(const uint4* in, uint4* out,
-                                                             int64_t nvec) {
-  scale_sign_run<kIType, kSign>(in, out, nvec, blockIdx.x);
+                                                             int64_t nvec, int n_tail) {
+  scale_sign_run<kIType, kSign>(in, out, nvec, n_tail, blockIdx.x);
 }
 
 // Algorithm 5 in one launch: the first f_groups workgroups write F_out = sign(x) F_in, the others N_out = |x| N_in
 template <int kIType, int kSign>
 __global__ __launch_bounds__(kThreads) void k_mul_scalar_vec(const uint4* Fin, uint4* Fout,
-                                                             int64_t nvec, unsigned f_groups,
+                                                             int64_t nvec, int n_tail, unsigned f_groups,
                                                              const void* Nin, void* Nout, int ntype, double ax,
                                                              int64_t n_blocks) {   // Nin may be Nout
 
   if (blockIdx.x < f_groups) {
-    scale_sign_run<kIType, kSign>(Fin, Fout, nvec, blockIdx.x);
+    scale_sign_run<kIType, kSign>(Fin, Fout, nvec, n_tail, blockIdx.x);
     return;
   }
   const int64_t nthreads = int64_t(gridDim.x - f_groups) * kThreads;
@@ -209,31 +83,39 @@ __global__ __launch_bounds__(kThreads) void k_scale_sign_scalar(const void* in, 
     store_index(out, itype, e, sign == 0 ? 0 : sign * load_index(in, itype, e));
 }
 
-template <int kSign>
-void launch_sign_vec(int itype, const void* in, void* out, int64_t nvec, hipStream_t s) {
+// workgroups for nvec vectors, at least one (which takes the tail)
+unsigned sign_groups(int64_t nvec) {
   const int64_t per_group = int64_t(kThreads) * kUnroll;
-  dim3 grid(static_cast<unsigned>((nvec + per_group - 1) / per_group)), block(kThreads);
+  const int64_t g = (nvec + per_group - 1) / per_group;
+  return g < 1 ? 1u : unsigned(g);
+}
+
+template <int kSign>
+void launch_sign_vec(int itype, const void* in, void* out, int64_t bytes, hipStream_t s) {
+  const int64_t nvec = bytes / 16;
+  const int n_tail = int(bytes % 16) / itype_bytes(itype);
+  dim3 grid(sign_groups(nvec)), block(kThreads);
   const uint4* i4 = static_cast<const uint4*>(in);
   uint4* o4 = static_cast<uint4*>(out);
   if (itype == PBZ_I8)
-    hipLaunchKernelGGL((k_scale_sign_vec<PBZ_I8, kSign>), grid, block, 0, s, i4, o4, nvec);
+    hipLaunchKernelGGL((k_scale_sign_vec<PBZ_I8, kSign>), grid, block, 0, s, i4, o4, nvec, n_tail);
   else if (itype == PBZ_I16)
-    hipLaunchKernelGGL((k_scale_sign_vec<PBZ_I16, kSign>), grid, block, 0, s, i4, o4, nvec);
+    hipLaunchKernelGGL((k_scale_sign_vec<PBZ_I16, kSign>), grid, block, 0, s, i4, o4, nvec, n_tail);
   else
-    hipLaunchKernelGGL((k_scale_sign_vec<PBZ_I32, kSign>), grid, block, 0, s, i4, o4, nvec);
+    hipLaunchKernelGGL((k_scale_sign_vec<PBZ_I32, kSign>), grid, block, 0, s, i4, o4, nvec, n_tail);
 }
 
 int scale_sign(const pbz_codec* c, int64_t n_blocks, const void* in, void* out, int sign, hipStream_t s) {
   if (sign > 0 && in == out) return PBZ_OK;
   const int64_t n = n_blocks * c->kept;
   const int64_t bytes = n * itype_bytes(c->itype);
-  if (bytes % 16 == 0 && aligned16(in) && aligned16(out)) {
+  if (aligned16(in) && aligned16(out)) {
     if (sign > 0)
-      launch_sign_vec<1>(c->itype, in, out, bytes / 16, s);
+      launch_sign_vec<1>(c->itype, in, out, bytes, s);
     else if (sign < 0)
-      launch_sign_vec<-1>(c->itype, in, out, bytes / 16, s);
+      launch_sign_vec<-1>(c->itype, in, out, bytes, s);
     else
-      launch_sign_vec<0>(c->itype, in, out, bytes / 16, s);
+      launch_sign_vec<0>(c->itype, in, out, bytes, s);
   } else {
     hipLaunchKernelGGL(k_scale_sign_scalar, dim3(stream_groups(n, 4)), dim3(kThreads), 0, s, in, out, int(c->itype),
                        sign, n);
@@ -254,44 +136,6 @@ __global__ __launch_bounds__(kThreads) void k_scale_N(const void* in, void* out,
 // C = F1 N1 + F2 N2 (each product and the sum rounded separately), N = max|C| / r, F = rint(C / N).
 // A block occupies kLanes consecutive lanes, 16 bytes of F per lane.
 // ---------------------------------------------------------------------------------------------
-// N comes in three widths: kNType = PBZ_F64, PBZ_F32, or kN16 for the two 16-bit types, which share a kernel:
-// the 16-bit load is the same, both decodings are computed and `f16` (uniform) selects one, so that no branch
-// surrounds a load.
-constexpr int kN16 = PBZ_BF16;
-constexpr int n_kernel_type(int ftype) { return ftype == PBZ_F64 ? PBZ_F64 : (ftype == PBZ_F32 ? PBZ_F32 : kN16); }
-
-template <int kNType>
-__device__ __forceinline__ double load_N(const void* N, int64_t k, bool f16 = false) {
-  if (kNType == PBZ_F64) return static_cast<const double*>(N)[k];
-  if (kNType == PBZ_F32) return double(static_cast<const float*>(N)[k]);
-  const uint16_t h = static_cast<const uint16_t*>(N)[k];
-  const float as_bf16 = bf16_bits_to_float(h);
-  const float as_f16 = float(__builtin_bit_cast(_Float16, h));
-  return double(f16 ? as_f16 : as_bf16);
-}
-
-template <int kNType>
-__device__ __forceinline__ void store_N(void* N, int64_t k, double v, bool f16 = false) {
-  if (kNType == PBZ_F64) {
-    static_cast<double*>(N)[k] = v;
-  } else if (kNType == PBZ_F32) {
-    static_cast<float*>(N)[k] = float(v);
-  } else {
-    const uint16_t as_bf16 = double_to_bf16_bits(v);
-    const uint16_t as_f16 = __builtin_bit_cast(uint16_t, double_to_f16(v));
-    static_cast<uint16_t*>(N)[k] = f16 ? as_f16 : as_bf16;
-  }
-}
-
-// a / b rounded to nearest from a correctly rounded reciprocal: one multiply, the exact remainder by fused
-// multiply-add, one correction.  Agrees with the hardware division sequence except in rare double-rounding
-// corner cases, at a sixth of its cost.
-__device__ __forceinline__ double div_by(double a, double b, double inv_b) {
-  const double q = a * inv_b;
-  const double rem = fma(-q, b, a);
-  return fma(rem, inv_b, q);
-}
-
 template <int kIType, int kNType>
 __global__ __launch_bounds__(kThreads) void k_add_vec(const void* N1, const uint4* F1,
                                                       const void* N2, const uint4* F2,
@@ -350,33 +194,6 @@ __global__ __launch_bounds__(kThreads) void k_add_vec(const void* N1, const uint
       Fout[v] = make_uint4(ow[0], ow[1], ow[2], ow[3]);
       if ((v & (lanes - 1)) == 0) store_N<kNType>(Nout, k, n, n_f16 != 0);
     }
-  }
-}
-
-// one wave per block, any kept count, any alignment
-__global__ __launch_bounds__(64) void k_add_generic(const void* N1, const void* F1,
-                                                    const void* N2, const void* F2,
-                                                    void* Nout, void* Fout, int ntype,
-                                                    int itype, double r, double sign2, int64_t n_blocks, int kept) {
-  for (int64_t k = blockIdx.x; k < n_blocks; k += gridDim.x) {
-    const double n1 = load_float<double>(N1, ntype, k), n2 = sign2 * load_float<double>(N2, ntype, k);
-    double m = 0.0;
-    for (int j = threadIdx.x; j < kept; j += 64) {
-      double ce = unfused_sum_of_products(double(load_index(F1, itype, k * kept + j)), n1,
-                                          double(load_index(F2, itype, k * kept + j)), n2);
-      m = fmax(m, fabs(ce));
-    }
-    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
-    const double n = m / r;
-    // F_out may alias an operand: every lane re-reads only the entries it then overwrites
-    for (int j = threadIdx.x; j < kept; j += 64) {
-      double ce = unfused_sum_of_products(double(load_index(F1, itype, k * kept + j)), n1,
-                                          double(load_index(F2, itype, k * kept + j)), n2);
-      double t = n > 0.0 ? ce / n : 0.0;
-      t = fmin(fmax(rint(t), -r), r);
-      store_index(Fout, itype, k * kept + j, int64_t(t));
-    }
-    if (threadIdx.x == 0) store_float(Nout, ntype, k, n);
   }
 }
 
@@ -443,34 +260,11 @@ __global__ __launch_bounds__(kThreads) void k_add_scalar_vec(const void* N1, con
   }
 }
 
-__global__ __launch_bounds__(64) void k_add_scalar_generic(const void* N1, const void* F1,
-                                                           void* Nout, void* Fout, int ntype,
-                                                           int itype, double r, double shift, int64_t n_blocks,
-                                                           int kept) {
-  for (int64_t k = blockIdx.x; k < n_blocks; k += gridDim.x) {
-    const double n1 = load_float<double>(N1, ntype, k);
-    double m = 0.0;
-    for (int j = threadIdx.x; j < kept; j += 64) {
-      double ce = (n1 * double(load_index(F1, itype, k * kept + j))) / r + (j == 0 ? shift : 0.0);
-      m = fmax(m, fabs(ce));
-    }
-    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
-    for (int j = threadIdx.x; j < kept; j += 64) {
-      double ce = (n1 * double(load_index(F1, itype, k * kept + j))) / r + (j == 0 ? shift : 0.0);
-      double t = m > 0.0 ? (ce * r) / m : 0.0;
-      store_index(Fout, itype, k * kept + j, int64_t(fmin(fmax(rint(t), -r), r)));
-    }
-    if (threadIdx.x == 0) store_float(Nout, ntype, k, m);
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // Block-wise statistics (Sec. IV-A): one FP64 value per block.
 //   mean_k = C_k0 / prod(sqrt(i));   covariance_k = (sum_j C1_kj C2_kj - C1_k0 C2_k0) / prod(i)
 // (centring a block by its own mean zeroes its first coefficient); variance = covariance(A, A); std = sqrt.
 // ---------------------------------------------------------------------------------------------
-enum BlockwiseMode { kBwVariance = 0, kBwStd = 1, kBwCovariance = 2 };
-
 __global__ __launch_bounds__(kThreads) void k_blockwise_mean(const void* __restrict__ N1, const void* __restrict__ F1,
                                                              int ntype, int itype, double scale, int64_t n_blocks,
                                                              int kept, double* __restrict__ out) {
@@ -512,23 +306,6 @@ __global__ __launch_bounds__(kThreads) void k_blockwise_vec(const void* __restri
   }
 }
 
-__global__ __launch_bounds__(64) void k_blockwise_generic(const void* __restrict__ N1, const void* __restrict__ F1,
-                                                          const void* __restrict__ N2, const void* __restrict__ F2,
-                                                          int ntype, int itype, double* __restrict__ out, double scale,
-                                                          int mode, int64_t n_blocks, int kept) {
-  for (int64_t k = blockIdx.x; k < n_blocks; k += gridDim.x) {
-    double sum = 0.0;
-    for (int j = 1 + threadIdx.x; j < kept; j += 64)
-      sum += double(load_index(F1, itype, k * kept + j)) * double(load_index(F2, itype, k * kept + j));
-    sum = wave_sum(sum);
-    if (threadIdx.x == 0) {
-      double res = sum * (load_float<double>(N1, ntype, k) * load_float<double>(N2, ntype, k)) * scale;
-      if (mode == kBwStd) res = sqrt(res);
-      out[k] = res;
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // Reductions (Algorithms 6-11).  One streaming pass produces five FP64 sums per workgroup,
 //   S12 = sum_k N1_k N2_k sum_j F1_kj F2_kj     S11, S22 likewise     D1 = sum_k N1_k F1_k0   D2 likewise
@@ -538,143 +315,6 @@ __global__ __launch_bounds__(64) void k_blockwise_generic(const void* __restrict
 // (A single launch in which the last workgroup to finish does the final sum was measured slower: the
 // per-workgroup ticket increments serialise on one address across the chip.)
 // ---------------------------------------------------------------------------------------------
-enum { kS12 = 0, kS11 = 1, kS22 = 2, kD1 = 3, kD2 = 4, kNumSums = 5 };
-
-struct ReduceTail {
-  double* partials;
-  double* out;
-  int op;
-  double r, n_blocks, vol;
-  double s_l, s_c, w_l, w_c, w_s;   // Algorithm 12's stabilisers and weights
-  int n_f16;                        // N is FP16 (as opposed to bfloat16) when it is 16 bits wide
-  // Shifted first coefficients.  Variance and covariance centre the first coefficients N_k F_k0 by their mean
-  // (Algorithms 8, 9); summing them and their squares raw and subtracting afterwards would cancel against the
-  // square of the mean.  The passes that need them therefore sum d_k = N_k F_k0 - K, with K the first
-  // coefficient of the segment's first block (a pilot value: exact centring needs the mean, which is not known
-  // yet, but any K near it removes the cancellation), and put d_k^2, d1_k d2_k into S11, S22, S12 in place of
-  // the raw squares and product.  pilot_n1 == nullptr: nothing is shifted (K = 0).
-  const void* pilot_n1;
-  const void* pilot_f1;
-  const void* pilot_n2;
-  const void* pilot_f2;
-  int64_t seg_n_bytes, seg_f_bytes;  // distance between the segments' first N and F
-  int ntype, itype;
-};
-
-// K of operand (N, F) in segment `segment`: the same expression wherever it is evaluated
-__device__ __forceinline__ double pilot_value(const void* N, const void* F, const ReduceTail& t, int64_t segment) {
-  if (!N) return 0.0;
-  const char* n = static_cast<const char*>(N) + segment * t.seg_n_bytes;
-  const char* f = static_cast<const char*>(F) + segment * t.seg_f_bytes;
-  return load_float<double>(n, t.ntype, 0) * double(load_index(f, t.itype, 0));
-}
-
-// s: the five sums, with the first coefficients shifted by K1 / K2 where the pass shifts them (else K = 0)
-__device__ __forceinline__ double finish_statistic(const double* s, const ReduceTail& t, double K1, double K2) {
-  const double n = t.n_blocks;
-  // the raw sums back from the shifted ones: sum (d + K) = D + n K, sum (d1 + K1)(d2 + K2) = S12 + K2 D1 + K1 D2 + n K1 K2
-  const double D1 = s[kD1] + n * K1, D2 = s[kD2] + n * K2;
-  const double S11 = s[kS11] + 2.0 * K1 * s[kD1] + n * K1 * K1;
-  const double S22 = s[kS22] + 2.0 * K2 * s[kD2] + n * K2 * K2;
-  const double S12 = s[kS12] + K2 * s[kD1] + K1 * s[kD2] + n * K1 * K2;
-  switch (t.op) {
-    case kDot: return S12 / (t.r * t.r);
-    case kNorm2: return sqrt(S11) / t.r;
-    case kDiffNorm2: return sqrt(s[kS11]) / t.r;    // S11 then holds sum (N1 F1 - N2 F2)^2
-    case kCosine: return S12 / (sqrt(S11) * sqrt(S22));
-    case kMean: return (D1 / t.r) / (n * sqrt(t.vol));
-    // centring the first coefficients by their mean removes (sum d1)(sum d2) / n_blocks from the sum of products,
-    // whatever constant they were shifted by
-    case kCovariance: return ((s[kS12] - s[kD1] * s[kD2] / n) / (t.r * t.r)) / (n * t.vol);
-    case kVariance: return ((s[kS11] - s[kD1] * s[kD1] / n) / (t.r * t.r)) / (n * t.vol);
-    case kSsim: {   // Algorithm 12 from the means, variances and covariance of Algorithms 7-9
-      const double scale = 1.0 / (t.r * n * sqrt(t.vol));
-      const double mu_a = D1 * scale, mu_b = D2 * scale;
-      const double per = 1.0 / (t.r * t.r * n * t.vol);
-      // a difference inside the rounding of its two terms is the variance of a constant array: zero (its root
-      // would turn 1e-16 into 1e-8)
-      const double noise = 8.0 * 2.220446049250313e-16;
-      double ca = s[kS11] - s[kD1] * s[kD1] / n, cb = s[kS22] - s[kD2] * s[kD2] / n;
-      if (ca <= noise * s[kS11]) ca = 0.0;
-      if (cb <= noise * s[kS22]) cb = 0.0;
-      const double var_a = ca * per, var_b = cb * per;
-      const double cov = (s[kS12] - s[kD1] * s[kD2] / n) * per;
-      const double sd = sqrt(var_a) * sqrt(var_b);
-      const double lum = (2.0 * mu_a * mu_b + t.s_l) / (mu_a * mu_a + mu_b * mu_b + t.s_l);
-      const double con = (2.0 * sd + t.s_c) / (var_a + var_b + t.s_c);
-      const double str = (cov + 0.5 * t.s_c) / (sd + 0.5 * t.s_c);
-      return pow(lum, t.w_l) * pow(con, t.w_c) * pow(str, t.w_s);
-    }
-    default: return 0.0;
-  }
-}
-
-// sum of `sums` over the workgroup, valid in threads 0 .. kNumSums-1 (thread i returns total i)
-template <int kWaves = kThreads / 64>
-__device__ __forceinline__ double group_total(const double* sums, double (*lds)[kNumSums]) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-#pragma unroll
-  for (int i = 0; i < kNumSums; ++i) {
-    double t = wave_sum(sums[i]);
-    if (lane == 0) lds[wave][i] = t;
-  }
-  __syncthreads();
-  double t = 0.0;
-  if (threadIdx.x < kNumSums)
-    for (int w = 0; w < kWaves; ++w) t += lds[w][threadIdx.x];
-  return t;
-}
-
-// the requested statistic(s) of segment `segment` from its five sums
-__device__ __forceinline__ void write_statistic(const double* fin, const ReduceTail& t, int64_t segment, double K1,
-                                                double K2) {
-  if (t.op == kStatistics) {            // mean, variance and norm2 of one array from the same two sums
-    ReduceTail one = t;
-    const int ops[3] = {kMean, kVariance, kNorm2};
-    for (int i = 0; i < 3; ++i) {
-      one.op = ops[i];
-      t.out[segment * 3 + i] = finish_statistic(fin, one, K1, K2);
-    }
-  } else if (t.op == kPairStatistics) { // every statistic of a pair of arrays from the five sums of one pass
-    ReduceTail one = t;
-    const double swapped[kNumSums] = {fin[kS12], fin[kS22], fin[kS11], fin[kD2], fin[kD1]};   // the operands exchanged
-    const int both[3] = {kDot, kCosine, kCovariance}, each[3] = {kMean, kVariance, kNorm2};
-    for (int i = 0; i < 3; ++i) {
-      one.op = both[i];
-      t.out[segment * 9 + i] = finish_statistic(fin, one, K1, K2);
-      one.op = each[i];
-      t.out[segment * 9 + 3 + 2 * i] = finish_statistic(fin, one, K1, K2);
-      t.out[segment * 9 + 4 + 2 * i] = finish_statistic(swapped, one, K2, K1);
-    }
-  } else {
-    t.out[segment] = finish_statistic(fin, t, K1, K2);
-  }
-}
-
-// grid y runs over the segments of a segmented reduction (1 otherwise).  A segment covered by a single
-// workgroup (small arrays) is finished here and needs no second launch; the sums are the same either way.
-// K1, K2: the pilot values the sums were shifted by (zero where the pass shifts nothing).  Every workgroup of a
-// segment has the same ones; they travel in the partial record (slots kPilot1, kPilot2), so that the final kernel
-// finds them in the records it reads anyway instead of fetching N and F of the segment's first block once more.
-constexpr int kPilot1 = 5, kPilot2 = 6;
-static_assert(kPilot2 < kReducePartialSlots, "record layout");
-
-__device__ __forceinline__ void reduce_tail(double* sums, const ReduceTail& t, double K1, double K2) {
-  __shared__ double lds[kThreads / 64][kNumSums];
-  __shared__ double fin[kNumSums];
-  const double total = group_total(sums, lds);
-  if (gridDim.x == 1) {
-    if (threadIdx.x < kNumSums) fin[threadIdx.x] = total;
-    __syncthreads();
-    if (threadIdx.x == 0) write_statistic(fin, t, blockIdx.y, K1, K2);
-    return;
-  }
-  double* record = t.partials + (int64_t(blockIdx.y) * gridDim.x + blockIdx.x) * kReducePartialSlots;
-  if (threadIdx.x < kNumSums) record[threadIdx.x] = total;
-  if (threadIdx.x == kPilot1) record[kPilot1] = K1;
-  if (threadIdx.x == kPilot2) record[kPilot2] = K2;
-}
-
 // one workgroup per segment: adds that segment's n_partials (<= kFinalMaxPartials) partial sums in a fixed order.
 // Every thread first issues all its loads (a partial is one 64-byte record, read as four 16-byte pieces,
 // kFinalRecords records per thread, from a clamped index: no branch around a load), then adds: the kernel's
@@ -708,7 +348,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_reduce_final(ReduceTail t, in
     acc[2] += rec[j][1].x; acc[3] += rec[j][1].y;
     acc[4] += rec[j][2].x;
   }
-  const double grand = group_total<kFinalThreads / 64>(acc, lds);
+  const double grand = group_total(acc, lds, kFinalThreads / 64);
   if (threadIdx.x < kNumSums) fin[threadIdx.x] = grand;
   __syncthreads();
   if (threadIdx.x == 0) write_statistic(fin, t, blockIdx.x, K1, K2);
@@ -884,55 +524,6 @@ __global__ __launch_bounds__(kThreads) void k_reduce_vec(const void* __restrict_
   reduce_tail(sums, tail, K1, K2);
 }
 
-// thread per block, any kept count, alignment and N type
-__global__ __launch_bounds__(kThreads) void k_reduce_generic(const void* __restrict__ N1, const void* __restrict__ F1,
-                                                             const void* __restrict__ N2, const void* __restrict__ F2,
-                                                             int ntype, int itype, int64_t n_blocks, int kept,
-                                                             int two, int dc, int diff, ReduceTail tail) {
-  double sums[kNumSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  const int64_t nthreads = int64_t(gridDim.x) * kThreads;
-  const int64_t k0 = int64_t(blockIdx.y) * n_blocks;     // first block of this segment
-  const double K1 = dc ? pilot_value(tail.pilot_n1, tail.pilot_f1, tail, blockIdx.y) : 0.0;
-  const double K2 = dc && two ? pilot_value(tail.pilot_n2, tail.pilot_f2, tail, blockIdx.y) : 0.0;
-  for (int64_t kk = int64_t(blockIdx.x) * kThreads + threadIdx.x; kk < n_blocks; kk += nthreads) {
-    const int64_t k = k0 + kk;
-    const double n1 = load_float<double>(N1, ntype, k);
-    const double n2 = two ? load_float<double>(N2, ntype, k) : 0.0;
-    if (diff) {
-      double acc = 0.0;
-      for (int j = 0; j < kept; ++j) {
-        const double d = n1 * double(load_index(F1, itype, k * kept + j)) - n2 * double(load_index(F2, itype, k * kept + j));
-        acc += d * d;
-      }
-      sums[kS11] += acc;
-      continue;
-    }
-    double s11 = 0.0, s12 = 0.0, s22 = 0.0;
-    for (int j = dc ? 1 : 0; j < kept; ++j) {       // dc: the first coefficient enters shifted, below
-      const double f1 = double(load_index(F1, itype, k * kept + j));
-      s11 += f1 * f1;
-      if (two) {
-        const double f2 = double(load_index(F2, itype, k * kept + j));
-        s12 += f1 * f2;
-        s22 += f2 * f2;
-      }
-    }
-    sums[kS11] += s11 * (n1 * n1);
-    sums[kS12] += s12 * (n1 * n2);
-    sums[kS22] += s22 * (n2 * n2);
-    if (dc) {
-      const double d1 = n1 * double(load_index(F1, itype, k * kept)) - K1;
-      const double d2 = two ? n2 * double(load_index(F2, itype, k * kept)) - K2 : 0.0;
-      sums[kS11] += d1 * d1;
-      sums[kS12] += d1 * d2;
-      sums[kS22] += d2 * d2;
-      sums[kD1] += d1;
-      sums[kD2] += d2;
-    }
-  }
-  reduce_tail(sums, tail, K1, K2);
-}
-
 // Algorithm 7 needs only N and the first kept index of every block
 __global__ __launch_bounds__(kThreads) void k_reduce_dc(const void* __restrict__ N1, const void* __restrict__ F1,
                                                         int ntype, int itype, int64_t n_blocks, int kept,
@@ -996,20 +587,21 @@ int launch_negate(const pbz_codec* c, int64_t n_blocks, const void* Fin, void* F
 
 template <int kSign>
 static void launch_mul_scalar_vec(const pbz_codec* c, int64_t n_blocks, const void* Nin, const void* Fin, double ax,
-                                  void* Nout, void* Fout, int64_t nvec, hipStream_t s) {
-  const int64_t per_group = int64_t(kThreads) * kUnroll;
-  const unsigned f_groups = static_cast<unsigned>((nvec + per_group - 1) / per_group);
+                                  void* Nout, void* Fout, int64_t bytes, hipStream_t s) {
+  const int64_t nvec = bytes / 16;
+  const int n_tail = int(bytes % 16) / itype_bytes(c->itype);
+  const unsigned f_groups = sign_groups(nvec);
   dim3 grid(f_groups + unsigned(stream_groups(n_blocks, 4))), block(kThreads);
   const uint4* i4 = static_cast<const uint4*>(Fin);
   uint4* o4 = static_cast<uint4*>(Fout);
   if (c->itype == PBZ_I8)
-    hipLaunchKernelGGL((k_mul_scalar_vec<PBZ_I8, kSign>), grid, block, 0, s, i4, o4, nvec, f_groups, Nin, Nout,
+    hipLaunchKernelGGL((k_mul_scalar_vec<PBZ_I8, kSign>), grid, block, 0, s, i4, o4, nvec, n_tail, f_groups, Nin, Nout,
                        int(c->ftype), ax, n_blocks);
   else if (c->itype == PBZ_I16)
-    hipLaunchKernelGGL((k_mul_scalar_vec<PBZ_I16, kSign>), grid, block, 0, s, i4, o4, nvec, f_groups, Nin, Nout,
+    hipLaunchKernelGGL((k_mul_scalar_vec<PBZ_I16, kSign>), grid, block, 0, s, i4, o4, nvec, n_tail, f_groups, Nin, Nout,
                        int(c->ftype), ax, n_blocks);
   else
-    hipLaunchKernelGGL((k_mul_scalar_vec<PBZ_I32, kSign>), grid, block, 0, s, i4, o4, nvec, f_groups, Nin, Nout,
+    hipLaunchKernelGGL((k_mul_scalar_vec<PBZ_I32, kSign>), grid, block, 0, s, i4, o4, nvec, n_tail, f_groups, Nin, Nout,
                        int(c->ftype), ax, n_blocks);
 }
 
@@ -1018,10 +610,10 @@ int launch_mul_scalar(const pbz_codec* c, int64_t n_blocks, const void* Nin, con
   const int sign = x > 0.0 ? 1 : (x < 0.0 ? -1 : 0);
   const int64_t f_bytes = n_blocks * c->kept * itype_bytes(c->itype);
   const bool f_untouched = sign > 0 && Fin == Fout;
-  if (!f_untouched && f_bytes % 16 == 0 && aligned16(Fin) && aligned16(Fout)) {
-    if (sign > 0) launch_mul_scalar_vec<1>(c, n_blocks, Nin, Fin, std::fabs(x), Nout, Fout, f_bytes / 16, s);
-    else if (sign < 0) launch_mul_scalar_vec<-1>(c, n_blocks, Nin, Fin, std::fabs(x), Nout, Fout, f_bytes / 16, s);
-    else launch_mul_scalar_vec<0>(c, n_blocks, Nin, Fin, std::fabs(x), Nout, Fout, f_bytes / 16, s);
+  if (!f_untouched && aligned16(Fin) && aligned16(Fout)) {
+    if (sign > 0) launch_mul_scalar_vec<1>(c, n_blocks, Nin, Fin, std::fabs(x), Nout, Fout, f_bytes, s);
+    else if (sign < 0) launch_mul_scalar_vec<-1>(c, n_blocks, Nin, Fin, std::fabs(x), Nout, Fout, f_bytes, s);
+    else launch_mul_scalar_vec<0>(c, n_blocks, Nin, Fin, std::fabs(x), Nout, Fout, f_bytes, s);
     return hip_status(hipGetLastError());
   }
   hipLaunchKernelGGL(k_scale_N, dim3(stream_groups(n_blocks, 4)), dim3(kThreads), 0, s, Nin, Nout, int(c->ftype),
@@ -1060,9 +652,7 @@ int launch_add(const pbz_codec* c, int64_t n_blocks, const void* N1, const void*
     }
 #undef PBZ_ADD
   } else {
-    int64_t g = n_blocks < 65536 ? n_blocks : 65536;
-    hipLaunchKernelGGL(k_add_generic, dim3(int(g)), dim3(64), 0, s, N1, F1, N2, F2, Nout, Fout, int(c->ftype),
-                       int(c->itype), c->r, sign2, n_blocks, c->kept);
+    return launch_rebin_staged(c, n_blocks, N1, F1, N2, F2, Nout, Fout, sign2, 0.0, s);
   }
   return hip_status(hipGetLastError());
 }
@@ -1146,10 +736,8 @@ int launch_reduce(const pbz_codec* c, ReduceOp op, int64_t n_blocks, const void*
       else
         launch_reduce_vec<PBZ_I32>(int(c->ftype), two, dc, diff, grid, s, n1, f1, n2, f2, nvec, chunk, shift, vpb, n_blocks, tail);
     } else {
-      groups = stream_groups(n_blocks, 1);
-      if (groups > max_groups) groups = max_groups;
-      hipLaunchKernelGGL(k_reduce_generic, dim3(groups, batch), dim3(kThreads), 0, s, n1, f1, n2, f2, int(c->ftype),
-                         int(c->itype), n_blocks, c->kept, two ? 1 : 0, dc ? 1 : 0, diff ? 1 : 0, tail);
+      const int st = launch_reduce_staged(c, two, dc, diff, n_blocks, batch, max_groups, n1, f1, n2, f2, tail, &groups, s);
+      if (st != PBZ_OK) return st;
     }
     int st = hip_status(hipGetLastError());
     if (st != PBZ_OK) return st;
@@ -1233,9 +821,7 @@ int launch_add_scalar(const pbz_codec* c, int64_t n_blocks, const void* Nin, con
     }
 #undef PBZ_ADDS
   } else {
-    int64_t g = n_blocks < 65536 ? n_blocks : 65536;
-    hipLaunchKernelGGL(k_add_scalar_generic, dim3(int(g)), dim3(64), 0, s, Nin, Fin, Nout, Fout, int(c->ftype),
-                       int(c->itype), c->r, shift, n_blocks, c->kept);
+    return launch_rebin_staged(c, n_blocks, Nin, Fin, nullptr, nullptr, Nout, Fout, 1.0, shift, s);
   }
   return hip_status(hipGetLastError());
 }
@@ -1291,9 +877,7 @@ int launch_blockwise(const pbz_codec* c, int mode, int64_t n_blocks, const void*
     }
 #undef PBZ_BW
   } else {
-    int64_t g = n_blocks < 65536 ? n_blocks : 65536;
-    hipLaunchKernelGGL(k_blockwise_generic, dim3(int(g)), dim3(64), 0, s, N1, F1, N2, F2, int(c->ftype), int(c->itype),
-                       out, scale, mode, n_blocks, c->kept);
+    return launch_blockwise_staged(c, mode, n_blocks, N1, F1, N2, F2, out, scale, s);
   }
   return hip_status(hipGetLastError());
 }

@@ -1,0 +1,551 @@
+// Compressed-space operations for kept counts and alignments that the 16-byte-vector kernels of pbz_ops.hip do not
+// take: blocks whose indices are no multiple of 16 bytes or of a power of two of them (zonal masks: 19 of 64 int16
+// indices are 38 bytes), and F pointers that are not 16-byte aligned (a step in the middle of such a series).
+//
+// What bounds them is HBM, provided that F moves in 16-byte pieces although blocks start at any element.  A wave
+// therefore owns a run of consecutive blocks, whose indices are one contiguous span of F:
+//   stage    the span is copied to the wave's own LDS region in aligned 16-byte pieces, at the same phase (address
+//            modulo 16) that it has in memory; N goes along, widened to FP64;
+//   work     a team of 2^k consecutive lanes takes a block, consecutive lanes consecutive dwords of it: two
+//            neighbouring aligned LDS words shifted against each other by the block's phase, the last dword masked,
+//            so that the packed arithmetic of the vector kernels applies;
+//   unstage  new indices collect in another LDS region at the phase of the output pointer and leave in 16-byte pieces,
+//            the span's ends element by element.
+// Waves never wait for each other (no workgroup barrier), so the loads of some overlap the arithmetic of others.
+// 2M blocks of 19 int16 indices (80 MB of F an operand): add and subtract 1016 -> 99 us, addition of a scalar
+// 592 -> 71 us, against the kernels before these, in which a wave read one block element by element; the
+// variance of 128 steps of 16384 blocks of 10 int8 indices 18 us, with a thread per block 30 us (its covariance of adjacent steps 23 against 42 us).
+// Tried and not kept: dword accesses of LDS at any byte instead of shifting two aligned words (add 99 -> 140 us), six
+// waves per SIMD (80 registers, 128 bytes of spills: 106 us), spans of 1 or 4 KiB per wave and operand (15-35 % slower).
+#include "pbz_ops_common.h"
+
+namespace pbz {
+namespace ops {
+namespace {
+
+constexpr int kMaxWaves = 4;             // waves per workgroup, fewer when a wave's regions are large
+constexpr int kCached = 4;               // dwords of a block per lane that the rebinning kernels keep in registers
+constexpr int kTeamDwords = 4;           // a team is the fewest lanes with at most this many dwords each (64 at most)
+constexpr int kMaxBlocksPerWave = 256;
+constexpr int kNPerLane = kMaxBlocksPerWave / 64;
+
+struct Stage {
+  int kept;         // indices per block
+  int bpb;          // bytes of F per block
+  int dwords;       // dwords per block, the last one possibly partial
+  int team_shift;   // log2 of the lanes per block
+  int blocks;       // blocks per wave and tile, a multiple of the blocks per round (64 lanes over the team)
+  int region;       // bytes of an LDS region: a span at any phase and one word more, a multiple of 16
+};
+
+__device__ __forceinline__ void wave_lds_sync() {   // orders one wave's LDS accesses; no workgroup barrier involved
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ int phase_of(const void* p) { return int(reinterpret_cast<uintptr_t>(p) & 15u); }
+
+// [p, p + len) -> LDS, at the phase of p.  Only 16-byte pieces that lie inside the operand [lo, hi) are read as such
+// (they may hold bytes of neighbouring blocks, which nobody uses); the bytes of the others are read one by one.
+__device__ __forceinline__ void stage_span(const uint8_t* lo, const uint8_t* hi, const uint8_t* p, int len, uint8_t* lds) {
+  constexpr int kBatch = 2;                          // 16-byte loads in flight per lane and operand
+  const int lane = threadIdx.x & 63;
+  const int a = phase_of(p);
+  const uint8_t* base = p - a;
+  const int pieces = (a + len + 15) >> 4;
+  const int first = base < lo ? 1 : 0;
+  const int last = base + 16 * int64_t(pieces) > hi ? pieces - 1 : pieces;
+  for (int i0 = first; i0 < last; i0 += 64 * kBatch) {
+    uint4 v[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = i0 + u * 64 + lane;
+      v[u] = reinterpret_cast<const uint4*>(base)[i < last ? i : last - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = i0 + u * 64 + lane;
+      if (i < last) reinterpret_cast<uint4*>(lds)[i] = v[u];
+    }
+  }
+  if (first != 0 && lane < 16 - a && lane < len) lds[a + lane] = p[lane];
+  if (last < pieces) {
+    const int i = 16 * last + lane;
+    if (lane < 16 && i >= a && i < a + len) lds[i] = base[i];
+  }
+}
+
+// LDS -> [p, p + len), from the phase of p; nothing outside is written
+__device__ __forceinline__ void unstage_span(const uint8_t* lds, uint8_t* p, int len) {
+  const int lane = threadIdx.x & 63;
+  const int a = phase_of(p);
+  uint8_t* base = p - a;
+  const int first = a != 0 ? 1 : 0, last = (a + len) >> 4;
+  for (int i = first + lane; i < last; i += 64) reinterpret_cast<uint4*>(base)[i] = reinterpret_cast<const uint4*>(lds)[i];
+  if (a != 0) {
+    const int i = a + lane;
+    if (i < 16 && i < a + len) base[i] = lds[i];
+  }
+  const int i = 16 * last + lane;
+  if (i >= a && i < a + len) base[i] = lds[i];
+}
+
+// N of `count` (at most kMaxBlocksPerWave) blocks from k0 on, widened: requested, then put away
+template <int kNType>
+struct StagedN {
+  double v[kNPerLane];
+  __device__ __forceinline__ void request(const void* N, int64_t k0, int count, bool f16) {
+#pragma unroll
+    for (int u = 0; u < kNPerLane; ++u) {
+      const int i = u * 64 + int(threadIdx.x & 63);
+      if (u * 64 < count) v[u] = load_N<kNType>(N, k0 + (i < count ? i : count - 1), f16);
+    }
+  }
+  __device__ __forceinline__ void put(double* lds, int count) {
+#pragma unroll
+    for (int u = 0; u < kNPerLane; ++u) {
+      const int i = u * 64 + int(threadIdx.x & 63);
+      if (i < count) lds[i] = v[u];
+    }
+  }
+};
+
+// dword d of the block that starts at byte `start` of the LDS region; bytes past the block's end are zero
+__device__ __forceinline__ uint32_t block_dword(const uint8_t* lds, int start, int d, int bpb) {
+  const int at = start + 4 * d;
+  const uint32_t* w = reinterpret_cast<const uint32_t*>(lds) + (at >> 2);
+  const uint32_t v = __builtin_amdgcn_alignbyte(w[1], w[0], uint32_t(at & 3));
+  const int rest = bpb - 4 * d;
+  return rest >= 4 ? v : (rest <= 0 ? 0u : v & ((1u << (8 * rest)) - 1u));
+}
+
+template <int kIType>
+__device__ __forceinline__ void put_dword(uint8_t* lds, int start, int d, int kept, const int* q) {
+  constexpr int kPer = PerDword<kIType>::value;
+  uint8_t* at = lds + start + 4 * d;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    if (d * kPer + e < kept) {
+      if (kIType == PBZ_I8) at[e] = uint8_t(q[e]);
+      else if (kIType == PBZ_I16) reinterpret_cast<uint16_t*>(at)[e] = uint16_t(q[e]);
+      else *reinterpret_cast<uint32_t*>(at) = uint32_t(q[e]);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Algorithms 2 and 4: coefficients from one or two operands, then a new N and new indices; the arithmetic of
+// k_add_vec / k_add_scalar_vec, element by element.  kTwo: C = F1 N1 + F2 (sign2 N2); otherwise
+// C = N1 F1 / r, the first one moved by `shift`.
+// ---------------------------------------------------------------------------------------------
+template <int kIType, int kNType, bool kTwo>
+struct Rebin {
+  static constexpr int kPer = PerDword<kIType>::value;
+  static constexpr bool kExactProducts = kNType != PBZ_F64 && kIType != PBZ_I32;
+  double n1, n2, r, inv_r, shift;
+  // the coefficients of dword d; entries past the block's end come out as zero
+  __device__ __forceinline__ void coefficients(uint32_t a, uint32_t b, int d, double* c) const {
+    double fa[kPer], fb[kPer];
+    unpack_dword<kIType>(a, fa);
+    if (kTwo) unpack_dword<kIType>(b, fb);
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      if (kTwo) {
+        c[e] = kExactProducts ? fma(fa[e], n1, fb[e] * n2) : unfused_sum_of_products(fa[e], n1, fb[e], n2);
+      } else {
+        c[e] = div_by(n1 * fa[e], r, inv_r);
+        if (e == 0 && d == 0) c[e] += shift;
+      }
+    }
+  }
+  // scale: the value an index is a multiple of (kTwo: the new N = max / r; otherwise the maximum itself)
+  __device__ __forceinline__ void indices(const double* c, double scale, double inv, int* q) const {
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) q[e] = rint_to_int(div_by(kTwo ? c[e] : c[e] * r, scale, inv));
+  }
+};
+
+template <int kIType, int kNType, bool kTwo>
+__global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const void* N1, const uint8_t* F1, const void* N2,
+                                                                 const uint8_t* F2, void* Nout, uint8_t* Fout, double r,
+                                                                 double sign2, double shift, int64_t n_blocks, int n_f16) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  constexpr int kPer = PerDword<kIType>::value;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int wave_bytes = (kTwo ? 3 : 2) * st.region + (kTwo ? 2 : 1) * 8 * st.blocks;
+  uint8_t* sa = smem + wave * wave_bytes;
+  uint8_t* so = sa + st.region;
+  uint8_t* sb = so + st.region;                            // used with two operands only
+  double* na = reinterpret_cast<double*>(sa + (kTwo ? 3 : 2) * st.region);
+  double* nb = na + st.blocks;
+  const int team = 1 << st.team_shift, t = lane & (team - 1), slot = lane >> st.team_shift;
+  const int per_round = 64 >> st.team_shift;
+  const int steps = (st.dwords + team - 1) >> st.team_shift;          // dwords per lane, at most
+  const uint8_t* a_end = F1 + n_blocks * st.bpb;
+  const uint8_t* b_end = kTwo ? F2 + n_blocks * st.bpb : nullptr;
+  const int64_t stride = int64_t(gridDim.x) * waves * st.blocks;
+  Rebin<kIType, kNType, kTwo> op;
+  op.r = r;
+  op.inv_r = 1.0 / r;
+  op.shift = shift;
+  for (int64_t k0 = (int64_t(blockIdx.x) * waves + wave) * st.blocks; k0 < n_blocks; k0 += stride) {
+    const int count = n_blocks - k0 < st.blocks ? int(n_blocks - k0) : st.blocks;
+    const int64_t at = k0 * st.bpb;
+    const int len = count * st.bpb;
+    StagedN<kNType> n1, n2;
+    n1.request(N1, k0, count, n_f16 != 0);
+    if (kTwo) n2.request(N2, k0, count, n_f16 != 0);
+    stage_span(F1, a_end, F1 + at, len, sa);
+    if (kTwo) stage_span(F2, b_end, F2 + at, len, sb);
+    n1.put(na, count);
+    if (kTwo) n2.put(nb, count);
+    wave_lds_sync();
+    const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : 0, po = phase_of(Fout + at);
+    for (int b0 = 0; b0 < count; b0 += per_round) {        // uniform: the lane exchanges below are convergent
+      const int b = b0 + slot;
+      const bool live = b < count;
+      const int bc = live ? b : count - 1;                 // slots past the end redo the last block and store nothing
+      op.n1 = na[bc];
+      op.n2 = kTwo ? sign2 * nb[bc] : 0.0;
+      double c[kCached * kPer];
+      double m = 0.0;
+      for (int s0 = 0; s0 < steps; s0 += kCached) {        // one turn unless a block has over 256 dwords
+#pragma unroll
+        for (int s = 0; s < kCached; ++s) {
+          if (s0 + s < steps) {
+            const int d = ((s0 + s) << st.team_shift) + t;
+            if (d < st.dwords) {
+              op.coefficients(block_dword(sa, pa + bc * st.bpb, d, st.bpb),
+                              kTwo ? block_dword(sb, pb + bc * st.bpb, d, st.bpb) : 0u, d, c + s * kPer);
+#pragma unroll
+              for (int e = 0; e < kPer; ++e) m = fmax(m, fabs(c[s * kPer + e]));
+            }
+          }
+        }
+      }
+      for (int off = team >> 1; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+      // an all-zero block has scale = inv = 0 and every c = 0, which gives 0; no quotient rounds beyond r
+      const double n = kTwo ? m / r : m;
+      const double inv = n > 0.0 ? 1.0 / n : 0.0;
+      for (int s0 = 0; s0 < steps; s0 += kCached) {
+#pragma unroll
+        for (int s = 0; s < kCached; ++s) {
+          const int d = ((s0 + s) << st.team_shift) + t;
+          if (s0 + s < steps && d < st.dwords && live) {
+            if (steps > kCached)                           // not in registers any more
+              op.coefficients(block_dword(sa, pa + bc * st.bpb, d, st.bpb),
+                              kTwo ? block_dword(sb, pb + bc * st.bpb, d, st.bpb) : 0u, d, c + s * kPer);
+            int q[kPer];
+            op.indices(c + s * kPer, n, inv, q);
+            put_dword<kIType>(so, po + bc * st.bpb, d, st.kept, q);
+          }
+        }
+      }
+      if (live && t == 0) store_N<kNType>(Nout, k0 + b, n, n_f16 != 0);
+    }
+    wave_lds_sync();
+    unstage_span(so, Fout + at, len);
+    wave_lds_sync();
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Sums over blocks
+// ---------------------------------------------------------------------------------------------
+// exact integer sum of products over a lane's dwords of a block (FP64 for 32-bit indices)
+template <int kIType>
+struct Dot {
+  typedef typename std::conditional<kIType == PBZ_I8, int, typename std::conditional<kIType == PBZ_I16, long long, double>::type>::type acc_t;
+  static __device__ __forceinline__ acc_t add(acc_t acc, uint32_t a, uint32_t b) {
+    if constexpr (kIType == PBZ_I8) return __builtin_amdgcn_sdot4(int(a), int(b), acc, false);
+    else if constexpr (kIType == PBZ_I16) return acc + (long long)__builtin_amdgcn_sdot2(as_short2(a), as_short2(b), 0, false);
+    else return acc + dot_dword<PBZ_I32>(a, b);
+  }
+};
+template <int kIType>
+__host__ __device__ constexpr uint32_t rest_of_first() {   // a block's first dword without its first index
+  return kIType == PBZ_I8 ? 0xffffff00u : (kIType == PBZ_I16 ? 0xffff0000u : 0u);
+}
+
+template <int kIType, int kNType, bool kTwo>
+__global__ __launch_bounds__(64 * kMaxWaves) void k_blockwise_staged(Stage st, const void* __restrict__ N1, const uint8_t* __restrict__ F1,
+                                                                     const void* __restrict__ N2, const uint8_t* __restrict__ F2,
+                                                                     double* __restrict__ out, double scale, int mode,
+                                                                     int64_t n_blocks, int n_f16) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int wave_bytes = (kTwo ? 2 : 1) * (st.region + 8 * st.blocks);
+  uint8_t* sa = smem + wave * wave_bytes;
+  uint8_t* sb = kTwo ? sa + st.region : sa;
+  double* na = reinterpret_cast<double*>(sa + (kTwo ? 2 : 1) * st.region);
+  double* nb = kTwo ? na + st.blocks : na;
+  const int team = 1 << st.team_shift, t = lane & (team - 1), slot = lane >> st.team_shift;
+  const int per_round = 64 >> st.team_shift;
+  const uint8_t* a_end = F1 + n_blocks * st.bpb;
+  const uint8_t* b_end = kTwo ? F2 + n_blocks * st.bpb : nullptr;
+  const int64_t stride = int64_t(gridDim.x) * waves * st.blocks;
+  for (int64_t k0 = (int64_t(blockIdx.x) * waves + wave) * st.blocks; k0 < n_blocks; k0 += stride) {
+    const int count = n_blocks - k0 < st.blocks ? int(n_blocks - k0) : st.blocks;
+    const int64_t at = k0 * st.bpb;
+    StagedN<kNType> n1, n2;
+    n1.request(N1, k0, count, n_f16 != 0);
+    if (kTwo) n2.request(N2, k0, count, n_f16 != 0);
+    stage_span(F1, a_end, F1 + at, count * st.bpb, sa);
+    if (kTwo) stage_span(F2, b_end, F2 + at, count * st.bpb, sb);
+    n1.put(na, count);
+    if (kTwo) n2.put(nb, count);
+    wave_lds_sync();
+    const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : pa;
+    for (int b0 = 0; b0 < count; b0 += per_round) {
+      const int b = b0 + slot;
+      const int bc = b < count ? b : count - 1;
+      typename Dot<kIType>::acc_t acc = 0;
+      for (int d = t; d < st.dwords; d += team) {
+        const uint32_t a = block_dword(sa, pa + bc * st.bpb, d, st.bpb) & (d == 0 ? rest_of_first<kIType>() : 0xffffffffu);
+        const uint32_t c = kTwo ? block_dword(sb, pb + bc * st.bpb, d, st.bpb) : a;
+        acc = Dot<kIType>::add(acc, a, c);
+      }
+      double sum = double(acc);
+      for (int off = team >> 1; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+      if (b < count && t == 0) {
+        double res = sum * (na[bc] * nb[bc]) * scale;
+        if (mode == kBwStd) res = sqrt(res);
+        out[k0 + b] = res;
+      }
+    }
+    wave_lds_sync();
+  }
+}
+
+// the five sums of a reduction (see pbz_ops_common.h); grid y = segment of n_blocks blocks
+template <int kIType, int kNType, bool kTwo, bool kDC, bool kDiff>
+__global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, const void* __restrict__ N1, const uint8_t* __restrict__ F1,
+                                                                  const void* __restrict__ N2, const uint8_t* __restrict__ F2,
+                                                                  int64_t n_blocks, ReduceTail tail) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int wave_bytes = (kTwo ? 2 : 1) * (st.region + 8 * st.blocks);
+  uint8_t* sa = smem + wave * wave_bytes;
+  uint8_t* sb = kTwo ? sa + st.region : sa;
+  double* na = reinterpret_cast<double*>(sa + (kTwo ? 2 : 1) * st.region);
+  double* nb = kTwo ? na + st.blocks : na;
+  const int team = 1 << st.team_shift, t = lane & (team - 1), slot = lane >> st.team_shift;
+  const int per_round = 64 >> st.team_shift;
+  const int64_t seg0 = int64_t(blockIdx.y) * n_blocks;             // the segment's first block
+  F1 += seg0 * st.bpb;
+  const uint8_t* a_end = F1 + n_blocks * st.bpb;
+  if (kTwo) F2 += seg0 * st.bpb;
+  const uint8_t* b_end = kTwo ? F2 + n_blocks * st.bpb : nullptr;
+  const double K1 = kDC ? pilot_value(tail.pilot_n1, tail.pilot_f1, tail, blockIdx.y) : 0.0;
+  const double K2 = kDC && kTwo ? pilot_value(tail.pilot_n2, tail.pilot_f2, tail, blockIdx.y) : 0.0;
+  const bool f16 = tail.n_f16 != 0;
+  double sums[kNumSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  const int64_t stride = int64_t(gridDim.x) * waves * st.blocks;
+  for (int64_t k0 = (int64_t(blockIdx.x) * waves + wave) * st.blocks; k0 < n_blocks; k0 += stride) {
+    const int count = n_blocks - k0 < st.blocks ? int(n_blocks - k0) : st.blocks;
+    const int64_t at = k0 * st.bpb;
+    StagedN<kNType> n1, n2;
+    n1.request(N1, seg0 + k0, count, f16);
+    if (kTwo) n2.request(N2, seg0 + k0, count, f16);
+    stage_span(F1, a_end, F1 + at, count * st.bpb, sa);
+    if (kTwo) stage_span(F2, b_end, F2 + at, count * st.bpb, sb);
+    n1.put(na, count);
+    if (kTwo) n2.put(nb, count);
+    wave_lds_sync();
+    const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : pa;
+    for (int b = slot; b < count; b += per_round) {
+      const double v1 = na[b], v2 = nb[b];
+      typename Dot<kIType>::acc_t s11 = 0, s12 = 0, s22 = 0;
+      double diff = 0.0;
+      for (int d = t; d < st.dwords; d += team) {
+        uint32_t a = block_dword(sa, pa + b * st.bpb, d, st.bpb);
+        uint32_t c = kTwo ? block_dword(sb, pb + b * st.bpb, d, st.bpb) : a;
+        if constexpr (kDiff) {
+          constexpr int kPer = PerDword<kIType>::value;
+          double fa[kPer], fb[kPer];
+          unpack_dword<kIType>(a, fa);
+          unpack_dword<kIType>(c, fb);
+#pragma unroll
+          for (int e = 0; e < kPer; ++e) {
+            const double x = v1 * fa[e] - v2 * fb[e];
+            diff += x * x;
+          }
+        } else {
+          if (kDC && d == 0) {                    // the first coefficient enters shifted by the pilot value
+            const double d1 = fma(v1, double(first_element<kIType>(a)), -K1);
+            sums[kS11] = fma(d1, d1, sums[kS11]);
+            sums[kD1] += d1;
+            a &= rest_of_first<kIType>();
+            if (kTwo) {
+              const double d2 = fma(v2, double(first_element<kIType>(c)), -K2);
+              sums[kS12] = fma(d1, d2, sums[kS12]);
+              sums[kS22] = fma(d2, d2, sums[kS22]);
+              sums[kD2] += d2;
+              c &= rest_of_first<kIType>();
+            }
+          }
+          s11 = Dot<kIType>::add(s11, a, a);
+          if (kTwo) {
+            s12 = Dot<kIType>::add(s12, a, c);
+            s22 = Dot<kIType>::add(s22, c, c);
+          }
+        }
+      }
+      if constexpr (kDiff) {
+        sums[kS11] += diff;
+      } else {
+        sums[kS11] = fma(double(s11), v1 * v1, sums[kS11]);
+        if (kTwo) {
+          sums[kS12] = fma(double(s12), v1 * v2, sums[kS12]);
+          sums[kS22] = fma(double(s22), v2 * v2, sums[kS22]);
+        }
+      }
+    }
+    wave_lds_sync();
+  }
+  reduce_tail(sums, tail, K1, K2, blockDim.x >> 6);
+}
+
+// ---------------------------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------------------------
+// `target`: bytes of a span that a wave should have in flight per operand; `min_waves`: smaller spans are taken before
+// the launch falls below that many waves
+Stage make_stage(const pbz_codec* c, int64_t n_blocks, int target, int64_t min_waves) {
+  Stage st;
+  st.kept = c->kept;
+  st.bpb = c->kept * itype_bytes(c->itype);
+  st.dwords = (st.bpb + 3) / 4;
+  st.team_shift = 0;
+  while (st.team_shift < 6 && ((st.dwords - 1) >> st.team_shift) + 1 > kTeamDwords) ++st.team_shift;
+  const int per_round = 64 >> st.team_shift;
+  int rounds = target / st.bpb / per_round;
+  if (rounds * per_round > kMaxBlocksPerWave) rounds = kMaxBlocksPerWave / per_round;
+  while (rounds > 1 && n_blocks / (int64_t(rounds) * per_round) < min_waves) rounds >>= 1;
+  if (rounds < 1) rounds = 1;
+  st.blocks = rounds * per_round;
+  st.region = (15 + st.blocks * st.bpb + 8 + 15) / 16 * 16;      // the last dword is cut from two whole words
+  return st;
+}
+
+// regions per wave -> waves per workgroup that 60 KiB of LDS hold (the reductions' final sums need some, too), and the
+// bytes they take.  A block has at most 4096 indices of 4 bytes: three regions and N are below that for one wave.
+int waves_for(const Stage& st, int regions, int numbers, size_t* lds) {
+  const size_t per_wave = size_t(regions) * st.region + size_t(numbers) * 8 * st.blocks;
+  int waves = kMaxWaves;
+  while (waves > 1 && per_wave * waves > 60 * 1024) waves >>= 1;
+  *lds = per_wave * waves;
+  return waves;
+}
+
+unsigned group_count(int64_t n_blocks, const Stage& st, int waves, int64_t cap) {
+  const int64_t per_group = int64_t(st.blocks) * waves;
+  int64_t g = (n_blocks + per_group - 1) / per_group;
+  return unsigned(g < cap ? g : cap);
+}
+
+template <int kIType, int kNType>
+void rebin2(bool two, dim3 grid, dim3 block, size_t lds, hipStream_t s, const Stage& st, const void* N1, const void* F1,
+            const void* N2, const void* F2, void* Nout, void* Fout, double r, double sign2, double shift, int64_t n_blocks,
+            int n_f16) {
+  const uint8_t *a = static_cast<const uint8_t*>(F1), *b = static_cast<const uint8_t*>(F2);
+  uint8_t* o = static_cast<uint8_t*>(Fout);
+  if (two)
+    hipLaunchKernelGGL((k_rebin_staged<kIType, kNType, true>), grid, block, lds, s, st, N1, a, N2, b, Nout, o, r, sign2,
+                       shift, n_blocks, n_f16);
+  else
+    hipLaunchKernelGGL((k_rebin_staged<kIType, kNType, false>), grid, block, lds, s, st, N1, a, N2, b, Nout, o, r, sign2,
+                       shift, n_blocks, n_f16);
+}
+
+template <int kIType, int kNType>
+void blockwise2(bool two, dim3 grid, dim3 block, size_t lds, hipStream_t s, const Stage& st, const void* N1, const void* F1,
+                const void* N2, const void* F2, double* out, double scale, int mode, int64_t n_blocks, int n_f16) {
+  const uint8_t *a = static_cast<const uint8_t*>(F1), *b = static_cast<const uint8_t*>(F2);
+  if (two)
+    hipLaunchKernelGGL((k_blockwise_staged<kIType, kNType, true>), grid, block, lds, s, st, N1, a, N2, b, out, scale, mode,
+                       n_blocks, n_f16);
+  else
+    hipLaunchKernelGGL((k_blockwise_staged<kIType, kNType, false>), grid, block, lds, s, st, N1, a, N2, b, out, scale, mode,
+                       n_blocks, n_f16);
+}
+
+template <int kIType, int kNType>
+void reduce2(bool two, bool dc, bool diff, dim3 grid, dim3 block, size_t lds, hipStream_t s, const Stage& st, const void* N1,
+             const void* F1, const void* N2, const void* F2, int64_t n_blocks, const ReduceTail& tail) {
+  const uint8_t *a = static_cast<const uint8_t*>(F1), *b = static_cast<const uint8_t*>(F2);
+#define PBZ_REDUCE(TWO, DC, DIFF) \
+  hipLaunchKernelGGL((k_reduce_staged<kIType, kNType, TWO, DC, DIFF>), grid, block, lds, s, st, N1, a, N2, b, n_blocks, tail)
+  if (diff) PBZ_REDUCE(true, false, true);
+  else if (two && dc) PBZ_REDUCE(true, true, false);
+  else if (two) PBZ_REDUCE(true, false, false);
+  else if (dc) PBZ_REDUCE(false, true, false);
+  else PBZ_REDUCE(false, false, false);
+#undef PBZ_REDUCE
+}
+
+// CALL<index type, width of N>(arguments) for the codec's types
+#define PBZ_BY_TYPES(CALL, ...)                                              \
+  do {                                                                       \
+    if (c->ftype == PBZ_F64) {                                               \
+      if (c->itype == PBZ_I8) CALL<PBZ_I8, PBZ_F64>(__VA_ARGS__);            \
+      else if (c->itype == PBZ_I16) CALL<PBZ_I16, PBZ_F64>(__VA_ARGS__);     \
+      else CALL<PBZ_I32, PBZ_F64>(__VA_ARGS__);                              \
+    } else if (c->ftype == PBZ_F32) {                                        \
+      if (c->itype == PBZ_I8) CALL<PBZ_I8, PBZ_F32>(__VA_ARGS__);            \
+      else if (c->itype == PBZ_I16) CALL<PBZ_I16, PBZ_F32>(__VA_ARGS__);     \
+      else CALL<PBZ_I32, PBZ_F32>(__VA_ARGS__);                              \
+    } else {                                                                 \
+      if (c->itype == PBZ_I8) CALL<PBZ_I8, kN16>(__VA_ARGS__);               \
+      else if (c->itype == PBZ_I16) CALL<PBZ_I16, kN16>(__VA_ARGS__);        \
+      else CALL<PBZ_I32, kN16>(__VA_ARGS__);                                 \
+    }                                                                        \
+  } while (0)
+
+constexpr int kRebinSpan = 2048, kReduceSpan = 4096;       // bytes of F per wave and operand
+constexpr int64_t kMinWaves = 4096;                        // 16 per compute unit
+constexpr int64_t kGroupCap = int64_t(1) << 30;            // the kernels loop beyond that
+
+}  // namespace
+
+int launch_rebin_staged(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2,
+                        void* Nout, void* Fout, double sign2, double shift, hipStream_t s) {
+  const bool two = F2 != nullptr;
+  const Stage st = make_stage(c, n_blocks, kRebinSpan, kMinWaves);
+  size_t lds;
+  const int waves = waves_for(st, two ? 3 : 2, two ? 2 : 1, &lds);
+  const dim3 grid(group_count(n_blocks, st, waves, kGroupCap)), block(64 * waves);
+  const int n_f16 = c->ftype == PBZ_F16 ? 1 : 0;
+  PBZ_BY_TYPES(rebin2, two, grid, block, lds, s, st, N1, F1, N2, F2, Nout, Fout, c->r, sign2, shift, n_blocks, n_f16);
+  return hip_status(hipGetLastError());
+}
+
+int launch_blockwise_staged(const pbz_codec* c, int mode, int64_t n_blocks, const void* N1, const void* F1, const void* N2,
+                            const void* F2, double* out, double scale, hipStream_t s) {
+  const bool two = mode == kBwCovariance;
+  const Stage st = make_stage(c, n_blocks, kReduceSpan, kMinWaves);
+  size_t lds;
+  const int waves = waves_for(st, two ? 2 : 1, two ? 2 : 1, &lds);
+  const dim3 grid(group_count(n_blocks, st, waves, kGroupCap)), block(64 * waves);
+  const int n_f16 = c->ftype == PBZ_F16 ? 1 : 0;
+  PBZ_BY_TYPES(blockwise2, two, grid, block, lds, s, st, N1, F1, N2, F2, out, scale, mode, n_blocks, n_f16);
+  return hip_status(hipGetLastError());
+}
+
+int launch_reduce_staged(const pbz_codec* c, bool two, bool dc, bool diff, int64_t n_blocks, int n_segments, int max_groups,
+                         const void* N1, const void* F1, const void* N2, const void* F2, const ReduceTail& tail, int* groups,
+                         hipStream_t s) {
+  Stage st = make_stage(c, n_blocks, kReduceSpan, kMinWaves / n_segments);
+  size_t lds;
+  const int waves = waves_for(st, two ? 2 : 1, two ? 2 : 1, &lds);
+  unsigned g = group_count(n_blocks, st, waves, max_groups);
+  if (g <= 2) g = 1;                       // two tiles per wave: cheaper than a second launch
+  *groups = int(g);
+  const dim3 grid(g, unsigned(n_segments)), block(64 * waves);
+  PBZ_BY_TYPES(reduce2, two, dc, diff, grid, block, lds, s, st, N1, F1, N2, F2, n_blocks, tail);
+  return hip_status(hipGetLastError());
+}
+
+}  // namespace ops
+}  // namespace pbz
