@@ -306,8 +306,9 @@ int pbz_approximate_wasserstein(const pbz_codec* codec, int64_t n_blocks, const 
 int pbz_stream_copy(void* dst, const void* src, size_t bytes, void* stream);
 
 /* Name of the kernel family pbz_compress ("compress") or pbz_decompress ("decompress") would run for
- * this shape and array type: "generic" or the name of a specialised kernel.  Host only; returns a static
- * string, or NULL on invalid arguments. */
+ * this shape and array type: the name of a kernel specialised to exactly this setting, mask included, or
+ * "generic" for the kernels that take any mask (of the specialised families' block shapes and types) or any
+ * setting at all.  Host only; returns a static string, or NULL on invalid arguments. */
 const char* pbz_kernel_name(const pbz_codec* codec, const char* op, const int64_t* shape, pbz_ftype array_type);
 
 /* Human-readable text for a status code (static string, never NULL). */

@@ -81,7 +81,12 @@ int pbz::ensure_tables(const pbz_codec* c, const DeviceTables** out) {
   std::lock_guard<std::mutex> lock(c->mu);
   DeviceTables& t = c->dev[dev];
   if (!t.ready) {
-    bool ok = hipMalloc(&t.H, sizeof(double) * c->h_total) == hipSuccess &&
+    static_assert(PBZ_MAX_BLOCK_VOLUME < kPruned, "positions fit 16 bits");
+    uint16_t places[PBZ_MAX_BLOCK_VOLUME];
+    for (int j = 0; j < c->vol; ++j) places[j] = c->kept_pos[j] < 0 ? kPruned : uint16_t(c->kept_pos[j]);
+    bool ok = hipMalloc(&t.places, sizeof(uint16_t) * (c->vol < 8 ? 8 : c->vol)) == hipSuccess &&
+              hipMemcpy(t.places, places, sizeof(uint16_t) * c->vol, hipMemcpyHostToDevice) == hipSuccess &&
+              hipMalloc(&t.H, sizeof(double) * c->h_total) == hipSuccess &&
               hipMalloc(&t.kept_pos, sizeof(int32_t) * c->vol) == hipSuccess &&
               hipMalloc(&t.kept_list, sizeof(int32_t) * c->kept) == hipSuccess &&
               hipMemcpy(t.kept_list, c->kept_list, sizeof(int32_t) * c->kept, hipMemcpyHostToDevice) == hipSuccess &&
@@ -91,6 +96,8 @@ int pbz::ensure_tables(const pbz_codec* c, const DeviceTables** out) {
       if (t.H) (void)hipFree(t.H);
       if (t.kept_pos) (void)hipFree(t.kept_pos);
       if (t.kept_list) (void)hipFree(t.kept_list);
+      if (t.places) (void)hipFree(t.places);
+      t.places = nullptr;
       t.kept_list = nullptr;
       t.H = nullptr;
       t.kept_pos = nullptr;
@@ -198,6 +205,7 @@ void pbz_codec_destroy(pbz_codec* c) {
         if (c->dev[d].H) (void)hipFree(c->dev[d].H);
         if (c->dev[d].kept_pos) (void)hipFree(c->dev[d].kept_pos);
         if (c->dev[d].kept_list) (void)hipFree(c->dev[d].kept_list);
+        if (c->dev[d].places) (void)hipFree(c->dev[d].places);
         (void)hipSetDevice(cur);
       }
     }
@@ -272,6 +280,10 @@ int pbz_compress(const pbz_codec* c, const void* x, pbz_ftype x_type, const int6
   const DeviceTables* t = nullptr;
   st = ensure_tables(c, &t);
   if (st != PBZ_OK) return st;
+  if (c->path == PBZ_PATH_AUTO) {
+    const int r = try_compress_masked(c, g, t->places, x, x_type, N, F, s);
+    if (r != 0) return r < 0 ? r : PBZ_OK;
+  }
   if (tiled_kernels_cover(c)) return launch_compress_tiled(c, g, t, x, x_type, N, F, s);
   return launch_compress_generic(c, g, t, x, x_type, N, F, s);
 }
@@ -338,6 +350,10 @@ int pbz_decompress(const pbz_codec* c, const void* N, const void* F, const int64
   const DeviceTables* t = nullptr;
   st = ensure_tables(c, &t);
   if (st != PBZ_OK) return st;
+  if (c->path == PBZ_PATH_AUTO) {
+    const int r = try_decompress_masked(c, g, t->places, N, F, y, y_type, s);
+    if (r != 0) return r < 0 ? r : PBZ_OK;
+  }
   if (tiled_kernels_cover(c)) return launch_decompress_tiled(c, g, t, N, F, y, y_type, s);
   return launch_decompress_generic(c, g, t, N, F, y, y_type, s);
 }

@@ -83,6 +83,14 @@ __device__ __forceinline__ void store_index(void* p, int itype, int64_t i, int64
   }
 }
 
+// Orders this wave's LDS writes before its later LDS reads.  LDS operations of one wave execute in
+// order; the fences keep the compiler from moving accesses across, no workgroup barrier is involved.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // sum over the 64 lanes of a wave; every lane gets the total.  Fixed butterfly order.
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll

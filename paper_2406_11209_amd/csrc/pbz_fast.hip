@@ -33,6 +33,9 @@
 // (compress also leaves the per-wave sums from which mean, variance and norm follow).  N is stored in the
 // codec's working type, converted on load / store.
 //
+// kMasked variants take any pruning mask (and any alignment of F); they serve the settings that differ from a family's
+// only in the mask, without statistics, and count as general kernels: pbz_kernel_name says "generic".
+//
 // Preconditions checked on the host (otherwise the call falls back to the general kernels): the array
 // reduces to at most three dimensions (leading dimensions with block extent 1 fold into the slowest one),
 // the block shape / types / mask box match an instantiation, rows are at least one 16-byte piece long and
@@ -76,6 +79,33 @@ int try_decompress_fast(const pbz_codec* c, const Geom& geo, const void* N, cons
   if (!*name) r = fast::quad16_decompress(c, f, ytype, N, F, y, s, dry_run, name);
   if (!*name) r = fast::oct8_decompress(c, f, ytype, N, F, y, s, dry_run, name);
   if (!*name) r = fast::cube16_decompress(c, f, ytype, N, F, y, s, dry_run, name);
+  return r;
+}
+
+// The kernels of the same families that take any mask, in the order above.  They are asked after the kernels for one
+// mask (everything, or a box), which skip work that these cannot, and before the kernels for any block shape, which take 1.4 to
+// 3 times as long on every setting measured (the figures are with MaskArgs)
+int try_compress_masked(const pbz_codec* c, const Geom& geo, const uint16_t* pos, const void* x, int xtype, void* N, void* F,
+                        hipStream_t s) {
+  if (c->kept == c->vol || !fast::aligned16(x)) return 0;
+  const fast::Folded f = fast::fold(c, geo);
+  if (!f.ok) return 0;
+  int r = fast::lane_compress_masked(c, f, xtype, pos, x, N, F, s);
+  if (r == 0) r = fast::quad16_compress_masked(c, f, xtype, pos, x, N, F, s);
+  if (r == 0) r = fast::oct8_compress_masked(c, f, xtype, pos, x, N, F, s);
+  if (r == 0) r = fast::cube16_compress_masked(c, f, xtype, pos, x, N, F, s);
+  return r;
+}
+
+int try_decompress_masked(const pbz_codec* c, const Geom& geo, const uint16_t* pos, const void* N, const void* F, void* y,
+                          int ytype, hipStream_t s) {
+  if (c->kept == c->vol || !fast::aligned16(y)) return 0;
+  const fast::Folded f = fast::fold(c, geo);
+  if (!f.ok) return 0;
+  int r = fast::lane_decompress_masked(c, f, ytype, pos, N, F, y, s);
+  if (r == 0) r = fast::quad16_decompress_masked(c, f, ytype, pos, N, F, y, s);
+  if (r == 0) r = fast::oct8_decompress_masked(c, f, ytype, pos, N, F, y, s);
+  if (r == 0) r = fast::cube16_decompress_masked(c, f, ytype, pos, N, F, y, s);
   return r;
 }
 

@@ -107,13 +107,22 @@ __device__ __forceinline__ void cube_exchange_zx(uint4* st, int lane, const T* f
   }
 }
 
-template <int TF, typename T, typename IT, typename XT, bool kRagged, bool kStats, bool kTailX>
+// Any mask: a wave's region for its block's span of F (4095 indices of 32 bits: 16392 bytes with their phase) and a dword
+// per lane for the pruned ones is half a KiB larger than its half of the exchange buffer.  That half lies at the end of
+// the first wave's region and at the start of the second's, so that neither region touches the other wave's half.
+constexpr int kCubePad = 32;                                          // uint4
+constexpr int kCubeRegion = kCubeSlots + kCubePad;
+constexpr uint32_t kCubeAside = kCubeRegion * 16 - 256;
+
+template <int TF, typename T, typename IT, typename XT, bool kRagged, bool kStats, bool kTailX, bool kMasked = false>
 __global__ __launch_bounds__(128) void k_compress_cube16(FastGeom g, const XT* __restrict__ x, void* __restrict__ N,
-                                                         IT* __restrict__ F, double* __restrict__ tile_sums) {
+                                                         IT* __restrict__ F, double* __restrict__ tile_sums,
+                                                         MaskArgs<kMasked> mask) {
   using Q4 = Quad4<XT>;
   constexpr int PER = IdxPack<IT>::per;            // indices per dword
   constexpr int ROWW = 16 / PER;                   // dwords per row of 16 indices
-  __shared__ uint4 lds[2 * kCubeSlots];
+  __shared__ uint4 buffer[kMasked ? 2 * kCubeRegion : 2 * kCubeSlots];
+  uint4* lds = kMasked ? buffer + kCubePad : buffer;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int64_t pair_x, by, bz;
@@ -186,6 +195,26 @@ __global__ __launch_bounds__(128) void k_compress_cube16(FastGeom g, const XT* _
   const T inv = m > T(0) ? T(g.r) / m : T(0);
   const int ky = lane & 15, zh = lane >> 4;
   const int64_t block = (bz * g.gy + by) * g.gx + bx;
+  if constexpr (kMasked) {
+    const int bytes = mask.kept * int(sizeof(IT));
+    uint8_t* region = reinterpret_cast<uint8_t*>(buffer + wave * kCubeRegion);
+    uint8_t* dst = reinterpret_cast<uint8_t*>(F) + block * bytes;
+    const uint32_t aside = kCubeAside + uint32_t(lane) * 4u;
+    wave_lds_sync();                                 // the exchange's last reads precede the span's writes
+#pragma unroll
+    for (int zl = 0; zl < 4; ++zl) {
+      uint4 places[2];
+      load_places<2>(mask.pos + ((4 * zh + zl) * 16 + ky) * 16, places);
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        put_index<IT>(region, masked_address<IT>(places[e >> 3], e & 7, uint32_t(phase_of(dst)), aside),
+                      bin_bits(a[zl * 16 + e], inv));
+    }
+    if (lane == 0) store_float(N, g.ntype, block, m);
+    wave_lds_sync();
+    unstage_span(region, dst, bytes);
+    return;
+  }
   uint32_t w[4 * ROWW];
 #pragma unroll
   for (int zl = 0; zl < 4; ++zl)
@@ -216,13 +245,15 @@ __global__ __launch_bounds__(128) void k_compress_cube16(FastGeom g, const XT* _
   }
 }
 
-template <int TF, typename T, typename IT, typename XT, bool kTailX>
+template <int TF, typename T, typename IT, typename XT, bool kTailX, bool kMasked = false>
 __global__ __launch_bounds__(128) void k_decompress_cube16(FastGeom g, const void* __restrict__ N,
-                                                           const IT* __restrict__ F, XT* __restrict__ y) {
+                                                           const IT* __restrict__ F, XT* __restrict__ y,
+                                                           MaskArgs<kMasked> mask) {
   using Q4 = Quad4<XT>;
   constexpr int PER = IdxPack<IT>::per;
   constexpr int ROWW = 16 / PER;
-  __shared__ uint4 lds[2 * kCubeSlots];
+  __shared__ uint4 buffer[kMasked ? 2 * kCubeRegion : 2 * kCubeSlots];
+  uint4* lds = kMasked ? buffer + kCubePad : buffer;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int64_t pair_x, by, bz;
@@ -235,25 +266,47 @@ __global__ __launch_bounds__(128) void k_decompress_cube16(FastGeom g, const voi
   T a[64], c[64];
   {  // layout B: rows (kz = 4 zh + zl, ky) of the indices
     const int ky = lane & 15, zh = lane >> 4;
-    const uint4* src = reinterpret_cast<const uint4*>(F + block * 4096);
-    uint4 f[4 * (ROWW / 4)];
+    if constexpr (kMasked) {
+      const int bytes = mask.kept * int(sizeof(IT));
+      uint8_t* region = reinterpret_cast<uint8_t*>(buffer + wave * kCubeRegion);
+      const uint8_t* lo = reinterpret_cast<const uint8_t*>(F);
+      const uint8_t* src = lo + block * bytes;
+      const uint32_t aside = kCubeAside + uint32_t(lane) * 4u;
+      put_index<int32_t>(region, aside, 0u);
+      stage_span<4>(lo, lo + g.gz * g.gy * g.gx * bytes, src, bytes, region);
+      const T scale = load_float<T>(N, g.ntype, block) / T(g.r);
+      wave_lds_sync();
 #pragma unroll
-    for (int zl = 0; zl < 4; ++zl)
+      for (int zl = 0; zl < 4; ++zl) {
+        uint4 places[2];
+        load_places<2>(mask.pos + ((4 * zh + zl) * 16 + ky) * 16, places);
 #pragma unroll
-      for (int k = 0; k < ROWW / 4; ++k) f[zl * (ROWW / 4) + k] = src[(((4 * zh + zl) * 16 + ky) * ROWW) / 4 + k];
-    const T scale = load_float<T>(N, g.ntype, block) / T(g.r);        // Algorithm 3: N F / r
-#pragma unroll
-    for (int zl = 0; zl < 4; ++zl)
-#pragma unroll
-      for (int k = 0; k < ROWW / 4; ++k) {
-        const uint4 u = f[zl * (ROWW / 4) + k];
-        const uint32_t uw[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-          for (int e = 0; e < PER; ++e)
-            a[zl * 16 + (4 * k + d) * PER + e] = scale * T(IdxPack<IT>::get(uw[d], e));
+        for (int e = 0; e < 16; ++e)
+          a[zl * 16 + e] =
+              scale * T(get_index<IT>(region, masked_address<IT>(places[e >> 3], e & 7, uint32_t(phase_of(src)), aside)));
       }
+      wave_lds_sync();                                                // the exchange below writes the same LDS
+    } else {
+      const uint4* src = reinterpret_cast<const uint4*>(F + block * 4096);
+      uint4 f[4 * (ROWW / 4)];
+#pragma unroll
+      for (int zl = 0; zl < 4; ++zl)
+#pragma unroll
+        for (int k = 0; k < ROWW / 4; ++k) f[zl * (ROWW / 4) + k] = src[(((4 * zh + zl) * 16 + ky) * ROWW) / 4 + k];
+      const T scale = load_float<T>(N, g.ntype, block) / T(g.r);        // Algorithm 3: N F / r
+#pragma unroll
+      for (int zl = 0; zl < 4; ++zl)
+#pragma unroll
+        for (int k = 0; k < ROWW / 4; ++k) {
+          const uint4 u = f[zl * (ROWW / 4) + k];
+          const uint32_t uw[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+          for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int e = 0; e < PER; ++e)
+              a[zl * 16 + (4 * k + d) * PER + e] = scale * T(IdxPack<IT>::get(uw[d], e));
+        }
+    }
 #pragma unroll
     for (int zl = 0; zl < 4; ++zl) tf_inverse<TF, T, 16, 1, 16>(a + zl * 16);
   }
@@ -314,7 +367,7 @@ struct Cube16Kernel {
   template <bool kRagged, bool kStats, bool kTailX>
   static void launch(const FastGeom& g, dim3 grid, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     hipLaunchKernelGGL((k_compress_cube16<TF, T, IT, XT, kRagged, kStats, kTailX>), grid, dim3(128), 0, s, g,
-                       static_cast<const XT*>(x), N, static_cast<IT*>(F), tile_sums);
+                       static_cast<const XT*>(x), N, static_cast<IT*>(F), tile_sums, MaskArgs<false>());
   }
   static int compress(FastGeom g, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     dim3 grid;
@@ -330,10 +383,53 @@ struct Cube16Kernel {
     if (!grid_for(g, &grid)) return 0;
     if (g.X % 16)
       hipLaunchKernelGGL((k_decompress_cube16<TF, T, IT, XT, true>), grid, dim3(128), 0, s, g, N,
-                         static_cast<const IT*>(F), static_cast<XT*>(y));
+                         static_cast<const IT*>(F), static_cast<XT*>(y), MaskArgs<false>());
     else
       hipLaunchKernelGGL((k_decompress_cube16<TF, T, IT, XT, false>), grid, dim3(128), 0, s, g, N,
-                         static_cast<const IT*>(F), static_cast<XT*>(y));
+                         static_cast<const IT*>(F), static_cast<XT*>(y), MaskArgs<false>());
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+};
+
+// Any mask, on the same kernels
+template <typename K> struct CubeMasked;
+template <int TF, typename T, typename IT, typename XT>
+struct CubeMasked<Cube16Kernel<TF, T, IT, XT>> {
+  using Base = Cube16Kernel<TF, T, IT, XT>;
+  static bool matches(const pbz_codec* c, Folded f, int xtype) {
+    f.kz = f.ky = f.kx = 16;
+    return Base::matches(c, f, xtype);
+  }
+  static MaskArgs<true> args(const pbz_codec* c, const uint16_t* pos) {
+    MaskArgs<true> m;
+    m.pos = pos;
+    m.keep = 0;
+    m.kept = c->kept;
+    return m;
+  }
+  template <bool kTailX>
+  static void launch(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* x, void* N, void* F,
+                     hipStream_t s) {
+    hipLaunchKernelGGL((k_compress_cube16<TF, T, IT, XT, true, false, kTailX, true>), grid, dim3(128), 0, s, g,
+                       static_cast<const XT*>(x), N, static_cast<IT*>(F), nullptr, args(c, pos));
+  }
+  template <bool kTailX>
+  static void launch_inverse(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* N,
+                             const void* F, void* y, hipStream_t s) {
+    hipLaunchKernelGGL((k_decompress_cube16<TF, T, IT, XT, kTailX, true>), grid, dim3(128), 0, s, g, N,
+                       static_cast<const IT*>(F), static_cast<XT*>(y), args(c, pos));
+  }
+  static int compress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* x, void* N, void* F, hipStream_t s) {
+    dim3 grid;
+    if (!Base::grid_for(g, &grid)) return 0;
+    g.X % 16 ? launch<true>(c, g, grid, pos, x, N, F, s) : launch<false>(c, g, grid, pos, x, N, F, s);
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+  static int decompress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* N, const void* F, void* y,
+                        hipStream_t s) {
+    dim3 grid;
+    if (!Base::grid_for(g, &grid)) return 0;
+    g.X % 16 ? launch_inverse<true>(c, g, grid, pos, N, F, y, s) : launch_inverse<false>(c, g, grid, pos, N, F, y, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
   }
 };
@@ -347,9 +443,19 @@ struct Cube16Kernel {
   X(Cube16Kernel<TF COMMA double COMMA int32_t COMMA double>, "cube16_f64_16x16x16_i32" SUFFIX) \
   X(Cube16Kernel<TF COMMA float COMMA int8_t COMMA double>, "cube16_f64_w32_16x16x16_i8" SUFFIX)
 
+#define PBZ_MASKED_ROWS(X, TF) \
+  X(CubeMasked<Cube16Kernel<TF COMMA double COMMA int16_t COMMA float>>) \
+  X(CubeMasked<Cube16Kernel<TF COMMA float COMMA int8_t COMMA float>>) \
+  X(CubeMasked<Cube16Kernel<TF COMMA double COMMA int32_t COMMA float>>) \
+  X(CubeMasked<Cube16Kernel<TF COMMA double COMMA int8_t COMMA double>>) \
+  X(CubeMasked<Cube16Kernel<TF COMMA double COMMA int16_t COMMA double>>) \
+  X(CubeMasked<Cube16Kernel<TF COMMA double COMMA int32_t COMMA double>>) \
+  X(CubeMasked<Cube16Kernel<TF COMMA float COMMA int8_t COMMA double>>)
+
 }  // namespace
 
 PBZ_DEFINE_FAST_FAMILY(cube16, PBZ_ROWS)
+PBZ_DEFINE_MASKED_FAMILY(cube16, PBZ_MASKED_ROWS)
 
 }  // namespace fast
 }  // namespace pbz

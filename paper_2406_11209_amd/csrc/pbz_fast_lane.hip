@@ -10,13 +10,23 @@ namespace {
 // =====================================================================================================
 // Family "lane": one lane = one block
 // =====================================================================================================
+// Any mask: bytes of the LDS region of a wave that holds the span of 64 blocks, in two halves where indices are 32 bits
+// (63 of 64 kept: 15.8 KiB for all)
+template <typename IT>
+__host__ __device__ constexpr int lane_mask_rounds() { return sizeof(IT) == 4 ? 2 : 1; }
+template <typename IT>
+__host__ __device__ constexpr int lane_mask_region(int kept) {
+  return (15 + 64 / lane_mask_rounds<IT>() * kept * int(sizeof(IT)) + 15) / 16 * 16;
+}
+
 // kRagged: the slow dimensions are not multiples of the block extents, so some block rows lie outside the
 // array.  Such rows are still loaded (from a clamped, valid address: a branch around a load would make the
 // compiler wait for all outstanding loads at the join) and zeroed afterwards.
 template <int TF, typename T, typename XT, typename IT, typename NT, int BZ, int BY, int BX, int KZ, int KY, int KX,
-          bool kRagged, bool kStats, bool kTailX = false>
+          bool kRagged, bool kStats, bool kTailX = false, bool kMasked = false>
 __global__ __launch_bounds__(256) void k_compress_lane(FastGeom g, const XT* __restrict__ x, void* __restrict__ N,
-                                                       IT* __restrict__ F, double* __restrict__ tile_sums) {
+                                                       IT* __restrict__ F, double* __restrict__ tile_sums,
+                                                       MaskArgs<kMasked> mask) {
   constexpr int VOL = BZ * BY * BX, ROWS = BZ * BY;
   constexpr int RV = BX * int(sizeof(XT)) / 16;       // 16-byte loads per block row
   constexpr int PER16 = Unpack<T, XT>::n;
@@ -126,6 +136,38 @@ __global__ __launch_bounds__(256) void k_compress_lane(FastGeom g, const XT* __r
   for (int i = 0; i < VOL; ++i) m = fmax(m, abs_t(v[i]));
   const T inv = m > T(0) ? T(g.r) / m : T(0);
 
+  if constexpr (kMasked) {
+    // Every lane knows its block's place in the span and the mask is the same for all of them: which entries are kept
+    // and where the next one goes is scalar work, and pruned entries are not binned.
+    extern __shared__ __align__(16) uint8_t spans[];
+    constexpr int kRounds = lane_mask_rounds<IT>(), kBlocks = 64 / kRounds;
+    const int bytes = mask.kept * int(sizeof(IT));
+    uint8_t* st = spans + (threadIdx.x >> 6) * lane_mask_region<IT>(mask.kept);
+    const int64_t first_block = (bz * g.gy + by) * g.gx + tx * 64;
+    const int n_active = int(g.gx - tx * 64 < 64 ? g.gx - tx * 64 : 64);
+    if (active) store_float(N, g.ntype, first_block + lane, m);
+#pragma unroll
+    for (int round = 0; round < kRounds; ++round) {
+      uint8_t* dst = reinterpret_cast<uint8_t*>(F) + (first_block + round * kBlocks) * bytes;
+      const int count = n_active - round * kBlocks < kBlocks ? n_active - round * kBlocks : kBlocks;
+      if (count <= 0) break;                                     // uniform
+      if (kRounds == 1 || lane / kBlocks == round) {
+        uint32_t at = uint32_t(phase_of(dst) + (lane - round * kBlocks) * bytes);
+#pragma unroll
+        for (int j = 0; j < VOL; ++j) {
+          if ((mask.keep >> j) & 1u) {
+            put_index<IT>(st, at, bin_bits(v[j], inv));
+            at += uint32_t(sizeof(IT));
+          }
+        }
+      }
+      wave_lds_sync();
+      unstage_span(st, dst, count * bytes);
+      wave_lds_sync();
+    }
+    return;
+  }
+
   uint32_t w[KW];
   constexpr int PER = IdxPack<IT>::per;
 #pragma unroll
@@ -184,9 +226,9 @@ __global__ __launch_bounds__(256) void k_compress_lane(FastGeom g, const XT* __r
 // and those of a partly filled wave made once, outside the loops over the rows, the bound costs no spill (with
 // the choice inside the loops: nine values per lane, 4.5 % more bytes written than the array has).
 template <int TF, typename T, typename XT, typename IT, typename NT, int BZ, int BY, int BX, int KZ, int KY, int KX,
-          bool kRagged, bool kTailX = false>
+          bool kRagged, bool kTailX = false, bool kMasked = false>
 __global__ __launch_bounds__(256, 2) void k_decompress_lane(FastGeom g, const void* __restrict__ N, const IT* __restrict__ F,
-                                                         XT* __restrict__ y) {
+                                                         XT* __restrict__ y, MaskArgs<kMasked> mask) {
   constexpr int VOL = BZ * BY * BX, ROWS = BZ * BY;
   constexpr int RV = BX * int(sizeof(XT)) / 16;
   constexpr int PER16 = Unpack<T, XT>::n;
@@ -198,26 +240,60 @@ __global__ __launch_bounds__(256, 2) void k_decompress_lane(FastGeom g, const vo
   int64_t tx, by, bz;
   if (!decode_tile<4>(g, tx, by, bz)) return;
   const int64_t bx = tx * 64 + lane;
+  T v[VOL];
+  if constexpr (kMasked) {
+    extern __shared__ __align__(16) uint8_t spans[];
+    constexpr int kRounds = lane_mask_rounds<IT>(), kBlocks = 64 / kRounds;
+    const int bytes = mask.kept * int(sizeof(IT));
+    uint8_t* st = spans + (threadIdx.x >> 6) * lane_mask_region<IT>(mask.kept);
+    const uint8_t* lo = reinterpret_cast<const uint8_t*>(F);
+    const uint8_t* hi = lo + g.gz * g.gy * g.gx * bytes;
+    const int64_t first_block = (bz * g.gy + by) * g.gx + tx * 64;
+    const int n_active = int(g.gx - tx * 64 < 64 ? g.gx - tx * 64 : 64);
+    const T scale = load_float<T>(N, g.ntype, first_block + (lane < n_active ? lane : n_active - 1)) / T(g.r);
+#pragma unroll
+    for (int i = 0; i < VOL; ++i) v[i] = T(0);
+#pragma unroll
+    for (int round = 0; round < kRounds; ++round) {
+      const uint8_t* src = lo + (first_block + round * kBlocks) * bytes;
+      const int count = n_active - round * kBlocks < kBlocks ? n_active - round * kBlocks : kBlocks;
+      if (count <= 0) break;                                     // uniform
+      stage_span<4>(lo, hi, src, count * bytes, st);
+      wave_lds_sync();
+      if (kRounds == 1 || lane / kBlocks == round) {
+        const int mine = lane - round * kBlocks < count ? lane - round * kBlocks : count - 1;
+        uint32_t at = uint32_t(phase_of(src) + mine * bytes);
+#pragma unroll
+        for (int j = 0; j < VOL; ++j) {
+          if ((mask.keep >> j) & 1u) {                           // uniform: scalar work, as in compress
+            v[j] = scale * T(get_index<IT>(st, at));
+            at += uint32_t(sizeof(IT));
+          }
+        }
+      }
+      wave_lds_sync();
+    }
+  }
   if (bx >= g.gx) return;
   const int64_t block = (bz * g.gy + by) * g.gx + bx;
   const bool whole_wave = tx * 64 + 64 <= g.gx;       // uniform: all 64 lanes hold a block
 
-  uint32_t w[KW];
-  const uint4* src = reinterpret_cast<const uint4*>(F + block * KEPT);
+  if constexpr (!kMasked) {
+    uint32_t w[KW];
+    const uint4* src = reinterpret_cast<const uint4*>(F + block * KEPT);
 #pragma unroll
-  for (int k = 0; k < KW / 4; ++k) {
-    const uint4 u = src[k];
-    w[4 * k] = u.x; w[4 * k + 1] = u.y; w[4 * k + 2] = u.z; w[4 * k + 3] = u.w;
-  }
-  const T scale = load_float<T>(N, g.ntype, block) / T(g.r);          // Algorithm 3: N F / r, the division hoisted per block
-
-  T v[VOL];
+    for (int k = 0; k < KW / 4; ++k) {
+      const uint4 u = src[k];
+      w[4 * k] = u.x; w[4 * k + 1] = u.y; w[4 * k + 2] = u.z; w[4 * k + 3] = u.w;
+    }
+    const T scale = load_float<T>(N, g.ntype, block) / T(g.r);          // Algorithm 3: N F / r, the division hoisted per block
 #pragma unroll
-  for (int i = 0; i < VOL; ++i) v[i] = T(0);
+    for (int i = 0; i < VOL; ++i) v[i] = T(0);
 #pragma unroll
-  for (int j = 0; j < KEPT; ++j) {
-    const int kx = j % KX, ky = (j / KX) % KY, kz = j / (KX * KY);
-    v[(kz * BY + ky) * BX + kx] = scale * T(IdxPack<IT>::get(w[j / PER], j % PER));
+    for (int j = 0; j < KEPT; ++j) {
+      const int kx = j % KX, ky = (j / KX) % KY, kz = j / (KX * KY);
+      v[(kz * BY + ky) * BX + kx] = scale * T(IdxPack<IT>::get(w[j / PER], j % PER));
+    }
   }
 
   inverse_block<TF, T, BZ, BY, BX, KZ, KY, KX>(v);
@@ -318,12 +394,12 @@ struct LaneKernel {
   template <bool kRagged, bool kStats, bool kTailX>
   static void launch(const FastGeom& g, dim3 grid, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     hipLaunchKernelGGL((k_compress_lane<TF, T, XT, IT, NT, BZ, BY, BX, KZ, KY, KX, kRagged, kStats, kTailX>), grid,
-                       dim3(256), 0, s, g, static_cast<const XT*>(x), N, static_cast<IT*>(F), tile_sums);
+                       dim3(256), 0, s, g, static_cast<const XT*>(x), N, static_cast<IT*>(F), tile_sums, MaskArgs<false>());
   }
   template <bool kRagged, bool kTailX>
   static void launch_inverse(const FastGeom& g, dim3 grid, const void* N, const void* F, void* y, hipStream_t s) {
     hipLaunchKernelGGL((k_decompress_lane<TF, T, XT, IT, NT, BZ, BY, BX, KZ, KY, KX, kRagged, kTailX>), grid, dim3(256), 0,
-                       s, g, N, static_cast<const IT*>(F), static_cast<XT*>(y));
+                       s, g, N, static_cast<const IT*>(F), static_cast<XT*>(y), MaskArgs<false>());
   }
   // tile_sums != nullptr: also the per-wave statistic sums (four doubles per tile)
   static int compress(FastGeom g, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
@@ -341,6 +417,48 @@ struct LaneKernel {
     if (g.X % BX) launch_inverse<true, true>(g, grid, N, F, y, s);
     else if (g.Z % BZ || g.Y % BY) launch_inverse<true, false>(g, grid, N, F, y, s);
     else launch_inverse<false, false>(g, grid, N, F, y, s);
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+};
+
+// The same kernel for any mask but its own box (BZ = KZ and so on: K is a kernel that keeps everything)
+template <typename K> struct LaneMasked;
+template <int TF, typename T, typename XT, typename IT, typename NT, int BZ, int BY, int BX>
+struct LaneMasked<LaneKernel<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX>> {
+  static bool matches(const pbz_codec* c, Folded f, int xtype) {
+    f.kz = BZ; f.ky = BY; f.kx = BX;
+    return LaneKernel<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX>::matches(c, f, xtype);
+  }
+  static MaskArgs<true> args(const pbz_codec* c) {
+    MaskArgs<true> m;
+    m.pos = nullptr;
+    m.kept = c->kept;
+    m.keep = 0;
+    for (int j = 0; j < 64; ++j) m.keep |= uint64_t(c->mask[j] != 0) << j;
+    return m;
+  }
+  static int compress(const pbz_codec* c, FastGeom g, const uint16_t*, const void* x, void* N, void* F, hipStream_t s) {
+    dim3 grid;
+    if (!tile_grid(g, 64, 4, &grid)) return 0;
+    const size_t lds = 4 * size_t(lane_mask_region<IT>(c->kept));
+    if (g.X % BX)
+      hipLaunchKernelGGL((k_compress_lane<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX, true, false, true, true>), grid, dim3(256),
+                         lds, s, g, static_cast<const XT*>(x), N, static_cast<IT*>(F), nullptr, args(c));
+    else
+      hipLaunchKernelGGL((k_compress_lane<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX, true, false, false, true>), grid, dim3(256),
+                         lds, s, g, static_cast<const XT*>(x), N, static_cast<IT*>(F), nullptr, args(c));
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+  static int decompress(const pbz_codec* c, FastGeom g, const uint16_t*, const void* N, const void* F, void* y, hipStream_t s) {
+    dim3 grid;
+    if (!tile_grid(g, 64, 4, &grid)) return 0;
+    const size_t lds = 4 * size_t(lane_mask_region<IT>(c->kept));
+    if (g.X % BX)
+      hipLaunchKernelGGL((k_decompress_lane<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX, true, true, true>), grid, dim3(256), lds,
+                         s, g, N, static_cast<const IT*>(F), static_cast<XT*>(y), args(c));
+    else
+      hipLaunchKernelGGL((k_decompress_lane<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX, true, false, true>), grid, dim3(256), lds,
+                         s, g, N, static_cast<const IT*>(F), static_cast<XT*>(y), args(c));
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
   }
 };
@@ -395,9 +513,18 @@ template <int TF> using Lane_f64_4x4x4_i32 = LaneKernel<TF, double, double, int3
   X(Lane_f32_4x4x4_i32<TF>, "lane_f32_4x4x4_i32" SUFFIX) \
   X(Lane_f64_4x4x4_i32<TF>, "lane_f64_4x4x4_i32" SUFFIX)
 
+#define PBZ_MASKED_ROWS(X, TF) \
+  X(LaneMasked<Lane_f32_8x8_i8<TF>>) X(LaneMasked<Lane_bf16_8x8_i8<TF>>) X(LaneMasked<Lane_f16_8x8_i8<TF>>) \
+  X(LaneMasked<Lane_f32_8x8_i16<TF>>) X(LaneMasked<Lane_f32_8x8_i32<TF>>) X(LaneMasked<Lane_f64_8x8_i8<TF>>) \
+  X(LaneMasked<Lane_f64_8x8_i16<TF>>) X(LaneMasked<Lane_f64_8x8_i32<TF>>) X(LaneMasked<Lane_f64_w32_8x8_i8<TF>>) \
+  X(LaneMasked<Lane_f64_w32_8x8_i16<TF>>) X(LaneMasked<Lane_f32_4x4x4_i8<TF>>) X(LaneMasked<Lane_f32_4x4x4_i16<TF>>) \
+  X(LaneMasked<Lane_f32_4x4x4_i32<TF>>) X(LaneMasked<Lane_f64_4x4x4_i8<TF>>) X(LaneMasked<Lane_f64_4x4x4_i16<TF>>) \
+  X(LaneMasked<Lane_f64_4x4x4_i32<TF>>) X(LaneMasked<Lane_f64_w32_4x4x4_i8<TF>>) X(LaneMasked<Lane_f64_w32_4x4x4_i16<TF>>)
+
 }  // namespace
 
 PBZ_DEFINE_FAST_FAMILY(lane, PBZ_ROWS)
+PBZ_DEFINE_MASKED_FAMILY(lane, PBZ_MASKED_ROWS)
 
 }  // namespace fast
 }  // namespace pbz

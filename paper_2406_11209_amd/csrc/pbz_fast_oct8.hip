@@ -126,15 +126,89 @@ __device__ __forceinline__ void oct_load_rows_through_lds(const FastGeom& g, uin
   }
 }
 
-template <int TF, typename XT, int KZ, int KY, int KX, bool kRagged, bool kStats, bool kTailX = false>
+// Any mask: the wave's LDS region holds the span of eight blocks, of four at a time where indices are 32 bits (511 of
+// 512 kept: 8176 bytes at any phase), and, from kOctAside on, a dword per lane for the pruned ones.
+constexpr int kOctMaskedSlots = 8 * 64 + 32;                     // uint4 per wave
+constexpr uint32_t kOctAside = kOctMaskedSlots * 16 - 256;
+template <typename IT>
+constexpr int oct_mask_rounds() { return sizeof(IT) == 4 ? 2 : 1; }
+
+// the lane's row j of eight planes u of block bb, binned, to F
+template <typename IT, typename T>
+__device__ __forceinline__ void oct_put_masked(const FastGeom& g, const MaskArgs<true>& mask, uint4* region, IT* F, int64_t tx,
+                                               int64_t block0, int lane, const T* u, T inv) {
+  constexpr int kRounds = oct_mask_rounds<IT>(), kBlocks = 8 / kRounds;
+  const int bb = lane >> 3, j = lane & 7;
+  const int bytes = mask.kept * int(sizeof(IT));
+  const int n_active = int(g.gx - tx * 8 < 8 ? g.gx - tx * 8 : 8);
+  uint8_t* st = reinterpret_cast<uint8_t*>(region);
+  const uint32_t aside = kOctAside + uint32_t(lane) * 4u;
+#pragma unroll
+  for (int round = 0; round < kRounds; ++round) {
+    uint8_t* dst = reinterpret_cast<uint8_t*>(F) + (block0 + round * kBlocks) * bytes;
+    const int count = n_active - round * kBlocks < kBlocks ? n_active - round * kBlocks : kBlocks;
+    if (count <= 0) break;                                       // uniform
+    if (kRounds == 1 || bb / kBlocks == round) {
+      const uint32_t base = uint32_t(phase_of(dst) + (bb - round * kBlocks) * bytes);
+#pragma unroll
+      for (int zq = 0; zq < 8; ++zq) {
+        uint4 places;
+        load_places<1>(mask.pos + zq * 64 + j * 8, &places);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          put_index<IT>(st, masked_address<IT>(places, e, base, aside), bin_bits(u[zq * 8 + e], inv));
+      }
+    }
+    wave_lds_sync();
+    unstage_span(st, dst, count * bytes);
+    wave_lds_sync();
+  }
+}
+
+// the other way: row j of all eight planes of block bb from F, times `scale`
+template <typename IT, typename T>
+__device__ __forceinline__ void oct_get_masked(const FastGeom& g, const MaskArgs<true>& mask, uint4* region, const IT* F,
+                                               int64_t tx, int64_t block0, int lane, T scale, T* u) {
+  constexpr int kRounds = oct_mask_rounds<IT>(), kBlocks = 8 / kRounds;
+  const int bb = lane >> 3, j = lane & 7;
+  const int bytes = mask.kept * int(sizeof(IT));
+  const int n_active = int(g.gx - tx * 8 < 8 ? g.gx - tx * 8 : 8);
+  uint8_t* st = reinterpret_cast<uint8_t*>(region);
+  const uint8_t* lo = reinterpret_cast<const uint8_t*>(F);
+  const uint8_t* hi = lo + g.gz * g.gy * g.gx * bytes;
+  const uint32_t aside = kOctAside + uint32_t(lane) * 4u;
+  put_index<int32_t>(st, aside, 0u);
+#pragma unroll
+  for (int round = 0; round < kRounds; ++round) {
+    const uint8_t* src = lo + (block0 + round * kBlocks) * bytes;
+    const int count = n_active - round * kBlocks < kBlocks ? n_active - round * kBlocks : kBlocks;
+    if (count <= 0) break;                                       // uniform
+    stage_span<4>(lo, hi, src, count * bytes, st);
+    wave_lds_sync();
+    if (kRounds == 1 || bb / kBlocks == round) {
+      const int mine = bb - round * kBlocks < count ? bb - round * kBlocks : count - 1;     // past the end: stored nowhere
+      const uint32_t base = uint32_t(phase_of(src) + mine * bytes);
+#pragma unroll
+      for (int zq = 0; zq < 8; ++zq) {
+        uint4 places;
+        load_places<1>(mask.pos + zq * 64 + j * 8, &places);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[zq * 8 + e] = scale * T(get_index<IT>(st, masked_address<IT>(places, e, base, aside)));
+      }
+    }
+    wave_lds_sync();
+  }
+}
+
+template <int TF, typename XT, int KZ, int KY, int KX, bool kRagged, bool kStats, bool kTailX = false, bool kMasked = false>
 __global__ __launch_bounds__(kOctWaves * 64) void k_compress_oct8(FastGeom g, const XT* __restrict__ x,
                                                                   void* __restrict__ N, int8_t* __restrict__ F,
-                                                                  double* __restrict__ tile_sums) {
+                                                                  double* __restrict__ tile_sums, MaskArgs<kMasked> mask) {
   static_assert(KX == 4 || KX == 8, "a kept row is one or two dwords of int8");
   constexpr int KEPT = KZ * KY * KX;
   constexpr int PER16 = Unpack<float, XT>::n;     // elements per 16-byte piece: 8 (bfloat16) or 4 (FP32)
   constexpr int RV = 8 / PER16;                   // pieces per block row
-  __shared__ uint4 lds[kOctWaves][8 * 64];
+  __shared__ uint4 lds[kOctWaves][kMasked ? kOctMaskedSlots : 8 * 64];
   // a wave that is fetching its tile goes ahead of the waves that are busy transforming theirs
   __builtin_amdgcn_s_setprio(3);
   const int lane = threadIdx.x & 63;
@@ -232,6 +306,12 @@ __global__ __launch_bounds__(kOctWaves * 64) void k_compress_oct8(FastGeom g, co
 #pragma unroll
   for (int off = 1; off < 8; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, 64));     // the 8 rows of the block
   const float inv = m > 0.0f ? float(g.r) / m : 0.0f;
+  if constexpr (kMasked) {
+    const int64_t block0 = (bz * g.gy + by) * g.gx + tx * 8;
+    if (j == 0 && tx * 8 + bb < g.gx) store_float(N, g.ntype, block0 + bb, m);
+    oct_put_masked<int8_t, float>(g, mask, st, F, tx, block0, lane, u, inv);
+    return;
+  }
 
   // kept entries of this lane: z < KZ, x < KX when j < KY; staged in LDS at their position in the wave's span of F
   static_assert(8 * KEPT <= 8 * 64 * 16, "the staged F of a tile fits the exchange buffer");
@@ -367,11 +447,11 @@ __global__ __launch_bounds__(256) void k_decompress_oct8(FastGeom g, const void*
 // exchanges through LDS (the same slots and two half rounds as compress), then lane = (plane z, block b)
 // transforms back along y and x and stores its plane.  512 x 512 x 1024: FP32 0.458 -> 0.338 ms, bfloat16 0.395 -> 0.144 ms;
 // FP32 rows regrouped through LDS before they are stored: 0.338 -> 0.214 ms.
-template <int TF, typename XT, bool kTailX>
+template <int TF, typename XT, bool kTailX, bool kMasked = false>
 __global__ __launch_bounds__(kOctWaves * 64) void k_decompress_oct8_full(FastGeom g, const void* __restrict__ N,
                                                                          const int8_t* __restrict__ F,
-                                                                         XT* __restrict__ y) {
-  __shared__ uint4 lds[kOctWaves][8 * 64];
+                                                                         XT* __restrict__ y, MaskArgs<kMasked> mask) {
+  __shared__ uint4 lds[kOctWaves][kMasked ? kOctMaskedSlots : 8 * 64];
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
   if (!decode_tile<kOctWaves>(g, tx, by, bz)) return;
@@ -383,16 +463,21 @@ __global__ __launch_bounds__(kOctWaves * 64) void k_decompress_oct8_full(FastGeo
     const int bb = lane >> 3, j = lane & 7;
     // a block past the end of the row: decode the row's last block again; nothing of it is stored
     const int64_t blk = tx * 8 + bb < g.gx ? bb : g.gx - 1 - tx * 8;
-    const uint2* rows = reinterpret_cast<const uint2*>(F + (block0 + blk) * 512) + j;     // row (kz, j) at rows[kz * 8]
-    uint2 f[8];
+    if constexpr (kMasked) {
+      const float scale = load_float<float>(N, g.ntype, block0 + blk) / float(g.r);
+      oct_get_masked<int8_t, float>(g, mask, st, F, tx, block0, lane, scale, u);
+    } else {
+      const uint2* rows = reinterpret_cast<const uint2*>(F + (block0 + blk) * 512) + j;   // row (kz, j) at rows[kz * 8]
+      uint2 f[8];
 #pragma unroll
-    for (int kz = 0; kz < 8; ++kz) f[kz] = rows[kz * 8];
-    const float scale = load_float<float>(N, g.ntype, block0 + blk) / float(g.r);         // Algorithm 3: N F / r
+      for (int kz = 0; kz < 8; ++kz) f[kz] = rows[kz * 8];
+      const float scale = load_float<float>(N, g.ntype, block0 + blk) / float(g.r);       // Algorithm 3: N F / r
 #pragma unroll
-    for (int kz = 0; kz < 8; ++kz) {
-      const uint32_t w[2] = {f[kz].x, f[kz].y};
+      for (int kz = 0; kz < 8; ++kz) {
+        const uint32_t w[2] = {f[kz].x, f[kz].y};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) u[kz * 8 + e] = scale * float(IdxPack<int8_t>::get(w[e >> 2], e & 3));
+        for (int e = 0; e < 8; ++e) u[kz * 8 + e] = scale * float(IdxPack<int8_t>::get(w[e >> 2], e & 3));
+      }
     }
 #pragma unroll
     for (int xx = 0; xx < 8; ++xx) tf_inverse<TF, float, 8, 8, 8>(u + xx);
@@ -539,7 +624,7 @@ struct Oct8Kernel {
   template <bool kRagged, bool kStats, bool kTailX>
   static void launch(const FastGeom& g, dim3 grid, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     hipLaunchKernelGGL((k_compress_oct8<TF, XT, KZ, KY, KX, kRagged, kStats, kTailX>), grid, dim3(kOctWaves * 64), 0, s, g,
-                       static_cast<const XT*>(x), N, static_cast<int8_t*>(F), tile_sums);
+                       static_cast<const XT*>(x), N, static_cast<int8_t*>(F), tile_sums, MaskArgs<false>());
   }
   static int compress(FastGeom g, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     dim3 grid;
@@ -558,8 +643,8 @@ struct Oct8Kernel {
     const bool tail = g.X % 8 != 0;
     if constexpr (KZ == 8 && KY == 8 && KX == 8) {
       if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
-      if (tail) hipLaunchKernelGGL((k_decompress_oct8_full<TF, XT, true>), grid, dim3(kOctWaves * 64), 0, s, g, n, f, out);
-      else hipLaunchKernelGGL((k_decompress_oct8_full<TF, XT, false>), grid, dim3(kOctWaves * 64), 0, s, g, n, f, out);
+      if (tail) hipLaunchKernelGGL((k_decompress_oct8_full<TF, XT, true>), grid, dim3(kOctWaves * 64), 0, s, g, n, f, out, MaskArgs<false>());
+      else hipLaunchKernelGGL((k_decompress_oct8_full<TF, XT, false>), grid, dim3(kOctWaves * 64), 0, s, g, n, f, out, MaskArgs<false>());
     } else if (g.gx >= 48) {        // at least three quarters of the lanes of a 64-block tile busy
       if (!tile_grid(g, 64, 1, &grid)) return 0;
       if (tail) hipLaunchKernelGGL((k_decompress_oct8_rows<TF, XT, KZ, KY, KX, true>), grid, dim3(512), 0, s, g, n, f, out);
@@ -603,15 +688,16 @@ __device__ __forceinline__ void load_words(const void* src, uint32_t* w) {
   }
 }
 
-template <int TF, typename XT, typename IT, bool kRagged, bool kStats, bool kTailX>
+template <int TF, typename XT, typename IT, bool kRagged, bool kStats, bool kTailX, bool kMasked = false>
 __global__ __launch_bounds__(kOctWaves * 64) void k_compress_oct8_wide(FastGeom g, const XT* __restrict__ x,
                                                                        void* __restrict__ N, IT* __restrict__ F,
-                                                                       double* __restrict__ tile_sums) {
+                                                                       double* __restrict__ tile_sums,
+                                                                       MaskArgs<kMasked> mask) {
   using Slot = ExchangeSlot<double>;
   constexpr int PER16 = Unpack<double, XT>::n;     // elements per 16-byte piece: 4 (FP32) or 2 (FP64)
   constexpr int RV = 8 / PER16;                    // pieces per block row
   constexpr int PER = IdxPack<IT>::per, RW = 8 / PER;       // indices per dword, dwords per row of eight indices
-  __shared__ uint4 lds[kOctWaves][8 * 64];
+  __shared__ uint4 lds[kOctWaves][kMasked ? kOctMaskedSlots : 8 * 64];
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
   if (!decode_tile<kOctWaves>(g, tx, by, bz)) return;
@@ -705,6 +791,11 @@ __global__ __launch_bounds__(kOctWaves * 64) void k_compress_oct8_wide(FastGeom 
   const double inv = m > 0.0 ? g.r / m : 0.0;
   const int64_t block0 = (bz * g.gy + by) * g.gx + tx * 8;
   const bool inside = tx * 8 + bb < g.gx;
+  if constexpr (kMasked) {
+    if (inside && j == 0) store_float(N, g.ntype, block0 + bb, m);
+    oct_put_masked<IT, double>(g, mask, st, F, tx, block0, lane, u, inv);
+    return;
+  }
   uint32_t w[8 * RW];
 #pragma unroll
   for (int zq = 0; zq < 8; ++zq)
@@ -758,13 +849,13 @@ __device__ __forceinline__ void oct_store_row_wide(const FastGeom& g, XT* row, i
   }
 }
 
-template <int TF, typename XT, typename IT, bool kTailX>
+template <int TF, typename XT, typename IT, bool kTailX, bool kMasked = false>
 __global__ __launch_bounds__(kOctWaves * 64) void k_decompress_oct8_wide(FastGeom g, const void* __restrict__ N,
                                                                          const IT* __restrict__ F,
-                                                                         XT* __restrict__ y) {
+                                                                         XT* __restrict__ y, MaskArgs<kMasked> mask) {
   using Slot = ExchangeSlot<double>;
   constexpr int PER = IdxPack<IT>::per, RW = 8 / PER;
-  __shared__ uint4 lds[kOctWaves][8 * 64];
+  __shared__ uint4 lds[kOctWaves][kMasked ? kOctMaskedSlots : 8 * 64];
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
   if (!decode_tile<kOctWaves>(g, tx, by, bz)) return;
@@ -777,15 +868,20 @@ __global__ __launch_bounds__(kOctWaves * 64) void k_decompress_oct8_wide(FastGeo
   {
     // a block past the end of the row: decode the row's last block again; nothing of it is stored
     const int64_t blk = tx * 8 + bb < g.gx ? bb : g.gx - 1 - tx * 8;
-    const IT* rows = F + (block0 + blk) * 512 + j * 8;
-    uint32_t fw[8][RW];
+    if constexpr (kMasked) {
+      const double scale = load_float<double>(N, g.ntype, block0 + blk) / g.r;
+      oct_get_masked<IT, double>(g, mask, st, F, tx, block0, lane, scale, u);
+    } else {
+      const IT* rows = F + (block0 + blk) * 512 + j * 8;
+      uint32_t fw[8][RW];
 #pragma unroll
-    for (int kz = 0; kz < 8; ++kz) load_words<RW>(rows + kz * 64, fw[kz]);
-    const double scale = load_float<double>(N, g.ntype, block0 + blk) / g.r;          // Algorithm 3: N F / r
+      for (int kz = 0; kz < 8; ++kz) load_words<RW>(rows + kz * 64, fw[kz]);
+      const double scale = load_float<double>(N, g.ntype, block0 + blk) / g.r;        // Algorithm 3: N F / r
 #pragma unroll
-    for (int kz = 0; kz < 8; ++kz) {
+      for (int kz = 0; kz < 8; ++kz) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) u[kz * 8 + e] = scale * double(IdxPack<IT>::get(fw[kz][e / PER], e % PER));
+        for (int e = 0; e < 8; ++e) u[kz * 8 + e] = scale * double(IdxPack<IT>::get(fw[kz][e / PER], e % PER));
+      }
     }
 #pragma unroll
     for (int xx = 0; xx < 8; ++xx) tf_inverse<TF, double, 8, 8, 8>(u + xx);
@@ -836,7 +932,7 @@ struct Oct8WideKernel {
   template <bool kRagged, bool kStats, bool kTailX>
   static void launch(const FastGeom& g, dim3 grid, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     hipLaunchKernelGGL((k_compress_oct8_wide<TF, XT, IT, kRagged, kStats, kTailX>), grid, dim3(kOctWaves * 64), 0, s, g,
-                       static_cast<const XT*>(x), N, static_cast<IT*>(F), tile_sums);
+                       static_cast<const XT*>(x), N, static_cast<IT*>(F), tile_sums, MaskArgs<false>());
   }
   static int compress(FastGeom g, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     dim3 grid;
@@ -852,10 +948,84 @@ struct Oct8WideKernel {
     if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
     if (g.X % 8)
       hipLaunchKernelGGL((k_decompress_oct8_wide<TF, XT, IT, true>), grid, dim3(kOctWaves * 64), 0, s, g, N,
-                         static_cast<const IT*>(F), static_cast<XT*>(y));
+                         static_cast<const IT*>(F), static_cast<XT*>(y), MaskArgs<false>());
     else
       hipLaunchKernelGGL((k_decompress_oct8_wide<TF, XT, IT, false>), grid, dim3(kOctWaves * 64), 0, s, g, N,
-                         static_cast<const IT*>(F), static_cast<XT*>(y));
+                         static_cast<const IT*>(F), static_cast<XT*>(y), MaskArgs<false>());
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+};
+
+// Any mask, on the kernels that keep everything
+inline MaskArgs<true> oct_mask_args(const pbz_codec* c, const uint16_t* pos) {
+  MaskArgs<true> m;
+  m.pos = pos;
+  m.keep = 0;
+  m.kept = c->kept;
+  return m;
+}
+template <typename K> struct OctMasked;
+template <int TF, typename XT>
+struct OctMasked<Oct8Kernel<TF, XT, 8, 8, 8>> {
+  static bool matches(const pbz_codec* c, Folded f, int xtype) {
+    f.kz = f.ky = f.kx = 8;
+    return Oct8Kernel<TF, XT, 8, 8, 8>::matches(c, f, xtype);
+  }
+  template <bool kTailX>
+  static void launch(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* x, void* N, void* F,
+                     hipStream_t s) {
+    hipLaunchKernelGGL((k_compress_oct8<TF, XT, 8, 8, 8, true, false, kTailX, true>), grid, dim3(kOctWaves * 64), 0, s, g,
+                       static_cast<const XT*>(x), N, static_cast<int8_t*>(F), nullptr, oct_mask_args(c, pos));
+  }
+  template <bool kTailX>
+  static void launch_inverse(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* N,
+                             const void* F, void* y, hipStream_t s) {
+    hipLaunchKernelGGL((k_decompress_oct8_full<TF, XT, kTailX, true>), grid, dim3(kOctWaves * 64), 0, s, g, N,
+                       static_cast<const int8_t*>(F), static_cast<XT*>(y), oct_mask_args(c, pos));
+  }
+  static int compress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* x, void* N, void* F, hipStream_t s) {
+    dim3 grid;
+    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    g.X % 8 ? launch<true>(c, g, grid, pos, x, N, F, s) : launch<false>(c, g, grid, pos, x, N, F, s);
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+  static int decompress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* N, const void* F, void* y,
+                        hipStream_t s) {
+    dim3 grid;
+    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    g.X % 8 ? launch_inverse<true>(c, g, grid, pos, N, F, y, s) : launch_inverse<false>(c, g, grid, pos, N, F, y, s);
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+};
+template <int TF, typename XT, typename IT>
+struct OctMasked<Oct8WideKernel<TF, XT, IT>> {
+  static bool matches(const pbz_codec* c, Folded f, int xtype) {
+    f.kz = f.ky = f.kx = 8;
+    return Oct8WideKernel<TF, XT, IT>::matches(c, f, xtype);
+  }
+  template <bool kTailX>
+  static void launch(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* x, void* N, void* F,
+                     hipStream_t s) {
+    hipLaunchKernelGGL((k_compress_oct8_wide<TF, XT, IT, true, false, kTailX, true>), grid, dim3(kOctWaves * 64), 0, s, g,
+                       static_cast<const XT*>(x), N, static_cast<IT*>(F), nullptr, oct_mask_args(c, pos));
+  }
+  template <bool kTailX>
+  static void launch_inverse(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* N,
+                             const void* F, void* y, hipStream_t s) {
+    hipLaunchKernelGGL((k_decompress_oct8_wide<TF, XT, IT, kTailX, true>), grid, dim3(kOctWaves * 64), 0, s, g, N,
+                       static_cast<const IT*>(F), static_cast<XT*>(y), oct_mask_args(c, pos));
+  }
+  static int compress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* x, void* N, void* F, hipStream_t s) {
+    dim3 grid;
+    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    g.X % 8 ? launch<true>(c, g, grid, pos, x, N, F, s) : launch<false>(c, g, grid, pos, x, N, F, s);
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+  static int decompress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* N, const void* F, void* y,
+                        hipStream_t s) {
+    dim3 grid;
+    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    g.X % 8 ? launch_inverse<true>(c, g, grid, pos, N, F, y, s) : launch_inverse<false>(c, g, grid, pos, N, F, y, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
   }
 };
@@ -889,9 +1059,15 @@ template <int TF> using Oct8_f64_i32 = Oct8WideKernel<TF, double, int32_t>;
   X(Oct8_f64_i16<TF>, "oct8_f64_8x8x8_i16" SUFFIX) \
   X(Oct8_f64_i32<TF>, "oct8_f64_8x8x8_i32" SUFFIX)
 
+#define PBZ_MASKED_ROWS(X, TF) \
+  X(OctMasked<Oct8_full<TF>>) X(OctMasked<Oct8_f32_full<TF>>) X(OctMasked<Oct8_f16_full<TF>>) \
+  X(OctMasked<Oct8_f64w32_full<TF>>) X(OctMasked<Oct8_f32_i16<TF>>) X(OctMasked<Oct8_f32_i32<TF>>) \
+  X(OctMasked<Oct8_f64_i8<TF>>) X(OctMasked<Oct8_f64_i16<TF>>) X(OctMasked<Oct8_f64_i32<TF>>)
+
 }  // namespace
 
 PBZ_DEFINE_FAST_FAMILY(oct8, PBZ_ROWS)
+PBZ_DEFINE_MASKED_FAMILY(oct8, PBZ_MASKED_ROWS)
 
 }  // namespace fast
 }  // namespace pbz

@@ -23,9 +23,15 @@ struct QuadMap {
   static __device__ __forceinline__ int plane_of(int p) { return BZ == 1 ? 0 : (p >> 2); }
 };
 
-template <int TF, typename T, typename IT, typename XT, int BZ, bool kRagged, bool kStats, bool kTailX = false>
+// Any mask: the exchange buffer holds the span of a wave's blocks (16 of 255 kept indices or 4 of 1023, 32 bits each:
+// 16380 bytes with their phase) and a dword per lane for the pruned ones.
+constexpr uint32_t kQuadAside = 16 * kQuadRow * 16 - 256;
+
+template <int TF, typename T, typename IT, typename XT, int BZ, bool kRagged, bool kStats, bool kTailX = false,
+          bool kMasked = false>
 __global__ __launch_bounds__(128) void k_compress_quad16(FastGeom g, const XT* __restrict__ x, void* __restrict__ N,
-                                                         IT* __restrict__ F, double* __restrict__ tile_sums) {
+                                                         IT* __restrict__ F, double* __restrict__ tile_sums,
+                                                         MaskArgs<kMasked> mask) {
   using Q4 = Quad4<XT>;
   using Slot = ExchangeSlot<T>;
   constexpr int PER = IdxPack<IT>::per;            // indices per dword
@@ -119,6 +125,13 @@ __global__ __launch_bounds__(128) void k_compress_quad16(FastGeom g, const XT* _
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) m4 = fmax(m4, __shfl_xor(m4, off, 64));
   }
+  uint4 places[2];                                     // masks: where the lane's row goes (BZ = 1: one row for all j)
+  uint8_t* span = nullptr;                             // of F, in memory
+  if constexpr (kMasked) {
+    wave_lds_sync();                                   // the exchange's last reads precede the span's writes
+    span = reinterpret_cast<uint8_t*>(F) + block0 * mask.kept * int(sizeof(IT));
+    if constexpr (BZ == 1) load_places<2>(mask.pos + yrow * 16, places);
+  }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     T m = m4;
@@ -129,6 +142,18 @@ __global__ __launch_bounds__(128) void k_compress_quad16(FastGeom g, const XT* _
       for (int off = 1; off < 16; off <<= 1) m = fmax(m, __shfl_xor(m, off, 64));   // the 16 rows of the block
     }
     const T inv = m > T(0) ? T(g.r) / m : T(0);
+    if constexpr (kMasked) {
+      const int blk = Map::block_of(4 * j + bsub);
+      if constexpr (BZ == 4) load_places<2>(mask.pos + (j * 16 + yrow) * 16, places);
+      const uint32_t base = uint32_t(phase_of(span) + blk * mask.kept * int(sizeof(IT)));
+      const uint32_t aside = kQuadAside + uint32_t(lane) * 4u;
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        put_index<IT>(reinterpret_cast<uint8_t*>(st), masked_address<IT>(places[e >> 3], e & 7, base, aside),
+                      bin_bits(u[j * 16 + e], inv));
+      if (yrow == 0 && (BZ == 1 || j == 0) && tx * BPW + blk < g.gx) store_float(N, g.ntype, block0 + blk, m);
+      continue;
+    }
     uint32_t w[ROWW];
 #pragma unroll
     for (int k = 0; k < ROWW; ++k) {
@@ -155,6 +180,11 @@ __global__ __launch_bounds__(128) void k_compress_quad16(FastGeom g, const XT* _
       }
     }
   }
+  if constexpr (kMasked) {
+    wave_lds_sync();
+    const int n_active = int(g.gx - tx * BPW < BPW ? g.gx - tx * BPW : BPW);
+    unstage_span(reinterpret_cast<const uint8_t*>(st), span, n_active * mask.kept * int(sizeof(IT)));
+  }
   if constexpr (kStats) {
     const double K = tile_pilot(firsts[0]);            // lane 0, j = 0: the tile's first block, always inside the array
     double sq = 0.0, d = 0.0, count = 0.0;
@@ -169,9 +199,10 @@ __global__ __launch_bounds__(128) void k_compress_quad16(FastGeom g, const XT* _
   }
 }
 
-template <int TF, typename T, typename IT, typename XT, int BZ, bool kTailX = false>
+template <int TF, typename T, typename IT, typename XT, int BZ, bool kTailX = false, bool kMasked = false>
 __global__ __launch_bounds__(128) void k_decompress_quad16(FastGeom g, const void* __restrict__ N,
-                                                           const IT* __restrict__ F, XT* __restrict__ y) {
+                                                           const IT* __restrict__ F, XT* __restrict__ y,
+                                                           MaskArgs<kMasked> mask) {
   using Q4 = Quad4<XT>;
   using Map = QuadMap<BZ>;
   using Slot = ExchangeSlot<T>;
@@ -195,24 +226,50 @@ __global__ __launch_bounds__(128) void k_decompress_quad16(FastGeom g, const voi
       int64_t blk = Map::block_of(4 * j + bsub);
       if (tx * BPW + blk >= g.gx) blk = g.gx - 1 - tx * BPW;   // past the end: decode the last block again, stored nowhere
       blocks[j] = block0 + blk;
-      const int piece = BZ == 1 ? yrow : j * 16 + yrow;
-      const uint4* src = reinterpret_cast<const uint4*>(F + blocks[j] * (BZ * 256)) + piece * (ROWW / 4);
+      if constexpr (!kMasked) {
+        const int piece = BZ == 1 ? yrow : j * 16 + yrow;
+        const uint4* src = reinterpret_cast<const uint4*>(F + blocks[j] * (BZ * 256)) + piece * (ROWW / 4);
 #pragma unroll
-      for (int k = 0; k < ROWW / 4; ++k) fs[j][k] = src[k];
+        for (int k = 0; k < ROWW / 4; ++k) fs[j][k] = src[k];
+      }
     }
     load_N_many<4, T>(N, g.ntype, blocks, ns);
+    if constexpr (kMasked) {
+      const int bytes = mask.kept * int(sizeof(IT));
+      const uint8_t* lo = reinterpret_cast<const uint8_t*>(F);
+      const uint8_t* span = lo + block0 * bytes;
+      uint8_t* st8 = reinterpret_cast<uint8_t*>(st);
+      const uint32_t aside = kQuadAside + uint32_t(lane) * 4u;
+      put_index<int32_t>(st8, aside, 0u);
+      const int n_active = int(g.gx - tx * BPW < BPW ? g.gx - tx * BPW : BPW);
+      stage_span<4>(lo, lo + g.gz * g.gy * g.gx * bytes, span, n_active * bytes, st8);
+      uint4 places[2];
+      if constexpr (BZ == 1) load_places<2>(mask.pos + yrow * 16, places);
+      wave_lds_sync();
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const T scale = ns[j] / T(g.r);
+      for (int j = 0; j < 4; ++j) {
+        if constexpr (BZ == 4) load_places<2>(mask.pos + (j * 16 + yrow) * 16, places);
+        const T scale = ns[j] / T(g.r);
+        const uint32_t base = uint32_t(phase_of(span) + int(blocks[j] - block0) * bytes);
 #pragma unroll
-      for (int k = 0; k < ROWW / 4; ++k) {
-        const uint4 f = fs[j][k];
-        const uint32_t w[4] = {f.x, f.y, f.z, f.w};
+        for (int e = 0; e < 16; ++e)
+          u[j * 16 + e] = scale * T(get_index<IT>(st8, masked_address<IT>(places[e >> 3], e & 7, base, aside)));
+      }
+      wave_lds_sync();                                         // the exchange below writes the same LDS
+    } else {
 #pragma unroll
-        for (int d = 0; d < 4; ++d)
+      for (int j = 0; j < 4; ++j) {
+        const T scale = ns[j] / T(g.r);
 #pragma unroll
-          for (int e = 0; e < PER; ++e)
-            u[j * 16 + (4 * k + d) * PER + e] = scale * T(IdxPack<IT>::get(w[d], e));
+        for (int k = 0; k < ROWW / 4; ++k) {
+          const uint4 f = fs[j][k];
+          const uint32_t w[4] = {f.x, f.y, f.z, f.w};
+#pragma unroll
+          for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int e = 0; e < PER; ++e)
+              u[j * 16 + (4 * k + d) * PER + e] = scale * T(IdxPack<IT>::get(w[d], e));
+        }
       }
     }
     if constexpr (BZ == 4) {
@@ -286,7 +343,7 @@ struct Quad16Kernel {
   template <bool kRagged, bool kStats, bool kTailX>
   static void launch(const FastGeom& g, dim3 grid, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     hipLaunchKernelGGL((k_compress_quad16<TF, T, IT, XT, BZ, kRagged, kStats, kTailX>), grid, dim3(128), 0, s, g,
-                       static_cast<const XT*>(x), N, static_cast<IT*>(F), tile_sums);
+                       static_cast<const XT*>(x), N, static_cast<IT*>(F), tile_sums, MaskArgs<false>());
   }
   static int compress(FastGeom g, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     dim3 grid;
@@ -302,10 +359,53 @@ struct Quad16Kernel {
     if (!tile_grid(g, kBlocksPerWave, 2, &grid)) return 0;
     if (g.X % 16)
       hipLaunchKernelGGL((k_decompress_quad16<TF, T, IT, XT, BZ, true>), grid, dim3(128), 0, s, g, N,
-                         static_cast<const IT*>(F), static_cast<XT*>(y));
+                         static_cast<const IT*>(F), static_cast<XT*>(y), MaskArgs<false>());
     else
       hipLaunchKernelGGL((k_decompress_quad16<TF, T, IT, XT, BZ, false>), grid, dim3(128), 0, s, g, N,
-                         static_cast<const IT*>(F), static_cast<XT*>(y));
+                         static_cast<const IT*>(F), static_cast<XT*>(y), MaskArgs<false>());
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+};
+
+// Any mask, on the same kernels
+template <typename K> struct QuadMasked;
+template <int TF, typename T, typename IT, typename XT, int BZ>
+struct QuadMasked<Quad16Kernel<TF, T, IT, XT, BZ>> {
+  using Base = Quad16Kernel<TF, T, IT, XT, BZ>;
+  static bool matches(const pbz_codec* c, Folded f, int xtype) {
+    f.kz = BZ; f.ky = f.kx = 16;
+    return Base::matches(c, f, xtype);
+  }
+  static MaskArgs<true> args(const pbz_codec* c, const uint16_t* pos) {
+    MaskArgs<true> m;
+    m.pos = pos;
+    m.keep = 0;
+    m.kept = c->kept;
+    return m;
+  }
+  template <bool kTailX>
+  static void launch(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* x, void* N, void* F,
+                     hipStream_t s) {
+    hipLaunchKernelGGL((k_compress_quad16<TF, T, IT, XT, BZ, true, false, kTailX, true>), grid, dim3(128), 0, s, g,
+                       static_cast<const XT*>(x), N, static_cast<IT*>(F), nullptr, args(c, pos));
+  }
+  template <bool kTailX>
+  static void launch_inverse(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* N,
+                             const void* F, void* y, hipStream_t s) {
+    hipLaunchKernelGGL((k_decompress_quad16<TF, T, IT, XT, BZ, kTailX, true>), grid, dim3(128), 0, s, g, N,
+                       static_cast<const IT*>(F), static_cast<XT*>(y), args(c, pos));
+  }
+  static int compress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* x, void* N, void* F, hipStream_t s) {
+    dim3 grid;
+    if (!tile_grid(g, Base::kBlocksPerWave, 2, &grid)) return 0;
+    g.X % 16 ? launch<true>(c, g, grid, pos, x, N, F, s) : launch<false>(c, g, grid, pos, x, N, F, s);
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+  static int decompress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* N, const void* F, void* y,
+                        hipStream_t s) {
+    dim3 grid;
+    if (!tile_grid(g, Base::kBlocksPerWave, 2, &grid)) return 0;
+    g.X % 16 ? launch_inverse<true>(c, g, grid, pos, N, F, y, s) : launch_inverse<false>(c, g, grid, pos, N, F, y, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
   }
 };
@@ -329,9 +429,29 @@ struct Quad16Kernel {
   X(Quad16Kernel<TF COMMA float COMMA int8_t COMMA double COMMA 1>, "quad16_f64_w32_16x16_i8" SUFFIX) \
   X(Quad16Kernel<TF COMMA float COMMA int8_t COMMA double COMMA 4>, "quad16_f64_w32_4x16x16_i8" SUFFIX)
 
+#define PBZ_MASKED_ROWS(X, TF) \
+  X(QuadMasked<Quad16Kernel<TF COMMA float COMMA int8_t COMMA float COMMA 1>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA float COMMA int8_t COMMA float COMMA 4>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA float COMMA int8_t COMMA f16_t COMMA 1>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA float COMMA int8_t COMMA bf16_t COMMA 1>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA float COMMA int8_t COMMA f16_t COMMA 4>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA double COMMA int16_t COMMA float COMMA 1>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA double COMMA int16_t COMMA float COMMA 4>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA double COMMA int32_t COMMA float COMMA 1>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA double COMMA int32_t COMMA float COMMA 4>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA double COMMA int8_t COMMA double COMMA 1>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA double COMMA int16_t COMMA double COMMA 1>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA double COMMA int32_t COMMA double COMMA 1>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA double COMMA int16_t COMMA double COMMA 4>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA double COMMA int8_t COMMA double COMMA 4>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA double COMMA int32_t COMMA double COMMA 4>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA float COMMA int8_t COMMA double COMMA 1>>) \
+  X(QuadMasked<Quad16Kernel<TF COMMA float COMMA int8_t COMMA double COMMA 4>>)
+
 }  // namespace
 
 PBZ_DEFINE_FAST_FAMILY(quad16, PBZ_ROWS)
+PBZ_DEFINE_MASKED_FAMILY(quad16, PBZ_MASKED_ROWS)
 
 }  // namespace fast
 }  // namespace pbz

@@ -13,6 +13,7 @@
 namespace pbz {
 
 constexpr int kMaxDevices = 16;
+constexpr uint16_t kPruned = 0x7fff;        // beyond every position, also as a byte offset after any LDS base
 constexpr int kReducePartialSlots = 8;      // doubles per workgroup partial
 constexpr int kReduceMaxGroups = 4096;      // upper bound on reduction workgroups
 constexpr size_t kWorkspaceBytes = size_t(kReduceMaxGroups) * kReducePartialSlots * sizeof(double);
@@ -23,6 +24,7 @@ struct DeviceTables {
   double* H = nullptr;          // concatenated forward matrices H_d[m][q], row-major, one per dimension
   int32_t* kept_pos = nullptr;  // [vol] position in F of intra-block entry j, or -1 when pruned
   int32_t* kept_list = nullptr; // [kept] intra-block entry stored at position pos of F (the inverse of kept_pos)
+  uint16_t* places = nullptr;   // [vol] kept_pos in 16 bits (a block has at most 4096 entries), kPruned when pruned
 };
 
 }  // namespace pbz
@@ -94,6 +96,12 @@ int try_compress_fast(const pbz_codec* c, const Geom& g, const void* x, int xtyp
 int64_t fast_compress_tiles(const pbz_codec* c, const Geom& g, int xtype);   // 0: no specialised kernel covers it
 int try_decompress_fast(const pbz_codec* c, const Geom& g, const void* N, const void* F, void* y, int ytype,
                         hipStream_t s, bool dry_run, const char** name);
+
+// the same families for settings that only differ from theirs in the mask; `places`: DeviceTables::places
+int try_compress_masked(const pbz_codec* c, const Geom& g, const uint16_t* places, const void* x, int xtype, void* N, void* F,
+                        hipStream_t s);
+int try_decompress_masked(const pbz_codec* c, const Geom& g, const uint16_t* places, const void* N, const void* F, void* y,
+                          int ytype, hipStream_t s);
 
 // element-wise compressed-space operations
 int launch_negate(const pbz_codec* c, int64_t n_blocks, const void* Fin, void* Fout, hipStream_t s);

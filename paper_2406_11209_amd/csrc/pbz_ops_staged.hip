@@ -18,6 +18,7 @@
 // Tried and not kept: dword accesses of LDS at any byte instead of shifting two aligned words (add 99 -> 140 us), six
 // waves per SIMD (80 registers, 128 bytes of spills: 106 us), spans of 1 or 4 KiB per wave and operand (15-35 % slower).
 #include "pbz_ops_common.h"
+#include "pbz_span.h"
 
 namespace pbz {
 namespace ops {
@@ -37,59 +38,6 @@ struct Stage {
   int blocks;       // blocks per wave and tile, a multiple of the blocks per round (64 lanes over the team)
   int region;       // bytes of an LDS region: a span at any phase and one word more, a multiple of 16
 };
-
-__device__ __forceinline__ void wave_lds_sync() {   // orders one wave's LDS accesses; no workgroup barrier involved
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ int phase_of(const void* p) { return int(reinterpret_cast<uintptr_t>(p) & 15u); }
-
-// [p, p + len) -> LDS, at the phase of p.  Only 16-byte pieces that lie inside the operand [lo, hi) are read as such
-// (they may hold bytes of neighbouring blocks, which nobody uses); the bytes of the others are read one by one.
-__device__ __forceinline__ void stage_span(const uint8_t* lo, const uint8_t* hi, const uint8_t* p, int len, uint8_t* lds) {
-  constexpr int kBatch = 2;                          // 16-byte loads in flight per lane and operand
-  const int lane = threadIdx.x & 63;
-  const int a = phase_of(p);
-  const uint8_t* base = p - a;
-  const int pieces = (a + len + 15) >> 4;
-  const int first = base < lo ? 1 : 0;
-  const int last = base + 16 * int64_t(pieces) > hi ? pieces - 1 : pieces;
-  for (int i0 = first; i0 < last; i0 += 64 * kBatch) {
-    uint4 v[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int i = i0 + u * 64 + lane;
-      v[u] = reinterpret_cast<const uint4*>(base)[i < last ? i : last - 1];
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int i = i0 + u * 64 + lane;
-      if (i < last) reinterpret_cast<uint4*>(lds)[i] = v[u];
-    }
-  }
-  if (first != 0 && lane < 16 - a && lane < len) lds[a + lane] = p[lane];
-  if (last < pieces) {
-    const int i = 16 * last + lane;
-    if (lane < 16 && i >= a && i < a + len) lds[i] = base[i];
-  }
-}
-
-// LDS -> [p, p + len), from the phase of p; nothing outside is written
-__device__ __forceinline__ void unstage_span(const uint8_t* lds, uint8_t* p, int len) {
-  const int lane = threadIdx.x & 63;
-  const int a = phase_of(p);
-  uint8_t* base = p - a;
-  const int first = a != 0 ? 1 : 0, last = (a + len) >> 4;
-  for (int i = first + lane; i < last; i += 64) reinterpret_cast<uint4*>(base)[i] = reinterpret_cast<const uint4*>(lds)[i];
-  if (a != 0) {
-    const int i = a + lane;
-    if (i < 16 && i < a + len) base[i] = lds[i];
-  }
-  const int i = 16 * last + lane;
-  if (i >= a && i < a + len) base[i] = lds[i];
-}
 
 // N of `count` (at most kMaxBlocksPerWave) blocks from k0 on, widened: requested, then put away
 template <int kNType>
@@ -196,8 +144,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const
     StagedN<kNType> n1, n2;
     n1.request(N1, k0, count, n_f16 != 0);
     if (kTwo) n2.request(N2, k0, count, n_f16 != 0);
-    stage_span(F1, a_end, F1 + at, len, sa);
-    if (kTwo) stage_span(F2, b_end, F2 + at, len, sb);
+    stage_span<2>(F1, a_end, F1 + at, len, sa);
+    if (kTwo) stage_span<2>(F2, b_end, F2 + at, len, sb);
     n1.put(na, count);
     if (kTwo) n2.put(nb, count);
     wave_lds_sync();
@@ -291,8 +239,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_blockwise_staged(Stage st, c
     StagedN<kNType> n1, n2;
     n1.request(N1, k0, count, n_f16 != 0);
     if (kTwo) n2.request(N2, k0, count, n_f16 != 0);
-    stage_span(F1, a_end, F1 + at, count * st.bpb, sa);
-    if (kTwo) stage_span(F2, b_end, F2 + at, count * st.bpb, sb);
+    stage_span<2>(F1, a_end, F1 + at, count * st.bpb, sa);
+    if (kTwo) stage_span<2>(F2, b_end, F2 + at, count * st.bpb, sb);
     n1.put(na, count);
     if (kTwo) n2.put(nb, count);
     wave_lds_sync();
@@ -348,8 +296,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
     StagedN<kNType> n1, n2;
     n1.request(N1, seg0 + k0, count, f16);
     if (kTwo) n2.request(N2, seg0 + k0, count, f16);
-    stage_span(F1, a_end, F1 + at, count * st.bpb, sa);
-    if (kTwo) stage_span(F2, b_end, F2 + at, count * st.bpb, sb);
+    stage_span<2>(F1, a_end, F1 + at, count * st.bpb, sa);
+    if (kTwo) stage_span<2>(F2, b_end, F2 + at, count * st.bpb, sb);
     n1.put(na, count);
     if (kTwo) n2.put(nb, count);
     wave_lds_sync();

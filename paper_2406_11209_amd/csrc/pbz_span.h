@@ -1,0 +1,57 @@
+// A span of F (a run of whole blocks, starting at any element) between memory and a wave's own LDS region, in aligned
+// 16-byte pieces.  The region holds the span at the phase (address modulo 16) it has in memory.
+#pragma once
+
+#include "pbz_device.h"
+
+namespace pbz {
+
+__device__ __forceinline__ int phase_of(const void* p) { return int(reinterpret_cast<uintptr_t>(p) & 15u); }
+
+// [p, p + len) -> LDS, at the phase of p.  Only 16-byte pieces that lie inside the operand [lo, hi) are read as such
+// (they may hold bytes of neighbouring blocks, which nobody uses); the bytes of the others are read one by one.
+// kBatch: 16-byte loads in flight per lane.
+template <int kBatch>
+__device__ __forceinline__ void stage_span(const uint8_t* lo, const uint8_t* hi, const uint8_t* p, int len, uint8_t* lds) {
+  const int lane = threadIdx.x & 63;
+  const int a = phase_of(p);
+  const uint8_t* base = p - a;
+  const int pieces = (a + len + 15) >> 4;
+  const int first = base < lo ? 1 : 0;
+  const int last = base + 16 * int64_t(pieces) > hi ? pieces - 1 : pieces;
+  for (int i0 = first; i0 < last; i0 += 64 * kBatch) {
+    uint4 v[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = i0 + u * 64 + lane;
+      v[u] = reinterpret_cast<const uint4*>(base)[i < last ? i : last - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = i0 + u * 64 + lane;
+      if (i < last) reinterpret_cast<uint4*>(lds)[i] = v[u];
+    }
+  }
+  if (first != 0 && lane < 16 - a && lane < len) lds[a + lane] = p[lane];
+  if (last < pieces) {
+    const int i = 16 * last + lane;
+    if (lane < 16 && i >= a && i < a + len) lds[i] = base[i];
+  }
+}
+
+// LDS -> [p, p + len), from the phase of p; nothing outside is written
+__device__ __forceinline__ void unstage_span(const uint8_t* lds, uint8_t* p, int len) {
+  const int lane = threadIdx.x & 63;
+  const int a = phase_of(p);
+  uint8_t* base = p - a;
+  const int first = a != 0 ? 1 : 0, last = (a + len) >> 4;
+  for (int i = first + lane; i < last; i += 64) reinterpret_cast<uint4*>(base)[i] = reinterpret_cast<const uint4*>(lds)[i];
+  if (a != 0) {
+    const int i = a + lane;
+    if (i < 16 && i < a + len) base[i] = lds[i];
+  }
+  const int i = 16 * last + lane;
+  if (i >= a && i < a + len) base[i] = lds[i];
+}
+
+}  // namespace pbz

@@ -77,12 +77,6 @@ size_t carve(void* base, int64_t n, Workspace* w) {
   return off;
 }
 
-__device__ __forceinline__ void wave_lds_sync() {   // orders one wave's LDS accesses; no workgroup barrier involved
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // doubles <-> unsigned keys with the same order (negative values: all bits flipped; others: sign bit set)
 __device__ __forceinline__ uint64_t key_of(double v) {
   const uint64_t u = uint64_t(__double_as_longlong(v));
