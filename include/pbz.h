@@ -287,7 +287,7 @@ int pbz_blockwise_covariance(const pbz_codec* codec, int64_t n_blocks, const voi
  * through softmax unless it already sums to one (taken as |sum - 1| <= 1e-9), are sorted, and
  * (sum |P_A - P_B|^p / n_blocks)^(1/p) goes to out (device, one FP64).  The power sum is scaled by its largest
  * term, which changes nothing in exact arithmetic and keeps the orders the paper uses (p = 68 .. 80) from
- * underflowing.  All work (means, reductions, an 8-bit-digit radix sort of both sequences, power mean) is enqueued
+ * underflowing.  All work (means, reductions, a sort of both sequences, power mean) is enqueued
  * on `stream`; nothing is read back to the host.
  *   p           order, finite and >= 1 (PBZ_ERR_SCALAR otherwise).
  *   workspace   device, 16-byte aligned, at least the bytes pbz_approximate_wasserstein_workspace reports for

@@ -3,12 +3,12 @@
 // differences of the two sorted sequences.
 //
 // Everything stays on the device and on the caller's stream:
-//   1. block means of both operands (the block-wise mean kernel) into the workspace,
-//   2. their sum and maximum, then sum of exp(x - max) (two-stage reductions; a one-workgroup kernel turns the
-//      partial sums into the parameters of the softmax and the decision whether to apply it),
-//   3. the raw means are sorted (softmax is increasing, so it commutes with sorting) by a least-significant-digit
-//      radix sort on an order-preserving 64-bit image of the doubles, 8 bits per pass and three launches per pass,
-//      both operands in the same launches (grid y),
+//   1. block means of both operands into the workspace, as unsigned keys in the order of the doubles, with their
+//      partial sums and maxima,
+//   2. sum, maximum and sum of exp(x - max) (two-stage reductions): the parameters of the softmax and the decision whether
+//      to apply it,
+//   3. the raw means are sorted (softmax is increasing, so it commutes with sorting), both operands in the same
+//      launches (grid y): a sample sort up to kSampleSortMax keys, a least-significant-digit radix sort beyond,
 //   4. m = max |P_A - P_B|, then sum (|P_A - P_B| / m)^p, then m (sum / n)^(1/p): the scaling by m changes
 //      nothing in exact arithmetic and keeps orders such as p = 68 .. 80 from underflowing.
 // All sums are two-stage with a fixed order, so the result is reproducible run to run.
@@ -27,9 +27,27 @@ constexpr int kSortThreads = 256;                // threads of a sorting workgro
 constexpr int kKeysPerLane = 16;
 constexpr int kWaveKeys = 64 * kKeysPerLane;     // keys one wave ranks
 constexpr int kTileKeys = kSortThreads * kKeysPerLane;   // keys of a tile (one workgroup)
-// workgroups per operand in the small reductions, at most: 8 per compute unit (exp and pow are long dependent chains;
-// with 256 the power sum over 2M keys took 36 us)
-constexpr int kStatGroups = 2048;
+// workgroups per operand in the small reductions, at most
+constexpr int kStatGroups = 1024;
+constexpr int kMeansPerThread = 8;               // blocks whose N and first index a thread requests together
+constexpr int kDistancesInFlight = 4;
+constexpr int kKeysInFlight = 8;                 // keys a thread of the passes below requests together
+
+// Sample sort: 4 K keys drawn from the n (one from each run of n / 4K, at a place that depends on the run's number) and
+// sorted give K - 1 splitters; one pass counts and one pass scatters the keys into the 2 K - 1 buckets (between two
+// splitters, or equal to one: a value that many blocks share fills a bucket that needs no sorting); a workgroup sorts a
+// bucket in LDS.  What bounds it: 8-byte scatters and LDS, 16 bytes a key and pass against memory otherwise.
+// K = n / 2048 rounded up to a power of two, so that a bucket has some 1024 to 2048 keys: smaller ones would make the
+// runs that a tile scatters into a bucket shorter than the 64 bytes they are, larger ones would not fit LDS beside
+// three more.  2 x 2M keys: the eight radix passes (three launches each) took 301 us of 491, these six launches
+// take 160 of 290: counting 27, scattering 39, sorting the buckets 62, the splitters 19.
+constexpr int kSampleSortMax = 1 << 22;          // 2048 buckets: fewer than two samples each would leave them too uneven
+constexpr int kBucketKeys = 2048;                // on average, at most
+constexpr int kBucketCap = 4096;                 // keys sorted in LDS at once: larger buckets take more than one round
+constexpr int kMaxSamples = 4096;                 // four per bucket, two where there are 2048 buckets
+constexpr int kMaxTiles = 256;                   // tiles per operand of the counting and scattering passes
+constexpr int kMinTileKeys = 8192;
+constexpr int kPassThreads = 512;
 constexpr double kSumTolerance = 1e-9;           // "the means sum to one" is taken as |sum - 1| <= this
 
 // per operand: written by the one-workgroup kernels, read by everything after them
@@ -40,17 +58,41 @@ struct OperandParams {
 struct Workspace {
   OperandParams* params;   // [2]
   double* partials;        // [2][kStatGroups][2]
-  double* scalars;         // [2]: the largest difference, the result's power sum
-  uint64_t* buf0;          // [2][n]: means, then keys; the sorted keys end up here
-  uint64_t* buf1;          // [2][n]
-  uint32_t* hist;          // [2][kBins][n_tiles]
-  uint32_t* sums;          // [2][kBins]: the digits' totals
+  uint64_t* buf0;          // [2][n]: keys; the sorted keys end up here
+  uint64_t* buf1;          // [2][n]: keys by bucket, later the differences
+  uint32_t* hist;          // sample sort: [2][tiles][2 K]; radix sort: [2][kBins][n_tiles]
+  uint32_t* sums;          // [2][2 K] / [2][kBins]: the buckets' / digits' totals
+  uint64_t* splitters;     // [2][K]
+  uint32_t* rest;          // [1 + 2 K]: buckets left for the second sorting kernel, their number first
 };
+
+struct SortPlan {
+  bool sample;             // else radix
+  int buckets;             // K
+  int tiles;               // of the counting and scattering passes
+  int64_t tile_keys;
+};
+
+SortPlan sort_plan(int64_t n) {
+  SortPlan p;
+  p.sample = n <= kSampleSortMax;
+  p.buckets = 1;
+  if (p.sample && n > kBucketCap)
+    while (int64_t(p.buckets) * kBucketKeys < n) p.buckets *= 2;
+  int64_t tiles = (n + kMinTileKeys - 1) / kMinTileKeys;
+  if (tiles > kMaxTiles) tiles = kMaxTiles;
+  p.tile_keys = (n + tiles - 1) / tiles;
+  p.tiles = int((n + p.tile_keys - 1) / p.tile_keys);
+  return p;
+}
 
 size_t align_up(size_t v) { return (v + 255) & ~size_t(255); }
 
 size_t carve(void* base, int64_t n, Workspace* w) {
+  const SortPlan plan = sort_plan(n);
   const int64_t n_tiles = (n + kTileKeys - 1) / kTileKeys;
+  const size_t counts = plan.sample ? size_t(plan.tiles) * 2 * size_t(plan.buckets) : size_t(kBins) * size_t(n_tiles);
+  const size_t totals = plan.sample ? 2 * size_t(plan.buckets) : size_t(kBins);
   size_t off = 0;
   char* p = static_cast<char*>(base);
   auto take = [&](size_t bytes) {
@@ -60,19 +102,21 @@ size_t carve(void* base, int64_t n, Workspace* w) {
   };
   char* a = take(sizeof(OperandParams) * 2);
   char* b = take(sizeof(double) * 2 * kStatGroups * 2);
-  char* c = take(sizeof(double) * 2);
   char* d = take(sizeof(uint64_t) * 2 * size_t(n));
   char* e = take(sizeof(uint64_t) * 2 * size_t(n));
-  char* f = take(sizeof(uint32_t) * 2 * kBins * size_t(n_tiles));
-  char* g = take(sizeof(uint32_t) * 2 * kBins);
+  char* f = take(sizeof(uint32_t) * 2 * counts);
+  char* g = take(sizeof(uint32_t) * 2 * totals);
+  char* h = take(sizeof(uint64_t) * 2 * size_t(plan.buckets));
+  char* i = take(sizeof(uint32_t) * (1 + 2 * size_t(plan.buckets)));
   if (w) {
-    w->sums = reinterpret_cast<uint32_t*>(g);
     w->params = reinterpret_cast<OperandParams*>(a);
     w->partials = reinterpret_cast<double*>(b);
-    w->scalars = reinterpret_cast<double*>(c);
     w->buf0 = reinterpret_cast<uint64_t*>(d);
     w->buf1 = reinterpret_cast<uint64_t*>(e);
     w->hist = reinterpret_cast<uint32_t*>(f);
+    w->sums = reinterpret_cast<uint32_t*>(g);
+    w->splitters = reinterpret_cast<uint64_t*>(h);
+    w->rest = reinterpret_cast<uint32_t*>(i);
   }
   return off;
 }
@@ -93,9 +137,9 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// workgroup totals of two values (sum, max) in thread 0
+// workgroup totals of two values (sum, max) in thread 0; at most 1024 threads
 __device__ __forceinline__ void group_sum_max(double& s, double& m) {
-  __shared__ double ls[kThreads / 64], lm[kThreads / 64];
+  __shared__ double ls[16], lm[16];
   s = wave_sum(s);
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) {
@@ -106,53 +150,78 @@ __device__ __forceinline__ void group_sum_max(double& s, double& m) {
   if (threadIdx.x == 0) {
     s = ls[0];
     m = lm[0];
-    for (int w = 1; w < kThreads / 64; ++w) {
+    for (int w = 1; w < int(blockDim.x >> 6); ++w) {
       s += ls[w];
       m = fmax(m, lm[w]);
     }
   }
 }
 
-// stage 0: sum and max of the means; stage 1: sum of exp(x - max).  grid (kStatGroups, 2)
-template <int kStage>
-__global__ __launch_bounds__(kThreads) void k_mean_stats(const double* __restrict__ means, int64_t n, int64_t chunk,
-                                                         const OperandParams* __restrict__ params,
-                                                         double* __restrict__ partials) {
-  const double* x = means + int64_t(blockIdx.y) * n;
+// Block means N_k F_k0 * scale of both operands (grid y) as keys, with the partial sums and maxima of the means.  Where a
+// block's indices fill a 128-byte line or more every line of F is fetched for two bytes of it: that is the time, and a
+// thread has kMeansPerThread lines on the way (2 x 2M blocks of 128 bytes: 112 us, 4.9 TB/s; k_blockwise_mean, the passes for
+// sum and maximum and the one that made the keys took 137).  Streaming whole vectors instead, of which one lane in
+// eight needs the first dword, took 121.
+__global__ __launch_bounds__(kThreads) void k_means(const void* __restrict__ N1, const void* __restrict__ F1,
+                                                    const void* __restrict__ N2, const void* __restrict__ F2, int ntype,
+                                                    int itype, double scale, int64_t n, int64_t chunk, int kept,
+                                                    uint64_t* __restrict__ keys, double* __restrict__ partials) {
+  const void* N = blockIdx.y ? N2 : N1;
+  const void* F = blockIdx.y ? F2 : F1;
+  uint64_t* out = keys + int64_t(blockIdx.y) * n;
   const int64_t begin = int64_t(blockIdx.x) * chunk;
   const int64_t end = begin + chunk < n ? begin + chunk : n;
   double s = 0.0, m = -INFINITY;
-  const double shift = kStage == 1 ? params[blockIdx.y].max : 0.0;
-  for (int64_t i = begin + threadIdx.x; i < end; i += kThreads) {
-    const double v = x[i];
-    if (kStage == 0) {
-      s += v;
-      m = fmax(m, v);
-    } else {
-      s += exp(v - shift);
+  auto run = [&](auto load_n, auto load_f) {
+    for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kThreads * kMeansPerThread) {
+      double v[kMeansPerThread], f[kMeansPerThread];
+#pragma unroll
+      for (int u = 0; u < kMeansPerThread; ++u) {
+        const int64_t i = i0 + u * kThreads < end ? i0 + u * kThreads : end - 1;
+        f[u] = load_f(i * kept);
+        v[u] = load_n(i);
+      }
+#pragma unroll
+      for (int u = 0; u < kMeansPerThread; ++u) {
+        const int64_t i = i0 + u * kThreads;
+        if (i < end) {
+          const double x = v[u] * f[u] * scale;
+          out[i] = key_of(x);
+          s += x;
+          m = fmax(m, x);
+        }
+      }
     }
-  }
+  };
+  auto by_index = [&](auto load_n) {                       // the types are uniform: one branch outside the loop
+    if (itype == PBZ_I8) run(load_n, [&](int64_t i) { return double(static_cast<const int8_t*>(F)[i]); });
+    else if (itype == PBZ_I16) run(load_n, [&](int64_t i) { return double(static_cast<const int16_t*>(F)[i]); });
+    else run(load_n, [&](int64_t i) { return double(static_cast<const int32_t*>(F)[i]); });
+  };
+  if (ntype == PBZ_F64) by_index([&](int64_t i) { return static_cast<const double*>(N)[i]; });
+  else if (ntype == PBZ_F32) by_index([&](int64_t i) { return double(static_cast<const float*>(N)[i]); });
+  else if (ntype == PBZ_BF16) by_index([&](int64_t i) { return double(bf16_bits_to_float(static_cast<const uint16_t*>(N)[i])); });
+  else by_index([&](int64_t i) { return double(float(static_cast<const _Float16*>(N)[i])); });
   group_sum_max(s, m);
   if (threadIdx.x == 0) {
-    double* out = partials + (int64_t(blockIdx.y) * kStatGroups + blockIdx.x) * 2;
-    out[0] = s;
-    out[1] = m;
+    double* p = partials + (int64_t(blockIdx.y) * kStatGroups + blockIdx.x) * 2;
+    p[0] = s;
+    p[1] = m;
   }
 }
 
-// one workgroup per operand: partials -> parameters
+// One workgroup of an operand: partials -> parameters.  Stage 0: sum and maximum of the means; stage 1: sum of exp.
 template <int kStage>
-__global__ __launch_bounds__(kThreads) void k_mean_params(const double* __restrict__ partials, int groups,
-                                                          OperandParams* __restrict__ params) {
-  const double* in = partials + int64_t(blockIdx.x) * kStatGroups * 2;
+__device__ __forceinline__ void mean_params(const double* partials, int groups, OperandParams* params) {
+  const double* in = partials + int64_t(blockIdx.y) * kStatGroups * 2;
   double s = 0.0, m = -INFINITY;
-  for (int g = threadIdx.x; g < groups; g += kThreads) {
+  for (int g = threadIdx.x; g < groups; g += blockDim.x) {
     s += in[2 * g];
     m = fmax(m, in[2 * g + 1]);
   }
   group_sum_max(s, m);
   if (threadIdx.x == 0) {
-    OperandParams& p = params[blockIdx.x];
+    OperandParams& p = params[blockIdx.y];
     if (kStage == 0) {
       p.sum = s;
       p.max = m;
@@ -163,9 +232,551 @@ __global__ __launch_bounds__(kThreads) void k_mean_params(const double* __restri
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_to_keys(uint64_t* __restrict__ buf, int64_t total) {
-  const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  if (i < total) buf[i] = key_of(__longlong_as_double((long long)buf[i]));
+// ---- sample sort -----------------------------------------------------------------------------------------------
+// sample i of 2^shift <= n (both below 2^23): from the i-th run of the keys, at a place that looks arbitrary
+__device__ __forceinline__ int64_t sample_place(int i, int shift, int64_t n) {
+  const int64_t lo = (n * i) >> shift, hi = (n * (i + 1)) >> shift;
+  return lo + int64_t((uint64_t(uint32_t(i) * 2654435761u) * uint64_t(hi - lo)) >> 32);
+}
+
+// Ascending order of p[0 .. m) by the whole workgroup: bitonic merges whose first step folds a run onto itself, so that every
+// exchange is ascending and a count that is no power of two needs no padding.  int_t: wide enough for 4 m.
+template <typename int_t>
+__device__ __forceinline__ void fold_sort(uint64_t* p, int_t m) {
+  for (int_t k = 2; k / 2 < m; k *= 2) {
+    for (int_t j = k / 2; j > 0; j /= 2) {
+      __syncthreads();
+      for (int_t i = threadIdx.x; 2 * i < m + j; i += int_t(blockDim.x)) {
+        const int_t lo = 2 * (i & ~(j - 1)) + (i & (j - 1));
+        const int_t hi = j == k / 2 ? lo + k - 1 - 2 * (lo & (k - 1)) : lo + j;
+        if (hi < m) {
+          const uint64_t a = p[lo], b = p[hi];
+          if (a > b) {
+            p[lo] = b;
+            p[hi] = a;
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// The last workgroup of an operand makes the parameters of stage 0 and clears the list of left-over buckets; the others
+// rank kRankThreads / kRankLanes samples each, by counting the smaller ones (and the equal ones before them), kRankLanes lanes
+// per sample.  (One workgroup sorting the samples in its LDS: 50 us for 4096, at 0.65 us a step of fold_sort.)
+constexpr int kRankLanes = 16;
+constexpr int kRankThreads = 512;
+__global__ __launch_bounds__(kRankThreads) void k_splitters(const uint64_t* __restrict__ keys, int64_t n, int buckets,
+                                                        uint64_t* __restrict__ splitters, int sample_shift,
+                                                        const double* __restrict__ partials, int groups,
+                                                        OperandParams* __restrict__ params, uint32_t* __restrict__ rest) {
+  if (blockIdx.x + 1 == gridDim.x) {
+    mean_params<0>(partials, groups, params);
+    if (threadIdx.x == 0 && blockIdx.y == 0) rest[0] = 0;
+    return;
+  }
+  __shared__ uint64_t sample[kMaxSamples];
+  constexpr int kLoads = kMaxSamples / kRankThreads;
+  const int samples = 1 << sample_shift;                   // kRankLanes at least
+  const uint64_t* in = keys + int64_t(blockIdx.y) * n;
+  const int mine = int(blockIdx.x) * (kRankThreads / kRankLanes) + int(threadIdx.x) / kRankLanes;
+  uint64_t v[kLoads];
+#pragma unroll
+  for (int u = 0; u < kLoads; ++u) {
+    const int i = u * kRankThreads + int(threadIdx.x);
+    if (u * kRankThreads < samples) v[u] = in[sample_place(i < samples ? i : samples - 1, sample_shift, n)];
+  }
+#pragma unroll
+  for (int u = 0; u < kLoads; ++u)
+    if (u * kRankThreads < samples)                            // fewer than a step's: padded with what is below no key
+      sample[u * kRankThreads + threadIdx.x] = u * kRankThreads + int(threadIdx.x) < samples ? v[u] : ~uint64_t(0);
+  __syncthreads();
+  const uint64_t key = sample[mine < samples ? mine : 0];
+  int rank = 0;
+  constexpr int kAhead = 8;                                // look-ups in flight
+  static_assert(kMaxSamples % (kRankLanes * kAhead) == 0, "the steps stay inside the samples and what pads them");
+  for (int j0 = threadIdx.x % kRankLanes; j0 < samples; j0 += kRankLanes * kAhead) {
+    uint64_t other[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) other[u] = sample[j0 + u * kRankLanes];
+    // all of these before `mine`: up to and with the equal ones; otherwise the smaller ones, and then equal ones before it
+    const uint64_t bound = key + (j0 + (kAhead - 1) * kRankLanes < mine ? 1 : 0);
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) rank += other[u] < bound ? 1 : 0;
+    if (bound == key && j0 < mine) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) rank += other[u] == key && j0 + u * kRankLanes < mine ? 1 : 0;
+    }
+  }
+#pragma unroll
+  for (int off = 1; off < kRankLanes; off <<= 1) rank += __shfl_xor(rank, off, 64);
+  const int each = samples / buckets;
+  if (threadIdx.x % kRankLanes == 0 && mine < samples && rank % each == each - 1 && rank / each < buckets - 1)
+    splitters[int64_t(blockIdx.y) * buckets + rank / each] = key;
+}
+
+// buckets of kCount keys: 2 (number of splitters below it), and one more when it equals the next splitter.  The keys take
+// the steps of the search together, so that their look-ups are in flight together.
+template <int kCount>
+__device__ __forceinline__ void buckets_of(const uint64_t* splitters, int buckets, const uint64_t* key, int* bucket) {
+#pragma unroll
+  for (int u = 0; u < kCount; ++u) bucket[u] = 0;
+  for (int step = buckets >> 1; step > 0; step >>= 1)      // buckets - 1 splitters, a power of two less one
+#pragma unroll
+    for (int u = 0; u < kCount; ++u)
+      if (splitters[bucket[u] + step - 1] < key[u]) bucket[u] += step;
+#pragma unroll
+  for (int u = 0; u < kCount; ++u)
+    bucket[u] = 2 * bucket[u] + (bucket[u] < buckets - 1 && splitters[bucket[u]] == key[u] ? 1 : 0);
+}
+
+// kStage 0: the keys of each bucket in the tile are counted, and exp(x - max) is summed on the way.
+// kStage 1: the keys go to their buckets (hist then holds the keys of the bucket in earlier tiles).
+// The order of equal or unequal keys within a bucket does not matter, so places are handed out by LDS atomics.
+template <int kStage>
+__global__ __launch_bounds__(kPassThreads) void k_buckets(const uint64_t* __restrict__ keys, uint64_t* __restrict__ out,
+                                                          int64_t n, int64_t tile_keys, int tiles, int buckets,
+                                                          const uint64_t* __restrict__ splitters,
+                                                          uint32_t* __restrict__ hist, const uint32_t* __restrict__ totals,
+                                                          const OperandParams* __restrict__ params,
+                                                          double* __restrict__ partials) {
+  extern __shared__ __align__(16) uint64_t split[];         // [buckets], then the counts or cursors [2 buckets]
+  uint32_t* count = reinterpret_cast<uint32_t*>(split + buckets);
+  // consecutive workgroups go to the eight dies in turn: each die gets a run of tiles, whose pieces of a bucket are
+  // neighbours, so that its L2 completes their lines
+  const int tile = int(blockIdx.x & 7u) * int(gridDim.x >> 3) + int(blockIdx.x >> 3);
+  if (tile >= tiles) return;                                // uniform over the workgroup
+  const uint64_t* in = keys + int64_t(blockIdx.y) * n;
+  uint32_t* h = hist + (int64_t(blockIdx.y) * tiles + tile) * 2 * buckets;
+  for (int i = threadIdx.x; i < buckets - 1; i += kPassThreads) split[i] = splitters[int64_t(blockIdx.y) * buckets + i];
+  if (kStage == 0) {
+    for (int i = threadIdx.x; i < 2 * buckets; i += kPassThreads) count[i] = 0;
+  } else {
+    // the buckets' first places: every thread adds up a run of totals, the runs are chained over the workgroup
+    __shared__ uint32_t wave_total[kPassThreads / 64];
+    const uint32_t* t = totals + int64_t(blockIdx.y) * 2 * buckets;
+    const int run = (2 * buckets + kPassThreads - 1) / kPassThreads;
+    const int first = int(threadIdx.x) * run;
+    uint32_t sum = 0;
+    for (int i = first; i < first + run && i < 2 * buckets; ++i) sum += t[i];
+    uint32_t before = sum;                                  // inclusive over the wave, then exclusive
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t up = __shfl_up(before, off, 64);
+      if (int(threadIdx.x & 63) >= off) before += up;
+    }
+    if ((threadIdx.x & 63) == 63) wave_total[threadIdx.x >> 6] = before;
+    __syncthreads();
+    before -= sum;
+    for (int w = 0; w < int(threadIdx.x >> 6); ++w) before += wave_total[w];
+    for (int i = first; i < first + run && i < 2 * buckets; ++i) {
+      count[i] = before + h[i];
+      before += t[i];
+    }
+  }
+  __syncthreads();
+  const int64_t begin = int64_t(tile) * tile_keys;
+  const int64_t end = begin + tile_keys < n ? begin + tile_keys : n;
+  const double shift = kStage == 0 ? params[blockIdx.y].max : 0.0;
+  double s = 0.0;
+  for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kPassThreads * kKeysInFlight) {
+    uint64_t key[kKeysInFlight];
+#pragma unroll
+    for (int u = 0; u < kKeysInFlight; ++u) {
+      const int64_t i = i0 + u * kPassThreads;
+      key[u] = in[i < end ? i : end - 1];
+    }
+    if (kStage == 0) {
+#pragma unroll
+      for (int u = 0; u < kKeysInFlight; ++u) {
+        const double e = exp(value_of(key[u]) - shift);
+        s += i0 + u * kPassThreads < end ? e : 0.0;
+      }
+    }
+    if (buckets > 1) {
+      int b[kKeysInFlight];
+      uint32_t place[kKeysInFlight];
+      buckets_of<kKeysInFlight>(split, buckets, key, b);
+#pragma unroll
+      for (int u = 0; u < kKeysInFlight; ++u)
+        if (i0 + u * kPassThreads < end) place[u] = atomicAdd(&count[b[u]], 1u);
+      if (kStage == 1) {
+#pragma unroll
+        for (int u = 0; u < kKeysInFlight; ++u)
+          if (i0 + u * kPassThreads < end) out[int64_t(blockIdx.y) * n + place[u]] = key[u];
+      }
+    }
+  }
+  if (kStage == 0) {
+    double none = 0.0;
+    group_sum_max(s, none);                                 // (contains the barrier)
+    if (threadIdx.x == 0) partials[(int64_t(blockIdx.y) * kStatGroups + tile) * 2] = s;
+    if (buckets > 1)
+      for (int i = threadIdx.x; i < 2 * buckets; i += kPassThreads) h[i] = count[i];
+  }
+}
+
+// hist [tile][bucket] -> keys of the bucket in earlier tiles, in place, and the buckets' totals.  A workgroup takes 64
+// buckets, wave w the w-th run of tiles; the last workgroup along x makes the parameters of stage 1.
+constexpr int kScanWaves = 16;
+__global__ __launch_bounds__(64 * kScanWaves) void k_bucket_scan(uint32_t* __restrict__ hist, int tiles, int bins,
+                                                                 uint32_t* __restrict__ totals,
+                                                                 const double* __restrict__ partials,
+                                                                 OperandParams* __restrict__ params) {
+  if (blockIdx.x + 1 == gridDim.x) {
+    mean_params<1>(partials, tiles, params);
+    return;
+  }
+  __shared__ uint32_t part[kScanWaves][64];
+  constexpr int kRun = kMaxTiles / kScanWaves;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int b = int(blockIdx.x) * 64 + lane;
+  uint32_t* column = hist + int64_t(blockIdx.y) * tiles * bins + (b < bins ? b : bins - 1);
+  uint32_t v[kRun];
+  uint32_t sum = 0;
+#pragma unroll
+  for (int j = 0; j < kRun; ++j) {
+    const int t = wave * kRun + j;
+    v[j] = column[int64_t(t < tiles ? t : tiles - 1) * bins];
+  }
+#pragma unroll
+  for (int j = 0; j < kRun; ++j) sum += wave * kRun + j < tiles ? v[j] : 0u;
+  part[wave][lane] = sum;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int w = 0; w < wave; ++w) before += part[w][lane];
+  if (b < bins) {
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) {
+      const int t = wave * kRun + j;
+      if (t < tiles) {
+        column[int64_t(t) * bins] = before;
+        before += v[j];
+      }
+    }
+    if (wave == kScanWaves - 1) totals[int64_t(blockIdx.y) * bins + b] = before;
+  }
+}
+
+constexpr int kSubs = 2048;
+constexpr int kMaxSub = 128;
+constexpr int kRestGroups = 64;                  // workgroups of the second sorting kernel
+constexpr int kBucketThreads = 1024;
+constexpr int kBucketWaves = kBucketThreads / 64;
+
+// cursor[] -> first[]: exclusive prefix sums, by the whole workgroup
+__device__ __forceinline__ void scan_intervals(const uint32_t* cursor, uint32_t* first, uint32_t* wave_total) {
+  constexpr int kEach = kSubs / kBucketThreads;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t c[kEach], sum = 0;
+#pragma unroll
+  for (int j = 0; j < kEach; ++j) {
+    c[j] = cursor[int(threadIdx.x) * kEach + j];
+    sum += c[j];
+  }
+  uint32_t before = sum;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t up = __shfl_up(before, off, 64);
+    if (lane >= off) before += up;
+  }
+  if (lane == 63) wave_total[wave] = before;
+  __syncthreads();
+  before -= sum;
+  for (int w = 0; w < wave; ++w) before += wave_total[w];
+#pragma unroll
+  for (int j = 0; j < kEach; ++j) {
+    first[int(threadIdx.x) * kEach + j] = before;
+    before += c[j];
+  }
+  if (threadIdx.x == kBucketThreads - 1) first[kSubs] = before;
+}
+
+// smallest and largest of the threads' (lo, hi), in every thread
+__device__ __forceinline__ void group_bounds(uint64_t& lo, uint64_t& hi, uint64_t* bounds) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int off = 32; off > 0; off >>= 1) {
+    const uint64_t l = __shfl_xor((unsigned long long)lo, off, 64), h = __shfl_xor((unsigned long long)hi, off, 64);
+    lo = l < lo ? l : lo;
+    hi = h > hi ? h : hi;
+  }
+  if (lane == 0) {
+    bounds[2 * wave] = lo;
+    bounds[2 * wave + 1] = hi;
+  }
+  __syncthreads();
+  for (int w = 0; w < kBucketWaves; ++w) {
+    lo = bounds[2 * w] < lo ? bounds[2 * w] : lo;
+    hi = bounds[2 * w + 1] > hi ? bounds[2 * w + 1] : hi;
+  }
+}
+
+// Bucket b of operand y: its first key and, for 2 b, its number of keys (sums: scratch of one value per wave)
+struct BucketPlace { int64_t base, m, equal; };
+__device__ __forceinline__ BucketPlace bucket_place(int b, int operand, int64_t n, int buckets, const uint32_t* totals,
+                                                    uint32_t* sums) {
+  BucketPlace p;
+  p.base = 0;
+  p.m = n;
+  p.equal = 0;
+  if (buckets > 1) {
+    const uint32_t* t = totals + int64_t(operand) * 2 * buckets;
+    uint32_t sum = 0;
+    for (int i = threadIdx.x; i < 2 * b; i += kBucketThreads) sum += t[i];
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    for (int w = 0; w < kBucketWaves; ++w) p.base += sums[w];
+    p.m = t[2 * b];
+    p.equal = t[2 * b + 1];
+  }
+  return p;
+}
+
+// A workgroup sorts bucket 2 b of its operand and copies bucket 2 b + 1, whose keys are equal.  The bucket's keys, at most
+// kHeldKeys, are read once and stay in registers.  They are dealt into kSubs equal intervals between the smallest and the
+// largest of their values (between neighbouring quantiles the means are spread nearly evenly: one key an interval), put
+// together by interval in LDS, at most kBucketCap keys a round, and every key counts the smaller ones of its interval.
+// Larger buckets, and those with more than kMaxSub keys in one interval, go to the list of k_bucket_sort_rest (one in a
+// thousand).  With one bucket in == out.
+constexpr int kHeldKeys = 8192;
+__global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_t* in_all, uint64_t* out_all, int64_t n,
+                                                                   int buckets, const uint32_t* __restrict__ totals,
+                                                                   uint32_t* __restrict__ rest) {
+  __shared__ uint64_t key[kBucketCap];
+  __shared__ uint32_t first[kSubs + 1], cursor[kSubs];
+  __shared__ uint32_t wave_total[kBucketWaves];
+  __shared__ double2 bounds[kBucketWaves];
+  constexpr int kPerThread = kHeldKeys / kBucketThreads;
+  const BucketPlace place = bucket_place(blockIdx.x, blockIdx.y, n, buckets, totals, wave_total);
+  const uint64_t* in = in_all + int64_t(blockIdx.y) * n + place.base;
+  uint64_t* out = out_all + int64_t(blockIdx.y) * n + place.base;
+  for (int64_t i = threadIdx.x; i < place.equal; i += kBucketThreads) out[place.m + i] = in[place.m + i];
+  if (place.m == 0) return;                                // uniform over the workgroup, here and below
+  if (place.m > kHeldKeys) {
+    if (threadIdx.x == 0) rest[1 + atomicAdd(rest, 1u)] = blockIdx.x * 2 + blockIdx.y;
+    return;
+  }
+  const int m = int(place.m), t = int(threadIdx.x);
+  uint64_t held[kPerThread];
+#pragma unroll
+  for (int j = 0; j < kPerThread; ++j)
+    if (j * kBucketThreads < m) held[j] = in[j * kBucketThreads + t < m ? j * kBucketThreads + t : m - 1];
+  for (int i = t; i < kSubs; i += kBucketThreads) cursor[i] = 0;
+  double least = value_of(held[0]), most = least;
+#pragma unroll
+  for (int j = 1; j < kPerThread; ++j)
+    if (j * kBucketThreads < m) {
+      least = fmin(least, value_of(held[j]));
+      most = fmax(most, value_of(held[j]));
+    }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    least = fmin(least, __shfl_xor(least, off, 64));
+    most = fmax(most, __shfl_xor(most, off, 64));
+  }
+  if ((t & 63) == 0) bounds[t >> 6] = make_double2(least, most);
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kBucketWaves; ++w) {
+    least = fmin(least, bounds[w].x);
+    most = fmax(most, bounds[w].y);
+  }
+  // subtraction, product and truncation are all non-decreasing: intervals follow the order of the values
+  const double span = most - least;
+  const double scale = span > 0.0 ? double(kSubs) / span : 0.0;
+  uint32_t where[kPerThread];                              // interval, and the key's number in it above
+  bool crowded = false;
+#pragma unroll
+  for (int j = 0; j < kPerThread; ++j)
+    if (j * kBucketThreads + t < m) {
+      int s = int((value_of(held[j]) - least) * scale);
+      s = s < 0 ? 0 : (s < kSubs ? s : kSubs - 1);
+      const uint32_t at = atomicAdd(&cursor[s], 1u);
+      where[j] = uint32_t(s) | (at << 16);
+      crowded = crowded || at >= uint32_t(kMaxSub);
+    }
+  if (__syncthreads_or(crowded)) {
+    if (t == 0) rest[1 + atomicAdd(rest, 1u)] = blockIdx.x * 2 + blockIdx.y;
+    return;
+  }
+  scan_intervals(cursor, first, wave_total);
+  __syncthreads();
+  for (int s0 = 0; s0 < kSubs;) {
+    int s1 = kSubs;                                        // this round: intervals s0 .. s1 - 1, the same in every thread
+    if (m > kBucketCap) {
+      s1 = s0;
+      for (int step = kSubs; step > 0; step >>= 1)
+        if (s1 + step <= kSubs && first[s1 + step] - first[s0] <= uint32_t(kBucketCap)) s1 += step;
+    }
+    const int from = int(first[s0]), count = int(first[s1]) - from;
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j)
+      if (j * kBucketThreads + t < m) {
+        const int s = int(where[j] & 0xffffu);
+        if (s >= s0 && s < s1) key[int(first[s]) - from + int(where[j] >> 16)] = held[j];
+      }
+    __syncthreads();
+    uint32_t rank[kPerThread];                             // among the keys of its interval
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j)
+      if (j * kBucketThreads + t < m) {
+        const int s = int(where[j] & 0xffffu);
+        rank[j] = 0;
+        if (s >= s0 && s < s1) {
+          const int a = int(first[s]) - from, b = int(first[s + 1]) - from, self = a + int(where[j] >> 16);
+          for (int q = a; q < b; ++q) {
+            const uint64_t other = key[q];
+            rank[j] += other < held[j] || (other == held[j] && q < self) ? 1u : 0u;
+          }
+        }
+      }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j)
+      if (j * kBucketThreads + t < m) {
+        const int s = int(where[j] & 0xffffu);
+        if (s >= s0 && s < s1) key[int(first[s]) - from + int(rank[j])] = held[j];
+      }
+    __syncthreads();
+    for (int i = t; i < count; i += kBucketThreads) out[from + i] = key[i];
+    __syncthreads();
+    s0 = s1;
+  }
+}
+
+// The buckets that k_bucket_sort leaves, listed in rest (their number first), any number of keys in any distribution.  As there,
+// with the keys read again where they are needed and intervals of one shared value left as they are.  Where an interval
+// has more than kMaxSub keys of several values the intervals are made equal in the keys instead (values over many orders
+// of magnitude); if that does not help, fold_sort takes over.  A bucket that does not fit LDS takes several rounds.
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_sort_rest(const uint64_t* in_all, uint64_t* out_all, int64_t n,
+                                                                     int buckets, const uint32_t* __restrict__ totals,
+                                                                     const uint32_t* __restrict__ rest) {
+  __shared__ uint64_t key[kBucketCap];
+  __shared__ uint32_t first[kSubs + 1], cursor[kSubs];
+  __shared__ uint32_t wave_total[kBucketWaves];
+  __shared__ uint64_t bounds[2 * kBucketWaves];
+  constexpr int kPerThread = kBucketCap / kBucketThreads;
+  const uint32_t listed = rest[0];
+  for (uint32_t r = blockIdx.x; r < listed; r += gridDim.x) {
+    const uint32_t which = rest[1 + r];
+    const BucketPlace bucket = bucket_place(int(which >> 1), int(which & 1u), n, buckets, totals, wave_total);
+    const uint64_t* in = in_all + int64_t(which & 1u) * n + bucket.base;
+    uint64_t* out = out_all + int64_t(which & 1u) * n + bucket.base;
+    const int64_t m = bucket.m;
+    const bool fits = m <= kBucketCap;
+    // calls f(key) for the thread's keys, kPerThread of them requested together
+    auto each = [&](auto f) {
+      for (int64_t i0 = threadIdx.x; i0 < m; i0 += kBucketCap) {
+        uint64_t v[kPerThread];
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j) v[j] = in[i0 + j * kBucketThreads < m ? i0 + j * kBucketThreads : m - 1];
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j)
+          if (i0 + j * kBucketThreads < m) f(v[j]);
+      }
+    };
+    uint64_t lo = ~uint64_t(0), hi = 0;
+    each([&](uint64_t k) {
+      lo = k < lo ? k : lo;
+      hi = k > hi ? k : hi;
+    });
+    group_bounds(lo, hi, bounds);
+    bool by_value = true;
+    for (;;) {
+      // subtraction, conversion, product and truncation are all non-decreasing: intervals follow the order of the keys
+      const double least = value_of(lo);
+      const double span = by_value ? value_of(hi) - least : double(hi - lo);
+      const double scale = span > 0.0 ? double(kSubs) / span : 0.0;
+      auto sub_of = [&](uint64_t k) {
+        const int s = int((by_value ? value_of(k) - least : double(k - lo)) * scale);
+        return s < 0 ? 0 : (s < kSubs ? s : kSubs - 1);
+      };
+      for (int i = threadIdx.x; i < kSubs; i += kBucketThreads) cursor[i] = 0;
+      __syncthreads();
+      each([&](uint64_t k) { atomicAdd(&cursor[sub_of(k)], 1u); });
+      __syncthreads();
+      scan_intervals(cursor, first, wave_total);
+      __syncthreads();
+      bool again = false;
+      for (int s0 = 0; s0 < kSubs;) {
+        // intervals s0 .. s1 - 1 fit; the same in every thread
+        int s1 = kSubs;
+        if (!fits) {
+          s1 = s0;
+          for (int step = kSubs; step > 0; step >>= 1)
+            if (s1 + step <= kSubs && first[s1 + step] - first[s0] <= uint32_t(kBucketCap)) s1 += step;
+          if (s1 == s0) {                                    // an interval larger than LDS
+            if (by_value) {
+              again = true;
+              break;
+            }
+            for (int64_t i = threadIdx.x; i < m; i += kBucketThreads) out[i] = in[i];
+            fold_sort<int64_t>(out, m);
+            break;
+          }
+        }
+        const uint32_t from = first[s0];
+        const int count = int(first[s1] - from);
+        for (int i = threadIdx.x; i < kSubs; i += kBucketThreads) cursor[i] = first[i] - from;
+        __syncthreads();
+        each([&](uint64_t k) {
+          const int s = sub_of(k);
+          if (s >= s0 && s < s1) key[atomicAdd(&cursor[s], 1u)] = k;
+        });
+        __syncthreads();
+        for (int i = threadIdx.x; i < kSubs; i += kBucketThreads) cursor[i] = 0;      // now: the interval has several values
+        __syncthreads();
+        for (int i = threadIdx.x; i < count; i += kBucketThreads) {
+          const int s = sub_of(key[i]);
+          if (key[i] != key[first[s] - from]) cursor[s] = 1;
+        }
+        __syncthreads();
+        uint64_t mine[kPerThread];
+        int place[kPerThread];
+        bool crowded = false;
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j) {
+          const int i = j * kBucketThreads + int(threadIdx.x);
+          place[j] = -1;
+          if (i < count) {
+            mine[j] = key[i];
+            const int s = sub_of(mine[j]);
+            const int a = int(first[s] - from), b = int(first[s + 1] - from);
+            place[j] = i;
+            if (cursor[s] != 0) {
+              crowded = crowded || b - a > kMaxSub;
+              if (b - a <= kMaxSub) {
+                int p = a;
+                for (int q = a; q < b; ++q) {
+                  const uint64_t other = key[q];
+                  p += other < mine[j] || (other == mine[j] && q < i) ? 1 : 0;
+                }
+                place[j] = p;
+              }
+            }
+          }
+        }
+        if (__syncthreads_or(crowded)) {
+          if (by_value && s0 == 0) {                         // nothing has been written yet
+            again = true;
+            break;
+          }
+          fold_sort<int>(key, count);
+        } else {
+#pragma unroll
+          for (int j = 0; j < kPerThread; ++j)
+            if (place[j] >= 0) key[place[j]] = mine[j];
+          __syncthreads();
+        }
+        for (int i = threadIdx.x; i < count; i += kBucketThreads) out[from + i] = key[i];
+        __syncthreads();
+        s0 = s1;
+      }
+      if (!again) break;
+      by_value = false;
+    }
+  }
 }
 
 // ---- radix sort, one pass = histogram per tile, exclusive scan over (digit, tile), stable scatter --------------
@@ -351,47 +962,67 @@ __device__ __forceinline__ double mapped(uint64_t key, const OperandParams& p) {
   return p.use_softmax != 0.0 ? exp(v - p.max) / p.exp_sum : v;
 }
 
-// stage 0: max |P_A - P_B|; stage 1: sum (|P_A - P_B| / m)^p.  grid (kStatGroups)
+// Stage 0: d = |P_A - P_B| into `diff`, and the workgroups' maxima.  Stage 1: sum (d / m)^p, m the largest of the maxima.  A term
+// with (d / m)^p below 2^-100 is left at zero: all of the up to 2^31 of them together are below 2^-69 of the sum, whose
+// largest term is 1, and at the orders in use (68 and more) that is every d below a third of m, whose pow would be most of
+// the pass (2M keys: 10.7 us, 25.7 with a pow for each).  grid (groups)
 template <int kStage>
-__global__ __launch_bounds__(kThreads) void k_distance(const uint64_t* __restrict__ sorted, int64_t n, int64_t chunk,
-                                                       const OperandParams* __restrict__ params, double order,
-                                                       const double* __restrict__ scalars,
-                                                       double* __restrict__ partials) {
-  const OperandParams pa = params[0], pb = params[1];
-  const double m_all = kStage == 1 ? scalars[0] : 0.0;
+__global__ __launch_bounds__(kThreads) void k_distance(const uint64_t* __restrict__ sorted, double* __restrict__ diff, int64_t n,
+                                                       int64_t chunk, const OperandParams* __restrict__ params, double order,
+                                                       const double* __restrict__ maxima, double* __restrict__ partials) {
+  __shared__ double m_all;
   const int64_t begin = int64_t(blockIdx.x) * chunk;
   const int64_t end = begin + chunk < n ? begin + chunk : n;
   double s = 0.0, m = 0.0;
-  for (int64_t i = begin + threadIdx.x; i < end; i += kThreads) {
-    const double d = fabs(mapped(sorted[i], pa) - mapped(sorted[n + i], pb));
-    if (kStage == 0) m = fmax(m, d);
-    else if (m_all > 0.0) s += pow(d / m_all, order);
+  if (kStage == 0) {
+    const OperandParams pa = params[0], pb = params[1];
+    for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kThreads * kDistancesInFlight) {
+      uint64_t a[kDistancesInFlight], b[kDistancesInFlight];
+#pragma unroll
+      for (int u = 0; u < kDistancesInFlight; ++u) {
+        const int64_t i = i0 + u * kThreads < end ? i0 + u * kThreads : end - 1;     // the last one again changes nothing
+        a[u] = sorted[i];
+        b[u] = sorted[n + i];
+      }
+#pragma unroll
+      for (int u = 0; u < kDistancesInFlight; ++u) {
+        const int64_t i = i0 + u * kThreads < end ? i0 + u * kThreads : end - 1;
+        const double d = fabs(mapped(a[u], pa) - mapped(b[u], pb));
+        diff[i] = d;
+        m = fmax(m, d);
+      }
+    }
+  } else {
+    for (int g = threadIdx.x; g < int(gridDim.x); g += kThreads) m = fmax(m, maxima[2 * g + 1]);
+    double none = 0.0;
+    group_sum_max(none, m);
+    if (threadIdx.x == 0) m_all = m;
+    __syncthreads();
+    m = m_all;
+    const double least = exp2(-100.0 / order);
+    if (m > 0.0)
+      for (int64_t i = begin + threadIdx.x; i < end; i += kThreads) {
+        const double x = diff[i] / m;
+        if (!(x < least)) s += pow(x, order);
+      }
+    __syncthreads();                                         // group_sum_max's buffers once more
   }
   group_sum_max(s, m);
   if (threadIdx.x == 0) {
     partials[2 * blockIdx.x] = s;
-    partials[2 * blockIdx.x + 1] = m;
+    if (kStage == 0) partials[2 * blockIdx.x + 1] = m;
   }
 }
 
-template <int kStage>
-__global__ __launch_bounds__(kThreads) void k_distance_final(const double* __restrict__ partials, int groups,
-                                                             double n, double order, double* __restrict__ scalars,
-                                                             double* __restrict__ out) {
+__global__ __launch_bounds__(kThreads) void k_distance_final(const double* __restrict__ sums, const double* __restrict__ maxima,
+                                                             int groups, double n, double order, double* __restrict__ out) {
   double s = 0.0, m = 0.0;
   for (int g = threadIdx.x; g < groups; g += kThreads) {
-    s += partials[2 * g];
-    m = fmax(m, partials[2 * g + 1]);
+    s += sums[2 * g];
+    m = fmax(m, maxima[2 * g + 1]);
   }
   group_sum_max(s, m);
-  if (threadIdx.x == 0) {
-    if (kStage == 0) {
-      scalars[0] = m;
-    } else {
-      const double m_all = scalars[0];
-      out[0] = m_all > 0.0 ? m_all * pow(s / n, 1.0 / order) : 0.0;
-    }
-  }
+  if (threadIdx.x == 0) out[0] = m > 0.0 ? m * pow(s / n, 1.0 / order) : 0.0;
 }
 
 }  // namespace
@@ -402,47 +1033,61 @@ int launch_approximate_wasserstein(const pbz_codec* c, int64_t n, const void* N1
                                    const void* F2, double order, double* out, void* workspace, hipStream_t s) {
   Workspace w;
   carve(workspace, n, &w);
-  double* means = reinterpret_cast<double*>(w.buf0);
-  int st = launch_blockwise_mean(c, n, N1, F1, means, s);
-  if (st != PBZ_OK) return st;
-  st = launch_blockwise_mean(c, n, N2, F2, means + n, s);
-  if (st != PBZ_OK) return st;
-
-  int64_t chunk = ((n + kStatGroups - 1) / kStatGroups + kThreads - 1) / kThreads * kThreads;
+  const SortPlan plan = sort_plan(n);
+  const int64_t chunk = ((n + kStatGroups - 1) / kStatGroups + kThreads - 1) / kThreads * kThreads;
   const int groups = int((n + chunk - 1) / chunk);
-  hipLaunchKernelGGL(k_mean_stats<0>, dim3(groups, 2), dim3(kThreads), 0, s, means, n, chunk, w.params, w.partials);
-  hipLaunchKernelGGL(k_mean_params<0>, dim3(2), dim3(kThreads), 0, s, w.partials, groups, w.params);
-  hipLaunchKernelGGL(k_mean_stats<1>, dim3(groups, 2), dim3(kThreads), 0, s, means, n, chunk, w.params, w.partials);
-  hipLaunchKernelGGL(k_mean_params<1>, dim3(2), dim3(kThreads), 0, s, w.partials, groups, w.params);
-  st = hip_status(hipGetLastError());
+  const double scale = 1.0 / (c->r * std::sqrt(double(c->vol)));
+  const int K = plan.buckets;
+  hipLaunchKernelGGL(k_means, dim3(groups, 2), dim3(kThreads), 0, s, N1, F1, N2, F2, int(c->ftype), int(c->itype), scale, n,
+                     chunk, c->kept, w.buf0, w.partials);
+  int sample_shift = 0;
+  while ((1 << sample_shift) < 4 * K && (1 << sample_shift) < kMaxSamples) ++sample_shift;
+  constexpr int kPerGroup = kRankThreads / kRankLanes;
+  const int rank_groups = K > 1 ? ((1 << sample_shift) + kPerGroup - 1) / kPerGroup : 0;
+  hipLaunchKernelGGL(k_splitters, dim3(rank_groups + 1, 2), dim3(kRankThreads), 0, s, w.buf0, n, K, w.splitters, sample_shift,
+                     w.partials, groups, w.params, w.rest);
+  const size_t pass_bytes = size_t(K) * 16;
+  const dim3 pass_grid(unsigned((plan.tiles + 7) / 8 * 8), 2);
+  hipLaunchKernelGGL(k_buckets<0>, pass_grid, dim3(kPassThreads), pass_bytes, s, w.buf0, w.buf1, n, plan.tile_keys, plan.tiles, K,
+                     w.splitters, w.hist, w.sums, w.params, w.partials);
+  const int scan_groups = K > 1 ? (2 * K + 63) / 64 : 0;
+  hipLaunchKernelGGL(k_bucket_scan, dim3(scan_groups + 1, 2), dim3(64 * kScanWaves), 0, s, w.hist, plan.tiles, 2 * K, w.sums,
+                     w.partials, w.params);
+  int st = hip_status(hipGetLastError());
   if (st != PBZ_OK) return st;
-
-  const int64_t total = 2 * n;
-  hipLaunchKernelGGL(k_to_keys, dim3(unsigned((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, w.buf0, total);
-  const int64_t n_tiles = (n + kTileKeys - 1) / kTileKeys;
-  uint64_t* src = w.buf0;
-  uint64_t* dst = w.buf1;
-  for (int pass = 0; pass < 64 / kRadixBits; ++pass) {
-    const int shift = pass * kRadixBits;
-    hipLaunchKernelGGL(k_radix_hist, dim3(unsigned(n_tiles), 2), dim3(kSortThreads), 0, s, src, n, n_tiles, shift, w.hist);
-    hipLaunchKernelGGL(k_scan_digit, dim3(kBins, 2), dim3(kSortThreads), 0, s, w.hist, n_tiles, w.sums);
-    hipLaunchKernelGGL(k_radix_scatter, dim3(unsigned(n_tiles), 2), dim3(kSortThreads), 0, s, src, dst, n, n_tiles, shift,
-                       w.hist, w.sums);
-    uint64_t* t = src;
-    src = dst;
-    dst = t;
+  if (plan.sample) {
+    if (K > 1)
+      hipLaunchKernelGGL(k_buckets<1>, pass_grid, dim3(kPassThreads), pass_bytes, s, w.buf0, w.buf1, n, plan.tile_keys,
+                         plan.tiles, K, w.splitters, w.hist, w.sums, w.params, w.partials);
+    const uint64_t* grouped = K > 1 ? w.buf1 : w.buf0;
+    hipLaunchKernelGGL(k_bucket_sort, dim3(K, 2), dim3(kBucketThreads), 0, s, grouped, w.buf0, n, K, w.sums, w.rest);
+    hipLaunchKernelGGL(k_bucket_sort_rest, dim3(2 * K < kRestGroups ? 2 * K : kRestGroups), dim3(kBucketThreads), 0, s, grouped,
+                       w.buf0, n, K, w.sums, w.rest);
+  } else {
+    const int64_t n_tiles = (n + kTileKeys - 1) / kTileKeys;
+    uint64_t* src = w.buf0;
+    uint64_t* dst = w.buf1;
+    for (int pass = 0; pass < 64 / kRadixBits; ++pass) {      // an even number: the sorted keys are back in buf0
+      const int shift = pass * kRadixBits;
+      hipLaunchKernelGGL(k_radix_hist, dim3(unsigned(n_tiles), 2), dim3(kSortThreads), 0, s, src, n, n_tiles, shift, w.hist);
+      hipLaunchKernelGGL(k_scan_digit, dim3(kBins, 2), dim3(kSortThreads), 0, s, w.hist, n_tiles, w.sums);
+      hipLaunchKernelGGL(k_radix_scatter, dim3(unsigned(n_tiles), 2), dim3(kSortThreads), 0, s, src, dst, n, n_tiles, shift,
+                         w.hist, w.sums);
+      uint64_t* t = src;
+      src = dst;
+      dst = t;
+    }
   }
   st = hip_status(hipGetLastError());
   if (st != PBZ_OK) return st;
-  // an even number of passes: the sorted keys are back in buf0 (== src)
-  hipLaunchKernelGGL(k_distance<0>, dim3(groups), dim3(kThreads), 0, s, src, n, chunk, w.params, order, w.scalars,
+  // the maxima in the first operand's partials, the sums of powers in the second's
+  double* diff = reinterpret_cast<double*>(w.buf1);
+  double* sums = w.partials + 2 * kStatGroups;
+  hipLaunchKernelGGL(k_distance<0>, dim3(groups), dim3(kThreads), 0, s, w.buf0, diff, n, chunk, w.params, order, w.partials,
                      w.partials);
-  hipLaunchKernelGGL(k_distance_final<0>, dim3(1), dim3(kThreads), 0, s, w.partials, groups, double(n), order, w.scalars,
-                     out);
-  hipLaunchKernelGGL(k_distance<1>, dim3(groups), dim3(kThreads), 0, s, src, n, chunk, w.params, order, w.scalars,
-                     w.partials);
-  hipLaunchKernelGGL(k_distance_final<1>, dim3(1), dim3(kThreads), 0, s, w.partials, groups, double(n), order, w.scalars,
-                     out);
+  hipLaunchKernelGGL(k_distance<1>, dim3(groups), dim3(kThreads), 0, s, w.buf0, diff, n, chunk, w.params, order, w.partials,
+                     sums);
+  hipLaunchKernelGGL(k_distance_final, dim3(1), dim3(kThreads), 0, s, sums, w.partials, groups, double(n), order, out);
   return hip_status(hipGetLastError());
 }
 
