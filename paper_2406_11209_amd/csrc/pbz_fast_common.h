@@ -27,10 +27,23 @@ struct FastGeom {
 // Which tile does this wave own?  Grid x runs over the tiles of one z-slab (kWaves per workgroup), grid y / z
 // over the slabs.  Everything here is uniform over the wave and 32-bit, so it compiles to a handful of
 // scalar instructions instead of 64-bit vector divisions.
-template <int kWaves>
+//
+// kRuns: rows start anywhere (the last extent is no multiple of the block's), so neighbouring workgroups share a line in
+// every row.  Workgroups go to the eight dies in turn, each with an L2 of its own: dealt out plainly, those lines are
+// fetched twice and written in two parts.  Of every 64 workgroups each die therefore takes a run of eight consecutive
+// ones (tile_grid pads the grid to a multiple of 64 where that is little).  Compress and decompress together: 125 x 1000 x
+// 1003 FP32 in 4x16x16 blocks int16 402 -> 343 us, int8 340 -> 283; 250 x 510 x 511 in 16x16x16 blocks int16 281 -> 222;
+// 250 x 1022 x 1022 bfloat16 in 8x8x8 blocks 316 -> 290; 8190 x 8189 in 16x16 blocks 179 -> 160, in 8x8 blocks 195 -> 192.
+// The FP64 lane and oct8 kernels, whose workgroups own 2 KiB and more of a row, gained nothing (0-1.5 % slower) and keep
+// the plain order; so do arrays whose rows are whole blocks, where no line is shared.
+__device__ __forceinline__ uint32_t group_in_run_order() {
+  const uint32_t b = blockIdx.x;
+  return (gridDim.x & 63u) == 0 ? (b & ~63u) | ((b & 7u) << 3) | ((b >> 3) & 7u) : b;
+}
+template <int kWaves, bool kRuns = false>
 __device__ __forceinline__ bool decode_tile(const FastGeom& g, int64_t& tx, int64_t& by, int64_t& bz) {
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t t = blockIdx.x * kWaves + w;
+  const uint32_t t = (kRuns ? group_in_run_order() : blockIdx.x) * kWaves + w;
   const uint32_t slab = blockIdx.y + blockIdx.z * gridDim.y;
   if (t >= g.tiles_yx || slab >= g.gz) return false;
   const uint32_t row = t / g.tiles_x;
@@ -40,15 +53,18 @@ __device__ __forceinline__ bool decode_tile(const FastGeom& g, int64_t& tx, int6
   return true;
 }
 
-// launch geometry shared by all kernels; false when the tile counts do not fit the grid limits
-inline bool tile_grid(FastGeom& g, int blocks_per_wave, int waves_per_group, dim3* grid) {
+// launch geometry shared by all kernels; false when the tile counts do not fit the grid limits.  ragged_x: for kernels
+// built with kTailX
+inline bool tile_grid(FastGeom& g, int blocks_per_wave, int waves_per_group, dim3* grid, bool ragged_x = false) {
   const int64_t tiles_x = (g.gx + blocks_per_wave - 1) / blocks_per_wave;
   const int64_t tiles_yx = tiles_x * g.gy;
   if (tiles_yx >= (int64_t(1) << 31) || g.gz > int64_t(65535) * 65535) return false;
   g.tiles_x = uint32_t(tiles_x);
   g.tiles_yx = uint32_t(tiles_yx);
   const unsigned gy = unsigned(g.gz < 65535 ? g.gz : 65535);
-  *grid = dim3(unsigned((tiles_yx + waves_per_group - 1) / waves_per_group), gy, unsigned((g.gz + gy - 1) / gy));
+  unsigned gx = unsigned((tiles_yx + waves_per_group - 1) / waves_per_group);
+  if (ragged_x && gx >= 256) gx = (gx + 63) / 64 * 64;          // see decode_tile; at most a quarter more, which leave at once
+  *grid = dim3(gx, gy, unsigned((g.gz + gy - 1) / gy));
   return true;
 }
 

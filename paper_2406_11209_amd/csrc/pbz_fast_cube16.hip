@@ -41,8 +41,9 @@ __device__ __forceinline__ int cube_slot_zy(int blk, int y, int z, int q) {
 __device__ __forceinline__ int cube_slot_zx(int kz, int q, int y) { return kz * kCubeRow + q * 16 + ((y + 2 * q) & 15); }
 
 // Which pair of blocks does this workgroup own?  Uniform over the workgroup (both waves stay or leave together).
+template <bool kRuns>
 __device__ __forceinline__ bool decode_pair(const FastGeom& g, int64_t& pair_x, int64_t& by, int64_t& bz) {
-  const uint32_t t = blockIdx.x;
+  const uint32_t t = kRuns ? group_in_run_order() : blockIdx.x;
   const uint32_t slab = blockIdx.y + blockIdx.z * gridDim.y;
   if (t >= g.tiles_yx || slab >= g.gz) return false;
   const uint32_t row = t / g.tiles_x;
@@ -126,7 +127,7 @@ __global__ __launch_bounds__(128) void k_compress_cube16(FastGeom g, const XT* _
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int64_t pair_x, by, bz;
-  if (!decode_pair(g, pair_x, by, bz)) return;
+  if (!decode_pair<kTailX>(g, pair_x, by, bz)) return;
   // The pair's second block may lie past the end of the row: its lanes then load the first block again, and the
   // wave that would own it works on those values and stores nothing (it still takes part in the barriers).
   const int64_t bx = pair_x * 2 + wave;            // this wave's block
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(128) void k_decompress_cube16(FastGeom g, const voi
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int64_t pair_x, by, bz;
-  if (!decode_pair(g, pair_x, by, bz)) return;
+  if (!decode_pair<kTailX>(g, pair_x, by, bz)) return;
   // a second block past the end of the row: that wave decodes the first block again, and nothing of it is stored
   const int64_t bx = pair_x * 2 + wave < g.gx ? pair_x * 2 + wave : g.gx - 1;
   const int64_t block = (bz * g.gy + by) * g.gx + bx;
@@ -354,7 +355,7 @@ struct Cube16Kernel {
   }
   // one workgroup per pair of blocks; the statistics records are per block
   static bool grid_for(FastGeom& g, dim3* grid) {
-    return g.gx * g.gy < (int64_t(1) << 31) && tile_grid(g, 2, 1, grid);
+    return g.gx * g.gy < (int64_t(1) << 31) && tile_grid(g, 2, 1, grid, g.X % 16 != 0);
   }
   static int fits(FastGeom g) {
     dim3 grid;

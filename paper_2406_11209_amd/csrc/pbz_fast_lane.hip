@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void k_compress_lane(FastGeom g, const XT* __r
 
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
-  if (!decode_tile<4>(g, tx, by, bz)) return;
+  if (!decode_tile<4, kTailX && sizeof(XT) < 8>(g, tx, by, bz)) return;
   const int64_t bx = tx * 64 + lane;
   const bool active = bx < g.gx;
   const int64_t bxc = active ? bx : g.gx - 1;   // lanes past the end re-read the last block and store nothing
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256, 2) void k_decompress_lane(FastGeom g, const vo
 
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
-  if (!decode_tile<4>(g, tx, by, bz)) return;
+  if (!decode_tile<4, kTailX && sizeof(XT) < 8>(g, tx, by, bz)) return;
   const int64_t bx = tx * 64 + lane;
   T v[VOL];
   if constexpr (kMasked) {
@@ -385,11 +385,11 @@ struct LaneKernel {
   }
   static int fits(FastGeom g) {
     dim3 grid;
-    return tile_grid(g, 64, 4, &grid) ? 1 : 0;
+    return tile_grid(g, 64, 4, &grid, g.X % BX != 0) ? 1 : 0;
   }
   static int64_t tiles(FastGeom g) {
     dim3 grid;
-    return tile_grid(g, 64, 4, &grid) ? g.gz * int64_t(g.tiles_yx) : 0;
+    return tile_grid(g, 64, 4, &grid, g.X % BX != 0) ? g.gz * int64_t(g.tiles_yx) : 0;
   }
   template <bool kRagged, bool kStats, bool kTailX>
   static void launch(const FastGeom& g, dim3 grid, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
@@ -404,7 +404,7 @@ struct LaneKernel {
   // tile_sums != nullptr: also the per-wave statistic sums (four doubles per tile)
   static int compress(FastGeom g, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 64, 4, &grid)) return 0;
+    if (!tile_grid(g, 64, 4, &grid, g.X % BX != 0)) return 0;
     const bool ragged = g.Z % BZ || g.Y % BY;
     if (g.X % BX) tile_sums ? launch<true, true, true>(g, grid, x, N, F, tile_sums, s) : launch<true, false, true>(g, grid, x, N, F, nullptr, s);
     else if (tile_sums) ragged ? launch<true, true, false>(g, grid, x, N, F, tile_sums, s) : launch<false, true, false>(g, grid, x, N, F, tile_sums, s);
@@ -413,7 +413,7 @@ struct LaneKernel {
   }
   static int decompress(FastGeom g, const void* N, const void* F, void* y, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 64, 4, &grid)) return 0;
+    if (!tile_grid(g, 64, 4, &grid, g.X % BX != 0)) return 0;
     if (g.X % BX) launch_inverse<true, true>(g, grid, N, F, y, s);
     else if (g.Z % BZ || g.Y % BY) launch_inverse<true, false>(g, grid, N, F, y, s);
     else launch_inverse<false, false>(g, grid, N, F, y, s);
@@ -439,7 +439,7 @@ struct LaneMasked<LaneKernel<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX>> {
   }
   static int compress(const pbz_codec* c, FastGeom g, const uint16_t*, const void* x, void* N, void* F, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 64, 4, &grid)) return 0;
+    if (!tile_grid(g, 64, 4, &grid, g.X % BX != 0)) return 0;
     const size_t lds = 4 * size_t(lane_mask_region<IT>(c->kept));
     if (g.X % BX)
       hipLaunchKernelGGL((k_compress_lane<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX, true, false, true, true>), grid, dim3(256),
@@ -451,7 +451,7 @@ struct LaneMasked<LaneKernel<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX>> {
   }
   static int decompress(const pbz_codec* c, FastGeom g, const uint16_t*, const void* N, const void* F, void* y, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 64, 4, &grid)) return 0;
+    if (!tile_grid(g, 64, 4, &grid, g.X % BX != 0)) return 0;
     const size_t lds = 4 * size_t(lane_mask_region<IT>(c->kept));
     if (g.X % BX)
       hipLaunchKernelGGL((k_decompress_lane<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX, true, true, true>), grid, dim3(256), lds,

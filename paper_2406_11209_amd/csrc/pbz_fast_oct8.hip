@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kOctWaves * 64) void k_compress_oct8(FastGeom g, co
   __builtin_amdgcn_s_setprio(3);
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
-  if (!decode_tile<kOctWaves>(g, tx, by, bz)) return;
+  if (!decode_tile<kOctWaves, kTailX && sizeof(XT) < 8>(g, tx, by, bz)) return;
   uint4* st = lds[threadIdx.x >> 6];
   const int z = lane >> 3, b = lane & 7;      // phase A: lane = (plane z, block b)
   const int bb = lane >> 3, j = lane & 7;     // phase B: lane = (block bb, row j)
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(256) void k_decompress_oct8(FastGeom g, const void*
   static_assert(KEPT % 16 == 0, "F blocks are whole 16-byte vectors");
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
-  if (!decode_tile<4>(g, tx, by, bz)) return;
+  if (!decode_tile<4, kTailX && sizeof(XT) < 8>(g, tx, by, bz)) return;
   const int z = lane >> 3, b = lane & 7;
   const int64_t bx = tx * 8 + b;
   const int64_t zz = bz * 8 + z;
@@ -454,7 +454,7 @@ __global__ __launch_bounds__(kOctWaves * 64) void k_decompress_oct8_full(FastGeo
   __shared__ uint4 lds[kOctWaves][kMasked ? kOctMaskedSlots : 8 * 64];
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
-  if (!decode_tile<kOctWaves>(g, tx, by, bz)) return;
+  if (!decode_tile<kOctWaves, kTailX && sizeof(XT) < 8>(g, tx, by, bz)) return;
   uint4* st = lds[threadIdx.x >> 6];
   const int64_t block0 = (bz * g.gy + by) * g.gx + tx * 8;
 
@@ -527,7 +527,7 @@ __global__ __launch_bounds__(512) void k_decompress_oct8_rows(FastGeom g, const 
   static_assert(KEPT % 16 == 0, "F blocks are whole 16-byte vectors");
   const int lane = threadIdx.x & 63;
   const int z = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t t = blockIdx.x;                               // tile of 64 blocks within the z-slab
+  const uint32_t t = kTailX && sizeof(XT) < 8 ? group_in_run_order() : blockIdx.x;     // tile of 64 blocks within the z-slab
   const uint32_t slab = blockIdx.y + blockIdx.z * gridDim.y;
   if (t >= g.tiles_yx || slab >= g.gz) return;
   const int64_t by = t / g.tiles_x, tx = t - uint32_t(by) * g.tiles_x, bz = slab;
@@ -615,11 +615,11 @@ struct Oct8Kernel {
   }
   static int fits(FastGeom g) {
     dim3 grid;
-    return tile_grid(g, 8, kOctWaves, &grid) ? 1 : 0;
+    return tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0) ? 1 : 0;
   }
   static int64_t tiles(FastGeom g) {
     dim3 grid;
-    return tile_grid(g, 8, kOctWaves, &grid) ? g.gz * int64_t(g.tiles_yx) : 0;
+    return tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0) ? g.gz * int64_t(g.tiles_yx) : 0;
   }
   template <bool kRagged, bool kStats, bool kTailX>
   static void launch(const FastGeom& g, dim3 grid, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
@@ -628,7 +628,7 @@ struct Oct8Kernel {
   }
   static int compress(FastGeom g, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    if (!tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0)) return 0;
     const bool ragged = g.Z % 8 || g.Y % 8;
     if (g.X % 8) tile_sums ? launch<true, true, true>(g, grid, x, N, F, tile_sums, s) : launch<true, false, true>(g, grid, x, N, F, nullptr, s);
     else if (tile_sums) ragged ? launch<true, true, false>(g, grid, x, N, F, tile_sums, s) : launch<false, true, false>(g, grid, x, N, F, tile_sums, s);
@@ -642,15 +642,15 @@ struct Oct8Kernel {
     XT* out = static_cast<XT*>(y);
     const bool tail = g.X % 8 != 0;
     if constexpr (KZ == 8 && KY == 8 && KX == 8) {
-      if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+      if (!tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0)) return 0;
       if (tail) hipLaunchKernelGGL((k_decompress_oct8_full<TF, XT, true>), grid, dim3(kOctWaves * 64), 0, s, g, n, f, out, MaskArgs<false>());
       else hipLaunchKernelGGL((k_decompress_oct8_full<TF, XT, false>), grid, dim3(kOctWaves * 64), 0, s, g, n, f, out, MaskArgs<false>());
     } else if (g.gx >= 48) {        // at least three quarters of the lanes of a 64-block tile busy
-      if (!tile_grid(g, 64, 1, &grid)) return 0;
+      if (!tile_grid(g, 64, 1, &grid, g.X % 8 != 0)) return 0;
       if (tail) hipLaunchKernelGGL((k_decompress_oct8_rows<TF, XT, KZ, KY, KX, true>), grid, dim3(512), 0, s, g, n, f, out);
       else hipLaunchKernelGGL((k_decompress_oct8_rows<TF, XT, KZ, KY, KX, false>), grid, dim3(512), 0, s, g, n, f, out);
     } else {
-      if (!tile_grid(g, 8, 4, &grid)) return 0;
+      if (!tile_grid(g, 8, 4, &grid, g.X % 8 != 0)) return 0;
       if (tail) hipLaunchKernelGGL((k_decompress_oct8<TF, XT, KZ, KY, KX, true>), grid, dim3(256), 0, s, g, n, f, out);
       else hipLaunchKernelGGL((k_decompress_oct8<TF, XT, KZ, KY, KX, false>), grid, dim3(256), 0, s, g, n, f, out);
     }
@@ -700,7 +700,7 @@ __global__ __launch_bounds__(kOctWaves * 64) void k_compress_oct8_wide(FastGeom 
   __shared__ uint4 lds[kOctWaves][kMasked ? kOctMaskedSlots : 8 * 64];
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
-  if (!decode_tile<kOctWaves>(g, tx, by, bz)) return;
+  if (!decode_tile<kOctWaves, kTailX && sizeof(XT) < 8>(g, tx, by, bz)) return;
   uint4* st = lds[threadIdx.x >> 6];
   const int z = lane >> 3, b = lane & 7;      // phase A: lane = (plane z, block b)
   const int bb = lane >> 3, j = lane & 7;     // phase B: lane = (block bb, row j)
@@ -858,7 +858,7 @@ __global__ __launch_bounds__(kOctWaves * 64) void k_decompress_oct8_wide(FastGeo
   __shared__ uint4 lds[kOctWaves][kMasked ? kOctMaskedSlots : 8 * 64];
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
-  if (!decode_tile<kOctWaves>(g, tx, by, bz)) return;
+  if (!decode_tile<kOctWaves, kTailX && sizeof(XT) < 8>(g, tx, by, bz)) return;
   uint4* st = lds[threadIdx.x >> 6];
   const int64_t block0 = (bz * g.gy + by) * g.gx + tx * 8;
   const int z = lane >> 3, b = lane & 7;
@@ -923,11 +923,11 @@ struct Oct8WideKernel {
   }
   static int fits(FastGeom g) {
     dim3 grid;
-    return tile_grid(g, 8, kOctWaves, &grid) ? 1 : 0;
+    return tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0) ? 1 : 0;
   }
   static int64_t tiles(FastGeom g) {
     dim3 grid;
-    return tile_grid(g, 8, kOctWaves, &grid) ? g.gz * int64_t(g.tiles_yx) : 0;
+    return tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0) ? g.gz * int64_t(g.tiles_yx) : 0;
   }
   template <bool kRagged, bool kStats, bool kTailX>
   static void launch(const FastGeom& g, dim3 grid, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
@@ -936,7 +936,7 @@ struct Oct8WideKernel {
   }
   static int compress(FastGeom g, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    if (!tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0)) return 0;
     const bool ragged = g.Y % 8 || g.Z % 8;
     if (g.X % 8) tile_sums ? launch<true, true, true>(g, grid, x, N, F, tile_sums, s) : launch<true, false, true>(g, grid, x, N, F, nullptr, s);
     else if (tile_sums) ragged ? launch<true, true, false>(g, grid, x, N, F, tile_sums, s) : launch<false, true, false>(g, grid, x, N, F, tile_sums, s);
@@ -945,7 +945,7 @@ struct Oct8WideKernel {
   }
   static int decompress(FastGeom g, const void* N, const void* F, void* y, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    if (!tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0)) return 0;
     if (g.X % 8)
       hipLaunchKernelGGL((k_decompress_oct8_wide<TF, XT, IT, true>), grid, dim3(kOctWaves * 64), 0, s, g, N,
                          static_cast<const IT*>(F), static_cast<XT*>(y), MaskArgs<false>());
@@ -985,14 +985,14 @@ struct OctMasked<Oct8Kernel<TF, XT, 8, 8, 8>> {
   }
   static int compress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* x, void* N, void* F, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    if (!tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0)) return 0;
     g.X % 8 ? launch<true>(c, g, grid, pos, x, N, F, s) : launch<false>(c, g, grid, pos, x, N, F, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
   }
   static int decompress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* N, const void* F, void* y,
                         hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    if (!tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0)) return 0;
     g.X % 8 ? launch_inverse<true>(c, g, grid, pos, N, F, y, s) : launch_inverse<false>(c, g, grid, pos, N, F, y, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
   }
@@ -1017,14 +1017,14 @@ struct OctMasked<Oct8WideKernel<TF, XT, IT>> {
   }
   static int compress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* x, void* N, void* F, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    if (!tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0)) return 0;
     g.X % 8 ? launch<true>(c, g, grid, pos, x, N, F, s) : launch<false>(c, g, grid, pos, x, N, F, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
   }
   static int decompress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* N, const void* F, void* y,
                         hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, 8, kOctWaves, &grid)) return 0;
+    if (!tile_grid(g, 8, kOctWaves, &grid, g.X % 8 != 0)) return 0;
     g.X % 8 ? launch_inverse<true>(c, g, grid, pos, N, F, y, s) : launch_inverse<false>(c, g, grid, pos, N, F, y, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
   }

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(128) void k_compress_quad16(FastGeom g, const XT* _
   __shared__ uint4 lds[2][16 * kQuadRow];
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
-  if (!decode_tile<2>(g, tx, by, bz)) return;
+  if (!decode_tile<2, kTailX>(g, tx, by, bz)) return;
   uint4* st = lds[threadIdx.x >> 6];
 
   T v[64];
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(128) void k_decompress_quad16(FastGeom g, const voi
   __shared__ uint4 lds[2][16 * kQuadRow];
   const int lane = threadIdx.x & 63;
   int64_t tx, by, bz;
-  if (!decode_tile<2>(g, tx, by, bz)) return;
+  if (!decode_tile<2, kTailX>(g, tx, by, bz)) return;
   uint4* st = lds[threadIdx.x >> 6];
   const int64_t block0 = (bz * g.gy + by) * g.gx + tx * BPW;
   const int yrow = lane & 15, bsub = lane >> 4;
@@ -334,11 +334,11 @@ struct Quad16Kernel {
   }
   static int fits(FastGeom g) {
     dim3 grid;
-    return tile_grid(g, kBlocksPerWave, 2, &grid) ? 1 : 0;
+    return tile_grid(g, kBlocksPerWave, 2, &grid, g.X % 16 != 0) ? 1 : 0;
   }
   static int64_t tiles(FastGeom g) {
     dim3 grid;
-    return tile_grid(g, kBlocksPerWave, 2, &grid) ? g.gz * int64_t(g.tiles_yx) : 0;
+    return tile_grid(g, kBlocksPerWave, 2, &grid, g.X % 16 != 0) ? g.gz * int64_t(g.tiles_yx) : 0;
   }
   template <bool kRagged, bool kStats, bool kTailX>
   static void launch(const FastGeom& g, dim3 grid, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
@@ -347,7 +347,7 @@ struct Quad16Kernel {
   }
   static int compress(FastGeom g, const void* x, void* N, void* F, double* tile_sums, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, kBlocksPerWave, 2, &grid)) return 0;
+    if (!tile_grid(g, kBlocksPerWave, 2, &grid, g.X % 16 != 0)) return 0;
     const bool ragged = g.Y % 16 || g.Z % BZ;
     if (g.X % 16) tile_sums ? launch<true, true, true>(g, grid, x, N, F, tile_sums, s) : launch<true, false, true>(g, grid, x, N, F, nullptr, s);
     else if (tile_sums) ragged ? launch<true, true, false>(g, grid, x, N, F, tile_sums, s) : launch<false, true, false>(g, grid, x, N, F, tile_sums, s);
@@ -356,7 +356,7 @@ struct Quad16Kernel {
   }
   static int decompress(FastGeom g, const void* N, const void* F, void* y, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, kBlocksPerWave, 2, &grid)) return 0;
+    if (!tile_grid(g, kBlocksPerWave, 2, &grid, g.X % 16 != 0)) return 0;
     if (g.X % 16)
       hipLaunchKernelGGL((k_decompress_quad16<TF, T, IT, XT, BZ, true>), grid, dim3(128), 0, s, g, N,
                          static_cast<const IT*>(F), static_cast<XT*>(y), MaskArgs<false>());
@@ -397,14 +397,14 @@ struct QuadMasked<Quad16Kernel<TF, T, IT, XT, BZ>> {
   }
   static int compress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* x, void* N, void* F, hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, Base::kBlocksPerWave, 2, &grid)) return 0;
+    if (!tile_grid(g, Base::kBlocksPerWave, 2, &grid, g.X % 16 != 0)) return 0;
     g.X % 16 ? launch<true>(c, g, grid, pos, x, N, F, s) : launch<false>(c, g, grid, pos, x, N, F, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
   }
   static int decompress(const pbz_codec* c, FastGeom g, const uint16_t* pos, const void* N, const void* F, void* y,
                         hipStream_t s) {
     dim3 grid;
-    if (!tile_grid(g, Base::kBlocksPerWave, 2, &grid)) return 0;
+    if (!tile_grid(g, Base::kBlocksPerWave, 2, &grid, g.X % 16 != 0)) return 0;
     g.X % 16 ? launch_inverse<true>(c, g, grid, pos, N, F, y, s) : launch_inverse<false>(c, g, grid, pos, N, F, y, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
   }
