@@ -8,6 +8,9 @@ namespace pbz {
 
 __device__ __forceinline__ int phase_of(const void* p) { return int(reinterpret_cast<uintptr_t>(p) & 15u); }
 
+typedef uint32_t raw16 __attribute__((ext_vector_type(4)));   // not uint4: an array of that struct in flight stayed in
+                                                              // scratch memory (add of 64 Mi values in 20 kept: 295 us, 281 so)
+
 // [p, p + len) -> LDS, at the phase of p.  Only 16-byte pieces that lie inside the operand [lo, hi) are read as such
 // (they may hold bytes of neighbouring blocks, which nobody uses); the bytes of the others are read one by one.
 // kBatch: 16-byte loads in flight per lane.
@@ -20,16 +23,16 @@ __device__ __forceinline__ void stage_span(const uint8_t* lo, const uint8_t* hi,
   const int first = base < lo ? 1 : 0;
   const int last = base + 16 * int64_t(pieces) > hi ? pieces - 1 : pieces;
   for (int i0 = first; i0 < last; i0 += 64 * kBatch) {
-    uint4 v[kBatch];
+    raw16 v[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int i = i0 + u * 64 + lane;
-      v[u] = reinterpret_cast<const uint4*>(base)[i < last ? i : last - 1];
+      v[u] = reinterpret_cast<const raw16*>(base)[i < last ? i : last - 1];
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int i = i0 + u * 64 + lane;
-      if (i < last) reinterpret_cast<uint4*>(lds)[i] = v[u];
+      if (i < last) reinterpret_cast<raw16*>(lds)[i] = v[u];
     }
   }
   if (first != 0 && lane < 16 - a && lane < len) lds[a + lane] = p[lane];
