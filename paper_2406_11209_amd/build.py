@@ -17,7 +17,9 @@ LIB = os.path.join(PKG, "libpbz.so")
 EXAMPLE = os.path.join(PKG, "c_abi_roundtrip")
 PATTERNS = os.path.join(PKG, "memory_patterns")
 SOURCES = ["pbz_api.hip", "pbz_generic.hip", "pbz_ops.hip", "pbz_ops_staged.hip", "pbz_fast.hip", "pbz_fast_lane.hip", "pbz_fast_quad16.hip",
-           "pbz_fast_oct8.hip", "pbz_fast_cube16.hip", "pbz_wasserstein.hip", "pbz_tiled.hip", "pbz_static.hip", "pbz_copy.hip"]
+           "pbz_fast_oct8.hip", "pbz_fast_cube16.hip", "pbz_wasserstein.hip", "pbz_tiled.hip", "pbz_brick.hip", "pbz_brick_lines.hip", "pbz_brick_small.hip",
+           "pbz_brick_flat.hip", "pbz_brick_wide.hip", "pbz_brick_planes.hip", "pbz_brick_cubes.hip", "pbz_brick_tesseracts.hip",
+           "pbz_brick_long_tesseracts.hip", "pbz_static.hip", "pbz_copy.hip"]
 
 # Packed-FP32 code generation is switched off on purpose (the flag applies to the device pass; the host
 # pass prints a harmless "unknown feature" warning).
@@ -48,7 +50,7 @@ def build(verbose: bool = False) -> str:
     os.makedirs(objdir, exist_ok=True)
     objs = [os.path.join(objdir, s.replace(".hip", ".o")) for s in SOURCES]
     cmds = [[cc] + FLAGS + ["-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
-    with ThreadPoolExecutor(max_workers=6) as pool:
+    with ThreadPoolExecutor(max_workers=8) as pool:
         for out in pool.map(_run, cmds):
             if verbose and out.strip():
                 print(out)
@@ -80,7 +82,7 @@ def build_host_sanitized(outdir: str) -> tuple:
     cmds = [[cc, "--cuda-host-only", "-O1", "-g", "-std=c++17", "-fPIC"] + san +
             ["-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-c", os.path.join(CSRC, s), "-o", o]
             for s, o in zip(SOURCES, objs)]
-    with ThreadPoolExecutor(max_workers=6) as pool:
+    with ThreadPoolExecutor(max_workers=8) as pool:
         list(pool.map(_run, cmds))
     # a host-only object still refers to its translation unit's device image: give each an empty stand-in
     undefined = subprocess.run(["nm", "-u"] + objs, stdout=subprocess.PIPE, text=True, check=True).stdout.split()

@@ -281,7 +281,8 @@ int pbz_compress(const pbz_codec* c, const void* x, pbz_ftype x_type, const int6
   st = ensure_tables(c, &t);
   if (st != PBZ_OK) return st;
   if (c->path == PBZ_PATH_AUTO) {
-    const int r = try_compress_masked(c, g, t->places, x, x_type, N, F, s);
+    int r = try_compress_masked(c, g, t->places, x, x_type, N, F, s);
+    if (r == 0) r = try_compress_brick(c, g, t, x, x_type, N, F, s);
     if (r != 0) return r < 0 ? r : PBZ_OK;
   }
   if (tiled_kernels_cover(c)) return launch_compress_tiled(c, g, t, x, x_type, N, F, s);
@@ -351,7 +352,8 @@ int pbz_decompress(const pbz_codec* c, const void* N, const void* F, const int64
   st = ensure_tables(c, &t);
   if (st != PBZ_OK) return st;
   if (c->path == PBZ_PATH_AUTO) {
-    const int r = try_decompress_masked(c, g, t->places, N, F, y, y_type, s);
+    int r = try_decompress_masked(c, g, t->places, N, F, y, y_type, s);
+    if (r == 0) r = try_decompress_brick(c, g, t, N, F, y, y_type, s);
     if (r != 0) return r < 0 ? r : PBZ_OK;
   }
   if (tiled_kernels_cover(c)) return launch_decompress_tiled(c, g, t, N, F, y, y_type, s);

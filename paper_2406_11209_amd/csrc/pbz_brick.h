@@ -1,0 +1,902 @@
+// General codec kernels for a list of block shapes, any array, working and index type, any mask, any alignment: what the
+// specialised families leave to "generic" of the shapes that programs use (4-D and flat blocks, 4x8x8, 8x16, 32x32, 1-D,
+// and the families' shapes with types they are not built for).  pbz_tiled.hip takes the shapes that are not listed.
+//
+// Wave autonomous like the families: a wave owns a tile of consecutive blocks, VALUES (64, or 32 in FP64 work) values per
+// lane in registers, no workgroup barrier, LDS private to the wave.  Two layouts, each with whole lines of its dimensions
+// in a lane:
+//   A  lane (s, b): rows s RA .. s RA + RA - 1 of block b, all of x (a block's rows in row-major order of the other
+//      dimensions; RA = VALUES / BX).  How the array is read and written: the rows a lane needs come as 16-byte pieces, the
+//      lanes of neighbouring blocks next to each other.  Transforms along x and the dimensions whole in RA rows.
+//   B  lane (sr, sx, b): BXB columns of NR rows for every index of the remaining ("outer") dimensions, which are
+//      transformed there.  How indices are made and read.
+// Blocks of up to VALUES elements stay in layout A, several to a lane if smaller.  Between the layouts the tile passes through
+// LDS, 16 bytes a slot, in as many rounds as a lane's BXB columns have slots, so that LDS holds a part of the tile at a time.
+// Indices enter and leave F as in the families' kernels for any mask: dropped at their places in the span of F that the
+// tile's blocks are, which moves in 16-byte pieces.
+// The block shape is a template argument, so every index and bound is a constant but for the lane's own and the block's
+// place in the array; types, mask and geometry are arguments, with one uniform branch around each loop.
+// Memory bounds the FP32 work (4.3 - 5.1 TB/s of the copy's 5.6), registers the FP64 work (two waves per SIMD).  Measured,
+// us, with pbz_tiled.hip -> here:
+//                                      compress      decompress
+//   256x512x512 FP32, 4x8x8, i8        110 ->  64    100 ->  67
+//   32x64x128x256 FP32, 2x4x8x8, i8    129 ->  64    112 ->  67
+//   8192^2 FP32, 4x4, i8               101 ->  67     96 ->  68
+//   8192^2 FP32, 8x16, i8               99 ->  71    107 ->  78
+//   8192^2 FP32, 32x32, i8             134 ->  93    118 -> 101
+//   256x512x512 FP32, 2x8x8, i16       168 ->  99    166 -> 111
+//   16x32x128x256 FP64, 4^4, i32        65 ->  43     58 ->  50
+//   509x509x251 bf16, 8x8x8, i8        138 ->  55    120 ->  58
+//   4 Mi FP32, 64 (dense kernels)      181 ->  10    486 ->  11
+#pragma once
+
+#include <type_traits>
+
+#include "pbz_fast_common.h"
+
+namespace pbz {
+namespace brick {
+namespace {
+
+using fast::bf16_t;
+using fast::f16_t;
+using fast::get_index;
+using fast::put_index;
+
+// n / d for n < 2^31: with s = ceil(log2 d) and m = floor(2^(31 + s) / d) + 1 the product exceeds n 2^(31 + s) / d by less
+// than 2^(31 + s) / d, which never carries the quotient to the next integer
+struct Divisor {
+  uint32_t d, m, shift;
+};
+Divisor make_divisor(int64_t d) {
+  Divisor v;
+  uint32_t s = 0;
+  while ((int64_t(1) << s) < d) ++s;
+  v.d = uint32_t(d);
+  v.shift = 31 + s;
+  v.m = uint32_t((uint64_t(1) << v.shift) / uint64_t(d)) + 1;
+  return v;
+}
+__device__ __forceinline__ uint32_t divide(uint32_t n, const Divisor& v, uint32_t* rest) {
+  const uint32_t q = uint32_t((uint64_t(n) * v.m) >> v.shift);
+  *rest = n - q * v.d;
+  return q;
+}
+
+struct BrickGeom {
+  uint32_t n_blocks;
+  Divisor gx, gy, gz, gw;              // blocks along each dimension; what precedes them is folded (block extents 1)
+  int64_t sy, sz, sw, sb;              // elements from one row, plane, ... to the next
+  int lx, ly, lz, lw;                  // entries of the last block along each dimension that lie in the array
+  int whole;                           // every block lies in the array
+  int xtype, ntype, itype, kept;
+  int per_round;                       // blocks whose span of F is in LDS at a time
+  uint32_t region;                     // bytes of a wave's LDS
+  double r;
+  const uint16_t* places;
+};
+
+// Values a lane holds of blocks of the shape.  FP64 work holds 32 where two outer dimensions at most remain: with 64 (128
+// registers, twice where the layout changes) it spills or leaves one wave per SIMD: 4^4 blocks of FP64, 16x32x128x256,
+// compress 70 us with 64, 42 with 32; decompress 53 and 50; 2x8x8 FP32 / i16, 256x512x512: 158 and 104, 126 and 119
+constexpr int lane_values(bool wide, int bw, int bz, int by, int bx) {
+  if (!wide || bx > 16) return 64;
+  const int rows = bw * bz * by, ra = 32 / bx;
+  if (rows * bx <= 32) return 32;
+  const int in = ra >= rows ? rows : (ra % (by * bz) == 0 ? by * bz : (ra % by == 0 ? by : 1));
+  const int outer = (bw > 1 && in < rows) + (bz > 1 && in < by * bz) + (by > 1 && in < by);
+  return outer <= 2 && rows / in <= 16 ? 32 : 64;
+}
+
+template <typename T, int BW_, int BZ_, int BY_, int BX_>
+struct Shape {
+  static constexpr int BW = BW_, BZ = BZ_, BY = BY_, BX = BX_;
+  static constexpr int ROWS = BW * BZ * BY, VOL = ROWS * BX;
+  static constexpr int VALUES = lane_values(sizeof(T) == 8, BW, BZ, BY, BX);    // a lane's
+  static constexpr int PER_LANE = VOL < VALUES ? VALUES / VOL : 1; // blocks a lane holds
+  static constexpr int LANES = VOL < VALUES ? 1 : VOL / VALUES;    // lanes a block takes
+  static constexpr int NB = VOL < VALUES ? 64 * PER_LANE : 64 / LANES; // blocks of a tile
+  static constexpr int RA = VOL < VALUES ? ROWS : VALUES / BX;     // rows per lane (and block)
+  // rows of the dimensions that are whole in layout A, and of the outer ones
+  static constexpr int IN = RA >= ROWS ? ROWS : (RA % (BY * BZ) == 0 ? BY * BZ : (RA % BY == 0 ? BY : 1));
+  static constexpr int OUT = ROWS / IN;
+  static_assert(BX <= VALUES && LANES <= 64 && RA % IN == 0, "a lane holds whole rows, and whole inner dimensions");
+  static_assert(OUT <= VALUES, "a lane holds every outer index");
+  static constexpr int BXB = OUT == 1 ? BX : (VALUES / OUT < BX ? VALUES / OUT : BX);
+  static constexpr int NR = OUT == 1 ? RA : VALUES / (OUT * BXB);
+  static constexpr int XG = BX / BXB;                              // groups of columns
+  // the outer dimensions, from the inside: E1 and E2
+  static constexpr int E1 = OUT == 1 ? 1 : (IN == BY * BZ ? BW : (IN == BY ? BZ : BY));
+  static constexpr int E2 = OUT / E1;
+};
+
+template <typename T, typename S>
+struct Exchange {
+  static constexpr int CH = S::BXB < 16 / int(sizeof(T)) ? S::BXB : 16 / int(sizeof(T));    // values per slot
+  static constexpr int ROUNDS = S::BXB / CH;
+  static constexpr int BYTES = S::LANES == 1 ? 0 : 64 * S::VALUES / ROUNDS * int(sizeof(T));
+  struct __attribute__((aligned(CH * sizeof(T)))) Slot { T v[CH]; };
+  // slots of eight consecutive lanes should differ modulo 8 on both sides: the bits that vary from lane to lane, which
+  // are above bit 2, are folded onto the low three
+  static __device__ __forceinline__ int slot(int b, int row, int xg) {
+    const int q = (b * S::ROWS + row) * S::XG + xg;
+    return q ^ ((q >> 3) & 7) ^ ((q >> 6) & 7);
+  }
+  // kToB: v (layout A) -> u (layout B); otherwise back
+  template <bool kToB>
+  static __device__ __forceinline__ void run(uint8_t* lds, int lane, T* v, T* u) {
+    Slot* st = reinterpret_cast<Slot*>(lds);
+    const int b = lane % S::NB, s = lane / S::NB;
+    const int sx = s % S::XG, sr = s / S::XG;
+#pragma unroll
+    for (int rd = 0; rd < ROUNDS; ++rd) {
+      if (rd) wave_lds_sync();
+      if constexpr (kToB) {
+#pragma unroll
+        for (int i = 0; i < S::RA; ++i)
+#pragma unroll
+          for (int xg = 0; xg < S::XG; ++xg) {
+            Slot t;
+#pragma unroll
+            for (int e = 0; e < CH; ++e) t.v[e] = v[i * S::BX + xg * S::BXB + rd * CH + e];
+            st[slot(b, s * S::RA + i, xg)] = t;
+          }
+      } else {
+#pragma unroll
+        for (int o = 0; o < S::OUT; ++o)
+#pragma unroll
+          for (int j = 0; j < S::NR; ++j) {
+            Slot t;
+#pragma unroll
+            for (int e = 0; e < CH; ++e) t.v[e] = u[(o * S::NR + j) * S::BXB + rd * CH + e];
+            st[slot(b, o * S::IN + sr * S::NR + j, sx)] = t;
+          }
+      }
+      wave_lds_sync();
+      if constexpr (kToB) {
+#pragma unroll
+        for (int o = 0; o < S::OUT; ++o)
+#pragma unroll
+          for (int j = 0; j < S::NR; ++j) {
+            const Slot t = st[slot(b, o * S::IN + sr * S::NR + j, sx)];
+#pragma unroll
+            for (int e = 0; e < CH; ++e) u[(o * S::NR + j) * S::BXB + rd * CH + e] = t.v[e];
+          }
+      } else {
+#pragma unroll
+        for (int i = 0; i < S::RA; ++i)
+#pragma unroll
+          for (int xg = 0; xg < S::XG; ++xg) {
+            const Slot t = st[slot(b, s * S::RA + i, xg)];
+#pragma unroll
+            for (int e = 0; e < CH; ++e) v[i * S::BX + xg * S::BXB + rd * CH + e] = t.v[e];
+          }
+      }
+    }
+    wave_lds_sync();                       // the span of F uses the same LDS
+  }
+};
+
+// the dimensions whole in layout A, of one block's RA x BX values
+template <int TF, typename T, typename S, bool kForward>
+__device__ __forceinline__ void inner_transforms(T* v) {
+  auto along_x = [&]() {
+#pragma unroll
+    for (int i = 0; i < S::RA; ++i) {
+      if constexpr (kForward) tf_forward<TF, T, S::BX, 1>(v + i * S::BX);
+      else tf_inverse<TF, T, S::BX, 1, S::BX>(v + i * S::BX);
+    }
+  };
+  // lines of n rows `stride` rows apart in runs of n * stride rows
+  auto along_rows = [&](auto n_tag, auto stride_tag) {
+    constexpr int n = decltype(n_tag)::value, stride = decltype(stride_tag)::value;
+    if constexpr (n > 1) {
+#pragma unroll
+      for (int run = 0; run < S::RA / (n * stride); ++run)
+#pragma unroll
+        for (int k = 0; k < stride * S::BX; ++k) {
+          T* line = v + run * n * stride * S::BX + k;
+          if constexpr (kForward) tf_forward<TF, T, n, stride * S::BX>(line);
+          else tf_inverse<TF, T, n, stride * S::BX, n>(line);
+        }
+    }
+  };
+  constexpr int ny = S::IN >= S::BY ? S::BY : 1;
+  constexpr int nz = S::IN >= S::BY * S::BZ ? S::BZ : 1;
+  constexpr int nw = S::IN >= S::BY * S::BZ * S::BW ? S::BW : 1;
+  using y_t = std::integral_constant<int, ny>;
+  using z_t = std::integral_constant<int, nz>;
+  using w_t = std::integral_constant<int, nw>;
+  if constexpr (kForward) {
+    along_x();
+    along_rows(y_t(), std::integral_constant<int, 1>());
+    along_rows(z_t(), std::integral_constant<int, ny>());
+    along_rows(w_t(), std::integral_constant<int, ny * nz>());
+  } else {
+    along_rows(w_t(), std::integral_constant<int, ny * nz>());
+    along_rows(z_t(), std::integral_constant<int, ny>());
+    along_rows(y_t(), std::integral_constant<int, 1>());
+    along_x();
+  }
+}
+
+template <int TF, typename T, typename S, bool kForward>
+__device__ __forceinline__ void outer_transforms(T* u) {
+  constexpr int step = S::NR * S::BXB;
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    const bool first = (pass == 0) == kForward;            // the inner of the two outer dimensions
+    if (first) {
+      if constexpr (S::E1 > 1) {
+#pragma unroll
+        for (int o = 0; o < S::E2; ++o)
+#pragma unroll
+          for (int k = 0; k < step; ++k) {
+            if constexpr (kForward) tf_forward<TF, T, S::E1, step>(u + o * S::E1 * step + k);
+            else tf_inverse<TF, T, S::E1, step, S::E1>(u + o * S::E1 * step + k);
+          }
+      }
+    } else {
+      if constexpr (S::E2 > 1) {
+#pragma unroll
+        for (int k = 0; k < S::E1 * step; ++k) {
+          if constexpr (kForward) tf_forward<TF, T, S::E2, S::E1 * step>(u + k);
+          else tf_inverse<TF, T, S::E2, S::E1 * step, S::E2>(u + k);
+        }
+      }
+    }
+  }
+}
+
+// ---- the array ---------------------------------------------------------------------------------------------------
+struct Place {               // of a block, for one lane
+  int64_t origin;            // element offset of its first row that the lane holds (clamped rows: of its first row)
+  int ly, lz, lw;            // how many of the coordinates from the lane's first row on lie in the array
+  bool tail;                 // the last block of its rows
+};
+
+// block k; first: the lane's first row in the block
+template <typename S>
+__device__ __forceinline__ Place place_of(const BrickGeom& g, uint32_t k, int first, int64_t* block_origin) {
+  uint32_t kx, ky = 0, kz = 0, kw = 0;
+  uint32_t rest = divide(k, g.gx, &kx);
+  if (g.gy.d > 1) rest = divide(rest, g.gy, &ky);          // uniform
+  if (g.gz.d > 1) rest = divide(rest, g.gz, &kz);
+  if (g.gw.d > 1) rest = divide(rest, g.gw, &kw);
+  const int64_t at = int64_t(rest) * g.sb + int64_t(kw) * S::BW * g.sw + int64_t(kz) * S::BZ * g.sz +
+                     int64_t(ky) * S::BY * g.sy + int64_t(kx) * S::BX;
+  *block_origin = at;
+  const int y0 = first % S::BY, z0 = first / S::BY % S::BZ, w0 = first / (S::BY * S::BZ);
+  Place p;
+  p.origin = at + y0 * g.sy + z0 * g.sz + w0 * g.sw;
+  p.tail = kx == g.gx.d - 1;
+  p.ly = (ky == g.gy.d - 1 ? g.ly : S::BY) - y0;
+  p.lz = (kz == g.gz.d - 1 ? g.lz : S::BZ) - z0;
+  p.lw = (kw == g.gw.d - 1 ? g.lw : S::BW) - w0;
+  return p;
+}
+
+// row i of the lane's: offset from its first, and whether it lies in the array
+template <typename S>
+__device__ __forceinline__ int64_t row_offset(const BrickGeom& g, int i) {
+  return (i % S::BY) * g.sy + (i / S::BY % S::BZ) * g.sz + (i / (S::BY * S::BZ)) * g.sw;
+}
+template <typename S>
+__device__ __forceinline__ bool row_inside(const Place& p, int i) {
+  bool in = true;
+  if (S::BY > 1) in = in && i % S::BY < p.ly;
+  if (S::BZ > 1) in = in && i / S::BY % S::BZ < p.lz;
+  if (S::BW > 1) in = in && i / (S::BY * S::BZ) < p.lw;
+  return in;
+}
+
+constexpr int kStoreBytes = 8192;      // of LDS that rows pass through on their way out, unless a row of every lane is more
+
+// pieces of a row: 16 bytes, or the whole row where it is shorter
+template <typename XT, typename S>
+struct Piece {
+  static constexpr int BYTES = S::BX * int(sizeof(XT)) < 16 ? S::BX * int(sizeof(XT)) : 16;
+  static constexpr int PER = BYTES / int(sizeof(XT)), COUNT = S::BX / PER;
+  struct __attribute__((packed, aligned(sizeof(XT) < 4 ? 2 : 4))) Loose { uint32_t w[BYTES / 4]; };
+  struct __attribute__((aligned(BYTES))) Aligned { uint32_t w[BYTES / 4]; };
+  template <typename T>
+  static __device__ __forceinline__ void unpack(const uint32_t* w, T* out) {
+    if constexpr (sizeof(XT) == 8) {
+#pragma unroll
+      for (int e = 0; e < PER; ++e)
+        out[e] = T(__longlong_as_double((long long)((uint64_t(w[2 * e + 1]) << 32) | w[2 * e])));
+    } else if constexpr (sizeof(XT) == 4) {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) out[e] = T(__uint_as_float(w[e]));
+    } else {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const uint16_t h = uint16_t(w[e / 2] >> (16 * (e & 1)));
+        if constexpr (std::is_same<XT, bf16_t>::value) out[e] = T(bf16_bits_to_float(h));
+        else out[e] = T(float(__builtin_bit_cast(_Float16, h)));
+      }
+    }
+  }
+  // one rounding from T to the array's type
+  template <typename T>
+  static __device__ __forceinline__ uint16_t half_bits(T v) {
+    if constexpr (std::is_same<XT, bf16_t>::value) return sizeof(T) == 8 ? double_to_bf16_bits(double(v)) : float_to_bf16_bits(float(v));
+    else return __builtin_bit_cast(uint16_t, sizeof(T) == 8 ? double_to_f16(double(v)) : _Float16(float(v)));
+  }
+  template <typename T>
+  static __device__ __forceinline__ void pack(const T* v, uint32_t* w) {
+    if constexpr (sizeof(XT) == 8) {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const uint64_t bits = uint64_t(__double_as_longlong(double(v[e])));
+        w[2 * e] = uint32_t(bits);
+        w[2 * e + 1] = uint32_t(bits >> 32);
+      }
+    } else if constexpr (sizeof(XT) == 4) {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) w[e] = __float_as_uint(float(v[e]));
+    } else {
+#pragma unroll
+      for (int e = 0; e < PER; e += 2) w[e / 2] = uint32_t(half_bits<T>(v[e])) | (uint32_t(half_bits<T>(v[e + 1])) << 16);
+    }
+  }
+};
+
+// the lane's RA rows of a block into v, padding as zeros
+template <typename T, typename XT, typename S>
+__device__ __forceinline__ void load_rows(const BrickGeom& g, const XT* x, const Place& p, int64_t block_origin, T* v) {
+  using P = Piece<XT, S>;
+  constexpr int N = S::RA * P::COUNT;
+  if (g.whole) {                                           // uniform
+    typename P::Aligned raw[N];
+#pragma unroll
+    for (int i = 0; i < S::RA; ++i)
+#pragma unroll
+      for (int k = 0; k < P::COUNT; ++k)
+        raw[i * P::COUNT + k] = *reinterpret_cast<const typename P::Aligned*>(x + p.origin + row_offset<S>(g, i) + k * P::PER);
+#pragma unroll
+    for (int i = 0; i < N; ++i) P::template unpack<T>(raw[i].w, v + i * P::PER);
+    return;
+  }
+  // Rows that start anywhere.  Rows outside the array: the block's first one instead, zeroed below.  In the last block of a
+  // row a piece that reaches beyond it is read from as much further to the left (a row has a piece's elements at least),
+  // and shifted into place.
+  typename P::Loose raw[N];
+#pragma unroll
+  for (int i = 0; i < S::RA; ++i) {
+    const int64_t row = row_inside<S>(p, i) ? p.origin + row_offset<S>(g, i) : block_origin;
+#pragma unroll
+    for (int k = 0; k < P::COUNT; ++k) {
+      const int over = (k + 1) * P::PER - g.lx;            // uniform
+      raw[i * P::COUNT + k] = *reinterpret_cast<const typename P::Loose*>(x + row + k * P::PER - (p.tail && over > 0 ? over : 0));
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < S::RA; ++i) {
+    const bool in = row_inside<S>(p, i);
+#pragma unroll
+    for (int k = 0; k < P::COUNT; ++k) {
+      T* out = v + i * S::BX + k * P::PER;
+      P::template unpack<T>(raw[i * P::COUNT + k].w, out);
+      const int over = (k + 1) * P::PER - g.lx;
+      if (over > 0) {                                      // uniform
+#pragma unroll
+        for (int sh = 1; sh < P::PER; sh *= 2)
+          if (over & sh) {
+#pragma unroll
+            for (int e = 0; e < P::PER; ++e)
+              out[e] = p.tail ? (e + sh < P::PER ? out[e + sh < P::PER ? e + sh : 0] : T(0)) : out[e];
+          }
+        if (over >= P::PER) {
+#pragma unroll
+          for (int e = 0; e < P::PER; ++e) out[e] = p.tail ? T(0) : out[e];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < P::PER; ++e) out[e] = in ? out[e] : T(0);
+    }
+  }
+}
+
+// The lane's RA rows of a block to the array.  Rows of several pieces leave through LDS: written as they are, an instruction
+// would store every second to sixteenth piece of the run that neighbouring blocks' rows are (decompress of 8192^2 FP32 in
+// 8x16 blocks 110 us, 78 as here; in 32x32 blocks 135 and 101; 4x8x8 of the same size 77 and 67).  Piece k of lane L goes
+// to slot L COUNT + k, and 64 consecutive slots are stored at a time, each by a lane that has got lane L's place from it.
+// active: the lane's block exists
+template <bool kWhole, typename T, typename XT, typename S>
+__device__ __forceinline__ void store_rows(const BrickGeom& g, uint8_t* lds, int lane, XT* y, const Place& p, bool active,
+                                           const T* v) {
+  using P = Piece<XT, S>;
+  constexpr int COUNT = P::COUNT;
+  uint32_t rows = 0;                                       // which of the lane's rows lie in the array
+#pragma unroll
+  for (int i = 0; i < S::RA; ++i) rows |= row_inside<S>(p, i) ? 1u << i : 0u;
+  const uint32_t flags = active ? rows | (p.tail ? 1u << 31 : 0u) : 0u;
+  static_assert(S::RA <= 16, "rows and the tail's mark share a word");
+  auto put_piece = [&](int64_t origin, uint32_t f, int i, int k, const uint32_t* w) {
+    XT* at = y + origin + row_offset<S>(g, i) + k * P::PER;
+    if constexpr (kWhole) {
+      if (f != 0u) {
+        typename P::Aligned raw;
+#pragma unroll
+        for (int e = 0; e < P::BYTES / 4; ++e) raw.w[e] = w[e];
+        *reinterpret_cast<typename P::Aligned*>(at) = raw;
+      }
+    } else if ((f >> i) & 1u) {
+      if (!(f >> 31) || (k + 1) * P::PER <= g.lx) {
+        typename P::Loose raw;
+#pragma unroll
+        for (int e = 0; e < P::BYTES / 4; ++e) raw.w[e] = w[e];
+        *reinterpret_cast<typename P::Loose*>(at) = raw;
+      } else {
+#pragma unroll
+        for (int e = 0; e < P::PER; ++e)
+          if (k * P::PER + e < g.lx) {
+            if constexpr (sizeof(XT) == 8) at[e] = __longlong_as_double((long long)((uint64_t(w[2 * e + 1]) << 32) | w[2 * e]));
+            else if constexpr (sizeof(XT) == 4) at[e] = __uint_as_float(w[e]);
+            else at[e].bits = uint16_t(w[e / 2] >> (16 * (e & 1)));
+          }
+      }
+    }
+  };
+  if constexpr (COUNT == 1) {
+#pragma unroll
+    for (int i = 0; i < S::RA; ++i) {
+      uint32_t w[P::BYTES / 4];
+      P::template pack<T>(v + i * S::BX, w);
+      put_piece(p.origin, flags, i, 0, w);
+    }
+  } else {
+    constexpr int FIT = kStoreBytes / (1024 * COUNT);      // rows of every lane that the LDS holds
+    constexpr int BATCH = FIT < 1 ? 1 : (FIT < S::RA ? FIT : S::RA);
+    auto slot = [](int i) { return i ^ ((i >> 3) & 7) ^ ((i >> 6) & 7); };
+    int64_t origin[COUNT];
+    uint32_t f[COUNT];
+#pragma unroll
+    for (int t = 0; t < COUNT; ++t) {
+      const int from = (t * 64 + lane) / COUNT;
+      origin[t] = __shfl((long long)p.origin, from, 64);
+      f[t] = __shfl(flags, from, 64);
+    }
+    uint4* st = reinterpret_cast<uint4*>(lds);
+#pragma unroll
+    for (int i0 = 0; i0 < S::RA; i0 += BATCH) {
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i)
+#pragma unroll
+        for (int k = 0; k < COUNT; ++k) {
+          uint32_t w[4];
+          P::template pack<T>(v + (i0 + i) * S::BX + k * P::PER, w);
+          st[i * 64 * COUNT + slot(lane * COUNT + k)] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+      wave_lds_sync();
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i)
+#pragma unroll
+        for (int t = 0; t < COUNT; ++t) {
+          const uint4 q = st[i * 64 * COUNT + slot(t * 64 + lane)];
+          const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+          put_piece(origin[t], f[t], i0 + i, (t * 64 + lane) % COUNT, w);
+        }
+      wave_lds_sync();
+    }
+  }
+}
+
+// f(XT()) for the array's type
+template <typename F>
+__device__ __forceinline__ void by_array_type(int xtype, F f) {
+  switch (xtype) {
+    case PBZ_F64: f(double()); break;
+    case PBZ_F32: f(float()); break;
+    case PBZ_BF16: f(bf16_t()); break;
+    default: f(f16_t()); break;
+  }
+}
+template <typename F>
+__device__ __forceinline__ void by_index_type(int itype, F f) {
+  switch (itype) {
+    case PBZ_I8: f(int8_t()); break;
+    case PBZ_I16: f(int16_t()); break;
+    default: f(int32_t()); break;
+  }
+}
+
+// rint(t) as an integer for |t| below 2^22 (FP32) / 2^31 (FP64), see pbz_tiled.hip
+__device__ __forceinline__ uint32_t round_bits(float t) { return __float_as_uint(t + 12582912.0f); }
+__device__ __forceinline__ uint32_t round_bits(double t) { return uint32_t(__builtin_bit_cast(uint64_t, t + 6755399441055744.0)); }
+
+// the places of kCount (1, 2, 4, or a multiple of 8) entries in a row of the table, in 16-bit halves of w
+template <int kCount>
+__device__ __forceinline__ void load_place_row(const uint16_t* pos, uint32_t* w) {
+  if constexpr (kCount == 1) {
+    w[0] = pos[0];
+  } else if constexpr (kCount == 2) {
+    w[0] = *reinterpret_cast<const uint32_t*>(pos);
+  } else if constexpr (kCount == 4) {
+    const uint2 t = *reinterpret_cast<const uint2*>(pos);
+    w[0] = t.x; w[1] = t.y;
+  } else {
+#pragma unroll
+    for (int k = 0; k < kCount / 8; ++k) {
+      const uint4 t = reinterpret_cast<const uint4*>(pos)[k];
+      w[4 * k] = t.x; w[4 * k + 1] = t.y; w[4 * k + 2] = t.z; w[4 * k + 3] = t.w;
+    }
+  }
+}
+template <typename IT>
+__device__ __forceinline__ uint32_t place_address(const uint32_t* w, int e, uint32_t base, uint32_t aside) {
+  const uint32_t p = (e & 1) ? w[e >> 1] >> 16 : w[e >> 1] & 0xffffu;
+  const uint32_t at = base + p * uint32_t(sizeof(IT));
+  return at < aside ? at : aside;
+}
+
+// kCount packed indices from LDS address `at` (a multiple of 4, or of kCount bytes where that is less)
+template <typename IT, int kCount>
+__device__ __forceinline__ void put_run(uint8_t* lds, uint32_t at, const uint32_t* q) {
+  constexpr int PER = fast::IdxPack<IT>::per;
+  if constexpr (kCount < PER) {
+#pragma unroll
+    for (int e = 0; e < kCount; ++e) put_index<IT>(lds, at + e * uint32_t(sizeof(IT)), q[e]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < kCount / PER; ++k) *reinterpret_cast<uint32_t*>(lds + at + 4 * k) = fast::IdxPack<IT>::pack(q + k * PER);
+  }
+}
+template <typename IT, int kCount>
+__device__ __forceinline__ void get_run(const uint8_t* lds, uint32_t at, int* f) {
+  constexpr int PER = fast::IdxPack<IT>::per;
+  if constexpr (kCount < PER) {
+#pragma unroll
+    for (int e = 0; e < kCount; ++e) f[e] = get_index<IT>(lds, at + e * uint32_t(sizeof(IT)));
+  } else {
+#pragma unroll
+    for (int k = 0; k < kCount / PER; ++k) {
+      const uint32_t w = *reinterpret_cast<const uint32_t*>(lds + at + 4 * k);
+#pragma unroll
+      for (int e = 0; e < PER; ++e) f[k * PER + e] = fast::IdxPack<IT>::get(w, e);
+    }
+  }
+}
+
+// Walks the lane's values in layout B: f(block of the tile, first entry in the block, first value, count tag) for each
+// run of BXB values whose entries are consecutive.
+template <typename S, typename F>
+__device__ __forceinline__ void each_run(int lane, F f) {
+  if constexpr (S::PER_LANE > 1) {
+#pragma unroll
+    for (int p = 0; p < S::PER_LANE; ++p)
+#pragma unroll
+      for (int i = 0; i < S::ROWS; ++i) f(p * 64 + lane, i * S::BX, p * S::VOL + i * S::BX);
+  } else {
+    const int b = lane % S::NB, s = lane / S::NB, sx = s % S::XG, sr = s / S::XG;
+#pragma unroll
+    for (int o = 0; o < S::OUT; ++o)
+#pragma unroll
+      for (int j = 0; j < S::NR; ++j)
+        f(b, (o * S::IN + sr * S::NR + j) * S::BX + sx * S::BXB, (o * S::NR + j) * S::BXB);
+  }
+}
+
+template <int TF, typename T, typename S>
+__global__ __launch_bounds__(256, 2) void k_compress_brick(BrickGeom g, const void* __restrict__ x, void* __restrict__ N,
+                                                        void* __restrict__ F) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int lane = threadIdx.x & 63;
+  uint8_t* st = smem + (threadIdx.x >> 6) * g.region;
+  const uint32_t tile = blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t k0 = tile * S::NB;
+  if (k0 >= g.n_blocks) return;                            // uniform over the wave
+  const int n_active = int(g.n_blocks - k0 < uint32_t(S::NB) ? g.n_blocks - k0 : S::NB);
+  T v[S::VALUES], u_[S::LANES > 1 ? S::VALUES : 1];
+  T* u = S::LANES > 1 ? u_ : v;
+  by_array_type(g.xtype, [&](auto tag) {
+    using XT = decltype(tag);
+#pragma unroll
+    for (int p = 0; p < S::PER_LANE; ++p) {
+      const int b = S::PER_LANE > 1 ? p * 64 + lane : lane % S::NB;
+      int64_t block_origin;
+      const Place at = place_of<S>(g, k0 + (b < n_active ? b : n_active - 1), S::LANES > 1 ? lane / S::NB * S::RA : 0, &block_origin);
+      load_rows<T, XT, S>(g, static_cast<const XT*>(x), at, block_origin, v + p * S::VOL);
+    }
+  });
+#pragma unroll
+  for (int p = 0; p < S::PER_LANE; ++p) inner_transforms<TF, T, S, true>(v + p * S::VOL);
+  if constexpr (S::LANES > 1) {
+    Exchange<T, S>::template run<true>(st, lane, v, u);
+    outer_transforms<TF, T, S, true>(u);
+  }
+  T most[S::PER_LANE], inv[S::PER_LANE];
+#pragma unroll
+  for (int p = 0; p < S::PER_LANE; ++p) {
+    constexpr int kValues = S::PER_LANE > 1 ? S::VOL : S::VALUES;
+    T m = T(0);
+#pragma unroll
+    for (int i = 0; i < kValues; ++i) m = fmax(m, fabs(u[p * S::VOL + i]));
+    if constexpr (S::LANES > 1) {
+#pragma unroll
+      for (int off = S::NB; off < 64; off <<= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    }
+    most[p] = m;
+    inv[p] = m > T(0) ? T(1) / m : T(0);
+    const int b = S::PER_LANE > 1 ? p * 64 + lane : lane % S::NB;
+    if (b < n_active && lane / S::NB == 0) store_float(N, g.ntype, int64_t(k0) + b, m);
+  }
+  // (r C) / N from the correctly rounded reciprocal with one remainder correction, as in pbz_tiled.hip
+  const T r = T(g.r);
+  by_index_type(g.itype, [&](auto tag) {
+    using IT = decltype(tag);
+    if constexpr (sizeof(T) == 8 || sizeof(IT) == 1) {
+      const int bytes = g.kept * int(sizeof(IT));
+      const uint32_t aside = g.region - 256 + uint32_t(lane) * 4u;
+      for (int first = 0; first < n_active; first += g.per_round) {
+        const int count = n_active - first < g.per_round ? n_active - first : g.per_round;
+        uint8_t* dst = static_cast<uint8_t*>(F) + (int64_t(k0) + first) * bytes;
+        const int phase = phase_of(dst);
+        const bool runs = g.kept == S::VOL && (phase & 3) == 0;             // uniform: entries are their own places
+        each_run<S>(lane, [&](int b, int entry, int value) {
+          if (b >= first && b < first + count) {
+            const int p = S::PER_LANE > 1 ? value / S::VOL : 0;
+            const uint32_t base = uint32_t(phase + (b - first) * bytes);
+            uint32_t q[S::BXB];
+#pragma unroll
+            for (int e = 0; e < S::BXB; ++e) {
+              const T a = r * u[value + e];
+              const T quo = a * inv[p];
+              q[e] = round_bits(fma(fma(-quo, most[p], a), inv[p], quo));
+            }
+            if (runs) {
+              put_run<IT, S::BXB>(st, base + uint32_t(entry) * uint32_t(sizeof(IT)), q);
+            } else {
+              uint32_t places[(S::BXB + 1) / 2];
+              load_place_row<S::BXB>(g.places + entry, places);
+#pragma unroll
+              for (int e = 0; e < S::BXB; ++e) put_index<IT>(st, place_address<IT>(places, e, base, aside), q[e]);
+            }
+          }
+        });
+        wave_lds_sync();
+        unstage_span(st, dst, count * bytes);
+        wave_lds_sync();
+      }
+    }
+  });
+}
+
+template <int TF, typename T, typename S>
+__global__ __launch_bounds__(256, 2) void k_decompress_brick(BrickGeom g, const void* __restrict__ N, const void* __restrict__ F,
+                                                          void* __restrict__ y) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int lane = threadIdx.x & 63;
+  uint8_t* st = smem + (threadIdx.x >> 6) * g.region;
+  const uint32_t tile = blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t k0 = tile * S::NB;
+  if (k0 >= g.n_blocks) return;                            // uniform over the wave
+  const int n_active = int(g.n_blocks - k0 < uint32_t(S::NB) ? g.n_blocks - k0 : S::NB);
+  T v[S::VALUES], u_[S::LANES > 1 ? S::VALUES : 1];
+  T* u = S::LANES > 1 ? u_ : v;
+  T scale[S::PER_LANE];
+#pragma unroll
+  for (int p = 0; p < S::PER_LANE; ++p) {
+    const int b = S::PER_LANE > 1 ? p * 64 + lane : lane % S::NB;
+    scale[p] = load_float<T>(N, g.ntype, int64_t(k0) + (b < n_active ? b : n_active - 1)) / T(g.r);   // Algorithm 3: N F / r
+  }
+#pragma unroll
+  for (int i = 0; i < S::VALUES; ++i) u[i] = T(0);                // blocks past the end
+  by_index_type(g.itype, [&](auto tag) {
+    using IT = decltype(tag);
+    if constexpr (sizeof(T) == 8 || sizeof(IT) == 1) {
+      const int bytes = g.kept * int(sizeof(IT));
+      const uint8_t* lo = static_cast<const uint8_t*>(F);
+      const uint8_t* hi = lo + int64_t(g.n_blocks) * bytes;
+      const uint32_t aside = g.region - 256 + uint32_t(lane) * 4u;
+      for (int first = 0; first < n_active; first += g.per_round) {
+        const int count = n_active - first < g.per_round ? n_active - first : g.per_round;
+        const uint8_t* src = lo + (int64_t(k0) + first) * bytes;
+        const int phase = phase_of(src);
+        const bool runs = g.kept == S::VOL && (phase & 3) == 0;
+        put_index<int32_t>(st, aside, 0u);
+        stage_span<4>(lo, hi, src, count * bytes, st);
+        wave_lds_sync();
+        each_run<S>(lane, [&](int b, int entry, int value) {
+          if (b >= first && b < first + count) {
+            const int p = S::PER_LANE > 1 ? value / S::VOL : 0;
+            const uint32_t base = uint32_t(phase + (b - first) * bytes);
+            int f[S::BXB];
+            if (runs) {
+              get_run<IT, S::BXB>(st, base + uint32_t(entry) * uint32_t(sizeof(IT)), f);
+            } else {
+              uint32_t places[(S::BXB + 1) / 2];
+              load_place_row<S::BXB>(g.places + entry, places);
+#pragma unroll
+              for (int e = 0; e < S::BXB; ++e) f[e] = get_index<IT>(st, place_address<IT>(places, e, base, aside));
+            }
+#pragma unroll
+            for (int e = 0; e < S::BXB; ++e) u[value + e] = scale[p] * T(f[e]);
+          }
+        });
+        wave_lds_sync();
+      }
+    }
+  });
+  if constexpr (S::LANES > 1) {
+    outer_transforms<TF, T, S, false>(u);
+    Exchange<T, S>::template run<false>(st, lane, v, u);
+  }
+#pragma unroll
+  for (int p = 0; p < S::PER_LANE; ++p) inner_transforms<TF, T, S, false>(v + p * S::VOL);
+  by_array_type(g.xtype, [&](auto tag) {
+    using XT = decltype(tag);
+#pragma unroll
+    for (int p = 0; p < S::PER_LANE; ++p) {
+      const int b = S::PER_LANE > 1 ? p * 64 + lane : lane % S::NB;
+      int64_t block_origin;
+      const Place at = place_of<S>(g, k0 + (b < n_active ? b : n_active - 1), S::LANES > 1 ? lane / S::NB * S::RA : 0, &block_origin);
+      if (g.whole) store_rows<true, T, XT, S>(g, st, lane, static_cast<XT*>(y), at, b < n_active, v + p * S::VOL);
+      else store_rows<false, T, XT, S>(g, st, lane, static_cast<XT*>(y), at, b < n_active, v + p * S::VOL);
+    }
+  });
+}
+
+// ---- host side -----------------------------------------------------------------------------------------------------
+// fills the geometry; false when the array does not fold into it
+bool make_brick(const pbz_codec* c, const Geom& geo, const void* array, int xtype, const DeviceTables* t, int bw, int bz, int by,
+                int bx, BrickGeom* g) {
+  const int nd = c->ndim;
+  const int want[4] = {bw, bz, by, bx};
+  int64_t ext[4] = {1, 1, 1, 1}, lead = 1;
+  for (int d = 0; d < nd; ++d) {
+    const int slot = 4 - (nd - d);
+    if (slot < 0) {
+      if (c->block[d] != 1) return false;
+      lead *= geo.shape[d];
+    } else {
+      if (c->block[d] != want[slot]) return false;
+      ext[slot] = geo.shape[d];
+    }
+  }
+  for (int slot = 0; slot < 4 - nd; ++slot)
+    if (want[slot] != 1) return false;
+  if (geo.n_blocks >= (int64_t(1) << 31) || (reinterpret_cast<uintptr_t>(array) & 15u) != 0) return false;
+  int64_t grid[4];
+  bool whole = true;
+  int last[4];
+  for (int i = 0; i < 4; ++i) {
+    grid[i] = (ext[i] + want[i] - 1) / want[i];
+    last[i] = int(ext[i] - (grid[i] - 1) * want[i]);
+    whole = whole && last[i] == want[i];
+  }
+  const int piece = bx * ftype_bytes(xtype) < 16 ? bx : 16 / ftype_bytes(xtype);
+  if (ext[3] < piece) return false;                        // a row holds a piece's elements at least
+  g->n_blocks = uint32_t(geo.n_blocks);
+  g->gw = make_divisor(grid[0]);
+  g->gz = make_divisor(grid[1]);
+  g->gy = make_divisor(grid[2]);
+  g->gx = make_divisor(grid[3]);
+  g->sy = ext[3];
+  g->sz = g->sy * ext[2];
+  g->sw = g->sz * ext[1];
+  g->sb = g->sw * ext[0];
+  g->lw = last[0];
+  g->lz = last[1];
+  g->ly = last[2];
+  g->lx = last[3];
+  g->whole = whole ? 1 : 0;
+  g->xtype = xtype;
+  g->ntype = int(c->ftype);
+  g->itype = int(c->itype);
+  g->kept = c->kept;
+  g->r = c->r;
+  g->places = t->places;
+  return true;
+}
+
+constexpr int kSpanBytes = 8192;                 // of F in LDS at a time, unless one block is larger
+
+template <typename T, typename S, bool kStore>
+dim3 brick_launch(BrickGeom* g, int* threads, size_t* lds) {
+  const int bytes = g->kept * itype_bytes(g->itype);
+  int per = S::NB;
+  while (per > 1 && per * bytes > kSpanBytes) per /= 2;
+  g->per_round = per;
+  const int span = (15 + per * bytes + 15) / 16 * 16 + 256;
+  int region = span > Exchange<T, S>::BYTES ? span : Exchange<T, S>::BYTES;
+  const int pieces = S::BX * ftype_bytes(g->xtype) / 16;
+  if (kStore && pieces > 1) {
+    const int rows = 1024 * pieces > kStoreBytes ? 1024 * pieces : kStoreBytes;
+    if (region < rows) region = rows;
+  }
+  g->region = uint32_t(region);
+  int waves = 4;
+  while (waves > 1 && waves * region > 64 * 1024) waves /= 2;
+  *threads = 64 * waves;
+  *lds = size_t(region) * waves;
+  const int64_t tiles = (int64_t(g->n_blocks) + S::NB - 1) / S::NB;
+  return dim3(unsigned((tiles + waves - 1) / waves));
+}
+
+template <int TF, typename T, typename S>
+void compress_with(BrickGeom g, const void* x, void* N, void* F, hipStream_t s) {
+  int threads;
+  size_t lds;
+  const dim3 grid = brick_launch<T, S, false>(&g, &threads, &lds);
+  hipLaunchKernelGGL((k_compress_brick<TF, T, S>), grid, dim3(threads), lds, s, g, x, N, F);
+}
+template <int TF, typename T, typename S>
+void decompress_with(BrickGeom g, const void* N, const void* F, void* y, hipStream_t s) {
+  int threads;
+  size_t lds;
+  const dim3 grid = brick_launch<T, S, true>(&g, &threads, &lds);
+  hipLaunchKernelGGL((k_decompress_brick<TF, T, S>), grid, dim3(threads), lds, s, g, N, F, y);
+}
+
+// Whether blocks of the shape are taken here for the codec's arithmetic.  Lines of 64 in FP64 are not: the dense kernels' direct
+// sums are the more accurate there (decompressed values, rms relative to theirs: 4.6e-15 with the split transform; in FP32
+// work it is the other way round, 1.6e-7 dense and 9.6e-8 split)
+template <typename T, int BX>
+constexpr bool kTaken = BX < 64 || sizeof(T) == 4;
+
+template <typename T, int BW, int BZ, int BY, int BX>
+int compress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* x, int xtype, void* N, void* F,
+                   hipStream_t s) {
+  if constexpr (kTaken<T, BX>) {
+    BrickGeom g;
+    if (!make_brick(c, geo, x, xtype, t, BW, BZ, BY, BX, &g)) return 0;
+    using S = Shape<T, BW, BZ, BY, BX>;
+    if (c->transform == PBZ_TRANSFORM_HAAR) compress_with<kTfHaar, T, S>(g, x, N, F, s);
+    else compress_with<kTfDct, T, S>(g, x, N, F, s);
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+  return 0;
+}
+template <typename T, int BW, int BZ, int BY, int BX>
+int decompress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* N, const void* F, void* y,
+                     int ytype, hipStream_t s) {
+  if constexpr (kTaken<T, BX>) {
+    BrickGeom g;
+    if (!make_brick(c, geo, y, ytype, t, BW, BZ, BY, BX, &g)) return 0;
+    using S = Shape<T, BW, BZ, BY, BX>;
+    if (c->transform == PBZ_TRANSFORM_HAAR) decompress_with<kTfHaar, T, S>(g, N, F, y, s);
+    else decompress_with<kTfDct, T, S>(g, N, F, y, s);
+    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+  }
+  return 0;
+}
+
+// Defines the two entry points of a part from its list of shapes X(BW, BZ, BY, BX)
+#define PBZ_DEFINE_BRICK_PART(PART, SHAPES)                                                                             \
+  int PART##_compress(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* x, int xtype, void* N,    \
+                      void* F, hipStream_t s) {                                                                         \
+    int r = 0;                                                                                                          \
+    SHAPES(PBZ_BRICK_COMPRESS_ROW)                                                                                      \
+    return r;                                                                                                           \
+  }                                                                                                                     \
+  int PART##_decompress(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* N, const void* F,       \
+                        void* y, int ytype, hipStream_t s) {                                                            \
+    int r = 0;                                                                                                          \
+    SHAPES(PBZ_BRICK_DECOMPRESS_ROW)                                                                                    \
+    return r;                                                                                                           \
+  }
+#define PBZ_BRICK_COMPRESS_ROW(W, Z, Y, XX)                                                                             \
+  if (r == 0)                                                                                                           \
+    r = c->compute_f64 ? compress_shape<double, W, Z, Y, XX>(c, geo, t, x, xtype, N, F, s)                              \
+                       : compress_shape<float, W, Z, Y, XX>(c, geo, t, x, xtype, N, F, s);
+#define PBZ_BRICK_DECOMPRESS_ROW(W, Z, Y, XX)                                                                           \
+  if (r == 0)                                                                                                           \
+    r = c->compute_f64 ? decompress_shape<double, W, Z, Y, XX>(c, geo, t, N, F, y, ytype, s)                            \
+                       : decompress_shape<float, W, Z, Y, XX>(c, geo, t, N, F, y, ytype, s);
+
+}  // namespace
+
+// the parts: a translation unit each
+#define PBZ_BRICK_PARTS(X) X(lines) X(small) X(flat) X(wide) X(planes) X(cubes) X(tesseracts) X(long_tesseracts)
+#define PBZ_BRICK_DECLARE(PART)                                                                                         \
+  int PART##_compress(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* x, int xtype, void* N,    \
+                      void* F, hipStream_t s);                                                                          \
+  int PART##_decompress(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* N, const void* F,       \
+                        void* y, int ytype, hipStream_t s);
+PBZ_BRICK_PARTS(PBZ_BRICK_DECLARE)
+#undef PBZ_BRICK_DECLARE
+
+}  // namespace brick
+}  // namespace pbz

@@ -1,0 +1,11 @@
+// Block shapes of pbz_brick.h, a translation unit of their own.
+#include "pbz_brick.h"
+
+namespace pbz {
+namespace brick {
+
+#define PBZ_SHAPES(X) X(1, 1, 16, 16) X(1, 1, 32, 32)
+PBZ_DEFINE_BRICK_PART(wide, PBZ_SHAPES)
+
+}  // namespace brick
+}  // namespace pbz

@@ -103,6 +103,12 @@ int try_compress_masked(const pbz_codec* c, const Geom& g, const uint16_t* place
 int try_decompress_masked(const pbz_codec* c, const Geom& g, const uint16_t* places, const void* N, const void* F, void* y,
                           int ytype, hipStream_t s);
 
+// general kernels for a list of block shapes (pbz_brick.h); 1 when they handled the call, 0 when they do not cover it
+int try_compress_brick(const pbz_codec* c, const Geom& g, const DeviceTables* t, const void* x, int xtype, void* N, void* F,
+                       hipStream_t s);
+int try_decompress_brick(const pbz_codec* c, const Geom& g, const DeviceTables* t, const void* N, const void* F, void* y,
+                         int ytype, hipStream_t s);
+
 // element-wise compressed-space operations
 int launch_negate(const pbz_codec* c, int64_t n_blocks, const void* Fin, void* Fout, hipStream_t s);
 int launch_mul_scalar(const pbz_codec* c, int64_t n_blocks, const void* Nin, const void* Fin, double x,

@@ -1,4 +1,5 @@
-// General codec kernels for every setting without a specialised kernel whose block extents are at most 32:
+// General codec kernels for every setting whose block extents are at most 32 and that neither a specialised kernel nor
+// pbz_brick.h (its list of shapes, arrays on 16-byte boundaries with rows of a piece at least) takes:
 // any dimensionality up to 8, any such block shape, any mask, every array / working / index type, any shape.
 //
 // A workgroup owns a tile of G consecutive blocks (block-major order, so usually neighbours along the last
