@@ -16,17 +16,18 @@
 // tile's blocks are, which moves in 16-byte pieces.
 // The block shape is a template argument, so every index and bound is a constant but for the lane's own and the block's
 // place in the array; types, mask and geometry are arguments, with one uniform branch around each loop.
-// Memory bounds the FP32 work (4.3 - 5.1 TB/s of the copy's 5.6), registers the FP64 work (two waves per SIMD).  Measured,
-// us, with pbz_tiled.hip -> here:
+// Memory bounds the FP32 work (4.3 - 5.1 TB/s of the copy's 5.6; wide blocks less, in the regrouped stores), FP64 work what
+// is in flight (four waves per SIMD, two where blocks leave a lane 64 values).  Measured, us, with pbz_tiled.hip -> here:
 //                                      compress      decompress
-//   256x512x512 FP32, 4x8x8, i8        110 ->  64    100 ->  67
-//   32x64x128x256 FP32, 2x4x8x8, i8    129 ->  64    112 ->  67
-//   8192^2 FP32, 4x4, i8               101 ->  67     96 ->  68
-//   8192^2 FP32, 8x16, i8               99 ->  71    107 ->  78
-//   8192^2 FP32, 32x32, i8             134 ->  93    118 -> 101
-//   256x512x512 FP32, 2x8x8, i16       168 ->  99    166 -> 111
-//   16x32x128x256 FP64, 4^4, i32        65 ->  43     58 ->  50
-//   509x509x251 bf16, 8x8x8, i8        138 ->  55    120 ->  58
+//   256x512x512 FP32, 4x8x8, i8        110 ->  66    100 ->  67
+//   32x64x128x256 FP32, 2x4x8x8, i8    129 ->  66    112 ->  66
+//   8192^2 FP32, 4x4, i8               101 ->  68     96 ->  68
+//   8192^2 FP32, 8x16, i8               99 ->  68    107 ->  86
+//   8192^2 FP32, 32x32, i8             134 ->  85    118 ->  99
+//   256x512x512 FP32, 2x8x8, i16       168 ->  87    166 ->  91
+//   16x32x128x256 FP64, 4^4, i32        65 ->  44     58 ->  47
+//   512x512x256 bf16, 8x8x8, i16       193 ->  81    200 -> 131
+//   509x509x251 bf16, 8x8x8, i8        138 ->  52    120 ->  59
 //   4 Mi FP32, 64 (dense kernels)      181 ->  10    486 ->  11
 #pragma once
 
@@ -78,7 +79,7 @@ struct BrickGeom {
 
 // Values a lane holds of blocks of the shape.  FP64 work holds 32 where two outer dimensions at most remain: with 64 (128
 // registers, twice where the layout changes) it spills or leaves one wave per SIMD: 4^4 blocks of FP64, 16x32x128x256,
-// compress 70 us with 64, 42 with 32; decompress 53 and 50; 2x8x8 FP32 / i16, 256x512x512: 158 and 104, 126 and 119
+// compress 70 us with 64, 44 with 32; decompress 53 and 47; 2x8x8 FP32 / i16, 256x512x512: 158 and 87, 126 and 91
 constexpr int lane_values(bool wide, int bw, int bz, int by, int bx) {
   if (!wide || bx > 16) return 64;
   const int rows = bw * bz * by, ra = 32 / bx;
@@ -112,15 +113,22 @@ struct Shape {
 
 template <typename T, typename S>
 struct Exchange {
-  static constexpr int CH = S::BXB < 16 / int(sizeof(T)) ? S::BXB : 16 / int(sizeof(T));    // values per slot
+  // Values per slot: 16 bytes, less where that would put the whole tile into LDS at once (16 KiB a wave: two waves per SIMD).
+  // In two rounds at least: round trip of a 4-D FP64 field in 4^4 blocks 165 -> 153 us, 4096^2 FP16 / i16 in 32x32 blocks
+  // compress 51 -> 33, decompress 77 -> 47
+  static constexpr int FIT = 16 / int(sizeof(T)), HALF = S::BXB > 1 ? S::BXB / 2 : 1;
+  static constexpr int CH = HALF < FIT ? HALF : FIT;
   static constexpr int ROUNDS = S::BXB / CH;
   static constexpr int BYTES = S::LANES == 1 ? 0 : 64 * S::VALUES / ROUNDS * int(sizeof(T));
   struct __attribute__((aligned(CH * sizeof(T)))) Slot { T v[CH]; };
-  // slots of eight consecutive lanes should differ modulo 8 on both sides: the bits that vary from lane to lane, which
-  // are above bit 2, are folded onto the low three
+  // The slots of the lanes that LDS serves at once (256 bytes' worth: 16 lanes of 16 bytes, 32 of 8, 64 of 4) should differ
+  // modulo their number on both sides: the bits that vary from lane to lane are above that and folded onto the low ones.
+  // At most two lanes meet, for most shapes none
   static __device__ __forceinline__ int slot(int b, int row, int xg) {
     const int q = (b * S::ROWS + row) * S::XG + xg;
-    return q ^ ((q >> 3) & 7) ^ ((q >> 6) & 7);
+    if constexpr (sizeof(Slot) == 16) return q ^ ((q >> 4) & 15) ^ ((q >> 8) & 15);
+    else if constexpr (sizeof(Slot) == 8) return q ^ ((q >> 5) & 31);
+    else return q ^ ((q >> 6) & 63);
   }
   // kToB: v (layout A) -> u (layout B); otherwise back
   template <bool kToB>
@@ -342,65 +350,76 @@ struct Piece {
   }
 };
 
-// the lane's RA rows of a block into v, padding as zeros
+// the lane's RA rows of a block into v, padding as zeros; sixteen pieces in flight (more would be registers for FP64 arrays
+// in FP32 work only)
 template <typename T, typename XT, typename S>
 __device__ __forceinline__ void load_rows(const BrickGeom& g, const XT* x, const Place& p, int64_t block_origin, T* v) {
   using P = Piece<XT, S>;
-  constexpr int N = S::RA * P::COUNT;
+  constexpr int ROWS = P::COUNT * S::RA <= 16 ? S::RA : (P::COUNT >= 16 ? 1 : 16 / P::COUNT), N = ROWS * P::COUNT;
   if (g.whole) {                                           // uniform
-    typename P::Aligned raw[N];
 #pragma unroll
-    for (int i = 0; i < S::RA; ++i)
+    for (int i0 = 0; i0 < S::RA; i0 += ROWS) {
+      typename P::Aligned raw[N];
+      if (i0 > 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int k = 0; k < P::COUNT; ++k)
-        raw[i * P::COUNT + k] = *reinterpret_cast<const typename P::Aligned*>(x + p.origin + row_offset<S>(g, i) + k * P::PER);
+      for (int i = 0; i < ROWS; ++i)
 #pragma unroll
-    for (int i = 0; i < N; ++i) P::template unpack<T>(raw[i].w, v + i * P::PER);
+        for (int k = 0; k < P::COUNT; ++k)
+          raw[i * P::COUNT + k] =
+              *reinterpret_cast<const typename P::Aligned*>(x + p.origin + row_offset<S>(g, i0 + i) + k * P::PER);
+#pragma unroll
+      for (int i = 0; i < N; ++i) P::template unpack<T>(raw[i].w, v + i0 * S::BX + i * P::PER);
+    }
     return;
   }
   // Rows that start anywhere.  Rows outside the array: the block's first one instead, zeroed below.  In the last block of a
   // row a piece that reaches beyond it is read from as much further to the left (a row has a piece's elements at least),
   // and shifted into place.
-  typename P::Loose raw[N];
 #pragma unroll
-  for (int i = 0; i < S::RA; ++i) {
-    const int64_t row = row_inside<S>(p, i) ? p.origin + row_offset<S>(g, i) : block_origin;
+  for (int i0 = 0; i0 < S::RA; i0 += ROWS) {
+    typename P::Loose raw[N];
+    if (i0 > 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int k = 0; k < P::COUNT; ++k) {
-      const int over = (k + 1) * P::PER - g.lx;            // uniform
-      raw[i * P::COUNT + k] = *reinterpret_cast<const typename P::Loose*>(x + row + k * P::PER - (p.tail && over > 0 ? over : 0));
-    }
-  }
+    for (int i = 0; i < ROWS; ++i) {
+      const int64_t row = row_inside<S>(p, i0 + i) ? p.origin + row_offset<S>(g, i0 + i) : block_origin;
 #pragma unroll
-  for (int i = 0; i < S::RA; ++i) {
-    const bool in = row_inside<S>(p, i);
-#pragma unroll
-    for (int k = 0; k < P::COUNT; ++k) {
-      T* out = v + i * S::BX + k * P::PER;
-      P::template unpack<T>(raw[i * P::COUNT + k].w, out);
-      const int over = (k + 1) * P::PER - g.lx;
-      if (over > 0) {                                      // uniform
-#pragma unroll
-        for (int sh = 1; sh < P::PER; sh *= 2)
-          if (over & sh) {
-#pragma unroll
-            for (int e = 0; e < P::PER; ++e)
-              out[e] = p.tail ? (e + sh < P::PER ? out[e + sh < P::PER ? e + sh : 0] : T(0)) : out[e];
-          }
-        if (over >= P::PER) {
-#pragma unroll
-          for (int e = 0; e < P::PER; ++e) out[e] = p.tail ? T(0) : out[e];
-        }
+      for (int k = 0; k < P::COUNT; ++k) {
+        const int over = (k + 1) * P::PER - g.lx;          // uniform
+        raw[i * P::COUNT + k] =
+            *reinterpret_cast<const typename P::Loose*>(x + row + k * P::PER - (p.tail && over > 0 ? over : 0));
       }
+    }
 #pragma unroll
-      for (int e = 0; e < P::PER; ++e) out[e] = in ? out[e] : T(0);
+    for (int i = 0; i < ROWS; ++i) {
+      const bool in = row_inside<S>(p, i0 + i);
+#pragma unroll
+      for (int k = 0; k < P::COUNT; ++k) {
+        T* out = v + (i0 + i) * S::BX + k * P::PER;
+        P::template unpack<T>(raw[i * P::COUNT + k].w, out);
+        const int over = (k + 1) * P::PER - g.lx;
+        if (over > 0) {                                    // uniform
+#pragma unroll
+          for (int sh = 1; sh < P::PER; sh *= 2)
+            if (over & sh) {
+#pragma unroll
+              for (int e = 0; e < P::PER; ++e)
+                out[e] = p.tail ? (e + sh < P::PER ? out[e + sh < P::PER ? e + sh : 0] : T(0)) : out[e];
+            }
+          if (over >= P::PER) {
+#pragma unroll
+            for (int e = 0; e < P::PER; ++e) out[e] = p.tail ? T(0) : out[e];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < P::PER; ++e) out[e] = in ? out[e] : T(0);
+      }
     }
   }
 }
 
 // The lane's RA rows of a block to the array.  Rows of several pieces leave through LDS: written as they are, an instruction
 // would store every second to sixteenth piece of the run that neighbouring blocks' rows are (decompress of 8192^2 FP32 in
-// 8x16 blocks 110 us, 78 as here; in 32x32 blocks 135 and 101; 4x8x8 of the same size 77 and 67).  Piece k of lane L goes
+// 8x16 blocks 110 us, 86 as here; in 32x32 blocks 135 and 99; 4x8x8 of the same size 77 and 67).  Piece k of lane L goes
 // to slot L COUNT + k, and 64 consecutive slots are stored at a time, each by a lane that has got lane L's place from it.
 // active: the lane's block exists
 template <bool kWhole, typename T, typename XT, typename S>
@@ -624,6 +643,17 @@ __global__ __launch_bounds__(256, 2) void k_compress_brick(BrickGeom g, const vo
   }
   // (r C) / N from the correctly rounded reciprocal with one remainder correction, as in pbz_tiled.hip
   const T r = T(g.r);
+  uint32_t q[S::VALUES];
+#pragma unroll
+  for (int i = 0; i < S::VALUES; ++i) {
+    const int p = S::PER_LANE > 1 ? i / S::VOL : 0;
+    const T a = r * u[i];
+    const T quo = a * inv[p];
+    q[i] = round_bits(fma(fma(-quo, most[p], a), inv[p], quo));
+  }
+  // once for all index types and before anything is placed: 64 registers less than quotients formed at each place (FP64
+  // work: 98 instead of 214; compress of 512x512x256 bf16 / i16 in 8x8x8 blocks 108 -> 80 us)
+  __builtin_amdgcn_sched_barrier(0);
   by_index_type(g.itype, [&](auto tag) {
     using IT = decltype(tag);
     if constexpr (sizeof(T) == 8 || sizeof(IT) == 1) {
@@ -636,22 +666,14 @@ __global__ __launch_bounds__(256, 2) void k_compress_brick(BrickGeom g, const vo
         const bool runs = g.kept == S::VOL && (phase & 3) == 0;             // uniform: entries are their own places
         each_run<S>(lane, [&](int b, int entry, int value) {
           if (b >= first && b < first + count) {
-            const int p = S::PER_LANE > 1 ? value / S::VOL : 0;
             const uint32_t base = uint32_t(phase + (b - first) * bytes);
-            uint32_t q[S::BXB];
-#pragma unroll
-            for (int e = 0; e < S::BXB; ++e) {
-              const T a = r * u[value + e];
-              const T quo = a * inv[p];
-              q[e] = round_bits(fma(fma(-quo, most[p], a), inv[p], quo));
-            }
             if (runs) {
-              put_run<IT, S::BXB>(st, base + uint32_t(entry) * uint32_t(sizeof(IT)), q);
+              put_run<IT, S::BXB>(st, base + uint32_t(entry) * uint32_t(sizeof(IT)), q + value);
             } else {
               uint32_t places[(S::BXB + 1) / 2];
               load_place_row<S::BXB>(g.places + entry, places);
 #pragma unroll
-              for (int e = 0; e < S::BXB; ++e) put_index<IT>(st, place_address<IT>(places, e, base, aside), q[e]);
+              for (int e = 0; e < S::BXB; ++e) put_index<IT>(st, place_address<IT>(places, e, base, aside), q[value + e]);
             }
           }
         });
