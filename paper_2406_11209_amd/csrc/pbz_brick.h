@@ -22,8 +22,8 @@
 //   256x512x512 FP32, 4x8x8, i8        110 ->  66    100 ->  67
 //   32x64x128x256 FP32, 2x4x8x8, i8    129 ->  66    112 ->  66
 //   8192^2 FP32, 4x4, i8               101 ->  68     96 ->  68
-//   8192^2 FP32, 8x16, i8               99 ->  68    107 ->  86
-//   8192^2 FP32, 32x32, i8             134 ->  85    118 ->  99
+//   8192^2 FP32, 8x16, i8               99 ->  68    107 ->  79
+//   8192^2 FP32, 32x32, i8             134 ->  85    118 ->  90
 //   256x512x512 FP32, 2x8x8, i16       168 ->  87    166 ->  91
 //   16x32x128x256 FP64, 4^4, i32        65 ->  44     58 ->  47
 //   512x512x256 bf16, 8x8x8, i16       193 ->  81    200 -> 131
@@ -419,7 +419,7 @@ __device__ __forceinline__ void load_rows(const BrickGeom& g, const XT* x, const
 
 // The lane's RA rows of a block to the array.  Rows of several pieces leave through LDS: written as they are, an instruction
 // would store every second to sixteenth piece of the run that neighbouring blocks' rows are (decompress of 8192^2 FP32 in
-// 8x16 blocks 110 us, 86 as here; in 32x32 blocks 135 and 99; 4x8x8 of the same size 77 and 67).  Piece k of lane L goes
+// 8x16 blocks 110 us, 79 as here; in 32x32 blocks 135 and 90; 4x8x8 of the same size 77 and 67).  Piece k of lane L goes
 // to slot L COUNT + k, and 64 consecutive slots are stored at a time, each by a lane that has got lane L's place from it.
 // active: the lane's block exists
 template <bool kWhole, typename T, typename XT, typename S>
@@ -469,14 +469,6 @@ __device__ __forceinline__ void store_rows(const BrickGeom& g, uint8_t* lds, int
     constexpr int FIT = kStoreBytes / (1024 * COUNT);      // rows of every lane that the LDS holds
     constexpr int BATCH = FIT < 1 ? 1 : (FIT < S::RA ? FIT : S::RA);
     auto slot = [](int i) { return i ^ ((i >> 3) & 7) ^ ((i >> 6) & 7); };
-    int64_t origin[COUNT];
-    uint32_t f[COUNT];
-#pragma unroll
-    for (int t = 0; t < COUNT; ++t) {
-      const int from = (t * 64 + lane) / COUNT;
-      origin[t] = __shfl((long long)p.origin, from, 64);
-      f[t] = __shfl(flags, from, 64);
-    }
     uint4* st = reinterpret_cast<uint4*>(lds);
 #pragma unroll
     for (int i0 = 0; i0 < S::RA; i0 += BATCH) {
@@ -489,14 +481,21 @@ __device__ __forceinline__ void store_rows(const BrickGeom& g, uint8_t* lds, int
           st[i * 64 * COUNT + slot(lane * COUNT + k)] = make_uint4(w[0], w[1], w[2], w[3]);
         }
       wave_lds_sync();
+      // of the lanes' places in registers at a time (all of them, for all rows: 32x32 blocks 196 registers and 102 us; so 164
+      // and 90)
+      constexpr int TOGETHER = COUNT < 4 ? COUNT : 4;
+#pragma unroll TOGETHER
+      for (int t = 0; t < COUNT; ++t) {
+        const int from = (t * 64 + lane) / COUNT;
+        const int64_t origin = __shfl((long long)p.origin, from, 64);
+        const uint32_t f = __shfl(flags, from, 64);
 #pragma unroll
-      for (int i = 0; i < BATCH; ++i)
-#pragma unroll
-        for (int t = 0; t < COUNT; ++t) {
+        for (int i = 0; i < BATCH; ++i) {
           const uint4 q = st[i * 64 * COUNT + slot(t * 64 + lane)];
           const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-          put_piece(origin[t], f[t], i0 + i, (t * 64 + lane) % COUNT, w);
+          put_piece(origin, f, i0 + i, lane % COUNT, w);
         }
+      }
       wave_lds_sync();
     }
   }
