@@ -520,10 +520,6 @@ __device__ __forceinline__ void by_index_type(int itype, F f) {
   }
 }
 
-// rint(t) as an integer for |t| below 2^22 (FP32) / 2^31 (FP64), see pbz_tiled.hip
-__device__ __forceinline__ uint32_t round_bits(float t) { return __float_as_uint(t + 12582912.0f); }
-__device__ __forceinline__ uint32_t round_bits(double t) { return uint32_t(__builtin_bit_cast(uint64_t, t + 6755399441055744.0)); }
-
 // the places of kCount (1, 2, 4, or a multiple of 8) entries in a row of the table, in 16-bit halves of w
 template <int kCount>
 __device__ __forceinline__ void load_place_row(const uint16_t* pos, uint32_t* w) {
@@ -624,7 +620,7 @@ __global__ __launch_bounds__(256, 2) void k_compress_brick(BrickGeom g, const vo
     Exchange<T, S>::template run<true>(st, lane, v, u);
     outer_transforms<TF, T, S, true>(u);
   }
-  T most[S::PER_LANE], inv[S::PER_LANE];
+  fast::Binner<T> binner[S::PER_LANE];
 #pragma unroll
   for (int p = 0; p < S::PER_LANE; ++p) {
     constexpr int kValues = S::PER_LANE > 1 ? S::VOL : S::VALUES;
@@ -635,21 +631,13 @@ __global__ __launch_bounds__(256, 2) void k_compress_brick(BrickGeom g, const vo
 #pragma unroll
       for (int off = S::NB; off < 64; off <<= 1) m = fmax(m, __shfl_xor(m, off, 64));
     }
-    most[p] = m;
-    inv[p] = m > T(0) ? T(1) / m : T(0);
+    binner[p] = fast::Binner<T>(m, g.r);
     const int b = S::PER_LANE > 1 ? p * 64 + lane : lane % S::NB;
     if (b < n_active && lane / S::NB == 0) store_float(N, g.ntype, int64_t(k0) + b, m);
   }
-  // (r C) / N from the correctly rounded reciprocal with one remainder correction, as in pbz_tiled.hip
-  const T r = T(g.r);
   uint32_t q[S::VALUES];
 #pragma unroll
-  for (int i = 0; i < S::VALUES; ++i) {
-    const int p = S::PER_LANE > 1 ? i / S::VOL : 0;
-    const T a = r * u[i];
-    const T quo = a * inv[p];
-    q[i] = round_bits(fma(fma(-quo, most[p], a), inv[p], quo));
-  }
+  for (int i = 0; i < S::VALUES; ++i) q[i] = binner[S::PER_LANE > 1 ? i / S::VOL : 0].bits(u[i]);
   // once for all index types and before anything is placed: 64 registers less than quotients formed at each place (FP64
   // work: 98 instead of 214; compress of 512x512x256 bf16 / i16 in 8x8x8 blocks 108 -> 80 us)
   __builtin_amdgcn_sched_barrier(0);
@@ -696,11 +684,18 @@ __global__ __launch_bounds__(256, 2) void k_decompress_brick(BrickGeom g, const 
   const int n_active = int(g.n_blocks - k0 < uint32_t(S::NB) ? g.n_blocks - k0 : S::NB);
   T v[S::VALUES], u_[S::LANES > 1 ? S::VALUES : 1];
   T* u = S::LANES > 1 ? u_ : v;
+  constexpr bool kLinesOf64 = S::BX == 64;
+  constexpr T kFar = T(18446744073709551616.0);                   // 2^64
   T scale[S::PER_LANE];
+  bool small[S::PER_LANE];
 #pragma unroll
   for (int p = 0; p < S::PER_LANE; ++p) {
     const int b = S::PER_LANE > 1 ? p * 64 + lane : lane % S::NB;
-    scale[p] = load_float<T>(N, g.ntype, int64_t(k0) + (b < n_active ? b : n_active - 1)) / T(g.r);   // Algorithm 3: N F / r
+    const T n = load_float<T>(N, g.ntype, int64_t(k0) + (b < n_active ? b : n_active - 1));
+    // Algorithm 3: N F / r, the division hoisted per block.  Where N / r is below the normal numbers it would lose digits that the
+    // dense kernels, which divide N F, keep: lines of 64 were theirs, so N is scaled up and the products back down
+    small[p] = kLinesOf64 && n < T(1) / kFar;
+    scale[p] = (small[p] ? n * kFar : n) / T(g.r);
   }
 #pragma unroll
   for (int i = 0; i < S::VALUES; ++i) u[i] = T(0);                // blocks past the end
@@ -733,7 +728,10 @@ __global__ __launch_bounds__(256, 2) void k_decompress_brick(BrickGeom g, const 
               for (int e = 0; e < S::BXB; ++e) f[e] = get_index<IT>(st, place_address<IT>(places, e, base, aside));
             }
 #pragma unroll
-            for (int e = 0; e < S::BXB; ++e) u[value + e] = scale[p] * T(f[e]);
+            for (int e = 0; e < S::BXB; ++e) {
+              u[value + e] = scale[p] * T(f[e]);
+              if (kLinesOf64) u[value + e] *= small[p] ? T(1) / kFar : T(1);
+            }
           }
         });
         wave_lds_sync();

@@ -175,6 +175,59 @@ __device__ __forceinline__ uint32_t bin_bits(double t, double inv) {
   return uint32_t(__builtin_bit_cast(uint64_t, __builtin_fma(t, inv, 6755399441055744.0)));
 }
 
+// r C / N of a block by its correctly rounded reciprocal with one remainder correction, as the kernels that take any shape form it
+// (pbz_tiled.hip), so that those per block shape give the same indices for the same coefficients.  1 / N is infinite for the smallest N
+// and r C for the largest C: where N is far from one, r and N are scaled by a power of two, which is exact, and a = (r 2^k) C and
+// N 2^k stay in the range of the type for every finite N.
+template <typename T>
+struct Binner {
+  T r, n, inv;
+  __device__ __forceinline__ Binner() {}
+  __device__ __forceinline__ Binner(T most, double radius) {
+    constexpr T kFar = sizeof(T) == 8 ? T(1.3407807929942597e154) : T(18446744073709551616.0);      // 2^512, 2^64
+    const T scale = most < T(1) / kFar ? kFar : (most > kFar ? T(1) / kFar : T(1));
+    r = T(radius) * scale;
+    n = most * scale;
+    inv = n > T(0) ? T(1) / n : T(0);
+  }
+  __device__ __forceinline__ uint32_t bits(T c) const {
+    const T a = r * c;
+    const T quo = a * inv;
+    return bin_bits(T(1), fma(fma(-quo, n, a), inv, quo));
+  }
+};
+
+// r / N for the kernels that take any mask, and C with it.  r / N is infinite for N below 3.7e-37 (FP32, int8; FP64: 1.8e-304 with int16, 1.2e-299
+// with int32), which the kernels for any shape bin like any other: a wave that holds such a block scales its coefficients and
+// N up by a power of two, which is exact.  (The quotient of Binner instead, for every block: 3-9 % slower.)
+// kParts blocks of kCount values each, their maxima and factors in a row; one branch for all of them.
+template <typename T, int kCount, int kParts>
+__device__ __forceinline__ void bin_factors(const T* most, double r, T* c, T* inv) {
+  constexpr T kSmall = sizeof(T) == 8 ? T(1.0261342003245941e-289) : T(7.888609052210118e-31);      // 2^-960, 2^-100
+  constexpr T kUp = sizeof(T) == 8 ? T(1.3407807929942597e154) : T(18446744073709551616.0);         // 2^512, 2^64
+  bool small = false;
+#pragma unroll
+  for (int p = 0; p < kParts; ++p) {
+    inv[p] = most[p] > T(0) ? T(r) / most[p] : T(0);
+    small = small || (most[p] < kSmall && most[p] > T(0));
+  }
+  if (__any(small)) {
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) {
+      const bool up = most[p] < kSmall && most[p] > T(0);
+#pragma unroll
+      for (int i = 0; i < kCount; ++i) c[p * kCount + i] *= up ? kUp : T(1);
+      if (up) inv[p] = T(r) / (most[p] * kUp);
+    }
+  }
+}
+template <typename T, int kCount>
+__device__ __forceinline__ T bin_factor(T most, double r, T* c) {
+  T inv;
+  bin_factors<T, kCount, 1>(&most, r, c, &inv);
+  return inv;
+}
+
 // the low bytes / halves of `per` words gathered into one dword by byte permutes
 template <typename IT>
 struct IdxPack;   // kPer indices per dword

@@ -193,10 +193,10 @@ __global__ __launch_bounds__(128) void k_compress_cube16(FastGeom g, const XT* _
   for (int i = 0; i < 64; ++i) m = fmax(m, fabs(a[i]));
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) m = fmax(m, __shfl_xor(m, off, 64));
-  const T inv = m > T(0) ? T(g.r) / m : T(0);
   const int ky = lane & 15, zh = lane >> 4;
   const int64_t block = (bz * g.gy + by) * g.gx + bx;
   if constexpr (kMasked) {
+    const T inv = bin_factor<T, 64>(m, g.r, a);
     const int bytes = mask.kept * int(sizeof(IT));
     uint8_t* region = reinterpret_cast<uint8_t*>(buffer + wave * kCubeRegion);
     uint8_t* dst = reinterpret_cast<uint8_t*>(F) + block * bytes;
@@ -216,6 +216,7 @@ __global__ __launch_bounds__(128) void k_compress_cube16(FastGeom g, const XT* _
     unstage_span(region, dst, bytes);
     return;
   }
+  const T inv = m > T(0) ? T(g.r) / m : T(0);
   uint32_t w[4 * ROWW];
 #pragma unroll
   for (int zl = 0; zl < 4; ++zl)

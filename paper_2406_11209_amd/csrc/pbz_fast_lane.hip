@@ -134,7 +134,9 @@ __global__ __launch_bounds__(256) void k_compress_lane(FastGeom g, const XT* __r
   T m = T(0);
 #pragma unroll
   for (int i = 0; i < VOL; ++i) m = fmax(m, abs_t(v[i]));
-  const T inv = m > T(0) ? T(g.r) / m : T(0);
+  T inv = T(0);
+  if constexpr (kMasked) inv = bin_factor<T, VOL>(m, g.r, v);
+  else inv = m > T(0) ? T(g.r) / m : T(0);
 
   if constexpr (kMasked) {
     // Every lane knows its block's place in the span and the mask is the same for all of them: which entries are kept

@@ -133,10 +133,11 @@ constexpr uint32_t kOctAside = kOctMaskedSlots * 16 - 256;
 template <typename IT>
 constexpr int oct_mask_rounds() { return sizeof(IT) == 4 ? 2 : 1; }
 
-// the lane's row j of eight planes u of block bb, binned, to F
+// the lane's row j of eight planes u of block bb, whose maximum is `most`, binned, to F
 template <typename IT, typename T>
 __device__ __forceinline__ void oct_put_masked(const FastGeom& g, const MaskArgs<true>& mask, uint4* region, IT* F, int64_t tx,
-                                               int64_t block0, int lane, const T* u, T inv) {
+                                               int64_t block0, int lane, T* u, T most) {
+  const T inv = bin_factor<T, 64>(most, g.r, u);
   constexpr int kRounds = oct_mask_rounds<IT>(), kBlocks = 8 / kRounds;
   const int bb = lane >> 3, j = lane & 7;
   const int bytes = mask.kept * int(sizeof(IT));
@@ -305,13 +306,13 @@ __global__ __launch_bounds__(kOctWaves * 64) void k_compress_oct8(FastGeom g, co
   for (int i = 0; i < 64; ++i) m = fmaxf(m, fabsf(u[i]));
 #pragma unroll
   for (int off = 1; off < 8; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, 64));     // the 8 rows of the block
-  const float inv = m > 0.0f ? float(g.r) / m : 0.0f;
   if constexpr (kMasked) {
     const int64_t block0 = (bz * g.gy + by) * g.gx + tx * 8;
     if (j == 0 && tx * 8 + bb < g.gx) store_float(N, g.ntype, block0 + bb, m);
-    oct_put_masked<int8_t, float>(g, mask, st, F, tx, block0, lane, u, inv);
+    oct_put_masked<int8_t, float>(g, mask, st, F, tx, block0, lane, u, m);
     return;
   }
+  const float inv = m > 0.0f ? float(g.r) / m : 0.0f;
 
   // kept entries of this lane: z < KZ, x < KX when j < KY; staged in LDS at their position in the wave's span of F
   static_assert(8 * KEPT <= 8 * 64 * 16, "the staged F of a tile fits the exchange buffer");
@@ -788,14 +789,14 @@ __global__ __launch_bounds__(kOctWaves * 64) void k_compress_oct8_wide(FastGeom 
   for (int i = 0; i < 64; ++i) m = fmax(m, fabs(u[i]));
 #pragma unroll
   for (int off = 1; off < 8; off <<= 1) m = fmax(m, __shfl_xor(m, off, 64));     // the 8 rows of the block
-  const double inv = m > 0.0 ? g.r / m : 0.0;
   const int64_t block0 = (bz * g.gy + by) * g.gx + tx * 8;
   const bool inside = tx * 8 + bb < g.gx;
   if constexpr (kMasked) {
     if (inside && j == 0) store_float(N, g.ntype, block0 + bb, m);
-    oct_put_masked<IT, double>(g, mask, st, F, tx, block0, lane, u, inv);
+    oct_put_masked<IT, double>(g, mask, st, F, tx, block0, lane, u, m);
     return;
   }
+  const double inv = m > 0.0 ? g.r / m : 0.0;
   uint32_t w[8 * RW];
 #pragma unroll
   for (int zq = 0; zq < 8; ++zq)

@@ -132,8 +132,7 @@ __global__ __launch_bounds__(128) void k_compress_quad16(FastGeom g, const XT* _
     span = reinterpret_cast<uint8_t*>(F) + block0 * mask.kept * int(sizeof(IT));
     if constexpr (BZ == 1) load_places<2>(mask.pos + yrow * 16, places);
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  auto block_max = [&](int j) {
     T m = m4;
     if constexpr (BZ == 1) {
 #pragma unroll
@@ -141,8 +140,20 @@ __global__ __launch_bounds__(128) void k_compress_quad16(FastGeom g, const XT* _
 #pragma unroll
       for (int off = 1; off < 16; off <<= 1) m = fmax(m, __shfl_xor(m, off, 64));   // the 16 rows of the block
     }
-    const T inv = m > T(0) ? T(g.r) / m : T(0);
+    return m;
+  };
+  T most[4], factor[4];                                // masks
+  if constexpr (kMasked) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) most[j] = block_max(j);
+    if constexpr (BZ == 1) bin_factors<T, 16, 4>(most, g.r, u, factor);
+    else factor[0] = factor[1] = factor[2] = factor[3] = bin_factor<T, 64>(m4, g.r, u);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const T m = kMasked ? most[j] : block_max(j);
     if constexpr (kMasked) {
+      const T inv = factor[j];
       const int blk = Map::block_of(4 * j + bsub);
       if constexpr (BZ == 4) load_places<2>(mask.pos + (j * 16 + yrow) * 16, places);
       const uint32_t base = uint32_t(phase_of(span) + blk * mask.kept * int(sizeof(IT)));
@@ -154,6 +165,7 @@ __global__ __launch_bounds__(128) void k_compress_quad16(FastGeom g, const XT* _
       if (yrow == 0 && (BZ == 1 || j == 0) && tx * BPW + blk < g.gx) store_float(N, g.ntype, block0 + blk, m);
       continue;
     }
+    const T inv = m > T(0) ? T(g.r) / m : T(0);
     uint32_t w[ROWW];
 #pragma unroll
     for (int k = 0; k < ROWW; ++k) {
