@@ -50,6 +50,12 @@ struct StagedN {
       if (u * 64 < count) v[u] = load_N<kNType>(N, k0 + (i < count ? i : count - 1), f16);
     }
   }
+  __device__ __forceinline__ bool beyond(double limit, int count) const {         // any of the lane's, NaN included
+    bool any = false;
+#pragma unroll
+    for (int u = 0; u < kNPerLane; ++u) any = any || (u * 64 < count && !(fabs(v[u]) < limit));
+    return any;
+  }
   __device__ __forceinline__ void put(double* lds, int count) {
 #pragma unroll
     for (int u = 0; u < kNPerLane; ++u) {
@@ -112,7 +118,37 @@ struct Rebin {
 #pragma unroll
     for (int e = 0; e < kPer; ++e) q[e] = rint_to_int(div_by(kTwo ? c[e] : c[e] * r, scale, inv));
   }
+
+  // A block whose numbers are out of reach of the products with reciprocals above, the whole way by division: a scale whose reciprocal is
+  // infinite (below 5.6e-309) or whose own rounding leaves quotients beyond r (subnormal), infinite N (whose coefficients
+  // div_by would turn into NaN) and NaN.  NaN counts for nothing in the maximum, and becomes the index -r.  One index at a
+  // time: the path takes no registers from the others.  a, b, o: the block in LDS; one team of lanes.  Returns the new N.
+  // (Every block of a wave's tile that holds one such block goes this way: the others' indices come out the same.  The check for them
+  // costs the ordinary blocks 2-4 %: 2M blocks of 19 int16 indices, sum 64.1 -> 66.6 us.)
+  typedef typename std::conditional<kIType == PBZ_I8, int8_t, typename std::conditional<kIType == PBZ_I16, int16_t, int32_t>::type>::type index_t;
+  __device__ __forceinline__ double far_block(int t, int team, int kept, const uint8_t* a, const uint8_t* b, uint8_t* o) const {
+    double m = 0.0, n = 0.0;
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll 1
+      for (int j = t; j < kept; j += team) {
+        const double fa = double(reinterpret_cast<const index_t*>(a)[j]);
+        double c;
+        if (kTwo) c = unfused_sum_of_products(fa, n1, double(reinterpret_cast<const index_t*>(b)[j]), n2);
+        else c = (n1 * fa) / r + (j == 0 ? shift : 0.0);
+        m = fmax(m, fabs(c));
+        if (pass == 1) {
+          const double quo = n > 0.0 ? (kTwo ? c : c * r) / n : 0.0;
+          reinterpret_cast<index_t*>(o)[j] = index_t(fmin(fmax(rint(quo), -r), r));
+        }
+      }
+      for (int off = team >> 1; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+      n = kTwo ? m / r : m;
+    }
+    return n;
+  }
 };
+constexpr double kFarNumber = 0x1p960;             // below it, products with an index and sums of two of them are finite
 
 template <int kIType, int kNType, bool kTwo>
 __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const void* N1, const uint8_t* F1, const void* N2,
@@ -150,6 +186,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const
     if (kTwo) n2.put(nb, count);
     wave_lds_sync();
     const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : 0, po = phase_of(Fout + at);
+    // a block that needs far_block: after the others, which that keeps out of the registers of this loop
+    bool far = n1.beyond(kFarNumber, count) || (kTwo && n2.beyond(kFarNumber, count));
     for (int b0 = 0; b0 < count; b0 += per_round) {        // uniform: the lane exchanges below are convergent
       const int b = b0 + slot;
       const bool live = b < count;
@@ -190,7 +228,17 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const
           }
         }
       }
+      far = far || !(inv < kFarNumber);
       if (live && t == 0) store_N<kNType>(Nout, k0 + b, n, n_f16 != 0);
+    }
+    if (__any(far)) {
+      wave_lds_sync();                                     // other lanes' writes to the same places precede these
+      for (int b = slot; b < count; b += per_round) {
+        op.n1 = na[b];
+        op.n2 = kTwo ? sign2 * nb[b] : 0.0;
+        const double n = op.far_block(t, team, st.kept, sa + pa + b * st.bpb, sb + pb + b * st.bpb, so + po + b * st.bpb);
+        if (t == 0) store_N<kNType>(Nout, k0 + b, n, n_f16 != 0);
+      }
     }
     wave_lds_sync();
     unstage_span(so, Fout + at, len);

@@ -65,3 +65,47 @@ def test_lines_of_64_keep_their_digits_below_the_normal_numbers():
     # 6 u; the transform's passes round some twelve times, up to as much again each: 18 u.  N / 127 is 1e-40: rounded to a
     # multiple of u it is off by 7e-6 of itself, and the maxima of 1.7e-38 by some 90 u
     assert np.abs(y.cpu().numpy().astype(np.float64) - ref).max() <= 24 * 2.0 ** -149 + 2e-7 * np.abs(ref).max()
+
+
+def operand(n_blocks, kept, bits, N, seed):
+    """Random indices with a full range in every block, and the given N."""
+    g = np.random.Generator(np.random.PCG64(seed))
+    r = 2 ** (bits - 1) - 1
+    F = g.integers(-r, r + 1, (n_blocks, kept)).astype({8: np.int8, 16: np.int16, 32: np.int32}[bits])
+    F[:, 0] = r
+    return torch.from_numpy(np.asarray(N)).cuda(), torch.from_numpy(F).cuda()
+
+
+@pytest.mark.parametrize("bits", [8, 16, 32])
+@pytest.mark.parametrize("kept", [5, 19, 33])
+def test_rebinning_of_blocks_at_the_ends_of_the_range(kept, bits):
+    """Sum, difference and shift of blocks whose kept counts make no whole vectors, N from the smallest subnormal numbers up."""
+    mask = np.zeros(64, dtype=bool)
+    mask[:kept] = True
+    case = Case(np.zeros((8 * 24, 8)), None, "f64", (8, 8), bits, "f64", mask.reshape(8, 8))
+    scales = np.array([5e-324, 3e-322, 1e-320, 1e-310, 1e-308, 1e-305, 1e-300, 1.0, 1e150, 1e290, 1e298, 0.0])
+    N1, F1 = operand(24, kept, bits, np.tile(scales, 2), kept)
+    N2, F2 = operand(24, kept, bits, np.tile(scales, 2) * np.repeat([0.5, 3.0], 12), kept + 1)
+    for got, want in ((case.codec.add(N1, F1, N2, F2), po.add(case.oc(N1, F1), case.oc(N2, F2))),
+                      (case.codec.subtract(N1, F1, N2, F2), po.add(case.oc(N1, F1), po.negate(case.oc(N2, F2)))),
+                      (case.codec.add_scalar(N1, F1, 0.0), po.add_scalar(case.oc(N1, F1), 0.0))):
+        n, f = got[0].cpu().numpy(), got[1].cpu().numpy().astype(np.int64)
+        assert np.array_equal(n, want.N.reshape(-1))
+        r = 2 ** (bits - 1) - 1
+        # where N is subnormal its rounding can put a quotient beyond r: the index is then r
+        assert np.array_equal(f, np.clip(np.nan_to_num(want.t, nan=0.0).round(), -r, r).astype(np.int64))
+
+
+@pytest.mark.parametrize("kept", [5, 19, 33])
+def test_rebinning_keeps_infinities(kept):
+    """A block whose N has overflowed (FP16) stays infinite through the operations, and its neighbours stay what they are."""
+    mask = np.zeros(64, dtype=bool)
+    mask[:kept] = True
+    case = Case(np.zeros((8 * 6, 8)), None, "f64", (8, 8), 8, "f16", mask.reshape(8, 8))
+    N1, F1 = operand(6, kept, 8, np.array([1.0, np.inf, 2.0, np.inf, 0.5, 0.0], dtype=np.float16), kept)
+    N2, F2 = operand(6, kept, 8, np.array([1.0, 1.0, 2.0, 0.0, 0.5, 3.0], dtype=np.float16), kept + 1)
+    fine = [0, 2, 4, 5]
+    for got, plain in ((case.codec.add(N1, F1, N2, F2), case.codec.add(N1[fine], F1[fine], N2[fine], F2[fine])),
+                       (case.codec.add_scalar(N1, F1, 0.75), case.codec.add_scalar(N1[fine], F1[fine], 0.75))):
+        assert bool(torch.isinf(got[0][[1, 3]]).all())
+        assert torch.equal(got[0][fine], plain[0]) and torch.equal(got[1][fine], plain[1])
