@@ -338,67 +338,100 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
   const bool f16 = tail.n_f16 != 0;
   double sums[kNumSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
   const int64_t stride = int64_t(gridDim.x) * waves * st.blocks;
-  for (int64_t k0 = (int64_t(blockIdx.x) * waves + wave) * st.blocks; k0 < n_blocks; k0 += stride) {
-    const int count = n_blocks - k0 < st.blocks ? int(n_blocks - k0) : st.blocks;
-    const int64_t at = k0 * st.bpb;
-    StagedN<kNType> n1, n2;
-    n1.request(N1, seg0 + k0, count, f16);
-    if (kTwo) n2.request(N2, seg0 + k0, count, f16);
-    stage_span<2>(F1, a_end, F1 + at, count * st.bpb, sa);
-    if (kTwo) stage_span<2>(F2, b_end, F2 + at, count * st.bpb, sb);
-    n1.put(na, count);
-    if (kTwo) n2.put(nb, count);
-    wave_lds_sync();
-    const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : pa;
-    for (int b = slot; b < count; b += per_round) {
-      const double v1 = na[b], v2 = nb[b];
-      typename Dot<kIType>::acc_t s11 = 0, s12 = 0, s22 = 0;
-      double diff = 0.0;
-      for (int d = t; d < st.dwords; d += team) {
-        uint32_t a = block_dword(sa, pa + b * st.bpb, d, st.bpb);
-        uint32_t c = kTwo ? block_dword(sb, pb + b * st.bpb, d, st.bpb) : a;
-        if constexpr (kDiff) {
-          constexpr int kPer = PerDword<kIType>::value;
-          double fa[kPer], fb[kPer];
-          unpack_dword<kIType>(a, fa);
-          unpack_dword<kIType>(c, fb);
+  // A lane's sums that are no finite numbers at the end: an infinite N times a zero is NaN, and zero is what a block's padding is, and what
+  // the lane's own share of a block's indices may come to.  The wave then takes its blocks once more (far): without the
+  // padding, and with the integer sums of whole blocks.
+  bool far = false;                                          // uniform over the wave
+  for (;;) {
+    for (int64_t k0 = (int64_t(blockIdx.x) * waves + wave) * st.blocks; k0 < n_blocks; k0 += stride) {
+      const int count = n_blocks - k0 < st.blocks ? int(n_blocks - k0) : st.blocks;
+      const int64_t at = k0 * st.bpb;
+      StagedN<kNType> n1, n2;
+      n1.request(N1, seg0 + k0, count, f16);
+      if (kTwo) n2.request(N2, seg0 + k0, count, f16);
+      stage_span<2>(F1, a_end, F1 + at, count * st.bpb, sa);
+      if (kTwo) stage_span<2>(F2, b_end, F2 + at, count * st.bpb, sb);
+      n1.put(na, count);
+      if (kTwo) n2.put(nb, count);
+      wave_lds_sync();
+      const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : pa;
+      for (int b = slot; b < count; b += per_round) {
+        const double v1 = na[b], v2 = nb[b];
+        typename Dot<kIType>::acc_t s11 = 0, s12 = 0, s22 = 0;
+        double diff = 0.0;
+        for (int d = t; d < st.dwords; d += team) {
+          uint32_t a = block_dword(sa, pa + b * st.bpb, d, st.bpb);
+          uint32_t c = kTwo ? block_dword(sb, pb + b * st.bpb, d, st.bpb) : a;
+          if constexpr (kDiff) {
+            constexpr int kPer = PerDword<kIType>::value;
+            double fa[kPer], fb[kPer];
+            unpack_dword<kIType>(a, fa);
+            unpack_dword<kIType>(c, fb);
 #pragma unroll
-          for (int e = 0; e < kPer; ++e) {
-            const double x = v1 * fa[e] - v2 * fb[e];
-            diff += x * x;
-          }
-        } else {
-          if (kDC && d == 0) {                    // the first coefficient enters shifted by the pilot value
-            const double d1 = fma(v1, double(first_element<kIType>(a)), -K1);
-            sums[kS11] = fma(d1, d1, sums[kS11]);
-            sums[kD1] += d1;
-            a &= rest_of_first<kIType>();
+            for (int e = 0; e < kPer; ++e) {
+              const double x = v1 * fa[e] - v2 * fb[e];
+              diff += x * x;
+            }
+          } else {
+            if (kDC && d == 0) {                    // the first coefficient enters shifted by the pilot value
+              const double d1 = fma(v1, double(first_element<kIType>(a)), -K1);
+              sums[kS11] = fma(d1, d1, sums[kS11]);
+              sums[kD1] += d1;
+              a &= rest_of_first<kIType>();
+              if (kTwo) {
+                const double d2 = fma(v2, double(first_element<kIType>(c)), -K2);
+                sums[kS12] = fma(d1, d2, sums[kS12]);
+                sums[kS22] = fma(d2, d2, sums[kS22]);
+                sums[kD2] += d2;
+                c &= rest_of_first<kIType>();
+              }
+            }
+            s11 = Dot<kIType>::add(s11, a, a);
             if (kTwo) {
-              const double d2 = fma(v2, double(first_element<kIType>(c)), -K2);
-              sums[kS12] = fma(d1, d2, sums[kS12]);
-              sums[kS22] = fma(d2, d2, sums[kS22]);
-              sums[kD2] += d2;
-              c &= rest_of_first<kIType>();
+              s12 = Dot<kIType>::add(s12, a, c);
+              s22 = Dot<kIType>::add(s22, c, c);
             }
           }
-          s11 = Dot<kIType>::add(s11, a, a);
+        }
+        if constexpr (kDiff) {
+          if (far) {                                         // uniform
+            diff = 0.0;
+            constexpr int kPer = PerDword<kIType>::value;
+#pragma unroll 1
+            for (int j = t; j < st.kept; j += team) {
+              double fa[kPer], fb[kPer];
+              unpack_dword<kIType>(block_dword(sa, pa + b * st.bpb, j / kPer, st.bpb) >> (j % kPer * (32 / kPer)), fa);
+              unpack_dword<kIType>(block_dword(sb, pb + b * st.bpb, j / kPer, st.bpb) >> (j % kPer * (32 / kPer)), fb);
+              const double x = v1 * fa[0] - v2 * fb[0];
+              diff += x * x;
+            }
+          }
+          sums[kS11] += diff;
+        } else {
+          if (far) {                                         // uniform
+            for (int off = team >> 1; off > 0; off >>= 1) {
+              s11 += __shfl_xor(s11, off, 64);
+              s12 += __shfl_xor(s12, off, 64);
+              s22 += __shfl_xor(s22, off, 64);
+            }
+            if (t != 0) continue;
+          }
+          sums[kS11] = fma(double(s11), v1 * v1, sums[kS11]);
           if (kTwo) {
-            s12 = Dot<kIType>::add(s12, a, c);
-            s22 = Dot<kIType>::add(s22, c, c);
+            sums[kS12] = fma(double(s12), v1 * v2, sums[kS12]);
+            sums[kS22] = fma(double(s22), v2 * v2, sums[kS22]);
           }
         }
       }
-      if constexpr (kDiff) {
-        sums[kS11] += diff;
-      } else {
-        sums[kS11] = fma(double(s11), v1 * v1, sums[kS11]);
-        if (kTwo) {
-          sums[kS12] = fma(double(s12), v1 * v2, sums[kS12]);
-          sums[kS22] = fma(double(s22), v2 * v2, sums[kS22]);
-        }
-      }
+      wave_lds_sync();
     }
-    wave_lds_sync();
+    bool finite = true;
+#pragma unroll
+    for (int i = 0; i < kNumSums; ++i) finite = finite && fabs(sums[i]) < INFINITY;
+    if (far || __all(finite)) break;
+    far = true;
+#pragma unroll
+    for (int i = 0; i < kNumSums; ++i) sums[i] = 0.0;
   }
   reduce_tail(sums, tail, K1, K2, blockDim.x >> 6);
 }

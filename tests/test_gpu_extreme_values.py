@@ -109,3 +109,22 @@ def test_rebinning_keeps_infinities(kept):
                        (case.codec.add_scalar(N1, F1, 0.75), case.codec.add_scalar(N1[fine], F1[fine], 0.75))):
         assert bool(torch.isinf(got[0][[1, 3]]).all())
         assert torch.equal(got[0][fine], plain[0]) and torch.equal(got[1][fine], plain[1])
+
+
+@pytest.mark.parametrize("bits,kept", [(8, 5), (8, 19), (8, 33), (8, 63), (16, 5), (16, 19), (16, 63), (32, 19)])
+def test_reductions_keep_infinities(bits, kept):
+    """A block whose N has overflowed (FP16) makes norms, distances and products infinite, not NaN: not where its last indices
+    are padding, and not where most of them are zero."""
+    mask = np.zeros(64, dtype=bool)
+    mask[:kept] = True
+    case = Case(np.zeros((8 * 40, 8)), None, "f64", (8, 8), bits, "f16", mask.reshape(8, 8))
+    N1, F1 = operand(40, kept, bits, np.full(40, 1.5, dtype=np.float16), kept)
+    N2, F2 = operand(40, kept, bits, np.full(40, 0.5, dtype=np.float16), kept + 1)
+    N1[17] = float("inf")
+    F1[F1 == 0] = 1                              # infinity times a zero index is no number, and neither is a distance of it
+    assert case.codec.difference_norm2(N1, F1, N2, F2).item() == np.inf
+    F1[17, 1:] = 0
+    assert case.codec.norm2(N1, F1).item() == np.inf
+    assert case.codec.dot(N1, F1, N2, F2).item() == np.inf
+    assert case.codec.segmented("norm2", 4, 10, N1, F1).tolist()[1] == np.inf
+    assert np.isfinite(case.codec.segmented("norm2", 4, 10, N1, F1).cpu().numpy()[[0, 2, 3]]).all()
