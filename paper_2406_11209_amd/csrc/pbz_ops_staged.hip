@@ -19,25 +19,14 @@
 // waves per SIMD (80 registers, 128 bytes of spills: 106 us), spans of 1 or 4 KiB per wave and operand (15-35 % slower).
 #include "pbz_ops_common.h"
 #include "pbz_span.h"
+#include "pbz_stage_layout.h"
 
 namespace pbz {
 namespace ops {
 namespace {
 
-constexpr int kMaxWaves = 4;             // waves per workgroup, fewer when a wave's regions are large
 constexpr int kCached = 4;               // dwords of a block per lane that the rebinning kernels keep in registers
-constexpr int kTeamDwords = 4;           // a team is the fewest lanes with at most this many dwords each (64 at most)
-constexpr int kMaxBlocksPerWave = 256;
 constexpr int kNPerLane = kMaxBlocksPerWave / 64;
-
-struct Stage {
-  int kept;         // indices per block
-  int bpb;          // bytes of F per block
-  int dwords;       // dwords per block, the last one possibly partial
-  int team_shift;   // log2 of the lanes per block
-  int blocks;       // blocks per wave and tile, a multiple of the blocks per round (64 lanes over the team)
-  int region;       // bytes of an LDS region: a span at any phase and one word more, a multiple of 16
-};
 
 // N of `count` (at most kMaxBlocksPerWave) blocks from k0 on, widened: requested, then put away
 template <int kNType>
@@ -157,12 +146,11 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const
   extern __shared__ __align__(16) uint8_t smem[];
   constexpr int kPer = PerDword<kIType>::value;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-  const int wave_bytes = (kTwo ? 3 : 2) * st.region + (kTwo ? 2 : 1) * 8 * st.blocks;
-  uint8_t* sa = smem + wave * wave_bytes;
+  uint8_t* sa = smem + wave * wave_bytes(st, kTwo ? 3 : 2, kTwo ? 2 : 1);
   uint8_t* so = sa + st.region;
   uint8_t* sb = so + st.region;                            // used with two operands only
   double* na = reinterpret_cast<double*>(sa + (kTwo ? 3 : 2) * st.region);
-  double* nb = na + st.blocks;
+  double* nb = na + st.numbers / 8;
   const int team = 1 << st.team_shift, t = lane & (team - 1), slot = lane >> st.team_shift;
   const int per_round = 64 >> st.team_shift;
   const int steps = (st.dwords + team - 1) >> st.team_shift;          // dwords per lane, at most
@@ -271,11 +259,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_blockwise_staged(Stage st, c
                                                                      int64_t n_blocks, int n_f16) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-  const int wave_bytes = (kTwo ? 2 : 1) * (st.region + 8 * st.blocks);
-  uint8_t* sa = smem + wave * wave_bytes;
+  uint8_t* sa = smem + wave * wave_bytes(st, kTwo ? 2 : 1, kTwo ? 2 : 1);
   uint8_t* sb = kTwo ? sa + st.region : sa;
   double* na = reinterpret_cast<double*>(sa + (kTwo ? 2 : 1) * st.region);
-  double* nb = kTwo ? na + st.blocks : na;
+  double* nb = kTwo ? na + st.numbers / 8 : na;
   const int team = 1 << st.team_shift, t = lane & (team - 1), slot = lane >> st.team_shift;
   const int per_round = 64 >> st.team_shift;
   const uint8_t* a_end = F1 + n_blocks * st.bpb;
@@ -321,11 +308,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
                                                                   int64_t n_blocks, ReduceTail tail) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-  const int wave_bytes = (kTwo ? 2 : 1) * (st.region + 8 * st.blocks);
-  uint8_t* sa = smem + wave * wave_bytes;
+  uint8_t* sa = smem + wave * wave_bytes(st, kTwo ? 2 : 1, kTwo ? 2 : 1);
   uint8_t* sb = kTwo ? sa + st.region : sa;
   double* na = reinterpret_cast<double*>(sa + (kTwo ? 2 : 1) * st.region);
-  double* nb = kTwo ? na + st.blocks : na;
+  double* nb = kTwo ? na + st.numbers / 8 : na;
   const int team = 1 << st.team_shift, t = lane & (team - 1), slot = lane >> st.team_shift;
   const int per_round = 64 >> st.team_shift;
   const int64_t seg0 = int64_t(blockIdx.y) * n_blocks;             // the segment's first block
@@ -439,35 +425,6 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
-// `target`: bytes of a span that a wave should have in flight per operand; `min_waves`: smaller spans are taken before
-// the launch falls below that many waves
-Stage make_stage(const pbz_codec* c, int64_t n_blocks, int target, int64_t min_waves) {
-  Stage st;
-  st.kept = c->kept;
-  st.bpb = c->kept * itype_bytes(c->itype);
-  st.dwords = (st.bpb + 3) / 4;
-  st.team_shift = 0;
-  while (st.team_shift < 6 && ((st.dwords - 1) >> st.team_shift) + 1 > kTeamDwords) ++st.team_shift;
-  const int per_round = 64 >> st.team_shift;
-  int rounds = target / st.bpb / per_round;
-  if (rounds * per_round > kMaxBlocksPerWave) rounds = kMaxBlocksPerWave / per_round;
-  while (rounds > 1 && n_blocks / (int64_t(rounds) * per_round) < min_waves) rounds >>= 1;
-  if (rounds < 1) rounds = 1;
-  st.blocks = rounds * per_round;
-  st.region = (15 + st.blocks * st.bpb + 8 + 15) / 16 * 16;      // the last dword is cut from two whole words
-  return st;
-}
-
-// regions per wave -> waves per workgroup that 60 KiB of LDS hold (the reductions' final sums need some, too), and the
-// bytes they take.  A block has at most 4096 indices of 4 bytes: three regions and N are below that for one wave.
-int waves_for(const Stage& st, int regions, int numbers, size_t* lds) {
-  const size_t per_wave = size_t(regions) * st.region + size_t(numbers) * 8 * st.blocks;
-  int waves = kMaxWaves;
-  while (waves > 1 && per_wave * waves > 60 * 1024) waves >>= 1;
-  *lds = per_wave * waves;
-  return waves;
-}
-
 unsigned group_count(int64_t n_blocks, const Stage& st, int waves, int64_t cap) {
   const int64_t per_group = int64_t(st.blocks) * waves;
   int64_t g = (n_blocks + per_group - 1) / per_group;
@@ -541,7 +498,7 @@ constexpr int64_t kGroupCap = int64_t(1) << 30;            // the kernels loop b
 int launch_rebin_staged(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2,
                         void* Nout, void* Fout, double sign2, double shift, hipStream_t s) {
   const bool two = F2 != nullptr;
-  const Stage st = make_stage(c, n_blocks, kRebinSpan, kMinWaves);
+  const Stage st = make_stage(c->kept, itype_bytes(c->itype), n_blocks, kRebinSpan, kMinWaves);
   size_t lds;
   const int waves = waves_for(st, two ? 3 : 2, two ? 2 : 1, &lds);
   const dim3 grid(group_count(n_blocks, st, waves, kGroupCap)), block(64 * waves);
@@ -553,7 +510,7 @@ int launch_rebin_staged(const pbz_codec* c, int64_t n_blocks, const void* N1, co
 int launch_blockwise_staged(const pbz_codec* c, int mode, int64_t n_blocks, const void* N1, const void* F1, const void* N2,
                             const void* F2, double* out, double scale, hipStream_t s) {
   const bool two = mode == kBwCovariance;
-  const Stage st = make_stage(c, n_blocks, kReduceSpan, kMinWaves);
+  const Stage st = make_stage(c->kept, itype_bytes(c->itype), n_blocks, kReduceSpan, kMinWaves);
   size_t lds;
   const int waves = waves_for(st, two ? 2 : 1, two ? 2 : 1, &lds);
   const dim3 grid(group_count(n_blocks, st, waves, kGroupCap)), block(64 * waves);
@@ -565,7 +522,7 @@ int launch_blockwise_staged(const pbz_codec* c, int mode, int64_t n_blocks, cons
 int launch_reduce_staged(const pbz_codec* c, bool two, bool dc, bool diff, int64_t n_blocks, int n_segments, int max_groups,
                          const void* N1, const void* F1, const void* N2, const void* F2, const ReduceTail& tail, int* groups,
                          hipStream_t s) {
-  Stage st = make_stage(c, n_blocks, kReduceSpan, kMinWaves / n_segments);
+  Stage st = make_stage(c->kept, itype_bytes(c->itype), n_blocks, kReduceSpan, kMinWaves / n_segments);
   size_t lds;
   const int waves = waves_for(st, two ? 2 : 1, two ? 2 : 1, &lds);
   unsigned g = group_count(n_blocks, st, waves, max_groups);
