@@ -325,7 +325,39 @@ __device__ __forceinline__ void reduce_tail(double* sums, const ReduceTail& t, d
   if (threadIdx.x == kPilot2) record[kPilot2] = K2;
 }
 
-// pbz_ops_staged.hip: any kept count, any alignment.  F2 == nullptr: addition of `shift` to the first coefficients.
+// Whether the sum and the shift of blocks that make no 16-byte vectors go straight from memory, a wave per block, or through LDS.  Few
+// blocks of up to 128 indices: the call is a round trip to memory, and the detour is 0.3-1.2 us more (1000 blocks of 33
+// int8 indices: sum 4.2 us, 5.1 through LDS; 10000 blocks: 7.9 and 5.1).  Blocks of over 8 KiB: LDS holds a wave or two,
+// unless there are so few blocks that the chip is not filled either way (4096 int32 indices: 1000 blocks 93 us, 54 through LDS; 4096
+// blocks 111 and 154).
+inline bool direct_blocks(int64_t n_blocks, int kept, int64_t block_bytes) {
+  return n_blocks <= 2048 ? kept <= 128 : block_bytes > 8192;
+}
+// The same of the block-wise statistics.  They store nothing but a number a block, so the detour pays later (covariance of 1000 blocks of
+// 129 int8 indices 4.0 us, 4.3 through LDS); and from one to three words a lane, which 65 to 160 indices of 32 bits are, it
+// leaves lanes idle (10000 blocks of 129: 6.5 and 9.0, 130000: 50 and 52).
+inline bool direct_blockwise(int64_t n_blocks, int kept, int64_t block_bytes) {
+  if (block_bytes == 4 * int64_t(kept) && kept > 64 && kept <= 160) return n_blocks <= 16384;
+  return n_blocks <= 2048 ? kept <= 192 : block_bytes > 8192;
+}
+// The same of the reductions, a thread per block.  A few bytes per block (1000 to 16384 blocks of one to three indices: 7.5-8.3 us,
+// 0.4-1.0 more through LDS), whatever their number where that is one index of 8 or 16 bits of one operand (4M blocks, int16: 17.3 us
+// and 18.8); and up to 256 blocks of 20 to 80 bytes
+// (five indices: from 10 bytes), which are one workgroup's (156 blocks of 10 int32 indices: 5.8 and 7.3).
+inline bool direct_reduction(int64_t n_blocks, int kept, int64_t block_bytes, bool two) {
+  if (n_blocks <= 256 && kept <= 24 && block_bytes >= (kept <= 5 ? 10 : 20) && block_bytes <= 80) return true;
+  return n_blocks <= 16384 ? kept <= 3 : !two && block_bytes <= 2;
+}
+
+// pbz_ops_direct.hip and pbz_ops_staged.hip: any kept count, any alignment.  F2 == nullptr: addition of `shift` to the first
+// coefficients.
+int launch_rebin_direct(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2,
+                        void* Nout, void* Fout, double sign2, double shift, hipStream_t s);
+int launch_blockwise_direct(const pbz_codec* c, int mode, int64_t n_blocks, const void* N1, const void* F1, const void* N2,
+                            const void* F2, double* out, double scale, hipStream_t s);
+int launch_reduce_direct(const pbz_codec* c, bool two, bool dc, bool diff, int64_t n_blocks, int n_segments, int max_groups,
+                         const void* N1, const void* F1, const void* N2, const void* F2, const ReduceTail& tail, int* groups,
+                         hipStream_t s);
 int launch_rebin_staged(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2,
                         void* Nout, void* Fout, double sign2, double shift, hipStream_t s);
 int launch_blockwise_staged(const pbz_codec* c, int mode, int64_t n_blocks, const void* N1, const void* F1, const void* N2,

@@ -522,11 +522,14 @@ int launch_blockwise_staged(const pbz_codec* c, int mode, int64_t n_blocks, cons
 int launch_reduce_staged(const pbz_codec* c, bool two, bool dc, bool diff, int64_t n_blocks, int n_segments, int max_groups,
                          const void* N1, const void* F1, const void* N2, const void* F2, const ReduceTail& tail, int* groups,
                          hipStream_t s) {
-  Stage st = make_stage(c->kept, itype_bytes(c->itype), n_blocks, kReduceSpan, kMinWaves / n_segments);
+  // Up to 256 blocks in 16 KiB (a step of a short series): one workgroup, which takes them in a tile per wave or two.  Dealt out to
+  // more workgroups they need the second launch
+  const bool few = n_blocks <= 256 && n_blocks * c->kept * itype_bytes(c->itype) <= 16 * 1024;
+  const Stage st = make_stage(c->kept, itype_bytes(c->itype), n_blocks, kReduceSpan, few ? kMaxWaves : kMinWaves / n_segments);
   size_t lds;
   const int waves = waves_for(st, two ? 2 : 1, two ? 2 : 1, &lds);
   unsigned g = group_count(n_blocks, st, waves, max_groups);
-  if (g <= 2) g = 1;                       // two tiles per wave: cheaper than a second launch
+  if (g <= 2 || few) g = 1;                // two tiles per wave: cheaper than a second launch
   *groups = int(g);
   const dim3 grid(g, unsigned(n_segments)), block(64 * waves);
   PBZ_BY_TYPES(reduce2, two, dc, diff, grid, block, lds, s, st, N1, F1, N2, F2, n_blocks, tail);

@@ -6,6 +6,7 @@ import torch
 
 import parity
 from paper_2406_11209_amd import synth
+from paper_2406_11209_amd.api import Codec
 from parity import Case
 
 pytestmark = pytest.mark.gpu
@@ -43,6 +44,17 @@ def check_everything(case, N1, F1, N2, F2):
 @pytest.mark.parametrize("bits,ftype", [(8, "f32"), (16, "f64"), (32, "f32"), (16, "f16"), (8, "f64"), (32, "f64")])
 def test_any_kept_count_and_alignment(extent, kept, bits, ftype):
     n_blocks = 5 if extent > 256 else (300 if kept > 64 else 1031)
+    check_kept_count(extent, kept, bits, ftype, n_blocks)
+
+
+@pytest.mark.parametrize("extent,kept", KEPT[:-2], ids=["%d_of_%d" % (k, e) for e, k in KEPT[:-2]])
+@pytest.mark.parametrize("bits,ftype", [(8, "f32"), (16, "f64"), (32, "f32"), (16, "f16"), (8, "f64"), (32, "f64")])
+def test_any_kept_count_of_more_blocks(extent, kept, bits, ftype):
+    """So many that small ones go through LDS, too: fewer are taken element by element from memory."""
+    check_kept_count(extent, kept, bits, ftype, 2300 if kept > 64 else 2531)
+
+
+def check_kept_count(extent, kept, bits, ftype, n_blocks):
     case = make(extent, kept, bits, ftype, n_blocks, 1000 * kept + bits)
     N1, F1 = case.codec.compress(case.xA)
     N2, F2 = case.codec.compress(case.xB)
@@ -78,3 +90,45 @@ def test_segments_at_every_phase():
             nxt = (N[(t + 1) * run:(t + 2) * run], F[(t + 1) * run:(t + 2) * run])
             assert dist[t].item() == pytest.approx(one("difference_norm2", t, *nxt), rel=1e-13)
             assert abs(cov[t].item() - one("covariance", t, *nxt)) <= 1e-13 * abs(got[t].item())
+
+
+# kept counts and block counts around which a call changes from one kernel to another: element by element or through LDS
+HALVES = [(8, 1, 8, 16385), (8, 3, 16, 16385), (64, 19, 8, 2049), (128, 128, 32, 2049), (128, 100, 32, 16385), (256, 160, 32, 16385),
+          (256, 192, 16, 2049), (64, 20, 32, 257), (16, 5, 16, 257), (4096, 2049, 32, 2049), (4096, 4096, 32, 2049), (4096, 4096, 16, 2049)]
+
+
+@pytest.mark.parametrize("extent,kept,bits,n", HALVES, ids=["%d_of_%d_i%d_x%d" % (k, e, b, n) for e, k, b, n in HALVES])
+def test_a_call_agrees_with_the_calls_on_its_halves(extent, kept, bits, n):
+    g = torch.Generator("cuda").manual_seed(kept + n)
+    block = (extent,) if extent <= 256 else (64, extent // 64)
+    mask = np.zeros(extent, dtype=bool)
+    mask[:kept] = True
+    codec = Codec(block, "f32", bits, mask.reshape(block))
+    r = 2 ** (bits - 1) - 1
+    ops = []
+    for _ in range(2):
+        F = torch.randint(-r, r + 1, (n + 1, kept), generator=g, device="cuda").to({8: torch.int8, 16: torch.int16, 32: torch.int32}[bits])
+        ops.append((torch.rand(n + 1, generator=g, device="cuda") + 0.1, F))
+    # one block on, so that aligned blocks of whole vectors come this way, too
+    (N1, F1), (N2, F2) = [(N[1:], F[1:]) for N, F in ops]
+    h = n // 2
+    parts = [slice(0, h), slice(h, n)]
+    for whole, halves in ((codec.add(N1, F1, N2, F2), [codec.add(N1[p], F1[p], N2[p], F2[p]) for p in parts]),
+                          (codec.add_scalar(N1, F1, 0.75), [codec.add_scalar(N1[p], F1[p], 0.75) for p in parts])):
+        assert torch.equal(whole[0], torch.cat([p[0] for p in halves]))
+        # both quotients are rounded correctly, up to double rounding within 2^-53 of a tie
+        assert int((whole[1] != torch.cat([p[1] for p in halves])).sum()) <= (2 if bits == 32 else 0)
+    for op, args in (("blockwise_variance", (N1, F1)), ("blockwise_covariance", (N1, F1, N2, F2))):
+        whole = getattr(codec, op)(*args)
+        split = torch.cat([getattr(codec, op)(*[a[p] for a in args]) for p in parts])
+        scale = codec.blockwise_variance(N1, F1).abs() + codec.blockwise_variance(N2, F2).abs()
+        assert bool(((whole - split).abs() <= 1e-13 * scale).all())
+    for op, args, power in (("norm2", (N1, F1), 2), ("difference_norm2", (N1, F1, N2, F2), 2), ("dot", (N1, F1, N2, F2), 1)):
+        whole = getattr(codec, op)(*args).item() ** power
+        split = sum(getattr(codec, op)(*[a[p] for a in args]).item() ** power for p in parts)
+        size = codec.norm2(N1, F1).item() ** 2 + codec.norm2(N2, F2).item() ** 2
+        assert abs(whole - split) <= 1e-12 * size, op
+    for op in ("variance", "norm2"):
+        halves = codec.segmented(op, 2, h, N1[:2 * h], F1[:2 * h])
+        for half, p in zip(halves.tolist(), (slice(0, h), slice(h, 2 * h))):
+            assert half == pytest.approx(getattr(codec, op)(N1[p], F1[p]).item(), rel=1e-12)

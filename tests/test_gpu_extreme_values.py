@@ -78,14 +78,15 @@ def operand(n_blocks, kept, bits, N, seed):
 
 @pytest.mark.parametrize("bits", [8, 16, 32])
 @pytest.mark.parametrize("kept", [5, 19, 33])
-def test_rebinning_of_blocks_at_the_ends_of_the_range(kept, bits):
+@pytest.mark.parametrize("times", [1, 100])                  # few blocks: element by element from memory; more: through LDS
+def test_rebinning_of_blocks_at_the_ends_of_the_range(times, kept, bits):
     """Sum, difference and shift of blocks whose kept counts make no whole vectors, N from the smallest subnormal numbers up."""
     mask = np.zeros(64, dtype=bool)
     mask[:kept] = True
-    case = Case(np.zeros((8 * 24, 8)), None, "f64", (8, 8), bits, "f64", mask.reshape(8, 8))
+    case = Case(np.zeros((8 * 24 * times, 8)), None, "f64", (8, 8), bits, "f64", mask.reshape(8, 8))
     scales = np.array([5e-324, 3e-322, 1e-320, 1e-310, 1e-308, 1e-305, 1e-300, 1.0, 1e150, 1e290, 1e298, 0.0])
-    N1, F1 = operand(24, kept, bits, np.tile(scales, 2), kept)
-    N2, F2 = operand(24, kept, bits, np.tile(scales, 2) * np.repeat([0.5, 3.0], 12), kept + 1)
+    N1, F1 = operand(24 * times, kept, bits, np.tile(scales, 2 * times), kept)
+    N2, F2 = operand(24 * times, kept, bits, np.tile(np.tile(scales, 2) * np.repeat([0.5, 3.0], 12), times), kept + 1)
     for got, want in ((case.codec.add(N1, F1, N2, F2), po.add(case.oc(N1, F1), case.oc(N2, F2))),
                       (case.codec.subtract(N1, F1, N2, F2), po.add(case.oc(N1, F1), po.negate(case.oc(N2, F2)))),
                       (case.codec.add_scalar(N1, F1, 0.0), po.add_scalar(case.oc(N1, F1), 0.0))):
@@ -97,34 +98,37 @@ def test_rebinning_of_blocks_at_the_ends_of_the_range(kept, bits):
 
 
 @pytest.mark.parametrize("kept", [5, 19, 33])
-def test_rebinning_keeps_infinities(kept):
+@pytest.mark.parametrize("times", [1, 400])
+def test_rebinning_keeps_infinities(times, kept):
     """A block whose N has overflowed (FP16) stays infinite through the operations, and its neighbours stay what they are."""
     mask = np.zeros(64, dtype=bool)
     mask[:kept] = True
-    case = Case(np.zeros((8 * 6, 8)), None, "f64", (8, 8), 8, "f16", mask.reshape(8, 8))
-    N1, F1 = operand(6, kept, 8, np.array([1.0, np.inf, 2.0, np.inf, 0.5, 0.0], dtype=np.float16), kept)
-    N2, F2 = operand(6, kept, 8, np.array([1.0, 1.0, 2.0, 0.0, 0.5, 3.0], dtype=np.float16), kept + 1)
-    fine = [0, 2, 4, 5]
+    case = Case(np.zeros((8 * 6 * times, 8)), None, "f64", (8, 8), 8, "f16", mask.reshape(8, 8))
+    N1, F1 = operand(6 * times, kept, 8, np.tile(np.array([1.0, np.inf, 2.0, np.inf, 0.5, 0.0], dtype=np.float16), times), kept)
+    N2, F2 = operand(6 * times, kept, 8, np.tile(np.array([1.0, 1.0, 2.0, 0.0, 0.5, 3.0], dtype=np.float16), times), kept + 1)
+    at = torch.arange(6 * times, device="cuda")
+    fine, infinite = at[(at % 6 != 1) & (at % 6 != 3)], at[(at % 6 == 1) | (at % 6 == 3)]
     for got, plain in ((case.codec.add(N1, F1, N2, F2), case.codec.add(N1[fine], F1[fine], N2[fine], F2[fine])),
                        (case.codec.add_scalar(N1, F1, 0.75), case.codec.add_scalar(N1[fine], F1[fine], 0.75))):
-        assert bool(torch.isinf(got[0][[1, 3]]).all())
+        assert bool(torch.isinf(got[0][infinite]).all())
         assert torch.equal(got[0][fine], plain[0]) and torch.equal(got[1][fine], plain[1])
 
 
 @pytest.mark.parametrize("bits,kept", [(8, 5), (8, 19), (8, 33), (8, 63), (16, 5), (16, 19), (16, 63), (32, 19)])
-def test_reductions_keep_infinities(bits, kept):
+@pytest.mark.parametrize("n", [40, 2400])
+def test_reductions_keep_infinities(n, bits, kept):
     """A block whose N has overflowed (FP16) makes norms, distances and products infinite, not NaN: not where its last indices
     are padding, and not where most of them are zero."""
     mask = np.zeros(64, dtype=bool)
     mask[:kept] = True
-    case = Case(np.zeros((8 * 40, 8)), None, "f64", (8, 8), bits, "f16", mask.reshape(8, 8))
-    N1, F1 = operand(40, kept, bits, np.full(40, 1.5, dtype=np.float16), kept)
-    N2, F2 = operand(40, kept, bits, np.full(40, 0.5, dtype=np.float16), kept + 1)
+    case = Case(np.zeros((8 * n, 8)), None, "f64", (8, 8), bits, "f16", mask.reshape(8, 8))
+    N1, F1 = operand(n, kept, bits, np.full(n, 1.5, dtype=np.float16), kept)
+    N2, F2 = operand(n, kept, bits, np.full(n, 0.5, dtype=np.float16), kept + 1)
     N1[17] = float("inf")
     F1[F1 == 0] = 1                              # infinity times a zero index is no number, and neither is a distance of it
     assert case.codec.difference_norm2(N1, F1, N2, F2).item() == np.inf
     F1[17, 1:] = 0
     assert case.codec.norm2(N1, F1).item() == np.inf
     assert case.codec.dot(N1, F1, N2, F2).item() == np.inf
-    assert case.codec.segmented("norm2", 4, 10, N1, F1).tolist()[1] == np.inf
-    assert np.isfinite(case.codec.segmented("norm2", 4, 10, N1, F1).cpu().numpy()[[0, 2, 3]]).all()
+    assert case.codec.segmented("norm2", 4, n // 4, N1, F1).tolist()[17 // (n // 4)] == np.inf
+    assert np.isfinite(case.codec.segmented("norm2", 4, n // 4, N1, F1).cpu().numpy()[2:]).all()
