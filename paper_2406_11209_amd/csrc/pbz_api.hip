@@ -144,6 +144,7 @@ int pbz_codec_create(pbz_codec** out, int ndim, const int64_t* block_shape, pbz_
   c->compute_f64 = (work_type == PBZ_F64) || (c->index_bits > 8);
   c->kept = kept;
   c->path = PBZ_PATH_AUTO;
+  c->route = kRouteAuto;
   c->transform = PBZ_TRANSFORM_DCT;
   c->mask = static_cast<uint8_t*>(std::malloc(size_t(vol)));
   c->kept_pos = static_cast<int32_t*>(std::malloc(sizeof(int32_t) * size_t(vol)));
@@ -281,8 +282,8 @@ int pbz_compress(const pbz_codec* c, const void* x, pbz_ftype x_type, const int6
   st = ensure_tables(c, &t);
   if (st != PBZ_OK) return st;
   if (c->path == PBZ_PATH_AUTO) {
-    int r = try_compress_masked(c, g, t->places, x, x_type, N, F, s);
-    if (r == 0) r = try_compress_brick(c, g, t, x, x_type, N, F, s);
+    int r = try_compress_masked(c, g, t->places, x, x_type, N, F, s, false);
+    if (r == 0) r = try_compress_brick(c, g, t, x, x_type, N, F, s, false);
     if (r != 0) return r < 0 ? r : PBZ_OK;
   }
   if (tiled_kernels_cover(c)) return launch_compress_tiled(c, g, t, x, x_type, N, F, s);
@@ -352,8 +353,8 @@ int pbz_decompress(const pbz_codec* c, const void* N, const void* F, const int64
   st = ensure_tables(c, &t);
   if (st != PBZ_OK) return st;
   if (c->path == PBZ_PATH_AUTO) {
-    int r = try_decompress_masked(c, g, t->places, N, F, y, y_type, s);
-    if (r == 0) r = try_decompress_brick(c, g, t, N, F, y, y_type, s);
+    int r = try_decompress_masked(c, g, t->places, N, F, y, y_type, s, false);
+    if (r == 0) r = try_decompress_brick(c, g, t, N, F, y, y_type, s, false);
     if (r != 0) return r < 0 ? r : PBZ_OK;
   }
   if (tiled_kernels_cover(c)) return launch_decompress_tiled(c, g, t, N, F, y, y_type, s);
@@ -381,6 +382,38 @@ const char* pbz_kernel_name(const pbz_codec* c, const char* op, const int64_t* s
     return nullptr;
   }
   return name;
+}
+
+// Not part of the interface: the tests' means to see that a call goes to the kernels it is meant for.  Host only.  `array`: the address the
+// array would have (its alignment counts; nothing is read); F is taken to be 16-byte aligned.
+int pbz_internal_route(const pbz_codec* c, int decompress, const int64_t* shape, pbz_ftype array_type, uint64_t array) {
+  if (!c || !shape) return PBZ_ERR_NULL;
+  Geom g;
+  const int st = make_geom(c, shape, &g);
+  if (st != PBZ_OK) return st;
+  if (c->path == PBZ_PATH_AUTO) {
+    void* const a = reinterpret_cast<void*>(uintptr_t(array));
+    void* const f = reinterpret_cast<void*>(uintptr_t(256));
+    const char* name = nullptr;
+    const DeviceTables none;
+    int r = decompress ? try_decompress_fast(c, g, f, f, a, array_type, nullptr, true, &name)
+                       : try_compress_fast(c, g, a, array_type, f, f, nullptr, true, &name);
+    if (r != 0) return kRouteExact;
+    r = decompress ? try_decompress_masked(c, g, nullptr, f, f, a, array_type, nullptr, true)
+                   : try_compress_masked(c, g, nullptr, a, array_type, f, f, nullptr, true);
+    if (r != 0) return kRouteMasked;
+    r = decompress ? try_decompress_brick(c, g, &none, f, f, a, array_type, nullptr, true)
+                   : try_compress_brick(c, g, &none, a, array_type, f, f, nullptr, true);
+    if (r != 0) return kRouteShape;
+  }
+  return tiled_kernels_cover(c) ? kRouteTiled : kRouteDense;
+}
+
+int pbz_internal_set_route(pbz_codec* c, int route) {
+  if (!c) return PBZ_ERR_NULL;
+  if (route != kRouteAuto && route != kRouteMasked && route != kRouteShape) return PBZ_ERR_TYPE;
+  c->route = route;
+  return PBZ_OK;
 }
 
 int pbz_negate(const pbz_codec* c, int64_t n_blocks, const void* F_in, void* F_out, void* stream) {

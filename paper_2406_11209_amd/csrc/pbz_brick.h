@@ -857,10 +857,11 @@ constexpr bool kTaken = BX < 64 || sizeof(T) == 4;
 
 template <typename T, int BW, int BZ, int BY, int BX>
 int compress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* x, int xtype, void* N, void* F,
-                   hipStream_t s) {
+                   hipStream_t s, bool dry_run) {
   if constexpr (kTaken<T, BX>) {
     BrickGeom g;
     if (!make_brick(c, geo, x, xtype, t, BW, BZ, BY, BX, &g)) return 0;
+    if (dry_run) return 1;
     using S = Shape<T, BW, BZ, BY, BX>;
     if (c->transform == PBZ_TRANSFORM_HAAR) compress_with<kTfHaar, T, S>(g, x, N, F, s);
     else compress_with<kTfDct, T, S>(g, x, N, F, s);
@@ -870,10 +871,11 @@ int compress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t, c
 }
 template <typename T, int BW, int BZ, int BY, int BX>
 int decompress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* N, const void* F, void* y,
-                     int ytype, hipStream_t s) {
+                     int ytype, hipStream_t s, bool dry_run) {
   if constexpr (kTaken<T, BX>) {
     BrickGeom g;
     if (!make_brick(c, geo, y, ytype, t, BW, BZ, BY, BX, &g)) return 0;
+    if (dry_run) return 1;
     using S = Shape<T, BW, BZ, BY, BX>;
     if (c->transform == PBZ_TRANSFORM_HAAR) decompress_with<kTfHaar, T, S>(g, N, F, y, s);
     else decompress_with<kTfDct, T, S>(g, N, F, y, s);
@@ -885,25 +887,25 @@ int decompress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t,
 // Defines the two entry points of a part from its list of shapes X(BW, BZ, BY, BX)
 #define PBZ_DEFINE_BRICK_PART(PART, SHAPES)                                                                             \
   int PART##_compress(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* x, int xtype, void* N,    \
-                      void* F, hipStream_t s) {                                                                         \
+                      void* F, hipStream_t s, bool dry_run) {                                                           \
     int r = 0;                                                                                                          \
     SHAPES(PBZ_BRICK_COMPRESS_ROW)                                                                                      \
     return r;                                                                                                           \
   }                                                                                                                     \
   int PART##_decompress(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* N, const void* F,       \
-                        void* y, int ytype, hipStream_t s) {                                                            \
+                        void* y, int ytype, hipStream_t s, bool dry_run) {                                              \
     int r = 0;                                                                                                          \
     SHAPES(PBZ_BRICK_DECOMPRESS_ROW)                                                                                    \
     return r;                                                                                                           \
   }
 #define PBZ_BRICK_COMPRESS_ROW(W, Z, Y, XX)                                                                             \
   if (r == 0)                                                                                                           \
-    r = c->compute_f64 ? compress_shape<double, W, Z, Y, XX>(c, geo, t, x, xtype, N, F, s)                              \
-                       : compress_shape<float, W, Z, Y, XX>(c, geo, t, x, xtype, N, F, s);
+    r = c->compute_f64 ? compress_shape<double, W, Z, Y, XX>(c, geo, t, x, xtype, N, F, s, dry_run)                              \
+                       : compress_shape<float, W, Z, Y, XX>(c, geo, t, x, xtype, N, F, s, dry_run);
 #define PBZ_BRICK_DECOMPRESS_ROW(W, Z, Y, XX)                                                                           \
   if (r == 0)                                                                                                           \
-    r = c->compute_f64 ? decompress_shape<double, W, Z, Y, XX>(c, geo, t, N, F, y, ytype, s)                            \
-                       : decompress_shape<float, W, Z, Y, XX>(c, geo, t, N, F, y, ytype, s);
+    r = c->compute_f64 ? decompress_shape<double, W, Z, Y, XX>(c, geo, t, N, F, y, ytype, s, dry_run)                            \
+                       : decompress_shape<float, W, Z, Y, XX>(c, geo, t, N, F, y, ytype, s, dry_run);
 
 }  // namespace
 
@@ -911,9 +913,9 @@ int decompress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t,
 #define PBZ_BRICK_PARTS(X) X(lines) X(small) X(flat) X(wide) X(planes) X(cubes) X(tesseracts) X(long_tesseracts)
 #define PBZ_BRICK_DECLARE(PART)                                                                                         \
   int PART##_compress(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* x, int xtype, void* N,    \
-                      void* F, hipStream_t s);                                                                          \
+                      void* F, hipStream_t s, bool dry_run);                                                            \
   int PART##_decompress(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* N, const void* F,       \
-                        void* y, int ytype, hipStream_t s);
+                        void* y, int ytype, hipStream_t s, bool dry_run);
 PBZ_BRICK_PARTS(PBZ_BRICK_DECLARE)
 #undef PBZ_BRICK_DECLARE
 

@@ -86,26 +86,26 @@ int try_decompress_fast(const pbz_codec* c, const Geom& geo, const void* N, cons
 // mask (everything, or a box), which skip work that these cannot, and before the kernels for any block shape, which take 1.4 to
 // 3 times as long on every setting measured (the figures are with MaskArgs)
 int try_compress_masked(const pbz_codec* c, const Geom& geo, const uint16_t* pos, const void* x, int xtype, void* N, void* F,
-                        hipStream_t s) {
-  if (c->kept == c->vol || !fast::aligned16(x)) return 0;
+                        hipStream_t s, bool dry_run) {
+  if (c->kept == c->vol || !fast::aligned16(x) || c->route == kRouteShape) return 0;
   const fast::Folded f = fast::fold(c, geo);
   if (!f.ok) return 0;
-  int r = fast::lane_compress_masked(c, f, xtype, pos, x, N, F, s);
-  if (r == 0) r = fast::quad16_compress_masked(c, f, xtype, pos, x, N, F, s);
-  if (r == 0) r = fast::oct8_compress_masked(c, f, xtype, pos, x, N, F, s);
-  if (r == 0) r = fast::cube16_compress_masked(c, f, xtype, pos, x, N, F, s);
+  int r = fast::lane_compress_masked(c, f, xtype, pos, x, N, F, s, dry_run);
+  if (r == 0) r = fast::quad16_compress_masked(c, f, xtype, pos, x, N, F, s, dry_run);
+  if (r == 0) r = fast::oct8_compress_masked(c, f, xtype, pos, x, N, F, s, dry_run);
+  if (r == 0) r = fast::cube16_compress_masked(c, f, xtype, pos, x, N, F, s, dry_run);
   return r;
 }
 
 int try_decompress_masked(const pbz_codec* c, const Geom& geo, const uint16_t* pos, const void* N, const void* F, void* y,
-                          int ytype, hipStream_t s) {
-  if (c->kept == c->vol || !fast::aligned16(y)) return 0;
+                          int ytype, hipStream_t s, bool dry_run) {
+  if (c->kept == c->vol || !fast::aligned16(y) || c->route == kRouteShape) return 0;
   const fast::Folded f = fast::fold(c, geo);
   if (!f.ok) return 0;
-  int r = fast::lane_decompress_masked(c, f, ytype, pos, N, F, y, s);
-  if (r == 0) r = fast::quad16_decompress_masked(c, f, ytype, pos, N, F, y, s);
-  if (r == 0) r = fast::oct8_decompress_masked(c, f, ytype, pos, N, F, y, s);
-  if (r == 0) r = fast::cube16_decompress_masked(c, f, ytype, pos, N, F, y, s);
+  int r = fast::lane_decompress_masked(c, f, ytype, pos, N, F, y, s, dry_run);
+  if (r == 0) r = fast::quad16_decompress_masked(c, f, ytype, pos, N, F, y, s, dry_run);
+  if (r == 0) r = fast::oct8_decompress_masked(c, f, ytype, pos, N, F, y, s, dry_run);
+  if (r == 0) r = fast::cube16_decompress_masked(c, f, ytype, pos, N, F, y, s, dry_run);
   return r;
 }
 

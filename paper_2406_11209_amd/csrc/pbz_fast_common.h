@@ -775,9 +775,9 @@ template <> constexpr int itype_code<int32_t>() { return PBZ_I32; }
   int FAMILY##_decompress(const pbz_codec* c, const Folded& f, int ytype, const void* N, const void* F, void* y,      \
                           hipStream_t s, bool dry_run, const char** name);                                            \
   int FAMILY##_compress_masked(const pbz_codec* c, const Folded& f, int xtype, const uint16_t* pos, const void* x,    \
-                               void* N, void* F, hipStream_t s);                                                      \
+                               void* N, void* F, hipStream_t s, bool dry_run);                                        \
   int FAMILY##_decompress_masked(const pbz_codec* c, const Folded& f, int xtype, const uint16_t* pos, const void* N,  \
-                                 const void* F, void* y, hipStream_t s);
+                                 const void* F, void* y, hipStream_t s, bool dry_run);
 PBZ_FAST_FAMILY(lane)
 PBZ_FAST_FAMILY(quad16)
 PBZ_FAST_FAMILY(oct8)
@@ -808,21 +808,21 @@ PBZ_FAST_FAMILY(cube16)
 // The same for the kernels that take any mask: 1 when one of them handled the call, 0 when none covers the setting.
 #define PBZ_DEFINE_MASKED_FAMILY(FAMILY, FOR_EACH)                                                                    \
   int FAMILY##_compress_masked(const pbz_codec* c, const Folded& f, int xtype, const uint16_t* pos, const void* x,    \
-                               void* N, void* F, hipStream_t s) {                                                     \
+                               void* N, void* F, hipStream_t s, bool dry_run) {                                       \
     FOR_EACH(PBZ_MASKED_COMPRESS_ROW, kTfDct)                                                                         \
     FOR_EACH(PBZ_MASKED_COMPRESS_ROW, kTfHaar)                                                                        \
     return 0;                                                                                                         \
   }                                                                                                                   \
   int FAMILY##_decompress_masked(const pbz_codec* c, const Folded& f, int xtype, const uint16_t* pos, const void* N,  \
-                                 const void* F, void* y, hipStream_t s) {                                             \
+                                 const void* F, void* y, hipStream_t s, bool dry_run) {                               \
     FOR_EACH(PBZ_MASKED_DECOMPRESS_ROW, kTfDct)                                                                       \
     FOR_EACH(PBZ_MASKED_DECOMPRESS_ROW, kTfHaar)                                                                      \
     return 0;                                                                                                         \
   }
 #define PBZ_MASKED_COMPRESS_ROW(K) \
-  if (K::matches(c, f, xtype)) return K::compress(c, f.g, pos, x, N, F, s);
+  if (K::matches(c, f, xtype)) return dry_run ? K::fits(f.g) : K::compress(c, f.g, pos, x, N, F, s);
 #define PBZ_MASKED_DECOMPRESS_ROW(K) \
-  if (K::matches(c, f, xtype)) return K::decompress(c, f.g, pos, N, F, y, s);
+  if (K::matches(c, f, xtype)) return dry_run ? K::fits(f.g) : K::decompress(c, f.g, pos, N, F, y, s);
 
 #define PBZ_FAST_COMPRESS_ROW(K, NAME)                                         \
   if (K::matches(c, f, xtype)) {                                               \

@@ -402,6 +402,7 @@ struct CubeMasked<Cube16Kernel<TF, T, IT, XT>> {
     f.kz = f.ky = f.kx = 16;
     return Base::matches(c, f, xtype);
   }
+  static int fits(const FastGeom& g) { return Base::fits(g); }
   static MaskArgs<true> args(const pbz_codec* c, const uint16_t* pos) {
     MaskArgs<true> m;
     m.pos = pos;

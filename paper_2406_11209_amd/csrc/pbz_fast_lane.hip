@@ -431,6 +431,7 @@ struct LaneMasked<LaneKernel<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX>> {
     f.kz = BZ; f.ky = BY; f.kx = BX;
     return LaneKernel<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX>::matches(c, f, xtype);
   }
+  static int fits(const FastGeom& g) { return LaneKernel<TF, T, XT, IT, NT, BZ, BY, BX, BZ, BY, BX>::fits(g); }
   static MaskArgs<true> args(const pbz_codec* c) {
     MaskArgs<true> m;
     m.pos = nullptr;

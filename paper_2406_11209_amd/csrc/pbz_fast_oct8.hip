@@ -972,6 +972,7 @@ struct OctMasked<Oct8Kernel<TF, XT, 8, 8, 8>> {
     f.kz = f.ky = f.kx = 8;
     return Oct8Kernel<TF, XT, 8, 8, 8>::matches(c, f, xtype);
   }
+  static int fits(const FastGeom& g) { return Oct8Kernel<TF, XT, 8, 8, 8>::fits(g); }
   template <bool kTailX>
   static void launch(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* x, void* N, void* F,
                      hipStream_t s) {
@@ -1004,6 +1005,7 @@ struct OctMasked<Oct8WideKernel<TF, XT, IT>> {
     f.kz = f.ky = f.kx = 8;
     return Oct8WideKernel<TF, XT, IT>::matches(c, f, xtype);
   }
+  static int fits(const FastGeom& g) { return Oct8WideKernel<TF, XT, IT>::fits(g); }
   template <bool kTailX>
   static void launch(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* x, void* N, void* F,
                      hipStream_t s) {

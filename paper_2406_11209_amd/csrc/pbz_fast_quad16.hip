@@ -388,6 +388,7 @@ struct QuadMasked<Quad16Kernel<TF, T, IT, XT, BZ>> {
     f.kz = BZ; f.ky = f.kx = 16;
     return Base::matches(c, f, xtype);
   }
+  static int fits(const FastGeom& g) { return Base::fits(g); }
   static MaskArgs<true> args(const pbz_codec* c, const uint16_t* pos) {
     MaskArgs<true> m;
     m.pos = pos;

@@ -16,6 +16,11 @@ constexpr int kMaxDevices = 16;
 constexpr uint16_t kPruned = 0x7fff;        // beyond every position, also as a byte offset after any LDS base
 constexpr int kReducePartialSlots = 8;      // doubles per workgroup partial
 constexpr int kReduceMaxGroups = 4096;      // upper bound on reduction workgroups
+// Which kernels take a compress or decompress call, in the order in which they are asked.  A codec's route is kRouteAuto; the tests
+// set kRouteMasked or kRouteShape to have that kind taken wherever it can be, whatever the rules on sizes say
+// (pbz_internal_set_route), and ask which one a call would go to (pbz_internal_route).
+enum Route { kRouteAuto = -1, kRouteExact = 0, kRouteMasked = 1, kRouteShape = 2, kRouteTiled = 3, kRouteDense = 4 };
+
 constexpr size_t kWorkspaceBytes = size_t(kReduceMaxGroups) * kReducePartialSlots * sizeof(double);
 
 // Per-device constant tables, created lazily at the first launch.
@@ -48,6 +53,7 @@ struct pbz_codec {
   int h_total;
   double* H_host;       // concatenated matrices
   pbz_kernel_path path;
+  int route;                  // pbz::Route; kRouteAuto outside the tests
   int transform;        // pbz_transform
   mutable std::atomic<bool> used{false};   // a compress / decompress has been issued: the transform is fixed from then on
   mutable std::mutex mu;
@@ -99,15 +105,15 @@ int try_decompress_fast(const pbz_codec* c, const Geom& g, const void* N, const 
 
 // the same families for settings that only differ from theirs in the mask; `places`: DeviceTables::places
 int try_compress_masked(const pbz_codec* c, const Geom& g, const uint16_t* places, const void* x, int xtype, void* N, void* F,
-                        hipStream_t s);
+                        hipStream_t s, bool dry_run);
 int try_decompress_masked(const pbz_codec* c, const Geom& g, const uint16_t* places, const void* N, const void* F, void* y,
-                          int ytype, hipStream_t s);
+                          int ytype, hipStream_t s, bool dry_run);
 
 // general kernels for a list of block shapes (pbz_brick.h); 1 when they handled the call, 0 when they do not cover it
 int try_compress_brick(const pbz_codec* c, const Geom& g, const DeviceTables* t, const void* x, int xtype, void* N, void* F,
-                       hipStream_t s);
+                       hipStream_t s, bool dry_run);
 int try_decompress_brick(const pbz_codec* c, const Geom& g, const DeviceTables* t, const void* N, const void* F, void* y,
-                         int ytype, hipStream_t s);
+                         int ytype, hipStream_t s, bool dry_run);
 
 // element-wise compressed-space operations
 int launch_negate(const pbz_codec* c, int64_t n_blocks, const void* Fin, void* Fout, hipStream_t s);
@@ -143,3 +149,8 @@ int launch_blockwise(const pbz_codec* c, int mode, int64_t n_blocks, const void*
 inline int hip_status(hipError_t e) { return e == hipSuccess ? PBZ_OK : PBZ_ERR_HIP; }
 
 }  // namespace pbz
+
+extern "C" {
+int pbz_internal_route(const pbz_codec* c, int decompress, const int64_t* shape, pbz_ftype array_type, uint64_t array);
+int pbz_internal_set_route(pbz_codec* c, int route);
+}

@@ -19,6 +19,7 @@ Tolerances
 """
 from __future__ import annotations
 
+import ctypes
 import math
 from dataclasses import dataclass
 from typing import Optional, Sequence
@@ -27,6 +28,7 @@ import numpy as np
 import torch
 
 from oracle import pbz_oracle as po
+from paper_2406_11209_amd import api
 from paper_2406_11209_amd.api import Codec
 
 TORCH_DTYPE = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
@@ -36,6 +38,27 @@ MAX_MISMATCH_FRACTION = 1e-4
 # the 16 x 16 case), so FP32 arithmetic of any order flips more of them; every flip must still be a tie and +-1.
 MAX_MISMATCH_FRACTION_HAAR = 1e-3
 EXACT_TIE = 1e-9     # |frac(t) - 1/2| below this: a tie in exact arithmetic
+
+
+# Which kernels take a compress or decompress call (the library's internal numbering, in the order in which it asks them): those for
+# exactly this setting, the same families under any mask, those per block shape, the tiled and the dense ones.
+EXACT, MASKED, SHAPE, TILED, DENSE = range(5)
+
+
+def route(codec: Codec, op: str, shape, dtype: str, array: int = 256) -> int:
+    """Where a call would go; `array`: the array's address (its alignment counts)."""
+    fn = codec._lib.pbz_internal_route
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.POINTER(ctypes.c_int64), ctypes.c_int, ctypes.c_uint64]
+    got = fn(codec._h, int(op == "decompress"), (ctypes.c_int64 * len(shape))(*shape), api.FTYPES[dtype], array)
+    assert got >= 0
+    return got
+
+
+def take_wherever_possible(codec: Codec, kind: int) -> None:
+    """MASKED or SHAPE: that kind of kernels for every call they can take, whatever the rules on sizes say."""
+    fn = codec._lib.pbz_internal_set_route
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int]
+    assert fn(codec._h, kind) == 0
 
 
 def value_tol(ftype: str) -> float:

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2406_11209_amd import api, synth
-from parity import Case
+from parity import MASKED, TILED, Case, route, take_wherever_possible
 
 pytestmark = pytest.mark.gpu
 
@@ -40,6 +40,8 @@ def test_any_mask_on_the_specialised_families(block, dtype, ftype, bits, transfo
         x = cast(synth.bump_field(shape, 6, g, (2.0, 8.0)) + 0.2 + 0.01 * g.standard_normal(shape))
         mask = random_mask(block, kept, g)
         case = Case(x, None, dtype, block, bits, ftype, mask, transform=transform)
+        take_wherever_possible(case.codec, MASKED)
+        assert route(case.codec, "compress", shape, dtype) == route(case.codec, "decompress", shape, dtype) == MASKED
         N, F, _, _ = case.check_compress("A")
         case.check_decompress(N, F)
         # the same into and from F one block on, which is another phase unless a block is whole 16-byte pieces
@@ -50,6 +52,7 @@ def test_any_mask_on_the_specialised_families(block, dtype, ftype, bits, transfo
         torch.cuda.synchronize()
         assert torch.equal(far_F[1:-1], F) and torch.equal(far_N[1:-1], N) and torch.equal(far_y, y)
         assert bool((far_F[0] == 55).all()) and bool((far_F[-1] == 55).all()) and float(far_N[0]) == 0.0 == float(far_N[-1])
-        # the kernels for any block shape see the same: their N, and their reconstruction of the same {N, F}
+        # the tiled kernels see the same: their reconstruction of the same {N, F}
         slow = Case(x, None, dtype, block, bits, ftype, mask, api.PBZ_PATH_GENERIC, transform=transform)
+        assert route(slow.codec, "decompress", shape, dtype) == TILED
         slow.check_decompress(N, F)

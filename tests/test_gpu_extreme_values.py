@@ -6,7 +6,7 @@ import torch
 
 from oracle import pbz_oracle as po
 from paper_2406_11209_amd import synth
-from parity import Case
+from parity import MASKED, SHAPE, Case, route, take_wherever_possible
 
 pytestmark = pytest.mark.gpu
 
@@ -14,11 +14,11 @@ pytestmark = pytest.mark.gpu
 # overflows below 1.8e-304 (int16), 1.2e-299 (int32) and 7e-307 (int8); r C above 5e303 and 8e298.
 NARROW, WIDE = (1e-37, 2e36), (1e-305, 1e-307, 1e304)
 # block, array, working and index type of every masked family's kernels ...
-MASKED = [((8, 8), "f32", "f32", 8), ((8, 8), "f64", "f64", 16), ((8, 8), "f64", "f32", 8), ((8, 8), "f64", "f64", 32),
-          ((4, 4, 4), "f32", "f32", 8), ((4, 4, 4), "f64", "f64", 16), ((16, 16), "f32", "f32", 8), ((16, 16), "f64", "f64", 16),
-          ((16, 16), "f64", "f64", 32), ((4, 16, 16), "f32", "f32", 8), ((4, 16, 16), "f64", "f64", 16), ((8, 8, 8), "f32", "f32", 8),
-          ((8, 8, 8), "bf16", "f32", 8), ((8, 8, 8), "f64", "f64", 16), ((8, 8, 8), "f64", "f64", 32),
-          ((16, 16, 16), "f32", "f32", 8), ((16, 16, 16), "f64", "f64", 16)]
+MASKED_ROWS = [((8, 8), "f32", "f32", 8), ((8, 8), "f64", "f64", 16), ((8, 8), "f64", "f32", 8), ((8, 8), "f64", "f64", 32),
+               ((4, 4, 4), "f32", "f32", 8), ((4, 4, 4), "f64", "f64", 16), ((16, 16), "f32", "f32", 8), ((16, 16), "f64", "f64", 16),
+               ((16, 16), "f64", "f64", 32), ((4, 16, 16), "f32", "f32", 8), ((4, 16, 16), "f64", "f64", 16), ((8, 8, 8), "f32", "f32", 8),
+               ((8, 8, 8), "bf16", "f32", 8), ((8, 8, 8), "f64", "f64", 16), ((8, 8, 8), "f64", "f64", 32),
+               ((16, 16, 16), "f32", "f32", 8), ((16, 16, 16), "f64", "f64", 16)]
 # ... and of the kernels per block shape
 SHAPES = [((16,), "f32", "f32", 8), ((64,), "f32", "f32", 8), ((8, 16), "f32", "f32", 8), ((4, 4), "f32", "f32", 8),
           ((32, 32), "f32", "f32", 8), ((32, 32), "f64", "f64", 16), ((4, 8, 8), "f32", "f32", 8), ((2, 8, 8), "f64", "f64", 16),
@@ -26,7 +26,7 @@ SHAPES = [((16,), "f32", "f32", 8), ((64,), "f32", "f32", 8), ((8, 16), "f32", "
 EXTENTS = {1: (65536,), 2: (1024, 1040), 3: (64, 96, 520), 4: (16, 16, 32, 64)}
 
 
-@pytest.mark.parametrize("masked,block,dtype,ftype,bits", [(True,) + s for s in MASKED] + [(False,) + s for s in SHAPES],
+@pytest.mark.parametrize("masked,block,dtype,ftype,bits", [(True,) + s for s in MASKED_ROWS] + [(False,) + s for s in SHAPES],
                          ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_blocks_at_the_ends_of_the_range(masked, block, dtype, ftype, bits):
     g = np.random.Generator(np.random.PCG64(len(block) + bits))
@@ -45,6 +45,8 @@ def test_blocks_at_the_ends_of_the_range(masked, block, dtype, ftype, bits):
             factor = 1e297                                       # the oracle forms r C in 64 bits, too
         largest = {1: 8.0, 2: 32.0, 3: 64.0, 4: 32.0}[len(block)] if factor > 1.0 else 1.0      # keeps coefficients finite
         case = Case(cast(field * (factor / largest)), None, dtype, block, bits, ftype, mask)
+        take_wherever_possible(case.codec, MASKED if masked else SHAPE)
+        assert route(case.codec, "compress", shape, dtype) == (MASKED if masked else SHAPE)
         N, F, ref, _ = case.check_compress("A")
         assert np.abs(ref.F).max() > 100                         # ordinary indices: nothing vanished
         y = case.codec.decompress(N, F, shape, case.xA.dtype)
@@ -58,6 +60,7 @@ def test_lines_of_64_keep_their_digits_below_the_normal_numbers():
     g = np.random.Generator(np.random.PCG64(3))
     x = (g.standard_normal(64 * 1024) * 4e-39).astype(np.float32)
     case = Case(x, None, "f32", (64,), 8, "f32")
+    assert route(case.codec, "decompress", x.shape, "f32") == SHAPE
     N, F = case.codec.compress(case.xA)
     y = case.codec.decompress(N, F, x.shape, torch.float32)
     ref = po.decompress(case.oc(N, F))

@@ -350,3 +350,66 @@ def test_every_specialised_kernel_has_a_gpu_parity_row():
     assert len(reachable) > 100
     missing = {name: how for name, how in reachable.items() if name not in covered}
     assert not missing, f"specialised kernels without a GPU parity row: {missing}"
+
+
+def test_every_general_kernel_has_a_gpu_parity_row():
+    """The same for the kernels that pbz_kernel_name calls "generic": every one of the families' kernels under any mask that the
+    dispatch can reach is run by a row of test_gpu_any_mask, and every block shape with kernels of its own by test_gpu_block_shapes
+    (their types are run-time arguments; FP32 and FP64 work and both transforms are separate kernels)."""
+    import itertools
+
+    import test_gpu_any_mask as masks
+    import test_gpu_block_shapes as shapes
+    from parity import MASKED, SHAPE, route, take_wherever_possible
+    def kernel(block, dtype, ftype, bits):       # whether N is FP64 is the kernel's own in one family, whether the work is in the others
+        lane = block in ((8, 8), (4, 4, 4))
+        return block, dtype, ftype == "f64" or (bits > 8 and not lane), bits
+
+    run = {kernel(block, dtype, ftype, int(bits)) for block, dtype, ftype, bits in masks.ROWS}
+    reachable = set()
+    blocks = list(masks.SHAPES) + [(4, 8), (16, 8), (8, 16), (32, 32), (2, 8, 8), (4, 8, 8), (8, 4, 4), (4, 4, 8), (16,), (4, 4, 4, 4)]
+    for block, dtype, ftype, bits in itertools.product(blocks, api.FTYPES, api.FTYPES, (8, 16, 32)):
+        mask = np.ones(block, dtype=bool)
+        mask.reshape(-1)[-1] = False
+        c = Codec(block, ftype, bits, mask)
+        take_wherever_possible(c, MASKED)
+        for shape in (tuple(8 * b for b in block), tuple(3 * b + 1 for b in block[:-1]) + (8 * block[-1] + 4,)):
+            if MASKED in (route(c, "compress", shape, dtype), route(c, "decompress", shape, dtype)):
+                reachable.add(kernel(block, dtype, ftype, bits))
+    assert len(reachable) >= 51
+    assert reachable <= run, f"kernels for any mask without a GPU parity row: {sorted(reachable - run)}"
+    works = {ftype == "f64" or bits > 8 for _, ftype, bits in shapes.TYPES}
+    assert works == {False, True}
+    for extents in itertools.chain.from_iterable(itertools.product((1, 2, 4, 8, 16, 32, 64), repeat=nd) for nd in (1, 2, 3, 4)):
+        if extents[0] == 1 or np.prod(extents) > 4096:
+            continue                                       # leading extents of one fold away
+        for ftype in ("f32", "f64"):
+            c = Codec(extents, ftype, "i8", None)
+            take_wherever_possible(c, SHAPE)
+            got = route(c, "compress", tuple(4 * e for e in extents), "bf16" if ftype == "f32" else "f16")
+            if got == SHAPE:
+                assert extents in shapes.SHAPES, extents
+
+
+def test_kernels_for_any_mask_and_per_block_shape_take_their_rows():
+    """What the GPU rows force is what they get: also without a GPU, so that a shape that drops out of a list is seen here."""
+    import test_gpu_any_mask as masks
+    import test_gpu_block_shapes as shapes
+    from parity import DENSE, MASKED, SHAPE, TILED, route, take_wherever_possible
+    for block, dtype, ftype, bits in masks.ROWS:
+        mask = np.ones(block, dtype=bool)
+        mask.reshape(-1)[-1] = False
+        c = Codec(block, ftype, int(bits), mask)
+        take_wherever_possible(c, MASKED)
+        for shape in masks.SHAPES[block]:
+            assert route(c, "compress", shape, dtype) == route(c, "decompress", shape, dtype) == MASKED, (block, dtype, bits, shape)
+            assert route(c, "compress", shape, dtype, 264) == TILED
+    for block in shapes.SHAPES:
+        for dtype, ftype, bits in shapes.TYPES:
+            mask = np.ones(block, dtype=bool)
+            mask.reshape(-1)[-1] = False
+            c = Codec(block, ftype, bits, mask)
+            take_wherever_possible(c, SHAPE)
+            want = SHAPE if shapes.taken(block, ftype, bits) else DENSE
+            shape = tuple(3 * b + 1 for b in block)
+            assert route(c, "compress", shape, dtype) == route(c, "decompress", shape, dtype) == want, (block, dtype, ftype, bits)
