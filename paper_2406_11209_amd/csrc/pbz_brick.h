@@ -855,14 +855,48 @@ void decompress_with(BrickGeom g, const void* N, const void* F, void* y, hipStre
 template <typename T, int BX>
 constexpr bool kTaken = BX < 64 || sizeof(T) == 4;
 
+// When these kernels take a call, against the tiled ones: a wave does a tile in one long straight run of code, so that one alone
+// takes longer than a workgroup with its phases, while many overlap.  Decompress, whose rows pass LDS once more, up to some 2^21
+// elements: 1.05-1.6 of the tiled kernels' time (FP64 work with blocks of 256 and more and 16-bit or 32-bit indices: 9 -> 15 us; FP32 work
+// with rows of 8 to 32: 7 -> 9), 0.75-0.95 from 2^22 on, rows of 16 and more in FP32 work and int32 in small flat blocks from
+// 2^23; not so rows of 4, 4-D blocks in FP32 work, int8 in FP64 work and small blocks there (0.6-1.03 at any size; FP64 arrays in rows
+// of 4: 1.0-1.09).  Under a mask the tiled kernels look every entry up: 8x8, and 16x16 in FP64 work, 0.7-1.0.  Compress: 0.4-1.05 but for
+// FP64 arrays in rows of 16 and more in FP32 work (1.1-1.2), 32x32 blocks of FP32 (1.05), and FP64 work that leaves a lane 64
+// values, with int32 or FP64 arrays and nothing pruned (1.1-1.6), from 2^14 to 2^20 elements.  32-bit indices of flat blocks with
+// nothing pruned stay with the tiled kernels where measured slower at every size above a few blocks: 8x8 both ways (1.05-1.3), 4x8 and
+// 8x4 of FP64 arrays decompressing (1.05-1.15); and so do 32x32 blocks of FP64 arrays in FP32 work under a mask, decompressing
+// (1.2).
+template <typename T, typename S>
+bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements) {
+  constexpr int64_t kMi = int64_t(1) << 20;
+  constexpr bool kWide = sizeof(T) == 8, kFlat = S::BW == 1 && S::BZ == 1;
+  constexpr bool k8x8 = kFlat && S::BY == 8 && S::BX == 8, k4x8 = kFlat && S::VOL == 32 && S::BX < 16;
+  const int array = ftype_bytes(xtype), index = itype_bytes(c->itype);
+  const bool pruned = c->kept != c->vol;
+  if (c->route == kRouteShape || S::BX == 64) return true;
+  if (index == 4 && !pruned && (k8x8 || (k4x8 && !compress && array == 8))) return elements <= (compress ? 4096 : 1024);
+  if (compress) {
+    const bool enough = elements <= 4096 || elements >= 3 * kMi;
+    if (kWide) return pruned || !(S::VALUES == 64 && (index == 4 || array == 8)) || enough;
+    return !((array == 8 && S::BX >= 16) || (array == 4 && S::VOL == 1024)) || enough;
+  }
+  if (!kWide && S::VOL == 1024 && array == 8 && pruned) return false;
+  if (S::BX == 4 && (kWide || array < 8 || S::BW > 1 || pruned)) return true;
+  if (!kWide && S::BW > 1) return true;
+  if (kWide && ((index == 1 && S::VOL < 1024) || (!kFlat && S::VOL <= 128) || (index == 2 && S::VOL <= 32 && S::BX <= 8))) return true;
+  if (pruned && (k8x8 || (kWide && kFlat && S::BY == 16 && S::BX == 16))) return true;
+  return elements >= ((!kWide && S::BX >= 16 && !pruned) || (index == 4 && kFlat && S::VOL < 256) ? 8 * kMi : 3 * kMi);
+}
+
 template <typename T, int BW, int BZ, int BY, int BX>
 int compress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* x, int xtype, void* N, void* F,
                    hipStream_t s, bool dry_run) {
   if constexpr (kTaken<T, BX>) {
     BrickGeom g;
     if (!make_brick(c, geo, x, xtype, t, BW, BZ, BY, BX, &g)) return 0;
-    if (dry_run) return 1;
     using S = Shape<T, BW, BZ, BY, BX>;
+    if (!pays<T, S>(c, true, xtype, geo.n_blocks * S::VOL)) return 0;
+    if (dry_run) return 1;
     if (c->transform == PBZ_TRANSFORM_HAAR) compress_with<kTfHaar, T, S>(g, x, N, F, s);
     else compress_with<kTfDct, T, S>(g, x, N, F, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
@@ -875,8 +909,9 @@ int decompress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t,
   if constexpr (kTaken<T, BX>) {
     BrickGeom g;
     if (!make_brick(c, geo, y, ytype, t, BW, BZ, BY, BX, &g)) return 0;
-    if (dry_run) return 1;
     using S = Shape<T, BW, BZ, BY, BX>;
+    if (!pays<T, S>(c, false, ytype, geo.n_blocks * S::VOL)) return 0;
+    if (dry_run) return 1;
     if (c->transform == PBZ_TRANSFORM_HAAR) decompress_with<kTfHaar, T, S>(g, N, F, y, s);
     else decompress_with<kTfDct, T, S>(g, N, F, y, s);
     return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;

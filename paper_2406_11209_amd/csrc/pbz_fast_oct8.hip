@@ -965,6 +965,21 @@ inline MaskArgs<true> oct_mask_args(const pbz_codec* c, const uint16_t* pos) {
   m.kept = c->kept;
   return m;
 }
+// 2^24 elements in rows of 1 / 4 / 8 / 24 blocks, FP32 / int8: compress 3.6 / 1.2 / 0.94 / 0.88, decompress 3.9 / 1.3 / 0.82 / 0.75.  Rows of an odd
+// number of blocks start half a wave's piece into a line, which two waves then fetch or write: FP32 compress 1.1-1.3, int8
+// decompress 1.4, int16 0.95.  FP64 arrays compressing want all lanes busy (0.9; 1.1 at three quarters).  int32 compressing 1.06-1.3
+// (few elements: equal).  Rows that are no whole blocks: 0.87-1.0 compressing, 0.9-1.3 decompressing, FP64 arrays 1.4 and 1.2; few elements
+// 0.7-0.85, FP64 arrays 1.06-1.5 and 0.7.
+template <typename XT, typename IT>
+inline bool oct_masked_pays(const MaskedCall& m) {
+  const bool even = m.gx % 2 == 0;
+  if (m.whole_rows) {
+    if (!m.compress) return m.few || (m.fill(8) >= 0.7 && (even || sizeof(IT) > 1));
+    return sizeof(IT) < 4 && (m.few || (m.fill(8) >= (sizeof(XT) == 8 ? 0.95 : 0.7) && (even || sizeof(XT) == 2)));
+  }
+  if (m.compress) return sizeof(XT) < 8 && (m.few || m.fill(8) >= 0.75);
+  return m.few;
+}
 template <typename K> struct OctMasked;
 template <int TF, typename XT>
 struct OctMasked<Oct8Kernel<TF, XT, 8, 8, 8>> {
@@ -972,6 +987,7 @@ struct OctMasked<Oct8Kernel<TF, XT, 8, 8, 8>> {
     f.kz = f.ky = f.kx = 8;
     return Oct8Kernel<TF, XT, 8, 8, 8>::matches(c, f, xtype);
   }
+  static bool pays(const MaskedCall& m) { return oct_masked_pays<XT, int8_t>(m); }
   static int fits(const FastGeom& g) { return Oct8Kernel<TF, XT, 8, 8, 8>::fits(g); }
   template <bool kTailX>
   static void launch(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* x, void* N, void* F,
@@ -1005,6 +1021,7 @@ struct OctMasked<Oct8WideKernel<TF, XT, IT>> {
     f.kz = f.ky = f.kx = 8;
     return Oct8WideKernel<TF, XT, IT>::matches(c, f, xtype);
   }
+  static bool pays(const MaskedCall& m) { return oct_masked_pays<XT, IT>(m); }
   static int fits(const FastGeom& g) { return Oct8WideKernel<TF, XT, IT>::fits(g); }
   template <bool kTailX>
   static void launch(const pbz_codec* c, const FastGeom& g, dim3 grid, const uint16_t* pos, const void* x, void* N, void* F,

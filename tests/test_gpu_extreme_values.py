@@ -6,7 +6,8 @@ import torch
 
 from oracle import pbz_oracle as po
 from paper_2406_11209_amd import synth
-from parity import MASKED, SHAPE, Case, route, take_wherever_possible
+from parity import SHAPE, Case, route, take_wherever_possible
+from test_gpu_any_mask import kind
 
 pytestmark = pytest.mark.gpu
 
@@ -45,8 +46,9 @@ def test_blocks_at_the_ends_of_the_range(masked, block, dtype, ftype, bits):
             factor = 1e297                                       # the oracle forms r C in 64 bits, too
         largest = {1: 8.0, 2: 32.0, 3: 64.0, 4: 32.0}[len(block)] if factor > 1.0 else 1.0      # keeps coefficients finite
         case = Case(cast(field * (factor / largest)), None, dtype, block, bits, ftype, mask)
-        take_wherever_possible(case.codec, MASKED if masked else SHAPE)
-        assert route(case.codec, "compress", shape, dtype) == (MASKED if masked else SHAPE)
+        want = kind(block, dtype, ftype, bits) if masked else SHAPE
+        take_wherever_possible(case.codec, want)
+        assert route(case.codec, "compress", shape, dtype) == want
         N, F, ref, _ = case.check_compress("A")
         assert np.abs(ref.F).max() > 100                         # ordinary indices: nothing vanished
         y = case.codec.decompress(N, F, shape, case.xA.dtype)
