@@ -121,10 +121,13 @@ size_t carve(void* base, int64_t n, Workspace* w) {
   return off;
 }
 
-// doubles <-> unsigned keys with the same order (negative values: all bits flipped; others: sign bit set)
+// doubles <-> unsigned keys with the same order (negative values: all bits flipped; others: sign bit set).  NaN comes before
+// -infinity or after infinity, by its sign; the one whose key would be the largest number, which k_splitters needs free, takes the
+// key before it.
 __device__ __forceinline__ uint64_t key_of(double v) {
   const uint64_t u = uint64_t(__double_as_longlong(v));
-  return (u >> 63) ? ~u : (u | (uint64_t(1) << 63));
+  const uint64_t k = (u >> 63) ? ~u : (u | (uint64_t(1) << 63));
+  return k - (k == ~uint64_t(0) ? 1u : 0u);
 }
 __device__ __forceinline__ double value_of(uint64_t k) {
   const uint64_t u = (k >> 63) ? (k & ~(uint64_t(1) << 63)) : ~k;
@@ -537,8 +540,8 @@ __device__ __forceinline__ BucketPlace bucket_place(int b, int operand, int64_t 
 // kHeldKeys, are read once and stay in registers.  They are dealt into kSubs equal intervals between the smallest and the
 // largest of their values (between neighbouring quantiles the means are spread nearly evenly: one key an interval), put
 // together by interval in LDS, at most kBucketCap keys a round, and every key counts the smaller ones of its interval.
-// Larger buckets, and those with more than kMaxSub keys in one interval, go to the list of k_bucket_sort_rest (one in a
-// thousand).  With one bucket in == out.
+// Larger buckets, those with more than kMaxSub keys in one interval (one in a thousand) and those with NaN, which has no
+// interval among the values, go to the list of k_bucket_sort_rest.  With one bucket in == out.
 constexpr int kHeldKeys = 8192;
 __global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_t* in_all, uint64_t* out_all, int64_t n,
                                                                    int buckets, const uint32_t* __restrict__ totals,
@@ -590,11 +593,11 @@ __global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_
 #pragma unroll
   for (int j = 0; j < kPerThread; ++j)
     if (j * kBucketThreads + t < m) {
-      int s = int((value_of(held[j]) - least) * scale);
-      s = s < 0 ? 0 : (s < kSubs ? s : kSubs - 1);
+      const double value = value_of(held[j]);
+      const int s = int(fmin(fmax((value - least) * scale, 0.0), double(kSubs - 1)));
       const uint32_t at = atomicAdd(&cursor[s], 1u);
       where[j] = uint32_t(s) | (at << 16);
-      crowded = crowded || at >= uint32_t(kMaxSub);
+      crowded = crowded || at >= uint32_t(kMaxSub) || value != value;
     }
   if (__syncthreads_or(crowded)) {
     if (t == 0) rest[1 + atomicAdd(rest, 1u)] = blockIdx.x * 2 + blockIdx.y;
@@ -647,8 +650,8 @@ __global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_
 
 // The buckets that k_bucket_sort leaves, listed in rest (their number first), any number of keys in any distribution.  As there,
 // with the keys read again where they are needed and intervals of one shared value left as they are.  Where an interval
-// has more than kMaxSub keys of several values the intervals are made equal in the keys instead (values over many orders
-// of magnitude); if that does not help, fold_sort takes over.  A bucket that does not fit LDS takes several rounds.
+// has more than kMaxSub keys of several values, or there is NaN or infinity at an end, the intervals are made equal in the keys
+// instead (values over many orders of magnitude); if that does not help, fold_sort takes over.  A bucket that does not fit LDS takes several rounds.
 __global__ __launch_bounds__(kBucketThreads) void k_bucket_sort_rest(const uint64_t* in_all, uint64_t* out_all, int64_t n,
                                                                      int buckets, const uint32_t* __restrict__ totals,
                                                                      const uint32_t* __restrict__ rest) {
@@ -682,15 +685,14 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_sort_rest(const uint6
       hi = k > hi ? k : hi;
     });
     group_bounds(lo, hi, bounds);
-    bool by_value = true;
+    bool by_value = isfinite(value_of(lo)) && isfinite(value_of(hi));
     for (;;) {
       // subtraction, conversion, product and truncation are all non-decreasing: intervals follow the order of the keys
       const double least = value_of(lo);
       const double span = by_value ? value_of(hi) - least : double(hi - lo);
       const double scale = span > 0.0 ? double(kSubs) / span : 0.0;
       auto sub_of = [&](uint64_t k) {
-        const int s = int((by_value ? value_of(k) - least : double(k - lo)) * scale);
-        return s < 0 ? 0 : (s < kSubs ? s : kSubs - 1);
+        return int(fmin((by_value ? value_of(k) - least : double(k - lo)) * scale, double(kSubs - 1)));
       };
       for (int i = threadIdx.x; i < kSubs; i += kBucketThreads) cursor[i] = 0;
       __syncthreads();

@@ -1,10 +1,13 @@
 """GPU parity of the approximate Wasserstein distance over the sizes and distributions at which its sort takes another
 path: one bucket, several, more than the sample sort takes; shared values, one value, a few intervals crowded."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 from oracle import pbz_oracle as po
+from paper_2406_11209_amd import api
 from paper_2406_11209_amd.api import Codec
 from parity import oracle_compressed
 
@@ -49,3 +52,78 @@ def test_more_blocks_than_the_sample_sort_takes():
     n = (1 << 22) + 1
     test_distance_at_every_path_of_the_sort(n, "smooth")
     test_distance_at_every_path_of_the_sort(n - 1, "mostly zero")
+
+
+def sampled(n):
+    """The places in the input from which the splitters of the sample sort are drawn (sample_place of the kernel)."""
+    buckets = 1
+    while n > 4096 and buckets * 2048 < n:
+        buckets *= 2
+    shift = min(4 * buckets, 4096).bit_length() - 1
+    i = np.arange(1 << shift, dtype=np.int64)
+    lo, hi = (n * i) >> shift, (n * (i + 1)) >> shift
+    return lo + ((((i * 2654435761) & 0xFFFFFFFF) * (hi - lo)) >> 32)
+
+
+def hidden_cluster(g, n):
+    """Two fifths of the keys within 1e-6 of each other, between two splitters 1e-3 or more apart, none of them sampled: an interval with more
+    keys than LDS takes, by value and by key."""
+    v = g.random(n)
+    free = np.setdiff1d(np.arange(n), sampled(n))
+    take = free[g.random(free.size) < 0.4]
+    v[take] = 0.5 + 1e-6 * g.random(take.size)
+    return v
+
+
+def not_finite(bits):
+    def values(g, n):
+        v = np.where(g.random(n) < 0.5, g.standard_normal(n), np.exp(20.0 * g.standard_normal(n)))
+        at = g.random(n) < 0.3
+        v[at] = g.choice(np.array(bits, dtype=np.uint64), int(at.sum())).view(np.float64)
+        return v
+    return values
+
+
+INFINITY, MINUS = 0x7FF0 << 48, 1 << 63
+ORDERS = {
+    **VALUES,
+    "small and large": lambda g, n: np.exp(g.uniform(-27.6, 0.0, n)) * g.choice([-1.0, 1.0], n),
+    "hidden cluster": hidden_cluster,
+    "infinite": not_finite([INFINITY, INFINITY | MINUS]),
+    "rarely NaN": lambda g, n: np.where(np.arange(n) % 4099 == 7, np.nan, g.standard_normal(n)),
+    "NaN": not_finite([INFINITY, INFINITY | MINUS, 0x7FF8 << 48, 0xFFF8 << 48, 0x7FFFFFFFFFFFFFFF, 0xFFFFFFFFFFFFFFFF]),
+}
+
+
+def keys(v):
+    """Unsigned numbers in the order of the doubles, NaN by its sign at either end."""
+    u = v.view(np.uint64)
+    return np.where(u >> np.uint64(63), ~u, u | np.uint64(1 << 63))
+
+
+@pytest.mark.parametrize("values", list(ORDERS))
+@pytest.mark.parametrize("n", SIZES + [(1 << 22) + 1])
+def test_block_means_come_out_in_order(n, values):
+    """The keys that the workspace is left with (behind the parameters and the partial sums) are the block means in order, bit for bit: what the
+    softmax hides of a wrong order shows here.  A NaN's bits may change, its place in the order is by its sign."""
+    g = np.random.Generator(np.random.PCG64(n + len(values)))
+    codec = Codec((2,), "f64", "i8", np.array([True, False]))
+    operands, means = [], []
+    for scale in (1.0, -1.5):
+        v = ORDERS[values](g, n) * scale
+        F = np.where(v < 0, -127, 127).astype(np.int8).reshape(n, 1)
+        N = np.where(np.isnan(v), v, np.abs(v))
+        operands += [torch.from_numpy(N).cuda(), torch.from_numpy(F).cuda()]
+        means.append(N * F[:, 0].astype(np.float64) * (1.0 / (127.0 * np.sqrt(2.0))))
+    need = ctypes.c_size_t()
+    api.check(codec._lib.pbz_approximate_wasserstein_workspace(codec._h, n, ctypes.byref(need)))
+    workspace = torch.zeros(need.value, dtype=torch.uint8, device="cuda")
+    codec.approximate_wasserstein(*operands, 2.0, workspace=workspace)
+    first = 256 + 2 * 1024 * 2 * 8
+    got = workspace[first:first + 16 * n].cpu().numpy().view(np.uint64).reshape(2, n)
+    for have, mean in zip(got, means):
+        assert np.all(have[:-1] <= have[1:])
+        value = np.where(have >> np.uint64(63), have & np.uint64((1 << 63) - 1), ~have).view(np.float64)
+        assert np.isnan(value).sum() == np.isnan(mean).sum()
+        want = np.sort(keys(mean[~np.isnan(mean)]))
+        assert np.array_equal(have[~np.isnan(value)], want)
