@@ -90,10 +90,15 @@ SortPlan sort_plan(int64_t n) {
 size_t align_up(size_t v) { return (v + 255) & ~size_t(255); }
 
 size_t carve(void* base, int64_t n, Workspace* w) {
-  const SortPlan plan = sort_plan(n);
-  const int64_t n_tiles = (n + kTileKeys - 1) / kTileKeys;
-  const size_t counts = plan.sample ? size_t(plan.tiles) * 2 * size_t(plan.buckets) : size_t(kBins) * size_t(n_tiles);
-  const size_t totals = plan.sample ? 2 * size_t(plan.buckets) : size_t(kBins);
+  // Never less than for fewer blocks, so that a workspace for the largest array serves all: beyond the sample sort's
+  // sizes its largest needs count, and tiles count before they are evened out.
+  const int64_t sampled = n < kSampleSortMax ? n : kSampleSortMax;
+  const size_t buckets = size_t(sort_plan(sampled).buckets);
+  const int64_t tiles = (sampled + kMinTileKeys - 1) / kMinTileKeys;
+  const size_t sample_counts = size_t(tiles < kMaxTiles ? tiles : kMaxTiles) * 2 * buckets;
+  const size_t radix_counts = n > kSampleSortMax ? size_t(kBins) * size_t((n + kTileKeys - 1) / kTileKeys) : 0;
+  const size_t counts = sample_counts > radix_counts ? sample_counts : radix_counts;
+  const size_t totals = 2 * buckets;
   size_t off = 0;
   char* p = static_cast<char*>(base);
   auto take = [&](size_t bytes) {
@@ -107,9 +112,9 @@ size_t carve(void* base, int64_t n, Workspace* w) {
   char* e = take(sizeof(uint64_t) * 2 * size_t(n));
   char* f = take(sizeof(uint32_t) * 2 * counts);
   char* g = take(sizeof(uint32_t) * 2 * totals);
-  char* h = take(sizeof(uint64_t) * 2 * size_t(plan.buckets));
-  char* i = take(sizeof(uint32_t) * (2 + 2 * size_t(plan.buckets)));
-  char* j = take(sizeof(uint2) * size_t(plan.buckets));
+  char* h = take(sizeof(uint64_t) * 2 * buckets);
+  char* i = take(sizeof(uint32_t) * (2 + 2 * buckets));
+  char* j = take(sizeof(uint2) * buckets);
   if (w) {
     w->params = reinterpret_cast<OperandParams*>(a);
     w->partials = reinterpret_cast<double*>(b);
@@ -549,6 +554,7 @@ __device__ __forceinline__ BucketPlace bucket_place(int b, int operand, int64_t 
 constexpr int kHeldKeys = 8192;
 // above, the pieces of a bucket are at most twice its keys / kPieceKeys, those of both operands at most 2 * 2 n / kPieceKeys <= K
 constexpr int kPieceKeys = 4 * kBucketKeys;
+static_assert(2 * kSampleSortMax / kBucketKeys >= kBins, "the workspace's totals hold the radix sort's digits");
 __global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_t* in_all, uint64_t* out_all, int64_t n,
                                                                    int buckets, const uint32_t* __restrict__ totals,
                                                                    uint32_t* __restrict__ rest, uint2* __restrict__ pieces) {
@@ -663,11 +669,12 @@ __global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_
   }
 }
 
-// The pieces of large buckets of one value, and the buckets that k_bucket_sort leaves, listed in rest, any number of keys in any distribution.  As there,
-// with the keys read again where they are needed and intervals of one shared value left as they are.  Where an interval
-// has more than kMaxSub keys of several values, or there is NaN or infinity at an end, the intervals are made equal in the keys
-// instead (values over many orders of magnitude); if that does not help, fold_sort takes over (a
-// cluster of two fifths of all keys that the samples miss altogether: 0.9 ms for 70001 keys, 18 for 2^20).  A bucket that does not fit LDS takes several rounds.
+// The pieces of large buckets of one value, and the buckets that k_bucket_sort leaves, listed in rest, any number of keys in
+// any distribution.  As there, with the keys read again where they are needed and intervals of one shared value left as
+// they are.  Where an interval has more than kMaxSub keys of several values (values over many orders of magnitude), or there
+// is NaN or infinity at an end, the intervals are made equal in the keys instead; if that does not help, fold_sort takes over
+// (a cluster of two fifths of all keys that the samples miss altogether: 0.9 ms for 70001 keys, 18 for 2^20).  A bucket that
+// does not fit LDS takes several rounds.
 __global__ __launch_bounds__(kBucketThreads) void k_bucket_sort_rest(const uint64_t* in_all, uint64_t* out_all, int64_t n,
                                                                      int buckets, const uint32_t* __restrict__ totals,
                                                                      const uint32_t* __restrict__ rest,

@@ -179,6 +179,22 @@ def test_entry_points_reject_bad_arguments_before_any_launch():
     assert lib.pbz_ssim(h, 4, p, p, p, p, 0.0, 0.0, 1.0, 1.0, 1.0, p, p, 64, None) == -8
 
 
+def test_wasserstein_workspace_never_shrinks_with_more_blocks():
+    """A workspace for the largest array serves every smaller one: around each size at which the sort's plan changes, and between."""
+    codec = Codec((8, 8), "f32", "i8")
+    need = ctypes.c_size_t()
+
+    def bytes_for(n):
+        assert api.load_library().pbz_approximate_wasserstein_workspace(codec._h, n, ctypes.byref(need)) == 0
+        return need.value
+
+    edges = [4096, 8192, 1 << 22] + [2048 << k for k in range(12)] + [8192 * k for k in (2, 3, 100, 255, 256, 257)]
+    sizes = sorted({max(1, e + d) for e in edges for d in (-2, -1, 0, 1, 2)} | set(range(1, 30000, 7)) | {int(1.03 ** k) for k in range(720)})
+    needs = [bytes_for(n) for n in sizes]
+    for n, a, b in zip(sizes, needs, needs[1:]):
+        assert a <= b, (n, a, b)
+
+
 def test_transform_switch():
     lib = api.load_library()
     c = Codec((8, 8), "f32", "i8", transform="haar")
