@@ -28,15 +28,18 @@ namespace {
 constexpr int kCached = 4;               // dwords of a block per lane that the rebinning kernels keep in registers
 constexpr int kNPerLane = kMaxBlocksPerWave / 64;
 
-// N of `count` (at most kMaxBlocksPerWave) blocks from k0 on, widened: requested, then put away
+// N of `count` (at most kMaxBlocksPerWave) blocks from k0 on: requested, as they are stored, and widened when they are put away,
+// so that the requests for the indices do not wait for them
 template <int kNType>
 struct StagedN {
+  typedef typename std::conditional<kNType == PBZ_F64, double, typename std::conditional<kNType == PBZ_F32, float, uint16_t>::type>::type stored_t;
+  stored_t raw[kNPerLane];
   double v[kNPerLane];
-  __device__ __forceinline__ void request(const void* N, int64_t k0, int count, bool f16) {
+  __device__ __forceinline__ void request(const void* N, int64_t k0, int count) {
 #pragma unroll
     for (int u = 0; u < kNPerLane; ++u) {
       const int i = u * 64 + int(threadIdx.x & 63);
-      if (u * 64 < count) v[u] = load_N<kNType>(N, k0 + (i < count ? i : count - 1), f16);
+      if (u * 64 < count) raw[u] = static_cast<const stored_t*>(N)[k0 + (i < count ? i : count - 1)];
     }
   }
   __device__ __forceinline__ bool beyond(double limit, int count) const {         // any of the lane's, NaN included
@@ -45,10 +48,11 @@ struct StagedN {
     for (int u = 0; u < kNPerLane; ++u) any = any || (u * 64 < count && !(fabs(v[u]) < limit));
     return any;
   }
-  __device__ __forceinline__ void put(double* lds, int count) {
+  __device__ __forceinline__ void put(double* lds, int count, bool f16) {
 #pragma unroll
     for (int u = 0; u < kNPerLane; ++u) {
       const int i = u * 64 + int(threadIdx.x & 63);
+      if (u * 64 < count) v[u] = load_N<kNType>(raw + u, 0, f16);
       if (i < count) lds[i] = v[u];
     }
   }
@@ -112,8 +116,7 @@ struct Rebin {
   // infinite (below 5.6e-309) or whose own rounding leaves quotients beyond r (subnormal), infinite N (whose coefficients
   // div_by would turn into NaN) and NaN.  NaN counts for nothing in the maximum, and becomes the index -r.  One index at a
   // time: the path takes no registers from the others.  a, b, o: the block in LDS; one team of lanes.  Returns the new N.
-  // (Every block of a wave's tile that holds one such block goes this way: the others' indices come out the same.  The check for them
-  // costs the ordinary blocks 2-4 %: 2M blocks of 19 int16 indices, sum 64.1 -> 66.6 us.)
+  // (Every block of a wave's tile that holds one such block goes this way: the others' indices come out the same.)
   typedef typename std::conditional<kIType == PBZ_I8, int8_t, typename std::conditional<kIType == PBZ_I16, int16_t, int32_t>::type>::type index_t;
   __device__ __forceinline__ double far_block(int t, int team, int kept, const uint8_t* a, const uint8_t* b, uint8_t* o) const {
     double m = 0.0, n = 0.0;
@@ -145,7 +148,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const
                                                                  double sign2, double shift, int64_t n_blocks, int n_f16) {
   extern __shared__ __align__(16) uint8_t smem[];
   constexpr int kPer = PerDword<kIType>::value;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
   uint8_t* sa = smem + wave * wave_bytes(st, kTwo ? 3 : 2, kTwo ? 2 : 1);
   uint8_t* so = sa + st.region;
   uint8_t* sb = so + st.region;                            // used with two operands only
@@ -166,12 +169,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const
     const int64_t at = k0 * st.bpb;
     const int len = count * st.bpb;
     StagedN<kNType> n1, n2;
-    n1.request(N1, k0, count, n_f16 != 0);
-    if (kTwo) n2.request(N2, k0, count, n_f16 != 0);
+    n1.request(N1, k0, count);
+    if (kTwo) n2.request(N2, k0, count);
     stage_span<2>(F1, a_end, F1 + at, len, sa);
     if (kTwo) stage_span<2>(F2, b_end, F2 + at, len, sb);
-    n1.put(na, count);
-    if (kTwo) n2.put(nb, count);
+    n1.put(na, count, n_f16 != 0);
+    if (kTwo) n2.put(nb, count, n_f16 != 0);
     wave_lds_sync();
     const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : 0, po = phase_of(Fout + at);
     // a block that needs far_block: after the others, which that keeps out of the registers of this loop
@@ -216,7 +219,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const
           }
         }
       }
-      far = far || !(inv < kFarNumber);
+      if (!kTwo || kNType == PBZ_F64) far = far || !(inv < kFarNumber);     // sums of multiples of 2^-149 are within reach
       if (live && t == 0) store_N<kNType>(Nout, k0 + b, n, n_f16 != 0);
     }
     if (__any(far)) {
@@ -258,7 +261,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_blockwise_staged(Stage st, c
                                                                      double* __restrict__ out, double scale, int mode,
                                                                      int64_t n_blocks, int n_f16) {
   extern __shared__ __align__(16) uint8_t smem[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
   uint8_t* sa = smem + wave * wave_bytes(st, kTwo ? 2 : 1, kTwo ? 2 : 1);
   uint8_t* sb = kTwo ? sa + st.region : sa;
   double* na = reinterpret_cast<double*>(sa + (kTwo ? 2 : 1) * st.region);
@@ -272,12 +275,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_blockwise_staged(Stage st, c
     const int count = n_blocks - k0 < st.blocks ? int(n_blocks - k0) : st.blocks;
     const int64_t at = k0 * st.bpb;
     StagedN<kNType> n1, n2;
-    n1.request(N1, k0, count, n_f16 != 0);
-    if (kTwo) n2.request(N2, k0, count, n_f16 != 0);
+    n1.request(N1, k0, count);
+    if (kTwo) n2.request(N2, k0, count);
     stage_span<2>(F1, a_end, F1 + at, count * st.bpb, sa);
     if (kTwo) stage_span<2>(F2, b_end, F2 + at, count * st.bpb, sb);
-    n1.put(na, count);
-    if (kTwo) n2.put(nb, count);
+    n1.put(na, count, n_f16 != 0);
+    if (kTwo) n2.put(nb, count, n_f16 != 0);
     wave_lds_sync();
     const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : pa;
     for (int b0 = 0; b0 < count; b0 += per_round) {
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
                                                                   const void* __restrict__ N2, const uint8_t* __restrict__ F2,
                                                                   int64_t n_blocks, ReduceTail tail) {
   extern __shared__ __align__(16) uint8_t smem[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
   uint8_t* sa = smem + wave * wave_bytes(st, kTwo ? 2 : 1, kTwo ? 2 : 1);
   uint8_t* sb = kTwo ? sa + st.region : sa;
   double* na = reinterpret_cast<double*>(sa + (kTwo ? 2 : 1) * st.region);
@@ -324,77 +327,76 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
   const bool f16 = tail.n_f16 != 0;
   double sums[kNumSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
   const int64_t stride = int64_t(gridDim.x) * waves * st.blocks;
-  // A lane's sums that are no finite numbers at the end: an infinite N times a zero is NaN, and zero is what a block's padding is, and what
-  // the lane's own share of a block's indices may come to.  The wave then takes its blocks once more (far): without the
-  // padding, and with the integer sums of whole blocks.
-  bool far = false;                                          // uniform over the wave
-  for (;;) {
-    for (int64_t k0 = (int64_t(blockIdx.x) * waves + wave) * st.blocks; k0 < n_blocks; k0 += stride) {
+  const int64_t first = (int64_t(blockIdx.x) * waves + wave) * st.blocks;
+  const auto take = [&](auto far_t) __attribute__((always_inline)) {
+    constexpr bool far = decltype(far_t)::value;
+#pragma unroll 1
+    for (int64_t k0 = first; k0 < n_blocks; k0 += stride) {
       const int count = n_blocks - k0 < st.blocks ? int(n_blocks - k0) : st.blocks;
       const int64_t at = k0 * st.bpb;
       StagedN<kNType> n1, n2;
-      n1.request(N1, seg0 + k0, count, f16);
-      if (kTwo) n2.request(N2, seg0 + k0, count, f16);
+      n1.request(N1, seg0 + k0, count);
+      if (kTwo) n2.request(N2, seg0 + k0, count);
       stage_span<2>(F1, a_end, F1 + at, count * st.bpb, sa);
       if (kTwo) stage_span<2>(F2, b_end, F2 + at, count * st.bpb, sb);
-      n1.put(na, count);
-      if (kTwo) n2.put(nb, count);
+      n1.put(na, count, f16);
+      if (kTwo) n2.put(nb, count, f16);
       wave_lds_sync();
       const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : pa;
       for (int b = slot; b < count; b += per_round) {
         const double v1 = na[b], v2 = nb[b];
         typename Dot<kIType>::acc_t s11 = 0, s12 = 0, s22 = 0;
         double diff = 0.0;
-        for (int d = t; d < st.dwords; d += team) {
-          uint32_t a = block_dword(sa, pa + b * st.bpb, d, st.bpb);
-          uint32_t c = kTwo ? block_dword(sb, pb + b * st.bpb, d, st.bpb) : a;
-          if constexpr (kDiff) {
-            constexpr int kPer = PerDword<kIType>::value;
+        if constexpr (kDiff && far) {
+          constexpr int kPer = PerDword<kIType>::value;
+#pragma unroll 1
+          for (int j = t; j < st.kept; j += team) {
             double fa[kPer], fb[kPer];
-            unpack_dword<kIType>(a, fa);
-            unpack_dword<kIType>(c, fb);
+            unpack_dword<kIType>(block_dword(sa, pa + b * st.bpb, j / kPer, st.bpb) >> (j % kPer * (32 / kPer)), fa);
+            unpack_dword<kIType>(block_dword(sb, pb + b * st.bpb, j / kPer, st.bpb) >> (j % kPer * (32 / kPer)), fb);
+            const double x = v1 * fa[0] - v2 * fb[0];
+            diff += x * x;
+          }
+        } else {
+          for (int d = t; d < st.dwords; d += team) {
+            uint32_t a = block_dword(sa, pa + b * st.bpb, d, st.bpb);
+            uint32_t c = kTwo ? block_dword(sb, pb + b * st.bpb, d, st.bpb) : a;
+            if constexpr (kDiff) {
+              constexpr int kPer = PerDword<kIType>::value;
+              double fa[kPer], fb[kPer];
+              unpack_dword<kIType>(a, fa);
+              unpack_dword<kIType>(c, fb);
 #pragma unroll
-            for (int e = 0; e < kPer; ++e) {
-              const double x = v1 * fa[e] - v2 * fb[e];
-              diff += x * x;
-            }
-          } else {
-            if (kDC && d == 0) {                    // the first coefficient enters shifted by the pilot value
-              const double d1 = fma(v1, double(first_element<kIType>(a)), -K1);
-              sums[kS11] = fma(d1, d1, sums[kS11]);
-              sums[kD1] += d1;
-              a &= rest_of_first<kIType>();
-              if (kTwo) {
-                const double d2 = fma(v2, double(first_element<kIType>(c)), -K2);
-                sums[kS12] = fma(d1, d2, sums[kS12]);
-                sums[kS22] = fma(d2, d2, sums[kS22]);
-                sums[kD2] += d2;
-                c &= rest_of_first<kIType>();
+              for (int e = 0; e < kPer; ++e) {
+                const double x = v1 * fa[e] - v2 * fb[e];
+                diff += x * x;
               }
-            }
-            s11 = Dot<kIType>::add(s11, a, a);
-            if (kTwo) {
-              s12 = Dot<kIType>::add(s12, a, c);
-              s22 = Dot<kIType>::add(s22, c, c);
+            } else {
+              if (kDC && d == 0) {                  // the first coefficient enters shifted by the pilot value
+                const double d1 = fma(v1, double(first_element<kIType>(a)), -K1);
+                sums[kS11] = fma(d1, d1, sums[kS11]);
+                sums[kD1] += d1;
+                a &= rest_of_first<kIType>();
+                if (kTwo) {
+                  const double d2 = fma(v2, double(first_element<kIType>(c)), -K2);
+                  sums[kS12] = fma(d1, d2, sums[kS12]);
+                  sums[kS22] = fma(d2, d2, sums[kS22]);
+                  sums[kD2] += d2;
+                  c &= rest_of_first<kIType>();
+                }
+              }
+              s11 = Dot<kIType>::add(s11, a, a);
+              if (kTwo) {
+                s12 = Dot<kIType>::add(s12, a, c);
+                s22 = Dot<kIType>::add(s22, c, c);
+              }
             }
           }
         }
         if constexpr (kDiff) {
-          if (far) {                                         // uniform
-            diff = 0.0;
-            constexpr int kPer = PerDword<kIType>::value;
-#pragma unroll 1
-            for (int j = t; j < st.kept; j += team) {
-              double fa[kPer], fb[kPer];
-              unpack_dword<kIType>(block_dword(sa, pa + b * st.bpb, j / kPer, st.bpb) >> (j % kPer * (32 / kPer)), fa);
-              unpack_dword<kIType>(block_dword(sb, pb + b * st.bpb, j / kPer, st.bpb) >> (j % kPer * (32 / kPer)), fb);
-              const double x = v1 * fa[0] - v2 * fb[0];
-              diff += x * x;
-            }
-          }
           sums[kS11] += diff;
         } else {
-          if (far) {                                         // uniform
+          if constexpr (far) {
             for (int off = team >> 1; off > 0; off >>= 1) {
               s11 += __shfl_xor(s11, off, 64);
               s12 += __shfl_xor(s12, off, 64);
@@ -411,13 +413,18 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
       }
       wave_lds_sync();
     }
-    bool finite = true;
+  };
+  take(std::false_type());
+  // A lane's sums that are no finite numbers: an infinite N times a zero is NaN, and zero is what a block's padding is, and what
+  // the lane's own share of a block's indices may come to.  The wave then takes its blocks once more: without the
+  // padding, and with the integer sums of whole blocks.
+  bool finite = true;
 #pragma unroll
-    for (int i = 0; i < kNumSums; ++i) finite = finite && fabs(sums[i]) < INFINITY;
-    if (far || __all(finite)) break;
-    far = true;
+  for (int i = 0; i < kNumSums; ++i) finite = finite && fabs(sums[i]) < INFINITY;
+  if (!__all(finite)) {                                      // uniform over the wave
 #pragma unroll
     for (int i = 0; i < kNumSums; ++i) sums[i] = 0.0;
+    take(std::true_type());
   }
   reduce_tail(sums, tail, K1, K2, blockDim.x >> 6);
 }
