@@ -326,27 +326,27 @@ __device__ __forceinline__ void reduce_tail(double* sums, const ReduceTail& t, d
 }
 
 // Whether the sum and the shift of blocks that make no 16-byte vectors go straight from memory, a wave per block, or through LDS.  Few
-// blocks of up to 128 indices: the call is a round trip to memory, and the detour is 0.3-1.2 us more (1000 blocks of 33
-// int8 indices: sum 4.2 us, 5.1 through LDS; 10000 blocks: 7.9 and 5.1).  Blocks of over 8 KiB: LDS holds a wave or two,
-// unless there are so few blocks that the chip is not filled either way (4096 int32 indices: 1000 blocks 93 us, 54 through LDS; 4096
-// blocks 111 and 154).
-inline bool direct_blocks(int64_t n_blocks, int kept, int64_t block_bytes) {
-  return n_blocks <= 2048 ? kept <= 128 : block_bytes > 8192;
+// blocks of up to 128 indices: the call is a round trip to memory, and the detour is 0.2-0.8 us more (1000 blocks of 33
+// int8 indices: sum 4.2 us, 5.0 through LDS; 2000: 4.5 and 5.0, but for one to three indices 4.6 and 4.4).  Many blocks
+// of over 8 KiB (11 KiB where there is one operand): LDS holds a wave or two (sum of 4096 int32 indices: 4000 blocks 109 us, 152
+// through LDS; 2500 blocks, which do not fill the chip either way, 107 and 103, of 2500 indices 71 and 55).
+inline bool direct_blocks(int64_t n_blocks, int kept, int64_t block_bytes, bool two) {
+  return n_blocks <= 1024 ? kept <= 128 : n_blocks > 3072 && block_bytes > (two ? 8192 : 11 * 1024);
 }
-// The same of the block-wise statistics.  They store nothing but a number a block, so the detour pays later (covariance of 1000 blocks of
-// 129 int8 indices 4.0 us, 4.3 through LDS); and from one to three words a lane, which 65 to 160 indices of 32 bits are, it
-// leaves lanes idle (10000 blocks of 129: 6.5 and 9.0, 130000: 50 and 52).
-inline bool direct_blockwise(int64_t n_blocks, int kept, int64_t block_bytes) {
+// The same of the block-wise statistics.  The covariance has two operands to put into LDS: up to 1024 blocks 0.2-0.7 us more (129 int8
+// indices: 3.8 us, 4.1 through LDS); from one to three words a lane, which 65 to 160 indices of 32 bits are, leave
+// lanes idle (10000 blocks of 129: 6.5 and 8.9); large blocks as above (4000 of 4096: 51 and 58, of 3000: 41 and 38).  The variance gains
+// 0.1-0.3 us on up to 512 blocks of 33 to 128 (64 blocks and fewer of 65: 3.1 and 3.4); its large blocks take twice as long (43 and 28).
+inline bool direct_blockwise(int64_t n_blocks, int kept, int64_t block_bytes, bool two) {
+  if (!two) return n_blocks <= 512 && kept >= 33 && kept <= 128;
   if (block_bytes == 4 * int64_t(kept) && kept > 64 && kept <= 160) return n_blocks <= 16384;
-  return n_blocks <= 2048 ? kept <= 192 : block_bytes > 8192;
+  return n_blocks <= 1024 ? kept <= 192 : n_blocks > 3072 && block_bytes > 12 * 1024;
 }
-// The same of the reductions, a thread per block.  A few bytes per block (1000 to 16384 blocks of one to three indices: 7.5-8.3 us,
-// 0.4-1.0 more through LDS), whatever their number where that is one index of 8 or 16 bits of one operand (4M blocks, int16: 17.3 us
-// and 18.8); and up to 256 blocks of 20 to 80 bytes
-// (five indices: from 10 bytes), which are one workgroup's (156 blocks of 10 int32 indices: 5.8 and 7.3).
-inline bool direct_reduction(int64_t n_blocks, int kept, int64_t block_bytes, bool two) {
-  if (n_blocks <= 256 && kept <= 24 && block_bytes >= (kept <= 5 ? 10 : 20) && block_bytes <= 80) return true;
-  return n_blocks <= 16384 ? kept <= 3 : !two && block_bytes <= 2;
+// The same of the reductions, a thread per block: two operands of one index a block, or up to three where sums with and without the first
+// index are wanted (pair statistics of 1000 to 16384 blocks 8.8 us, 9.6 through LDS; one operand 7.6 either way), except 257
+// to 512 blocks, which LDS lets one workgroup take without a second launch (8.4 and 7.6).
+inline bool direct_reduction(int64_t n_blocks, int kept, bool two, bool dc) {
+  return two && kept <= (dc ? 3 : 1) && (n_blocks <= 256 || (n_blocks > 512 && n_blocks <= 16384));
 }
 
 // pbz_ops_direct.hip and pbz_ops_staged.hip: any kept count, any alignment.  F2 == nullptr: addition of `shift` to the first

@@ -1,7 +1,7 @@
 // Compressed-space operations straight from memory, element by element: any kept count, any alignment, any type at run time.
 // For the sizes at which putting blocks through LDS (pbz_ops_staged.hip) costs more than it saves: few blocks, where a
 // call is one memory round trip and the launch, and blocks so large that LDS holds one wave's only.  The rules and both sides' times
-// are with direct_blocks and direct_reduction.
+// are with direct_blocks, direct_blockwise and direct_reduction.
 #include "pbz_ops_common.h"
 
 namespace pbz {
@@ -56,17 +56,16 @@ __global__ __launch_bounds__(64) void k_blockwise_direct(const void* __restrict_
 // the five sums of a reduction, one thread per block; grid y = segment of n_blocks blocks
 __global__ __launch_bounds__(kThreads) void k_reduce_direct(const void* __restrict__ N1, const void* __restrict__ F1,
                                                             const void* __restrict__ N2, const void* __restrict__ F2, int ntype,
-                                                            int itype, int64_t n_blocks, int kept, int two, int dc, int diff,
-                                                            ReduceTail tail) {
+                                                            int itype, int64_t n_blocks, int kept, int dc, int diff, ReduceTail tail) {
   double sums[kNumSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
   const int64_t nthreads = int64_t(gridDim.x) * kThreads;
   const int64_t k0 = int64_t(blockIdx.y) * n_blocks;     // first block of this segment
   const double K1 = dc ? pilot_value(tail.pilot_n1, tail.pilot_f1, tail, blockIdx.y) : 0.0;
-  const double K2 = dc && two ? pilot_value(tail.pilot_n2, tail.pilot_f2, tail, blockIdx.y) : 0.0;
+  const double K2 = dc ? pilot_value(tail.pilot_n2, tail.pilot_f2, tail, blockIdx.y) : 0.0;
   for (int64_t kk = int64_t(blockIdx.x) * kThreads + threadIdx.x; kk < n_blocks; kk += nthreads) {
     const int64_t k = k0 + kk;
     const double n1 = load_float<double>(N1, ntype, k);
-    const double n2 = two ? load_float<double>(N2, ntype, k) : 0.0;
+    const double n2 = load_float<double>(N2, ntype, k);
     if (diff) {
       double acc = 0.0;
       for (int j = 0; j < kept; ++j) {
@@ -79,19 +78,17 @@ __global__ __launch_bounds__(kThreads) void k_reduce_direct(const void* __restri
     double s11 = 0.0, s12 = 0.0, s22 = 0.0;
     for (int j = dc ? 1 : 0; j < kept; ++j) {       // dc: the first coefficient enters shifted, below
       const double f1 = double(load_index(F1, itype, k * kept + j));
+      const double f2 = double(load_index(F2, itype, k * kept + j));
       s11 += f1 * f1;
-      if (two) {
-        const double f2 = double(load_index(F2, itype, k * kept + j));
-        s12 += f1 * f2;
-        s22 += f2 * f2;
-      }
+      s12 += f1 * f2;
+      s22 += f2 * f2;
     }
     sums[kS11] += s11 * (n1 * n1);
     sums[kS12] += s12 * (n1 * n2);
     sums[kS22] += s22 * (n2 * n2);
     if (dc) {
       const double d1 = n1 * double(load_index(F1, itype, k * kept)) - K1;
-      const double d2 = two ? n2 * double(load_index(F2, itype, k * kept)) - K2 : 0.0;
+      const double d2 = n2 * double(load_index(F2, itype, k * kept)) - K2;
       sums[kS11] += d1 * d1;
       sums[kS12] += d1 * d2;
       sums[kS22] += d2 * d2;
@@ -124,14 +121,14 @@ int launch_blockwise_direct(const pbz_codec* c, int mode, int64_t n_blocks, cons
   return hip_status(hipGetLastError());
 }
 
-int launch_reduce_direct(const pbz_codec* c, bool two, bool dc, bool diff, int64_t n_blocks, int n_segments, int max_groups,
+int launch_reduce_direct(const pbz_codec* c, bool /*two*/, bool dc, bool diff, int64_t n_blocks, int n_segments, int max_groups,
                          const void* N1, const void* F1, const void* N2, const void* F2, const ReduceTail& tail, int* groups,
                          hipStream_t s) {
   int g = stream_groups(n_blocks, 1);
   if (g > max_groups) g = max_groups;
   *groups = g;
   hipLaunchKernelGGL(k_reduce_direct, dim3(g, n_segments), dim3(kThreads), 0, s, N1, F1, N2, F2, int(c->ftype), int(c->itype),
-                     n_blocks, c->kept, two ? 1 : 0, dc ? 1 : 0, diff ? 1 : 0, tail);
+                     n_blocks, c->kept, dc ? 1 : 0, diff ? 1 : 0, tail);
   return hip_status(hipGetLastError());
 }
 

@@ -529,9 +529,10 @@ int launch_blockwise_staged(const pbz_codec* c, int mode, int64_t n_blocks, cons
 int launch_reduce_staged(const pbz_codec* c, bool two, bool dc, bool diff, int64_t n_blocks, int n_segments, int max_groups,
                          const void* N1, const void* F1, const void* N2, const void* F2, const ReduceTail& tail, int* groups,
                          hipStream_t s) {
-  // Up to 256 blocks in 16 KiB (a step of a short series): one workgroup, which takes them in a tile per wave or two.  Dealt out to
-  // more workgroups they need the second launch
-  const bool few = n_blocks <= 256 && n_blocks * c->kept * itype_bytes(c->itype) <= 16 * 1024;
+  // Up to 256 blocks in 16 KiB (a step of a short series; 12 KiB an operand where there are two: 13 KiB, pair statistics 11.5 us and
+  // 9.9): one workgroup, which takes them in a tile per wave or two.  Dealt out to more workgroups they need the second launch
+  // (156 blocks of 10 int32 indices, variance: 6.3 us and 8.1).
+  const bool few = n_blocks <= 256 && n_blocks * c->kept * itype_bytes(c->itype) <= (two ? 12 : 16) * 1024;
   const Stage st = make_stage(c->kept, itype_bytes(c->itype), n_blocks, kReduceSpan, few ? kMaxWaves : kMinWaves / n_segments);
   size_t lds;
   const int waves = waves_for(st, two ? 2 : 1, two ? 2 : 1, &lds);
