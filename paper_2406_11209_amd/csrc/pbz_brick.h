@@ -1,6 +1,9 @@
 // General codec kernels for a list of block shapes, any array, working and index type, any mask, any alignment: what the
-// specialised families leave to "generic" of the shapes that programs use (4-D and flat blocks, 4x8x8, 8x16, 32x32, 1-D,
-// and the families' shapes with types they are not built for).  pbz_tiled.hip takes the shapes that are not listed.
+// specialised families leave to "generic" (4-D and flat blocks, 4x8x8, 8x16, 32x32, 1-D, and the families' shapes with
+// types they are not built for).  pbz_tiled.hip takes the shapes that are not listed, and the calls that pays() below leaves it.
+// The list is a choice, not a bound: the families' shapes, the cubes, squares and lines that the method is described for, and their
+// neighbours.  The template takes any shape of its static_asserts' kind (8x8x4, 16x32 and 2x16 stay tiled at 2-3.4 TB/s); every
+// shape adds 0.4 MB to the library and some seconds to its build.
 //
 // Wave autonomous like the families: a wave owns a tile of consecutive blocks, VALUES (64, or 32 in FP64 work) values per
 // lane in registers, no workgroup barrier, LDS private to the wave.  Two layouts, each with whole lines of its dimensions
@@ -16,8 +19,9 @@
 // tile's blocks are, which moves in 16-byte pieces.
 // The block shape is a template argument, so every index and bound is a constant but for the lane's own and the block's
 // place in the array; types, mask and geometry are arguments, with one uniform branch around each loop.
-// Memory bounds the FP32 work (4.3 - 5.1 TB/s of the copy's 5.6; wide blocks less, in the regrouped stores), FP64 work what
-// is in flight (four waves per SIMD, two where blocks leave a lane 64 values).  Measured, us, with pbz_tiled.hip -> here:
+// Memory bounds the FP32 work (4.3 - 5.1 TB/s of the copy's 5.6; wide blocks less, in the regrouped stores, and 16-bit arrays with
+// int16 in 8x8x8 blocks, 2.1), FP64 work what is in flight (four waves per SIMD, two where blocks leave a lane 64 values; 4x4x4x4:
+// vector ALUs a quarter busy, waves waiting half of their time).  Measured, us, with pbz_tiled.hip -> here:
 //                                      compress      decompress
 //   256x512x512 FP32, 4x8x8, i8        110 ->  66    100 ->  67
 //   32x64x128x256 FP32, 2x4x8x8, i8    129 ->  66    112 ->  66
@@ -866,26 +870,36 @@ constexpr bool kTaken = BX < 64 || sizeof(T) == 4;
 // nothing pruned stay with the tiled kernels where measured slower at every size above a few blocks: 8x8 both ways (1.05-1.3), 4x8 and
 // 8x4 of FP64 arrays decompressing (1.05-1.15); and so do 32x32 blocks of FP64 arrays in FP32 work under a mask, decompressing
 // (1.2).
+// Rows that are no whole blocks, or no whole 16-byte pieces, the tiled kernels take element by element.  Decompressing, these
+// kernels then win at every size: in FP32 work blocks of up to 64 (0.6-0.9; 16-bit arrays 8x8 0.8), 3-D blocks of 16-bit arrays (0.75-0.9) and,
+// under a mask, of FP32 arrays (0.9); in FP64 work flat blocks of up to 128 in rows of less than 32 (0.65-0.9; FP64 arrays under a mask only, all of
+// them 1.15), 16x16 of 16-bit arrays with nothing pruned (0.9); and the others, too, from 2^22 on.  Compressing, 8x8 of 16-bit arrays with
+// 32-bit indices (0.88) and 32x32 of FP32 arrays (0.9).
 template <typename T, typename S>
-bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements) {
+bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_t row) {
   constexpr int64_t kMi = int64_t(1) << 20;
   constexpr bool kWide = sizeof(T) == 8, kFlat = S::BW == 1 && S::BZ == 1;
   constexpr bool k8x8 = kFlat && S::BY == 8 && S::BX == 8, k4x8 = kFlat && S::VOL == 32 && S::BX < 16;
   const int array = ftype_bytes(xtype), index = itype_bytes(c->itype);
-  const bool pruned = c->kept != c->vol;
+  const bool pruned = c->kept != c->vol, ragged = row % S::BX != 0 || row * array % 16 != 0;
   if (c->route == kRouteShape || S::BX == 64) return true;
-  if (index == 4 && !pruned && (k8x8 || (k4x8 && !compress && array == 8))) return elements <= (compress ? 4096 : 1024);
+  if (index == 4 && !pruned && ((k8x8 && !(compress && ragged && array == 2)) || (k4x8 && !compress && array == 8)))
+    return elements <= (compress ? 4096 : 1024);
   if (compress) {
     const bool enough = elements <= 4096 || elements >= 3 * kMi;
     if (kWide) return pruned || !(S::VALUES == 64 && (index == 4 || array == 8)) || enough;
-    return !((array == 8 && S::BX >= 16) || (array == 4 && S::VOL == 1024)) || enough;
+    return !((array == 8 && S::BX >= 16) || (array == 4 && S::VOL == 1024 && !ragged)) || enough;
   }
   if (!kWide && S::VOL == 1024 && array == 8 && pruned) return false;
   if (S::BX == 4 && (kWide || array < 8 || S::BW > 1 || pruned)) return true;
   if (!kWide && S::BW > 1) return true;
   if (kWide && ((index == 1 && S::VOL < 1024) || (!kFlat && S::VOL <= 128) || (index == 2 && S::VOL <= 32 && S::BX <= 8))) return true;
   if (pruned && (k8x8 || (kWide && kFlat && S::BY == 16 && S::BX == 16))) return true;
-  return elements >= ((!kWide && S::BX >= 16 && !pruned) || (index == 4 && kFlat && S::VOL < 256) ? 8 * kMi : 3 * kMi);
+  if (ragged && !kWide && array < 8 && (S::VOL <= 64 || (!kFlat && S::VOL <= 512 && (array == 2 || (pruned && S::VOL <= 256))))) return true;
+  if (ragged && kWide && kFlat && S::VOL <= 128 && S::BX < 32 && (array < 8 || pruned)) return true;
+  if (ragged && kWide && kFlat && S::VOL == 256 && array == 2 && !pruned) return true;
+  const bool late = (!kWide && S::BX >= 16 && !pruned) || (index == 4 && kFlat && S::VOL < 256);
+  return elements >= (late && !ragged ? 8 * kMi : 3 * kMi);
 }
 
 template <typename T, int BW, int BZ, int BY, int BX>
@@ -895,7 +909,7 @@ int compress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t, c
     BrickGeom g;
     if (!make_brick(c, geo, x, xtype, t, BW, BZ, BY, BX, &g)) return 0;
     using S = Shape<T, BW, BZ, BY, BX>;
-    if (!pays<T, S>(c, true, xtype, geo.n_blocks * S::VOL)) return 0;
+    if (!pays<T, S>(c, true, xtype, geo.n_blocks * S::VOL, geo.shape[c->ndim - 1])) return 0;
     if (dry_run) return 1;
     if (c->transform == PBZ_TRANSFORM_HAAR) compress_with<kTfHaar, T, S>(g, x, N, F, s);
     else compress_with<kTfDct, T, S>(g, x, N, F, s);
@@ -910,7 +924,7 @@ int decompress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t,
     BrickGeom g;
     if (!make_brick(c, geo, y, ytype, t, BW, BZ, BY, BX, &g)) return 0;
     using S = Shape<T, BW, BZ, BY, BX>;
-    if (!pays<T, S>(c, false, ytype, geo.n_blocks * S::VOL)) return 0;
+    if (!pays<T, S>(c, false, ytype, geo.n_blocks * S::VOL, geo.shape[c->ndim - 1])) return 0;
     if (dry_run) return 1;
     if (c->transform == PBZ_TRANSFORM_HAAR) decompress_with<kTfHaar, T, S>(g, N, F, y, s);
     else decompress_with<kTfDct, T, S>(g, N, F, y, s);
