@@ -83,8 +83,8 @@ int try_decompress_fast(const pbz_codec* c, const Geom& geo, const void* N, cons
 }
 
 // The kernels of the same families that take any mask, in the order above.  They are asked after the kernels for one
-// mask (everything, or a box), which skip work that these cannot, and before the kernels for any block shape, which take 1.4 to
-// 3 times as long on every setting measured (the figures are with MaskArgs)
+// mask (everything, or a box), which skip work that these cannot, and before the kernels for any block shape; each
+// family's pays() says where it is the faster one (the figures are there and with MaskArgs)
 int try_compress_masked(const pbz_codec* c, const Geom& geo, const uint16_t* pos, const void* x, int xtype, void* N, void* F,
                         hipStream_t s, bool dry_run) {
   if (c->kept == c->vol || !fast::aligned16(x) || c->route == kRouteShape) return 0;

@@ -264,7 +264,7 @@ struct IdxPack<int32_t> {
 // Where a place depends on the lane it comes from a table, [intra-block entry] -> position among the kept ones or
 // kPruned; a pruned entry's address is the smaller of a far away one and a slot set aside, so there is no branch.
 // (Dropping one index at a time costs an LDS instruction per index, 64 per lane and tile; it is less than the transform
-// and hides behind the other waves' loads.)  Against the kernels for any block shape, FP32 arrays, zonal masks:
+// and hides behind the other waves' loads.)  Against the tiled kernels, FP32 arrays, zonal masks:
 // 512 x 512 x 256 in 8x8x8 blocks, 128 of 512 int16 kept: compress 179 -> 81 us, decompress 181 -> 78; 8192^2 in 16x16
 // blocks, 64 of 256 int8: 93 -> 69 and 110 -> 57; 8192^2 in 8x8 blocks, 19 of 64 int8: 110 -> 54 and 114 -> 52;
 // 512^3 in 4x4x4 blocks, 19 of 64 int16: 351 -> 118 and 354 -> 116 (5.4 TB/s moved); 256 x 512 x 512 in 16x16x16 blocks,

@@ -12,9 +12,10 @@
 //   unstage  new indices collect in another LDS region at the phase of the output pointer and leave in 16-byte pieces,
 //            the span's ends element by element.
 // Waves never wait for each other (no workgroup barrier), so the loads of some overlap the arithmetic of others.
-// 2M blocks of 19 int16 indices (80 MB of F an operand): add and subtract 1016 -> 99 us, addition of a scalar
-// 592 -> 71 us, against the kernels before these, in which a wave read one block element by element; the
-// variance of 128 steps of 16384 blocks of 10 int8 indices 18 us, with a thread per block 30 us (its covariance of adjacent steps 23 against 42 us).
+// 2M blocks of 19 int16 indices (80 MB of F an operand): add and subtract 1016 -> 81 us, addition of a scalar
+// 592 -> 64 us, against the kernels before these, in which a wave read one block element by element; the
+// variance of 128 steps of 16384 blocks of 10 int8 indices 14 us, with a thread per block 30 us (its covariance of
+// adjacent steps 21 against 42 us).  The vector ALUs are busy three quarters of the sums' time, a third of the reductions'.
 // Tried and not kept: dword accesses of LDS at any byte instead of shifting two aligned words (add 99 -> 140 us), six
 // waves per SIMD (80 registers, 128 bytes of spills: 106 us), spans of 1 or 4 KiB per wave and operand (15-35 % slower).
 #include "pbz_ops_common.h"
