@@ -6,18 +6,17 @@
 // therefore owns a run of consecutive blocks, whose indices are one contiguous span of F:
 //   stage    the span is copied to the wave's own LDS region in aligned 16-byte pieces, at the same phase (address
 //            modulo 16) that it has in memory; N goes along, widened to FP64;
-//   work     a team of 2^k consecutive lanes takes a block, consecutive lanes consecutive dwords of it: two
-//            neighbouring aligned LDS words shifted against each other by the block's phase, the last dword masked,
-//            so that the packed arithmetic of the vector kernels applies;
-//   unstage  new indices collect in another LDS region at the phase of the output pointer and leave in 16-byte pieces,
-//            the span's ends element by element.
+//   work     a team of 2^k consecutive lanes takes a block, each a run of consecutive dwords of it: neighbouring aligned LDS words
+//            shifted against each other by the block's phase, every word read once, so that the packed arithmetic of the
+//            vector kernels applies.  A team is as few lanes as can be (up to 12 dwords each) while that leaves enough waves:
+//            what is done once per lane and block, two divisions above all, is spread over as many indices as possible;
+//   unstage  new indices collect in LDS at the phase of the output pointer and leave in 16-byte pieces, the span's ends element
+//            by element.
 // Waves never wait for each other (no workgroup barrier), so the loads of some overlap the arithmetic of others.
-// 2M blocks of 19 int16 indices (80 MB of F an operand): add and subtract 1016 -> 81 us, addition of a scalar
-// 592 -> 64 us, against the kernels before these, in which a wave read one block element by element; the
-// variance of 128 steps of 16384 blocks of 10 int8 indices 14 us, with a thread per block 30 us (its covariance of
-// adjacent steps 21 against 42 us).  The vector ALUs are busy three quarters of the sums' time, a third of the reductions'.
-// Tried and not kept: dword accesses of LDS at any byte instead of shifting two aligned words (add 99 -> 140 us), six
-// waves per SIMD (80 registers, 128 bytes of spills: 106 us), spans of 1 or 4 KiB per wave and operand (15-35 % slower).
+// 2M blocks of 19 int16 indices (80 MB of F an operand): add and subtract 56 us, addition of a scalar 48 us (1016 and 592 element by
+// element, 85 and 67 with teams of at most four dwords a lane, consecutive lanes consecutive dwords); the reductions are with k_reduce_staged.
+// Tried and not kept: dword accesses of LDS at any byte instead of shifting two aligned words (add 99 -> 140 us), spans of 1 or
+// 4 KiB per wave and operand (15-35 % slower).
 #include "pbz_ops_common.h"
 #include "pbz_span.h"
 #include "pbz_stage_layout.h"
@@ -26,7 +25,6 @@ namespace pbz {
 namespace ops {
 namespace {
 
-constexpr int kCached = 4;               // dwords of a block per lane that the rebinning kernels keep in registers
 constexpr int kNPerLane = kMaxBlocksPerWave / 64;
 
 // N of `count` (at most kMaxBlocksPerWave) blocks from k0 on: requested, as they are stored, and widened when they are put away,
@@ -59,6 +57,11 @@ struct StagedN {
   }
 };
 
+template <int kIType>
+struct IndexOf {
+  typedef typename std::conditional<kIType == PBZ_I8, int8_t, typename std::conditional<kIType == PBZ_I16, int16_t, int32_t>::type>::type type;
+};
+
 // dword d of the block that starts at byte `start` of the LDS region; bytes past the block's end are zero
 __device__ __forceinline__ uint32_t block_dword(const uint8_t* lds, int start, int d, int bpb) {
   const int at = start + 4 * d;
@@ -68,17 +71,78 @@ __device__ __forceinline__ uint32_t block_dword(const uint8_t* lds, int start, i
   return rest >= 4 ? v : (rest <= 0 ? 0u : v & ((1u << (8 * rest)) - 1u));
 }
 
-template <int kIType>
-__device__ __forceinline__ void put_dword(uint8_t* lds, int start, int d, int kept, const int* q) {
-  constexpr int kPer = PerDword<kIType>::value;
-  uint8_t* at = lds + start + 4 * d;
+// A lane's run of a block: `run` consecutive dwords from byte `start` of the LDS region on, of which `whole` lie in the block, and
+// the block's last one, where that is partial and the lane's.
+struct LaneRun {
+  int run, whole, part;            // part: bytes of the partial dword, zero unless it is this lane's
+  uint32_t cut;                    // mask of those bytes
+  int start;
+  __device__ __forceinline__ LaneRun(const Stage& st, int t) {
+    run = st.run;
+    start = 4 * t * st.run;
+    const int left = (st.bpb >> 2) - t * st.run;            // whole dwords from the lane's first one to the block's end
+    whole = left < 0 ? 0 : (left < st.run ? left : st.run);
+    part = left >= 0 && left < st.run ? st.bpb & 3 : 0;
+    cut = (1u << (8 * part)) - 1u;
+  }
+};
+
+// f(i, a, b) for the lane's whole dwords i of a block, in order, and then for the partial one, its other bytes zero.  a0, b0: the bytes of the two
+// operands' LDS regions at which the lane's run starts (at any alignment).  Every word is read once: a dword is cut from its own
+// and the next one.
+template <bool kTwo, typename Fn>
+__device__ __forceinline__ void for_dwords(const LaneRun& lane, const uint8_t* sa, int a0, const uint8_t* sb, int b0, Fn f) {
+  const uint32_t* wa = reinterpret_cast<const uint32_t*>(sa) + (a0 >> 2);
+  const uint32_t* wb = reinterpret_cast<const uint32_t*>(sb) + (b0 >> 2);
+  const uint32_t ca = uint32_t(a0 & 3), cb = uint32_t(b0 & 3);
+  constexpr int kAhead = 4;                                 // words requested together
+  uint32_t pa = wa[0], pb = kTwo ? wb[0] : 0u;
+  int i0 = 0;
+  for (; i0 + kAhead <= lane.run; i0 += kAhead) {
+    uint32_t va[kAhead], vb[kAhead];
 #pragma unroll
-  for (int e = 0; e < kPer; ++e) {
-    if (d * kPer + e < kept) {
-      if (kIType == PBZ_I8) at[e] = uint8_t(q[e]);
-      else if (kIType == PBZ_I16) reinterpret_cast<uint16_t*>(at)[e] = uint16_t(q[e]);
-      else *reinterpret_cast<uint32_t*>(at) = uint32_t(q[e]);
+    for (int u = 0; u < kAhead; ++u) {
+      va[u] = wa[i0 + u + 1];
+      vb[u] = kTwo ? wb[i0 + u + 1] : 0u;
     }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const uint32_t a = __builtin_amdgcn_alignbyte(va[u], pa, ca);
+      const uint32_t b = kTwo ? __builtin_amdgcn_alignbyte(vb[u], pb, cb) : a;
+      if (i0 + u < lane.whole) f(i0 + u, a, b);
+      pa = va[u];
+      pb = vb[u];
+    }
+  }
+  for (; i0 < lane.run; ++i0) {
+    const uint32_t va = wa[i0 + 1], vb = kTwo ? wb[i0 + 1] : 0u;
+    const uint32_t a = __builtin_amdgcn_alignbyte(va, pa, ca);
+    const uint32_t b = kTwo ? __builtin_amdgcn_alignbyte(vb, pb, cb) : a;
+    if (i0 < lane.whole) f(i0, a, b);
+    pa = va;
+    pb = vb;
+  }
+  if (lane.part) {
+    const int i = lane.whole;
+    const uint32_t a = __builtin_amdgcn_alignbyte(wa[i + 1], wa[i], ca) & lane.cut;
+    const uint32_t b = kTwo ? __builtin_amdgcn_alignbyte(wb[i + 1], wb[i], cb) & lane.cut : a;
+    f(i, a, b);
+  }
+}
+
+// indices q of a dword to byte `at` of the LDS region; `bytes`: 4, or those of a partial dword
+template <int kIType>
+__device__ __forceinline__ void put_indices(uint8_t* at, const int* q, int bytes) {
+  if (kIType == PBZ_I8) {
+    at[0] = uint8_t(q[0]);
+    if (bytes > 1) at[1] = uint8_t(q[1]);
+    if (bytes > 2) at[2] = uint8_t(q[2]);
+    if (bytes > 3) at[3] = uint8_t(q[3]);
+  } else if (kIType == PBZ_I16) {
+    reinterpret_cast<uint16_t*>(at)[0] = uint16_t(q[0]);
+    if (bytes > 2) reinterpret_cast<uint16_t*>(at)[1] = uint16_t(q[1]);
+  } else {
+    *reinterpret_cast<uint32_t*>(at) = uint32_t(q[0]);
   }
 }
 
@@ -92,8 +156,8 @@ struct Rebin {
   static constexpr int kPer = PerDword<kIType>::value;
   static constexpr bool kExactProducts = kNType != PBZ_F64 && kIType != PBZ_I32;
   double n1, n2, r, inv_r, shift;
-  // the coefficients of dword d; entries past the block's end come out as zero
-  __device__ __forceinline__ void coefficients(uint32_t a, uint32_t b, int d, double* c) const {
+  // the coefficients of a dword (`head`: the block's first); bytes that are zero come out as zero
+  __device__ __forceinline__ void coefficients(uint32_t a, uint32_t b, bool head, double* c) const {
     double fa[kPer], fb[kPer];
     unpack_dword<kIType>(a, fa);
     if (kTwo) unpack_dword<kIType>(b, fb);
@@ -103,7 +167,7 @@ struct Rebin {
         c[e] = kExactProducts ? fma(fa[e], n1, fb[e] * n2) : unfused_sum_of_products(fa[e], n1, fb[e], n2);
       } else {
         c[e] = div_by(n1 * fa[e], r, inv_r);
-        if (e == 0 && d == 0) c[e] += shift;
+        if (e == 0) c[e] += head ? shift : 0.0;
       }
     }
   }
@@ -118,7 +182,7 @@ struct Rebin {
   // div_by would turn into NaN) and NaN.  NaN counts for nothing in the maximum, and becomes the index -r.  One index at a
   // time: the path takes no registers from the others.  a, b, o: the block in LDS; one team of lanes.  Returns the new N.
   // (Every block of a wave's tile that holds one such block goes this way: the others' indices come out the same.)
-  typedef typename std::conditional<kIType == PBZ_I8, int8_t, typename std::conditional<kIType == PBZ_I16, int16_t, int32_t>::type>::type index_t;
+  typedef typename IndexOf<kIType>::type index_t;
   __device__ __forceinline__ double far_block(int t, int team, int kept, const uint8_t* a, const uint8_t* b, uint8_t* o) const {
     double m = 0.0, n = 0.0;
 #pragma unroll 1
@@ -157,7 +221,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const
   double* nb = na + st.numbers / 8;
   const int team = 1 << st.team_shift, t = lane & (team - 1), slot = lane >> st.team_shift;
   const int per_round = 64 >> st.team_shift;
-  const int steps = (st.dwords + team - 1) >> st.team_shift;          // dwords per lane, at most
+  const LaneRun run(st, t);
   const uint8_t* a_end = F1 + n_blocks * st.bpb;
   const uint8_t* b_end = kTwo ? F2 + n_blocks * st.bpb : nullptr;
   const int64_t stride = int64_t(gridDim.x) * waves * st.blocks;
@@ -186,40 +250,27 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const
       const int bc = live ? b : count - 1;                 // slots past the end redo the last block and store nothing
       op.n1 = na[bc];
       op.n2 = kTwo ? sign2 * nb[bc] : 0.0;
-      double c[kCached * kPer];
       double m = 0.0;
-      for (int s0 = 0; s0 < steps; s0 += kCached) {        // one turn unless a block has over 256 dwords
+      const int from = bc * st.bpb + run.start;
+      for_dwords<kTwo>(run, sa, pa + from, sb, pb + from, [&](int i, uint32_t va, uint32_t vb) {
+        double c[kPer];
+        op.coefficients(va, vb, i == 0 && t == 0, c);
 #pragma unroll
-        for (int s = 0; s < kCached; ++s) {
-          if (s0 + s < steps) {
-            const int d = ((s0 + s) << st.team_shift) + t;
-            if (d < st.dwords) {
-              op.coefficients(block_dword(sa, pa + bc * st.bpb, d, st.bpb),
-                              kTwo ? block_dword(sb, pb + bc * st.bpb, d, st.bpb) : 0u, d, c + s * kPer);
-#pragma unroll
-              for (int e = 0; e < kPer; ++e) m = fmax(m, fabs(c[s * kPer + e]));
-            }
-          }
-        }
-      }
+        for (int e = 0; e < kPer; ++e) m = fmax(m, fabs(c[e]));
+      });
       for (int off = team >> 1; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
       // an all-zero block has scale = inv = 0 and every c = 0, which gives 0; no quotient rounds beyond r
       const double n = kTwo ? m / r : m;
       const double inv = n > 0.0 ? 1.0 / n : 0.0;
-      for (int s0 = 0; s0 < steps; s0 += kCached) {
-#pragma unroll
-        for (int s = 0; s < kCached; ++s) {
-          const int d = ((s0 + s) << st.team_shift) + t;
-          if (s0 + s < steps && d < st.dwords && live) {
-            if (steps > kCached)                           // not in registers any more
-              op.coefficients(block_dword(sa, pa + bc * st.bpb, d, st.bpb),
-                              kTwo ? block_dword(sb, pb + bc * st.bpb, d, st.bpb) : 0u, d, c + s * kPer);
-            int q[kPer];
-            op.indices(c + s * kPer, n, inv, q);
-            put_dword<kIType>(so, po + bc * st.bpb, d, st.kept, q);
-          }
-        }
-      }
+      // the coefficients once more: cheaper than a place for them until the maximum is known
+      if (live)
+        for_dwords<kTwo>(run, sa, pa + from, sb, pb + from, [&](int i, uint32_t va, uint32_t vb) {
+          double c[kPer];
+          int q[kPer];
+          op.coefficients(va, vb, i == 0 && t == 0, c);
+          op.indices(c, n, inv, q);
+          put_indices<kIType>(so + po + from + 4 * i, q, i < run.whole ? 4 : run.part);
+        });
       if (!kTwo || kNType == PBZ_F64) far = far || !(inv < kFarNumber);     // sums of multiples of 2^-149 are within reach
       if (live && t == 0) store_N<kNType>(Nout, k0 + b, n, n_f16 != 0);
     }
@@ -238,6 +289,227 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_rebin_staged(Stage st, const
   }
 }
 
+// The same for blocks that a team holds in registers (at most held_dwords a lane), which is all but the largest.  Every lane takes `run`
+// dwords: the last lane's are the block's last ones, which may be another lane's, too (the maximum does not mind, and both write the
+// same indices); so is a lane's last dword where the block ends inside one, which starts four bytes before the block's end.
+// So no dword is partial, and nothing is masked; the coefficients are computed once, the two divisions of a block by as few
+// lanes as can hold it.
+// What bounds it: 16 and 32 bits, HBM; their spans go to LDS past the registers, and the new indices take the first operand's
+// place there where they are at the same phase, so that five waves fit a SIMD.  8 bits: the FP64 arithmetic (12 instructions an
+// index, 2 cycles and more each); the lanes read their dwords straight from memory, at any alignment, which costs the texture path a
+// look-up per lane and load (three quarters of its time with 38-byte blocks, where HBM would bind), but spares the detour's instructions.
+// 2M blocks of 19 indices, sum and shift: 16 bits 85 and 67 -> 56 and 48 us (both straight from memory 68 and 53), 8 bits 54 and
+// 41 -> 32 and 30 (through LDS 42 and 33); 300000 blocks of 33 32-bit ones 43 and 34 -> 28 and 17.  Before: teams of up to 4 dwords a
+// lane, masked one by one, and three regions of LDS.  Not kept: waves that stay, with the next tile's loads in flight (16
+// bits 78 us and 8 bits 55: 150 registers, three waves a SIMD); coefficients computed twice instead of held (76 and 57); dword stores to LDS at
+// any alignment (two thirds of the kernel's time waiting for LDS).
+constexpr int held_dwords(int itype, bool two) {          // what leaves five waves a SIMD without spills
+  return itype == PBZ_I8 ? (two ? 5 : 6) : (itype == PBZ_I16 && two ? 10 : 12);
+}
+template <int kIType>
+constexpr bool straight_from_memory() { return kIType == PBZ_I8; }
+
+// n (at most kMain, the same in every lane) dwords from p on, at any alignment
+template <int kMain>
+__device__ __forceinline__ void load_dwords(const uint8_t* p, int n, uint32_t* w) {
+#pragma unroll
+  for (int j = 0; j < kMain; j += 4) {
+    if (j + 4 <= n) {
+      raw16 v;
+      __builtin_memcpy(&v, p + 4 * j, 16);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (j + u < kMain) w[j + u] = v[u];
+    } else {
+#pragma unroll
+      for (int u = j; u < j + 4 && u < kMain; ++u)
+        if (u < n) __builtin_memcpy(w + u, p + 4 * u, 4);
+    }
+  }
+}
+
+// A lane's new dwords to its place in the LDS region, whatever its alignment: in whole aligned words and, where it shares one with a
+// neighbour, a half.  8-bit indices are put there one by one.
+template <int kIType>
+struct LaneOut {
+  uint32_t* word;            // the next whole one
+  uint32_t prev;
+  int head;                  // bytes before the first whole word
+  __device__ __forceinline__ LaneOut(uint8_t* lds, int at) {
+    head = kIType == PBZ_I16 ? at & 2 : 0;
+    word = reinterpret_cast<uint32_t*>(lds) + ((at + 3) >> 2);
+  }
+  __device__ __forceinline__ void put(uint32_t v, bool start) {
+    if (!start || kIType == PBZ_I32) *word++ = kIType == PBZ_I32 ? v : __builtin_amdgcn_alignbyte(v, prev, uint32_t(head));
+    else if (head) reinterpret_cast<uint16_t*>(word)[-1] = uint16_t(v);
+    prev = v;
+  }
+  __device__ __forceinline__ void some(uint32_t v, int bytes) {
+    if (bytes >= 4) *word = v;
+    else if (bytes > 0) *reinterpret_cast<uint16_t*>(word) = uint16_t(v);
+  }
+  // the last dword, of which the first `bytes` count; `start`: it is the first, too
+  __device__ __forceinline__ void finish(uint32_t v, int bytes, bool start) {
+    if (kIType == PBZ_I32) {
+      *word = v;
+    } else {
+      if (!start) {
+        some(__builtin_amdgcn_alignbyte(v, prev, uint32_t(head)), 4 + bytes - head);
+        ++word;
+      } else if (head) {
+        reinterpret_cast<uint16_t*>(word)[-1] = uint16_t(v);
+      }
+      some(v >> (8 * head), bytes - head);
+    }
+  }
+};
+
+// The bytes at p of a block of less than four in the operand [lo, hi), and others above them: one load, of the operand's last four bytes
+// where the block is among those.
+__device__ __forceinline__ uint32_t few_bytes(const uint8_t* lo, const uint8_t* hi, const uint8_t* p, int bytes) {
+  uint32_t w = 0;
+  if (hi - lo >= 4) {
+    const uint8_t* q = p + 4 <= hi ? p : hi - 4;
+    __builtin_memcpy(&w, q, 4);
+    return w >> (8 * int(p - q));
+  }
+  for (int e = 0; e < bytes; ++e) w |= uint32_t(p[e]) << (8 * e);
+  return w;
+}
+
+template <int kIType, int kNType, bool kTwo>
+__global__ __launch_bounds__(64 * kMaxWaves, 5) void k_rebin_held(Stage st, const void* N1, const uint8_t* F1, const void* N2,
+                                                               const uint8_t* F2, void* Nout, uint8_t* Fout, double r,
+                                                               double sign2, double shift, int64_t n_blocks, int n_f16, int regions) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  constexpr int kPer = PerDword<kIType>::value, kMain = held_dwords(kIType, kTwo) - 1;
+  constexpr bool kStraight = straight_from_memory<kIType>();
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+  // LDS: the first operand, the second, and the result unless it takes the first one's place; of straight_from_memory only the result
+  const bool in_place = !kStraight && regions == (kTwo ? 2 : 1);
+  uint8_t* sa = smem + wave * regions * st.region;
+  uint8_t* sb = sa + st.region;
+  uint8_t* so = in_place ? sa : sa + (regions - 1) * st.region;
+  const int team = 1 << st.team_shift, t = lane & (team - 1), slot = lane >> st.team_shift;
+  const int per_round = 64 >> st.team_shift, run = st.run;
+  const int start = 4 * (t * run < st.dwords - run ? t * run : st.dwords - run);
+  const int tail = start + 4 * run < st.bpb ? start + 4 * (run - 1) : (st.bpb > 4 ? st.bpb - 4 : 0);      // the lane's last dword
+  // bytes of the lane's run that only that dword holds (all of them where the block has no four bytes), and the bits of its others
+  const int last_bytes = start + 4 * run < st.bpb ? 4 : st.bpb - start - 4 * (run - 1);
+  const int drop = st.bpb < 4 ? 0 : 8 * (4 - last_bytes);
+  const uint32_t cut = st.bpb < 4 ? (1u << (8 * st.bpb)) - 1u : ~0u;
+  Rebin<kIType, kNType, kTwo> op;
+  op.r = r;
+  op.inv_r = 1.0 / r;
+  op.shift = shift;
+  // a tile per wave: memory ends before the largest grid does
+  const int64_t k0 = (int64_t(blockIdx.x) * waves + wave) * st.blocks;
+  if (k0 >= n_blocks) return;
+  const int count = n_blocks - k0 < st.blocks ? int(n_blocks - k0) : st.blocks;
+  const int64_t at = k0 * st.bpb;
+  const int len = count * st.bpb;
+  const uint8_t *a_end = F1 + n_blocks * st.bpb, *b_end = kTwo ? F2 + n_blocks * st.bpb : nullptr;
+  if (!kStraight) {
+    request_span(F1, a_end, F1 + at, len, sa);
+    if (kTwo) request_span(F2, b_end, F2 + at, len, sb);
+  }
+  const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : 0, po = phase_of(Fout + at);
+  // a block that needs far_block: after the others, which that keeps out of the registers of this loop
+  bool far = false;
+  for (int b0 = 0; b0 < count; b0 += per_round) {        // uniform: the lane exchanges below are convergent
+    const int b = b0 + slot;
+    const bool live = b < count;
+    const int bc = live ? b : count - 1;                 // slots past the end redo the last block and store nothing
+    const int base = bc * st.bpb;
+    op.n1 = load_N<kNType>(N1, k0 + bc, n_f16 != 0);
+    op.n2 = kTwo ? sign2 * load_N<kNType>(N2, k0 + bc, n_f16 != 0) : 0.0;
+    uint32_t wa[kMain + 1], wb[kMain + 1];               // the last one's are the last of each
+    wb[kMain] = 0;
+    if constexpr (kStraight) {
+      const uint8_t *a = F1 + at + base, *c = kTwo ? F2 + at + base : nullptr;
+      load_dwords<kMain>(a + start, run - 1, wa);
+      if (kTwo) load_dwords<kMain>(c + start, run - 1, wb);
+      if (st.bpb >= 4) {
+        __builtin_memcpy(wa + kMain, a + tail, 4);
+        if (kTwo) __builtin_memcpy(wb + kMain, c + tail, 4);
+      } else {
+        wa[kMain] = few_bytes(F1, a_end, a, st.bpb) & cut;
+        if (kTwo) wb[kMain] = few_bytes(F2, b_end, c, st.bpb) & cut;
+      }
+    } else {
+      if (b0 == 0) span_arrived();
+      const auto cut_out = [&](const uint8_t* lds, int from, int to, uint32_t* w) __attribute__((always_inline)) {
+        const uint32_t* x = reinterpret_cast<const uint32_t*>(lds) + (from >> 2);
+        const uint32_t* y = reinterpret_cast<const uint32_t*>(lds) + (to >> 2);
+        w[0] = x[0];
+#pragma unroll
+        for (int u = 0; u < kMain; ++u) {
+          if (u + 1 >= run) break;
+          w[u + 1] = x[u + 1];
+        }
+        const uint32_t last = __builtin_amdgcn_alignbyte(y[1], y[0], uint32_t(to & 3)) & cut;
+#pragma unroll
+        for (int u = 0; u < kMain; ++u) {
+          if (u + 1 >= run) break;
+          w[u] = __builtin_amdgcn_alignbyte(w[u + 1], w[u], uint32_t(from & 3));
+        }
+        w[kMain] = last;
+      };
+      cut_out(sa, pa + base + start, pa + base + tail, wa);
+      if (kTwo) cut_out(sb, pb + base + start, pb + base + tail, wb);
+    }
+    double c[(kMain + 1) * kPer], m = 0.0;
+#pragma unroll
+    for (int u = 0; u < kMain; ++u) {
+      if (u + 1 >= run) break;
+      op.coefficients(wa[u], kTwo ? wb[u] : 0u, u == 0 && t == 0, c + u * kPer);
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) m = fmax(m, fabs(c[u * kPer + e]));
+    }
+    op.coefficients(wa[kMain], wb[kMain], st.dwords == 1, c + kMain * kPer);
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) m = fmax(m, fabs(c[kMain * kPer + e]));
+    for (int off = team >> 1; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    // an all-zero block has scale = inv = 0 and every c = 0, which gives 0; no quotient rounds beyond r
+    const double n = kTwo ? m / r : m;
+    const double inv = n > 0.0 ? 1.0 / n : 0.0;
+    if (live) {
+      LaneOut<kIType> o(so, po + base + start);
+#pragma unroll
+      for (int u = 0; u < kMain; ++u) {
+        if (u + 1 >= run) break;
+        int q[kPer];
+        op.indices(c + u * kPer, n, inv, q);
+        if (kIType == PBZ_I8) put_indices<kIType>(so + po + base + start + 4 * u, q, 4);
+        else o.put(pack_dword<kIType>(q), u == 0);
+      }
+      int q[kPer];
+      op.indices(c + kMain * kPer, n, inv, q);
+      if (kIType == PBZ_I8) put_indices<kIType>(so + po + base + tail, q, st.bpb < 4 ? st.bpb : 4);
+      else o.finish(pack_dword<kIType>(q) >> drop, last_bytes, run == 1);
+    }
+    far = far || !(fabs(op.n1) < kFarNumber) || (kTwo && !(fabs(op.n2) < kFarNumber));
+    if (!kTwo || kNType == PBZ_F64) far = far || !(inv < kFarNumber);     // sums of multiples of 2^-149 are within reach
+    if (live && t == 0) store_N<kNType>(Nout, k0 + b, n, n_f16 != 0);
+  }
+  wave_lds_sync();
+  if (__any(far)) {                                      // other lanes' writes to the same places precede these
+    if (in_place) {                                      // the operand once more: its place in memory is written below
+      request_span(F1, a_end, F1 + at, len, sa);
+      span_arrived();
+    }
+    const uint8_t *a = kStraight ? F1 + at : sa + pa, *c = kStraight ? F2 + at : sb + pb;
+    for (int b = slot; b < count; b += per_round) {
+      op.n1 = load_N<kNType>(N1, k0 + b, n_f16 != 0);
+      op.n2 = kTwo ? sign2 * load_N<kNType>(N2, k0 + b, n_f16 != 0) : 0.0;
+      const double n = op.far_block(t, team, st.kept, a + b * st.bpb, kTwo ? c + b * st.bpb : nullptr, so + po + b * st.bpb);
+      if (t == 0) store_N<kNType>(Nout, k0 + b, n, n_f16 != 0);
+    }
+    wave_lds_sync();
+  }
+  unstage_span(so, Fout + at, len);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Sums over blocks
 // ---------------------------------------------------------------------------------------------
@@ -250,11 +522,13 @@ struct Dot {
     else if constexpr (kIType == PBZ_I16) return acc + (long long)__builtin_amdgcn_sdot2(as_short2(a), as_short2(b), 0, false);
     else return acc + dot_dword<PBZ_I32>(a, b);
   }
+  // the product of two blocks' first indices: taken out of a sum of integers, where that is exact; with 32 bits it is left out instead
+  static __device__ __forceinline__ acc_t first(const uint8_t* a, const uint8_t* b) {
+    if constexpr (kIType == PBZ_I8) return int(int8_t(*a)) * int(int8_t(*b));
+    else if constexpr (kIType == PBZ_I16) return (long long)(int(*reinterpret_cast<const int16_t*>(a)) * int(*reinterpret_cast<const int16_t*>(b)));
+    else return 0.0;
+  }
 };
-template <int kIType>
-__host__ __device__ constexpr uint32_t rest_of_first() {   // a block's first dword without its first index
-  return kIType == PBZ_I8 ? 0xffffff00u : (kIType == PBZ_I16 ? 0xffff0000u : 0u);
-}
 
 template <int kIType, int kNType, bool kTwo>
 __global__ __launch_bounds__(64 * kMaxWaves) void k_blockwise_staged(Stage st, const void* __restrict__ N1, const uint8_t* __restrict__ F1,
@@ -269,6 +543,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_blockwise_staged(Stage st, c
   double* nb = kTwo ? na + st.numbers / 8 : na;
   const int team = 1 << st.team_shift, t = lane & (team - 1), slot = lane >> st.team_shift;
   const int per_round = 64 >> st.team_shift;
+  const LaneRun run(st, t);
   const uint8_t* a_end = F1 + n_blocks * st.bpb;
   const uint8_t* b_end = kTwo ? F2 + n_blocks * st.bpb : nullptr;
   const int64_t stride = int64_t(gridDim.x) * waves * st.blocks;
@@ -288,11 +563,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_blockwise_staged(Stage st, c
       const int b = b0 + slot;
       const int bc = b < count ? b : count - 1;
       typename Dot<kIType>::acc_t acc = 0;
-      for (int d = t; d < st.dwords; d += team) {
-        const uint32_t a = block_dword(sa, pa + bc * st.bpb, d, st.bpb) & (d == 0 ? rest_of_first<kIType>() : 0xffffffffu);
-        const uint32_t c = kTwo ? block_dword(sb, pb + bc * st.bpb, d, st.bpb) : a;
-        acc = Dot<kIType>::add(acc, a, c);
-      }
+      const int from = bc * st.bpb + run.start;
+      for_dwords<kTwo>(run, sa, pa + from, sb, pb + from, [&](int i, uint32_t va, uint32_t vb) {
+        if (kIType != PBZ_I32 || i > 0 || t > 0) acc = Dot<kIType>::add(acc, va, vb);
+      });
+      if (kIType != PBZ_I32 && t == 0)
+        acc -= Dot<kIType>::first(sa + pa + bc * st.bpb, (kTwo ? sb + pb : sa + pa) + bc * st.bpb);
       double sum = double(acc);
       for (int off = team >> 1; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
       if (b < count && t == 0) {
@@ -318,6 +594,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
   double* nb = kTwo ? na + st.numbers / 8 : na;
   const int team = 1 << st.team_shift, t = lane & (team - 1), slot = lane >> st.team_shift;
   const int per_round = 64 >> st.team_shift;
+  const LaneRun run(st, t);
   const int64_t seg0 = int64_t(blockIdx.y) * n_blocks;             // the segment's first block
   F1 += seg0 * st.bpb;
   const uint8_t* a_end = F1 + n_blocks * st.bpb;
@@ -325,6 +602,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
   const uint8_t* b_end = kTwo ? F2 + n_blocks * st.bpb : nullptr;
   const double K1 = kDC ? pilot_value(tail.pilot_n1, tail.pilot_f1, tail, blockIdx.y) : 0.0;
   const double K2 = kDC && kTwo ? pilot_value(tail.pilot_n2, tail.pilot_f2, tail, blockIdx.y) : 0.0;
+  typedef typename IndexOf<kIType>::type index_t;
   const bool f16 = tail.n_f16 != 0;
   double sums[kNumSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
   const int64_t stride = int64_t(gridDim.x) * waves * st.blocks;
@@ -359,38 +637,39 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
             diff += x * x;
           }
         } else {
-          for (int d = t; d < st.dwords; d += team) {
-            uint32_t a = block_dword(sa, pa + b * st.bpb, d, st.bpb);
-            uint32_t c = kTwo ? block_dword(sb, pb + b * st.bpb, d, st.bpb) : a;
+          const int from = b * st.bpb + run.start;
+          for_dwords<kTwo>(run, sa, pa + from, sb, pb + from, [&](int i, uint32_t va, uint32_t vb) {
             if constexpr (kDiff) {
               constexpr int kPer = PerDword<kIType>::value;
               double fa[kPer], fb[kPer];
-              unpack_dword<kIType>(a, fa);
-              unpack_dword<kIType>(c, fb);
+              unpack_dword<kIType>(va, fa);
+              unpack_dword<kIType>(vb, fb);
 #pragma unroll
               for (int e = 0; e < kPer; ++e) {
                 const double x = v1 * fa[e] - v2 * fb[e];
                 diff += x * x;
               }
-            } else {
-              if (kDC && d == 0) {                  // the first coefficient enters shifted by the pilot value
-                const double d1 = fma(v1, double(first_element<kIType>(a)), -K1);
-                sums[kS11] = fma(d1, d1, sums[kS11]);
-                sums[kD1] += d1;
-                a &= rest_of_first<kIType>();
-                if (kTwo) {
-                  const double d2 = fma(v2, double(first_element<kIType>(c)), -K2);
-                  sums[kS12] = fma(d1, d2, sums[kS12]);
-                  sums[kS22] = fma(d2, d2, sums[kS22]);
-                  sums[kD2] += d2;
-                  c &= rest_of_first<kIType>();
-                }
-              }
-              s11 = Dot<kIType>::add(s11, a, a);
+            } else if (!kDC || kIType != PBZ_I32 || i > 0 || t > 0) {
+              s11 = Dot<kIType>::add(s11, va, va);
               if (kTwo) {
-                s12 = Dot<kIType>::add(s12, a, c);
-                s22 = Dot<kIType>::add(s22, c, c);
+                s12 = Dot<kIType>::add(s12, va, vb);
+                s22 = Dot<kIType>::add(s22, vb, vb);
               }
+            }
+          });
+          if (kDC && t == 0) {                      // the first coefficient enters shifted by the pilot value
+            const uint8_t *fa = sa + pa + b * st.bpb, *fb = kTwo ? sb + pb + b * st.bpb : fa;
+            const double d1 = fma(v1, double(*reinterpret_cast<const index_t*>(fa)), -K1);
+            sums[kS11] = fma(d1, d1, sums[kS11]);
+            sums[kD1] += d1;
+            s11 -= Dot<kIType>::first(fa, fa);
+            if (kTwo) {
+              const double d2 = fma(v2, double(*reinterpret_cast<const index_t*>(fb)), -K2);
+              sums[kS12] = fma(d1, d2, sums[kS12]);
+              sums[kS22] = fma(d2, d2, sums[kS22]);
+              sums[kD2] += d2;
+              s12 -= Dot<kIType>::first(fa, fb);
+              s22 -= Dot<kIType>::first(fb, fb);
             }
           }
         }
@@ -442,15 +721,17 @@ unsigned group_count(int64_t n_blocks, const Stage& st, int waves, int64_t cap) 
 template <int kIType, int kNType>
 void rebin2(bool two, dim3 grid, dim3 block, size_t lds, hipStream_t s, const Stage& st, const void* N1, const void* F1,
             const void* N2, const void* F2, void* Nout, void* Fout, double r, double sign2, double shift, int64_t n_blocks,
-            int n_f16) {
+            int n_f16, int regions) {
   const uint8_t *a = static_cast<const uint8_t*>(F1), *b = static_cast<const uint8_t*>(F2);
   uint8_t* o = static_cast<uint8_t*>(Fout);
-  if (two)
-    hipLaunchKernelGGL((k_rebin_staged<kIType, kNType, true>), grid, block, lds, s, st, N1, a, N2, b, Nout, o, r, sign2,
-                       shift, n_blocks, n_f16);
-  else
-    hipLaunchKernelGGL((k_rebin_staged<kIType, kNType, false>), grid, block, lds, s, st, N1, a, N2, b, Nout, o, r, sign2,
-                       shift, n_blocks, n_f16);
+  const bool held = st.run <= held_dwords(kIType, two);
+#define PBZ_REBIN(KERNEL, TWO, ...) \
+  hipLaunchKernelGGL((KERNEL<kIType, kNType, TWO>), grid, block, lds, s, st, N1, a, N2, b, Nout, o, r, sign2, shift, n_blocks, n_f16, ##__VA_ARGS__)
+  if (two && held) PBZ_REBIN(k_rebin_held, true, regions);
+  else if (held) PBZ_REBIN(k_rebin_held, false, regions);
+  else if (two) PBZ_REBIN(k_rebin_staged, true);
+  else PBZ_REBIN(k_rebin_staged, false);
+#undef PBZ_REBIN
 }
 
 template <int kIType, int kNType>
@@ -506,12 +787,17 @@ constexpr int64_t kGroupCap = int64_t(1) << 30;            // the kernels loop b
 int launch_rebin_staged(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2,
                         void* Nout, void* Fout, double sign2, double shift, hipStream_t s) {
   const bool two = F2 != nullptr;
-  const Stage st = make_stage(c->kept, itype_bytes(c->itype), n_blocks, kRebinSpan, kMinWaves);
+  const int team_dwords = held_dwords(c->itype, two);
+  const Stage st = make_stage(c->kept, itype_bytes(c->itype), n_blocks, kRebinSpan, kMinWaves, team_dwords);
+  const bool held = st.run <= team_dwords;
+  const bool same_phase = ((reinterpret_cast<uintptr_t>(F1) ^ reinterpret_cast<uintptr_t>(Fout)) & 15u) == 0;
+  const int regions = (two ? 3 : 2) - (held && same_phase ? 1 : 0);
+  const int used = held && c->itype == PBZ_I8 ? 1 : regions;
   size_t lds;
-  const int waves = waves_for(st, two ? 3 : 2, two ? 2 : 1, &lds);
+  const int waves = waves_for(st, used, held ? 0 : (two ? 2 : 1), &lds);
   const dim3 grid(group_count(n_blocks, st, waves, kGroupCap)), block(64 * waves);
   const int n_f16 = c->ftype == PBZ_F16 ? 1 : 0;
-  PBZ_BY_TYPES(rebin2, two, grid, block, lds, s, st, N1, F1, N2, F2, Nout, Fout, c->r, sign2, shift, n_blocks, n_f16);
+  PBZ_BY_TYPES(rebin2, two, grid, block, lds, s, st, N1, F1, N2, F2, Nout, Fout, c->r, sign2, shift, n_blocks, n_f16, used);
   return hip_status(hipGetLastError());
 }
 

@@ -43,6 +43,32 @@ __device__ __forceinline__ void stage_span(const uint8_t* lo, const uint8_t* hi,
   }
 }
 
+// The same copy, requested only: the pieces go from memory to LDS past the registers (64 lanes' pieces are consecutive there, too).
+// span_arrived() waits for them.  `lds`: the same in every lane.
+__device__ __forceinline__ void request_span(const uint8_t* lo, const uint8_t* hi, const uint8_t* p, int len, uint8_t* lds) {
+  const int lane = threadIdx.x & 63;
+  const int a = phase_of(p);
+  const uint8_t* base = p - a;
+  const int pieces = (a + len + 15) >> 4;
+  const int first = base < lo ? 1 : 0;
+  const int last = base + 16 * int64_t(pieces) > hi ? pieces - 1 : pieces;
+  for (int i0 = 0; i0 < last; i0 += 64) {
+    const int i = i0 + lane;
+    if (i >= first && i < last)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + 16 * i),
+                                       (__attribute__((address_space(3))) void*)(lds + 16 * i0), 16, 0, 0);
+  }
+  if (first != 0 && lane < 16 - a && lane < len) lds[a + lane] = p[lane];
+  if (last < pieces) {
+    const int i = 16 * last + lane;
+    if (lane < 16 && i >= a && i < a + len) lds[i] = base[i];
+  }
+}
+__device__ __forceinline__ void span_arrived() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  wave_lds_sync();
+}
+
 // LDS -> [p, p + len), from the phase of p; nothing outside is written
 __device__ __forceinline__ void unstage_span(const uint8_t* lds, uint8_t* p, int len) {
   const int lane = threadIdx.x & 63;

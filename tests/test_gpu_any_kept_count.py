@@ -133,3 +133,47 @@ def test_a_call_agrees_with_the_calls_on_its_halves(extent, kept, bits, n):
         halves = codec.segmented(op, 2, h, N1[:2 * h], F1[:2 * h])
         for half, p in zip(halves.tolist(), (slice(0, h), slice(h, 2 * h))):
             assert half == pytest.approx(getattr(codec, op)(N1[p], F1[p]).item(), rel=1e-12)
+
+
+# Around the most dwords that a lane holds (5 or 6, 10 or 12, 12), with every remainder of a dword, as many blocks as it takes to have a lane hold
+# that many; then the largest blocks that a team of 64 lanes holds, and the next
+HELD = ([(8, k, 64 * 4096 + 37) for k in (1, 3, 15, 19, 20, 21, 22, 24, 25)] + [(16, k, 64 * 4096 + 37) for k in (1, 3, 19, 20, 21, 23, 24, 25)] +
+        [(32, k, 64 * 4096 + 37) for k in (1, 11, 12, 13)] +
+        [(8, k, 70) for k in (1279, 1280, 1281, 1536, 1537)] + [(16, k, 70) for k in (1280, 1281, 1536, 1537)] + [(32, k, 70) for k in (768, 769)])
+
+
+@pytest.mark.parametrize("ftype", ["f32", "f64"])
+@pytest.mark.parametrize("bits,kept,n", HELD, ids=["i%d_%d_x%d" % h for h in HELD])
+def test_rebinning_of_blocks_held_in_registers(bits, kept, n, ftype):
+    g = torch.Generator("cuda").manual_seed(100 * kept + bits)
+    mask = np.zeros(64 if kept <= 64 else 4096, dtype=bool)
+    mask[:kept] = True
+    codec = Codec((64,) if kept <= 64 else (64, 64), ftype, bits, mask if kept <= 64 else mask.reshape(64, 64))
+    r = 2 ** (bits - 1) - 1
+    divisor = torch.tensor(float(r), dtype=torch.float64, device="cuda")      # torch multiplies by the reciprocal of a plain number
+    itype, ntype = {8: torch.int8, 16: torch.int16, 32: torch.int32}[bits], {"f32": torch.float32, "f64": torch.float64}[ftype]
+    make = lambda: (torch.rand(n + 1, generator=g, device="cuda", dtype=torch.float64).to(ntype) + 0.1,
+                    torch.randint(-r, r + 1, (n + 1, kept), generator=g, device="cuda").to(itype))
+    operands = [make(), make()]
+    operands[0][1][5] = 0
+    operands[1][1][5] = 0                                       # a block of zeros in both
+    for first, second in ((0, 0), (1, 0), (0, 1)):              # equal and different phases of the two operands
+        (N1, F1), (N2, F2) = [(N[p:p + n], F[p:p + n]) for (N, F), p in zip(operands, (first, second))]
+        # the three roundings of a coefficient as the kernels have them; |quotient| <= r
+        add = F1.double() * N1.double()[:, None] + F2.double() * N2.double()[:, None]
+        shift = N1.double()[:, None] * F1.double() / divisor
+        shift[:, 0] += 0.375 * np.sqrt(64.0 if kept <= 64 else 4096.0)
+        for c, scale, got in ((add, add.abs().amax(1) / divisor, codec.add(N1, F1, N2, F2)),
+                              (shift, shift.abs().amax(1), codec.add_scalar(N1, F1, 0.375))):
+            quotient = (c if c is add else c * r) / scale[:, None]
+            want = torch.where(scale[:, None] > 0, quotient, torch.zeros_like(c)).round()
+            # the sum's N is rounded correctly; N F / r before the shift is, too, up to double rounding: a unit in the last place
+            assert bool(((got[0] - scale.to(ntype)).abs() <= (2.0 ** -52 * scale if c is shift and ftype == "f64" else 0)).all())
+            # both quotients are rounded correctly, up to double rounding within 2^-53 of a tie
+            assert int((got[1] != want.to(itype)).sum()) <= (2 if bits == 32 else 0)
+        # the result in an operand's place, with its neighbours as they were
+        N, F = operands[0][0].clone(), operands[0][1].clone()
+        codec.add(N[first:first + n], F[first:first + n], N2, F2, N[first:first + n], F[first:first + n])
+        want = codec.add(N1, F1, N2, F2)
+        assert torch.equal(F[first:first + n], want[1]) and torch.equal(N[first:first + n], want[0])
+        assert torch.equal(F[:first], operands[0][1][:first]) and torch.equal(F[first + n:], operands[0][1][first + n:])
