@@ -4,15 +4,16 @@
 //
 // Everything stays on the device and on the caller's stream:
 //   1. block means of both operands into the workspace, as unsigned keys in the order of the doubles, with their
-//      partial sums and maxima,
-//   2. sum, maximum and sum of exp(x - max) (two-stage reductions): the parameters of the softmax and the decision whether
-//      to apply it,
-//   3. the raw means are sorted (softmax is increasing, so it commutes with sorting), both operands in the same
-//      launches (grid y): a sample sort up to kSampleSortMax keys, a least-significant-digit radix sort beyond,
-//   4. m = max |P_A - P_B|, then sum (|P_A - P_B| / m)^p, then m (sum / n)^(1/p): the scaling by m changes
+//      sums, maxima and sums of exp(x - max) per tile, and how many of a tile's keys fall between which splitters,
+//   2. the parameters of the softmax and the decision whether to apply it,
+//   3. which of the keys can matter for the distance at all (k_select); the raw means of these are sorted (softmax is
+//      increasing, so it commutes with sorting), both operands in the same launches (grid y): a sample sort up to
+//      kSampleSortMax keys, a least-significant-digit radix sort of all keys beyond,
+//   4. m = max |P_A - P_B| and sum (|P_A - P_B| / m)^p, then m (sum / n)^(1/p): the scaling by m changes
 //      nothing in exact arithmetic and keeps orders such as p = 68 .. 80 from underflowing.
 // All sums are two-stage with a fixed order, so the result is reproducible run to run.
 #include <cmath>
+#include <type_traits>
 
 #include "pbz_device.h"
 #include "pbz_internal.h"
@@ -30,7 +31,8 @@ constexpr int kTileKeys = kSortThreads * kKeysPerLane;   // keys of a tile (one 
 // workgroups per operand in the small reductions, at most
 constexpr int kStatGroups = 1024;
 constexpr int kMeansPerThread = 8;               // blocks whose N and first index a thread requests together
-constexpr int kDistancesInFlight = 4;
+constexpr int kDistancesInFlight = 2;
+constexpr int kKeptDifferences = 12;             // of a thread of k_distance, in LDS until the maximum is known; a multiple of those
 constexpr int kKeysInFlight = 8;                 // keys a thread of the passes below requests together
 
 // Sample sort: 4 K keys drawn from the n (one from each run of n / 4K, at a place that depends on the run's number) and
@@ -39,20 +41,34 @@ constexpr int kKeysInFlight = 8;                 // keys a thread of the passes 
 // bucket in LDS.  What bounds it: 8-byte scatters and LDS, 16 bytes a key and pass against memory otherwise.
 // K = n / 2048 rounded up to a power of two, so that a bucket has some 1024 to 2048 keys: smaller ones would make the
 // runs that a tile scatters into a bucket shorter than the 64 bytes they are, larger ones would not fit LDS beside
-// three more.  2 x 2M keys: the eight radix passes (three launches each) took 301 us of 491, these six launches
-// take 160 of 290: counting 27, scattering 39, sorting the buckets 62, the splitters 19.
+// three more.  2 x 2M keys, the whole distance: 491 us with eight radix passes, 290 with all buckets sorted, 193 with those that matter
+// (of that the means, a line of F each, and the counting 106; samples and splitters 13, k_select 16, scattering 15, sorting 20).
 constexpr int kSampleSortMax = 1 << 22;          // 2048 buckets: fewer than two samples each would leave them too uneven
 constexpr int kBucketKeys = 2048;                // on average, at most
 constexpr int kBucketCap = 4096;                 // keys sorted in LDS at once: larger buckets take more than one round
 constexpr int kMaxSamples = 4096;                 // four per bucket, two where there are 2048 buckets
 constexpr int kMaxTiles = 256;                   // tiles per operand of the counting and scattering passes
-constexpr int kMinTileKeys = 8192;
+constexpr int kMinTileKeys = 2048;
+constexpr int kSelectMin = 32;                   // buckets from which k_select pays
+constexpr int kPieceRanks = 512;                 // ranks of a piece of k_distance, at most
 constexpr int kPassThreads = 512;
+constexpr int kGoingInFlight = 4;
+constexpr int kGoing = kPassThreads * kGoingInFlight + 512;      // of the scattering pass: a step's keys and some before them
 constexpr double kSumTolerance = 1e-9;           // "the means sum to one" is taken as |sum - 1| <= this
 
 // per operand: written by the one-workgroup kernels, read by everything after them
 struct OperandParams {
   double sum, max, exp_sum, use_softmax;
+};
+
+// per operand, from k_select: keys from .. to (from > to: none) are in no bucket that matters
+struct Gap {
+  uint64_t from, to;
+};
+// for k_distance, from k_select
+struct Selection {
+  double threshold;        // differences below it do not matter
+  int pieces;              // of ranks that may
 };
 
 struct Workspace {
@@ -65,6 +81,9 @@ struct Workspace {
   uint64_t* splitters;     // [2][K]
   uint32_t* rest;          // [2 + 2 K]: the numbers of left-over buckets and of pieces, then the buckets
   uint2* pieces;           // [K]: pieces of buckets of one value (first key of both operands' 2 n, number of keys)
+  Gap* gap;                // [2], and the selection
+  uint8_t* needed;         // [2][2 K]: the bucket has keys whose order matters
+  uint2* ranks;            // pieces of the ranks at which differences matter (first rank, number)
 };
 
 struct SortPlan {
@@ -115,6 +134,9 @@ size_t carve(void* base, int64_t n, Workspace* w) {
   char* h = take(sizeof(uint64_t) * 2 * buckets);
   char* i = take(sizeof(uint32_t) * (2 + 2 * buckets));
   char* j = take(sizeof(uint2) * buckets);
+  char* k = take(sizeof(Gap) * 2 + sizeof(Selection));
+  char* l = take(2 * totals);
+  char* m = take(sizeof(uint2) * (2 * totals + size_t(sampled) / kPieceRanks + 1));
   if (w) {
     w->params = reinterpret_cast<OperandParams*>(a);
     w->partials = reinterpret_cast<double*>(b);
@@ -125,6 +147,9 @@ size_t carve(void* base, int64_t n, Workspace* w) {
     w->splitters = reinterpret_cast<uint64_t*>(h);
     w->rest = reinterpret_cast<uint32_t*>(i);
     w->pieces = reinterpret_cast<uint2*>(j);
+    w->gap = reinterpret_cast<Gap*>(k);
+    w->needed = reinterpret_cast<uint8_t*>(l);
+    w->ranks = reinterpret_cast<uint2*>(m);
   }
   return off;
 }
@@ -168,79 +193,44 @@ __device__ __forceinline__ void group_sum_max(double& s, double& m) {
   }
 }
 
-// Block means N_k F_k0 * scale of both operands (grid y) as keys, with the partial sums and maxima of the means.  Where a
-// block's indices fill a 128-byte line or more every line of F is fetched for two bytes of it: that is the time, and a
-// thread has kMeansPerThread lines on the way (2 x 2M blocks of 128 bytes: 112 us, 4.9 TB/s; k_blockwise_mean, the passes for
-// sum and maximum and the one that made the keys took 137).  Streaming whole vectors instead, of which one lane in
-// eight needs the first dword, took 121.
-__global__ __launch_bounds__(kThreads) void k_means(const void* __restrict__ N1, const void* __restrict__ F1,
-                                                    const void* __restrict__ N2, const void* __restrict__ F2, int ntype,
-                                                    int itype, double scale, int64_t n, int64_t chunk, int kept,
-                                                    uint64_t* __restrict__ keys, double* __restrict__ partials) {
-  const void* N = blockIdx.y ? N2 : N1;
-  const void* F = blockIdx.y ? F2 : F1;
-  uint64_t* out = keys + int64_t(blockIdx.y) * n;
-  const int64_t begin = int64_t(blockIdx.x) * chunk;
-  const int64_t end = begin + chunk < n ? begin + chunk : n;
-  double s = 0.0, m = -INFINITY;
-  auto run = [&](auto load_n, auto load_f) {
-    for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kThreads * kMeansPerThread) {
-      double v[kMeansPerThread], f[kMeansPerThread];
-#pragma unroll
-      for (int u = 0; u < kMeansPerThread; ++u) {
-        const int64_t i = i0 + u * kThreads < end ? i0 + u * kThreads : end - 1;
-        f[u] = load_f(i * kept);
-        v[u] = load_n(i);
-      }
-#pragma unroll
-      for (int u = 0; u < kMeansPerThread; ++u) {
-        const int64_t i = i0 + u * kThreads;
-        if (i < end) {
-          const double x = v[u] * f[u] * scale;
-          out[i] = key_of(x);
-          s += x;
-          m = fmax(m, x);
-        }
-      }
-    }
-  };
-  auto by_index = [&](auto load_n) {                       // the types are uniform: one branch outside the loop
-    if (itype == PBZ_I8) run(load_n, [&](int64_t i) { return double(static_cast<const int8_t*>(F)[i]); });
-    else if (itype == PBZ_I16) run(load_n, [&](int64_t i) { return double(static_cast<const int16_t*>(F)[i]); });
-    else run(load_n, [&](int64_t i) { return double(static_cast<const int32_t*>(F)[i]); });
+// Block mean N_k F_k0 * scale of both operands (grid y) as doubles: calls f(load) with a function that gives N and the first index of
+// block i.  The types are uniform: one branch outside the loops.
+template <typename Fn>
+__device__ __forceinline__ void with_loads(const void* N, const void* F, int ntype, int itype, int kept, Fn f) {
+  auto by_index = [&](auto load_n) {
+    if (itype == PBZ_I8) f(load_n, [&](int64_t i) { return double(__builtin_nontemporal_load(static_cast<const int8_t*>(F) + i * kept)); });
+    else if (itype == PBZ_I16) f(load_n, [&](int64_t i) { return double(__builtin_nontemporal_load(static_cast<const int16_t*>(F) + i * kept)); });
+    else f(load_n, [&](int64_t i) { return double(__builtin_nontemporal_load(static_cast<const int32_t*>(F) + i * kept)); });
   };
   if (ntype == PBZ_F64) by_index([&](int64_t i) { return static_cast<const double*>(N)[i]; });
   else if (ntype == PBZ_F32) by_index([&](int64_t i) { return double(static_cast<const float*>(N)[i]); });
   else if (ntype == PBZ_BF16) by_index([&](int64_t i) { return double(bf16_bits_to_float(static_cast<const uint16_t*>(N)[i])); });
   else by_index([&](int64_t i) { return double(float(static_cast<const _Float16*>(N)[i])); });
-  group_sum_max(s, m);
-  if (threadIdx.x == 0) {
-    double* p = partials + (int64_t(blockIdx.y) * kStatGroups + blockIdx.x) * 2;
-    p[0] = s;
-    p[1] = m;
-  }
 }
 
-// One workgroup of an operand: partials -> parameters.  Stage 0: sum and maximum of the means; stage 1: sum of exp.
-template <int kStage>
-__device__ __forceinline__ void mean_params(const double* partials, int groups, OperandParams* params) {
-  const double* in = partials + int64_t(blockIdx.y) * kStatGroups * 2;
+// One workgroup of an operand: the tiles' {sum, maximum, sum of exp(x - the tile's maximum)} -> parameters.
+__device__ __forceinline__ void mean_params(const double* partials, int tiles, OperandParams* params) {
+  const double* in = partials + int64_t(blockIdx.y) * kMaxTiles * 4;
+  __shared__ double top;
   double s = 0.0, m = -INFINITY;
-  for (int g = threadIdx.x; g < groups; g += blockDim.x) {
-    s += in[2 * g];
-    m = fmax(m, in[2 * g + 1]);
+  for (int g = threadIdx.x; g < tiles; g += blockDim.x) {
+    s += in[4 * g];
+    m = fmax(m, in[4 * g + 1]);
   }
   group_sum_max(s, m);
   if (threadIdx.x == 0) {
     OperandParams& p = params[blockIdx.y];
-    if (kStage == 0) {
-      p.sum = s;
-      p.max = m;
-      p.use_softmax = fabs(s - 1.0) > kSumTolerance ? 1.0 : 0.0;
-    } else {
-      p.exp_sum = s;
-    }
+    p.sum = s;
+    p.max = m;
+    p.use_softmax = fabs(s - 1.0) > kSumTolerance ? 1.0 : 0.0;
+    top = m;
   }
+  __syncthreads();
+  m = top;
+  double e = 0.0, none = 0.0;
+  for (int g = threadIdx.x; g < tiles; g += blockDim.x) e += in[4 * g + 2] * exp(in[4 * g + 1] - m);
+  group_sum_max(e, none);
+  if (threadIdx.x == 0) params[blockIdx.y].exp_sum = e;
 }
 
 // ---- sample sort -----------------------------------------------------------------------------------------------
@@ -273,30 +263,35 @@ __device__ __forceinline__ void fold_sort(uint64_t* p, int_t m) {
   __syncthreads();
 }
 
-// The last workgroup of an operand makes the parameters of stage 0 and clears the list of left-over buckets; the others
-// rank kRankThreads / kRankLanes samples each, by counting the smaller ones (and the equal ones before them), kRankLanes lanes
-// per sample.  (One workgroup sorting the samples in its LDS: 50 us for 4096, at 0.65 us a step of fold_sort.)
+// The workgroups rank kRankThreads / kRankLanes samples each, by counting the smaller ones (and the equal ones before them), kRankLanes lanes
+// per sample.  The samples are taken from N and F, once (by every ranking workgroup: 27 us for 2 x 2M blocks): the pass that makes all
+// keys counts them by bucket already.  (One workgroup sorting the samples in its LDS: 50 us for 4096, at 0.65 us a step of fold_sort.)
 constexpr int kRankLanes = 16;
 constexpr int kRankThreads = 512;
-__global__ __launch_bounds__(kRankThreads) void k_splitters(const uint64_t* __restrict__ keys, int64_t n, int buckets,
-                                                        uint64_t* __restrict__ splitters, int sample_shift,
-                                                        const double* __restrict__ partials, int groups,
-                                                        OperandParams* __restrict__ params, uint32_t* __restrict__ rest) {
-  if (blockIdx.x + 1 == gridDim.x) {
-    mean_params<0>(partials, groups, params);
-    if (threadIdx.x < 2 && blockIdx.y == 0) rest[threadIdx.x] = 0;
-    return;
-  }
+__global__ __launch_bounds__(64) void k_samples(const void* __restrict__ N1, const void* __restrict__ F1,
+                                                const void* __restrict__ N2, const void* __restrict__ F2, int ntype, int itype,
+                                                double scale, int kept, int64_t n, int sample_shift, uint64_t* __restrict__ samples) {
+  const int i = int(blockIdx.x) * 64 + int(threadIdx.x);
+  if (i >= 1 << sample_shift) return;
+  const int64_t at = sample_place(i, sample_shift, n);
+  with_loads(blockIdx.y ? N2 : N1, blockIdx.y ? F2 : F1, ntype, itype, kept, [&](auto load_n, auto load_f) {
+    const double f = load_f(at), x = load_n(at);
+    samples[int64_t(blockIdx.y) * kMaxSamples + i] = key_of(x * f * scale);
+  });
+}
+
+__global__ __launch_bounds__(kRankThreads) void k_splitters(const uint64_t* __restrict__ keys, int buckets,
+                                                            uint64_t* __restrict__ splitters, int sample_shift) {
   __shared__ uint64_t sample[kMaxSamples];
   constexpr int kLoads = kMaxSamples / kRankThreads;
   const int samples = 1 << sample_shift;                   // kRankLanes at least
-  const uint64_t* in = keys + int64_t(blockIdx.y) * n;
   const int mine = int(blockIdx.x) * (kRankThreads / kRankLanes) + int(threadIdx.x) / kRankLanes;
   uint64_t v[kLoads];
+  const uint64_t* in = keys + int64_t(blockIdx.y) * kMaxSamples;
 #pragma unroll
   for (int u = 0; u < kLoads; ++u) {
     const int i = u * kRankThreads + int(threadIdx.x);
-    if (u * kRankThreads < samples) v[u] = in[sample_place(i < samples ? i : samples - 1, sample_shift, n)];
+    if (u * kRankThreads < samples) v[u] = in[i < samples ? i : samples - 1];
   }
 #pragma unroll
   for (int u = 0; u < kLoads; ++u)
@@ -342,28 +337,111 @@ __device__ __forceinline__ void buckets_of(const uint64_t* splitters, int bucket
     bucket[u] = 2 * bucket[u] + (bucket[u] < buckets - 1 && splitters[bucket[u]] == key[u] ? 1 : 0);
 }
 
-// kStage 0: the keys of each bucket in the tile are counted, and exp(x - max) is summed on the way.
-// kStage 1: the keys go to their buckets (hist then holds the keys of the bucket in earlier tiles).
-// The order of equal or unequal keys within a bucket does not matter, so places are handed out by LDS atomics.
-template <int kStage>
-__global__ __launch_bounds__(kPassThreads) void k_buckets(const uint64_t* __restrict__ keys, uint64_t* __restrict__ out,
+// consecutive workgroups go to the eight dies in turn: each die gets a run of tiles, whose pieces of a bucket are
+// neighbours, so that its L2 completes their lines
+__device__ __forceinline__ int tile_of_group() { return int(blockIdx.x & 7u) * int(gridDim.x >> 3) + int(blockIdx.x >> 3); }
+
+// The means of a tile as keys, their sum, maximum and sum of exp (rescaled whenever a thread's maximum rises, once for
+// kMeansPerThread of them), and with kCount the tile's keys of each bucket.  Where a block's indices fill a 128-byte line or more every
+// line of F is fetched for two bytes of it (the L2 asks for whole lines, whatever the load's scope): that is the time, 82 us for 2 x 2M of
+// them alone, and the search, the exponentials and the counting run behind it: 106 us, with a pass of its own for these 112 and 27.
+// Non-temporal loads: a line is used once (a plain gather 80 us instead of 88).  The next step's loads ahead of this one's work: 112.
+template <bool kCount>
+__global__ __launch_bounds__(kPassThreads) void k_means(const void* __restrict__ N1, const void* __restrict__ F1,
+                                                        const void* __restrict__ N2, const void* __restrict__ F2, int ntype,
+                                                        int itype, double scale, int64_t n, int64_t tile_keys, int tiles, int kept,
+                                                        int buckets, const uint64_t* __restrict__ splitters,
+                                                        uint64_t* __restrict__ keys, uint32_t* __restrict__ hist,
+                                                        uint32_t* __restrict__ rest, double* __restrict__ partials) {
+  extern __shared__ __align__(16) uint64_t split[];         // [buckets], then the counts [2 buckets]
+  uint32_t* count = reinterpret_cast<uint32_t*>(split + buckets);
+  __shared__ double top;
+  const int tile = tile_of_group();
+  if (tile >= tiles) return;                                // uniform over the workgroup
+  if (tile == 0 && blockIdx.y == 0 && threadIdx.x < 2) rest[threadIdx.x] = 0;
+  if (kCount) {
+    for (int i = threadIdx.x; i < buckets - 1; i += kPassThreads) split[i] = splitters[int64_t(blockIdx.y) * buckets + i];
+    for (int i = threadIdx.x; i < 2 * buckets; i += kPassThreads) count[i] = 0;
+    __syncthreads();
+  }
+  uint64_t* out = keys + int64_t(blockIdx.y) * n;
+  const int64_t begin = int64_t(tile) * tile_keys;
+  const int64_t end = begin + tile_keys < n ? begin + tile_keys : n;
+  double s = 0.0, m = -INFINITY, e = 0.0;
+  with_loads(blockIdx.y ? N2 : N1, blockIdx.y ? F2 : F1, ntype, itype, kept, [&](auto load_n, auto load_f) {
+    for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kPassThreads * kMeansPerThread) {
+      double v[kMeansPerThread], f[kMeansPerThread];
+#pragma unroll
+      for (int u = 0; u < kMeansPerThread; ++u) {
+        const int64_t i = i0 + u * kPassThreads < end ? i0 + u * kPassThreads : end - 1;
+        f[u] = load_f(i);
+        v[u] = load_n(i);
+      }
+      uint64_t key[kMeansPerThread];
+      double most = m;
+#pragma unroll
+      for (int u = 0; u < kMeansPerThread; ++u) {
+        const int64_t i = i0 + u * kPassThreads;
+        v[u] = v[u] * f[u] * scale;
+        key[u] = key_of(v[u]);
+        if (i < end) {
+          out[i] = key[u];
+          s += v[u];
+          most = fmax(most, v[u]);
+        }
+      }
+      e *= most > m ? exp(m - most) : 1.0;
+      m = most;
+#pragma unroll
+      for (int u = 0; u < kMeansPerThread; ++u) {
+        const double x = exp(v[u] - m);
+        e += i0 + u * kPassThreads < end ? x : 0.0;
+      }
+      if (kCount) {
+        int b[kMeansPerThread];
+        buckets_of<kMeansPerThread>(split, buckets, key, b);
+#pragma unroll
+        for (int u = 0; u < kMeansPerThread; ++u)
+          if (i0 + u * kPassThreads < end) atomicAdd(&count[b[u]], 1u);
+      }
+    }
+  });
+  const double mine = m;
+  group_sum_max(s, m);
+  if (threadIdx.x == 0) top = m;
+  __syncthreads();
+  const double tile_max = top;
+  double none = 0.0;
+  e *= mine < tile_max ? exp(mine - tile_max) : 1.0;         // a thread without keys: nothing times exp(-infinity)
+  group_sum_max(e, none);
+  if (threadIdx.x == 0) {
+    double* p = partials + (int64_t(blockIdx.y) * kMaxTiles + tile) * 4;
+    p[0] = s;
+    p[1] = tile_max;
+    p[2] = e;
+  }
+  if (kCount) {
+    uint32_t* h = hist + (int64_t(blockIdx.y) * tiles + tile) * 2 * buckets;
+    for (int i = threadIdx.x; i < 2 * buckets; i += kPassThreads) h[i] = count[i];   // (group_sum_max has the barrier)
+  }
+}
+
+// The keys go to their buckets (hist holds the keys of the bucket in earlier tiles).  The order within a bucket does not matter, so
+// places are handed out by LDS atomics.  Keys of a gap stay behind: nobody reads their places.
+__global__ __launch_bounds__(kPassThreads) void k_scatter(const uint64_t* __restrict__ keys, uint64_t* __restrict__ out,
                                                           int64_t n, int64_t tile_keys, int tiles, int buckets,
                                                           const uint64_t* __restrict__ splitters,
-                                                          uint32_t* __restrict__ hist, const uint32_t* __restrict__ totals,
-                                                          const OperandParams* __restrict__ params,
-                                                          double* __restrict__ partials) {
-  extern __shared__ __align__(16) uint64_t split[];         // [buckets], then the counts or cursors [2 buckets]
+                                                          const uint32_t* __restrict__ hist, const uint32_t* __restrict__ totals,
+                                                          const Gap* __restrict__ gaps) {
+  extern __shared__ __align__(16) uint64_t split[];         // [buckets], then the cursors [2 buckets]
   uint32_t* count = reinterpret_cast<uint32_t*>(split + buckets);
-  // consecutive workgroups go to the eight dies in turn: each die gets a run of tiles, whose pieces of a bucket are
-  // neighbours, so that its L2 completes their lines
-  const int tile = int(blockIdx.x & 7u) * int(gridDim.x >> 3) + int(blockIdx.x >> 3);
+  const int tile = tile_of_group();
   if (tile >= tiles) return;                                // uniform over the workgroup
   const uint64_t* in = keys + int64_t(blockIdx.y) * n;
-  uint32_t* h = hist + (int64_t(blockIdx.y) * tiles + tile) * 2 * buckets;
+  const uint32_t* h = hist + (int64_t(blockIdx.y) * tiles + tile) * 2 * buckets;
+  const Gap gap = gaps ? gaps[blockIdx.y] : Gap{1, 0};
   for (int i = threadIdx.x; i < buckets - 1; i += kPassThreads) split[i] = splitters[int64_t(blockIdx.y) * buckets + i];
-  if (kStage == 0) {
-    for (int i = threadIdx.x; i < 2 * buckets; i += kPassThreads) count[i] = 0;
-  } else {
+  {
     // the buckets' first places: every thread adds up a run of totals, the runs are chained over the workgroup
     __shared__ uint32_t wave_total[kPassThreads / 64];
     const uint32_t* t = totals + int64_t(blockIdx.y) * 2 * buckets;
@@ -388,54 +466,74 @@ __global__ __launch_bounds__(kPassThreads) void k_buckets(const uint64_t* __rest
   __syncthreads();
   const int64_t begin = int64_t(tile) * tile_keys;
   const int64_t end = begin + tile_keys < n ? begin + tile_keys : n;
-  const double shift = kStage == 0 ? params[blockIdx.y].max : 0.0;
-  double s = 0.0;
-  for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kPassThreads * kKeysInFlight) {
-    uint64_t key[kKeysInFlight];
+  const auto send = [&](auto count_t, const uint64_t* key, const bool* goes) {
+    constexpr int kCount = decltype(count_t)::value;
+    int b[kCount];
+    uint32_t place[kCount];
+    buckets_of<kCount>(split, buckets, key, b);
 #pragma unroll
-    for (int u = 0; u < kKeysInFlight; ++u) {
-      const int64_t i = i0 + u * kPassThreads;
-      key[u] = in[i < end ? i : end - 1];
-    }
-    if (kStage == 0) {
+    for (int u = 0; u < kCount; ++u)
+      if (goes[u]) place[u] = atomicAdd(&count[b[u]], 1u);
+#pragma unroll
+    for (int u = 0; u < kCount; ++u)
+      if (goes[u]) out[int64_t(blockIdx.y) * n + place[u]] = key[u];
+  };
+  if (gap.from > gap.to) {
+    for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kPassThreads * kKeysInFlight) {
+      uint64_t key[kKeysInFlight];
+      bool goes[kKeysInFlight];
 #pragma unroll
       for (int u = 0; u < kKeysInFlight; ++u) {
-        const double e = exp(value_of(key[u]) - shift);
-        s += i0 + u * kPassThreads < end ? e : 0.0;
+        const int64_t i = i0 + u * kPassThreads;
+        goes[u] = i < end;
+        key[u] = in[goes[u] ? i : end - 1];
       }
+      send(std::integral_constant<int, kKeysInFlight>(), key, goes);
     }
-    if (buckets > 1) {
-      int b[kKeysInFlight];
-      uint32_t place[kKeysInFlight];
-      buckets_of<kKeysInFlight>(split, buckets, key, b);
-#pragma unroll
-      for (int u = 0; u < kKeysInFlight; ++u)
-        if (i0 + u * kPassThreads < end) place[u] = atomicAdd(&count[b[u]], 1u);
-      if (kStage == 1) {
-#pragma unroll
-        for (int u = 0; u < kKeysInFlight; ++u)
-          if (i0 + u * kPassThreads < end) out[int64_t(blockIdx.y) * n + place[u]] = key[u];
-      }
+    return;
+  }
+  // the few keys beside the gap are collected, and then looked up together
+  __shared__ uint64_t going[kGoing];
+  __shared__ uint32_t n_going;
+  if (threadIdx.x == 0) n_going = 0;
+  __syncthreads();
+  const auto send_going = [&]() {
+    for (uint32_t i0 = threadIdx.x; i0 < n_going; i0 += kPassThreads) {
+      const uint64_t key = going[i0];
+      const bool goes = true;
+      send(std::integral_constant<int, 1>(), &key, &goes);
     }
+    __syncthreads();
+    if (threadIdx.x == 0) n_going = 0;
+    __syncthreads();
+  };
+  for (int64_t j0 = begin; j0 < end; j0 += kPassThreads * kGoingInFlight) {
+    uint64_t key[kGoingInFlight];
+#pragma unroll
+    for (int u = 0; u < kGoingInFlight; ++u) {
+      const int64_t i = j0 + threadIdx.x + u * kPassThreads;
+      key[u] = in[i < end ? i : end - 1];
+    }
+    __syncthreads();
+    if (n_going > uint32_t(kGoing - kPassThreads * kGoingInFlight)) send_going();      // uniform: nobody adds between the barriers
+    else __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kGoingInFlight; ++u)
+      if (j0 + threadIdx.x + u * kPassThreads < end && (key[u] < gap.from || key[u] > gap.to)) going[atomicAdd(&n_going, 1u)] = key[u];
   }
-  if (kStage == 0) {
-    double none = 0.0;
-    group_sum_max(s, none);                                 // (contains the barrier)
-    if (threadIdx.x == 0) partials[(int64_t(blockIdx.y) * kStatGroups + tile) * 2] = s;
-    if (buckets > 1)
-      for (int i = threadIdx.x; i < 2 * buckets; i += kPassThreads) h[i] = count[i];
-  }
+  __syncthreads();
+  send_going();
 }
 
 // hist [tile][bucket] -> keys of the bucket in earlier tiles, in place, and the buckets' totals.  A workgroup takes 64
-// buckets, wave w the w-th run of tiles; the last workgroup along x makes the parameters of stage 1.
+// buckets, wave w the w-th run of tiles; the last workgroup along x makes the parameters.
 constexpr int kScanWaves = 16;
 __global__ __launch_bounds__(64 * kScanWaves) void k_bucket_scan(uint32_t* __restrict__ hist, int tiles, int bins,
                                                                  uint32_t* __restrict__ totals,
                                                                  const double* __restrict__ partials,
                                                                  OperandParams* __restrict__ params) {
   if (blockIdx.x + 1 == gridDim.x) {
-    mean_params<1>(partials, tiles, params);
+    mean_params(partials, tiles, params);
     return;
   }
   __shared__ uint32_t part[kScanWaves][64];
@@ -469,11 +567,215 @@ __global__ __launch_bounds__(64 * kScanWaves) void k_bucket_scan(uint32_t* __res
   }
 }
 
+__device__ __forceinline__ double mapped(uint64_t key, const OperandParams& p) {
+  const double v = value_of(key);
+  return p.use_softmax != 0.0 ? exp(v - p.max) / p.exp_sum : v;
+}
+
+// Which buckets matter.  A difference below `least` times the largest one, m, adds nothing to the distance (see k_distance).  The
+// buckets' totals say which rank is in which bucket of either operand, and the splitters between which bounds the two values of a rank
+// lie: a run of ranks in one bucket of A and one of B whose bounds are closer than `least` times a difference that is certain
+// to be reached (by two buckets that lie apart, or by the two maxima) need not be sorted, nor scattered into buckets.  With smooth fields, whose
+// largest values differ, that is all but some hundredth of the keys (2 x 2M: scatter 39 -> 15 us, sort 63 -> 22, distance 23 -> 7; this
+// kernel 16; 2 x 3.4M of 32-bit indices the whole distance 458 -> 198, 262144 of blocks of 8x8 138 -> 97).  With nearly equal operands nothing is
+// left out, and the call takes what it took before (2M: 277 and 274 us; 1M: 144 and 163).  What is found is the same: `threshold` is below
+// every difference that counts.  Below kSelectMin buckets the launch costs what it saves.
+// One workgroup.  A run of ranks starts where a bucket of A or of B does: kEach of each per thread, in the order of the buckets.
+constexpr int kSelectThreads = 1024;
+template <int kEach>
+__global__ __launch_bounds__(kSelectThreads) void k_select(int64_t n, int buckets, const uint64_t* __restrict__ splitters,
+                                                           const uint32_t* __restrict__ totals,
+                                                           const OperandParams* __restrict__ params, double least,
+                                                           Gap* __restrict__ gap, uint8_t* __restrict__ needed,
+                                                           uint2* __restrict__ ranks) {
+  constexpr int kBucketsMax = kEach * kSelectThreads;
+  constexpr int kWaves = kSelectThreads / 64;
+  __shared__ union {
+    uint32_t first[2][kBucketsMax];               // the buckets' first ranks ...
+    double value[2][kBucketsMax / 2];             // ... and then the mapped splitters
+  } lds;
+  __shared__ uint8_t need[2][kBucketsMax];
+  __shared__ uint32_t wave_count[2][kWaves];
+  __shared__ double wave_low[kWaves], wave_size[kWaves];
+  __shared__ int wave_last[2][kWaves];
+  __shared__ unsigned long long longest[2];
+  const int t = int(threadIdx.x), lane = t & 63, wave = t >> 6, bins = 2 * buckets;
+  const OperandParams p[2] = {params[0], params[1]};
+  // first ranks
+  uint32_t first[2][kEach], size[2][kEach];
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    uint32_t sum = 0;
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      const int b = t * kEach + j;
+      size[o][j] = b < bins ? totals[o * bins + b] : 0u;
+      sum += size[o][j];
+    }
+    uint32_t before = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t up = __shfl_up(before, off, 64);
+      if (lane >= off) before += up;
+    }
+    if (lane == 63) wave_count[o][wave] = before;
+    first[o][0] = before - sum;
+  }
+  if (t < 2) longest[t] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    for (int w = 0; w < wave; ++w) first[o][0] += wave_count[o][w];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      if (j > 0) first[o][j] = first[o][j - 1] + size[o][j - 1];
+      if (t * kEach + j < kBucketsMax) {
+        lds.first[o][t * kEach + j] = first[o][j];             // n beyond the last bucket
+        need[o][t * kEach + j] = 0;
+      }
+    }
+  }
+  __syncthreads();
+  // the runs: of thread t's buckets of operand o, the other operand's bucket in which they start, and their lengths
+  int other[2][kEach];
+  uint32_t length[2][kEach];
+#pragma unroll
+  for (int o = 0; o < 2; ++o)
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      int b = 0;                                              // the last bucket that starts at or before the rank
+      for (int step = bins >> 1; step > 0; step >>= 1)
+        if (b + step < bins && lds.first[1 - o][b + step] <= first[o][j]) b += step;
+      other[o][j] = b;
+      const uint32_t end = b + 1 < bins ? lds.first[1 - o][b + 1] : uint32_t(n), mine = first[o][j] + size[o][j];
+      length[o][j] = size[o][j] == 0 || (o == 1 && lds.first[0][b] == first[1][j]) ? 0u : (end < mine ? end : mine) - first[o][j];
+    }
+  __syncthreads();
+  // values at the splitters, and the largest magnitude among them
+  const double inv[2] = {1.0 / p[0].exp_sum, 1.0 / p[1].exp_sum};
+  const auto value_at = [&](double v, int o) { return p[o].use_softmax != 0.0 ? exp(v - p[o].max) * inv[o] : v; };
+  const double top[2] = {p[0].use_softmax != 0.0 ? inv[0] : p[0].max, p[1].use_softmax != 0.0 ? inv[1] : p[1].max};
+  double most = fmax(fabs(top[0]), fabs(top[1]));
+  for (int i = t; i < 2 * (buckets - 1); i += kSelectThreads) {
+    const int o = i >= buckets - 1 ? 1 : 0, b = i - o * (buckets - 1);
+    const double v = value_at(value_of(splitters[o * buckets + b]), o);
+    lds.value[o][b] = v;
+    most = fmax(most, fabs(v));
+  }
+  __syncthreads();
+  const auto low = [&](int o, int b) { return (b & 1) ? lds.value[o][b >> 1] : (b > 0 ? lds.value[o][(b >> 1) - 1] : (p[o].use_softmax != 0.0 ? 0.0 : -INFINITY)); };
+  const auto high = [&](int o, int b) { return (b >> 1) < buckets - 1 ? lds.value[o][b >> 1] : top[o]; };
+  double reached = fabs(top[0] - top[1]);
+  double apart[2][kEach];                                     // how far the run's two values can be from each other
+#pragma unroll
+  for (int o = 0; o < 2; ++o)
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      apart[o][j] = 0.0;
+      if (length[o][j] == 0) continue;
+      const int b = t * kEach + j, c = other[o][j];
+      apart[o][j] = fmax(high(o, b) - low(1 - o, c), high(1 - o, c) - low(o, b));
+      reached = fmax(reached, fmax(low(o, b) - high(1 - o, c), low(1 - o, c) - high(o, b)));
+    }
+  reached = wave_max(reached);
+  most = wave_max(most);
+  if (lane == 0) {
+    wave_low[wave] = reached;
+    wave_size[wave] = most;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    reached = fmax(reached, wave_low[w]);
+    most = fmax(most, wave_size[w]);
+  }
+  // The mapped values are off by a few 2^-53 of the largest; where means or their sums are no finite numbers, everything matters.
+  const double slack = 64.0 * 2.220446049250313e-16 * most;
+  const bool finite = fabs(p[0].sum) < INFINITY && fabs(p[1].sum) < INFINITY && fabs(p[0].exp_sum) < INFINITY && fabs(p[1].exp_sum) < INFINITY;
+  double threshold = least * (reached - slack) * (1.0 - 1e-12);
+  if (!finite || !(threshold > slack)) threshold = 0.0;
+  uint32_t pieces = 0;
+#pragma unroll
+  for (int o = 0; o < 2; ++o)
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      if (length[o][j] != 0 && !(apart[o][j] + slack < threshold)) {
+        need[o][t * kEach + j] = 1;
+        need[1 - o][other[o][j]] = 1;
+        pieces += (length[o][j] + kPieceRanks - 1) / kPieceRanks;
+      } else {
+        length[o][j] = 0;
+      }
+    }
+  uint32_t before = pieces;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t up = __shfl_up(before, off, 64);
+    if (lane >= off) before += up;
+  }
+  if (lane == 63) wave_count[0][wave] = before;
+  __syncthreads();
+  before -= pieces;
+  for (int w = 0; w < wave; ++w) before += wave_count[0][w];
+#pragma unroll
+  for (int o = 0; o < 2; ++o)
+#pragma unroll
+    for (int j = 0; j < kEach; ++j)
+      for (uint32_t k = 0; k < length[o][j]; k += kPieceRanks)
+        ranks[before++] = make_uint2(first[o][j] + k, length[o][j] - k < uint32_t(kPieceRanks) ? length[o][j] - k : uint32_t(kPieceRanks));
+  if (t == kSelectThreads - 1) {
+    Selection* sel = reinterpret_cast<Selection*>(gap + 2);
+    sel->threshold = threshold;
+    sel->pieces = int(before);
+  }
+  // the longest run of buckets between two that matter, of either operand: its keys need not be looked at again
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    int last = -1;                                            // of the thread's needed buckets, then of all before them
+#pragma unroll
+    for (int j = 0; j < kEach; ++j)
+      if (t * kEach + j < bins && need[o][t * kEach + j]) last = t * kEach + j;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int up = __shfl_up(last, off, 64);
+      if (lane >= off) last = up > last ? up : last;
+    }
+    if (lane == 63) wave_last[o][wave] = last;
+    last = __shfl_up(last, 1, 64);
+    if (lane == 0) last = -1;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) last = wave_last[o][w] > last ? wave_last[o][w] : last;
+    const auto run_below = [&](int b) {
+      if (b - last >= 2) atomicMax(&longest[o], (unsigned long long)(b - last) << 32 | (unsigned long long)(last + 1) << 16 | (unsigned long long)b);
+    };
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      const int b = t * kEach + j;
+      if (b < bins && need[o][b]) {
+        run_below(b);
+        last = b;
+      }
+    }
+    if (t == kSelectThreads - 1) run_below(bins);
+    for (int b = t; b < bins; b += kSelectThreads) needed[o * bins + b] = need[o][b];
+  }
+  __syncthreads();
+  if (t < 2) {
+    const int above = int(longest[t] & 0xffffu), below = int((longest[t] >> 16) & 0xffffu) - 1;
+    const uint64_t* split = splitters + t * buckets;
+    Gap g = {1, 0};
+    if (longest[t] != 0 && (below < 0 || (below >> 1) < buckets - 1)) {      // nothing is above the last splitter's last bucket
+      g.from = below < 0 ? 0 : split[below >> 1] + ((below & 1) ? 1u : 0u);
+      g.to = above == bins ? ~uint64_t(0) : ((above & 1) ? split[above >> 1] - 1u : split[(above >> 1) - 1]);
+    }
+    gap[t] = g;
+  }
+}
+
 constexpr int kSubs = 2048;
 constexpr int kMaxSub = 128;
 constexpr int kRestGroups = 64;                  // workgroups of the second sorting kernel
 constexpr int kBucketThreads = 1024;
 constexpr int kBucketWaves = kBucketThreads / 64;
+constexpr int kOwnSplitters = 256;               // that a crowded bucket draws from its keys ...
+constexpr int kOwnSlots = kSubs / kOwnSplitters; // ... and the intervals below each: the last for the keys that equal it
 
 // cursor[] -> first[]: exclusive prefix sums, by the whole workgroup
 __device__ __forceinline__ void scan_intervals(const uint32_t* cursor, uint32_t* first, uint32_t* wave_total) {
@@ -549,24 +851,28 @@ __device__ __forceinline__ BucketPlace bucket_place(int b, int operand, int64_t 
 // kHeldKeys, are read once and stay in registers.  They are dealt into kSubs equal intervals between the smallest and the
 // largest of their values (between neighbouring quantiles the means are spread nearly evenly: one key an interval), put
 // together by interval in LDS, at most kBucketCap keys a round, and every key counts the smaller ones of its interval.
-// Larger buckets, those with more than kMaxSub keys in one interval (one in a thousand) and those with NaN, which has no
-// interval among the values, go to the list of k_bucket_sort_rest.  With one bucket in == out.
+// Where that leaves more than kMaxSub keys in one interval (values over many orders of magnitude, as in the first and the last
+// bucket, or where there is one bucket only) or meets NaN, which has no interval among the values, the intervals are taken between
+// splitters drawn from the bucket itself (4096 means of 8x8 blocks: sort 84 -> 26 us, the distance 111 -> 46).  Larger buckets and those that
+// are crowded even so go to the list of k_bucket_sort_rest.  With one bucket in == out.
 constexpr int kHeldKeys = 8192;
 // above, the pieces of a bucket are at most twice its keys / kPieceKeys, those of both operands at most 2 * 2 n / kPieceKeys <= K
 constexpr int kPieceKeys = 4 * kBucketKeys;
 static_assert(2 * kSampleSortMax / kBucketKeys >= kBins, "the workspace's totals hold the radix sort's digits");
-__global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_t* in_all, uint64_t* out_all, int64_t n,
-                                                                   int buckets, const uint32_t* __restrict__ totals,
-                                                                   uint32_t* __restrict__ rest, uint2* __restrict__ pieces) {
+__device__ __forceinline__ void sort_bucket(int bucket, bool sorts, bool copies, const uint64_t* in_all, uint64_t* out_all, int64_t n,
+                                            int buckets, const uint32_t* __restrict__ totals, uint32_t* __restrict__ rest,
+                                            uint2* __restrict__ pieces) {
   __shared__ uint64_t key[kBucketCap];
   __shared__ uint32_t first[kSubs + 1], cursor[kSubs];
   __shared__ uint32_t wave_total[kBucketWaves];
   __shared__ double2 bounds[kBucketWaves];
+  __shared__ uint64_t split[kOwnSplitters], drawn[kOwnSplitters];
   constexpr int kPerThread = kHeldKeys / kBucketThreads;
-  const BucketPlace place = bucket_place(blockIdx.x, blockIdx.y, n, buckets, totals, wave_total);
+  const BucketPlace place = bucket_place(bucket, blockIdx.y, n, buckets, totals, wave_total);
   const uint64_t* in = in_all + int64_t(blockIdx.y) * n + place.base;
   uint64_t* out = out_all + int64_t(blockIdx.y) * n + place.base;
-  if (place.equal <= kPieceKeys) {
+  if (!copies) {
+  } else if (place.equal <= kPieceKeys) {
     for (int64_t i = threadIdx.x; i < place.equal; i += kBucketThreads) out[place.m + i] = in[place.m + i];
   } else if (threadIdx.x == 0) {
     const uint32_t count = uint32_t((place.equal + kPieceKeys - 1) / kPieceKeys), at = atomicAdd(rest + 1, count);
@@ -576,9 +882,9 @@ __global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_
       pieces[at + k] = make_uint2(uint32_t(begin + int64_t(k) * kPieceKeys), uint32_t(left < kPieceKeys ? left : kPieceKeys));
     }
   }
-  if (place.m == 0) return;                                // uniform over the workgroup, here and below
+  if (place.m == 0 || !sorts) return;                      // uniform over the workgroup, here and below
   if (place.m > kHeldKeys) {
-    if (threadIdx.x == 0) rest[2 + atomicAdd(rest, 1u)] = blockIdx.x * 2 + blockIdx.y;
+    if (threadIdx.x == 0) rest[2 + atomicAdd(rest, 1u)] = uint32_t(bucket) * 2 + blockIdx.y;
     return;
   }
   const int m = int(place.m), t = int(threadIdx.x);
@@ -616,13 +922,56 @@ __global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_
     if (j * kBucketThreads + t < m) {
       const double value = value_of(held[j]);
       const int s = int(fmin(fmax((value - least) * scale, 0.0), double(kSubs - 1)));
+      // a wave that has many keys in one interval need not have them counted one after the other there
+      if (m > 2 * kMaxSub && __popcll(__ballot(s == __builtin_amdgcn_readfirstlane(s))) > 24) {
+        crowded = true;
+        where[j] = 0;
+        continue;
+      }
       const uint32_t at = atomicAdd(&cursor[s], 1u);
       where[j] = uint32_t(s) | (at << 16);
       crowded = crowded || at >= uint32_t(kMaxSub) || value != value;
     }
-  if (__syncthreads_or(crowded)) {
-    if (t == 0) rest[2 + atomicAdd(rest, 1u)] = blockIdx.x * 2 + blockIdx.y;
-    return;
+  bool by_sample = false;
+  if (__syncthreads_or(crowded)) {                         // once more, between splitters of the bucket's own
+    by_sample = m <= kBucketCap;
+    crowded = !by_sample;
+    if (by_sample) {
+#pragma unroll
+      for (int j = 0; j < kPerThread; ++j)
+        if (j * kBucketThreads + t < m) key[j * kBucketThreads + t] = held[j];
+      for (int i = t; i < kSubs; i += kBucketThreads) cursor[i] = 0;
+      __syncthreads();
+      if (t < kOwnSplitters) drawn[t] = key[(t * m) / kOwnSplitters];
+      __syncthreads();
+      constexpr int kParts = kBucketThreads / kOwnSplitters, kEach = kOwnSplitters / kParts;
+      const int mine = t / kParts, part = t % kParts;
+      const uint64_t value = drawn[mine];
+      int rank = 0;
+      for (int i = part * kEach; i < (part + 1) * kEach; ++i) rank += drawn[i] < value || (drawn[i] == value && i < mine) ? 1 : 0;
+#pragma unroll
+      for (int off = 1; off < kParts; off <<= 1) rank += __shfl_xor(rank, off, 64);
+      if (part == 0) split[rank] = value;
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < kPerThread; ++j)
+        if (j * kBucketThreads + t < m) {
+          int b;
+          buckets_of<1>(split, kOwnSplitters, held + j, &b);
+          int s = (b >> 1) * kOwnSlots + ((b & 1) ? kOwnSlots - 1 : 0);
+          if ((b & 1) == 0 && b > 0 && b < 2 * (kOwnSplitters - 1)) {      // by the key between its two splitters
+            const uint64_t lo = split[(b >> 1) - 1], hi = split[b >> 1];
+            s += int(fmin(double(held[j] - lo) * (double(kOwnSlots - 1) / double(hi - lo)), double(kOwnSlots - 2)));
+          }
+          const uint32_t at = atomicAdd(&cursor[s], 1u);
+          where[j] = uint32_t(s) | (at << 16);
+          crowded = crowded || ((b & 1) == 0 && at >= uint32_t(kMaxSub));
+        }
+    }
+    if (__syncthreads_or(crowded)) {
+      if (t == 0) rest[2 + atomicAdd(rest, 1u)] = uint32_t(bucket) * 2 + blockIdx.y;
+      return;
+    }
   }
   scan_intervals(cursor, first, wave_total);
   __syncthreads();
@@ -649,7 +998,10 @@ __global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_
         rank[j] = 0;
         if (s >= s0 && s < s1) {
           const int a = int(first[s]) - from, b = int(first[s + 1]) - from, self = a + int(where[j] >> 16);
-          for (int q = a; q < b; ++q) {
+          if (by_sample && s % kOwnSlots == kOwnSlots - 1) rank[j] = where[j] >> 16;      // equal to a splitter
+          else
+#pragma unroll 4
+            for (int q = a; q < b; ++q) {
             const uint64_t other = key[q];
             rank[j] += other < held[j] || (other == held[j] && q < self) ? 1u : 0u;
           }
@@ -667,6 +1019,16 @@ __global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_
     __syncthreads();
     s0 = s1;
   }
+}
+
+// grid (buckets, operand): all of them, or those that k_select has marked
+__global__ __launch_bounds__(kBucketThreads, 8) void k_bucket_sort(const uint64_t* in_all, uint64_t* out_all, int64_t n,
+                                                                   int buckets, const uint32_t* __restrict__ totals,
+                                                                   uint32_t* __restrict__ rest, uint2* __restrict__ pieces,
+                                                                   const uint8_t* __restrict__ needed) {
+  const int bin = int(blockIdx.y) * 2 * buckets + 2 * int(blockIdx.x);
+  const bool sorts = !needed || needed[bin] != 0, copies = !needed || needed[bin + 1] != 0;
+  if (sorts || copies) sort_bucket(blockIdx.x, sorts, copies, in_all, out_all, n, buckets, totals, rest, pieces);
 }
 
 // The pieces of large buckets of one value, and the buckets that k_bucket_sort leaves, listed in rest, any number of keys in
@@ -988,71 +1350,92 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint64_t* 
 }
 
 // ---- the distance ------------------------------------------------------------------------------------------
-__device__ __forceinline__ double mapped(uint64_t key, const OperandParams& p) {
-  const double v = value_of(key);
-  return p.use_softmax != 0.0 ? exp(v - p.max) / p.exp_sum : v;
-}
-
-// Stage 0: d = |P_A - P_B| into `diff`, and the workgroups' maxima.  Stage 1: sum (d / m)^p, m the largest of the maxima.  A term
-// with (d / m)^p below 2^-100 is left at zero: all of the up to 2^31 of them together are below 2^-69 of the sum, whose
-// largest term is 1, and at the orders in use (68 and more) that is every d below a third of m, whose pow would be most of
-// the pass (2M keys: 10.7 us, 25.7 with a pow for each).  grid (groups)
-template <int kStage>
-__global__ __launch_bounds__(kThreads) void k_distance(const uint64_t* __restrict__ sorted, double* __restrict__ diff, int64_t n,
-                                                       int64_t chunk, const OperandParams* __restrict__ params, double order,
-                                                       const double* __restrict__ maxima, double* __restrict__ partials) {
-  __shared__ double m_all;
-  const int64_t begin = int64_t(blockIdx.x) * chunk;
-  const int64_t end = begin + chunk < n ? begin + chunk : n;
-  double s = 0.0, m = 0.0;
-  if (kStage == 0) {
-    const OperandParams pa = params[0], pb = params[1];
-    for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kThreads * kDistancesInFlight) {
-      uint64_t a[kDistancesInFlight], b[kDistancesInFlight];
-#pragma unroll
-      for (int u = 0; u < kDistancesInFlight; ++u) {
-        const int64_t i = i0 + u * kThreads < end ? i0 + u * kThreads : end - 1;     // the last one again changes nothing
-        a[u] = sorted[i];
-        b[u] = sorted[n + i];
+// d = |P_A - P_B| of a workgroup's ranks: their maximum m and the sum of (d / m)^p, in one launch (two, with the differences in memory: 23 us for
+// 2 x 2M ranks): the differences wait in LDS, those that do not fit are computed again.  A term with (d / m)^p below
+// 2^-100 is left at zero: all of the up to 2^31 of them together are below 2^-69 of the sum, whose largest term is 1, and at the
+// orders in use (68 and more) that is every d below a third of m, whose pow would be most of the pass.  `chosen`: the pieces of ranks
+// that k_select has left, in its order; otherwise `chunk` ranks per workgroup.
+__global__ __launch_bounds__(kThreads) void k_distance(const uint64_t* __restrict__ sorted, int64_t n, int64_t chunk,
+                                                       const OperandParams* __restrict__ params, double order, double least,
+                                                       const Selection* __restrict__ chosen, const uint2* __restrict__ ranks,
+                                                       double* __restrict__ partials) {
+  __shared__ double top;
+  const OperandParams pa = params[0], pb = params[1];
+  const int pieces = chosen ? chosen->pieces : int(gridDim.x);
+  __shared__ double kept[kKeptDifferences][kThreads];
+  // calls f(d) for the thread's differences from number `skip` on
+  const auto each = [&](int skip, auto f) {
+    int number = 0;
+    for (int k = blockIdx.x; k < pieces; k += gridDim.x) {
+      int64_t begin = int64_t(k) * chunk, end = begin + chunk < n ? begin + chunk : n;
+      if (chosen) {
+        const uint2 r = ranks[k];
+        begin = r.x;
+        end = begin + r.y;
       }
+      for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kThreads * kDistancesInFlight) {
+        if (number + kDistancesInFlight <= skip) {
+          number += kDistancesInFlight;
+          continue;
+        }
+        uint64_t a[kDistancesInFlight], b[kDistancesInFlight];
 #pragma unroll
-      for (int u = 0; u < kDistancesInFlight; ++u) {
-        const int64_t i = i0 + u * kThreads < end ? i0 + u * kThreads : end - 1;
-        const double d = fabs(mapped(a[u], pa) - mapped(b[u], pb));
-        diff[i] = d;
-        m = fmax(m, d);
+        for (int u = 0; u < kDistancesInFlight; ++u) {
+          const int64_t i = i0 + u * kThreads < end ? i0 + u * kThreads : end - 1;
+          a[u] = sorted[i];
+          b[u] = sorted[n + i];
+        }
+#pragma unroll
+        for (int u = 0; u < kDistancesInFlight; ++u, ++number)
+          f(number, i0 + u * kThreads < end ? fabs(mapped(a[u], pa) - mapped(b[u], pb)) : 0.0);
       }
     }
-  } else {
-    for (int g = threadIdx.x; g < int(gridDim.x); g += kThreads) m = fmax(m, maxima[2 * g + 1]);
-    double none = 0.0;
-    group_sum_max(none, m);
-    if (threadIdx.x == 0) m_all = m;
-    __syncthreads();
-    m = m_all;
-    const double least = exp2(-100.0 / order);
-    if (m > 0.0)
-      for (int64_t i = begin + threadIdx.x; i < end; i += kThreads) {
-        const double x = diff[i] / m;
-        if (!(x < least)) s += pow(x, order);
-      }
-    __syncthreads();                                         // group_sum_max's buffers once more
-  }
+    return number;
+  };
+  double s = 0.0, m = 0.0;
+  int held = each(0, [&](int number, double d) {
+    m = fmax(m, d);
+    if (number < kKeptDifferences) kept[number][threadIdx.x] = d;
+  });
   group_sum_max(s, m);
+  if (threadIdx.x == 0) top = m;
+  __syncthreads();
+  m = top;
+  s = 0.0;
+  const double cut = fmax(chosen ? chosen->threshold : 0.0, least * m);
+  const auto add = [&](double d) {
+    if (d != d) s += d;
+    else if (m > 0.0 && !(d < cut)) {
+      const double x = d / m;
+      if (!(x < least)) s += pow(x, order);
+    }
+  };
+  for (int k = 0; k < held && k < kKeptDifferences; ++k) add(kept[k][threadIdx.x]);
+  if (held > kKeptDifferences) each(kKeptDifferences, [&](int, double d) { add(d); });
+  double none = 0.0;
+  group_sum_max(s, none);
   if (threadIdx.x == 0) {
     partials[2 * blockIdx.x] = s;
-    if (kStage == 0) partials[2 * blockIdx.x + 1] = m;
+    partials[2 * blockIdx.x + 1] = m;
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_distance_final(const double* __restrict__ sums, const double* __restrict__ maxima,
-                                                             int groups, double n, double order, double* __restrict__ out) {
+__global__ __launch_bounds__(kThreads) void k_distance_final(const double* __restrict__ partials, int groups, double n, double order,
+                                                             double* __restrict__ out) {
+  __shared__ double top;
   double s = 0.0, m = 0.0;
-  for (int g = threadIdx.x; g < groups; g += kThreads) {
-    s += sums[2 * g];
-    m = fmax(m, maxima[2 * g + 1]);
-  }
+  for (int g = threadIdx.x; g < groups; g += kThreads) m = fmax(m, partials[2 * g + 1]);
   group_sum_max(s, m);
+  if (threadIdx.x == 0) top = m;
+  __syncthreads();
+  m = top;
+  s = 0.0;
+  for (int g = threadIdx.x; g < groups; g += kThreads) {     // the workgroups' sums are relative to their own maxima
+    const double part = partials[2 * g], x = partials[2 * g + 1] / m;
+    s += part != 0.0 && x < 1.0 ? part * pow(x, order) : part;
+  }
+  double none = 0.0;
+  group_sum_max(s, none);
   if (threadIdx.x == 0) out[0] = m > 0.0 ? m * pow(s / n, 1.0 / order) : 0.0;
 }
 
@@ -1068,31 +1451,44 @@ int launch_approximate_wasserstein(const pbz_codec* c, int64_t n, const void* N1
   const int64_t chunk = ((n + kStatGroups - 1) / kStatGroups + kThreads - 1) / kThreads * kThreads;
   const int groups = int((n + chunk - 1) / chunk);
   const double scale = 1.0 / (c->r * std::sqrt(double(c->vol)));
+  const double least = std::exp2(-100.0 / order);
   const int K = plan.buckets;
-  hipLaunchKernelGGL(k_means, dim3(groups, 2), dim3(kThreads), 0, s, N1, F1, N2, F2, int(c->ftype), int(c->itype), scale, n,
-                     chunk, c->kept, w.buf0, w.partials);
-  int sample_shift = 0;
-  while ((1 << sample_shift) < 4 * K && (1 << sample_shift) < kMaxSamples) ++sample_shift;
-  constexpr int kPerGroup = kRankThreads / kRankLanes;
-  const int rank_groups = K > 1 ? ((1 << sample_shift) + kPerGroup - 1) / kPerGroup : 0;
-  hipLaunchKernelGGL(k_splitters, dim3(rank_groups + 1, 2), dim3(kRankThreads), 0, s, w.buf0, n, K, w.splitters, sample_shift,
-                     w.partials, groups, w.params, w.rest);
-  const size_t pass_bytes = size_t(K) * 16;
+  const int nt = int(c->ftype), it = int(c->itype);
+  const bool select = plan.sample && K >= kSelectMin;
   const dim3 pass_grid(unsigned((plan.tiles + 7) / 8 * 8), 2);
-  hipLaunchKernelGGL(k_buckets<0>, pass_grid, dim3(kPassThreads), pass_bytes, s, w.buf0, w.buf1, n, plan.tile_keys, plan.tiles, K,
-                     w.splitters, w.hist, w.sums, w.params, w.partials);
+  const size_t pass_bytes = size_t(K) * 16;
+  if (K > 1) {
+    int sample_shift = 0;
+    while ((1 << sample_shift) < 4 * K && (1 << sample_shift) < kMaxSamples) ++sample_shift;
+    constexpr int kPerGroup = kRankThreads / kRankLanes;
+    static_assert(kBucketCap >= kMaxSamples, "the samples of both operands fit the keys' place");
+    hipLaunchKernelGGL(k_samples, dim3(((1 << sample_shift) + 63) / 64, 2), dim3(64), 0, s, N1, F1, N2, F2, nt, it, scale, c->kept, n,
+                       sample_shift, w.buf1);
+    hipLaunchKernelGGL(k_splitters, dim3(((1 << sample_shift) + kPerGroup - 1) / kPerGroup, 2), dim3(kRankThreads), 0, s, w.buf1, K,
+                       w.splitters, sample_shift);
+    hipLaunchKernelGGL(k_means<true>, pass_grid, dim3(kPassThreads), pass_bytes, s, N1, F1, N2, F2, nt, it, scale, n, plan.tile_keys,
+                       plan.tiles, c->kept, K, w.splitters, w.buf0, w.hist, w.rest, w.partials);
+  } else {
+    hipLaunchKernelGGL(k_means<false>, pass_grid, dim3(kPassThreads), 0, s, N1, F1, N2, F2, nt, it, scale, n, plan.tile_keys,
+                       plan.tiles, c->kept, K, w.splitters, w.buf0, w.hist, w.rest, w.partials);
+  }
   const int scan_groups = K > 1 ? (2 * K + 63) / 64 : 0;
   hipLaunchKernelGGL(k_bucket_scan, dim3(scan_groups + 1, 2), dim3(64 * kScanWaves), 0, s, w.hist, plan.tiles, 2 * K, w.sums,
                      w.partials, w.params);
   int st = hip_status(hipGetLastError());
   if (st != PBZ_OK) return st;
   if (plan.sample) {
+    if (select) {
+      static_assert(2 * (kSampleSortMax / kBucketKeys) <= 4 * kSelectThreads, "four buckets a thread are all");
+      const auto k = 2 * K <= kSelectThreads ? k_select<1> : (2 * K <= 2 * kSelectThreads ? k_select<2> : k_select<4>);
+      hipLaunchKernelGGL(k, dim3(1), dim3(kSelectThreads), 0, s, n, K, w.splitters, w.sums, w.params, least, w.gap, w.needed, w.ranks);
+    }
     if (K > 1)
-      hipLaunchKernelGGL(k_buckets<1>, pass_grid, dim3(kPassThreads), pass_bytes, s, w.buf0, w.buf1, n, plan.tile_keys,
-                         plan.tiles, K, w.splitters, w.hist, w.sums, w.params, w.partials);
+      hipLaunchKernelGGL(k_scatter, pass_grid, dim3(kPassThreads), pass_bytes, s, w.buf0, w.buf1, n, plan.tile_keys, plan.tiles, K,
+                         w.splitters, w.hist, w.sums, select ? w.gap : nullptr);
     const uint64_t* grouped = K > 1 ? w.buf1 : w.buf0;
     hipLaunchKernelGGL(k_bucket_sort, dim3(K, 2), dim3(kBucketThreads), 0, s, grouped, w.buf0, n, K, w.sums, w.rest,
-                       w.pieces);
+                       w.pieces, select ? w.needed : nullptr);
     hipLaunchKernelGGL(k_bucket_sort_rest, dim3(2 * K < kRestGroups ? 2 * K : kRestGroups), dim3(kBucketThreads), 0, s, grouped,
                        w.buf0, n, K, w.sums, w.rest, w.pieces);
   } else {
@@ -1112,14 +1508,9 @@ int launch_approximate_wasserstein(const pbz_codec* c, int64_t n, const void* N1
   }
   st = hip_status(hipGetLastError());
   if (st != PBZ_OK) return st;
-  // the maxima in the first operand's partials, the sums of powers in the second's
-  double* diff = reinterpret_cast<double*>(w.buf1);
-  double* sums = w.partials + 2 * kStatGroups;
-  hipLaunchKernelGGL(k_distance<0>, dim3(groups), dim3(kThreads), 0, s, w.buf0, diff, n, chunk, w.params, order, w.partials,
-                     w.partials);
-  hipLaunchKernelGGL(k_distance<1>, dim3(groups), dim3(kThreads), 0, s, w.buf0, diff, n, chunk, w.params, order, w.partials,
-                     sums);
-  hipLaunchKernelGGL(k_distance_final, dim3(1), dim3(kThreads), 0, s, sums, w.partials, groups, double(n), order, out);
+  hipLaunchKernelGGL(k_distance, dim3(groups), dim3(kThreads), 0, s, w.buf0, n, chunk, w.params, order, least,
+                     select ? reinterpret_cast<const Selection*>(w.gap + 2) : nullptr, w.ranks, w.partials);
+  hipLaunchKernelGGL(k_distance_final, dim3(1), dim3(kThreads), 0, s, w.partials, groups, double(n), order, out);
   return hip_status(hipGetLastError());
 }
 

@@ -127,3 +127,54 @@ def test_block_means_come_out_in_order(n, values):
         assert np.isnan(value).sum() == np.isnan(mean).sum()
         want = np.sort(keys(mean[~np.isnan(mean)]))
         assert np.array_equal(have[~np.isnan(value)], want)
+
+
+def near(g, n):
+    """Two sequences as close as two roundings of one: every bucket matters."""
+    v = g.standard_normal(n)
+    return v, v * (1.0 + 1e-7 * g.standard_normal(n))
+
+
+def tails(g, n):
+    """Equal but for a few of the largest, the smallest, or values in the middle: nearly all buckets can be left out, at either end or at both."""
+    v = g.standard_normal(n)
+    w = v + np.where(g.random(n) < 20.0 / n, 2.0, 0.0) - np.where(g.random(n) < 20.0 / n, 3.0, 0.0)
+    return v, w
+
+
+def sums_to_one(g, n):
+    """No softmax: the means are the probabilities, zeros and equal ones among them."""
+    a, b = g.exponential(1.0, n) ** 3, np.where(g.random(n) < 0.3, 0.0, g.exponential(1.0, n) ** 3)
+    b[g.random(n) < 0.1] = b.max()
+    return a / a.sum(), b / b.sum()
+
+
+def few_against_many(g, n):
+    """One operand of three values, the other of as many as there are blocks: its buckets meet one of the other's."""
+    return g.integers(0, 3, n).astype(np.float64), g.standard_normal(n)
+
+
+@pytest.mark.parametrize("values", [near, tails, sums_to_one, few_against_many], ids=lambda f: f.__name__)
+@pytest.mark.parametrize("n", [65535, 65537, 131073, (1 << 21) + 1])
+def test_distance_where_buckets_are_left_out(n, values):
+    """The sizes from which buckets that cannot matter are neither scattered nor sorted, and at which more of them come to a thread."""
+    g = np.random.Generator(np.random.PCG64(n))
+    codec = Codec((2,), "f64", "i8", np.array([True, False]))
+    factor = np.sqrt(2.0) if values is sums_to_one else 1.0        # a mean is N F0 / (r sqrt(2))
+    ops, oc = [], []
+    for v in values(g, n):
+        v = v * factor
+        N, F = torch.from_numpy(np.abs(v)).cuda(), torch.from_numpy(np.where(v < 0, -127, 127).astype(np.int8).reshape(n, 1)).cuda()
+        ops.append((N, F))
+        oc.append(oracle_compressed(N, F, (2 * n,), (2,), 8, "f64", np.array([True, False]), "dct"))
+    for p in (2.0, 68.0, 80.0):
+        got = float(codec.approximate_wasserstein(*ops[0], *ops[1], p).item())
+        want = po.approximate_wasserstein(oc[0], oc[1], p)
+        # 1e-9 as above; differences of nearly equal probabilities are off by the rounding of these, too: 2^-51 of the largest, which is
+        # exp(largest of n normal numbers) / (n exp(1/2)), below exp(5) / (1.6 n) = 90 / n
+        assert abs(got - want) <= 1e-9 * abs(want) + (90.0 * 2.0 ** -51 / n if values is near else 1e-300), (n, p, got, want)
+    # NaN in an operand whose means are the probabilities comes through, wherever it is in the order
+    if values is sums_to_one:
+        for where in (0, n // 2):
+            ops[0][0][where] = float("nan")
+            assert np.isnan(codec.approximate_wasserstein(*ops[0], *ops[1], 68.0).item())
