@@ -553,11 +553,11 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_blockwise_staged(Stage st, c
     StagedN<kNType> n1, n2;
     n1.request(N1, k0, count);
     if (kTwo) n2.request(N2, k0, count);
-    stage_span<2>(F1, a_end, F1 + at, count * st.bpb, sa);
-    if (kTwo) stage_span<2>(F2, b_end, F2 + at, count * st.bpb, sb);
+    request_span(F1, a_end, F1 + at, count * st.bpb, sa);
+    if (kTwo) request_span(F2, b_end, F2 + at, count * st.bpb, sb);
     n1.put(na, count, n_f16 != 0);
     if (kTwo) n2.put(nb, count, n_f16 != 0);
-    wave_lds_sync();
+    span_arrived();
     const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : pa;
     for (int b0 = 0; b0 < count; b0 += per_round) {
       const int b = b0 + slot;
@@ -581,7 +581,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_blockwise_staged(Stage st, c
   }
 }
 
-// the five sums of a reduction (see pbz_ops_common.h); grid y = segment of n_blocks blocks
+// the five sums of a reduction (see pbz_ops_common.h); grid y = segment of n_blocks blocks.  The spans go to LDS past the registers: 2M blocks of
+// 19 int16 indices, variance 27 -> 23 us, covariance 50 -> 41 (through registers; 35 and 61 with lanes that took every team's
+// dword); the block-wise covariance 40 -> 35 (53), which is what HBM gives.
 template <int kIType, int kNType, bool kTwo, bool kDC, bool kDiff>
 __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, const void* __restrict__ N1, const uint8_t* __restrict__ F1,
                                                                   const void* __restrict__ N2, const uint8_t* __restrict__ F2,
@@ -616,11 +618,11 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_reduce_staged(Stage st, cons
       StagedN<kNType> n1, n2;
       n1.request(N1, seg0 + k0, count);
       if (kTwo) n2.request(N2, seg0 + k0, count);
-      stage_span<2>(F1, a_end, F1 + at, count * st.bpb, sa);
-      if (kTwo) stage_span<2>(F2, b_end, F2 + at, count * st.bpb, sb);
+      request_span(F1, a_end, F1 + at, count * st.bpb, sa);
+      if (kTwo) request_span(F2, b_end, F2 + at, count * st.bpb, sb);
       n1.put(na, count, f16);
       if (kTwo) n2.put(nb, count, f16);
-      wave_lds_sync();
+      span_arrived();
       const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : pa;
       for (int b = slot; b < count; b += per_round) {
         const double v1 = na[b], v2 = nb[b];
@@ -823,7 +825,11 @@ int launch_reduce_staged(const pbz_codec* c, bool two, bool dc, bool diff, int64
   const Stage st = make_stage(c->kept, itype_bytes(c->itype), n_blocks, kReduceSpan, few ? kMaxWaves : kMinWaves / n_segments);
   size_t lds;
   const int waves = waves_for(st, two ? 2 : 1, two ? 2 : 1, &lds);
-  unsigned g = group_count(n_blocks, st, waves, max_groups);
+  // Four workgroups per compute unit for all segments together: what a workgroup does once, its sums over 64 lanes above all, is
+  // spread over as many tiles as can be (16 segments of 18750 blocks of 33 int32 indices: variance 20 -> 16 us, covariance 33 -> 24; eight
+  // per compute unit 18 and 27, two 20 and 28).
+  const int per_segment = kReduceGroupsOneSegment / n_segments < 1 ? 1 : kReduceGroupsOneSegment / n_segments;
+  unsigned g = group_count(n_blocks, st, waves, max_groups < per_segment ? max_groups : per_segment);
   if (g <= 2 || few) g = 1;                // two tiles per wave: cheaper than a second launch
   *groups = int(g);
   const dim3 grid(g, unsigned(n_segments)), block(64 * waves);
