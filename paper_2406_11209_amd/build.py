@@ -8,6 +8,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -15,6 +16,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libpbz.so")
 EXAMPLE = os.path.join(PKG, "c_abi_roundtrip")
+BINDING = os.path.join(PKG, "_binding.so")
 PATTERNS = os.path.join(PKG, "memory_patterns")
 SOURCES = ["pbz_api.hip", "pbz_generic.hip", "pbz_ops.hip", "pbz_ops_staged.hip", "pbz_ops_direct.hip", "pbz_fast.hip", "pbz_fast_lane.hip", "pbz_fast_quad16.hip",
            "pbz_fast_oct8.hip", "pbz_fast_cube16.hip", "pbz_wasserstein.hip", "pbz_tiled.hip", "pbz_brick.hip", "pbz_brick_lines.hip", "pbz_brick_small.hip",
@@ -57,6 +59,10 @@ def build(verbose: bool = False) -> str:
     tmp = LIB + ".tmp"
     _run([cc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", tmp])
     os.replace(tmp, LIB)
+    # the Python binding's calls (plain C, nothing linked but what the interpreter brings)
+    _run(["gcc", "-O2", "-std=c11", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "pbz_binding.c"), "-o", BINDING + ".tmp"])
+    os.replace(BINDING + ".tmp", BINDING)
     # the C ABI used from plain C (no Python, no torch): a small round-trip program next to the library
     _run([cc, "-x", "c", os.path.join(PKG, "examples", "c_abi_roundtrip.c"), "-D__HIP_PLATFORM_AMD__",
           "-I" + os.path.join(ROOT, "include"), "-I/opt/rocm/include", "-L" + PKG, "-lpbz", "-L/opt/rocm/lib",
