@@ -352,7 +352,9 @@ __global__ __launch_bounds__(kFinalThreads) void k_reduce_final(ReduceTail t, in
   const double grand = group_total(acc, lds, kFinalThreads / 64);
   if (threadIdx.x < kNumSums) fin[threadIdx.x] = grand;
   __syncthreads();
-  if (threadIdx.x == 0) write_statistic(fin, t, blockIdx.x, K1, K2);
+  // (the first wave's: the pilot values are thread 0's)
+  if (threadIdx.x < kMaxStatistics)
+    write_statistic(fin, t, blockIdx.x, __shfl(K1, 0, 64), __shfl(K2, 0, 64), threadIdx.x);
 }
 
 // per-tile records {S, D, K, count} left by a compress kernel (first coefficients shifted by the tile's own pilot

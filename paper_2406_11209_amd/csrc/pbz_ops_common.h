@@ -252,7 +252,8 @@ __device__ __forceinline__ double finish_statistic(const double* s, const Reduce
       const double lum = (2.0 * mu_a * mu_b + t.s_l) / (mu_a * mu_a + mu_b * mu_b + t.s_l);
       const double con = (2.0 * sd + t.s_c) / (var_a + var_b + t.s_c);
       const double str = (cov + 0.5 * t.s_c) / (sd + 0.5 * t.s_c);
-      return pow(lum, t.w_l) * pow(con, t.w_c) * pow(str, t.w_s);
+      // weights of one, the usual ones, leave what pow(x, 1) is: x
+      return (t.w_l == 1.0 ? lum : pow(lum, t.w_l)) * (t.w_c == 1.0 ? con : pow(con, t.w_c)) * (t.w_s == 1.0 ? str : pow(str, t.w_s));
     }
     default: return 0.0;
   }
@@ -273,28 +274,26 @@ __device__ __forceinline__ double group_total(const double* sums, double (*lds)[
   return t;
 }
 
-// the requested statistic(s) of segment `segment` from its five sums
+// The requested statistic(s) of segment `segment` from its five sums, `thread` of the first kMaxStatistics threads of a workgroup the
+// thread-th one: each is a chain of divisions and roots, nine of which by one thread took 3 us.
+constexpr int kMaxStatistics = 9;
 __device__ __forceinline__ void write_statistic(const double* fin, const ReduceTail& t, int64_t segment, double K1,
-                                                double K2) {
+                                                double K2, int thread) {
+  ReduceTail one = t;
   if (t.op == kStatistics) {            // mean, variance and norm2 of one array from the same two sums
-    ReduceTail one = t;
-    const int ops[3] = {kMean, kVariance, kNorm2};
-    for (int i = 0; i < 3; ++i) {
-      one.op = ops[i];
-      t.out[segment * 3 + i] = finish_statistic(fin, one, K1, K2);
-    }
+    if (thread >= 3) return;
+    one.op = thread == 0 ? kMean : (thread == 1 ? kVariance : kNorm2);
+    t.out[segment * 3 + thread] = finish_statistic(fin, one, K1, K2);
   } else if (t.op == kPairStatistics) { // every statistic of a pair of arrays from the five sums of one pass
-    ReduceTail one = t;
-    const double swapped[kNumSums] = {fin[kS12], fin[kS22], fin[kS11], fin[kD2], fin[kD1]};   // the operands exchanged
-    const int both[3] = {kDot, kCosine, kCovariance}, each[3] = {kMean, kVariance, kNorm2};
-    for (int i = 0; i < 3; ++i) {
-      one.op = both[i];
-      t.out[segment * 9 + i] = finish_statistic(fin, one, K1, K2);
-      one.op = each[i];
-      t.out[segment * 9 + 3 + 2 * i] = finish_statistic(fin, one, K1, K2);
-      t.out[segment * 9 + 4 + 2 * i] = finish_statistic(swapped, one, K2, K1);
-    }
-  } else {
+    if (thread >= 9) return;
+    const int which = (thread - 3) >> 1;
+    const bool second = thread >= 3 && ((thread - 3) & 1);          // of the second array: the operands exchanged
+    if (thread < 3) one.op = thread == 0 ? kDot : (thread == 1 ? kCosine : kCovariance);
+    else one.op = which == 0 ? kMean : (which == 1 ? kVariance : kNorm2);
+    const double of[kNumSums] = {fin[kS12], second ? fin[kS22] : fin[kS11], second ? fin[kS11] : fin[kS22],
+                                 second ? fin[kD2] : fin[kD1], second ? fin[kD1] : fin[kD2]};
+    t.out[segment * 9 + thread] = finish_statistic(of, one, second ? K2 : K1, second ? K1 : K2);
+  } else if (thread == 0) {
     t.out[segment] = finish_statistic(fin, t, K1, K2);
   }
 }
@@ -316,7 +315,7 @@ __device__ __forceinline__ void reduce_tail(double* sums, const ReduceTail& t, d
   if (gridDim.x == 1) {
     if (threadIdx.x < kNumSums) fin[threadIdx.x] = total;
     __syncthreads();
-    if (threadIdx.x == 0) write_statistic(fin, t, blockIdx.y, K1, K2);
+    if (threadIdx.x < kMaxStatistics) write_statistic(fin, t, blockIdx.y, K1, K2, threadIdx.x);
     return;
   }
   double* record = t.partials + (int64_t(blockIdx.y) * gridDim.x + blockIdx.x) * kReducePartialSlots;

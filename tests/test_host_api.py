@@ -431,3 +431,23 @@ def test_kernels_for_any_mask_and_per_block_shape_take_their_rows():
             want = SHAPE if shapes.taken(block, ftype, bits) else DENSE
             shape = tuple(3 * b + 1 for b in block)
             assert route(c, "compress", shape, dtype) == route(c, "decompress", shape, dtype) == want, (block, dtype, ftype, bits)
+
+
+def test_native_calls_refuse_what_the_device_could_not_read():
+    """Tensors in host memory, no tensors at all and wrong counts end in Python errors before an entry point is called."""
+    torch = pytest.importorskip("torch")
+    codec = Codec((8, 8), "f32", "i8")
+    N, F, x = torch.zeros(4), torch.zeros(4, 64, dtype=torch.int8), torch.zeros(16, 16)
+    one = torch.zeros(1, dtype=torch.float64)
+    for call in (lambda: codec.negate(F, F), lambda: codec.add(N, F, N, F, N, F), lambda: codec.mul_scalar(N, F, 2.0, N, F),
+                 lambda: codec.mean(N, F, one), lambda: codec.dot(N, F, N, F, one), lambda: codec.compress(x, N, F),
+                 lambda: codec.decompress(N, F, (16, 16), out=x), lambda: codec.blockwise_mean(N, F, torch.zeros(4, dtype=torch.float64)),
+                 lambda: codec.segmented("variance", 2, 2, N, F, out=torch.zeros(2, dtype=torch.float64))):
+        with pytest.raises(ValueError, match="contiguous device tensors"):
+            call()
+    with pytest.raises(AttributeError):
+        codec.negate(None, F)
+    from paper_2406_11209_amd import _binding
+    for name in ("blocks", "reduce", "scalar", "compress", "decompress", "segmented"):
+        with pytest.raises(TypeError):
+            getattr(_binding, name)(1, 2)
