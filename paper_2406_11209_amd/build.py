@@ -19,7 +19,7 @@ EXAMPLE = os.path.join(PKG, "c_abi_roundtrip")
 BINDING = os.path.join(PKG, "_binding.so")
 PATTERNS = os.path.join(PKG, "memory_patterns")
 SOURCES = ["pbz_api.hip", "pbz_generic.hip", "pbz_ops.hip", "pbz_ops_staged.hip", "pbz_ops_direct.hip", "pbz_fast.hip", "pbz_fast_lane.hip", "pbz_fast_quad16.hip",
-           "pbz_fast_oct8.hip", "pbz_fast_cube16.hip", "pbz_wasserstein.hip", "pbz_tiled.hip", "pbz_brick.hip", "pbz_brick_lines.hip", "pbz_brick_small.hip",
+           "pbz_fast_oct8.hip", "pbz_fast_cube16.hip", "pbz_wasserstein.hip", "pbz_tiled.hip", "pbz_lines.hip", "pbz_brick.hip", "pbz_brick_lines.hip", "pbz_brick_small.hip",
            "pbz_brick_flat.hip", "pbz_brick_wide.hip", "pbz_brick_planes.hip", "pbz_brick_cubes.hip", "pbz_brick_tesseracts.hip",
            "pbz_brick_long_tesseracts.hip", "pbz_static.hip", "pbz_copy.hip"]
 

@@ -285,6 +285,7 @@ int pbz_compress(const pbz_codec* c, const void* x, pbz_ftype x_type, const int6
     int r = try_compress_masked(c, g, t->places, x, x_type, N, F, s, false);
     if (r == 0) r = try_compress_brick(c, g, t, x, x_type, N, F, s, false);
     if (r != 0) return r < 0 ? r : PBZ_OK;
+    if (line_kernels_cover(c)) return launch_compress_lines(c, g, t, x, x_type, N, F, s);
   }
   if (tiled_kernels_cover(c)) return launch_compress_tiled(c, g, t, x, x_type, N, F, s);
   return launch_compress_generic(c, g, t, x, x_type, N, F, s);
@@ -356,6 +357,7 @@ int pbz_decompress(const pbz_codec* c, const void* N, const void* F, const int64
     int r = try_decompress_masked(c, g, t->places, N, F, y, y_type, s, false);
     if (r == 0) r = try_decompress_brick(c, g, t, N, F, y, y_type, s, false);
     if (r != 0) return r < 0 ? r : PBZ_OK;
+    if (line_kernels_cover(c)) return launch_decompress_lines(c, g, t, N, F, y, y_type, s);
   }
   if (tiled_kernels_cover(c)) return launch_decompress_tiled(c, g, t, N, F, y, y_type, s);
   return launch_decompress_generic(c, g, t, N, F, y, y_type, s);

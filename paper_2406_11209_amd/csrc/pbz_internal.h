@@ -93,6 +93,13 @@ int launch_compress_generic(const pbz_codec* c, const Geom& g, const DeviceTable
 int launch_decompress_generic(const pbz_codec* c, const Geom& g, const DeviceTables* t, const void* N,
                               const void* F, void* y, int ytype, hipStream_t s);
 
+// lines of 64 elements in FP64 work, on the matrix cores (pbz_lines.hip)
+bool line_kernels_cover(const pbz_codec* c);
+int launch_compress_lines(const pbz_codec* c, const Geom& g, const DeviceTables* t, const void* x, int xtype, void* N, void* F,
+                          hipStream_t s);
+int launch_decompress_lines(const pbz_codec* c, const Geom& g, const DeviceTables* t, const void* N, const void* F, void* y,
+                            int ytype, hipStream_t s);
+
 // specialised codec kernels; return 1 when they handled the call, 0 when the shape / types are not
 // covered (caller falls back to the generic kernels), negative on a HIP error
 // tile_sums != nullptr: the kernel also leaves two FP64 sums per tile (wave) there, fast_compress_tiles() pairs
