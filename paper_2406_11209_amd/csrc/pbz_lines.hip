@@ -3,14 +3,14 @@
 // v_mfma_f64_16x16x4, a wave per 16 blocks, 64 of them for 1024 elements.
 //
 // What bounds them: the matrix instructions (64 cycles each: 7 us for 4 Mi elements, 33 for 20 Mi) and HBM in turn.  4 Mi FP64 elements, int8: compress
-// 173 -> 24 us, decompress 512 -> 26; 20 Mi 85 and 94; 16384 elements 36 -> 9 (the dense kernels of pbz_generic.hip, which took these calls, loop
+// 173 -> 19 us, decompress 512 -> 26; 16 Mi 65 and 82; 16384 elements 36 -> 9 (the dense kernels of pbz_generic.hip, which took these calls, loop
 // over LDS element by element).  A fast transform would need a third of the operations, but its error is larger than the dense
 // sums'.  These have the error they had, 1.4e-16 of N: with the elements in another order, one share of sixteen after the other, it was
 // 2.4e-16, and no less in two, four or eight partial sums.
 // A step of the sums takes elements 4 s .. 4 s + 3 of a block, one by each quarter of the wave.  A lane loads sixteen consecutive elements, 16
 // bytes at a time, and the quarters then trade them in registers: the sums are in the order of the elements, as they were.  The
-// matrix stands in LDS with the halves of its odd rows' 256-byte runs exchanged, so that the four rows of a step use all banks.  F leaves and
-// comes through LDS spans like the other kernels', at any kept count and alignment.
+// matrix stands in LDS so that a step's numbers use all banks.  F leaves and comes through LDS spans like the other kernels', at any kept
+// count and alignment.
 #include "pbz_fast_common.h"
 #include "pbz_span.h"
 
@@ -21,14 +21,14 @@ using fast::Binner;
 using fast::bf16_t;
 using fast::f16_t;
 
-constexpr int kLine = 64, kTileBlocks = 16, kWaves = 4;
-constexpr int kSpanBytes = 16 + kTileBlocks * kLine * 4 + 16;            // a tile's F at any phase
+constexpr int kLine = 64, kTileBlocks = 16, kMaxWaves = 8;
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 struct Lines {
   int64_t X, gx, n_blocks, tiles;      // elements and blocks of a row; of all rows together
   double r;
   int kept, ntype, itype, index_bytes;
+  int span;                            // bytes of LDS for a tile's F at any phase
 };
 
 // where block k starts, and how many elements its row has from there on
@@ -63,10 +63,20 @@ __device__ __forceinline__ void load_share(const XT* p, int64_t inside, double* 
   }
 }
 
-// the table's number (row, column), see above
-__device__ __forceinline__ int table_slot(int row, int column) { return row * kLine + (column ^ ((row & 1) << 4)); }
+// Where H[m][q] stands in the table.  A step of the forward transform reads sixteen q of four m, one of the inverse four q of sixteen m: both are
+// spread over all banks.
+template <bool kForward>
+__device__ __forceinline__ int table_slot(int m, int q) {
+  if (kForward) return m * kLine + (q ^ ((m & 1) << 4));
+  return m * kLine + (((q >> 2) ^ (m & 15)) << 2 | (q & 3));
+}
+template <bool kForward>
+__device__ __forceinline__ void fill_table(double* table, const double* __restrict__ H) {
+  for (int e = threadIdx.x; e < kLine * kLine; e += blockDim.x) table[table_slot<kForward>(e >> 6, e & 63)] = H[e];
+}
 
-// acc[t]: columns 16 t .. of the product of the lanes' numbers (4 s + lane / 16 of block lane % 16) with the table
+// acc[t]: columns 16 t .. of the product of the lanes' numbers (4 s + lane / 16 of block lane % 16) with H or its transpose
+template <bool kForward>
 __device__ __forceinline__ void multiply(const double* a, const double* table, int lane, f64x4* acc) {
   const int row = lane >> 4, column = lane & 15;
 #pragma unroll
@@ -74,8 +84,10 @@ __device__ __forceinline__ void multiply(const double* a, const double* table, i
 #pragma unroll
   for (int s = 0; s < 16; ++s)
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-      acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], table[table_slot(4 * s + row, 16 * t + column)], acc[t], 0, 0, 0);
+    for (int t = 0; t < 4; ++t) {
+      const int k = 4 * s + row, j = 16 * t + column;
+      acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], table[kForward ? table_slot<true>(k, j) : table_slot<false>(j, k)], acc[t], 0, 0, 0);
+    }
 }
 
 // The lanes' shares (16 g + e of the block, g = lane / 16) become their numbers (4 s + g): the four quarters of the wave trade them
@@ -106,22 +118,23 @@ __device__ __forceinline__ void put(uint8_t* at, int bytes, int64_t v) {
   else *reinterpret_cast<uint32_t*>(at) = uint32_t(v);
 }
 
-__global__ __launch_bounds__(64 * kWaves) void k_compress_lines(Lines g, const void* __restrict__ x, int xtype,
+__global__ __launch_bounds__(64 * kMaxWaves) void k_compress_lines(Lines g, const void* __restrict__ x, int xtype,
                                                                 void* __restrict__ N, uint8_t* __restrict__ F,
                                                                 const double* __restrict__ H,
                                                                 const uint16_t* __restrict__ places) {
-  __shared__ double table[kLine * kLine];                                // H[m][q]
-  __shared__ __align__(16) uint8_t spans[kWaves][kSpanBytes];
+  __shared__ double table[kLine * kLine];
+  extern __shared__ __align__(16) uint8_t spans[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i = lane & 15, share = lane >> 4;
-  uint8_t* span = spans[wave];
-  for (int e = threadIdx.x; e < kLine * kLine; e += 64 * kWaves) table[table_slot(e >> 6, e & 63)] = H[e];
+  const int waves = blockDim.x >> 6;
+  uint8_t* span = spans + wave * g.span;
+  fill_table<true>(table, H);
   int place[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) place[t] = places[16 * t + i] == kPruned ? -1 : int(places[16 * t + i]) * g.index_bytes;
   __syncthreads();
   const int bytes = g.kept * g.index_bytes;
-  for (int64_t tile = int64_t(blockIdx.x) * kWaves + wave; tile < g.tiles; tile += int64_t(gridDim.x) * kWaves) {
+  for (int64_t tile = int64_t(blockIdx.x) * waves + wave; tile < g.tiles; tile += int64_t(gridDim.x) * waves) {
     const int64_t first = tile * kTileBlocks;
     const int count = g.n_blocks - first < kTileBlocks ? int(g.n_blocks - first) : kTileBlocks;
     double a[16];
@@ -138,7 +151,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_compress_lines(Lines g, const v
     }
     shares_to_numbers(a);
     f64x4 c[4];
-    multiply(a, table, lane, c);
+    multiply<true>(a, table, lane, c);
     // the lane has column 16 t + i of blocks 4 v + share
     const int phase = phase_of(F + first * bytes);
 #pragma unroll
@@ -166,23 +179,24 @@ __global__ __launch_bounds__(64 * kWaves) void k_compress_lines(Lines g, const v
   }
 }
 
-__global__ __launch_bounds__(64 * kWaves) void k_decompress_lines(Lines g, const void* __restrict__ N,
+__global__ __launch_bounds__(64 * kMaxWaves) void k_decompress_lines(Lines g, const void* __restrict__ N,
                                                                   const uint8_t* __restrict__ F, void* __restrict__ y, int ytype,
                                                                   const double* __restrict__ H,
                                                                   const uint16_t* __restrict__ places) {
-  __shared__ double table[kLine * kLine];                                // H[m][q] in row q
-  __shared__ __align__(16) uint8_t spans[kWaves][kSpanBytes];
+  __shared__ double table[kLine * kLine];
+  extern __shared__ __align__(16) uint8_t spans[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i = lane & 15, share = lane >> 4;
-  uint8_t* span = spans[wave];
-  for (int e = threadIdx.x; e < kLine * kLine; e += 64 * kWaves) table[table_slot(e & 63, e >> 6)] = H[e];
+  const int waves = blockDim.x >> 6;
+  uint8_t* span = spans + wave * g.span;
+  fill_table<false>(table, H);
   uint32_t place[16];                                                    // of the lane's sixteen entries
 #pragma unroll
   for (int k = 0; k < 16; ++k) place[k] = places[4 * k + share];
   __syncthreads();
   const int bytes = g.kept * g.index_bytes;
   const uint8_t* end = F + g.n_blocks * bytes;
-  for (int64_t tile = int64_t(blockIdx.x) * kWaves + wave; tile < g.tiles; tile += int64_t(gridDim.x) * kWaves) {
+  for (int64_t tile = int64_t(blockIdx.x) * waves + wave; tile < g.tiles; tile += int64_t(gridDim.x) * waves) {
     const int64_t first = tile * kTileBlocks;
     const int count = g.n_blocks - first < kTileBlocks ? int(g.n_blocks - first) : kTileBlocks;
     const int mine = i < count ? i : count - 1;                          // lanes past the end redo the last block and store nothing
@@ -197,7 +211,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_decompress_lines(Lines g, const
     }
     wave_lds_sync();
     f64x4 c[4];
-    multiply(a, table, lane, c);
+    multiply<false>(a, table, lane, c);
     const LinePlace own = place_of(g, first + mine);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -211,9 +225,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_decompress_lines(Lines g, const
   }
 }
 
-// LDS lets three workgroups stand on a compute unit; the matrix is fetched once by each
-dim3 lines_grid(const Lines& g) {
-  const int64_t groups = (g.tiles + kWaves - 1) / kWaves, most = 768;
+// Compressing, eight waves share a table where there are tiles for two workgroups on every compute unit: four waves a SIMD hide each
+// other's loads and quotients behind the matrix instructions (16 Mi FP32 elements, int16: 72 -> 61 us).  With fewer tiles four, which spreads
+// them over more units, and decompressing, which has its quotients before and its stores after (82 us, 85 with eight).
+int lines_waves(const Lines& g, bool compress) { return compress && g.tiles >= 2 * 256 * kMaxWaves ? kMaxWaves : 4; }
+dim3 lines_grid(const Lines& g, int waves) {
+  const int64_t groups = (g.tiles + waves - 1) / waves, most = waves == kMaxWaves ? 512 : 768;      // what LDS lets stand at once
   const int64_t turns = (groups + most - 1) / most;
   return dim3(unsigned((groups + turns - 1) / turns));
 }
@@ -229,6 +246,7 @@ Lines lines_of(const pbz_codec* c, const Geom& geo) {
   g.ntype = int(c->ftype);
   g.itype = int(c->itype);
   g.index_bytes = itype_bytes(c->itype);
+  g.span = (16 + kTileBlocks * g.kept * g.index_bytes + 16 + 15) / 16 * 16;
   return g;
 }
 
@@ -243,7 +261,8 @@ bool line_kernels_cover(const pbz_codec* c) {
 int launch_compress_lines(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* x, int xtype, void* N, void* F,
                           hipStream_t s) {
   const Lines g = lines_of(c, geo);
-  hipLaunchKernelGGL(k_compress_lines, lines_grid(g), dim3(64 * kWaves), 0, s, g, x, xtype, N, static_cast<uint8_t*>(F),
+  const int waves = lines_waves(g, true);
+  hipLaunchKernelGGL(k_compress_lines, lines_grid(g, waves), dim3(64 * waves), size_t(waves) * g.span, s, g, x, xtype, N, static_cast<uint8_t*>(F),
                      t->H + c->h_offset[c->ndim - 1], t->places);
   return hip_status(hipGetLastError());
 }
@@ -251,7 +270,8 @@ int launch_compress_lines(const pbz_codec* c, const Geom& geo, const DeviceTable
 int launch_decompress_lines(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* N, const void* F, void* y,
                             int ytype, hipStream_t s) {
   const Lines g = lines_of(c, geo);
-  hipLaunchKernelGGL(k_decompress_lines, lines_grid(g), dim3(64 * kWaves), 0, s, g, N, static_cast<const uint8_t*>(F), y, ytype,
+  const int waves = lines_waves(g, false);
+  hipLaunchKernelGGL(k_decompress_lines, lines_grid(g, waves), dim3(64 * waves), size_t(waves) * g.span, s, g, N, static_cast<const uint8_t*>(F), y, ytype,
                      t->H + c->h_offset[c->ndim - 1], t->places);
   return hip_status(hipGetLastError());
 }

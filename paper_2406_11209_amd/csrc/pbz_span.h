@@ -52,6 +52,8 @@ __device__ __forceinline__ void request_span(const uint8_t* lo, const uint8_t* h
   const int pieces = (a + len + 15) >> 4;
   const int first = base < lo ? 1 : 0;
   const int last = base + 16 * int64_t(pieces) > hi ? pieces - 1 : pieces;
+  // what the wave still has to read or write in the region comes first: these writes do not queue with its LDS operations
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   for (int i0 = 0; i0 < last; i0 += 64) {
     const int i = i0 + lane;
     if (i >= first && i < last)
