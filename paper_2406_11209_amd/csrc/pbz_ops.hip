@@ -655,8 +655,8 @@ int launch_add(const pbz_codec* c, int64_t n_blocks, const void* N1, const void*
     }
 #undef PBZ_ADD
   } else {
-    return (direct_blocks(n_blocks, c->kept, bpb, true) ? launch_rebin_direct : launch_rebin_staged)(
-        c, n_blocks, N1, F1, N2, F2, Nout, Fout, sign2, 0.0, s);
+    if (direct_sum(n_blocks, bpb)) return launch_sum_direct(c, n_blocks, N1, F1, N2, F2, Nout, Fout, sign2, s);
+    return launch_rebin_staged(c, n_blocks, N1, F1, N2, F2, Nout, Fout, sign2, 0.0, s);
   }
   return hip_status(hipGetLastError());
 }
@@ -740,7 +740,7 @@ int launch_reduce(const pbz_codec* c, ReduceOp op, int64_t n_blocks, const void*
       else
         launch_reduce_vec<PBZ_I32>(int(c->ftype), two, dc, diff, grid, s, n1, f1, n2, f2, nvec, chunk, shift, vpb, n_blocks, tail);
     } else {
-      const int st = (direct_reduction(n_blocks, c->kept, two, dc) ? launch_reduce_direct : launch_reduce_staged)(
+      const int st = (direct_reduction(n_blocks, c->kept, two) ? launch_reduce_direct : launch_reduce_staged)(
           c, two, dc, diff, n_blocks, batch, max_groups, n1, f1, n2, f2, tail, &groups, s);
       if (st != PBZ_OK) return st;
     }
@@ -826,8 +826,7 @@ int launch_add_scalar(const pbz_codec* c, int64_t n_blocks, const void* Nin, con
     }
 #undef PBZ_ADDS
   } else {
-    return (direct_blocks(n_blocks, c->kept, bpb, false) ? launch_rebin_direct : launch_rebin_staged)(
-        c, n_blocks, Nin, Fin, nullptr, nullptr, Nout, Fout, 1.0, shift, s);
+    return launch_rebin_staged(c, n_blocks, Nin, Fin, nullptr, nullptr, Nout, Fout, 1.0, shift, s);
   }
   return hip_status(hipGetLastError());
 }

@@ -324,34 +324,31 @@ __device__ __forceinline__ void reduce_tail(double* sums, const ReduceTail& t, d
   if (threadIdx.x == kPilot2) record[kPilot2] = K2;
 }
 
-// Whether the sum and the shift of blocks that make no 16-byte vectors go straight from memory, a wave per block, or through LDS.  Few
-// blocks of up to 128 indices: the call is a round trip to memory, and the detour is 0.2-0.8 us more (1000 blocks of 33
-// int8 indices: sum 4.2 us, 5.0 through LDS; 2000: 4.5 and 5.0, but for one to three indices 4.6 and 4.4).  Many blocks
-// of over 8 KiB (11 KiB where there is one operand): LDS holds a wave or two (sum of 4096 int32 indices: 4000 blocks 109 us, 152
-// through LDS; 2500 blocks, which do not fill the chip either way, 107 and 103, of 2500 indices 71 and 55).
-inline bool direct_blocks(int64_t n_blocks, int kept, int64_t block_bytes, bool two) {
-  return n_blocks <= 1024 ? kept <= 128 : n_blocks > 3072 && block_bytes > (two ? 8192 : 11 * 1024);
-}
-// The same of the block-wise statistics.  The covariance has two operands to put into LDS: up to 1024 blocks 0.2-0.7 us more (129 int8
-// indices: 3.8 us, 4.1 through LDS); from one to three words a lane, which 65 to 160 indices of 32 bits are, leave
-// lanes idle (10000 blocks of 129: 6.5 and 8.9); large blocks as above (4000 of 4096: 51 and 58, of 3000: 41 and 38).  The variance gains
-// 0.1-0.3 us on up to 512 blocks of 33 to 128 (64 blocks and fewer of 65: 3.1 and 3.4); its large blocks take twice as long (43 and 28).
+// Whether the sum of blocks that make no 16-byte vectors goes straight from memory, a wave per block, or through LDS (with which the times
+// are compared, as dependent launches of a graph).  Only many blocks of over 14 KiB: three regions leave three waves a compute unit (6000
+// blocks of 3600 32-bit indices 140 us, 158 through LDS; of 3300 130 and 118; 3500 blocks 120 and 98).  One operand's shift
+// never gains more than 2 %, and loses up to six times as much time elsewhere (1000 blocks of 2700: 39 and 14).
+inline bool direct_sum(int64_t n_blocks, int64_t block_bytes) { return n_blocks > 4096 && block_bytes > 14 * 1024; }
+// The same of the block-wise statistics.  The covariance has two operands to put into LDS: up to 1024 blocks of up to 160
+// indices 0.1-0.4 us more (129 int8 indices: 3.0 us, 3.3 through LDS; from there on the two are alike); two to three words a lane, which 65 to
+// 144 indices of 32 bits are, leave lanes idle (5000 blocks of 129: 4.7 and 5.4; 10000: 7.1 and 5.4).  The variance is within
+// 0.1 us either way on up to 512 blocks of 33 to 128.  Large blocks go through LDS (4000 of 4095: covariance 75 us and 33, variance 44 and 16).
 inline bool direct_blockwise(int64_t n_blocks, int kept, int64_t block_bytes, bool two) {
   if (!two) return n_blocks <= 512 && kept >= 33 && kept <= 128;
-  if (block_bytes == 4 * int64_t(kept) && kept > 64 && kept <= 160) return n_blocks <= 16384;
-  return n_blocks <= 1024 ? kept <= 192 : n_blocks > 3072 && block_bytes > 12 * 1024;
+  if (block_bytes == 4 * int64_t(kept) && kept > 64 && kept <= 144) return n_blocks <= 5120;
+  return n_blocks <= 1024 && kept <= 160;
 }
-// The same of the reductions, a thread per block: two operands of one index a block, or up to three where sums with and without the first
-// index are wanted (pair statistics of 1000 to 16384 blocks 8.8 us, 9.6 through LDS; one operand 7.6 either way), except 257
-// to 512 blocks, which LDS lets one workgroup take without a second launch (8.4 and 7.6).
-inline bool direct_reduction(int64_t n_blocks, int kept, bool two, bool dc) {
-  return two && kept <= (dc ? 3 : 1) && (n_blocks <= 256 || (n_blocks > 512 && n_blocks <= 16384));
+// The same of the reductions, a thread per block: two operands of one or two indices a block (1000 to 30000 blocks of one: pair
+// statistics 7.0 us, 7.6 through LDS, dot 5.8 and 6.3; of two 0.2 us less; of three they are alike), except 257 to 512 blocks, which LDS
+// lets one workgroup take without a second launch (dot 5.6 and 4.7).
+inline bool direct_reduction(int64_t n_blocks, int kept, bool two) {
+  return two && kept <= 2 && (n_blocks <= 256 || (n_blocks > 512 && n_blocks <= 32768));
 }
 
 // pbz_ops_direct.hip and pbz_ops_staged.hip: any kept count, any alignment.  F2 == nullptr: addition of `shift` to the first
 // coefficients.
-int launch_rebin_direct(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2,
-                        void* Nout, void* Fout, double sign2, double shift, hipStream_t s);
+int launch_sum_direct(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2, void* Nout,
+                      void* Fout, double sign2, hipStream_t s);
 int launch_blockwise_direct(const pbz_codec* c, int mode, int64_t n_blocks, const void* N1, const void* F1, const void* N2,
                             const void* F2, double* out, double scale, hipStream_t s);
 int launch_reduce_direct(const pbz_codec* c, bool two, bool dc, bool diff, int64_t n_blocks, int n_segments, int max_groups,

@@ -95,7 +95,8 @@ def test_segments_at_every_phase():
 # kept counts and block counts around which a call changes from one kernel to another: element by element or through LDS
 HALVES = [(8, 1, 8, 16385), (8, 3, 16, 16385), (64, 19, 8, 2049), (128, 128, 32, 2049), (128, 100, 32, 16385), (256, 160, 32, 16385),
           (256, 192, 16, 2049), (64, 20, 32, 257), (16, 5, 16, 257), (4096, 2049, 32, 2049), (4096, 4096, 32, 2049), (4096, 4096, 16, 2049),
-          (64, 19, 8, 1025), (256, 192, 16, 1025), (128, 65, 16, 513), (8, 3, 16, 257), (8, 1, 32, 513), (4096, 2500, 32, 3073), (4096, 3000, 32, 3073)]
+          (64, 19, 8, 1025), (256, 192, 16, 1025), (128, 65, 16, 513), (8, 3, 16, 257), (8, 1, 32, 513), (4096, 2500, 32, 3073), (4096, 3000, 32, 3073),
+          (4096, 3601, 32, 4097), (256, 144, 32, 5121), (256, 160, 8, 1025), (8, 2, 16, 32769)]
 
 
 @pytest.mark.parametrize("extent,kept,bits,n", HALVES, ids=["%d_of_%d_i%d_x%d" % (k, e, b, n) for e, k, b, n in HALVES])
@@ -139,7 +140,7 @@ def test_a_call_agrees_with_the_calls_on_its_halves(extent, kept, bits, n):
 # that many; then the largest blocks that a team of 64 lanes holds, and the next
 HELD = ([(8, k, 64 * 4096 + 37) for k in (1, 3, 15, 19, 20, 21, 22, 24, 25)] + [(16, k, 64 * 4096 + 37) for k in (1, 3, 19, 20, 21, 23, 24, 25)] +
         [(32, k, 64 * 4096 + 37) for k in (1, 11, 12, 13)] +
-        [(8, k, 70) for k in (1279, 1280, 1281, 1536, 1537)] + [(16, k, 70) for k in (1280, 1281, 1536, 1537)] + [(32, k, 70) for k in (768, 769)])
+        [(8, k, 70) for k in (1279, 1280, 1281, 1536, 1537)] + [(16, k, 70) for k in (1280, 1281, 1536, 1537)] + [(32, k, 70) for k in (768, 769, 1024, 2047, 4095)])
 
 
 @pytest.mark.parametrize("ftype", ["f32", "f64"])
