@@ -181,7 +181,7 @@ struct Rebin {
   // infinite (below 5.6e-309) or whose own rounding leaves quotients beyond r (subnormal), infinite N (whose coefficients
   // div_by would turn into NaN) and NaN.  NaN counts for nothing in the maximum, and becomes the index -r.  One index at a
   // time: the path takes no registers from the others.  a, b, o: the block in LDS; one team of lanes.  Returns the new N.
-  // (Every block of a wave's tile that holds one such block goes this way: the others' indices come out the same.)
+  // (Other blocks of the tile go this way with it: their indices come out the same.)
   typedef typename IndexOf<kIType>::type index_t;
   __device__ __forceinline__ double far_block(int t, int team, int kept, const uint8_t* a, const uint8_t* b, uint8_t* o) const {
     double m = 0.0, n = 0.0;
@@ -384,6 +384,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 5) void k_rebin_held(Stage st, cons
   extern __shared__ __align__(16) uint8_t smem[];
   constexpr int kPer = PerDword<kIType>::value, kMain = held_dwords(kIType, kTwo) - 1;
   constexpr bool kStraight = straight_from_memory<kIType>();
+  constexpr bool kLate = kStraight && !kTwo;             // the far blocks found behind the indices: shifts of 8 bits 1-4 % less, sums 1-2 % more
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
   // LDS: the first operand, the second, and the result unless it takes the first one's place; of straight_from_memory only the result
   const bool in_place = !kStraight && regions == (kTwo ? 2 : 1);
@@ -414,9 +415,8 @@ __global__ __launch_bounds__(64 * kMaxWaves, 5) void k_rebin_held(Stage st, cons
     if (kTwo) request_span(F2, b_end, F2 + at, len, sb);
   }
   const int pa = phase_of(F1 + at), pb = kTwo ? phase_of(F2 + at) : 0, po = phase_of(Fout + at);
-  // a block that needs far_block: after the others, which that keeps out of the registers of this loop
-  bool far = false;
-  for (int b0 = 0; b0 < count; b0 += per_round) {        // uniform: the lane exchanges below are convergent
+  int b0 = 0;
+  for (; b0 < count; b0 += per_round) {                  // uniform: the lane exchanges below are convergent
     const int b = b0 + slot;
     const bool live = b < count;
     const int bc = live ? b : count - 1;                 // slots past the end redo the last block and store nothing
@@ -473,6 +473,11 @@ __global__ __launch_bounds__(64 * kMaxWaves, 5) void k_rebin_held(Stage st, cons
     // an all-zero block has scale = inv = 0 and every c = 0, which gives 0; no quotient rounds beyond r
     const double n = kTwo ? m / r : m;
     const double inv = n > 0.0 ? 1.0 / n : 0.0;
+    // A block that needs far_block: its round and those after it go there, behind this loop, whose registers that stays out of.  No N of
+    // theirs has been written yet, nor an index where an operand is: both are the operands' still, whatever the result's buffers are.
+    bool far = !(fabs(op.n1) < kFarNumber) || (kTwo && !(fabs(op.n2) < kFarNumber));
+    if (!kTwo || kNType == PBZ_F64) far = far || !(inv < kFarNumber);     // sums of multiples of 2^-149 are within reach
+    if (!kLate && __any(far)) break;
     if (live) {
       LaneOut<kIType> o(so, po + base + start);
 #pragma unroll
@@ -488,18 +493,13 @@ __global__ __launch_bounds__(64 * kMaxWaves, 5) void k_rebin_held(Stage st, cons
       if (kIType == PBZ_I8) put_indices<kIType>(so + po + base + tail, q, st.bpb < 4 ? st.bpb : 4);
       else o.finish(pack_dword<kIType>(q) >> drop, last_bytes, run == 1);
     }
-    far = far || !(fabs(op.n1) < kFarNumber) || (kTwo && !(fabs(op.n2) < kFarNumber));
-    if (!kTwo || kNType == PBZ_F64) far = far || !(inv < kFarNumber);     // sums of multiples of 2^-149 are within reach
+    if (kLate && __any(far)) break;
     if (live && t == 0) store_N<kNType>(Nout, k0 + b, n, n_f16 != 0);
   }
   wave_lds_sync();
-  if (__any(far)) {                                      // other lanes' writes to the same places precede these
-    if (in_place) {                                      // the operand once more: its place in memory is written below
-      request_span(F1, a_end, F1 + at, len, sa);
-      span_arrived();
-    }
+  if (b0 < count) {
     const uint8_t *a = kStraight ? F1 + at : sa + pa, *c = kStraight ? F2 + at : sb + pb;
-    for (int b = slot; b < count; b += per_round) {
+    for (int b = b0 + slot; b < count; b += per_round) {
       op.n1 = load_N<kNType>(N1, k0 + b, n_f16 != 0);
       op.n2 = kTwo ? sign2 * load_N<kNType>(N2, k0 + b, n_f16 != 0) : 0.0;
       const double n = op.far_block(t, team, st.kept, a + b * st.bpb, kTwo ? c + b * st.bpb : nullptr, so + po + b * st.bpb);

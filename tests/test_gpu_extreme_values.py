@@ -119,6 +119,38 @@ def test_rebinning_keeps_infinities(times, kept):
         assert torch.equal(got[0][fine], plain[0]) and torch.equal(got[1][fine], plain[1])
 
 
+@pytest.mark.parametrize("ftype,bits", [("f64", 8), ("f64", 16), ("f64", 32), ("f16", 8), ("f16", 16), ("f32", 32)])
+@pytest.mark.parametrize("kept", [1, 5, 16, 19, 33, 64])
+@pytest.mark.parametrize("n", [24, 2407])
+def test_rebinning_in_place_at_the_ends_of_the_range(n, kept, ftype, bits):
+    """Sum, difference and shift into the buffers of an operand are what they are in buffers of their own, also where blocks whose N is
+    infinite or near the ends of the range are among the others: few of them, and many."""
+    mask = np.zeros(64, dtype=bool)
+    mask[:kept] = True
+    case = Case(np.zeros((8, 8)), None, "f64", (8, 8), bits, ftype, mask.reshape(8, 8))
+    ends = {"f64": [1e-320, 1e-300, 1e298, np.inf, 5e-324], "f32": [1e-44, np.inf, 3e38], "f16": [np.inf, 6e-8, 6e4]}[ftype]
+    g = np.random.Generator(np.random.PCG64(kept))
+    dtype = {"f64": np.float64, "f32": np.float32, "f16": np.float16}[ftype]
+    for share in (0.01, 0.3):
+        N = [g.uniform(0.5, 2.0, n) for _ in range(2)]
+        for k in range(2):
+            where = np.flatnonzero(g.uniform(size=n) < share)
+            where = np.union1d(where, [n - 1 - k])
+            N[k][where] = np.resize(ends, where.size)
+        (N1, F1), (N2, F2) = (operand(n, kept, bits, N[k].astype(dtype), kept + k) for k in range(2))
+        codec = case.codec
+        calls = [(lambda a, out: codec.add(*a, *out), 2), (lambda a, out: codec.subtract(*a, *out), 2),
+                 (lambda a, out: codec.add_scalar(*a, 0.75, *out), 1)]
+        for call, operands in calls:
+            args = [N1, F1, N2, F2][:2 * operands]
+            want = call(args, ())
+            for over in range(operands):
+                mine = [t.clone() for t in args]
+                got = call(mine, mine[2 * over:2 * over + 2])
+                assert got[0].data_ptr() == mine[2 * over].data_ptr()
+                assert torch.equal(got[0].nan_to_num(nan=-1.0), want[0].nan_to_num(nan=-1.0)) and torch.equal(got[1], want[1])
+
+
 @pytest.mark.parametrize("bits,kept", [(8, 5), (8, 19), (8, 33), (8, 63), (16, 5), (16, 19), (16, 63), (32, 19)])
 @pytest.mark.parametrize("n", [40, 2400])
 def test_reductions_keep_infinities(n, bits, kept):
