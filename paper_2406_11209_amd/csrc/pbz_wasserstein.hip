@@ -392,9 +392,10 @@ __global__ __launch_bounds__(kPassThreads) void k_means(const void* __restrict__
       }
       e *= most > m ? exp(m - most) : 1.0;
       m = most;
+      const double base = fmax(m, -1.7976931348623157e308);      // minus infinity weighs nothing, also where the thread has met nothing else
 #pragma unroll
       for (int u = 0; u < kMeansPerThread; ++u) {
-        const double x = exp(v[u] - m);
+        const double x = exp(v[u] - base);
         e += i0 + u * kPassThreads < end ? x : 0.0;
       }
       if (kCount) {

@@ -129,6 +129,31 @@ def test_block_means_come_out_in_order(n, values):
         assert np.array_equal(have[~np.isnan(value)], want)
 
 
+@pytest.mark.parametrize("ftype,low", [("f64", -np.inf), ("f64", -1.7e308), ("f16", -np.inf)])
+@pytest.mark.parametrize("n", [3, 300, 4097, 66001, (1 << 22) + 1])
+def test_means_below_all_numbers_have_no_weight(n, ftype, low):
+    """A block mean of minus infinity (N that has overflowed, or its product with the index) is a probability of zero, be it all that a
+    thread or a workgroup meets."""
+    g = np.random.Generator(np.random.PCG64(n))
+    codec = Codec((2,), ftype, "i8", np.array([True, False]))
+    for where in (g.random(n) < 0.01, np.arange(n) < n // 2, np.arange(n) > 0):
+        where[n // 2] = True
+        ops, oc = [], []
+        for k in range(2):
+            v = g.standard_normal(n)
+            if k == 0:
+                v[where] = low
+            N = torch.from_numpy(np.abs(v)).cuda().to(torch.float64 if ftype == "f64" else torch.float16)
+            F = torch.from_numpy(np.where(v < 0, -127, 127).astype(np.int8).reshape(n, 1)).cuda()
+            ops.append((N, F))
+            oc.append(oracle_compressed(N, F, (2 * n,), (2,), 8, ftype, np.array([True, False]), "dct"))
+        for p in (1.0, 68.0):
+            got = float(codec.approximate_wasserstein(*ops[0], *ops[1], p).item())
+            with np.errstate(over="ignore"):
+                want = po.approximate_wasserstein(oc[0], oc[1], p)
+            assert want > 0.0 and abs(got - want) <= 1e-9 * want, (n, p, got, want)
+
+
 def near(g, n):
     """Two sequences as close as two roundings of one: every bucket matters."""
     v = g.standard_normal(n)
