@@ -49,7 +49,8 @@ constexpr int kBucketCap = 4096;                 // keys sorted in LDS at once: 
 constexpr int kMaxSamples = 4096;                 // four per bucket, two where there are 2048 buckets
 constexpr int kMaxTiles = 256;                   // tiles per operand of the counting and scattering passes
 constexpr int kMinTileKeys = 2048;
-constexpr int kSelectMin = 32;                   // buckets from which k_select pays
+constexpr int kSelectMin = 128;                  // buckets from which k_select pays ...
+constexpr double kSelectGain = 640.0;            // ... where the gap of the maxima, in shares of the larger, times their square is above this
 constexpr int kPieceRanks = 512;                 // ranks of a piece of k_distance, at most
 constexpr int kPassThreads = 512;
 constexpr int kGoingInFlight = 4;
@@ -68,7 +69,7 @@ struct Gap {
 // for k_distance, from k_select
 struct Selection {
   double threshold;        // differences below it do not matter
-  int pieces;              // of ranks that may
+  int pieces;              // of ranks that may; -1: all do
 };
 
 struct Workspace {
@@ -578,9 +579,14 @@ __device__ __forceinline__ double mapped(uint64_t key, const OperandParams& p) {
 // lie: a run of ranks in one bucket of A and one of B whose bounds are closer than `least` times a difference that is certain
 // to be reached (by two buckets that lie apart, or by the two maxima) need not be sorted, nor scattered into buckets.  With smooth fields, whose
 // largest values differ, that is all but some hundredth of the keys (2 x 2M: scatter 39 -> 15 us, sort 63 -> 22, distance 23 -> 7; this
-// kernel 16; 2 x 3.4M of 32-bit indices the whole distance 458 -> 198, 262144 of blocks of 8x8 138 -> 97).  With nearly equal operands nothing is
-// left out, and the call takes what it took before (2M: 277 and 274 us; 1M: 144 and 163).  What is found is the same: `threshold` is below
-// every difference that counts.  Below kSelectMin buckets the launch costs what it saves.
+// kernel 16; 2 x 3.4M of 32-bit indices the whole distance 458 -> 198).  What is found is the
+// same: `threshold` is below every difference that counts.
+// What it can save grows with the buckets and, of these, with the share that the largest difference reaches past: where the maxima's gap, in shares
+// of the larger maximum, times the buckets squared is below kSelectGain, everything is handed on as it is, for 2 us instead of 10 to 16.
+// Measured with blocks of one and of 64 indices, with and without the selection: 512 buckets, gap 3.5e-4: 107 us without, 121 with;
+// 8e-3: 118 and 86; 1024 buckets, 2e-4: 160 and 176, 1.3e-3: 164 and 150; 2048 buckets, 1e-4: 349 and 374, 1e-3: 339 and 284.  Below
+// kSelectMin buckets it does not pay at any gap (64 buckets: 66000 blocks 46 and 57 us, 131072 56 and 67; 128, 6e-2: 65 and 56).  Two
+// versions of one field, 1M blocks: 144 us, 164 with the selection made whatever the gap (2M: 245 and 264; 66000: 46 and 58).
 // One workgroup.  A run of ranks starts where a bucket of A or of B does: kEach of each per thread, in the order of the buckets.
 constexpr int kSelectThreads = 1024;
 template <int kEach>
@@ -602,6 +608,14 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(int64_t n, int bucket
   __shared__ unsigned long long longest[2];
   const int t = int(threadIdx.x), lane = t & 63, wave = t >> 6, bins = 2 * buckets;
   const OperandParams p[2] = {params[0], params[1]};
+  const double inv[2] = {1.0 / p[0].exp_sum, 1.0 / p[1].exp_sum};
+  const double top[2] = {p[0].use_softmax != 0.0 ? inv[0] : p[0].max, p[1].use_softmax != 0.0 ? inv[1] : p[1].max};
+  if (!(fabs(top[0] - top[1]) * (double(buckets) * buckets) > kSelectGain * fmax(fabs(top[0]), fabs(top[1])))) {
+    for (int b = t; b < 2 * bins; b += kSelectThreads) needed[b] = 1;
+    if (t < 2) gap[t] = Gap{1, 0};
+    if (t == 0) *reinterpret_cast<Selection*>(gap + 2) = Selection{0.0, -1};
+    return;
+  }
   // first ranks
   uint32_t first[2][kEach], size[2][kEach];
 #pragma unroll
@@ -652,9 +666,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(int64_t n, int bucket
     }
   __syncthreads();
   // values at the splitters, and the largest magnitude among them
-  const double inv[2] = {1.0 / p[0].exp_sum, 1.0 / p[1].exp_sum};
   const auto value_at = [&](double v, int o) { return p[o].use_softmax != 0.0 ? exp(v - p[o].max) * inv[o] : v; };
-  const double top[2] = {p[0].use_softmax != 0.0 ? inv[0] : p[0].max, p[1].use_softmax != 0.0 ? inv[1] : p[1].max};
   double most = fmax(fabs(top[0]), fabs(top[1]));
   for (int i = t; i < 2 * (buckets - 1); i += kSelectThreads) {
     const int o = i >= buckets - 1 ? 1 : 0, b = i - o * (buckets - 1);
@@ -916,19 +928,16 @@ __device__ __forceinline__ void sort_bucket(int bucket, bool sorts, bool copies,
   // subtraction, product and truncation are all non-decreasing: intervals follow the order of the values
   const double span = most - least;
   const double scale = span > 0.0 ? double(kSubs) / span : 0.0;
-  uint32_t where[kPerThread];                              // interval, and the key's number in it above
+  uint32_t where[kPerThread] = {};                         // interval, and the key's number in it above
   bool crowded = false;
 #pragma unroll
   for (int j = 0; j < kPerThread; ++j)
     if (j * kBucketThreads + t < m) {
       const double value = value_of(held[j]);
       const int s = int(fmin(fmax((value - least) * scale, 0.0), double(kSubs - 1)));
-      // a wave that has many keys in one interval need not have them counted one after the other there
-      if (m > 2 * kMaxSub && __popcll(__ballot(s == __builtin_amdgcn_readfirstlane(s))) > 24) {
-        crowded = true;
-        where[j] = 0;
-        continue;
-      }
+      // a wave that has many of its first keys in one interval need not have them all counted one after the other there
+      if (j == 0 && m > 2 * kMaxSub) crowded = __popcll(__ballot(s == __builtin_amdgcn_readfirstlane(s))) > 24;
+      if (crowded) continue;
       const uint32_t at = atomicAdd(&cursor[s], 1u);
       where[j] = uint32_t(s) | (at << 16);
       crowded = crowded || at >= uint32_t(kMaxSub) || value != value;
@@ -999,12 +1008,17 @@ __device__ __forceinline__ void sort_bucket(int bucket, bool sorts, bool copies,
         rank[j] = 0;
         if (s >= s0 && s < s1) {
           const int a = int(first[s]) - from, b = int(first[s + 1]) - from, self = a + int(where[j] >> 16);
-          if (by_sample && s % kOwnSlots == kOwnSlots - 1) rank[j] = where[j] >> 16;      // equal to a splitter
-          else
-#pragma unroll 4
-            for (int q = a; q < b; ++q) {
+          const auto look = [&](int q) {
             const uint64_t other = key[q];
             rank[j] += other < held[j] || (other == held[j] && q < self) ? 1u : 0u;
+          };
+          if (!by_sample) {                                // one key on average: unrolled, the loop takes 3 us longer at 2 x 1M keys
+            for (int q = a; q < b; ++q) look(q);
+          } else if (s % kOwnSlots == kOwnSlots - 1) {
+            rank[j] = where[j] >> 16;                      // equal to a splitter
+          } else {
+#pragma unroll 4
+            for (int q = a; q < b; ++q) look(q);
           }
         }
       }
@@ -1362,14 +1376,16 @@ __global__ __launch_bounds__(kThreads) void k_distance(const uint64_t* __restric
                                                        double* __restrict__ partials) {
   __shared__ double top;
   const OperandParams pa = params[0], pb = params[1];
-  const int pieces = chosen ? chosen->pieces : int(gridDim.x);
+  const int left = chosen ? chosen->pieces : -1;
+  const bool all = left < 0;
+  const int pieces = all ? int(gridDim.x) : left;
   __shared__ double kept[kKeptDifferences][kThreads];
   // calls f(d) for the thread's differences from number `skip` on
   const auto each = [&](int skip, auto f) {
     int number = 0;
     for (int k = blockIdx.x; k < pieces; k += gridDim.x) {
       int64_t begin = int64_t(k) * chunk, end = begin + chunk < n ? begin + chunk : n;
-      if (chosen) {
+      if (!all) {
         const uint2 r = ranks[k];
         begin = r.x;
         end = begin + r.y;
@@ -1421,23 +1437,24 @@ __global__ __launch_bounds__(kThreads) void k_distance(const uint64_t* __restric
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_distance_final(const double* __restrict__ partials, int groups, double n, double order,
-                                                             double* __restrict__ out) {
+constexpr int kFinalThreads = 1024;
+static_assert(kStatGroups <= kFinalThreads, "a workgroup's record per thread");
+__global__ __launch_bounds__(kFinalThreads) void k_distance_final(const double* __restrict__ partials, int groups, double n, double order,
+                                                                  double* __restrict__ out) {
   __shared__ double top;
-  double s = 0.0, m = 0.0;
-  for (int g = threadIdx.x; g < groups; g += kThreads) m = fmax(m, partials[2 * g + 1]);
+  const int g = int(threadIdx.x);
+  const double part = g < groups ? partials[2 * g] : 0.0, most = g < groups ? partials[2 * g + 1] : 0.0;
+  double s = 0.0, m = most;
   group_sum_max(s, m);
-  if (threadIdx.x == 0) top = m;
+  if (g == 0) top = m;
   __syncthreads();
   m = top;
-  s = 0.0;
-  for (int g = threadIdx.x; g < groups; g += kThreads) {     // the workgroups' sums are relative to their own maxima
-    const double part = partials[2 * g], x = partials[2 * g + 1] / m;
-    s += part != 0.0 && x < 1.0 ? part * pow(x, order) : part;
-  }
+  // the workgroups' sums are relative to their own maxima
+  const double x = most / m;
+  s = part != 0.0 && x < 1.0 ? part * pow(x, order) : part;
   double none = 0.0;
   group_sum_max(s, none);
-  if (threadIdx.x == 0) out[0] = m > 0.0 ? m * pow(s / n, 1.0 / order) : 0.0;
+  if (g == 0) out[0] = m > 0.0 ? m * pow(s / n, 1.0 / order) : 0.0;
 }
 
 }  // namespace
@@ -1511,7 +1528,7 @@ int launch_approximate_wasserstein(const pbz_codec* c, int64_t n, const void* N1
   if (st != PBZ_OK) return st;
   hipLaunchKernelGGL(k_distance, dim3(groups), dim3(kThreads), 0, s, w.buf0, n, chunk, w.params, order, least,
                      select ? reinterpret_cast<const Selection*>(w.gap + 2) : nullptr, w.ranks, w.partials);
-  hipLaunchKernelGGL(k_distance_final, dim3(1), dim3(kThreads), 0, s, w.partials, groups, double(n), order, out);
+  hipLaunchKernelGGL(k_distance_final, dim3(1), dim3(kFinalThreads), 0, s, w.partials, groups, double(n), order, out);
   return hip_status(hipGetLastError());
 }
 

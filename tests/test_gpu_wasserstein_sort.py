@@ -180,7 +180,7 @@ def few_against_many(g, n):
 
 
 @pytest.mark.parametrize("values", [near, tails, sums_to_one, few_against_many], ids=lambda f: f.__name__)
-@pytest.mark.parametrize("n", [65535, 65537, 131073, (1 << 21) + 1])
+@pytest.mark.parametrize("n", [65535, 65537, 131073, 262145, (1 << 20) + 1, (1 << 21) + 1])
 def test_distance_where_buckets_are_left_out(n, values):
     """The sizes from which buckets that cannot matter are neither scattered nor sorted, and at which more of them come to a thread."""
     g = np.random.Generator(np.random.PCG64(n))
