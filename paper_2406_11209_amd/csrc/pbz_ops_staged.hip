@@ -782,6 +782,7 @@ void reduce2(bool two, bool dc, bool diff, dim3 grid, dim3 block, size_t lds, hi
 
 constexpr int kRebinSpan = 2048, kReduceSpan = 4096;       // bytes of F per wave and operand
 constexpr int64_t kMinWaves = 4096;                        // 16 per compute unit
+constexpr int64_t kSecondLaunchBytes = 28 * 1024;          // of a segment and operand that further workgroups have to spare the first
 constexpr int64_t kGroupCap = int64_t(1) << 30;            // the kernels loop beyond that
 
 }  // namespace
@@ -827,10 +828,18 @@ int launch_reduce_staged(const pbz_codec* c, bool two, bool dc, bool diff, int64
   const int waves = waves_for(st, two ? 2 : 1, two ? 2 : 1, &lds);
   // Four workgroups per compute unit for all segments together: what a workgroup does once, its sums over 64 lanes above all, is
   // spread over as many tiles as can be (16 segments of 18750 blocks of 33 int32 indices: variance 20 -> 16 us, covariance 33 -> 24; eight
-  // per compute unit 18 and 27, two 20 and 28).
-  const int per_segment = kReduceGroupsOneSegment / n_segments < 1 ? 1 : kReduceGroupsOneSegment / n_segments;
-  unsigned g = group_count(n_blocks, st, waves, max_groups < per_segment ? max_groups : per_segment);
-  if (g <= 2 || few) g = 1;                // two tiles per wave: cheaper than a second launch
+  // per compute unit 18 and 27, two 20 and 28).  From some 340 segments on that is two or three of a segment's own, or one: one
+  // where the others would spare it little, for they need the second launch (400 segments of 40 KiB, variance: 13.6 us, three 14.6; of
+  // 157 KiB 45.8 and 28.3, of 516 KiB 101 and 58).
+  const int64_t bytes = n_blocks * st.bpb;
+  int64_t share = kReduceGroupsOneSegment / n_segments;
+  if (share <= 2) {                        // to the nearest number then (150 segments of 516 KiB, covariance: six 40 us, seven, the nearest, 48)
+    share = (kReduceGroupsOneSegment + n_segments / 2) / n_segments;
+    if (share < 1 || bytes - bytes / share <= kSecondLaunchBytes) share = 1;
+  }
+  const unsigned all = group_count(n_blocks, st, waves, max_groups);
+  unsigned g = share < int64_t(all) ? unsigned(share) : all;
+  if (all <= 2 || few) g = 1;              // two tiles per wave: cheaper than a second launch
   *groups = int(g);
   const dim3 grid(g, unsigned(n_segments)), block(64 * waves);
   PBZ_BY_TYPES(reduce2, two, dc, diff, grid, block, lds, s, st, N1, F1, N2, F2, n_blocks, tail);

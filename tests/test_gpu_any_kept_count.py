@@ -92,6 +92,27 @@ def test_segments_at_every_phase():
             assert abs(cov[t].item() - one("covariance", t, *nxt)) <= 1e-13 * abs(got[t].item())
 
 
+@pytest.mark.parametrize("run", [70, 230, 700])                # 9, 30 and 92 KB a segment
+@pytest.mark.parametrize("segments", [341, 342, 400, 410, 682, 683, 1025, 2049])
+def test_many_segments_by_one_workgroup_each_or_a_few(segments, run):
+    g = torch.Generator("cuda").manual_seed(segments + run)
+    mask = np.zeros(64, dtype=bool)
+    mask[:33] = True
+    codec = Codec((8, 8), "f64", 32, mask.reshape(8, 8))
+    n, r = segments * run, 2 ** 31 - 1
+    (N1, F1), (N2, F2) = [(torch.rand(n, generator=g, device="cuda", dtype=torch.float64) + 0.1,
+                           torch.randint(-r, r + 1, (n, 33), generator=g, device="cuda").to(torch.int32)) for _ in range(2)]
+    C1, C2 = [(F.double() * (N / r)[:, None]).view(segments, run, 33) for N, F in ((N1, F1), (N2, F2))]
+    sums = lambda x: x.sum(dim=(1, 2))
+    size = sums(C1 * C1 + C2 * C2)
+    mean = C1[:, :, 0].sum(dim=1) / (8 * run)                  # a first coefficient is 8 times its block's mean
+    for got, want in ((codec.segmented("norm2", segments, run, N1, F1) ** 2, sums(C1 * C1)),
+                      (codec.segmented("variance", segments, run, N1, F1) * (64 * run), sums(C1 * C1) - mean * mean * (64 * run)),
+                      (codec.segmented("dot", segments, run, N1, F1, N2, F2), sums(C1 * C2)),
+                      (codec.segmented("difference_norm2", segments, run, N1, F1, N2, F2) ** 2, sums((C1 - C2) ** 2))):
+        assert bool(((got - want).abs() <= 1e-12 * size).all())      # 2^-53 a term, 23000 terms at most
+
+
 # kept counts and block counts around which a call changes from one kernel to another: element by element or through LDS
 HALVES = [(8, 1, 8, 16385), (8, 3, 16, 16385), (64, 19, 8, 2049), (128, 128, 32, 2049), (128, 100, 32, 16385), (256, 160, 32, 16385),
           (256, 192, 16, 2049), (64, 20, 32, 257), (16, 5, 16, 257), (4096, 2049, 32, 2049), (4096, 4096, 32, 2049), (4096, 4096, 16, 2049),
