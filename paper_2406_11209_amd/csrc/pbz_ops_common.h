@@ -331,10 +331,11 @@ __device__ __forceinline__ void reduce_tail(double* sums, const ReduceTail& t, d
 inline bool direct_sum(int64_t n_blocks, int64_t block_bytes) { return n_blocks > 4096 && block_bytes > 14 * 1024; }
 // The same of the block-wise statistics.  The covariance has two operands to put into LDS: up to 1024 blocks of up to 160
 // indices 0.1-0.4 us more (129 int8 indices: 3.0 us, 3.3 through LDS; from there on the two are alike); two to three words a lane, which 65 to
-// 144 indices of 32 bits are, leave lanes idle (5000 blocks of 129: 4.7 and 5.4; 10000: 7.1 and 5.4).  The variance is within
-// 0.1 us either way on up to 512 blocks of 33 to 128.  Large blocks go through LDS (4000 of 4095: covariance 75 us and 33, variance 44 and 16).
+// 144 indices of 32 bits are, leave lanes idle (5000 blocks of 129: 4.7 and 5.4; 10000: 7.1 and 5.4).  The variance of up to 512 blocks of 33 to
+// 65: a wave has them in one step, 0.05-0.3 us less (64 to 512 of 65 16-bit indices: 2.6-2.7 us, 2.9-3.0 through LDS; of 100 8-bit ones, in
+// two steps, 2.9-3.0 and 2.7-2.8).  Large blocks go through LDS (4000 of 4095: covariance 75 us and 33, variance 44 and 16).
 inline bool direct_blockwise(int64_t n_blocks, int kept, int64_t block_bytes, bool two) {
-  if (!two) return n_blocks <= 512 && kept >= 33 && kept <= 128;
+  if (!two) return n_blocks <= 512 && kept >= 33 && kept <= 65;
   if (block_bytes == 4 * int64_t(kept) && kept > 64 && kept <= 144) return n_blocks <= 5120;
   return n_blocks <= 1024 && kept <= 160;
 }
