@@ -655,8 +655,8 @@ int launch_add(const pbz_codec* c, int64_t n_blocks, const void* N1, const void*
     }
 #undef PBZ_ADD
   } else {
-    if (direct_sum(n_blocks, bpb)) return launch_sum_direct(c, n_blocks, N1, F1, N2, F2, Nout, Fout, sign2, s);
-    return launch_rebin_staged(c, n_blocks, N1, F1, N2, F2, Nout, Fout, sign2, 0.0, s);
+    return (direct_rebin(n_blocks, c->kept, bpb, true) ? launch_rebin_direct : launch_rebin_staged)(
+        c, n_blocks, N1, F1, N2, F2, Nout, Fout, sign2, 0.0, s);
   }
   return hip_status(hipGetLastError());
 }
@@ -826,7 +826,8 @@ int launch_add_scalar(const pbz_codec* c, int64_t n_blocks, const void* Nin, con
     }
 #undef PBZ_ADDS
   } else {
-    return launch_rebin_staged(c, n_blocks, Nin, Fin, nullptr, nullptr, Nout, Fout, 1.0, shift, s);
+    return (direct_rebin(n_blocks, c->kept, bpb, false) ? launch_rebin_direct : launch_rebin_staged)(
+        c, n_blocks, Nin, Fin, nullptr, nullptr, Nout, Fout, 1.0, shift, s);
   }
   return hip_status(hipGetLastError());
 }

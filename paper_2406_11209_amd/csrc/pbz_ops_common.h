@@ -324,11 +324,16 @@ __device__ __forceinline__ void reduce_tail(double* sums, const ReduceTail& t, d
   if (threadIdx.x == kPilot2) record[kPilot2] = K2;
 }
 
-// Whether the sum of blocks that make no 16-byte vectors goes straight from memory, a wave per block, or through LDS (with which the times
-// are compared, as dependent launches of a graph).  Only many blocks of over 14 KiB: three regions leave three waves a compute unit (6000
-// blocks of 3600 32-bit indices 140 us, 158 through LDS; of 3300 130 and 118; 3500 blocks 120 and 98).  One operand's shift
-// never gains more than 2 %, and loses up to six times as much time elsewhere (1000 blocks of 2700: 39 and 14).
-inline bool direct_sum(int64_t n_blocks, int64_t block_bytes) { return n_blocks > 4096 && block_bytes > 14 * 1024; }
+// Whether the sum or the shift of blocks that make no 16-byte vectors goes straight from memory, a wave per block, or through LDS (with which
+// the times are compared, as dependent launches of a graph).  Few blocks of 19 to 64 indices, which a wave has in one step: the call is one
+// round trip to memory, and the detour is up to 0.4 us more (300 blocks of 63 16-bit indices: sum 3.4 us, 3.8 through LDS, shift 3.1 and
+// 3.4; of 33 32-bit ones 3.5 and 3.6; of 65, in two steps, 4.1 and 3.7 to 3.9).  8-bit operands are read straight from memory there, too: only
+// shifts of 57 and more (63: 3.1 and 3.4; sums 3.4 and 3.4 to 3.5, of 32 blocks 3.3 and 3.1).  Many blocks of over 14 KiB: three regions leave three waves a compute unit (sum of 6000 blocks of 3600 32-bit indices
+// 140 us, 158 through LDS; of 3300 130 and 118; 3500 blocks 120 and 98); one operand's shift never gains more than 2 % there.
+inline bool direct_rebin(int64_t n_blocks, int kept, int64_t block_bytes, bool two) {
+  if (n_blocks <= 1024) return kept <= 64 && (block_bytes == kept ? !two && kept >= 57 : kept >= 19);
+  return two && n_blocks > 4096 && block_bytes > 14 * 1024;
+}
 // The same of the block-wise statistics.  The covariance has two operands to put into LDS: up to 1024 blocks of up to 160
 // indices 0.1-0.4 us more (129 int8 indices: 3.0 us, 3.3 through LDS; from there on the two are alike); two to three words a lane, which 65 to
 // 144 indices of 32 bits are, leave lanes idle (5000 blocks of 129: 4.7 and 5.4; 10000: 7.1 and 5.4).  The variance of up to 512 blocks of 33 to
@@ -348,8 +353,8 @@ inline bool direct_reduction(int64_t n_blocks, int kept, bool two) {
 
 // pbz_ops_direct.hip and pbz_ops_staged.hip: any kept count, any alignment.  F2 == nullptr: addition of `shift` to the first
 // coefficients.
-int launch_sum_direct(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2, void* Nout,
-                      void* Fout, double sign2, hipStream_t s);
+int launch_rebin_direct(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2,
+                        void* Nout, void* Fout, double sign2, double shift, hipStream_t s);
 int launch_blockwise_direct(const pbz_codec* c, int mode, int64_t n_blocks, const void* N1, const void* F1, const void* N2,
                             const void* F2, double* out, double scale, hipStream_t s);
 int launch_reduce_direct(const pbz_codec* c, bool two, bool dc, bool diff, int64_t n_blocks, int n_segments, int max_groups,

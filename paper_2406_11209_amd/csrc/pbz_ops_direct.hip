@@ -1,28 +1,34 @@
 // Compressed-space operations straight from memory, element by element: any kept count, any alignment, any type at run time.
 // For the sizes at which putting blocks through LDS (pbz_ops_staged.hip) costs more than it saves: few blocks, where a
 // call is one memory round trip and the launch, and sums of blocks so large that LDS holds one wave's only.  The rules and both sides' times
-// are with direct_sum, direct_blockwise and direct_reduction.
+// are with direct_rebin, direct_blockwise and direct_reduction.
 #include "pbz_ops_common.h"
 
 namespace pbz {
 namespace ops {
 namespace {
 
-// Algorithm 2, one wave per block: C = F1 N1 + F2 (sign2 N2), N = max|C| / r, F = rint(C / N).
-__global__ __launch_bounds__(64) void k_sum_direct(const void* N1, const void* F1, const void* N2, const void* F2, void* Nout,
-                                                   void* Fout, int ntype, int itype, double r, double sign2, int64_t n_blocks, int kept) {
+// Algorithms 2 and 4, one wave per block.  kTwo: C = F1 N1 + F2 (sign2 N2), N = max|C| / r, F = rint(C / N); otherwise
+// C = N1 F1 / r, the first one moved by `shift`, N = max|C|, F = rint(C r / N).
+template <bool kTwo>
+__global__ __launch_bounds__(64) void k_rebin_direct(const void* N1, const void* F1, const void* N2, const void* F2, void* Nout,
+                                                     void* Fout, int ntype, int itype, double r, double sign2, double shift,
+                                                     int64_t n_blocks, int kept) {
   for (int64_t k = blockIdx.x; k < n_blocks; k += gridDim.x) {
-    const double n1 = load_float<double>(N1, ntype, k), n2 = sign2 * load_float<double>(N2, ntype, k);
+    const double n1 = load_float<double>(N1, ntype, k), n2 = kTwo ? sign2 * load_float<double>(N2, ntype, k) : 0.0;
     auto coefficient = [&](int j) {
-      return unfused_sum_of_products(double(load_index(F1, itype, k * kept + j)), n1, double(load_index(F2, itype, k * kept + j)), n2);
+      const double f1 = double(load_index(F1, itype, k * kept + j));
+      if (kTwo) return unfused_sum_of_products(f1, n1, double(load_index(F2, itype, k * kept + j)), n2);
+      return (n1 * f1) / r + (j == 0 ? shift : 0.0);
     };
     double m = 0.0;
     for (int j = threadIdx.x; j < kept; j += 64) m = fmax(m, fabs(coefficient(j)));
     for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
-    const double n = m / r;
+    const double n = kTwo ? m / r : m;
     // F_out may alias an operand: every lane re-reads only the entries it then overwrites
     for (int j = threadIdx.x; j < kept; j += 64) {
-      const double t = n > 0.0 ? coefficient(j) / n : 0.0;
+      const double c = coefficient(j);
+      const double t = n > 0.0 ? (kTwo ? c : c * r) / n : 0.0;
       store_index(Fout, itype, k * kept + j, int64_t(fmin(fmax(rint(t), -r), r)));
     }
     if (threadIdx.x == 0) store_float(Nout, ntype, k, n);
@@ -97,10 +103,14 @@ dim3 wave_per_block(int64_t n_blocks) { return dim3(unsigned(n_blocks < 65536 ? 
 
 }  // namespace
 
-int launch_sum_direct(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2, void* Nout,
-                      void* Fout, double sign2, hipStream_t s) {
-  hipLaunchKernelGGL(k_sum_direct, wave_per_block(n_blocks), dim3(64), 0, s, N1, F1, N2, F2, Nout, Fout, int(c->ftype), int(c->itype),
-                     c->r, sign2, n_blocks, c->kept);
+int launch_rebin_direct(const pbz_codec* c, int64_t n_blocks, const void* N1, const void* F1, const void* N2, const void* F2,
+                        void* Nout, void* Fout, double sign2, double shift, hipStream_t s) {
+  if (F2)
+    hipLaunchKernelGGL(k_rebin_direct<true>, wave_per_block(n_blocks), dim3(64), 0, s, N1, F1, N2, F2, Nout, Fout, int(c->ftype),
+                       int(c->itype), c->r, sign2, shift, n_blocks, c->kept);
+  else
+    hipLaunchKernelGGL(k_rebin_direct<false>, wave_per_block(n_blocks), dim3(64), 0, s, N1, F1, N2, F2, Nout, Fout, int(c->ftype),
+                       int(c->itype), c->r, sign2, shift, n_blocks, c->kept);
   return hip_status(hipGetLastError());
 }
 

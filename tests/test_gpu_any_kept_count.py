@@ -117,7 +117,8 @@ def test_many_segments_by_one_workgroup_each_or_a_few(segments, run):
 HALVES = [(8, 1, 8, 16385), (8, 3, 16, 16385), (64, 19, 8, 2049), (128, 128, 32, 2049), (128, 100, 32, 16385), (256, 160, 32, 16385),
           (256, 192, 16, 2049), (64, 20, 32, 257), (16, 5, 16, 257), (4096, 2049, 32, 2049), (4096, 4096, 32, 2049), (4096, 4096, 16, 2049),
           (64, 19, 8, 1025), (256, 192, 16, 1025), (128, 65, 16, 513), (8, 3, 16, 257), (8, 1, 32, 513), (4096, 2500, 32, 3073), (4096, 3000, 32, 3073),
-          (4096, 3601, 32, 4097), (256, 144, 32, 5121), (256, 160, 8, 1025), (8, 2, 16, 32769), (128, 66, 16, 513)]
+          (4096, 3601, 32, 4097), (256, 144, 32, 5121), (256, 160, 8, 1025), (8, 2, 16, 32769), (128, 66, 16, 513),
+          (64, 18, 16, 1025), (64, 19, 16, 1025), (64, 63, 32, 1025), (128, 65, 32, 1025), (64, 56, 8, 1025), (64, 57, 8, 1025)]
 
 
 @pytest.mark.parametrize("extent,kept,bits,n", HALVES, ids=["%d_of_%d_i%d_x%d" % (k, e, b, n) for e, k, b, n in HALVES])
