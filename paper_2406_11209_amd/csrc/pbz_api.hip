@@ -407,6 +407,7 @@ int pbz_internal_route(const pbz_codec* c, int decompress, const int64_t* shape,
     r = decompress ? try_decompress_brick(c, g, &none, f, f, a, array_type, nullptr, true)
                    : try_compress_brick(c, g, &none, a, array_type, f, f, nullptr, true);
     if (r != 0) return kRouteShape;
+    if (line_kernels_cover(c)) return kRouteLines;
   }
   return tiled_kernels_cover(c) ? kRouteTiled : kRouteDense;
 }

@@ -19,7 +19,7 @@ constexpr int kReduceMaxGroups = 4096;      // upper bound on reduction workgrou
 // Which kernels take a compress or decompress call, in the order in which they are asked.  A codec's route is kRouteAuto; the tests
 // set kRouteMasked or kRouteShape to have that kind taken wherever it can be, whatever the rules on sizes say
 // (pbz_internal_set_route), and ask which one a call would go to (pbz_internal_route).
-enum Route { kRouteAuto = -1, kRouteExact = 0, kRouteMasked = 1, kRouteShape = 2, kRouteTiled = 3, kRouteDense = 4 };
+enum Route { kRouteAuto = -1, kRouteExact = 0, kRouteMasked = 1, kRouteShape = 2, kRouteLines = 3, kRouteTiled = 4, kRouteDense = 5 };
 
 constexpr size_t kWorkspaceBytes = size_t(kReduceMaxGroups) * kReducePartialSlots * sizeof(double);
 

@@ -41,8 +41,8 @@ EXACT_TIE = 1e-9     # |frac(t) - 1/2| below this: a tie in exact arithmetic
 
 
 # Which kernels take a compress or decompress call (the library's internal numbering, in the order in which it asks them): those for
-# exactly this setting, the same families under any mask, those per block shape, the tiled and the dense ones.
-EXACT, MASKED, SHAPE, TILED, DENSE = range(5)
+# exactly this setting, the same families under any mask, those per block shape, those for lines of 64, the tiled and the dense ones.
+EXACT, MASKED, SHAPE, LINES, TILED, DENSE = range(6)
 
 
 def route(codec: Codec, op: str, shape, dtype: str, array: int = 256) -> int:

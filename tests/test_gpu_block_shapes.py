@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2406_11209_amd import synth
-from parity import DENSE, SHAPE, Case, route, take_wherever_possible
+from parity import LINES, SHAPE, Case, route, take_wherever_possible
 
 pytestmark = pytest.mark.gpu
 
@@ -27,7 +27,7 @@ def extents(block, kind, g):
 
 
 def taken(block, ftype, bits):
-    """Lines of 64 in FP64 work are left to the dense kernels."""
+    """Lines of 64 in FP64 work are left to the kernels for these."""
     return not (block[-1] == 64 and (ftype == "f64" or bits > 8))
 
 
@@ -56,7 +56,7 @@ def test_every_listed_block_shape(block, kind):
         take_wherever_possible(case.codec, SHAPE)
         exact = case.codec.kernel_name("compress", shape, dtype) != "generic"
         if not exact:
-            want = SHAPE if taken(block, ftype, bits) else DENSE
+            want = SHAPE if taken(block, ftype, bits) else LINES
             assert route(case.codec, "compress", shape, dtype) == route(case.codec, "decompress", shape, dtype) == want
         N, F, _, _ = case.check_compress("A")
         case.check_decompress(N, F)

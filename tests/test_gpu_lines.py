@@ -6,7 +6,7 @@ import torch
 
 from paper_2406_11209_amd import synth
 from paper_2406_11209_amd.api import PBZ_PATH_GENERIC
-from parity import Case
+from parity import DENSE, LINES, Case, route
 
 pytestmark = pytest.mark.gpu
 
@@ -38,8 +38,14 @@ def test_lines(block, shape, dtype, ftype, bits, kept, transform):
     case = make(block, shape, dtype, bits, ftype, masked(block, kept), transform)
     N, F, _, _ = case.check_compress("A")
     case.check_decompress(N, F)
-    # the general kernels, which these calls went to before: equal up to the order of the sums
+    check_against_the_dense_kernels(case, N, F, shape, dtype, ftype)
+
+
+def check_against_the_dense_kernels(case, N, F, shape, dtype, ftype):
+    """Which these calls went to before: equal up to the order of the sums."""
+    assert route(case.codec, "compress", shape, dtype) == route(case.codec, "decompress", shape, dtype) == LINES
     case.codec.set_kernel_path(PBZ_PATH_GENERIC)
+    assert route(case.codec, "compress", shape, dtype) == DENSE
     Ng, Fg = case.codec.compress(case.xA)
     y = case.codec.decompress(N, F, shape, case.xA.dtype)
     case.codec.set_kernel_path(0)
@@ -49,6 +55,20 @@ def test_lines(block, shape, dtype, ftype, bits, kept, transform):
     assert int((F.to(torch.int64) - Fg.to(torch.int64)).abs().max()) <= 1
     steps = {"f64": 2.0 ** -46, "f32": 2.0 ** -23, "bf16": 2.0 ** -7, "f16": 2.0 ** -10}[dtype]
     assert bool(((y.double() - z.double()).abs() <= steps * y.double().abs().max()).all())
+
+
+# 4096 tiles of sixteen blocks are 4 Mi elements: from there on eight waves share a table when compressing; 3072 tiles, and 4096 with eight
+# waves, stand at once, so that waves take a second tile.  The last tile is not full, nor is its last block.
+@pytest.mark.parametrize("block,shape", [((64,), ((4 << 20) - 1025,)), ((64,), ((4 << 20) + 7,)), ((1, 64), (4099, 1030)), ((64,), ((9 << 20) + 999,))],
+                         ids=["below", "above", "rows", "two_turns"])
+@pytest.mark.parametrize("dtype,ftype,bits,kept", [("f64", "f64", 32, None), ("f32", "f32", 16, 19), ("bf16", "bf16", 16, 63), ("f32", "f64", 8, 33)])
+def test_more_lines_than_stand_at_once(block, shape, dtype, ftype, bits, kept):
+    case = make(block, (1,) * len(shape), dtype, bits, ftype, masked(block, kept))
+    g = torch.Generator("cuda").manual_seed(bits)
+    x = torch.rand(shape, generator=g, device="cuda").to(case.xA.dtype) + 0.25
+    case.xA = x
+    N, F = case.codec.compress(x)
+    check_against_the_dense_kernels(case, N, F, shape, dtype, ftype)
 
 
 @pytest.mark.parametrize("scale", [1e-305, 1e-307, 1e300])

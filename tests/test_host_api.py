@@ -412,7 +412,7 @@ def test_kernels_for_any_mask_and_per_block_shape_take_their_rows():
     """What the GPU rows force is what they get: also without a GPU, so that a shape that drops out of a list is seen here."""
     import test_gpu_any_mask as masks
     import test_gpu_block_shapes as shapes
-    from parity import DENSE, MASKED, SHAPE, TILED, route, take_wherever_possible
+    from parity import LINES, MASKED, SHAPE, TILED, route, take_wherever_possible
     for block, dtype, ftype, bits in masks.ROWS:
         mask = np.ones(block, dtype=bool)
         mask.reshape(-1)[-1] = False
@@ -428,7 +428,7 @@ def test_kernels_for_any_mask_and_per_block_shape_take_their_rows():
             mask.reshape(-1)[-1] = False
             c = Codec(block, ftype, bits, mask)
             take_wherever_possible(c, SHAPE)
-            want = SHAPE if shapes.taken(block, ftype, bits) else DENSE
+            want = SHAPE if shapes.taken(block, ftype, bits) else LINES
             shape = tuple(3 * b + 1 for b in block)
             assert route(c, "compress", shape, dtype) == route(c, "decompress", shape, dtype) == want, (block, dtype, ftype, bits)
 
