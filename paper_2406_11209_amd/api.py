@@ -73,7 +73,16 @@ SIGNATURES = {
 }
 
 _lib = None
-_binding = None      # the frequent calls' native side (csrc/pbz_binding.c), imported with the library
+
+
+class _Missing:
+    """In the place of the frequent calls' native side (csrc/pbz_binding.c) where that has not been built: host-only calls do without it."""
+
+    def __getattr__(self, name):
+        raise RuntimeError("the binding's _binding.so is missing: build it with `python -m paper_2406_11209_amd.build`")
+
+
+_binding = None      # imported with the library
 
 
 class PbzError(RuntimeError):
@@ -100,8 +109,8 @@ def load_library(path: Optional[str] = None):
     if _binding is None:
         try:
             from . import _binding as native
-        except ImportError as e:
-            raise RuntimeError("the binding's _binding.so is missing: build it with `python -m paper_2406_11209_amd.build`") from e
+        except ImportError:
+            native = _Missing()
         _binding = native
     _lib = lib
     return lib

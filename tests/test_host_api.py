@@ -433,6 +433,28 @@ def test_kernels_for_any_mask_and_per_block_shape_take_their_rows():
             assert route(c, "compress", shape, dtype) == route(c, "decompress", shape, dtype) == want, (block, dtype, ftype, bits)
 
 
+def test_host_only_calls_do_without_the_native_binding():
+    """A library without _binding.so beside it still loads; the first device call says what is missing."""
+    import subprocess
+    import sys
+    code = """
+import sys
+sys.modules["paper_2406_11209_amd._binding"] = None
+import torch
+from paper_2406_11209_amd import api
+api.load_library(api.LIB_PATH)
+codec = api.Codec((8, 8), "f32", "i8")
+assert codec.layout((16, 24)).n_blocks == 6 and codec.kernel_name("compress", (16, 24), "f32")
+try:
+    codec.negate(torch.zeros(4, 64, dtype=torch.int8))
+except RuntimeError as e:
+    assert "_binding.so is missing" in str(e)
+else:
+    raise AssertionError("no error")
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=300)
+
+
 def test_native_calls_refuse_what_the_device_could_not_read():
     """Tensors in host memory, no tensors at all and wrong counts end in Python errors before an entry point is called."""
     torch = pytest.importorskip("torch")
