@@ -416,25 +416,26 @@ class Codec:
         return out
 
     # ---- reductions (each returns a 1-element float64 device tensor) --------------------------
-    def _with_workspace(self, call, N, *args):
+    def _with_workspace(self, call, N, entry, handle, *args):
         """call(entry, codec, workspaces, ...): None where N's device and the current stream have no workspace yet."""
-        status = call(*args)
+        status = call(entry, handle, self._spaces, *args)
         if status is None:
             ws = self.workspace(N.device)
             if len(self._spaces) > 256:                    # addresses only: the workspaces themselves are in _ws
                 self._spaces.clear()
-            self._spaces[N.get_device(), _stream()] = (ws.data_ptr(), ws.numel())
-            status = call(*args)
+            key, space = (N.get_device(), _stream()), (ws.data_ptr(), ws.numel())
+            self._spaces[key] = space
+            status = call(entry, handle, {key: space}, *args)      # (another thread may clear _spaces any time)
         check(status)
 
     def _reduce2(self, name, N1, F1, N2, F2, out, values=1):
         out = _torch().empty(values, dtype=_torch().float64, device=N1.device) if out is None else out
-        self._with_workspace(_binding.reduce, N1, self._at[name], self._handle, self._spaces, F1, N1, F1, N2, F2, out)
+        self._with_workspace(_binding.reduce, N1, self._at[name], self._handle, F1, N1, F1, N2, F2, out)
         return out
 
     def _reduce1(self, name, N, F, out, values=1):
         out = _torch().empty(values, dtype=_torch().float64, device=N.device) if out is None else out
-        self._with_workspace(_binding.reduce, N, self._at[name], self._handle, self._spaces, F, N, F, out)
+        self._with_workspace(_binding.reduce, N, self._at[name], self._handle, F, N, F, out)
         return out
 
     def dot(self, N1, F1, N2, F2, out=None):
@@ -455,7 +456,7 @@ class Codec:
     def segmented(self, statistic: str, n_segments: int, blocks_per_segment: int, N1, F1, N2=None, F2=None, out=None):
         """pbz_segmented: one value per run of `blocks_per_segment` blocks; returns n_segments float64 values."""
         out = _torch().empty(n_segments, dtype=_torch().float64, device=N1.device) if out is None else out
-        self._with_workspace(_binding.segmented, N1, self._at["pbz_segmented"], self._handle, self._spaces, self.STATISTICS[statistic],
+        self._with_workspace(_binding.segmented, N1, self._at["pbz_segmented"], self._handle, self.STATISTICS[statistic],
                              int(n_segments), int(blocks_per_segment), N1, F1, N2, F2, out)
         return out
 

@@ -4,6 +4,7 @@ Sec. III-B and Sec. IV-C.  No compute call is made here."""
 import ctypes
 import os
 import re
+import types
 
 import numpy as np
 import pytest
@@ -453,6 +454,27 @@ else:
     raise AssertionError("no error")
 """
     subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=300)
+
+
+def test_a_reduction_keeps_its_workspace_while_others_come_and_go(monkeypatch):
+    """The table of workspaces' addresses is cleared when it is large, by any thread: the call that has just made its entry goes on."""
+    torch = pytest.importorskip("torch")
+    codec = Codec((8, 8), "f32", "i8")
+    space = torch.zeros(64, dtype=torch.uint8)
+    monkeypatch.setattr(codec, "workspace", lambda device: space)
+    monkeypatch.setattr(api, "_stream", lambda: 7)
+    calls = []
+
+    def entry(at, handle, spaces, *rest):
+        codec._spaces.clear()                          # as another thread might, between any two steps
+        calls.append(spaces.get((-1, 7)))
+        return None if calls[-1] is None else 0
+
+    codec._spaces.update({(0, s): (1, 1) for s in range(300)})
+    monkeypatch.setattr(api, "_binding", types.SimpleNamespace(reduce=entry))
+    for _ in range(2):
+        codec.norm2(torch.zeros(1), torch.zeros(1, 64, dtype=torch.int8), torch.zeros(1, dtype=torch.float64))
+    assert calls == [None, (space.data_ptr(), 64)] * 2
 
 
 def test_native_calls_refuse_what_the_device_could_not_read():
