@@ -249,7 +249,10 @@ class Codec:
 
     def layout(self, shape: Sequence[int]) -> Layout:
         if isinstance(shape, tuple):                       # torch.Size is one
-            hit = self._layouts.get(shape)
+            try:
+                hit = self._layouts.get(shape)
+            except TypeError:                              # extents that are no hashable objects (arrays of one number)
+                hit = None
             if hit is not None:
                 return hit
         key = tuple(int(v) for v in shape)

@@ -80,6 +80,13 @@ def test_layout_of_the_five_workloads():
         assert lay.workspace_bytes >= 8 * 5
 
 
+def test_layout_takes_extents_of_any_kind_of_number():
+    codec = Codec((8, 8), "f32", "i8")
+    want = codec.layout([20, 16])
+    for shape in ((20, 16), (np.int64(20), np.int32(16)), (np.array(20), np.array(16)), (20.0, 16), np.array([20, 16])):
+        assert codec.layout(shape) == want
+
+
 def test_layout_ragged_and_errors():
     c = Codec((2, 4), "f32", "i16")
     lay = c.layout((3, 5))
