@@ -79,6 +79,20 @@ def test_lines_at_the_ends_of_the_range(scale):
     case.check_decompress(N, F)
 
 
+@pytest.mark.parametrize("power", [1019, -1000])
+@pytest.mark.parametrize("bits,kept", [(8, None), (16, 19), (32, None)])
+def test_lines_come_out_the_same_times_a_power_of_two(bits, kept, power):
+    """N is that much larger and the indices are what they were, also where r times a coefficient (2^1019 2^3 2^31) leaves the range."""
+    case = make((64,), (64 * 300 + 5,), "f64", bits, "f64", masked((64,), kept))
+    x = case.xA / (8.0 * case.xA.abs().max())                   # coefficients below 1
+    N, F = case.codec.compress(x)
+    far_N, far_F = case.codec.compress(x * 2.0 ** power)
+    assert torch.equal(far_N, N * 2.0 ** power) and torch.equal(far_F, F)
+    far_y = case.codec.decompress(far_N, far_F, x.shape)
+    if power < 0:                                               # (N F is formed first: beyond the range with N this large)
+        assert torch.equal(far_y, case.codec.decompress(N, F, x.shape) * 2.0 ** power)
+
+
 def test_not_finite_blocks_keep_to_themselves():
     """NaN makes a block N = 0 and zeros, infinity N = infinity and the index -r, as on the general kernels; the blocks beside it stay."""
     case = make((64,), (64 * 40,), "f32", 16, "f32", None)
