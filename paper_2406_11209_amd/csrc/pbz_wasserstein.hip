@@ -41,8 +41,8 @@ constexpr int kKeysInFlight = 8;                 // keys a thread of the passes 
 // bucket in LDS.  What bounds it: 8-byte scatters and LDS, 16 bytes a key and pass against memory otherwise.
 // K = n / 2048 rounded up to a power of two, so that a bucket has some 1024 to 2048 keys: smaller ones would make the
 // runs that a tile scatters into a bucket shorter than the 64 bytes they are, larger ones would not fit LDS beside
-// three more.  2 x 2M keys, the whole distance: 491 us with eight radix passes, 290 with all buckets sorted, 193 with those that matter
-// (of that the means, a line of F each, and the counting 106; samples and splitters 13, k_select 16, scattering 15, sorting 20).
+// three more.  2 x 2M keys, the whole distance: 491 us with eight radix passes, 290 with all buckets sorted, 190 with those that matter
+// (of that the means, a line of F each, and the counting 105; samples and splitters 13, k_select 16, scattering 14, sorting 20).
 constexpr int kSampleSortMax = 1 << 22;          // 2048 buckets: fewer than two samples each would leave them too uneven
 constexpr int kBucketKeys = 2048;                // on average, at most
 constexpr int kBucketCap = 4096;                 // keys sorted in LDS at once: larger buckets take more than one round
@@ -1016,7 +1016,7 @@ __device__ __forceinline__ void sort_bucket(int bucket, bool sorts, bool copies,
             rank[j] = where[j] >> 16;                      // equal to a splitter
           } else {
             int q = a;
-            if (b - a >= 4)                                // an interval has one key on average, in crowded buckets many: 4096 means of an
+            if (b - a >= 4)                                // an interval has one key on average, in crowded buckets many: 15625 means of an
               for (; q + 4 <= b; q += 4)                   // image 33 -> 26 us; with the loop unrolled for all, 2 x 1M keys 41 -> 44
 #pragma unroll
                 for (int u = 0; u < 4; ++u) look(q + u);
