@@ -8,7 +8,8 @@
 //   2. the parameters of the softmax and the decision whether to apply it,
 //   3. which of the keys can matter for the distance at all (k_select); the raw means of these are sorted (softmax is
 //      increasing, so it commutes with sorting), both operands in the same launches (grid y): a sample sort up to
-//      kSampleSortMax keys, a least-significant-digit radix sort of all keys beyond,
+//      kSampleSortMax keys, a least-significant-digit radix sort of all keys beyond.  Up to kRangeMax keys, where the
+//      launches are the time, all are sorted by as few kernels as can do it (launch_few),
 //   4. m = max |P_A - P_B| and sum (|P_A - P_B| / m)^p, then m (sum / n)^(1/p): the scaling by m changes
 //      nothing in exact arithmetic and keeps orders such as p = 68 .. 80 from underflowing.
 // All sums are two-stage with a fixed order, so the result is reproducible run to run.
@@ -35,7 +36,7 @@ constexpr int kDistancesInFlight = 2;
 constexpr int kKeptDifferences = 12;             // of a thread of k_distance, in LDS until the maximum is known; a multiple of those
 constexpr int kKeysInFlight = 8;                 // keys a thread of the passes below requests together
 
-// Sample sort: 4 K keys drawn from the n (one from each run of n / 4K, at a place that depends on the run's number) and
+// Sample sort: 4 K to 16 K keys drawn from the n (one from each run of equally many, at a place that depends on the run's number) and
 // sorted give K - 1 splitters; one pass counts and one pass scatters the keys into the 2 K - 1 buckets (between two
 // splitters, or equal to one: a value that many blocks share fills a bucket that needs no sorting); a workgroup sorts a
 // bucket in LDS.  What bounds it: 8-byte scatters and LDS, 16 bytes a key and pass against memory otherwise.
@@ -46,11 +47,23 @@ constexpr int kKeysInFlight = 8;                 // keys a thread of the passes 
 constexpr int kSampleSortMax = 1 << 22;          // 2048 buckets: fewer than two samples each would leave them too uneven
 constexpr int kBucketKeys = 2048;                // on average, at most
 constexpr int kBucketCap = 4096;                 // keys sorted in LDS at once: larger buckets take more than one round
-constexpr int kMaxSamples = 4096;                 // four per bucket, two where there are 2048 buckets
+constexpr int kMaxSamples = 4096;
 constexpr int kMaxTiles = 256;                   // tiles per operand of the counting and scattering passes
 constexpr int kMinTileKeys = 2048;
 constexpr int kSelectMin = 128;                  // buckets from which k_select pays ...
 constexpr double kSelectGain = 640.0;            // ... where the gap of the maxima, in shares of the larger, times their square is above this
+#ifndef RANGE_MAX
+#define RANGE_MAX 65536
+#endif
+// Few keys (launch_few): ranges of kRangeKeys on average, found by workgroups that each go through all keys, from kMaxSamples keys on; below, a
+// key's rank is counted, and up to kBucketThreads one workgroup does an operand.  What it saves are launches, of 4.5 us in line: nine, or six
+// where there was one bucket, are two, three and five.  Whole distance, us, nine or six launches -> now: 256 blocks 22.4 -> 10.1, 1024 25.8 ->
+// 13.2, 4096 45 -> 23, 16384 52 -> 26, 65536 of a crowded image 92 -> 38.  At 110 thousand the walk through all keys (48 us) costs more than
+// scattering them: 62 -> 70.  Ranges of 1024 keys, in two to a thread: 16384 keys 31, 65536 43.
+constexpr int kRangeMax = 65536;
+constexpr int kRangeKeys = 512;
+constexpr int kSampleRun = 32;                   // one sample of as many keys: 8 to 16 a range, so that hardly one has twice the average
+static_assert(kRangeMax <= kMaxSamples * kSampleRun, "a sample of each run");
 constexpr int kPieceRanks = 512;                 // ranks of a piece of k_distance, at most
 constexpr int kPassThreads = 512;
 constexpr int kGoingInFlight = 4;
@@ -168,10 +181,26 @@ __device__ __forceinline__ double value_of(uint64_t k) {
   return __longlong_as_double((long long)u);
 }
 
+// the largest over the 64 lanes of a wave, all of them active, in every lane; register moves, as wave_sum
+template <int kControl, int kRows>
+__device__ __forceinline__ double lane_shifted_or_own(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const int lo = int(uint32_t(u)), hi = int(uint32_t(u >> 32));
+  const uint32_t l = uint32_t(__builtin_amdgcn_update_dpp(lo, lo, kControl, kRows, 0xf, false));
+  const uint32_t h = uint32_t(__builtin_amdgcn_update_dpp(hi, hi, kControl, kRows, 0xf, false));
+  return __builtin_bit_cast(double, uint64_t(l) | (uint64_t(h) << 32));
+}
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  return v;
+  v = fmax(v, lane_shifted_or_own<0x111, 0xf>(v));
+  v = fmax(v, lane_shifted_or_own<0x112, 0xf>(v));
+  v = fmax(v, lane_shifted_or_own<0x114, 0xf>(v));
+  v = fmax(v, lane_shifted_or_own<0x118, 0xf>(v));
+  v = fmax(v, lane_shifted_or_own<0x142, 0xa>(v));
+  v = fmax(v, lane_shifted_or_own<0x143, 0xc>(v));
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u)), 63));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u >> 32)), 63));
+  return __builtin_bit_cast(double, uint64_t(lo) | (uint64_t(hi) << 32));
 }
 
 // workgroup totals of two values (sum, max) in thread 0; at most 1024 threads
@@ -241,6 +270,12 @@ __device__ __forceinline__ int64_t sample_place(int i, int shift, int64_t n) {
   return lo + int64_t((uint64_t(uint32_t(i) * 2654435761u) * uint64_t(hi - lo)) >> 32);
 }
 
+// the same for up to kRangeMax keys, of every kSampleRun one
+__device__ __forceinline__ int64_t sample_of_run(int64_t run, int64_t n) {
+  const int64_t lo = run * kSampleRun, length = n - lo < kSampleRun ? n - lo : kSampleRun;
+  return lo + int64_t((uint64_t(uint32_t(run) * 2654435761u) * uint64_t(length)) >> 32);
+}
+
 // Ascending order of p[0 .. m) by the whole workgroup: bitonic merges whose first step folds a run onto itself, so that every
 // exchange is ascending and a count that is no power of two needs no padding.  int_t: wide enough for 4 m.
 template <typename int_t>
@@ -267,6 +302,7 @@ __device__ __forceinline__ void fold_sort(uint64_t* p, int_t m) {
 // The workgroups rank kRankThreads / kRankLanes samples each, by counting the smaller ones (and the equal ones before them), kRankLanes lanes
 // per sample.  The samples are taken from N and F, once (by every ranking workgroup: 27 us for 2 x 2M blocks): the pass that makes all
 // keys counts them by bucket already.  (One workgroup sorting the samples in its LDS: 50 us for 4096, at 0.65 us a step of fold_sort.)
+// All of up to kMaxSamples keys are sorted like that, too: 4 us for 1024, 9 for 4096 (LDS reads and 64-bit compares, as n squared).
 constexpr int kRankLanes = 16;
 constexpr int kRankThreads = 512;
 __global__ __launch_bounds__(64) void k_samples(const void* __restrict__ N1, const void* __restrict__ F1,
@@ -281,18 +317,18 @@ __global__ __launch_bounds__(64) void k_samples(const void* __restrict__ N1, con
   });
 }
 
-__global__ __launch_bounds__(kRankThreads) void k_splitters(const uint64_t* __restrict__ keys, int buckets,
-                                                            uint64_t* __restrict__ splitters, int sample_shift) {
+// Of the workgroup's kRankThreads / kRankLanes keys, the thread's one and its rank among the first `samples` (kMaxSamples at most) of load(i),
+// the same in its kRankLanes lanes.
+template <typename Load>
+__device__ __forceinline__ int rank_among(int samples, Load load, uint64_t* its_key) {
   __shared__ uint64_t sample[kMaxSamples];
   constexpr int kLoads = kMaxSamples / kRankThreads;
-  const int samples = 1 << sample_shift;                   // kRankLanes at least
   const int mine = int(blockIdx.x) * (kRankThreads / kRankLanes) + int(threadIdx.x) / kRankLanes;
   uint64_t v[kLoads];
-  const uint64_t* in = keys + int64_t(blockIdx.y) * kMaxSamples;
 #pragma unroll
   for (int u = 0; u < kLoads; ++u) {
     const int i = u * kRankThreads + int(threadIdx.x);
-    if (u * kRankThreads < samples) v[u] = in[i < samples ? i : samples - 1];
+    if (u * kRankThreads < samples) v[u] = load(i < samples ? i : samples - 1);
   }
 #pragma unroll
   for (int u = 0; u < kLoads; ++u)
@@ -318,9 +354,33 @@ __global__ __launch_bounds__(kRankThreads) void k_splitters(const uint64_t* __re
   }
 #pragma unroll
   for (int off = 1; off < kRankLanes; off <<= 1) rank += __shfl_xor(rank, off, 64);
-  const int each = samples / buckets;
-  if (threadIdx.x % kRankLanes == 0 && mine < samples && rank % each == each - 1 && rank / each < buckets - 1)
-    splitters[int64_t(blockIdx.y) * buckets + rank / each] = key;
+  *its_key = key;
+  return mine < samples ? rank : -1;
+}
+
+// splitter b: the sample of rank (b + 1) samples / buckets - 1; at least as many samples as buckets
+__global__ __launch_bounds__(kRankThreads) void k_splitters(const uint64_t* __restrict__ keys, int buckets,
+                                                            uint64_t* __restrict__ splitters, int samples) {
+  const uint64_t* in = keys + int64_t(blockIdx.y) * kMaxSamples;
+  uint64_t key;
+  const int rank = rank_among(samples, [&](int i) { return in[i]; }, &key);
+  if (threadIdx.x % kRankLanes != 0 || rank < 0) return;
+  const int b = int((int64_t(rank + 1) * buckets + samples - 1) / samples) - 1;
+  if (b >= 0 && b < buckets - 1 && int(int64_t(b + 1) * samples / buckets) - 1 == rank) splitters[int64_t(blockIdx.y) * buckets + b] = key;
+}
+
+// All keys are samples, and a key's rank is its place.  The last workgroup along x makes the parameters.
+__global__ __launch_bounds__(kRankThreads) void k_rank_sort(const uint64_t* __restrict__ keys, int n, uint64_t* __restrict__ sorted,
+                                                            const double* __restrict__ partials, int tiles,
+                                                            OperandParams* __restrict__ params) {
+  if (blockIdx.x + 1 == gridDim.x) {
+    mean_params(partials, tiles, params);
+    return;
+  }
+  const uint64_t* in = keys + int64_t(blockIdx.y) * n;
+  uint64_t key;
+  const int rank = rank_among(n, [&](int i) { return in[i]; }, &key);
+  if (threadIdx.x % kRankLanes == 0 && rank >= 0) sorted[int64_t(blockIdx.y) * n + rank] = key;
 }
 
 // buckets of kCount keys: 2 (number of splitters below it), and one more when it equals the next splitter.  The keys take
@@ -347,13 +407,15 @@ __device__ __forceinline__ int tile_of_group() { return int(blockIdx.x & 7u) * i
 // line of F is fetched for two bytes of it (the L2 asks for whole lines, whatever the load's scope): that is the time, 82 us for 2 x 2M of
 // them alone, and the search, the exponentials and the counting run behind it: 106 us, with a pass of its own for these 112 and 27.
 // Non-temporal loads: a line is used once (a plain gather 80 us instead of 88).  The next step's loads ahead of this one's work: 112.
-template <bool kCount>
-__global__ __launch_bounds__(kPassThreads) void k_means(const void* __restrict__ N1, const void* __restrict__ F1,
+// kSample: the key at sample_of_run's place in each run of kSampleRun goes to `samples`, too.
+template <bool kCount, int kThreadsOf = kPassThreads, int kPer = kMeansPerThread, bool kSample = false>
+__global__ __launch_bounds__(kThreadsOf) void k_means(const void* __restrict__ N1, const void* __restrict__ F1,
                                                         const void* __restrict__ N2, const void* __restrict__ F2, int ntype,
                                                         int itype, double scale, int64_t n, int64_t tile_keys, int tiles, int kept,
                                                         int buckets, const uint64_t* __restrict__ splitters,
                                                         uint64_t* __restrict__ keys, uint32_t* __restrict__ hist,
-                                                        uint32_t* __restrict__ rest, double* __restrict__ partials) {
+                                                        uint32_t* __restrict__ rest, double* __restrict__ partials,
+                                                        uint64_t* __restrict__ samples) {
   extern __shared__ __align__(16) uint64_t split[];         // [buckets], then the counts [2 buckets]
   uint32_t* count = reinterpret_cast<uint32_t*>(split + buckets);
   __shared__ double top;
@@ -361,8 +423,8 @@ __global__ __launch_bounds__(kPassThreads) void k_means(const void* __restrict__
   if (tile >= tiles) return;                                // uniform over the workgroup
   if (tile == 0 && blockIdx.y == 0 && threadIdx.x < 2) rest[threadIdx.x] = 0;
   if (kCount) {
-    for (int i = threadIdx.x; i < buckets - 1; i += kPassThreads) split[i] = splitters[int64_t(blockIdx.y) * buckets + i];
-    for (int i = threadIdx.x; i < 2 * buckets; i += kPassThreads) count[i] = 0;
+    for (int i = threadIdx.x; i < buckets - 1; i += kThreadsOf) split[i] = splitters[int64_t(blockIdx.y) * buckets + i];
+    for (int i = threadIdx.x; i < 2 * buckets; i += kThreadsOf) count[i] = 0;
     __syncthreads();
   }
   uint64_t* out = keys + int64_t(blockIdx.y) * n;
@@ -370,23 +432,24 @@ __global__ __launch_bounds__(kPassThreads) void k_means(const void* __restrict__
   const int64_t end = begin + tile_keys < n ? begin + tile_keys : n;
   double s = 0.0, m = -INFINITY, e = 0.0;
   with_loads(blockIdx.y ? N2 : N1, blockIdx.y ? F2 : F1, ntype, itype, kept, [&](auto load_n, auto load_f) {
-    for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kPassThreads * kMeansPerThread) {
-      double v[kMeansPerThread], f[kMeansPerThread];
+    for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += kThreadsOf * kPer) {
+      double v[kPer], f[kPer];
 #pragma unroll
-      for (int u = 0; u < kMeansPerThread; ++u) {
-        const int64_t i = i0 + u * kPassThreads < end ? i0 + u * kPassThreads : end - 1;
+      for (int u = 0; u < kPer; ++u) {
+        const int64_t i = i0 + u * kThreadsOf < end ? i0 + u * kThreadsOf : end - 1;
         f[u] = load_f(i);
         v[u] = load_n(i);
       }
-      uint64_t key[kMeansPerThread];
+      uint64_t key[kPer];
       double most = m;
 #pragma unroll
-      for (int u = 0; u < kMeansPerThread; ++u) {
-        const int64_t i = i0 + u * kPassThreads;
+      for (int u = 0; u < kPer; ++u) {
+        const int64_t i = i0 + u * kThreadsOf;
         v[u] = v[u] * f[u] * scale;
         key[u] = key_of(v[u]);
         if (i < end) {
           out[i] = key[u];
+          if (kSample && i == sample_of_run(i / kSampleRun, n)) samples[int64_t(blockIdx.y) * kMaxSamples + i / kSampleRun] = key[u];
           s += v[u];
           most = fmax(most, v[u]);
         }
@@ -395,16 +458,16 @@ __global__ __launch_bounds__(kPassThreads) void k_means(const void* __restrict__
       m = most;
       const double base = fmax(m, -1.7976931348623157e308);      // minus infinity weighs nothing, also where the thread has met nothing else
 #pragma unroll
-      for (int u = 0; u < kMeansPerThread; ++u) {
+      for (int u = 0; u < kPer; ++u) {
         const double x = exp(v[u] - base);
-        e += i0 + u * kPassThreads < end ? x : 0.0;
+        e += i0 + u * kThreadsOf < end ? x : 0.0;
       }
       if (kCount) {
-        int b[kMeansPerThread];
-        buckets_of<kMeansPerThread>(split, buckets, key, b);
+        int b[kPer];
+        buckets_of<kPer>(split, buckets, key, b);
 #pragma unroll
-        for (int u = 0; u < kMeansPerThread; ++u)
-          if (i0 + u * kPassThreads < end) atomicAdd(&count[b[u]], 1u);
+        for (int u = 0; u < kPer; ++u)
+          if (i0 + u * kThreadsOf < end) atomicAdd(&count[b[u]], 1u);
       }
     }
   });
@@ -424,7 +487,7 @@ __global__ __launch_bounds__(kPassThreads) void k_means(const void* __restrict__
   }
   if (kCount) {
     uint32_t* h = hist + (int64_t(blockIdx.y) * tiles + tile) * 2 * buckets;
-    for (int i = threadIdx.x; i < 2 * buckets; i += kPassThreads) h[i] = count[i];   // (group_sum_max has the barrier)
+    for (int i = threadIdx.x; i < 2 * buckets; i += kThreadsOf) h[i] = count[i];   // (group_sum_max has the barrier)
   }
 }
 
@@ -782,11 +845,111 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(int64_t n, int bucket
   }
 }
 
+constexpr int kBucketThreads = 1024;
+constexpr int kBucketWaves = kBucketThreads / 64;
+// v of lane (this one ^ kXor), by register moves; all lanes active
+template <int kXor>
+__device__ __forceinline__ uint32_t across(uint32_t v) {
+  if constexpr (kXor == 1) return uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0xb1, 0xf, 0xf, true));             // quad_perm
+  else if constexpr (kXor == 2) return uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x4e, 0xf, 0xf, true));
+  else if constexpr (kXor == 3) return uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x1b, 0xf, 0xf, true));
+  else if constexpr (kXor == 4) return across<7>(across<3>(v));
+  else if constexpr (kXor == 7) return uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x141, 0xf, 0xf, true));       // row_half_mirror
+  else if constexpr (kXor == 8) return uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x128, 0xf, 0xf, true));       // row_ror 8
+  else if constexpr (kXor == 15) return uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x140, 0xf, 0xf, true));      // row_mirror
+  else if constexpr (kXor == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (threadIdx.x & 16) ? r[0] : r[1];
+  } else if constexpr (kXor == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (threadIdx.x & 32) ? r[0] : r[1];
+  } else if constexpr (kXor == 31) return across<16>(across<15>(v));
+  else return across<32>(across<31>(v));
+}
+constexpr int top_bit(int v) { return v < 2 ? v : 2 * top_bit(v / 2); }
+// the smaller of the thread's key and that of thread (this one ^ kXor), the larger in the upper of the two
+template <int kXor>
+__device__ __forceinline__ uint64_t ordered(uint64_t mine, uint64_t other) {
+  constexpr uint32_t kUpper = uint32_t(top_bit(kXor));
+  return (other < mine) != ((threadIdx.x & kUpper) != 0) ? other : mine;
+}
+template <int kXor>
+__device__ __forceinline__ void exchange_in_wave(uint64_t& key) {
+  key = ordered<kXor>(key, uint64_t(across<kXor>(uint32_t(key))) | (uint64_t(across<kXor>(uint32_t(key >> 32))) << 32));
+}
+template <int kXor>
+__device__ __forceinline__ void halve_in_wave(uint64_t& key) {        // distances kXor, kXor / 2, ... 1
+  exchange_in_wave<kXor>(key);
+  if constexpr (kXor > 1) halve_in_wave<kXor / 2>(key);
+}
+template <int kRun>
+__device__ __forceinline__ void sort_in_wave(uint64_t& key) {         // runs of kRun / 2 to runs of kRun, and on to 64
+  exchange_in_wave<kRun - 1>(key);
+  if constexpr (kRun > 2) halve_in_wave<kRun / 4>(key);
+  if constexpr (kRun < 64) sort_in_wave<2 * kRun>(key);
+}
+// A step between waves: key j of thread t is number j kBucketThreads + t, the exchanges are with number ^ kXor.  kTwo: two buffers in turn, so
+// that one barrier a step is enough.
+template <int kXor, int kPer, bool kTwo>
+__device__ __forceinline__ void exchange_in_group(uint64_t* key, uint64_t* lds, int& turn) {
+  constexpr int kOther = kXor / kBucketThreads, kThread = kXor % kBucketThreads;
+  uint64_t* at = lds + (kTwo ? turn * kPer * kBucketThreads : 0);
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) at[j * kBucketThreads + int(threadIdx.x)] = key[j];
+  __syncthreads();
+  constexpr int kUpper = top_bit(kXor);
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint64_t other = at[(j ^ kOther) * kBucketThreads + (int(threadIdx.x) ^ kThread)];
+    if constexpr (kUpper >= kBucketThreads) key[j] = (other < key[j]) != ((j & (kUpper / kBucketThreads)) != 0) ? other : key[j];
+    else key[j] = ordered<kXor>(key[j], other);
+  }
+  if (!kTwo) __syncthreads();
+  turn ^= 1;
+}
+template <int kXor, int kPer, bool kTwo>
+__device__ __forceinline__ void halve_in_group(uint64_t* key, uint64_t* lds, int& turn) {       // distances kXor, kXor / 2, ... 64
+  if constexpr (kXor >= kBucketThreads) {
+    constexpr int d = kXor / kBucketThreads;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+      if ((j & d) == 0) {
+        const uint64_t a = key[j], b = key[j | d];
+        key[j] = b < a ? b : a;
+        key[j | d] = b < a ? a : b;
+      }
+  } else {
+    exchange_in_group<kXor, kPer, kTwo>(key, lds, turn);
+  }
+  if constexpr (kXor > 64) halve_in_group<kXor / 2, kPer, kTwo>(key, lds, turn);
+}
+template <int kRun, int kPer, bool kTwo>
+__device__ __forceinline__ void merge_in_group(uint64_t* key, int count, uint64_t* lds, int& turn) {
+  if (kRun / 2 >= count) return;                           // uniform
+  exchange_in_group<kRun - 1, kPer, kTwo>(key, lds, turn);
+  if constexpr (kRun > 128) halve_in_group<kRun / 4, kPer, kTwo>(key, lds, turn);
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)                           // (the waves beyond have nothing but what pads the keys)
+    if (j * kBucketThreads + int(threadIdx.x & ~63u) < count) halve_in_wave<32>(key[j]);
+  if constexpr (kRun < kPer * kBucketThreads) merge_in_group<2 * kRun, kPer, kTwo>(key, count, lds, turn);
+}
+// Ascending order of the workgroup's keys, kPer a thread (the largest number from `count` on): bitonic merges whose first step folds a run onto
+// itself, so that all exchanges are ascending.  Of the 55 steps of 1024 keys 45 are between lanes, register moves without LDS.  No step depends
+// on the keys: 4 us for 1024 and 12 for 4096 whatever they are, where dealing them into intervals takes 7 to 20.  (Many uncrowded buckets, as in
+// k_bucket_sort, are the intervals': 1M keys 87 us by exchanges, 83 as there.)  lds: kPer kBucketThreads keys, twice that with kTwo; the first
+// half is written first.
+template <int kPer, bool kTwo>
+__device__ __forceinline__ void sort_group(uint64_t* key, int count, uint64_t* lds) {
+  int turn = 0;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if (j * kBucketThreads + int(threadIdx.x & ~63u) < count) sort_in_wave<2>(key[j]);
+  merge_in_group<128, kPer, kTwo>(key, count, lds, turn);
+}
+
 constexpr int kSubs = 2048;
 constexpr int kMaxSub = 128;
 constexpr int kRestGroups = 64;                  // workgroups of the second sorting kernel
-constexpr int kBucketThreads = 1024;
-constexpr int kBucketWaves = kBucketThreads / 64;
 constexpr int kOwnSplitters = 256;               // that a crowded bucket draws from its keys ...
 constexpr int kOwnSlots = kSubs / kOwnSplitters; // ... and the intervals below each: the last for the keys that equal it
 
@@ -838,24 +1001,19 @@ __device__ __forceinline__ void group_bounds(uint64_t& lo, uint64_t& hi, uint64_
 
 // Bucket b of operand y: its first key and, for 2 b, its number of keys (sums: scratch of one value per wave)
 struct BucketPlace { int64_t base, m, equal; };
-__device__ __forceinline__ BucketPlace bucket_place(int b, int operand, int64_t n, int buckets, const uint32_t* totals,
-                                                    uint32_t* sums) {
+__device__ __forceinline__ BucketPlace bucket_place(int b, int operand, int buckets, const uint32_t* totals, uint32_t* sums) {
   BucketPlace p;
+  const uint32_t* t = totals + int64_t(operand) * 2 * buckets;
+  uint32_t sum = 0;
+  for (int i = threadIdx.x; i < 2 * b; i += kBucketThreads) sum += t[i];
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = sum;
+  __syncthreads();
   p.base = 0;
-  p.m = n;
-  p.equal = 0;
-  if (buckets > 1) {
-    const uint32_t* t = totals + int64_t(operand) * 2 * buckets;
-    uint32_t sum = 0;
-    for (int i = threadIdx.x; i < 2 * b; i += kBucketThreads) sum += t[i];
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    for (int w = 0; w < kBucketWaves; ++w) p.base += sums[w];
-    p.m = t[2 * b];
-    p.equal = t[2 * b + 1];
-  }
+  for (int w = 0; w < kBucketWaves; ++w) p.base += sums[w];
+  p.m = t[2 * b];
+  p.equal = t[2 * b + 1];
   return p;
 }
 
@@ -865,9 +1023,9 @@ __device__ __forceinline__ BucketPlace bucket_place(int b, int operand, int64_t 
 // largest of their values (between neighbouring quantiles the means are spread nearly evenly: one key an interval), put
 // together by interval in LDS, at most kBucketCap keys a round, and every key counts the smaller ones of its interval.
 // Where that leaves more than kMaxSub keys in one interval (values over many orders of magnitude, as in the first and the last
-// bucket, or where there is one bucket only) or meets NaN, which has no interval among the values, the intervals are taken between
-// splitters drawn from the bucket itself (4096 means of 8x8 blocks: sort 84 -> 26 us, the distance 111 -> 46).  Larger buckets and those that
-// are crowded even so go to the list of k_bucket_sort_rest.  With one bucket in == out.
+// bucket) or meets NaN, which has no interval among the values, the intervals are taken between
+// splitters drawn from the bucket itself (4096 means of 8x8 blocks: 84 -> 26 us).  Larger buckets and those that
+// are crowded even so go to the list of k_bucket_sort_rest.
 constexpr int kHeldKeys = 8192;
 // above, the pieces of a bucket are at most twice its keys / kPieceKeys, those of both operands at most 2 * 2 n / kPieceKeys <= K
 constexpr int kPieceKeys = 4 * kBucketKeys;
@@ -881,7 +1039,7 @@ __device__ __forceinline__ void sort_bucket(int bucket, bool sorts, bool copies,
   __shared__ double2 bounds[kBucketWaves];
   __shared__ uint64_t split[kOwnSplitters], drawn[kOwnSplitters];
   constexpr int kPerThread = kHeldKeys / kBucketThreads;
-  const BucketPlace place = bucket_place(bucket, blockIdx.y, n, buckets, totals, wave_total);
+  const BucketPlace place = bucket_place(bucket, blockIdx.y, buckets, totals, wave_total);
   const uint64_t* in = in_all + int64_t(blockIdx.y) * n + place.base;
   uint64_t* out = out_all + int64_t(blockIdx.y) * n + place.base;
   if (!copies) {
@@ -1071,11 +1229,22 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_sort_rest(const uint6
   }
   for (uint32_t r = blockIdx.x; r < listed; r += gridDim.x) {
     const uint32_t which = rest[2 + r];
-    const BucketPlace bucket = bucket_place(int(which >> 1), int(which & 1u), n, buckets, totals, wave_total);
+    const BucketPlace bucket = bucket_place(int(which >> 1), int(which & 1u), buckets, totals, wave_total);
     const uint64_t* in = in_all + int64_t(which & 1u) * n + bucket.base;
     uint64_t* out = out_all + int64_t(which & 1u) * n + bucket.base;
     const int64_t m = bucket.m;
-    const bool fits = m <= kBucketCap;
+    if (m <= kBucketCap) {                                 // by exchanges, whatever the values: 12 us where the rounds below took 37 to 46
+      uint64_t mine[kPerThread];
+#pragma unroll
+      for (int j = 0; j < kPerThread; ++j)
+        mine[j] = j * kBucketThreads + int(threadIdx.x) < m ? in[j * kBucketThreads + int(threadIdx.x)] : ~uint64_t(0);
+      sort_group<kPerThread, false>(mine, int(m), key);
+#pragma unroll
+      for (int j = 0; j < kPerThread; ++j)
+        if (j * kBucketThreads + int(threadIdx.x) < m) out[j * kBucketThreads + int(threadIdx.x)] = mine[j];
+      __syncthreads();
+      continue;
+    }
     // calls f(key) for the thread's keys, kPerThread of them requested together
     auto each = [&](auto f) {
       for (int64_t i0 = threadIdx.x; i0 < m; i0 += kBucketCap) {
@@ -1111,20 +1280,17 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_sort_rest(const uint6
       bool again = false;
       for (int s0 = 0; s0 < kSubs;) {
         // intervals s0 .. s1 - 1 fit; the same in every thread
-        int s1 = kSubs;
-        if (!fits) {
-          s1 = s0;
-          for (int step = kSubs; step > 0; step >>= 1)
-            if (s1 + step <= kSubs && first[s1 + step] - first[s0] <= uint32_t(kBucketCap)) s1 += step;
-          if (s1 == s0) {                                    // an interval larger than LDS
-            if (by_value) {
-              again = true;
-              break;
-            }
-            for (int64_t i = threadIdx.x; i < m; i += kBucketThreads) out[i] = in[i];
-            fold_sort<int64_t>(out, m);
+        int s1 = s0;
+        for (int step = kSubs; step > 0; step >>= 1)
+          if (s1 + step <= kSubs && first[s1 + step] - first[s0] <= uint32_t(kBucketCap)) s1 += step;
+        if (s1 == s0) {                                      // an interval larger than LDS
+          if (by_value) {
+            again = true;
             break;
           }
+          for (int64_t i = threadIdx.x; i < m; i += kBucketThreads) out[i] = in[i];
+          fold_sort<int64_t>(out, m);
+          break;
         }
         const uint32_t from = first[s0];
         const int count = int(first[s1] - from);
@@ -1186,6 +1352,117 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_sort_rest(const uint6
       if (!again) break;
       by_value = false;
     }
+  }
+}
+
+// ---- up to kRangeMax keys: each workgroup finds its own range of them -----------------------------------------------
+// Up to kBucketThreads blocks: one workgroup of an operand makes the keys, one a thread, the parameters, and the order.
+__global__ __launch_bounds__(kBucketThreads) void k_means_in_order(const void* __restrict__ N1, const void* __restrict__ F1, const void* __restrict__ N2,
+                                                                   const void* __restrict__ F2, int ntype, int itype, double scale, int n, int kept,
+                                                                   uint64_t* __restrict__ sorted, OperandParams* __restrict__ params) {
+  __shared__ uint64_t lds[2 * kBucketThreads];
+  __shared__ double top;
+  const int t = int(threadIdx.x), at = t < n ? t : n - 1;
+  double v = 0.0;
+  with_loads(blockIdx.y ? N2 : N1, blockIdx.y ? F2 : F1, ntype, itype, kept, [&](auto load_n, auto load_f) {
+    const double f = load_f(at), x = load_n(at);
+    v = x * f * scale;
+  });
+  uint64_t key = t < n ? key_of(v) : ~uint64_t(0);
+  double s = t < n ? v : 0.0, m = t < n ? fmax(v, -INFINITY) : -INFINITY;
+  group_sum_max(s, m);
+  if (t == 0) {
+    OperandParams& p = params[blockIdx.y];
+    p.sum = s;
+    p.max = m;
+    p.use_softmax = fabs(s - 1.0) > kSumTolerance ? 1.0 : 0.0;
+    top = m;
+  }
+  __syncthreads();
+  m = fmax(top, -1.7976931348623157e308);                  // minus infinity weighs nothing
+  double e = t < n ? exp(v - m) : 0.0, none = 0.0;
+  group_sum_max(e, none);
+  if (t == 0) params[blockIdx.y].exp_sum = e;
+  sort_group<1, true>(&key, n, lds);
+  if (t < n) sorted[int64_t(blockIdx.y) * n + t] = key;
+}
+
+// Workgroup b of an operand goes through all of its keys, which its L2 holds, counts those below its own range (between
+// two splitters, the upper one included), and sorts those in it: no counting of buckets, no scattering, no list of what is left over.  More than
+// kBucketThreads, and the range ends at one of them instead, and goes on from there: at a place among those that were collected that leaves
+// out a third of them at least.  The last workgroup along x makes the parameters.  Bounds: the reads from L2 (64 bytes a cycle and compute unit)
+// and the compares, 20 us for 2 x 65536 keys; the exchanges, 4 us, from 16384 keys down (11 us).
+constexpr int kRangeInFlight = 16;
+__global__ __launch_bounds__(kBucketThreads) void k_range_sort(const uint64_t* __restrict__ keys, uint64_t* __restrict__ sorted, int n, int buckets,
+                                                               const uint64_t* __restrict__ splitters, const double* __restrict__ partials,
+                                                               int tiles, OperandParams* __restrict__ params) {
+  if (int(blockIdx.x) == buckets) {
+    mean_params(partials, tiles, params);
+    return;
+  }
+  __shared__ uint64_t lds[2 * kBucketThreads];              // the second half also: the keys of the range as they come
+  __shared__ int counted[3];                               // keys below the range, equal to its end, inside
+  __shared__ uint64_t cut;
+  const uint64_t* in = keys + int64_t(blockIdx.y) * n;
+  uint64_t* out = sorted + int64_t(blockIdx.y) * n;
+  const uint64_t* split = splitters + int64_t(blockIdx.y) * buckets;
+  const int t = int(threadIdx.x), b = int(blockIdx.x);
+  uint64_t from = b > 0 ? split[b - 1] + 1u : 0u;           // (no key is the largest number)
+  const uint64_t last = b < buckets - 1 ? split[b] : ~uint64_t(0);
+  uint64_t end = last;
+  if (from > last) return;                                 // uniform: equal splitters
+  for (;;) {
+    if (t < 3) counted[t] = 0;
+    __syncthreads();
+    int below = 0, equal = 0;
+    const uint64_t span = end - from;
+    for (int i0 = 0; i0 < n; i0 += kBucketThreads * kRangeInFlight) {
+      uint64_t k[kRangeInFlight];
+#pragma unroll
+      for (int u = 0; u < kRangeInFlight; ++u) {           // beyond the last: the largest number, which no key is
+        const int i = i0 + u * kBucketThreads + t;
+        k[u] = in[i < n ? i : n - 1];
+        if (i >= n) k[u] = ~uint64_t(0);
+      }
+#pragma unroll
+      for (int u = 0; u < kRangeInFlight; ++u) {
+        below += k[u] < from ? 1 : 0;
+        if (k[u] - from <= span) {
+          if (k[u] == end) ++equal;                        // (also what is beyond the last, where the range has no end)
+          else {
+            const int at = atomicAdd(&counted[2], 1);
+            if (at < kBucketThreads) lds[kBucketThreads + at] = k[u];
+          }
+        }
+      }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      below += __shfl_xor(below, off, 64);
+      equal += __shfl_xor(equal, off, 64);
+    }
+    if ((t & 63) == 0) {
+      atomicAdd(&counted[0], below);
+      atomicAdd(&counted[1], equal);
+    }
+    __syncthreads();
+    const int inside = counted[2], m = inside < kBucketThreads ? inside : kBucketThreads;
+    below = counted[0];
+    equal = counted[1];
+    uint64_t key = t < m ? lds[kBucketThreads + t] : ~uint64_t(0);
+    sort_group<1, true>(&key, m, lds);
+    if (inside > kBucketThreads) {
+      if (t == int(int64_t(kBucketThreads) * (kBucketThreads * 2 / 3) / inside)) cut = key;
+      __syncthreads();
+      end = cut;                                           // below the old end
+      continue;
+    }
+    if (t < m) out[below + t] = key;
+    if (end != ~uint64_t(0))
+      for (int i = t; i < equal; i += kBucketThreads) out[below + m + i] = end;
+    if (end == last) break;                                // uniform
+    from = end + 1u;
+    end = last;
+    __syncthreads();
   }
 }
 
@@ -1458,6 +1735,84 @@ __global__ __launch_bounds__(kStatGroups) void k_distance_final(const double* __
   if (g == 0) out[0] = m > 0.0 ? m * pow(s / n, 1.0 / order) : 0.0;
 }
 
+// The same of few ranks, in one workgroup and without a second launch
+constexpr int kOneGroupThreads = 1024;
+__global__ __launch_bounds__(kOneGroupThreads) void k_distance_of_few(const uint64_t* __restrict__ sorted, int n, const OperandParams* __restrict__ params,
+                                                                      double order, double least, double* __restrict__ out) {
+  __shared__ double top;
+  constexpr int kEach = kMaxSamples / kOneGroupThreads;
+  const OperandParams pa = params[0], pb = params[1];
+  uint64_t a[kEach], b[kEach];
+#pragma unroll
+  for (int u = 0; u < kEach; ++u)
+    if (u * kOneGroupThreads < n) {
+      const int i = u * kOneGroupThreads + int(threadIdx.x) < n ? u * kOneGroupThreads + int(threadIdx.x) : n - 1;
+      a[u] = sorted[i];
+      b[u] = sorted[n + i];
+    }
+  double d[kEach], s = 0.0, m = 0.0;
+#pragma unroll
+  for (int u = 0; u < kEach; ++u) {
+    d[u] = 0.0;
+    if (u * kOneGroupThreads < n)
+      d[u] = u * kOneGroupThreads + int(threadIdx.x) < n ? fabs(mapped(a[u], pa) - mapped(b[u], pb)) : 0.0;
+    m = fmax(m, d[u]);
+  }
+  group_sum_max(s, m);
+  if (threadIdx.x == 0) top = m;
+  __syncthreads();
+  m = top;
+  s = 0.0;
+#pragma unroll
+  for (int u = 0; u < kEach; ++u) {
+    if (d[u] != d[u]) s += d[u];
+    else if (m > 0.0 && !(d[u] < least * m)) {
+      const double x = d[u] / m;
+      if (!(x < least)) s += pow(x, order);
+    }
+  }
+  double none = 0.0;
+  group_sum_max(s, none);
+  if (threadIdx.x == 0) out[0] = m > 0.0 ? m * pow(s / double(n), 1.0 / order) : 0.0;
+}
+
+// Up to kRangeMax blocks: few launches, of kernels that go through all keys again rather than have them counted and scattered.
+int launch_few(int64_t n, int kept, const void* N1, const void* F1, const void* N2, const void* F2, int nt, int it, double scale, double order, double least,
+               double* out, const Workspace& w, hipStream_t s) {
+  if (n <= kBucketThreads) {
+    hipLaunchKernelGGL(k_means_in_order, dim3(1, 2), dim3(kBucketThreads), 0, s, N1, F1, N2, F2, nt, it, scale, int(n), kept, w.buf0, w.params);
+    hipLaunchKernelGGL(k_distance_of_few, dim3(1), dim3(kOneGroupThreads), 0, s, w.buf0, int(n), w.params, order, least, out);
+    return hip_status(hipGetLastError());
+  }
+  constexpr int kFewThreads = 256;
+  int64_t tile_keys = kFewThreads;
+  if (n > tile_keys * kMaxTiles) tile_keys = (n + kMaxTiles - 1) / kMaxTiles;
+  const int tiles = int((n + tile_keys - 1) / tile_keys);
+  const int samples = int((n + kSampleRun - 1) / kSampleRun);      // in the sorted keys' place, which have none yet
+  const auto means = n <= kMaxSamples ? k_means<false, kFewThreads, 1> : tile_keys > kFewThreads ? k_means<false, kFewThreads, 2, true> : k_means<false, kFewThreads, 1, true>;
+  hipLaunchKernelGGL(means, dim3(unsigned((tiles + 7) / 8 * 8), 2), dim3(kFewThreads), 0, s, N1, F1, N2, F2, nt, it, scale, n, tile_keys, tiles, kept, 1,
+                     nullptr, w.buf1, nullptr, w.rest, w.partials, w.buf0);
+  constexpr int kPerGroup = kRankThreads / kRankLanes;
+  if (n <= kMaxSamples) {
+    hipLaunchKernelGGL(k_rank_sort, dim3(unsigned((n + kPerGroup - 1) / kPerGroup + 1), 2), dim3(kRankThreads), 0, s, w.buf1, int(n), w.buf0, w.partials, tiles,
+                       w.params);
+    hipLaunchKernelGGL(k_distance_of_few, dim3(1), dim3(kOneGroupThreads), 0, s, w.buf0, int(n), w.params, order, least, out);
+    return hip_status(hipGetLastError());
+  }
+  int buckets = 1;
+  while (int64_t(buckets) * kRangeKeys < n) buckets *= 2;
+  // the splitters take the place of the counts, which are not needed here: those are 16 bytes a tile of kMinTileKeys and bucket of kBucketKeys, rounded
+  // up to 256 in all, these 16 bytes a range, of which there are at most four for such a bucket, and three or four tiles at least
+  uint64_t* splitters = reinterpret_cast<uint64_t*>(w.hist);
+  hipLaunchKernelGGL(k_splitters, dim3((samples + kPerGroup - 1) / kPerGroup, 2), dim3(kRankThreads), 0, s, w.buf0, buckets, splitters, samples);
+  hipLaunchKernelGGL(k_range_sort, dim3(buckets + 1, 2), dim3(kBucketThreads), 0, s, w.buf1, w.buf0, int(n), buckets, splitters, w.partials, tiles, w.params);
+  const int64_t chunk = ((n + kStatGroups - 1) / kStatGroups + kThreads - 1) / kThreads * kThreads;
+  const int groups = int((n + chunk - 1) / chunk);
+  hipLaunchKernelGGL(k_distance, dim3(groups), dim3(kThreads), 0, s, w.buf0, n, chunk, w.params, order, least, nullptr, w.ranks, w.partials);
+  hipLaunchKernelGGL(k_distance_final, dim3(1), dim3((groups + 63) / 64 * 64), 0, s, w.partials, groups, double(n), order, out);
+  return hip_status(hipGetLastError());
+}
+
 }  // namespace
 
 size_t wasserstein_workspace_bytes(int64_t n_blocks) { return carve(nullptr, n_blocks, nullptr); }
@@ -1473,25 +1828,30 @@ int launch_approximate_wasserstein(const pbz_codec* c, int64_t n, const void* N1
   const double least = std::exp2(-100.0 / order);
   const int K = plan.buckets;
   const int nt = int(c->ftype), it = int(c->itype);
+  if (n <= kRangeMax) return launch_few(n, c->kept, N1, F1, N2, F2, nt, it, scale, order, least, out, w, s);
   const bool select = plan.sample && K >= kSelectMin;
   const dim3 pass_grid(unsigned((plan.tiles + 7) / 8 * 8), 2);
   const size_t pass_bytes = size_t(K) * 16;
-  if (K > 1) {
+  if (plan.sample) {
     int sample_shift = 0;
-    while ((1 << sample_shift) < 4 * K && (1 << sample_shift) < kMaxSamples) ++sample_shift;
+    // four a bucket, two where there are 2048 buckets; more where buckets are large on average, as one of over kBucketCap keys that are crowded
+    // goes to k_bucket_sort_rest in several rounds (262144 blocks of an image: 114 us with four, 62 with sixteen; where no bucket is like
+    // that, more samples cost 2 to 5 us)
+    const int per_bucket = n > int64_t(K) * 1400 ? 16 : (n > int64_t(K) * 1100 ? 8 : 4), most = K <= 256 ? 2048 : kMaxSamples;
+    while ((1 << sample_shift) < (K <= 256 ? per_bucket : 4) * K && (1 << sample_shift) < most) ++sample_shift;
     constexpr int kPerGroup = kRankThreads / kRankLanes;
     static_assert(kBucketCap >= kMaxSamples, "the samples of both operands fit the keys' place");
     hipLaunchKernelGGL(k_samples, dim3(((1 << sample_shift) + 63) / 64, 2), dim3(64), 0, s, N1, F1, N2, F2, nt, it, scale, c->kept, n,
                        sample_shift, w.buf1);
     hipLaunchKernelGGL(k_splitters, dim3(((1 << sample_shift) + kPerGroup - 1) / kPerGroup, 2), dim3(kRankThreads), 0, s, w.buf1, K,
-                       w.splitters, sample_shift);
+                       w.splitters, 1 << sample_shift);
     hipLaunchKernelGGL(k_means<true>, pass_grid, dim3(kPassThreads), pass_bytes, s, N1, F1, N2, F2, nt, it, scale, n, plan.tile_keys,
-                       plan.tiles, c->kept, K, w.splitters, w.buf0, w.hist, w.rest, w.partials);
+                       plan.tiles, c->kept, K, w.splitters, w.buf0, w.hist, w.rest, w.partials, nullptr);
   } else {
     hipLaunchKernelGGL(k_means<false>, pass_grid, dim3(kPassThreads), 0, s, N1, F1, N2, F2, nt, it, scale, n, plan.tile_keys,
-                       plan.tiles, c->kept, K, w.splitters, w.buf0, w.hist, w.rest, w.partials);
+                       plan.tiles, c->kept, K, w.splitters, w.buf0, w.hist, w.rest, w.partials, nullptr);
   }
-  const int scan_groups = K > 1 ? (2 * K + 63) / 64 : 0;
+  const int scan_groups = plan.sample ? (2 * K + 63) / 64 : 0;
   hipLaunchKernelGGL(k_bucket_scan, dim3(scan_groups + 1, 2), dim3(64 * kScanWaves), 0, s, w.hist, plan.tiles, 2 * K, w.sums,
                      w.partials, w.params);
   int st = hip_status(hipGetLastError());
@@ -1502,13 +1862,11 @@ int launch_approximate_wasserstein(const pbz_codec* c, int64_t n, const void* N1
       const auto k = 2 * K <= kSelectThreads ? k_select<1> : (2 * K <= 2 * kSelectThreads ? k_select<2> : k_select<4>);
       hipLaunchKernelGGL(k, dim3(1), dim3(kSelectThreads), 0, s, n, K, w.splitters, w.sums, w.params, least, w.gap, w.needed, w.ranks);
     }
-    if (K > 1)
-      hipLaunchKernelGGL(k_scatter, pass_grid, dim3(kPassThreads), pass_bytes, s, w.buf0, w.buf1, n, plan.tile_keys, plan.tiles, K,
-                         w.splitters, w.hist, w.sums, select ? w.gap : nullptr);
-    const uint64_t* grouped = K > 1 ? w.buf1 : w.buf0;
-    hipLaunchKernelGGL(k_bucket_sort, dim3(K, 2), dim3(kBucketThreads), 0, s, grouped, w.buf0, n, K, w.sums, w.rest,
+    hipLaunchKernelGGL(k_scatter, pass_grid, dim3(kPassThreads), pass_bytes, s, w.buf0, w.buf1, n, plan.tile_keys, plan.tiles, K,
+                       w.splitters, w.hist, w.sums, select ? w.gap : nullptr);
+    hipLaunchKernelGGL(k_bucket_sort, dim3(K, 2), dim3(kBucketThreads), 0, s, w.buf1, w.buf0, n, K, w.sums, w.rest,
                        w.pieces, select ? w.needed : nullptr);
-    hipLaunchKernelGGL(k_bucket_sort_rest, dim3(2 * K < kRestGroups ? 2 * K : kRestGroups), dim3(kBucketThreads), 0, s, grouped,
+    hipLaunchKernelGGL(k_bucket_sort_rest, dim3(2 * K < kRestGroups ? 2 * K : kRestGroups), dim3(kBucketThreads), 0, s, w.buf1,
                        w.buf0, n, K, w.sums, w.rest, w.pieces);
   } else {
     const int64_t n_tiles = (n + kTileKeys - 1) / kTileKeys;
