@@ -275,7 +275,8 @@ int pbz_compress(const pbz_codec* c, const void* x, pbz_ftype x_type, const int6
   c->used.store(true);
   if (c->path == PBZ_PATH_AUTO) {
     const char* name = nullptr;
-    int r = try_compress_fast(c, g, x, x_type, N, F, s, false, &name);
+    int r = try_compress_shape_first(c, g, x, x_type, N, F, s, false);
+    if (r == 0) r = try_compress_fast(c, g, x, x_type, N, F, s, false, &name);
     if (r != 0) return r < 0 ? r : PBZ_OK;
   }
   const DeviceTables* t = nullptr;
@@ -347,7 +348,8 @@ int pbz_decompress(const pbz_codec* c, const void* N, const void* F, const int64
   c->used.store(true);
   if (c->path == PBZ_PATH_AUTO) {
     const char* name = nullptr;
-    int r = try_decompress_fast(c, g, N, F, y, y_type, s, false, &name);
+    int r = try_decompress_shape_first(c, g, N, F, y, y_type, s, false);
+    if (r == 0) r = try_decompress_fast(c, g, N, F, y, y_type, s, false, &name);
     if (r != 0) return r < 0 ? r : PBZ_OK;
   }
   const DeviceTables* t = nullptr;
@@ -373,12 +375,15 @@ const char* pbz_kernel_name(const pbz_codec* c, const char* op, const int64_t* s
     void* aligned = reinterpret_cast<void*>(uintptr_t(256));
     const char* fast = nullptr;
     int r = 0;
-    if (std::strcmp(op, "compress") == 0)
-      r = try_compress_fast(c, g, aligned, array_type, aligned, aligned, nullptr, true, &fast);
-    else if (std::strcmp(op, "decompress") == 0)
-      r = try_decompress_fast(c, g, aligned, aligned, aligned, array_type, nullptr, true, &fast);
-    else
+    if (std::strcmp(op, "compress") == 0) {
+      if (try_compress_shape_first(c, g, aligned, array_type, aligned, aligned, nullptr, true) == 0)
+        r = try_compress_fast(c, g, aligned, array_type, aligned, aligned, nullptr, true, &fast);
+    } else if (std::strcmp(op, "decompress") == 0) {
+      if (try_decompress_shape_first(c, g, aligned, aligned, aligned, array_type, nullptr, true) == 0)
+        r = try_decompress_fast(c, g, aligned, aligned, aligned, array_type, nullptr, true, &fast);
+    } else {
       return nullptr;
+    }
     if (r == 1 && fast) name = fast;
   } else if (std::strcmp(op, "compress") != 0 && std::strcmp(op, "decompress") != 0) {
     return nullptr;
@@ -398,8 +403,11 @@ int pbz_internal_route(const pbz_codec* c, int decompress, const int64_t* shape,
     void* const f = reinterpret_cast<void*>(uintptr_t(256));
     const char* name = nullptr;
     const DeviceTables none;
-    int r = decompress ? try_decompress_fast(c, g, f, f, a, array_type, nullptr, true, &name)
-                       : try_compress_fast(c, g, a, array_type, f, f, nullptr, true, &name);
+    int r = decompress ? try_decompress_shape_first(c, g, f, f, a, array_type, nullptr, true)
+                       : try_compress_shape_first(c, g, a, array_type, f, f, nullptr, true);
+    if (r != 0) return kRouteShape;
+    r = decompress ? try_decompress_fast(c, g, f, f, a, array_type, nullptr, true, &name)
+                   : try_compress_fast(c, g, a, array_type, f, f, nullptr, true, &name);
     if (r != 0) return kRouteExact;
     r = decompress ? try_decompress_masked(c, g, nullptr, f, f, a, array_type, nullptr, true)
                    : try_compress_masked(c, g, nullptr, a, array_type, f, f, nullptr, true);

@@ -46,6 +46,73 @@
 
 namespace pbz {
 
+// When the kernels per block shape (pbz_brick.h) take a call that a family has kernels for.  A family deals out the blocks of a row, 64 (lane), 16
+// (quad16) or 8 (oct8) to a wave: where rows have fewer, lanes idle, and a wave does as much for one block as for all; and where rows are no
+// whole blocks its lane and FP64 kernels take what is beyond the whole pieces element by element.  The kernels per block shape go by block
+// number and shift whole pieces into place.  The family keeps the call while its waves are too few to fill the chip, its own one wave being the
+// faster (1.1-1.4), and where a wave is full enough.  Measured for 2^16 to 2^25.5 elements in rows of 1 to 256 blocks, whole and not, family ->
+// here: FP32 / i8 in 8x8, 2^24 elements in rows of 2, 8 and 24 blocks, compress 0.13, 0.43, 0.86 of the time, decompress 0.14, 0.44, 0.83;
+// FP64 / i16 in 4x4x4 0.16, 0.55, 1.09; in rows that are no whole blocks, of 128 blocks, FP64 / i16 8x8 0.70 and 0.86, FP64 / i8 0.61 and 0.6, FP32 / i16
+// 16x16 0.83.  Over all measured widths and sizes 0.45-0.85 for lane, 0.75-0.95 for quad16, 0.7-0.97 for oct8; worst 1.2 (FP64 / i8
+// lane in rows of 60 whole blocks).  Calls under a mask have MaskedCall's rules.
+static bool shape_kernels_pay(const pbz_codec* c, const fast::Folded& f, int xtype, bool compress) {
+  const fast::FastGeom& g = f.g;
+  const bool flat = f.bz == 1, lane = (flat && f.by == 8 && f.bx == 8) || (f.bz == 4 && f.by == 4 && f.bx == 4);
+  const bool quad = flat && f.by == 16 && f.bx == 16, oct = f.bz == 8 && f.by == 8 && f.bx == 8;
+  if (!lane && !quad && !oct) return false;
+  const int per_wave = lane ? 64 : (quad ? 16 : 8);
+  const int64_t tiles = (g.gx + per_wave - 1) / per_wave, waves = g.gz * g.gy * tiles;
+  const int64_t blocks = g.gz * g.gy * g.gx;
+  if (blocks * f.bz * f.by * f.bx < int64_t(1) << 16) return false;      // a few us whichever way
+  const double fill = double(g.gx) / double(tiles * per_wave);
+  const int array = ftype_bytes(xtype), index = itype_bytes(c->itype);
+  const bool ragged = f.tail_x, wide = c->compute_f64;
+  const auto from = [&](int64_t least_waves, double most_fill) { return waves >= least_waves && fill <= most_fill; };
+  constexpr double kAny = 1.0, kNotFull = 0.95;
+  if (lane && compress) {
+    if (!ragged) return from(index == 1 && array < 8 ? 2800 : 2000, array == 8 ? (flat ? 0.5 : 0.35) : (index == 1 ? 0.35 : (index == 2 ? 0.3 : 0.15)));
+    if (array == 8 || (flat && index == 1)) return true;
+    return index == 1 ? from(2000, kAny) : from(1400, 0.35);
+  }
+  if (lane && !flat) {
+    if (fill <= 0.15) return true;
+    if (!ragged) return from(2500, array == 8 && !wide ? 0.35 : (index == 4 ? 0.15 : 0.2));
+    return from(2000, index == 2 ? 0.4 : (array == 8 ? 0.3 : 0.25));
+  }
+  if (lane) {
+    if (!ragged) return from(2500, index == 4 ? 0.15 : (index == 2 && array == 4 ? 0.25 : (array == 8 ? 0.5 : 0.45)));
+    if (array == 2) return true;
+    if (array == 8) return from(700, kAny);
+    return index == 1 ? from(2800, kAny) : from(2000, 0.4);
+  }
+  if (quad && compress) {
+    const bool late = array == 8 ? !wide : index == 1;                   // FP32 arithmetic
+    if (ragged) return from(late ? 2000 : 0, array == 8 ? 0.85 : kAny);
+    if (array == 8 && !wide) return from(1400, 0.4);
+    return late ? from(2000, 0.9) : from(700, index == 2 && array == 4 ? 0.85 : kNotFull);
+  }
+  if (quad) {
+    if (array == 8 && wide) return from(2000, ragged ? kAny : kNotFull);
+    return from(0, 0.5);
+  }
+  if (compress) return ragged && array == 8 ? true : from(2000, index == 1 && array == 4 ? 0.9 : 0.65);
+  if (ragged) return array == 8 ? true : (array == 4 && from(2800, index == 1 ? kNotFull : 0.4));
+  return from(2800, 0.4);
+}
+
+int try_compress_shape_first(const pbz_codec* c, const Geom& geo, const void* x, int xtype, void* N, void* F, hipStream_t s, bool dry_run) {
+  if (c->kept != c->vol || c->route != kRouteAuto || !fast::aligned16(x) || !fast::aligned16(F)) return 0;
+  const fast::Folded f = fast::fold(c, geo);
+  const DeviceTables none;               // with everything kept and F aligned an entry is its own place
+  return f.ok && shape_kernels_pay(c, f, xtype, true) ? try_compress_brick(c, geo, &none, x, xtype, N, F, s, dry_run) : 0;
+}
+int try_decompress_shape_first(const pbz_codec* c, const Geom& geo, const void* N, const void* F, void* y, int ytype, hipStream_t s, bool dry_run) {
+  if (c->kept != c->vol || c->route != kRouteAuto || !fast::aligned16(y) || !fast::aligned16(F)) return 0;
+  const fast::Folded f = fast::fold(c, geo);
+  const DeviceTables none;
+  return f.ok && shape_kernels_pay(c, f, ytype, false) ? try_decompress_brick(c, geo, &none, N, F, y, ytype, s, dry_run) : 0;
+}
+
 int try_compress_fast(const pbz_codec* c, const Geom& geo, const void* x, int xtype, void* N, void* F, hipStream_t s,
                       bool dry_run, const char** name, double* tile_sums) {
   if (!fast::aligned16(x) || !fast::aligned16(F)) return 0;
@@ -62,6 +129,11 @@ int try_compress_fast(const pbz_codec* c, const Geom& geo, const void* x, int xt
 int64_t fast_compress_tiles(const pbz_codec* c, const Geom& geo, int xtype) {
   const fast::Folded f = fast::fold(c, geo);
   if (!f.ok) return 0;
+  // statistics from the compress kernel's tiles spare a pass over F; not where its waves are so empty that the other way is twice as fast
+  if (c->kept == c->vol && f.g.gx <= (f.tail_x ? 16 : 8) && shape_kernels_pay(c, f, xtype, true)) {
+    const int64_t blocks = f.g.gz * f.g.gy * f.g.gx;
+    if (f.bz * f.by * f.bx == 64 && blocks / f.g.gx >= 4000) return 0;
+  }
   int64_t t = fast::lane_tiles(c, f, xtype);
   if (t < 0) t = fast::quad16_tiles(c, f, xtype);
   if (t < 0) t = fast::oct8_tiles(c, f, xtype);

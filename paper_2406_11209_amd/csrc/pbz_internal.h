@@ -110,6 +110,11 @@ int64_t fast_compress_tiles(const pbz_codec* c, const Geom& g, int xtype);   // 
 int try_decompress_fast(const pbz_codec* c, const Geom& g, const void* N, const void* F, void* y, int ytype,
                         hipStream_t s, bool dry_run, const char** name);
 
+// The kernels per block shape, where they are faster than the ones above (rows of few blocks, or of no whole ones) and need no tables: 1 when
+// they took the call, 0 when it is theirs no more than before, negative on a HIP error.  Asked first.
+int try_compress_shape_first(const pbz_codec* c, const Geom& g, const void* x, int xtype, void* N, void* F, hipStream_t s, bool dry_run);
+int try_decompress_shape_first(const pbz_codec* c, const Geom& g, const void* N, const void* F, void* y, int ytype, hipStream_t s, bool dry_run);
+
 // the same families for settings that only differ from theirs in the mask; `places`: DeviceTables::places
 int try_compress_masked(const pbz_codec* c, const Geom& g, const uint16_t* places, const void* x, int xtype, void* N, void* F,
                         hipStream_t s, bool dry_run);
