@@ -5,8 +5,8 @@
 // neighbours.  The template takes any shape of its static_asserts' kind (8x8x4, 16x32 and 2x16 stay tiled at 2-3.4 TB/s); every
 // shape adds 0.4 MB to the library and some seconds to its build.
 //
-// Wave autonomous like the families: a wave owns a tile of consecutive blocks, VALUES (64, or 32 in FP64 work) values per
-// lane in registers, no workgroup barrier, LDS private to the wave.  Two layouts, each with whole lines of its dimensions
+// Wave autonomous like the families: a wave owns a tile of consecutive blocks, VALUES (8 to 64, by shape and size of the
+// call: tiles()) values per lane in registers, no workgroup barrier, LDS private to the wave.  Two layouts, each with whole lines of its dimensions
 // in a lane:
 //   A  lane (s, b): rows s RA .. s RA + RA - 1 of block b, all of x (a block's rows in row-major order of the other
 //      dimensions; RA = VALUES / BX).  How the array is read and written: the rows a lane needs come as 16-byte pieces, the
@@ -81,29 +81,78 @@ struct BrickGeom {
   const uint16_t* places;
 };
 
-// Values a lane holds of blocks of the shape.  FP64 work holds 32 where two outer dimensions at most remain: with 64 (128
-// registers, twice where the layout changes) it spills or leaves one wave per SIMD: 4^4 blocks of FP64, 16x32x128x256,
-// compress 70 us with 64, 44 with 32; decompress 53 and 47; 2x8x8 FP32 / i16, 256x512x512: 158 and 87, 126 and 91
-constexpr int lane_values(bool wide, int bw, int bz, int by, int bx) {
-  if (!wide || bx > 16) return 64;
-  const int rows = bw * bz * by, ra = 32 / bx;
-  if (rows * bx <= 32) return 32;
-  const int in = ra >= rows ? rows : (ra % (by * bz) == 0 ? by * bz : (ra % by == 0 ? by : 1));
-  const int outer = (bw > 1 && in < rows) + (bz > 1 && in < by * bz) + (by > 1 && in < by);
-  return outer <= 2 && rows / in <= 16 ? 32 : 64;
+// Rows whole in a lane that holds v values, and the outer indices that leaves
+constexpr int inner_rows(int v, int bw, int bz, int by, int bx) {
+  const int rows = bw * bz * by, ra = v / bx;
+  return ra >= rows ? rows : (ra % (by * bz) == 0 ? by * bz : (ra % by == 0 ? by : 1));
+}
+constexpr int outer_rows(int v, int bw, int bz, int by, int bx) { return bw * bz * by / inner_rows(v, bw, bz, by, bx); }
+// Whether a lane can hold v values of the block: whole rows, and every index of two outer dimensions at most
+constexpr bool fits(int v, int bw, int bz, int by, int bx) {
+  if (bx > v || bw * bz * by * bx > 64 * v) return false;
+  if (bw * bz * by * bx < v) return true;
+  const int in = inner_rows(v, bw, bz, by, bx), outer = (bw > 1 && in < bw * bz * by) + (bz > 1 && in < bz * by) + (by > 1 && in < by);
+  return outer <= 2 && outer_rows(v, bw, bz, by, bx) <= v;
 }
 
-template <typename T, int BW_, int BZ_, int BY_, int BX_>
+// Values that a lane holds: `few` for arrays of up to `few_to` elements, `many` for larger ones.
+// A wave goes through its tile once, in one run of code as long as its lanes hold values, so that a call whose tiles leave SIMDs
+// without a wave takes what one wave takes: few is the least that fits (the block's rows and outer indices allow 16 mostly, 32 for
+// 32x32 and 4x8x8, 64 for 8x8x8, 2x2x8x8 and 2x4x8x8; 8 for blocks of 32 and 8x8, which are short enough to gain from it).  Time with
+// few / time with 64 values in FP32 work and 32 in FP64 work, 21 shapes, nine types, both directions, geometric means:
+//   elements       2^14 - 2^20    2^21    2^22    2^24    2^26
+//   FP32 work      0.50 - 0.65    0.70    0.82    1.00    1.10
+//   FP64 work      0.65 - 0.90    0.92    0.96    1.02    1.08
+// (2^17 elements: 4x4 FP32 / i8 7.1 -> 3.6 us, 4x4x4x4 FP64 / i16 5.7 -> 4.5, 8192x16 FP16 / i16 compress 6 -> 4.3.)
+// many: FP64 work holds 32 (16 for blocks of 16, and compressing where runs of two values and more of a row remain to each lane of
+// layout B, OUT <= 8: 0.80-0.95 of 32's time), FP32 work 32 (0.85-0.95 of 64's time) but for
+//   blocks of 256 and more that 16 does not fit: 64 (4x8x8, 32x32: 32 takes 1.05-1.2 of its time from 2^24 on);
+//   FP32 work, blocks of 64, whole in a lane then: 64 (32: 1.03);
+//   FP32 work, decompressing, blocks of 16, single rows under many outer indices, FP64 arrays: 64 (2x8x8: 32 takes 1.08 at 2^26; FP64 1.1);
+//   FP32 work, compressing, blocks of 16 and FP64 arrays: 16 (0.9).
+// few_to, where the two meet, is 4 Mi elements (one or two waves per SIMD with the larger tiles), 2 Mi for lanes of 8, and 8 Mi against
+// 64 values of FP32 and for the runs above, decompressing; in FP64 work 16-bit arrays, whose compression waits least, 1 Mi (4x4x8 at 2 and
+// 4 Mi: 1.08).
+struct Tiles {
+  int few, many;
+  int64_t few_to;
+};
+constexpr Tiles tiles(bool wide, bool compress, int array, int bw, int bz, int by, int bx) {
+  constexpr int64_t kMi = int64_t(1) << 20;
+  const int rows = bw * bz * by, vol = rows * bx;
+  const bool shortest = (vol == 32 && rows > 1) || (bw * bz == 1 && by == 8 && bx == 8);
+  const int few = shortest ? 8 : (fits(16, bw, bz, by, bx) ? 16 : (fits(32, bw, bz, by, bx) ? 32 : 64));
+  const bool narrow = vol != 32 && few <= 16 && outer_rows(16, bw, bz, by, bx) <= 8;
+  int many = 32;
+  if (bx == 64 || (few >= 32 && vol >= 256)) many = 64;
+  else if (wide) many = vol == 16 || (compress && narrow) ? 16 : 32;
+  else if (compress) many = vol <= 16 || (array == 8 && few == 16) ? 16 : (vol == 64 ? 64 : 32);
+  else if (array == 8 || vol <= 16 || vol == 64 || (inner_rows(32, bw, bz, by, bx) == 1 && outer_rows(32, bw, bz, by, bx) > 8)) many = 64;
+  int64_t to = few == 8 ? 2 * kMi : 4 * kMi;
+  if (wide ? !compress && narrow : many == 64) to = 8 * kMi;
+  if (wide && compress && array == 2) to = few == 32 ? 2 * kMi : kMi;
+  return {few, many, few == 64 ? 0 : to};
+}
+// whether kernels with v values are needed for any type of array
+constexpr bool needed(int v, bool wide, bool compress, int bw, int bz, int by, int bx) {
+  for (int array = 2; array <= 8; array *= 2) {
+    const Tiles t = tiles(wide, compress, array, bw, bz, by, bx);
+    if (v == t.many || (v == t.few && t.few_to > 0)) return true;
+  }
+  return false;
+}
+
+template <typename T, int BW_, int BZ_, int BY_, int BX_, int VALUES_>
 struct Shape {
   static constexpr int BW = BW_, BZ = BZ_, BY = BY_, BX = BX_;
   static constexpr int ROWS = BW * BZ * BY, VOL = ROWS * BX;
-  static constexpr int VALUES = lane_values(sizeof(T) == 8, BW, BZ, BY, BX);    // a lane's
+  static constexpr int VALUES = VALUES_;                           // a lane's
   static constexpr int PER_LANE = VOL < VALUES ? VALUES / VOL : 1; // blocks a lane holds
   static constexpr int LANES = VOL < VALUES ? 1 : VOL / VALUES;    // lanes a block takes
   static constexpr int NB = VOL < VALUES ? 64 * PER_LANE : 64 / LANES; // blocks of a tile
   static constexpr int RA = VOL < VALUES ? ROWS : VALUES / BX;     // rows per lane (and block)
   // rows of the dimensions that are whole in layout A, and of the outer ones
-  static constexpr int IN = RA >= ROWS ? ROWS : (RA % (BY * BZ) == 0 ? BY * BZ : (RA % BY == 0 ? BY : 1));
+  static constexpr int IN = inner_rows(VALUES, BW, BZ, BY, BX);
   static constexpr int OUT = ROWS / IN;
   static_assert(BX <= VALUES && LANES <= 64 && RA % IN == 0, "a lane holds whole rows, and whole inner dimensions");
   static_assert(OUT <= VALUES, "a lane holds every outer index");
@@ -113,6 +162,7 @@ struct Shape {
   // the outer dimensions, from the inside: E1 and E2
   static constexpr int E1 = OUT == 1 ? 1 : (IN == BY * BZ ? BW : (IN == BY ? BZ : BY));
   static constexpr int E2 = OUT / E1;
+  static_assert((BW > 1 && IN < ROWS) + (BZ > 1 && IN < BY * BZ) + (BY > 1 && IN < BY) <= 2, "E1 and E2 are one dimension each");
 };
 
 template <typename T, typename S>
@@ -810,7 +860,7 @@ bool make_brick(const pbz_codec* c, const Geom& geo, const void* array, int xtyp
   g->itype = int(c->itype);
   g->kept = c->kept;
   g->r = c->r;
-  g->places = t->places;
+  g->places = t ? t->places : nullptr;
   return true;
 }
 
@@ -875,19 +925,25 @@ constexpr bool kTaken = BX < 64 || sizeof(T) == 4;
 // under a mask, of FP32 arrays (0.9); in FP64 work flat blocks of up to 128 in rows of less than 32 (0.65-0.9; FP64 arrays under a mask only, all of
 // them 1.15), 16x16 of 16-bit arrays with nothing pruned (0.9); and the others, too, from 2^22 on.  Compressing, 8x8 of 16-bit arrays with
 // 32-bit indices (0.88) and 32x32 of FP32 arrays (0.9).
+// Up to few_to elements the smaller tiles win against the tiled kernels throughout (0.57-0.97), but for 32x32 blocks of FP32 and 16-bit
+// arrays in FP32 work and 4x8x8 blocks of 16-bit arrays, decompressing whole rows under a mask (1.04-1.09); what follows is for the larger
+// calls and the shapes that hold 64 values at any size.  first: asked before a specialised family's kernel (without tables), by a rule that was
+// measured with what follows alone.
 template <typename T, typename S>
-bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_t row) {
+bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_t row, const Tiles& t, bool first) {
   constexpr int64_t kMi = int64_t(1) << 20;
   constexpr bool kWide = sizeof(T) == 8, kFlat = S::BW == 1 && S::BZ == 1;
   constexpr bool k8x8 = kFlat && S::BY == 8 && S::BX == 8, k4x8 = kFlat && S::VOL == 32 && S::BX < 16;
   const int array = ftype_bytes(xtype), index = itype_bytes(c->itype);
   const bool pruned = c->kept != c->vol, ragged = row % S::BX != 0 || row * array % 16 != 0;
   if (c->route == kRouteShape || S::BX == 64) return true;
+  const bool looked_up = !compress && pruned && !ragged && t.few == 32 && (S::VOL == 1024 ? !kWide && array < 8 : S::VOL == 256 && array == 2);
+  if (elements <= t.few_to && !looked_up && !first) return true;
   if (index == 4 && !pruned && ((k8x8 && !(compress && ragged && array == 2)) || (k4x8 && !compress && array == 8)))
     return elements <= (compress ? 4096 : 1024);
   if (compress) {
     const bool enough = elements <= 4096 || elements >= 3 * kMi;
-    if (kWide) return pruned || !(S::VALUES == 64 && (index == 4 || array == 8)) || enough;
+    if (kWide) return pruned || !(t.many == 64 && (index == 4 || array == 8)) || enough;
     return !((array == 8 && S::BX >= 16) || (array == 4 && S::VOL == 1024 && !ragged)) || enough;
   }
   if (!kWide && S::VOL == 1024 && array == 8 && pruned) return false;
@@ -902,18 +958,33 @@ bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_
   return elements >= (late && !ragged ? 8 * kMi : 3 * kMi);
 }
 
+// The shape with the values per lane that the call gets
+template <typename T, bool kCompress, int BW, int BZ, int BY, int BX, typename F>
+int with_shape(const pbz_codec* c, int xtype, const BrickGeom& g, int64_t row, bool first, bool dry_run, F f) {
+  constexpr bool kWide = sizeof(T) == 8;
+  const Tiles t = tiles(kWide, kCompress, ftype_bytes(xtype), BW, BZ, BY, BX);
+  const int64_t elements = int64_t(g.n_blocks) * BW * BZ * BY * BX;
+  if (!pays<T, Shape<T, BW, BZ, BY, BX, 64>>(c, kCompress, xtype, elements, row, t, first)) return 0;
+  if (dry_run) return 1;
+  const int v = elements <= t.few_to ? t.few : t.many;
+  if constexpr (needed(8, kWide, kCompress, BW, BZ, BY, BX)) if (v == 8) f(Shape<T, BW, BZ, BY, BX, 8>());
+  if constexpr (needed(16, kWide, kCompress, BW, BZ, BY, BX)) if (v == 16) f(Shape<T, BW, BZ, BY, BX, 16>());
+  if constexpr (needed(32, kWide, kCompress, BW, BZ, BY, BX)) if (v == 32) f(Shape<T, BW, BZ, BY, BX, 32>());
+  if constexpr (needed(64, kWide, kCompress, BW, BZ, BY, BX)) if (v == 64) f(Shape<T, BW, BZ, BY, BX, 64>());
+  return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+}
+
 template <typename T, int BW, int BZ, int BY, int BX>
 int compress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t, const void* x, int xtype, void* N, void* F,
                    hipStream_t s, bool dry_run) {
   if constexpr (kTaken<T, BX>) {
     BrickGeom g;
     if (!make_brick(c, geo, x, xtype, t, BW, BZ, BY, BX, &g)) return 0;
-    using S = Shape<T, BW, BZ, BY, BX>;
-    if (!pays<T, S>(c, true, xtype, geo.n_blocks * S::VOL, geo.shape[c->ndim - 1])) return 0;
-    if (dry_run) return 1;
-    if (c->transform == PBZ_TRANSFORM_HAAR) compress_with<kTfHaar, T, S>(g, x, N, F, s);
-    else compress_with<kTfDct, T, S>(g, x, N, F, s);
-    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+    return with_shape<T, true, BW, BZ, BY, BX>(c, xtype, g, geo.shape[c->ndim - 1], t == nullptr, dry_run, [&](auto tag) {
+      using S = decltype(tag);
+      if (c->transform == PBZ_TRANSFORM_HAAR) compress_with<kTfHaar, T, S>(g, x, N, F, s);
+      else compress_with<kTfDct, T, S>(g, x, N, F, s);
+    });
   }
   return 0;
 }
@@ -923,12 +994,11 @@ int decompress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t,
   if constexpr (kTaken<T, BX>) {
     BrickGeom g;
     if (!make_brick(c, geo, y, ytype, t, BW, BZ, BY, BX, &g)) return 0;
-    using S = Shape<T, BW, BZ, BY, BX>;
-    if (!pays<T, S>(c, false, ytype, geo.n_blocks * S::VOL, geo.shape[c->ndim - 1])) return 0;
-    if (dry_run) return 1;
-    if (c->transform == PBZ_TRANSFORM_HAAR) decompress_with<kTfHaar, T, S>(g, N, F, y, s);
-    else decompress_with<kTfDct, T, S>(g, N, F, y, s);
-    return hipGetLastError() == hipSuccess ? 1 : PBZ_ERR_HIP;
+    return with_shape<T, false, BW, BZ, BY, BX>(c, ytype, g, geo.shape[c->ndim - 1], t == nullptr, dry_run, [&](auto tag) {
+      using S = decltype(tag);
+      if (c->transform == PBZ_TRANSFORM_HAAR) decompress_with<kTfHaar, T, S>(g, N, F, y, s);
+      else decompress_with<kTfDct, T, S>(g, N, F, y, s);
+    });
   }
   return 0;
 }

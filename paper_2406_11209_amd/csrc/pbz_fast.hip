@@ -103,14 +103,13 @@ static bool shape_kernels_pay(const pbz_codec* c, const fast::Folded& f, int xty
 int try_compress_shape_first(const pbz_codec* c, const Geom& geo, const void* x, int xtype, void* N, void* F, hipStream_t s, bool dry_run) {
   if (c->kept != c->vol || c->route != kRouteAuto || !fast::aligned16(x) || !fast::aligned16(F)) return 0;
   const fast::Folded f = fast::fold(c, geo);
-  const DeviceTables none;               // with everything kept and F aligned an entry is its own place
-  return f.ok && shape_kernels_pay(c, f, xtype, true) ? try_compress_brick(c, geo, &none, x, xtype, N, F, s, dry_run) : 0;
+  // no tables: with everything kept and F aligned an entry is its own place
+  return f.ok && shape_kernels_pay(c, f, xtype, true) ? try_compress_brick(c, geo, nullptr, x, xtype, N, F, s, dry_run) : 0;
 }
 int try_decompress_shape_first(const pbz_codec* c, const Geom& geo, const void* N, const void* F, void* y, int ytype, hipStream_t s, bool dry_run) {
   if (c->kept != c->vol || c->route != kRouteAuto || !fast::aligned16(y) || !fast::aligned16(F)) return 0;
   const fast::Folded f = fast::fold(c, geo);
-  const DeviceTables none;
-  return f.ok && shape_kernels_pay(c, f, ytype, false) ? try_decompress_brick(c, geo, &none, N, F, y, ytype, s, dry_run) : 0;
+  return f.ok && shape_kernels_pay(c, f, ytype, false) ? try_decompress_brick(c, geo, nullptr, N, F, y, ytype, s, dry_run) : 0;
 }
 
 int try_compress_fast(const pbz_codec* c, const Geom& geo, const void* x, int xtype, void* N, void* F, hipStream_t s,

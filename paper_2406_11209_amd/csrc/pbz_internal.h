@@ -121,7 +121,8 @@ int try_compress_masked(const pbz_codec* c, const Geom& g, const uint16_t* place
 int try_decompress_masked(const pbz_codec* c, const Geom& g, const uint16_t* places, const void* N, const void* F, void* y,
                           int ytype, hipStream_t s, bool dry_run);
 
-// general kernels for a list of block shapes (pbz_brick.h); 1 when they handled the call, 0 when they do not cover it
+// general kernels for a list of block shapes (pbz_brick.h); 1 when they handled the call, 0 when they do not cover it; t: nullptr from the
+// calls that are asked first (nothing pruned, F aligned)
 int try_compress_brick(const pbz_codec* c, const Geom& g, const DeviceTables* t, const void* x, int xtype, void* N, void* F,
                        hipStream_t s, bool dry_run);
 int try_decompress_brick(const pbz_codec* c, const Geom& g, const DeviceTables* t, const void* N, const void* F, void* y,
