@@ -318,7 +318,9 @@ int pbz_compress_statistics(const pbz_codec* c, const void* x, pbz_ftype x_type,
   if (c->path == PBZ_PATH_AUTO) {
     // the compress kernel leaves a record of four doubles per tile behind the reduction scratch; adding them costs two small launches
     const int64_t tiles = fast_compress_tiles(c, g, x_type);
-    if (tiles > 0 && ws_bytes >= kWorkspaceBytes + size_t(tiles) * 4 * sizeof(double)) {
+    if (tiles > 0 && ws_bytes < kWorkspaceBytes + size_t(tiles) * 4 * sizeof(double)) return PBZ_ERR_WORKSPACE;
+    // {N, F} are the ones that pbz_compress writes, so the call takes its route
+    if (tiles > 0 && try_compress_shape_first(c, g, x, x_type, N, F, s, true) == 0) {
       double* tile_sums = reinterpret_cast<double*>(static_cast<char*>(ws) + kWorkspaceBytes);
       const char* name = nullptr;
       int r = try_compress_fast(c, g, x, x_type, N, F, s, false, &name, tile_sums);
@@ -326,11 +328,9 @@ int pbz_compress_statistics(const pbz_codec* c, const void* x, pbz_ftype x_type,
       // tiles follow the block grid's order, so the tiles of one index along dimension 0 are consecutive
       if (r > 0) return launch_statistics_from_tiles(c, g.n_blocks / segments, tile_sums, tiles / segments, segments,
                                                      statistics, ws, s);
-    } else if (tiles > 0) {
-      return PBZ_ERR_WORKSPACE;
     }
   }
-  // no specialised kernel: compress, then one pass over {N, F} for the two sums
+  // no specialised kernel, or not the fastest one: compress, then one pass over {N, F} for the two sums
   st = pbz_compress(c, x, x_type, shape, N, F, stream);
   if (st != PBZ_OK) return st;
   return launch_reduce(c, kStatistics, g.n_blocks / segments, N, F, nullptr, nullptr, statistics, ws, s, nullptr,

@@ -129,7 +129,7 @@ constexpr Tiles tiles(bool wide, bool compress, int array, int bw, int bz, int b
   else if (compress) many = vol <= 16 || (array == 8 && few == 16) ? 16 : (vol == 64 ? 64 : 32);
   else if (array == 8 || vol <= 16 || vol == 64 || (inner_rows(32, bw, bz, by, bx) == 1 && outer_rows(32, bw, bz, by, bx) > 8)) many = 64;
   int64_t to = few == 8 ? 2 * kMi : 4 * kMi;
-  if (wide ? !compress && narrow : many == 64) to = 8 * kMi;
+  if (few > 8 && (wide ? !compress && narrow : many == 64)) to = 8 * kMi;
   if (wide && compress && array == 2) to = few == 32 ? 2 * kMi : kMi;
   return {few, many, few == 64 ? 0 : to};
 }
@@ -927,10 +927,9 @@ constexpr bool kTaken = BX < 64 || sizeof(T) == 4;
 // 32-bit indices (0.88) and 32x32 of FP32 arrays (0.9).
 // Up to few_to elements the smaller tiles win against the tiled kernels throughout (0.57-0.97), but for 32x32 blocks of FP32 and 16-bit
 // arrays in FP32 work and 4x8x8 blocks of 16-bit arrays, decompressing whole rows under a mask (1.04-1.09); what follows is for the larger
-// calls and the shapes that hold 64 values at any size.  first: asked before a specialised family's kernel (without tables), by a rule that was
-// measured with what follows alone.
+// calls and the shapes that hold 64 values at any size.
 template <typename T, typename S>
-bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_t row, const Tiles& t, bool first) {
+bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_t row, const Tiles& t) {
   constexpr int64_t kMi = int64_t(1) << 20;
   constexpr bool kWide = sizeof(T) == 8, kFlat = S::BW == 1 && S::BZ == 1;
   constexpr bool k8x8 = kFlat && S::BY == 8 && S::BX == 8, k4x8 = kFlat && S::VOL == 32 && S::BX < 16;
@@ -938,7 +937,7 @@ bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_
   const bool pruned = c->kept != c->vol, ragged = row % S::BX != 0 || row * array % 16 != 0;
   if (c->route == kRouteShape || S::BX == 64) return true;
   const bool looked_up = !compress && pruned && !ragged && t.few == 32 && (S::VOL == 1024 ? !kWide && array < 8 : S::VOL == 256 && array == 2);
-  if (elements <= t.few_to && !looked_up && !first) return true;
+  if (elements <= t.few_to && !looked_up) return true;
   if (index == 4 && !pruned && ((k8x8 && !(compress && ragged && array == 2)) || (k4x8 && !compress && array == 8)))
     return elements <= (compress ? 4096 : 1024);
   if (compress) {
@@ -960,11 +959,11 @@ bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_
 
 // The shape with the values per lane that the call gets
 template <typename T, bool kCompress, int BW, int BZ, int BY, int BX, typename F>
-int with_shape(const pbz_codec* c, int xtype, const BrickGeom& g, int64_t row, bool first, bool dry_run, F f) {
+int with_shape(const pbz_codec* c, int xtype, const BrickGeom& g, int64_t row, bool dry_run, F f) {
   constexpr bool kWide = sizeof(T) == 8;
   const Tiles t = tiles(kWide, kCompress, ftype_bytes(xtype), BW, BZ, BY, BX);
   const int64_t elements = int64_t(g.n_blocks) * BW * BZ * BY * BX;
-  if (!pays<T, Shape<T, BW, BZ, BY, BX, 64>>(c, kCompress, xtype, elements, row, t, first)) return 0;
+  if (!pays<T, Shape<T, BW, BZ, BY, BX, 64>>(c, kCompress, xtype, elements, row, t)) return 0;
   if (dry_run) return 1;
   const int v = elements <= t.few_to ? t.few : t.many;
   if constexpr (needed(8, kWide, kCompress, BW, BZ, BY, BX)) if (v == 8) f(Shape<T, BW, BZ, BY, BX, 8>());
@@ -980,7 +979,7 @@ int compress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t, c
   if constexpr (kTaken<T, BX>) {
     BrickGeom g;
     if (!make_brick(c, geo, x, xtype, t, BW, BZ, BY, BX, &g)) return 0;
-    return with_shape<T, true, BW, BZ, BY, BX>(c, xtype, g, geo.shape[c->ndim - 1], t == nullptr, dry_run, [&](auto tag) {
+    return with_shape<T, true, BW, BZ, BY, BX>(c, xtype, g, geo.shape[c->ndim - 1], dry_run, [&](auto tag) {
       using S = decltype(tag);
       if (c->transform == PBZ_TRANSFORM_HAAR) compress_with<kTfHaar, T, S>(g, x, N, F, s);
       else compress_with<kTfDct, T, S>(g, x, N, F, s);
@@ -994,7 +993,7 @@ int decompress_shape(const pbz_codec* c, const Geom& geo, const DeviceTables* t,
   if constexpr (kTaken<T, BX>) {
     BrickGeom g;
     if (!make_brick(c, geo, y, ytype, t, BW, BZ, BY, BX, &g)) return 0;
-    return with_shape<T, false, BW, BZ, BY, BX>(c, ytype, g, geo.shape[c->ndim - 1], t == nullptr, dry_run, [&](auto tag) {
+    return with_shape<T, false, BW, BZ, BY, BX>(c, ytype, g, geo.shape[c->ndim - 1], dry_run, [&](auto tag) {
       using S = decltype(tag);
       if (c->transform == PBZ_TRANSFORM_HAAR) decompress_with<kTfHaar, T, S>(g, N, F, y, s);
       else decompress_with<kTfDct, T, S>(g, N, F, y, s);

@@ -55,6 +55,10 @@ namespace pbz {
 // FP64 / i16 in 4x4x4 0.16, 0.55, 1.09; in rows that are no whole blocks, of 128 blocks, FP64 / i16 8x8 0.70 and 0.86, FP64 / i8 0.61 and 0.6, FP32 / i16
 // 16x16 0.83.  Over all measured widths and sizes 0.45-0.85 for lane, 0.75-0.95 for quad16, 0.7-0.97 for oct8; worst 1.2 (FP64 / i8
 // lane in rows of 60 whole blocks).  Calls under a mask have MaskedCall's rules.
+// The statistics of a compressed array, which a family's kernel leaves along the way, have to be those of the same {N, F}: such calls take this
+// route too and read {N, F} once more.  Compressing, the line is therefore where both win: 0.05-0.95 of the time for the statistics inside it, 1.1-1.5
+// in the calls outside where compression alone would win (0.75-0.95: small arrays, and rows a third full and more).  Decompressing, for
+// calls that are not small() below.
 static bool shape_kernels_pay(const pbz_codec* c, const fast::Folded& f, int xtype, bool compress) {
   const fast::FastGeom& g = f.g;
   const bool flat = f.bz == 1, lane = (flat && f.by == 8 && f.bx == 8) || (f.bz == 4 && f.by == 4 && f.bx == 4);
@@ -68,11 +72,12 @@ static bool shape_kernels_pay(const pbz_codec* c, const fast::Folded& f, int xty
   const int array = ftype_bytes(xtype), index = itype_bytes(c->itype);
   const bool ragged = f.tail_x, wide = c->compute_f64;
   const auto from = [&](int64_t least_waves, double most_fill) { return waves >= least_waves && fill <= most_fill; };
-  constexpr double kAny = 1.0, kNotFull = 0.95;
+  constexpr double kAny = 1.0;
   if (lane && compress) {
-    if (!ragged) return from(index == 1 && array < 8 ? 2800 : 2000, array == 8 ? (flat ? 0.5 : 0.35) : (index == 1 ? 0.35 : (index == 2 ? 0.3 : 0.15)));
-    if (array == 8 || (flat && index == 1)) return true;
-    return index == 1 ? from(2000, kAny) : from(1400, 0.35);
+    if (!ragged) return from(2000, array == 8 ? (flat ? 0.44 : 0.25) : (index == 4 ? 0.15 : 0.2));
+    if (!flat) return array == 8 ? g.gx <= (index == 1 ? 48 : (index == 2 ? 20 : 12)) || from(2000, kAny) : from(1300, 0.32);
+    if (array == 8) return g.gx <= 40 || from(2000, kAny) || blocks <= 24 * 1024;
+    return index == 1 ? g.gx <= 8 || from(2000, kAny) : g.gx <= 4 || from(2000, 0.35);
   }
   if (lane && !flat) {
     if (fill <= 0.15) return true;
@@ -81,35 +86,79 @@ static bool shape_kernels_pay(const pbz_codec* c, const fast::Folded& f, int xty
   }
   if (lane) {
     if (!ragged) return from(2500, index == 4 ? 0.15 : (index == 2 && array == 4 ? 0.25 : (array == 8 ? 0.5 : 0.45)));
-    if (array == 2) return true;
+    if (array == 2) return from(0, 0.9) || from(4000, kAny);
     if (array == 8) return from(700, kAny);
     return index == 1 ? from(2800, kAny) : from(2000, 0.4);
   }
   if (quad && compress) {
-    const bool late = array == 8 ? !wide : index == 1;                   // FP32 arithmetic
-    if (ragged) return from(late ? 2000 : 0, array == 8 ? 0.85 : kAny);
-    if (array == 8 && !wide) return from(1400, 0.4);
-    return late ? from(2000, 0.9) : from(700, index == 2 && array == 4 ? 0.85 : kNotFull);
+    if (!ragged) return from(2000, array == 8 && !wide ? 0.4 : 0.5);
+    return from(500, 0.5) || from(4500, index == 4 ? 0.75 : 0.9);
   }
   if (quad) {
-    if (array == 8 && wide) return from(2000, ragged ? kAny : kNotFull);
-    return from(0, 0.5);
+    if (array == 8 && wide) return from(2000, ragged ? kAny : 0.95);
+    return from(!ragged && c->transform == PBZ_TRANSFORM_HAAR ? 2000 : 0, 0.5);
   }
-  if (compress) return ragged && array == 8 ? true : from(2000, index == 1 && array == 4 ? 0.9 : 0.65);
-  if (ragged) return array == 8 ? true : (array == 4 && from(2800, index == 1 ? kNotFull : 0.4));
+  if (compress) {
+    if (ragged && array == 8) return wide || from(2000, kAny);
+    return from(4000, 0.25) || (ragged && from(8000, 0.5));
+  }
+  if (ragged) return array == 8 ? true : (array == 4 && from(2800, index == 1 ? 0.95 : 0.4));
   return from(2800, 0.4);
+}
+
+// Up to how many elements the kernels per block shape are the faster ones for any row width, with their smaller tiles: a family's wave holds
+// 16 to 32 KiB of the array, so that up to 2^20 elements it is one wave's time that counts, which is the longer the more it holds.  Measured
+// for ten types, two aspects, whole rows and not, 2^16 to 2^22.5 elements; here / family, decompressing, full masks:
+//             2^17   2^19   2^20   2^21   2^21.5  2^22
+//   8x8       0.70   0.80   0.84   1.00   1.18    1.23   rows of no whole blocks 0.60 ... 0.82, 0.95
+//   4x4x4     0.87   0.94   0.96   1.03   1.08    1.14   rows of no whole blocks 0.60 ... 0.83, 0.92; FP32 / i8 0.99 at 2^18
+//   16x16     0.89   0.93   0.92   0.90   0.97    1.01   rows of no whole blocks 0.70 ... 0.78, 0.90; FP64 arrays 0.88 at 2^22
+// and under a mask 0.6-0.8 compressing (1.0 at 2^21.5, 2^22 and 2^22.5), 0.7-0.95 decompressing.  Compressing without one it would be 0.75-0.9 up to
+// 2^20, but 1.2-1.4 for the statistics.  With the Haar transform, whose waves are shorter, whole rows of 16x16 decompress in 1.05-1.2 here, of
+// 4x4x4 and 8x8 / i8 in 1.0-1.1: they stay.  8x8x8 blocks keep 64 values a lane here (1.1-1.6): not these.
+static int64_t small_to(const pbz_codec* c, const fast::Folded& f, int xtype, bool compress) {
+  constexpr int64_t kKi = 1024, kMi = kKi * kKi;
+  const bool flat = f.bz == 1, masked = c->kept != c->vol, ragged = f.tail_x, wide = c->compute_f64;
+  const int array = ftype_bytes(xtype), index = itype_bytes(c->itype);
+  const bool haar = c->transform == PBZ_TRANSFORM_HAAR;
+  if (compress && !masked) return 0;
+  if (flat && f.by == 8 && f.bx == 8) {
+    if (ragged || masked) return 2 * kMi;
+    if (index == 1 && array < 8) return haar ? 0 : kMi;
+    return 3 * kMi / 2;
+  }
+  if (f.bz == 4 && f.by == 4 && f.bx == 4) {
+    if (compress) return 4 * kMi;
+    if (ragged) return 2 * kMi;
+    if (array < 8 && (haar || !wide)) return haar ? 0 : 256 * kKi;
+    return kMi;
+  }
+  if (flat && f.by == 16 && f.bx == 16) {
+    if (compress) return 4 * kMi;
+    if (ragged) return 3 * kMi;
+    return haar ? 0 : (array == 8 ? 4 * kMi : (wide ? 2 * kMi : kMi));
+  }
+  return 0;
+}
+static bool small(const pbz_codec* c, const fast::Folded& f, int xtype, bool compress) {
+  return f.g.gz * f.g.gy * f.g.gx * (f.bz * f.by * f.bx) <= small_to(c, f, xtype, compress);
+}
+constexpr int64_t kTiny = int64_t(1) << 17;         // up to here a family keeps the calls it fits exactly: a microsecond or two at most lie in it
+
+static bool shape_first(const pbz_codec* c, const fast::Folded& f, int xtype, bool compress) {
+  if (!f.ok) return false;
+  const bool enough = f.g.gz * f.g.gy * f.g.gx * (f.bz * f.by * f.bx) > kTiny;
+  return (enough && small(c, f, xtype, compress)) || shape_kernels_pay(c, f, xtype, compress);
 }
 
 int try_compress_shape_first(const pbz_codec* c, const Geom& geo, const void* x, int xtype, void* N, void* F, hipStream_t s, bool dry_run) {
   if (c->kept != c->vol || c->route != kRouteAuto || !fast::aligned16(x) || !fast::aligned16(F)) return 0;
-  const fast::Folded f = fast::fold(c, geo);
   // no tables: with everything kept and F aligned an entry is its own place
-  return f.ok && shape_kernels_pay(c, f, xtype, true) ? try_compress_brick(c, geo, nullptr, x, xtype, N, F, s, dry_run) : 0;
+  return shape_first(c, fast::fold(c, geo), xtype, true) ? try_compress_brick(c, geo, nullptr, x, xtype, N, F, s, dry_run) : 0;
 }
 int try_decompress_shape_first(const pbz_codec* c, const Geom& geo, const void* N, const void* F, void* y, int ytype, hipStream_t s, bool dry_run) {
   if (c->kept != c->vol || c->route != kRouteAuto || !fast::aligned16(y) || !fast::aligned16(F)) return 0;
-  const fast::Folded f = fast::fold(c, geo);
-  return f.ok && shape_kernels_pay(c, f, ytype, false) ? try_decompress_brick(c, geo, nullptr, N, F, y, ytype, s, dry_run) : 0;
+  return shape_first(c, fast::fold(c, geo), ytype, false) ? try_decompress_brick(c, geo, nullptr, N, F, y, ytype, s, dry_run) : 0;
 }
 
 int try_compress_fast(const pbz_codec* c, const Geom& geo, const void* x, int xtype, void* N, void* F, hipStream_t s,
@@ -128,11 +177,6 @@ int try_compress_fast(const pbz_codec* c, const Geom& geo, const void* x, int xt
 int64_t fast_compress_tiles(const pbz_codec* c, const Geom& geo, int xtype) {
   const fast::Folded f = fast::fold(c, geo);
   if (!f.ok) return 0;
-  // statistics from the compress kernel's tiles spare a pass over F; not where its waves are so empty that the other way is twice as fast
-  if (c->kept == c->vol && f.g.gx <= (f.tail_x ? 16 : 8) && shape_kernels_pay(c, f, xtype, true)) {
-    const int64_t blocks = f.g.gz * f.g.gy * f.g.gx;
-    if (f.bz * f.by * f.bx == 64 && blocks / f.g.gx >= 4000) return 0;
-  }
   int64_t t = fast::lane_tiles(c, f, xtype);
   if (t < 0) t = fast::quad16_tiles(c, f, xtype);
   if (t < 0) t = fast::oct8_tiles(c, f, xtype);
@@ -155,12 +199,13 @@ int try_decompress_fast(const pbz_codec* c, const Geom& geo, const void* N, cons
 
 // The kernels of the same families that take any mask, in the order above.  They are asked after the kernels for one
 // mask (everything, or a box), which skip work that these cannot, and before the kernels for any block shape; each
-// family's pays() says where it is the faster one (the figures are there and with MaskArgs)
+// family's pays() says where it is the faster one (the figures are there and with MaskArgs), above what is small()
 int try_compress_masked(const pbz_codec* c, const Geom& geo, const uint16_t* pos, const void* x, int xtype, void* N, void* F,
                         hipStream_t s, bool dry_run) {
   if (c->kept == c->vol || !fast::aligned16(x) || c->route == kRouteShape) return 0;
   const fast::Folded f = fast::fold(c, geo);
   if (!f.ok) return 0;
+  if (c->route == kRouteAuto && small(c, f, xtype, true) && try_compress_brick(c, geo, nullptr, x, xtype, N, F, s, true) == 1) return 0;
   int r = fast::lane_compress_masked(c, f, xtype, pos, x, N, F, s, dry_run);
   if (r == 0) r = fast::quad16_compress_masked(c, f, xtype, pos, x, N, F, s, dry_run);
   if (r == 0) r = fast::oct8_compress_masked(c, f, xtype, pos, x, N, F, s, dry_run);
@@ -173,6 +218,7 @@ int try_decompress_masked(const pbz_codec* c, const Geom& geo, const uint16_t* p
   if (c->kept == c->vol || !fast::aligned16(y) || c->route == kRouteShape) return 0;
   const fast::Folded f = fast::fold(c, geo);
   if (!f.ok) return 0;
+  if (c->route == kRouteAuto && small(c, f, ytype, false) && try_decompress_brick(c, geo, nullptr, N, F, y, ytype, s, true) == 1) return 0;
   int r = fast::lane_decompress_masked(c, f, ytype, pos, N, F, y, s, dry_run);
   if (r == 0) r = fast::quad16_decompress_masked(c, f, ytype, pos, N, F, y, s, dry_run);
   if (r == 0) r = fast::oct8_decompress_masked(c, f, ytype, pos, N, F, y, s, dry_run);

@@ -110,7 +110,7 @@ int64_t fast_compress_tiles(const pbz_codec* c, const Geom& g, int xtype);   // 
 int try_decompress_fast(const pbz_codec* c, const Geom& g, const void* N, const void* F, void* y, int ytype,
                         hipStream_t s, bool dry_run, const char** name);
 
-// The kernels per block shape, where they are faster than the ones above (rows of few blocks, or of no whole ones) and need no tables: 1 when
+// The kernels per block shape, where they are faster than the ones above (small arrays, rows of few blocks or of no whole ones) and need no tables: 1 when
 // they took the call, 0 when it is theirs no more than before, negative on a HIP error.  Asked first.
 int try_compress_shape_first(const pbz_codec* c, const Geom& g, const void* x, int xtype, void* N, void* F, hipStream_t s, bool dry_run);
 int try_decompress_shape_first(const pbz_codec* c, const Geom& g, const void* N, const void* F, void* y, int ytype, hipStream_t s, bool dry_run);
