@@ -308,7 +308,8 @@ int pbz_stream_copy(void* dst, const void* src, size_t bytes, void* stream);
 /* Name of the kernel family pbz_compress ("compress") or pbz_decompress ("decompress") would run for
  * this shape and array type: the name of a kernel specialised to exactly this setting, mask included, or
  * "generic" for the kernels that take any mask (of the specialised families' block shapes and types) or any
- * setting at all.  Host only; returns a static string, or NULL on invalid arguments. */
+ * setting at all, which also take calls that a specialised kernel covers where they are the faster ones (small
+ * arrays, rows of few or of partial blocks).  Host only; returns a static string, or NULL on invalid arguments. */
 const char* pbz_kernel_name(const pbz_codec* codec, const char* op, const int64_t* shape, pbz_ftype array_type);
 
 /* Human-readable text for a status code (static string, never NULL). */

@@ -40,6 +40,7 @@
 // reduces to at most three dimensions (leading dimensions with block extent 1 fold into the slowest one),
 // the block shape / types / mask box match an instantiation, rows are at least one 16-byte piece long and
 // start on a 4-byte boundary.
+// Where the kernels per block shape (pbz_brick.h) are faster they take such calls all the same: shape_kernels_pay() and small_to() below.
 // The families live in pbz_fast_lane.hip, pbz_fast_quad16.hip, pbz_fast_oct8.hip and pbz_fast_cube16.hip; this file folds the array
 // and asks each family in turn.
 #include "pbz_fast_common.h"

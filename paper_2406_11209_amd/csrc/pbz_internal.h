@@ -16,7 +16,8 @@ constexpr int kMaxDevices = 16;
 constexpr uint16_t kPruned = 0x7fff;        // beyond every position, also as a byte offset after any LDS base
 constexpr int kReducePartialSlots = 8;      // doubles per workgroup partial
 constexpr int kReduceMaxGroups = 4096;      // upper bound on reduction workgroups
-// Which kernels take a compress or decompress call, in the order in which they are asked.  A codec's route is kRouteAuto; the tests
+// Which kernels take a compress or decompress call, in the order in which they are asked (the third ones before the others, where a rule on sizes
+// and rows says so).  A codec's route is kRouteAuto; the tests
 // set kRouteMasked or kRouteShape to have that kind taken wherever it can be, whatever the rules on sizes say
 // (pbz_internal_set_route), and ask which one a call would go to (pbz_internal_route).
 enum Route { kRouteAuto = -1, kRouteExact = 0, kRouteMasked = 1, kRouteShape = 2, kRouteLines = 3, kRouteTiled = 4, kRouteDense = 5 };
