@@ -91,3 +91,28 @@ def test_counts_of_blocks_about_a_tile(block):
         take_wherever_possible(case.codec, SHAPE)
         N, F, _, _ = case.check_compress("A")
         case.check_decompress(N, F)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("block", SHAPES, ids=IDS)
+def test_rows_of_whole_lines(block):
+    """Rows of whole 128-byte lines are stored another way than rows that share lines: the same array to a place on a line's start and to one 16
+    bytes on, and the surroundings of the latter stay as they are."""
+    step = 64 * block[-1] // int(np.gcd(64, block[-1]))
+    shape = tuple(2 * b for b in block[:-1]) + (3 * step,)
+    for n, (dtype, ftype, bits) in enumerate(TYPES):
+        gen = torch.Generator("cuda").manual_seed(n)
+        x = torch.randn(shape, generator=gen, device="cuda", dtype=torch.float32).to(TORCH_DTYPE[dtype])
+        c = Codec(block, ftype, bits)
+        take_wherever_possible(c, SHAPE)
+        N, F = c.compress(x)
+        pad = 16 // x.element_size()
+        wide = torch.full((x.numel() + 2 * pad,), 7.0, dtype=x.dtype, device="cuda")
+        assert wide.data_ptr() % 128 == 0
+        off = wide[pad:pad + x.numel()].view(shape)
+        y = c.decompress(N, F, shape, x.dtype)
+        c.decompress(N, F, shape, out=off)
+        torch.cuda.synchronize()
+        assert y.data_ptr() % 128 == 0 and torch.equal(off, y)
+        assert bool((wide[:pad] == 7.0).all()) and bool((wide[pad + x.numel():] == 7.0).all())
+        assert float((y.double() - x.double()).abs().max()) <= (0.1 if bits == 8 else 1e-2) * float(x.double().abs().max())
