@@ -478,8 +478,8 @@ __device__ __forceinline__ void load_rows(const BrickGeom& g, const XT* x, const
 // to slot L COUNT + k, and 64 consecutive slots are stored at a time, each by a lane that has got lane L's place from it.
 // active: the lane's block exists.
 // kWhole as BrickGeom::whole.  Where rows are whole lines, pieces of 16 bytes go out with the non-temporal hint: what is written is not read back, and
-// the lines that neighbouring tiles complete leave the cache together.  Decompress of 32x64x128x128 FP64 / i16 in 4^4 blocks 86 -> 55 us; 21 shapes, nine
-// types, 2^21 to 2^26 elements: 0.89 of the time.  Lines that rows only share are written twice then: 92x92x92x88 FP32 in 4^4 blocks (352-byte rows) 1.37 of the
+// it does not stay in the caches to be written out beside the reads of the next call.  32x64x128x128 FP64 / i16 in 4^4 blocks, by turns: decompress 62 -> 54 us,
+// the compress that follows 89 -> 61.  Decompress of 21 shapes, nine types, with what is above: 0.94 of the time at 2^22 elements, 0.93 at 2^24, 0.97 at 2^26.  Lines that rows only share are written twice then: 92x92x92x88 FP32 in 4^4 blocks (352-byte rows) 1.37 of the
 // time, so not there; nor for loads, whose lines would be fetched anew by the next piece (1.1-2.4).
 template <int kWhole, typename T, typename XT, typename S>
 __device__ __forceinline__ void store_rows(const BrickGeom& g, uint8_t* lds, int lane, XT* y, const Place& p, bool active,
