@@ -25,7 +25,8 @@ VALUES = {
     # every 64th far away, the others one period after the other
     "periodic": lambda g, n: np.where(np.arange(n) % 64 == 5, 1e6, np.sin(np.arange(n) * (2 * np.pi / 64))),
 }
-SIZES = [1, 2, 255, 4095, 4096, 4097, 8193, 70001, 524288, 1 << 20]
+# 70001, 300001 and 524288: four, eight and sixteen samples a bucket; 2^20: four again, of which the sort takes as many as it can hold
+SIZES = [1, 2, 255, 4095, 4096, 4097, 8193, 70001, 300001, 524288, 1 << 20]
 
 
 @pytest.mark.parametrize("values", list(VALUES))
@@ -54,15 +55,32 @@ def test_more_blocks_than_the_sample_sort_takes():
     test_distance_at_every_path_of_the_sort(n - 1, "mostly zero")
 
 
-def sampled(n):
-    """The places in the input from which the splitters of the sample sort are drawn (sample_place of the kernel)."""
+def buckets_of_sort(n):
     buckets = 1
     while n > 4096 and buckets * 2048 < n:
         buckets *= 2
-    shift = min(4 * buckets, 4096).bit_length() - 1
+    return buckets
+
+
+def sampled(n):
+    """The places in the input from which the splitters of the sample sort are drawn: more of them a bucket where buckets are large, and at most
+    2048 of few buckets (sample_place of the kernels, and the rule where they are launched)."""
+    buckets = buckets_of_sort(n)
+    per_bucket, most = (16 if n > 1400 * buckets else 8 if n > 1100 * buckets else 4, 2048) if buckets <= 256 else (4, 4096)
+    shift = (min(per_bucket * buckets, most) - 1).bit_length()
     i = np.arange(1 << shift, dtype=np.int64)
     lo, hi = (n * i) >> shift, (n * (i + 1)) >> shift
     return lo + ((((i * 2654435761) & 0xFFFFFFFF) * (hi - lo)) >> 32)
+
+
+def keys_of_buckets(v):
+    """How many of the values lie between neighbouring splitters, which are left out."""
+    n = len(v)
+    drawn, buckets = np.sort(v[sampled(n)]), buckets_of_sort(n)
+    split = drawn[(np.arange(1, buckets) * len(drawn)) // buckets - 1]
+    ends = np.sort(v)
+    above = np.append(np.searchsorted(ends, split, "left"), n)
+    return above - np.append(0, np.searchsorted(ends, split, "right"))
 
 
 def hidden_cluster(g, n):
@@ -72,6 +90,8 @@ def hidden_cluster(g, n):
     free = np.setdiff1d(np.arange(n), sampled(n))
     take = free[g.random(free.size) < 0.4]
     v[take] = 0.5 + 1e-6 * g.random(take.size)
+    if 65536 < n <= 1 << 22:                                         # that the sample sort takes: one bucket with all of the cluster
+        assert keys_of_buckets(v).max() >= take.size > 8192
     return v
 
 
@@ -127,6 +147,60 @@ def test_block_means_come_out_in_order(n, values):
         assert np.isnan(value).sum() == np.isnan(mean).sum()
         want = np.sort(keys(mean[~np.isnan(mean)]))
         assert np.array_equal(have[~np.isnan(value)], want)
+
+
+@pytest.mark.parametrize("m", [1024, 1025, 2049, 4095, 4096])
+@pytest.mark.parametrize("n", [1 << 18, 300001, 1 << 20])
+def test_bucket_that_is_crowded_between_its_own_splitters(n, m):
+    """A bucket of m keys, 150 of them next to each other in the order and none where the bucket draws its own 256 splitters: too many in one
+    interval, by value and between those.  Such a bucket is left to k_bucket_sort_rest, which sorts it in registers, four keys a thread.  Tiles
+    of the input come into a bucket one after the other, so runs of keys that are drawn and runs that are not lie in a tile each."""
+    g = np.random.Generator(np.random.PCG64(n + m))
+    buckets, tiles = buckets_of_sort(n), min(-(-n // 2048), 256)
+    tile_keys = -(-n // tiles)
+    # all other keys at most 0 or at least 1, some of them 0 and 1: these two are splitters, and the bucket is what lies between
+    v = np.where(g.random(n) < 0.5, -1.0, 2.0) + g.random(n) * np.where(g.random(n) < 0.1, 0.0, 1e-3)
+    places = sampled(n)
+    v[places[::16]], v[places[8::16]] = 0.0, 1.0
+    v[(v > 0.0) & (v < 1.0)] = 0.0
+    group = np.ones(m, dtype=bool)
+    group[(np.arange(256) * m) // 256] = False
+    group &= np.cumsum(group) <= 150
+    assert group.sum() == 150
+    values = 0.05 + 0.9 * g.random(m)
+    values[np.abs(values - 0.5) < 1e-4] = 0.4
+    values[group] = 0.5 + 1e-9 * g.permutation(150)
+    free = np.setdiff1d(np.arange(n), places)
+    starts = np.flatnonzero(np.diff(group.astype(int), prepend=2))   # of runs
+    ends = np.append(starts[1:], m)
+    tile = 0
+    for a, b in zip(starts, ends):
+        while a < b:
+            room = free[(free >= tile * tile_keys) & (free < min((tile + 1) * tile_keys, n))]
+            take = min(b - a, room.size)
+            v[g.choice(room, take, replace=False)] = values[a:a + take]
+            a, tile = a + take, tile + 1
+    assert tile <= tiles and ((v > 0.0) & (v < 1.0)).sum() == m
+    drawn = np.sort(v[places])
+    split = drawn[(np.arange(1, buckets) * len(drawn)) // buckets - 1]
+    bucket = int(np.searchsorted(split, 1.0))
+    assert split[bucket - 1] == 0.0 and split[bucket] == 1.0 and keys_of_buckets(v)[bucket] == m
+    codec = Codec((2,), "f64", "i8", np.array([True, False]))
+    N = torch.from_numpy(np.abs(v)).cuda()
+    F = torch.from_numpy(np.where(v < 0, -127, 127).astype(np.int8).reshape(n, 1)).cuda()
+    need = ctypes.c_size_t()
+    api.check(codec._lib.pbz_approximate_wasserstein_workspace(codec._h, n, ctypes.byref(need)))
+    workspace = torch.zeros(need.value, dtype=torch.uint8, device="cuda")
+    assert float(codec.approximate_wasserstein(N, F, N, F, 2.0, workspace=workspace).item()) == 0.0
+    up = lambda size: (size + 255) // 256 * 256  # noqa: E731
+    first = 256 + 2 * 1024 * 2 * 8
+    # behind the two operands' keys, twice: the counts, the totals and the splitters; then the list of what was left over
+    rest = first + 2 * up(16 * n) + up(4 * 2 * tiles * 2 * buckets) + up(4 * 2 * 2 * buckets) + up(8 * 2 * buckets)
+    listed = workspace[rest:rest + 8 + 8 * buckets].cpu().numpy().view(np.uint32)
+    assert {2 * bucket, 2 * bucket + 1} <= set(listed[2:2 + int(listed[0])])        # of either operand
+    got = workspace[first:first + 16 * n].cpu().numpy().view(np.uint64).reshape(2, n)
+    want = np.sort(keys(np.abs(v) * np.where(v < 0, -127.0, 127.0) * (1.0 / (127.0 * np.sqrt(2.0)))))
+    assert np.array_equal(got[0], want) and np.array_equal(got[1], want)
 
 
 @pytest.mark.parametrize("ftype,low", [("f64", -np.inf), ("f64", -1.7e308), ("f16", -np.inf)])
