@@ -45,7 +45,7 @@ CASES = {"missed cluster": missed_cluster, "missed value": missed_value, **{k: O
 
 
 @pytest.mark.parametrize("values", list(CASES))
-@pytest.mark.parametrize("n", [64, 65, 1023, 1024, 1025, 4096, 4097, 4128, 5000, 32769, 65535, 65536, 65537])
+@pytest.mark.parametrize("n", [1, 2, 3, 33, 63, 64, 65, 1023, 1024, 1025, 4096, 4097, 4128, 5000, 32769, 65535, 65536, 65537])
 def test_few_block_means_come_out_in_order(n, values):
     g = np.random.Generator(np.random.PCG64(n + len(values)))
     codec = Codec((2,), "f64", "i8", np.array([True, False]))
