@@ -52,9 +52,6 @@ constexpr int kMaxTiles = 256;                   // tiles per operand of the cou
 constexpr int kMinTileKeys = 2048;
 constexpr int kSelectMin = 128;                  // buckets from which k_select pays ...
 constexpr double kSelectGain = 640.0;            // ... where the gap of the maxima, in shares of the larger, times their square is above this
-#ifndef RANGE_MAX
-#define RANGE_MAX 65536
-#endif
 // Few keys (launch_few): ranges of kRangeKeys on average, found by workgroups that each go through all keys, from kMaxSamples keys on; below, a
 // key's rank is counted, and up to kBucketThreads one workgroup does an operand.  What it saves are launches, of 4.5 us in line: nine, or six
 // where there was one bucket, are two, three and five.  Whole distance, us, nine or six launches -> now: 256 blocks 22.4 -> 10.1, 1024 25.8 ->
@@ -1784,13 +1781,12 @@ int launch_few(int64_t n, int kept, const void* N1, const void* F1, const void* 
     hipLaunchKernelGGL(k_distance_of_few, dim3(1), dim3(kOneGroupThreads), 0, s, w.buf0, int(n), w.params, order, least, out);
     return hip_status(hipGetLastError());
   }
-  constexpr int kFewThreads = 256;
-  int64_t tile_keys = kFewThreads;
-  if (n > tile_keys * kMaxTiles) tile_keys = (n + kMaxTiles - 1) / kMaxTiles;
-  const int tiles = int((n + tile_keys - 1) / tile_keys);
+  constexpr int kFewThreads = 256;                         // of k_means, a key each
+  static_assert(kRangeMax <= kFewThreads * kMaxTiles && kMaxTiles <= kStatGroups, "a tile of as many keys, and a record of each");
+  const int tiles = int((n + kFewThreads - 1) / kFewThreads);
   const int samples = int((n + kSampleRun - 1) / kSampleRun);      // in the sorted keys' place, which have none yet
-  const auto means = n <= kMaxSamples ? k_means<false, kFewThreads, 1> : tile_keys > kFewThreads ? k_means<false, kFewThreads, 2, true> : k_means<false, kFewThreads, 1, true>;
-  hipLaunchKernelGGL(means, dim3(unsigned((tiles + 7) / 8 * 8), 2), dim3(kFewThreads), 0, s, N1, F1, N2, F2, nt, it, scale, n, tile_keys, tiles, kept, 1,
+  const auto means = n <= kMaxSamples ? k_means<false, kFewThreads, 1> : k_means<false, kFewThreads, 1, true>;
+  hipLaunchKernelGGL(means, dim3(unsigned((tiles + 7) / 8 * 8), 2), dim3(kFewThreads), 0, s, N1, F1, N2, F2, nt, it, scale, n, int64_t(kFewThreads), tiles, kept, 1,
                      nullptr, w.buf1, nullptr, w.rest, w.partials, w.buf0);
   constexpr int kPerGroup = kRankThreads / kRankLanes;
   if (n <= kMaxSamples) {
