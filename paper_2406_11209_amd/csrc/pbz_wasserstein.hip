@@ -261,16 +261,28 @@ __device__ __forceinline__ void mean_params(const double* partials, int tiles, O
 }
 
 // ---- sample sort -----------------------------------------------------------------------------------------------
+// 32 bits that look arbitrary from a run's number: products with the golden ratio's, the square root of two's and of three's fractions, folded.  One
+// product alone is a lattice over the keys, and with the rows of an image another: places then miss columns (524288 blocks in rows of 725, runs of 256 keys:
+// buckets of up to 14137 keys, 4.6 times the expected most, and 111 us for the distance, 92 with half as many samples; simulated over
+// 1500 images of any size and width, the largest bucket is at most 3.7 of the average now, 41 with one product).
+__device__ __forceinline__ uint32_t scattered(uint32_t i) {
+  i *= 2654435761u;
+  i ^= i >> 15;
+  i *= 1779033703u;
+  i ^= i >> 13;
+  i *= 3144134277u;
+  return i ^ (i >> 16);
+}
 // sample i of 2^shift <= n (both below 2^23): from the i-th run of the keys, at a place that looks arbitrary
 __device__ __forceinline__ int64_t sample_place(int i, int shift, int64_t n) {
   const int64_t lo = (n * i) >> shift, hi = (n * (i + 1)) >> shift;
-  return lo + int64_t((uint64_t(uint32_t(i) * 2654435761u) * uint64_t(hi - lo)) >> 32);
+  return lo + int64_t((uint64_t(scattered(uint32_t(i))) * uint64_t(hi - lo)) >> 32);
 }
 
 // the same for up to kRangeMax keys, of every kSampleRun one
 __device__ __forceinline__ int64_t sample_of_run(int64_t run, int64_t n) {
   const int64_t lo = run * kSampleRun, length = n - lo < kSampleRun ? n - lo : kSampleRun;
-  return lo + int64_t((uint64_t(uint32_t(run) * 2654435761u) * uint64_t(length)) >> 32);
+  return lo + int64_t((uint64_t(scattered(uint32_t(run))) * uint64_t(length)) >> 32);
 }
 
 // Ascending order of p[0 .. m) by the whole workgroup: bitonic merges whose first step folds a run onto itself, so that every

@@ -10,7 +10,7 @@ from oracle import pbz_oracle as po
 from paper_2406_11209_amd import api
 from paper_2406_11209_amd.api import Codec
 from parity import oracle_compressed
-from test_gpu_wasserstein_sort import ORDERS, keys
+from test_gpu_wasserstein_sort import ORDERS, keys, scattered
 
 pytestmark = pytest.mark.gpu
 
@@ -20,7 +20,7 @@ RUN = 32        # of which one mean is a sample
 def unsampled(n):
     run = np.arange(-(-n // RUN), dtype=np.int64)
     length = np.minimum(n - run * RUN, RUN)
-    return np.setdiff1d(np.arange(n), run * RUN + ((((run * 2654435761) & 0xFFFFFFFF) * length) >> 32))
+    return np.setdiff1d(np.arange(n), run * RUN + ((scattered(run) * length) >> 32))
 
 
 def missed_cluster(g, n):

@@ -62,6 +62,15 @@ def buckets_of_sort(n):
     return buckets
 
 
+def scattered(i):
+    """The kernels' 32 bits of a run's number."""
+    x = i.astype(np.uint64)
+    for factor, shift in ((2654435761, 15), (1779033703, 13), (3144134277, 16)):
+        x = (x * np.uint64(factor)) & np.uint64(0xFFFFFFFF)
+        x ^= x >> np.uint64(shift)
+    return x.astype(np.int64)
+
+
 def sampled(n):
     """The places in the input from which the splitters of the sample sort are drawn: more of them a bucket where buckets are large, and at most
     2048 of few buckets (sample_place of the kernels, and the rule where they are launched)."""
@@ -70,7 +79,7 @@ def sampled(n):
     shift = (min(per_bucket * buckets, most) - 1).bit_length()
     i = np.arange(1 << shift, dtype=np.int64)
     lo, hi = (n * i) >> shift, (n * (i + 1)) >> shift
-    return lo + ((((i * 2654435761) & 0xFFFFFFFF) * (hi - lo)) >> 32)
+    return lo + ((scattered(i) * (hi - lo)) >> 32)
 
 
 def keys_of_buckets(v):
@@ -147,6 +156,34 @@ def test_block_means_come_out_in_order(n, values):
         assert np.isnan(value).sum() == np.isnan(mean).sum()
         want = np.sort(keys(mean[~np.isnan(mean)]))
         assert np.array_equal(have[~np.isnan(value)], want)
+
+
+@pytest.mark.parametrize("seed", range(3))
+@pytest.mark.parametrize("n,width", [(524288, 725), (131072, 363), (262144, 512), (400000, 1000), (99000, 330)])
+def test_buckets_of_an_image_are_even(n, width, seed):
+    """Means in the rows of a smooth image with a little noise: no bucket of its 4 to 16 samples has more keys than a workgroup holds, whatever the rows'
+    length is to the runs of which one key each is a sample (a bucket of 4 samples has 4 times the average once in 10^4)."""
+    g = np.random.Generator(np.random.PCG64(n + seed))
+    rows = -(-n // width)
+    y, x = np.arange(rows)[:, None] / rows, np.arange(width)[None, :] / width
+    v = 1e-3 * g.standard_normal((rows, width))
+    for _ in range(12):
+        cy, cx, size = g.random(), g.random(), g.uniform(0.02, 0.1)
+        v += g.uniform(-1, 1) * np.exp(-((y - cy) ** 2 + (x - cx) ** 2) / (2 * size * size))
+    v = v.reshape(-1)[:n]
+    codec = Codec((2,), "f64", "i8", np.array([True, False]))
+    N = torch.from_numpy(np.abs(v)).cuda()
+    F = torch.from_numpy(np.where(v < 0, -127, 127).astype(np.int8).reshape(n, 1)).cuda()
+    need = ctypes.c_size_t()
+    api.check(codec._lib.pbz_approximate_wasserstein_workspace(codec._h, n, ctypes.byref(need)))
+    workspace = torch.zeros(need.value, dtype=torch.uint8, device="cuda")
+    codec.approximate_wasserstein(N, F, N, F, 2.0, workspace=workspace)
+    buckets, tiles = buckets_of_sort(n), min(-(-n // 2048), 256)
+    up = lambda size: (size + 255) // 256 * 256  # noqa: E731
+    totals = 256 + 2 * 1024 * 2 * 8 + 2 * up(16 * n) + up(4 * 2 * tiles * 2 * buckets)
+    got = workspace[totals:totals + 16 * buckets].cpu().numpy().view(np.uint32).reshape(2, buckets, 2)
+    assert got[0].sum() == n and np.array_equal(got[0][:, 0], keys_of_buckets(v))
+    assert got[0][:, 0].max() <= 8192
 
 
 @pytest.mark.parametrize("m", [1024, 1025, 2049, 4095, 4096])
