@@ -1398,10 +1398,13 @@ __global__ __launch_bounds__(kBucketThreads) void k_means_in_order(const void* _
 
 // Workgroup b of an operand goes through all of its keys, which its L2 holds, counts those below its own range (between
 // two splitters, the upper one included), and sorts those in it: no counting of buckets, no scattering, no list of what is left over.  More than
-// kBucketThreads, and the range ends at one of them instead, and goes on from there: at a place among those that were collected that leaves
-// out a third of them at least.  The last workgroup along x makes the parameters.  Bounds: the reads from L2 (64 bytes a cycle and compute unit)
-// and the compares, 20 us for 2 x 65536 keys; the exchanges, 4 us, from 16384 keys down (11 us).
+// kBucketThreads are sorted in two to a thread (one range of some thousand at full size: 65536 blocks with such a range 69 -> 43 us, by another walk
+// through all keys before), more than kRangeHeld, and the range ends at one of them instead, and goes on from there: at a place among those that
+// were collected that leaves out a third of them at least.  The last workgroup along x makes the parameters.  Bounds: the reads from L2 (64 bytes a
+// cycle and compute unit) and the compares, 20 us for 2 x 65536 keys; the exchanges, 4 us, from 16384 keys down (11 us).  74 registers and so one
+// workgroup a compute unit: two, in 64 registers, are slower (52000 blocks 38 -> 45 us for the whole distance).
 constexpr int kRangeInFlight = 16;
+constexpr int kRangeHeld = 2 * kBucketThreads;
 __global__ __launch_bounds__(kBucketThreads) void k_range_sort(const uint64_t* __restrict__ keys, uint64_t* __restrict__ sorted, int n, int buckets,
                                                                const uint64_t* __restrict__ splitters, const double* __restrict__ partials,
                                                                int tiles, OperandParams* __restrict__ params) {
@@ -1409,7 +1412,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_range_sort(const uint64_t* _
     mean_params(partials, tiles, params);
     return;
   }
-  __shared__ uint64_t lds[2 * kBucketThreads];              // the second half also: the keys of the range as they come
+  __shared__ uint64_t lds[2 * kRangeHeld];                  // the second half also: the keys of the range as they come
   __shared__ int counted[3];                               // keys below the range, equal to its end, inside
   __shared__ uint64_t cut;
   const uint64_t* in = keys + int64_t(blockIdx.y) * n;
@@ -1440,7 +1443,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_range_sort(const uint64_t* _
           if (k[u] == end) ++equal;                        // (also what is beyond the last, where the range has no end)
           else {
             const int at = atomicAdd(&counted[2], 1);
-            if (at < kBucketThreads) lds[kBucketThreads + at] = k[u];
+            if (at < kRangeHeld) lds[kRangeHeld + at] = k[u];
           }
         }
       }
@@ -1454,18 +1457,24 @@ __global__ __launch_bounds__(kBucketThreads) void k_range_sort(const uint64_t* _
       atomicAdd(&counted[1], equal);
     }
     __syncthreads();
-    const int inside = counted[2], m = inside < kBucketThreads ? inside : kBucketThreads;
+    const int inside = counted[2], m = inside < kRangeHeld ? inside : kRangeHeld;
     below = counted[0];
     equal = counted[1];
-    uint64_t key = t < m ? lds[kBucketThreads + t] : ~uint64_t(0);
-    sort_group<1, true>(&key, m, lds);
-    if (inside > kBucketThreads) {
-      if (t == int(int64_t(kBucketThreads) * (kBucketThreads * 2 / 3) / inside)) cut = key;
+    uint64_t key[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) key[j] = j * kBucketThreads + t < m ? lds[kRangeHeld + j * kBucketThreads + t] : ~uint64_t(0);
+    if (m <= kBucketThreads) sort_group<1, true>(key, m, lds);            // uniform
+    else sort_group<2, true>(key, m, lds);
+    if (inside > kRangeHeld) {
+      const int place = int(int64_t(kRangeHeld) * (kRangeHeld * 2 / 3) / inside);
+      if (t == place % kBucketThreads) cut = place < kBucketThreads ? key[0] : key[1];
       __syncthreads();
       end = cut;                                           // below the old end
       continue;
     }
-    if (t < m) out[below + t] = key;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (j * kBucketThreads + t < m) out[below + j * kBucketThreads + t] = key[j];
     if (end != ~uint64_t(0))
       for (int i = t; i < equal; i += kBucketThreads) out[below + m + i] = end;
     if (end == last) break;                                // uniform

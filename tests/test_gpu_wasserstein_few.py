@@ -71,3 +71,26 @@ def test_few_block_means_come_out_in_order(n, values):
     if len(oc) == 2:
         want = po.approximate_wasserstein(*oc, 2.0)
         assert abs(got - want) <= 1e-9 * abs(want) + 1e-300, (got, want)      # the bar of the other tests of this distance
+
+
+@pytest.mark.parametrize("m", [1023, 1024, 1025, 1500, 2047, 2048, 2049, 4100])
+@pytest.mark.parametrize("n", [16384, 65536])
+def test_ranges_about_what_a_workgroup_sorts_at_once(n, m):
+    """A range of m means: one to a thread, two to a thread, and more than are held at once."""
+    g = np.random.Generator(np.random.PCG64(n + m))
+    free = unsampled(n)
+    drawn = np.setdiff1d(np.arange(n), free)
+    # all others at most 0 or at least 1, and enough samples 0 and 1 for both to be splitters: the range is what lies between
+    v = np.where(g.random(n) < 0.5, -g.random(n), 1.0 + g.random(n))
+    v[drawn[::8]], v[drawn[4::8]] = 0.0, 1.0
+    v[g.choice(free, m, replace=False)] = 0.01 + 0.98 * g.random(m)
+    codec = Codec((2,), "f64", "i8", np.array([True, False]))
+    N, F = torch.from_numpy(np.abs(v)).cuda(), torch.from_numpy(np.where(v < 0, -127, 127).astype(np.int8).reshape(n, 1)).cuda()
+    need = ctypes.c_size_t()
+    api.check(codec._lib.pbz_approximate_wasserstein_workspace(codec._h, n, ctypes.byref(need)))
+    workspace = torch.full((need.value,), 255, dtype=torch.uint8, device="cuda")
+    assert float(codec.approximate_wasserstein(N, F, N, F, 2.0, workspace=workspace).item()) == 0.0
+    first = 256 + 2 * 1024 * 2 * 8
+    out = workspace[first:first + 16 * n].cpu().numpy().view(np.uint64).reshape(2, n)
+    want = np.sort(keys(np.abs(v) * np.where(v < 0, -127.0, 127.0) * (1.0 / (127.0 * np.sqrt(2.0)))))
+    assert np.array_equal(out[0], want) and np.array_equal(out[1], want)
