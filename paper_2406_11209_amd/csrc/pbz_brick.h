@@ -113,32 +113,68 @@ constexpr bool fits(int v, int bw, int bz, int by, int bx) {
 // few_to, where the two meet, is 4 Mi elements (one or two waves per SIMD with the larger tiles), 2 Mi for lanes of 8, and 8 Mi against
 // 64 values of FP32 and for the runs above, decompressing; in FP64 work 16-bit arrays, whose compression waits least, 1 Mi (4x4x8 at 2 and
 // 4 Mi: 1.08).
+// What those means hide, by shape and mask: each line with the time at these sizes over the larger tiles' of 64
+// (FP32 work) and 32 (FP64 work) values:
+//   FP32 work, compressing, single rows under many outer indices (2x8x8, 16x8, 16x16): runs of two indices to a lane with 32 values, 1.15-1.45
+//     from 2^22 on; with 16, a store each, 0.82-0.98; under a mask 2x8x8 with 32 1.05-1.13 and 64 then (16x8 with 32 0.95-1.0);
+//   FP32 work, 4x4x4x4 of up to 32-bit arrays, nothing pruned: compressing 32 1.08-1.24, 16 0.87-1.0 up to 2^24 and 1.06-1.13 beyond, where 64;
+//     decompressing 16-bit arrays 32 1.05-1.09, so 64;
+//   4x8x8, compressing: 32 1.06-1.16 in FP32 work at 4 Mi (but FP64 arrays), under a mask at 2 Mi already (FP64 work 1.1-1.5); decompressing under
+//     one in FP32 work 1.05 at 4 Mi;
+//   4x4x8 in FP64 work under a mask, compressing: 16 1.1-1.4 from 1 Mi on;
+//   2x8x8 of FP32 and FP64 arrays in FP32 work under a mask, decompressing: 16 1.03-1.08 at 4 Mi;
+//   2x4x4x4 and 8x16 of up to 32-bit arrays in FP64 work under a mask, compressing: 16 0.87-1.0 up to 2^24, 1.04-1.07 beyond;
+//   FP64 arrays with 8-bit indices: 4x8 and 8x4 compressing 8 1.07-1.1 from 1.5 Mi on; 4x4 decompressing under a mask 16 0.98 up to 2^25, 1.1 beyond.
 struct Tiles {
   int few, many;
   int64_t few_to;
 };
-constexpr Tiles tiles(bool wide, bool compress, int array, int bw, int bz, int by, int bx) {
+constexpr Tiles tiles(bool wide, bool compress, int array, int index, bool pruned, int bw, int bz, int by, int bx) {
   constexpr int64_t kMi = int64_t(1) << 20;
   const int rows = bw * bz * by, vol = rows * bx;
   const bool shortest = (vol == 32 && rows > 1) || (bw * bz == 1 && by == 8 && bx == 8);
   const int few = shortest ? 8 : (fits(16, bw, bz, by, bx) ? 16 : (fits(32, bw, bz, by, bx) ? 32 : 64));
   const bool narrow = vol != 32 && few <= 16 && outer_rows(16, bw, bz, by, bx) <= 8;
+  const bool single = few == 16 && inner_rows(32, bw, bz, by, bx) == 1 && outer_rows(32, bw, bz, by, bx) > 8;
+  const bool flat = bw * bz == 1, tesseract = bw == 4 && vol == 256, slab = few == 32 && vol == 256;
   int many = 32;
   if (bx == 64 || (few >= 32 && vol >= 256)) many = 64;
   else if (wide) many = vol == 16 || (compress && narrow) ? 16 : 32;
+  else if (compress && single && (!pruned || !flat)) many = pruned ? 64 : 16;
+  else if (compress && tesseract && !pruned && array < 8) many = 64;
   else if (compress) many = vol <= 16 || (array == 8 && few == 16) ? 16 : (vol == 64 ? 64 : 32);
-  else if (array == 8 || vol <= 16 || vol == 64 || (inner_rows(32, bw, bz, by, bx) == 1 && outer_rows(32, bw, bz, by, bx) > 8)) many = 64;
+  else if (array == 8 || vol <= 16 || vol == 64 || single || (tesseract && !pruned && array == 2)) many = 64;
   int64_t to = few == 8 ? 2 * kMi : 4 * kMi;
   if (few > 8 && (wide ? !compress && narrow : many == 64)) to = 8 * kMi;
   if (wide && compress && array == 2) to = few == 32 ? 2 * kMi : kMi;
+  if (compress) {
+    if (slab && pruned) to = 2 * kMi;
+    else if (slab && array < 8 && to > 4 * kMi) to = 4 * kMi;
+    else if (!wide && tesseract && !pruned && array < 8) to = 16 * kMi;
+    else if (!wide && single && pruned && array < 8) to = 4 * kMi;
+    else if (wide && pruned && bz == 4 && by == 4 && bx == 8) to = kMi;
+    else if (wide && index == 1 && few == 8 && vol == 32) to = 3 * kMi / 2;
+    if (wide && pruned && narrow && vol == 128 && array < 8) {
+      many = 32;
+      to = 16 * kMi;
+    }
+  } else if (pruned) {
+    if (!wide && ((slab && array < 8) || (single && !flat && array > 2))) to = 4 * kMi;
+    if (wide && index == 1 && vol == 16 && rows > 1) {
+      many = 32;
+      to = 32 * kMi;
+    }
+  }
   return {few, many, few == 64 ? 0 : to};
 }
-// whether kernels with v values are needed for any type of array
+// whether kernels with v values are needed for any types and masks
 constexpr bool needed(int v, bool wide, bool compress, int bw, int bz, int by, int bx) {
-  for (int array = 2; array <= 8; array *= 2) {
-    const Tiles t = tiles(wide, compress, array, bw, bz, by, bx);
-    if (v == t.many || (v == t.few && t.few_to > 0)) return true;
-  }
+  for (int array = 2; array <= 8; array *= 2)
+    for (int index = 1; index <= 4; index *= 2)
+      for (int pruned = 0; pruned < 2; ++pruned) {
+        const Tiles t = tiles(wide, compress, array, index, pruned != 0, bw, bz, by, bx);
+        if (v == t.many || (v == t.few && t.few_to > 0)) return true;
+      }
   return false;
 }
 
@@ -949,9 +985,11 @@ bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_
   const bool pruned = c->kept != c->vol, ragged = row % S::BX != 0 || row * array % 16 != 0;
   if (c->route == kRouteShape || S::BX == 64) return true;
   const bool looked_up = !compress && pruned && !ragged && t.few == 32 && (S::VOL == 1024 ? !kWide && array < 8 : S::VOL == 256 && array == 2);
-  if (elements <= t.few_to && !looked_up) return true;
-  if (index == 4 && !pruned && ((k8x8 && !(compress && ragged && array == 2)) || (k4x8 && !compress && array == 8)))
-    return elements <= (compress ? 4096 : 1024);
+  const bool rows_of_32 = !compress && kWide && index == 4 && !pruned && !ragged &&
+                          ((S::ROWS == 1 && S::BX == 32 && elements <= kMi) || (t.few == 32 && S::VOL == 256 && array == 2 && elements <= kMi / 2));
+  const bool large = !compress && !kWide && S::VOL == 1024 && array == 8 && pruned && elements > 4 * kMi;
+  if (elements <= t.few_to && !looked_up && !rows_of_32 && !large) return true;
+  if (index == 4 && !pruned && ((k8x8 && !(compress && ragged && array == 2)) || (k4x8 && !compress && array == 8))) return false;
   if (compress) {
     const bool enough = elements <= 4096 || elements >= 3 * kMi;
     if (kWide) return pruned || !(t.many == 64 && (index == 4 || array == 8)) || enough;
@@ -973,7 +1011,7 @@ bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_
 template <typename T, bool kCompress, int BW, int BZ, int BY, int BX, typename F>
 int with_shape(const pbz_codec* c, int xtype, const BrickGeom& g, int64_t row, bool dry_run, F f) {
   constexpr bool kWide = sizeof(T) == 8;
-  const Tiles t = tiles(kWide, kCompress, ftype_bytes(xtype), BW, BZ, BY, BX);
+  const Tiles t = tiles(kWide, kCompress, ftype_bytes(xtype), itype_bytes(c->itype), c->kept != c->vol, BW, BZ, BY, BX);
   const int64_t elements = int64_t(g.n_blocks) * BW * BZ * BY * BX;
   if (!pays<T, Shape<T, BW, BZ, BY, BX, 64>>(c, kCompress, xtype, elements, row, t)) return 0;
   if (dry_run) return 1;
