@@ -71,14 +71,14 @@ static bool shape_kernels_pay(const pbz_codec* c, const fast::Folded& f, int xty
   if (blocks * f.bz * f.by * f.bx < int64_t(1) << 16) return false;      // a few us whichever way
   const double fill = double(g.gx) / double(tiles * per_wave);
   const int array = ftype_bytes(xtype), index = itype_bytes(c->itype);
-  const bool ragged = f.tail_x, wide = c->compute_f64;
+  const bool ragged = f.tail_x, wide = c->compute_f64, haar = c->transform == PBZ_TRANSFORM_HAAR;
   const auto from = [&](int64_t least_waves, double most_fill) { return waves >= least_waves && fill <= most_fill; };
   constexpr double kAny = 1.0;
   if (lane && compress) {
     if (!ragged) return from(2000, array == 8 ? (flat ? 0.44 : 0.25) : (index == 4 ? 0.15 : 0.2));
-    if (!flat) return array == 8 ? g.gx <= (index == 1 ? 48 : (index == 2 ? 20 : 12)) || from(2000, kAny) : from(1300, 0.32);
+    if (!flat) return array == 8 ? g.gx <= (index == 1 ? 48 : (index == 2 ? 20 : 12)) || from(2000, index == 4 ? 0.9 : kAny) : from(1300, 0.32);
     if (array == 8) return g.gx <= 40 || from(2000, kAny) || blocks <= 24 * 1024;
-    return index == 1 ? g.gx <= 8 || from(2000, kAny) : g.gx <= 4 || from(2000, 0.35);
+    return index == 1 ? g.gx <= 8 || from(2000, 0.8) : g.gx <= 4 || from(2000, 0.35);
   }
   if (lane && !flat) {
     if (fill <= 0.15) return true;
@@ -86,25 +86,26 @@ static bool shape_kernels_pay(const pbz_codec* c, const fast::Folded& f, int xty
     return from(2000, index == 2 ? 0.4 : (array == 8 ? 0.3 : 0.25));
   }
   if (lane) {
-    if (!ragged) return from(2500, index == 4 ? 0.15 : (index == 2 && array == 4 ? 0.25 : (array == 8 ? 0.5 : 0.45)));
-    if (array == 2) return from(0, 0.9) || from(4000, kAny);
+    if (!ragged) return from(2500, index == 4 || (haar && array < 8) ? 0.15 : (index == 2 && array == 4 ? 0.25 : (array == 8 ? 0.5 : 0.35)));
+    if (array == 2) return from(0, 0.6);
     if (array == 8) return from(700, kAny);
     return index == 1 ? from(2800, kAny) : from(2000, 0.4);
   }
   if (quad && compress) {
     if (!ragged) return from(2000, array == 8 && !wide ? 0.4 : 0.5);
-    return from(500, 0.5) || from(4500, index == 4 ? 0.75 : 0.9);
+    return from(500, 0.5) || from(4500, array == 8 || index == 4 ? 0.75 : 0.9);
   }
   if (quad) {
-    if (array == 8 && wide) return from(2000, ragged ? kAny : 0.95);
-    return from(!ragged && c->transform == PBZ_TRANSFORM_HAAR ? 2000 : 0, 0.5);
+    if (array == 8 && wide) return from(2000, index == 4 ? 0.5 : (ragged ? (index == 2 ? 0.8 : 0.65) : 0.95));
+    return haar && !ragged ? from(2000, 0.3) : from(0, ragged ? 0.5 : 0.4);
   }
   if (compress) {
     if (ragged && array == 8) return wide || from(2000, kAny);
     return from(4000, 0.25) || (ragged && from(8000, 0.5));
   }
-  if (ragged) return array == 8 ? true : (array == 4 && from(2800, index == 1 ? 0.95 : 0.4));
-  return from(2800, 0.4);
+  if (ragged && array == 8) return blocks >= (index == 4 ? 9 * 1024 : 6 * 1024);
+  if (ragged) return array == 4 && from(2800, index == 1 ? 0.95 : (index == 4 ? 0.25 : 0.4));
+  return from(2800, haar ? 0.15 : (index == 4 ? 0.25 : 0.4));
 }
 
 // Up to how many elements the kernels per block shape are the faster ones for any row width, with their smaller tiles: a family's wave holds

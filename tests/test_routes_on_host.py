@@ -1,0 +1,33 @@
+"""Which kernels a call of a specialised family goes to (host only): settings that the kernels per block shape took while the family's own were the faster
+ones, and the same settings on the other side of each line."""
+import pytest
+
+from paper_2406_11209_amd.api import Codec
+from parity import EXACT, SHAPE, route
+
+# direction, block, array, work, index bits, transform, [(shape, kernels)]
+LINES = [("decompress", (8, 8, 8), "f64", "f64", 8, "dct", [((4, 3, 1390), EXACT), ((48, 139, 76), EXACT), ((64, 184, 250), EXACT), ((64, 248, 250), SHAPE)]),    # 1.2-1.9 of the time up to 2 Mi
+         ("decompress", (8, 8, 8), "f64", "f64", 8, "haar", [((224, 146, 13), EXACT), ((64, 248, 250), SHAPE)]),
+         ("decompress", (8, 8, 8), "f64", "f64", 32, "dct", [((64, 248, 250), EXACT), ((64, 400, 250), SHAPE)]),
+         ("decompress", (8, 8, 8), "f32", "f32", 32, "dct", [((232, 816, 24), EXACT), ((320, 816, 16), SHAPE), ((648, 312, 23), EXACT)]),
+         ("decompress", (8, 8, 8), "f32", "f32", 16, "dct", [((232, 816, 24), SHAPE)]),
+         ("decompress", (8, 8, 8), "bf16", "bf16", 8, "haar", [((688, 384, 24), EXACT), ((1400, 384, 8), SHAPE)]),
+         ("decompress", (16, 16), "f64", "f64", 32, "dct", [((5401, 1336), EXACT), ((40000, 120), SHAPE), ((34144, 224), EXACT)]),
+         ("decompress", (16, 16), "f64", "f32", 32, "dct", [((34144, 226), EXACT)]),
+         ("decompress", (16, 16), "f64", "f64", 8, "dct", [((13264, 1114), EXACT), ((40000, 150), SHAPE)]),
+         ("decompress", (16, 16), "f64", "f64", 16, "dct", [((12640, 1580), EXACT), ((40000, 190), SHAPE)]),
+         ("decompress", (16, 16), "f32", "f32", 8, "haar", [((148560, 96), EXACT), ((148560, 64), SHAPE)]),
+         ("decompress", (16, 16), "f32", "f32", 8, "dct", [((148560, 128), EXACT), ((148560, 96), SHAPE)]),
+         ("decompress", (8, 8), "f16", "f16", 8, "dct", [((6640, 1294), EXACT), ((15651, 322), EXACT), ((20000, 300), SHAPE)]),
+         ("decompress", (8, 8), "f32", "f32", 8, "dct", [((20104, 216), EXACT), ((40000, 160), SHAPE)]),
+         ("decompress", (8, 8), "f32", "f32", 8, "haar", [((40000, 160), EXACT), ((60000, 72), SHAPE)]),
+         ("compress", (16, 16), "f64", "f64", 8, "haar", [((28083, 1538), EXACT), ((100000, 190), SHAPE)]),
+         ("compress", (8, 8), "f32", "f32", 8, "dct", [((4568, 1990), EXACT), ((30000, 398), SHAPE)]),
+         ("compress", (4, 4, 4), "f64", "f64", 32, "dct", [((60, 140, 1502), EXACT), ((60, 600, 226), SHAPE)])]
+
+
+@pytest.mark.parametrize("line", LINES, ids=lambda line: "-".join(map(str, line[:6])))
+def test_where_the_lines_lie(line):
+    op, block, dtype, ftype, bits, transform, calls = line
+    codec = Codec(block, ftype, bits, None, transform)
+    assert [(shape, route(codec, op, shape, dtype)) for shape, _ in calls] == calls
