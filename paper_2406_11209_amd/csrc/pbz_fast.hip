@@ -89,7 +89,7 @@ static bool shape_kernels_pay(const pbz_codec* c, const fast::Folded& f, int xty
     if (!ragged) return from(2500, index == 4 || (haar && array < 8) ? 0.15 : (index == 2 && array == 4 ? 0.25 : (array == 8 ? 0.5 : 0.35)));
     if (array == 2) return from(0, 0.6);
     if (array == 8) return from(700, kAny);
-    return index == 1 ? from(2800, kAny) : from(2000, 0.4);
+    return index == 1 ? from(2800, kAny) : from(2000, haar ? 0.22 : 0.4);
   }
   if (quad && compress) {
     if (!ragged) return from(2000, array == 8 && !wide ? 0.4 : 0.5);

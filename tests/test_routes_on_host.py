@@ -21,6 +21,8 @@ LINES = [("decompress", (8, 8, 8), "f64", "f64", 8, "dct", [((4, 3, 1390), EXACT
          ("decompress", (8, 8), "f16", "f16", 8, "dct", [((6640, 1294), EXACT), ((15651, 322), EXACT), ((20000, 300), SHAPE)]),
          ("decompress", (8, 8), "f32", "f32", 8, "dct", [((20104, 216), EXACT), ((40000, 160), SHAPE)]),
          ("decompress", (8, 8), "f32", "f32", 8, "haar", [((40000, 160), EXACT), ((60000, 72), SHAPE)]),
+         ("decompress", (8, 8), "f32", "f32", 16, "haar", [((16417, 191), EXACT), ((23974, 188), EXACT), ((79266, 107), SHAPE)]),     # 1.1-1.4
+         ("decompress", (8, 8), "f32", "f32", 16, "dct", [((126787, 178), SHAPE)]),
          ("compress", (16, 16), "f64", "f64", 8, "haar", [((28083, 1538), EXACT), ((100000, 190), SHAPE)]),
          ("compress", (8, 8), "f32", "f32", 8, "dct", [((4568, 1990), EXACT), ((30000, 398), SHAPE)]),
          ("compress", (4, 4, 4), "f64", "f64", 32, "dct", [((60, 140, 1502), EXACT), ((60, 600, 226), SHAPE)])]
