@@ -3,7 +3,7 @@
 // types they are not built for).  pbz_tiled.hip takes the shapes that are not listed, and the calls that pays() below leaves it.
 // The list is a choice, not a bound: the families' shapes, the cubes, squares and lines that the method is described for, and their
 // neighbours.  The template takes any shape of its static_asserts' kind (8x8x4, 16x32 and 2x16 stay tiled at 2-3.4 TB/s); every
-// shape adds 0.4 MB to the library and some seconds to its build.
+// shape adds 0.6 MB to the library, with two or three sizes of tile each way, and some seconds to its build.
 //
 // Wave autonomous like the families: a wave owns a tile of consecutive blocks, VALUES (8 to 64, by shape and size of the
 // call: tiles()) values per lane in registers, no workgroup barrier, LDS private to the wave.  Two layouts, each with whole lines of its dimensions
@@ -513,10 +513,17 @@ __device__ __forceinline__ void load_rows(const BrickGeom& g, const XT* x, const
 // 8x16 blocks 110 us, 79 as here; in 32x32 blocks 135 and 90; 4x8x8 of the same size 77 and 67).  Piece k of lane L goes
 // to slot L COUNT + k, and 64 consecutive slots are stored at a time, each by a lane that has got lane L's place from it.
 // active: the lane's block exists.
-// kWhole as BrickGeom::whole.  Where rows are whole lines, pieces of 16 bytes go out with the non-temporal hint: what is written is not read back, and
-// it does not stay in the caches to be written out beside the reads of the next call.  32x64x128x128 FP64 / i16 in 4^4 blocks, by turns: decompress 62 -> 54 us,
-// the compress that follows 89 -> 61.  Decompress of 21 shapes, nine types, with what is above: 0.94 of the time at 2^22 elements, 0.93 at 2^24, 0.97 at 2^26.  Lines that rows only share are written twice then: 92x92x92x88 FP32 in 4^4 blocks (352-byte rows) 1.37 of the
-// time, so not there; nor for loads, whose lines would be fetched anew by the next piece (1.1-2.4).
+// kWhole as BrickGeom::whole.  Where rows are whole lines, pieces of 16 bytes go out with the non-temporal hint: what is written does not stay in the
+// caches to be written out beside the reads of the next call.  32x64x128x128 FP64 / i16 in 4^4 blocks, by turns: decompress 62 -> 54 us, the compress of
+// another array that follows 89 -> 61.  At any size, as the array's reader is seldom the next kernel.  Time with the hint / without, of six shapes and
+// types, arrays one after another (least, mean and largest; us are decompress of 4x8x8 FP32):
+//   the array          4 MiB               16 MiB              32-128 MiB          256-512 MiB
+//   decompress         0.89 0.94 1.00      0.73 0.79 0.87      0.78 0.84 0.97      0.83 0.87 1.07     (7, 11 -> 9, 15 -> 12 ... 37 -> 32, 68 -> 59)
+//   and a pass         1.02 1.02 1.02      0.99 1.03 1.05      0.99 1.05 1.10      0.95 0.97 1.00     (of it that at once reads what was written)
+//   and its compress   1.01 1.01 1.02      0.91 0.94 0.99      0.93 1.01 1.09      0.84 0.91 1.03
+// Lines that rows only share are written twice then: 92x92x92x88 FP32 in 4^4 blocks (352-byte rows) 1.37 of the time, so not there; nor for loads, whose
+// lines would be fetched anew by the next piece (1.1-2.4).  A tile of 4^4 blocks of FP32 with 16 values a lane has half lines, whose other halves the
+// next wave stores at about the same time: 0.93-1.01 at 4 MiB, 0.87-0.92 at 16, no worse than the whole lines of larger arrays.
 template <int kWhole, typename T, typename XT, typename S>
 __device__ __forceinline__ void store_rows(const BrickGeom& g, uint8_t* lds, int lane, XT* y, const Place& p, bool active,
                                            const T* v) {
@@ -958,9 +965,9 @@ template <typename T, int BX>
 constexpr bool kTaken = BX < 64 || sizeof(T) == 4;
 
 // When these kernels take a call, against the tiled ones: a wave does a tile in one long straight run of code, so that one alone
-// takes longer than a workgroup with its phases, while many overlap.  Decompress, whose rows pass LDS once more, up to some 2^21
-// elements: 1.05-1.6 of the tiled kernels' time (FP64 work with blocks of 256 and more and 16-bit or 32-bit indices: 9 -> 15 us; FP32 work
-// with rows of 8 to 32: 7 -> 9), 0.75-0.95 from 2^22 on, rows of 16 and more in FP32 work and int32 in small flat blocks from
+// takes longer than a workgroup with its phases, while many overlap.  First what holds for 64 values a lane (32 in FP64 work), that is beyond few_to
+// and for the shapes without smaller tiles.  Decompress, whose rows pass LDS once more, up to some 2^21 elements: 1.05-1.6 of the tiled kernels' time
+// (FP64 work with blocks of 256 and more and 16-bit or 32-bit indices: 9 -> 15 us; FP32 work with rows of 8 to 32: 7 -> 9), 0.75-0.95 from 2^22 on, rows of 16 and more in FP32 work and int32 in small flat blocks from
 // 2^23; not so rows of 4, 4-D blocks in FP32 work, int8 in FP64 work and small blocks there (0.6-1.03 at any size; FP64 arrays in rows
 // of 4: 1.0-1.09).  Under a mask the tiled kernels look every entry up: 8x8, and 16x16 in FP64 work, 0.7-1.0.  Compress: 0.4-1.05 but for
 // FP64 arrays in rows of 16 and more in FP32 work (1.1-1.2), 32x32 blocks of FP32 (1.05), and FP64 work that leaves a lane 64
@@ -973,9 +980,12 @@ constexpr bool kTaken = BX < 64 || sizeof(T) == 4;
 // under a mask, of FP32 arrays (0.9); in FP64 work flat blocks of up to 128 in rows of less than 32 (0.65-0.9; FP64 arrays under a mask only, all of
 // them 1.15), 16x16 of 16-bit arrays with nothing pruned (0.9); and the others, too, from 2^22 on.  Compressing, 8x8 of 16-bit arrays with
 // 32-bit indices (0.88) and 32x32 of FP32 arrays (0.9).
-// Up to few_to elements the smaller tiles win against the tiled kernels throughout (0.57-0.97), but for 32x32 blocks of FP32 and 16-bit
-// arrays in FP32 work and 4x8x8 blocks of 16-bit arrays, decompressing whole rows under a mask (1.04-1.09); what follows is for the larger
-// calls and the shapes that hold 64 values at any size.
+// Up to few_to elements the smaller tiles win against the tiled kernels throughout (0.57-0.97), but, decompressing under a mask,
+//   whole rows of 32x32 blocks of FP32 and 16-bit arrays in FP32 work and of 4x8x8 blocks of 16-bit arrays (1.04-1.09);
+//   rows of whole 16-byte pieces, a quarter kept at most, of 4x8x8 blocks of FP32 and FP64 arrays (1.05-1.23 up to 2^20 elements, 0.83-1.0 with a
+//   half kept) and of 32x32 blocks of FP64 arrays, in FP32 work (1.08-1.27) or with the Haar transform (1.1-1.18; and FP32 work with a half: 1.14);
+// and 32-bit indices with nothing pruned: lines of 32 in rows of whole pieces (1.0-1.1 up to 2^20, the Haar transform 1.2-1.4 up to 2^22), 4x8x8 of
+// 16-bit arrays.  What follows is for the larger calls and the shapes that hold 64 values at any size.
 template <typename T, typename S>
 bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_t row, const Tiles& t) {
   constexpr int64_t kMi = int64_t(1) << 20;
@@ -984,9 +994,14 @@ bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_
   const int array = ftype_bytes(xtype), index = itype_bytes(c->itype);
   const bool pruned = c->kept != c->vol, ragged = row % S::BX != 0 || row * array % 16 != 0;
   if (c->route == kRouteShape || S::BX == 64) return true;
-  const bool looked_up = !compress && pruned && !ragged && t.few == 32 && (S::VOL == 1024 ? !kWide && array < 8 : S::VOL == 256 && array == 2);
-  const bool rows_of_32 = !compress && kWide && index == 4 && !pruned && !ragged &&
-                          ((S::ROWS == 1 && S::BX == 32 && elements <= kMi) || (t.few == 32 && S::VOL == 256 && array == 2 && elements <= kMi / 2));
+  const bool haar = c->transform == PBZ_TRANSFORM_HAAR, in_pieces = row * array % 16 == 0, quarter = 4 * c->kept <= c->vol;
+  const bool looked_up = !compress && pruned && t.few == 32 &&
+                         ((!ragged && (S::VOL == 1024 ? !kWide && array < 8 : S::VOL == 256 && array == 2)) ||
+                          (in_pieces && S::VOL == 256 && array > 2 && quarter && elements <= kMi) ||
+                          (in_pieces && S::VOL == 1024 && array == 8 && (kWide ? haar && quarter : haar || quarter)));
+  const bool rows_of_32 = !compress && kWide && index == 4 && !pruned && in_pieces &&
+                          ((S::ROWS == 1 && S::BX == 32 && elements <= (haar ? 4 * kMi : kMi)) ||
+                           (!ragged && t.few == 32 && S::VOL == 256 && array == 2 && elements <= kMi / 2));
   const bool large = !compress && !kWide && S::VOL == 1024 && array == 8 && pruned && elements > 4 * kMi;
   if (elements <= t.few_to && !looked_up && !rows_of_32 && !large) return true;
   if (index == 4 && !pruned && ((k8x8 && !(compress && ragged && array == 2)) || (k4x8 && !compress && array == 8))) return false;

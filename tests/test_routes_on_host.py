@@ -1,9 +1,10 @@
 """Which kernels a call of a specialised family goes to (host only): settings that the kernels per block shape took while the family's own were the faster
 ones, and the same settings on the other side of each line."""
+import numpy as np
 import pytest
 
 from paper_2406_11209_amd.api import Codec
-from parity import EXACT, SHAPE, route
+from parity import EXACT, SHAPE, TILED, route
 
 # direction, block, array, work, index bits, transform, [(shape, kernels)]
 LINES = [("decompress", (8, 8, 8), "f64", "f64", 8, "dct", [((4, 3, 1390), EXACT), ((48, 139, 76), EXACT), ((64, 184, 250), EXACT), ((64, 248, 250), SHAPE)]),    # 1.2-1.9 of the time up to 2 Mi
@@ -33,3 +34,24 @@ def test_where_the_lines_lie(line):
     op, block, dtype, ftype, bits, transform, calls = line
     codec = Codec(block, ftype, bits, None, transform)
     assert [(shape, route(codec, op, shape, dtype)) for shape, _ in calls] == calls
+
+
+# the same between the kernels per block shape and the tiled ones, with how many of a block's coefficients are kept
+SHAPE_LINES = [((4, 8, 8), "f64", "f32", 16, "dct", 4, [((10, 11, 86), TILED), ((272, 429, 2), TILED), ((10, 11, 86 * 128), SHAPE)]),    # 1.05-1.23 of the time
+               ((4, 8, 8), "f64", "f32", 16, "dct", 2, [((10, 11, 86), SHAPE)]),
+               ((4, 8, 8), "f32", "f32", 8, "dct", 4, [((48, 24, 80), TILED), ((48, 24, 77), SHAPE)]),
+               ((32, 32), "f64", "f32", 8, "dct", 4, [((646, 102), TILED), ((646, 101), SHAPE)]),
+               ((32, 32), "f64", "f32", 8, "dct", 2, [((646, 102), SHAPE)]),
+               ((32, 32), "f64", "f32", 8, "haar", 2, [((646, 102), TILED)]),
+               ((32, 32), "f64", "f64", 16, "haar", 4, [((760, 380), TILED)]),
+               ((32, 32), "f64", "f64", 16, "dct", 4, [((760, 380), SHAPE)]),
+               ((32,), "f32", "f32", 32, "haar", 1, [((24316,), TILED), ((2220256,), TILED), ((24317,), SHAPE)]),                          # 1.2-1.4
+               ((32,), "f64", "f64", 32, "dct", 1, [((24318,), TILED), ((1 << 21,), SHAPE)])]
+
+
+@pytest.mark.parametrize("line", SHAPE_LINES, ids=lambda line: "-".join(map(str, line[:6])))
+def test_where_decompressed_rows_of_whole_pieces_go(line):
+    block, dtype, ftype, bits, transform, share, calls = line
+    mask = np.arange(int(np.prod(block))).reshape(block) % share == 0 if share > 1 else None
+    codec = Codec(block, ftype, bits, mask, transform)
+    assert [(shape, route(codec, "decompress", shape, dtype)) for shape, _ in calls] == calls
