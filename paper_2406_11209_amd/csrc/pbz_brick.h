@@ -77,6 +77,7 @@ struct BrickGeom {
   int xtype, ntype, itype, kept;
   int per_round;                       // blocks whose span of F is in LDS at a time
   uint32_t region;                     // bytes of a wave's LDS
+  uint32_t run;                        // compressing: neighbouring workgroups that go to one die (group_in_runs)
   double r;
   const uint16_t* places;
 };
@@ -699,13 +700,21 @@ __device__ __forceinline__ void each_run(int lane, F f) {
   }
 }
 
+// Which tiles a workgroup of compress takes: its own number's, or, with runs (a power of two), those by which `run` neighbours in F are on one die.
+// Workgroups go to the eight dies in turn, each with an L2 of its own, and a reduction's workgroups take 32 KiB of F each: what a die wrote, it then
+// reads.  The smaller tiles, of 8 and 16 KiB of 32-bit indices, would have given each of its reads halves or quarters of two and four dies.  (Statistics along
+// with the compression, 132x206x136 FP32 / i32 in 4x4x8 blocks: with tiles of 32 values a lane 20.2 us, with 16 24.2, with 16 in runs 19.0; the compression alone 12.3, 11.2, 10.6.)
+__device__ __forceinline__ uint32_t group_in_runs(uint32_t run) {
+  const uint32_t b = blockIdx.x, q = b & (8 * run - 1);
+  return run > 1 && (b | (8 * run - 1)) < gridDim.x ? b - q + (q & 7) * run + (q >> 3) : b;
+}
 template <int TF, typename T, typename S>
 __global__ __launch_bounds__(256, 2) void k_compress_brick(BrickGeom g, const void* __restrict__ x, void* __restrict__ N,
                                                         void* __restrict__ F) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int lane = threadIdx.x & 63;
   uint8_t* st = smem + (threadIdx.x >> 6) * g.region;
-  const uint32_t tile = blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t tile = group_in_runs(g.run) * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t k0 = tile * S::NB;
   if (k0 >= g.n_blocks) return;                            // uniform over the wave
   const int n_active = int(g.n_blocks - k0 < uint32_t(S::NB) ? g.n_blocks - k0 : S::NB);
@@ -948,6 +957,10 @@ void compress_with(BrickGeom g, const void* x, void* N, void* F, hipStream_t s) 
   int threads;
   size_t lds;
   const dim3 grid = brick_launch<T, S, false>(&g, &threads, &lds);
+  const int64_t bytes = int64_t(threads / 64) * S::NB * g.kept * 4;      // of F that a workgroup writes, where indices are of 32 bits
+  g.run = 1;
+  if (g.itype == PBZ_I32 && g.kept == S::VOL && int64_t(g.n_blocks) * g.kept * 4 <= int64_t(1) << 25)      // (beyond, a reduction's workgroups take more)
+    while (g.run * bytes < 32 * 1024) g.run *= 2;
   hipLaunchKernelGGL((k_compress_brick<TF, T, S>), grid, dim3(threads), lds, s, g, x, N, F);
 }
 template <int TF, typename T, typename S>

@@ -116,3 +116,21 @@ def test_rows_of_whole_lines(block):
         assert y.data_ptr() % 128 == 0 and torch.equal(off, y)
         assert bool((wide[:pad] == 7.0).all()) and bool((wide[pad + x.numel():] == 7.0).all())
         assert float((y.double() - x.double()).abs().max()) <= (0.1 if bits == 8 else 1e-2) * float(x.double().abs().max())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("groups", [1, 15, 16, 17, 31, 32, 33, 64, 70])
+@pytest.mark.parametrize("block, step, row", [((4, 4, 8), 4, (16, 64)), ((4, 4, 8), 4, (16, 58)), ((4, 8), 4, (512,)), ((8, 4), 8, (254,)), ((16,), 4096, ())], ids=str)
+def test_workgroups_in_runs(groups, block, step, row):
+    """32-bit indices, nothing pruned: neighbouring workgroups are dealt out in runs.  Every tile is written, and as in calls of one workgroup; numbers of
+    workgroups around whole windows of runs, full and partial last ones."""
+    codec = Codec(block, "f32", 32)
+    x = torch.randn((groups * step,) + row, generator=torch.Generator("cuda").manual_seed(groups), device="cuda")
+    N, F = codec.empty_compressed(x.shape)
+    N.fill_(-1.0)
+    F.fill_(-(2 ** 31))
+    codec.compress(x, N, F)
+    parts = [codec.compress(x[i * step:(i + 1) * step].contiguous()) for i in range(groups)]
+    torch.cuda.synchronize()
+    assert torch.equal(N.flatten(), torch.cat([n.flatten() for n, _ in parts]))
+    assert torch.equal(F.flatten(), torch.cat([f.flatten() for _, f in parts]))
