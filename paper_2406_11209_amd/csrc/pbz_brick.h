@@ -996,9 +996,10 @@ constexpr bool kTaken = BX < 64 || sizeof(T) == 4;
 // Up to few_to elements the smaller tiles win against the tiled kernels throughout (0.57-0.97), but, decompressing under a mask,
 //   whole rows of 32x32 blocks of FP32 and 16-bit arrays in FP32 work and of 4x8x8 blocks of 16-bit arrays (1.04-1.09);
 //   rows of whole 16-byte pieces, a quarter kept at most, of 4x8x8 blocks of FP32 and FP64 arrays (1.05-1.23 up to 2^20 elements, 0.83-1.0 with a
-//   half kept) and of 32x32 blocks of FP64 arrays, in FP32 work (1.08-1.27) or with the Haar transform (1.1-1.18; and FP32 work with a half: 1.14);
-// and 32-bit indices with nothing pruned: lines of 32 in rows of whole pieces (1.0-1.1 up to 2^20, the Haar transform 1.2-1.4 up to 2^22), 4x8x8 of
-// 16-bit arrays.  What follows is for the larger calls and the shapes that hold 64 values at any size.
+//   half kept) and of 32x32 blocks, in FP32 work (1.08-1.27) or with the Haar transform (1.1-1.35; and FP64 arrays, FP32 work, with a half: 1.14),
+//   of 16-bit and FP32 arrays up to 2^20;
+// and 32-bit indices with nothing pruned: lines of 32 decompressing rows of whole pieces (1.0-1.1 up to 2^20, the Haar transform 1.2-1.4 up to 2^22) and
+// both ways between 2 and 3 Mi elements (1.0-1.25; 0.75-0.9 on both sides), 4x8x8 of 16-bit arrays.  What follows is for the larger calls and the shapes that hold 64 values at any size.
 template <typename T, typename S>
 bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_t row, const Tiles& t) {
   constexpr int64_t kMi = int64_t(1) << 20;
@@ -1011,7 +1012,8 @@ bool pays(const pbz_codec* c, bool compress, int xtype, int64_t elements, int64_
   const bool looked_up = !compress && pruned && t.few == 32 &&
                          ((!ragged && (S::VOL == 1024 ? !kWide && array < 8 : S::VOL == 256 && array == 2)) ||
                           (in_pieces && S::VOL == 256 && array > 2 && quarter && elements <= kMi) ||
-                          (in_pieces && S::VOL == 1024 && array == 8 && (kWide ? haar && quarter : haar || quarter)));
+                          (in_pieces && S::VOL == 1024 && (array == 8 || elements <= kMi) && (kWide ? haar && quarter : quarter || (haar && array == 8))));
+  if (S::ROWS == 1 && S::BX == 32 && kWide && index == 4 && !pruned && elements > 2 * kMi && elements < 3 * kMi) return false;
   const bool rows_of_32 = !compress && kWide && index == 4 && !pruned && in_pieces &&
                           ((S::ROWS == 1 && S::BX == 32 && elements <= (haar ? 4 * kMi : kMi)) ||
                            (!ragged && t.few == 32 && S::VOL == 256 && array == 2 && elements <= kMi / 2));

@@ -45,6 +45,9 @@ SHAPE_LINES = [((4, 8, 8), "f64", "f32", 16, "dct", 4, [((10, 11, 86), TILED), (
                ((32, 32), "f64", "f32", 8, "haar", 2, [((646, 102), TILED)]),
                ((32, 32), "f64", "f64", 16, "haar", 4, [((760, 380), TILED)]),
                ((32, 32), "f64", "f64", 16, "dct", 4, [((760, 380), SHAPE)]),
+               ((32, 32), "f32", "f32", 8, "dct", 4, [((752, 40), TILED), ((752, 41), SHAPE), ((2000, 1000), SHAPE)]),                     # 1.06-1.18
+               ((32, 32), "bf16", "f32", 16, "haar", 4, [((306, 312), TILED), ((306, 311), SHAPE), ((2000, 1000), SHAPE)]),                # 1.2-1.36
+               ((32,), "f64", "f64", 32, "haar", 1, [((2350099,), TILED), ((3300099,), SHAPE)]),
                ((32,), "f32", "f32", 32, "haar", 1, [((24316,), TILED), ((2220256,), TILED), ((24317,), SHAPE)]),                          # 1.2-1.4
                ((32,), "f64", "f64", 32, "dct", 1, [((24318,), TILED), ((1 << 21,), SHAPE)])]
 
@@ -55,3 +58,10 @@ def test_where_decompressed_rows_of_whole_pieces_go(line):
     mask = np.arange(int(np.prod(block))).reshape(block) % share == 0 if share > 1 else None
     codec = Codec(block, ftype, bits, mask, transform)
     assert [(shape, route(codec, "decompress", shape, dtype)) for shape, _ in calls] == calls
+
+
+def test_lines_of_32_with_32_bit_indices():
+    for ftype, transform in (("f32", "dct"), ("f64", "haar")):
+        codec = Codec((32,), ftype, 32, None, transform)
+        for n, where in ((2 << 20, SHAPE), ((2 << 20) + 32, TILED), ((3 << 20) - 32, TILED), (3 << 20, SHAPE)):
+            assert route(codec, "compress", (n,), ftype) == where
