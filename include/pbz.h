@@ -129,10 +129,12 @@ int pbz_compressed_bits(const pbz_codec* codec, const int64_t* shape, uint64_t* 
 int pbz_compress(const pbz_codec* codec, const void* x, pbz_ftype x_type, const int64_t* shape, void* N,
                  void* F, void* stream);
 
-/* Compression as pbz_compress plus, from the same pass over x, the statistics of the compressed array that a
+/* Compression as pbz_compress, with the same {N, F}, plus the statistics of the compressed array that a
  * time-series analysis takes of every step (Sec. V): statistics (device, FP64, written) receives the triple
  * {mean (Algorithm 7), variance (Algorithm 9), L2 norm (Algorithm 10)}, the values pbz_mean, pbz_variance and
- * pbz_norm2 return for the {N, F} produced, up to FP64 summation order, without reading {N, F} back.
+ * pbz_norm2 return for the {N, F} produced, up to FP64 summation order.  Where a kernel specialised to this setting takes the
+ * call (pbz_kernel_name says which) they come from the same pass over x, without reading {N, F} back; elsewhere one pass over {N, F}
+ * follows the compression.
  *   per_step    0: one triple for the whole array (3 values).  Non-zero: one triple per block index along
  *               dimension 0, i.e. per run of prod(b[1:]) consecutive blocks, 3 * ceil(shape[0] / block[0]) values,
  *               triple t at statistics[3 t]; with block extent 1 along time these are the statistics of every time

@@ -54,8 +54,10 @@ namespace pbz {
 // faster (1.1-1.4), and where a wave is full enough.  Measured for 2^16 to 2^25.5 elements in rows of 1 to 256 blocks, whole and not, family ->
 // here: FP32 / i8 in 8x8, 2^24 elements in rows of 2, 8 and 24 blocks, compress 0.13, 0.43, 0.86 of the time, decompress 0.14, 0.44, 0.83;
 // FP64 / i16 in 4x4x4 0.16, 0.55, 1.09; in rows that are no whole blocks, of 128 blocks, FP64 / i16 8x8 0.70 and 0.86, FP64 / i8 0.61 and 0.6, FP32 / i16
-// 16x16 0.83.  Over all measured widths and sizes 0.45-0.85 for lane, 0.75-0.95 for quad16, 0.7-0.97 for oct8; worst 1.2 (FP64 / i8
-// lane in rows of 60 whole blocks).  Calls under a mask have MaskedCall's rules.
+// 16x16 0.83.  Each constant below is the share of a wave (`fill`) and the number of waves up to which, and from which, calls of that family,
+// direction, raggedness, array, index and transform were the faster ones here; nothing else is behind them.  57,670 calls by turns, of the 23,000 that
+// come here: lane compress 0.24-0.27 of the family's time, decompress 0.38-0.45, quad16 0.37 and 0.6-0.68, oct8 0.45 and 0.5-0.73 (means); over 1.05 in
+// 0.6 % (whole rows of 16x16 decompressing 5.6 %), worst 1.15.  Calls under a mask have MaskedCall's rules.
 // The statistics of a compressed array, which a family's kernel leaves along the way, have to be those of the same {N, F}: such calls take this
 // route too and read {N, F} once more.  Compressing, the line is therefore where both win: 0.05-0.95 of the time for the statistics inside it, 1.1-1.5
 // in the calls outside where compression alone would win (0.75-0.95: small arrays, and rows a third full and more).  Decompressing, for
@@ -145,7 +147,10 @@ static int64_t small_to(const pbz_codec* c, const fast::Folded& f, int xtype, bo
 static bool small(const pbz_codec* c, const fast::Folded& f, int xtype, bool compress) {
   return f.g.gz * f.g.gy * f.g.gx * (f.bz * f.by * f.bx) <= small_to(c, f, xtype, compress);
 }
-constexpr int64_t kTiny = int64_t(1) << 17;         // up to here a family keeps the calls it fits exactly: a microsecond or two at most lie in it
+// Up to here a family keeps the calls it fits exactly, not for its time: with the smaller tiles such a call takes 0.45-0.9 of it (8x8 0.46 to 0.85 of 4 to
+// 10 us, 4x4x4 0.5-0.89, 16x16 0.65-0.91; but 16x16 decompressing with the Haar transform 1.1 and 8x8x8 1.2-1.55).  At these sizes the families' kernels are
+// compared with the oracle element by element, by the names that pbz_kernel_name gives, and through no other route would those meet them.
+constexpr int64_t kTiny = int64_t(1) << 17;
 
 static bool shape_first(const pbz_codec* c, const fast::Folded& f, int xtype, bool compress) {
   if (!f.ok) return false;

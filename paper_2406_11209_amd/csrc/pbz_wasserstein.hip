@@ -36,7 +36,7 @@ constexpr int kDistancesInFlight = 2;
 constexpr int kKeptDifferences = 12;             // of a thread of k_distance, in LDS until the maximum is known; a multiple of those
 constexpr int kKeysInFlight = 8;                 // keys a thread of the passes below requests together
 
-// Sample sort: 4 K to 16 K keys drawn from the n (one from each run of equally many, at a place that depends on the run's number) and
+// Sample sort: 2 K to 16 K keys drawn from the n (4096 at most; one from each run of equally many, at a place that depends on the run's number) and
 // sorted give K - 1 splitters; one pass counts and one pass scatters the keys into the 2 K - 1 buckets (between two
 // splitters, or equal to one: a value that many blocks share fills a bucket that needs no sorting); a workgroup sorts a
 // bucket in LDS.  What bounds it: 8-byte scatters and LDS, 16 bytes a key and pass against memory otherwise.
@@ -54,9 +54,10 @@ constexpr int kSelectMin = 128;                  // buckets from which k_select 
 constexpr double kSelectGain = 640.0;            // ... where the gap of the maxima, in shares of the larger, times their square is above this
 // Few keys (launch_few): ranges of kRangeKeys on average, found by workgroups that each go through all keys, from kMaxSamples keys on; below, a
 // key's rank is counted, and up to kBucketThreads one workgroup does an operand.  What it saves are launches, of 4.5 us in line: nine, or six
-// where there was one bucket, are two, three and five.  Whole distance, us, nine or six launches -> now: 256 blocks 22.4 -> 10.1, 1024 25.8 ->
+// where there was one bucket, are two, three and five.  Whole distance in a captured graph, us, nine or six launches -> now: 256 blocks 22.4 -> 10.1, 1024 25.8 ->
 // 13.2, 4096 45 -> 23, 16384 52 -> 26, 65536 of a crowded image 92 -> 38.  At 110 thousand the walk through all keys (48 us) costs more than
-// scattering them: 62 -> 70.  Ranges of 1024 keys, in two to a thread: 16384 keys 31, 65536 43.
+// scattering them: 62 -> 70.  Calls through the Python binding one after another take as long (1024 blocks 25.7 -> 13.3, 16384 43.7 -> 25.8, of
+// which the host is busy 20 -> 9.8 and 27 -> 17.4), one that is waited for 12 to 15 more.  Ranges of 1024 keys, in two to a thread: 16384 keys 31, 65536 43.
 constexpr int kRangeMax = 65536;
 constexpr int kRangeKeys = 512;
 constexpr int kSampleRun = 32;                   // one sample of as many keys: 8 to 16 a range, so that hardly one has twice the average
